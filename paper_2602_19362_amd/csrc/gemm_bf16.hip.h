@@ -67,14 +67,13 @@ struct TileCfg {
   static constexpr int PITCH_NM = BM * 2 + 16;  // tile stored [n][m]
   static constexpr int PITCH_MN = BN * 2 + 16;  // tile stored [m][n]
   static constexpr int NM_CHUNKS = WN, NM_ROWS = BN / WN;
-  static constexpr int MN_CHUNKS = WM >= 2 ? WM / 2 : 1, MN_ROWS = BM / MN_CHUNKS;
+  static constexpr int MN_CHUNKS = BM >= 128 ? BM / 128 : 1, MN_ROWS = BM / MN_CHUNKS;
   static constexpr int STAGE_NM = NM_ROWS * PITCH_NM;
   static constexpr int STAGE_MN = MN_ROWS * PITCH_MN;
   static constexpr int RED_BYTES = WM * BN * 8;
   static constexpr int LDS_BYTES =
       MAIN_BYTES > STAGE_NM ? (MAIN_BYTES > STAGE_MN ? MAIN_BYTES : STAGE_MN)
                             : (STAGE_NM > STAGE_MN ? STAGE_NM : STAGE_MN);
-  static_assert(BM == kPackRowsA, "the m side of a tile is one packed block tall");
   static_assert(NS == 2, "ring size");
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "block rows must split over waves");
   static_assert(RED_BYTES + RED_BYTES / 2 <= LDS_BYTES, "reduction scratch must fit");
@@ -96,7 +95,15 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_s_barrier();
 }
 
-template <class C>
+// ROWS: both operands are read from row-major matrices as the caller holds them (rows of `ld` elements, all of
+// them contracted) instead of from packed copies.  A k-step of one tile is then one 128-byte piece of every row,
+// `ld` apart; rows past the matrix and columns past `ld` read as zeros because their offsets are out of the buffer's
+// range, so edges still need no padding.  Packing W costs a pass over it, more than the whole contraction of a few
+// hundred tokens (0.48 ms at d = 4096, V = 151936); the loop runs at the same rate from either layout in a single
+// round of workgroups (12288 tokens: 10.68 / 10.67 ms in place / packed at d = 4096, 5.48 / 5.47 at d = 2048), 3 .. 8 %
+// slower in place over several rounds and 12 % slower where row pieces straddle lines (12.11 / 10.79 at d = 4104);
+// rows_pay in oapl_api.hip draws the line.
+template <class C, bool ROWS = false>
 struct Mainloop {
   // 16-byte chunk c of LDS row `row` lives at physical chunk c ^ ((row >> 1) & 7).  The operand
   // fetch of 16 consecutive rows at one logical chunk then touches 16 distinct 16-byte bank groups:
@@ -105,6 +112,8 @@ struct Mainloop {
 
   __amdgpu_buffer_rsrc_t ra, rb;
   int voff;                           // per-lane byte offset of this lane's chunk inside the first 8 rows a wave loads
+  int vlast;                          // ROWS: ... in the last k-block (lanes whose chunk lies past the row's end point out of range)
+  int istep;                          // ROWS: bytes from one load of a wave to the next (8 * NW rows)
   // LDS byte offsets of this lane's operand fragments at k-step 0 of ring slot 0.  K-step ks sits at the
   // same offset with address bits 5..6 flipped by ks (the swizzle is an XOR on the 16-byte chunk index and
   // the k-step is bits 1..2 of that index); deriving it where it is used costs one XOR per operand and
@@ -141,6 +150,26 @@ struct Mainloop {
     return x;
   }
 
+  // ROWS only: the per-lane offsets for rows of `ld` elements (after setup()).
+  __device__ __forceinline__ void rows_init(int ld) {
+    if (!ROWS) return;
+    const int row = wave * 8 + (lane >> 3), c = (lane & 7) ^ swz(row);
+    voff = row * ld * 2 + (c << 4);
+    vlast = ((ld - 1) & ~(C::BK - 1)) + c * 8 < ld ? voff : (int)0x80000000u;
+    istep = 8 * C::NW * ld * 2;
+  }
+  // Operand tile `rt` (BM / BN rows) of a matrix of R rows, row-major or packed as ROWS says.
+  __device__ __forceinline__ void set_a(const bf16_t* p, int64_t rt, int64_t R, int ld, int n_kt) {
+    const int64_t left = R - rt * C::BM;
+    if (ROWS) ra = __builtin_amdgcn_make_buffer_rsrc((void*)(p + rt * C::BM * ld), 0, (int)(left < C::BM ? left : C::BM) * ld * 2, 0x00020000);
+    else set_a(p + rt * n_kt * (C::STAGE_A / 2), n_kt);
+  }
+  __device__ __forceinline__ void set_b(const bf16_t* p, int64_t rt, int64_t R, int ld, int n_kt) {
+    const int64_t left = R - rt * C::BN;
+    if (ROWS) rb = __builtin_amdgcn_make_buffer_rsrc((void*)(p + rt * C::BN * ld), 0, (int)(left < C::BN ? left : C::BN) * ld * 2, 0x00020000);
+    else set_b(p + rt * n_kt * (C::STAGE_B / 2), n_kt);
+  }
+
   // Operand = one row-tile strip of a packed matrix: n_kt consecutive blocks of 32 KiB (A) / 48 KiB (B).
   __device__ __forceinline__ void set_a(const bf16_t* strip, int n_kt) {
     ra = __builtin_amdgcn_make_buffer_rsrc((void*)strip, 0, n_kt * C::STAGE_A, 0x00020000);
@@ -151,17 +180,18 @@ struct Mainloop {
 
   // Starts the direct-to-LDS loads of k-block kt into ring slot STAGE (a literal at the call sites,
   // so the LDS addresses fold to constants once inlined).
-  __device__ __forceinline__ void issue(const int STAGE, lds_char_ptr smem, int kt) {
+  __device__ __forceinline__ void issue(const int STAGE, lds_char_ptr smem, int kt, int nk) {
+    const int v = ROWS && kt + 1 == nk ? vlast : voff;
 #pragma unroll
     for (int i = 0; i < C::NI_A; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          ra, (lds_void_ptr)(smem + STAGE * C::SLOT + (i * C::NW + wave) * 1024), 16, voff,
-          kt * C::STAGE_A + i * C::NW * 1024, 0, 0);
+          ra, (lds_void_ptr)(smem + STAGE * C::SLOT + (i * C::NW + wave) * 1024), 16, v,
+          ROWS ? kt * C::ROW_BYTES + i * istep : kt * C::STAGE_A + i * C::NW * 1024, 0, 0);
 #pragma unroll
     for (int i = 0; i < C::NI_B; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rb, (lds_void_ptr)(smem + STAGE * C::SLOT + C::STAGE_A + (i * C::NW + wave) * 1024), 16, voff,
-          kt * C::STAGE_B + i * C::NW * 1024, 0, 0);
+          rb, (lds_void_ptr)(smem + STAGE * C::SLOT + C::STAGE_A + (i * C::NW + wave) * 1024), 16, v,
+          ROWS ? kt * C::ROW_BYTES + i * istep : kt * C::STAGE_B + i * C::NW * 1024, 0, 0);
   }
 
   __device__ __forceinline__ void compute(const int STAGE, lds_char_ptr smem, f32x16 (&acc)[C::TM][C::TN]) {
@@ -193,13 +223,13 @@ struct Mainloop {
   __device__ __forceinline__ void step(const int S, lds_char_ptr smem, int kt, int nk, f32x16 (&acc)[C::TM][C::TN]) {
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __syncthreads();
-    if (kt + 1 < nk) issue(S ^ 1, smem, kt + 1);
+    if (kt + 1 < nk) issue(S ^ 1, smem, kt + 1, nk);
     compute(S, smem, acc);
   }
 
   // Starts a tile: k-block 0 into slot 0.  Every wave must be past its last LDS read of the
   // previous tile (finish() ends with a barrier).
-  __device__ __forceinline__ void start(lds_char_ptr smem) { issue(0, smem, 0); }
+  __device__ __forceinline__ void start(lds_char_ptr smem, int nk) { issue(0, smem, 0, nk); }
 
   // k-blocks [k0, k1) of a tile with nk k-blocks in all (k0 even, after start() or an earlier steps()).
   // PRELOADED (with k0 = 0): k-block 1 was issued beforehand as well (start(), then issue(1, smem, 1) if the tile
@@ -523,9 +553,9 @@ __device__ __forceinline__ void strip_tile(int L, int MT, int NTl, int& mt, int&
 // splits.  With ENT it also carries u = sum_v 2^(z * log2(e) - m2) * z, from which
 // the policy entropy follows as  lse - u / s  (one more FMA per logit).
 // ---------------------------------------------------------------------------
-template <class C, bool ENT>
+template <class C, bool ENT, bool ROWS>
 __global__ void __launch_bounds__(C::NT)
-k_fwd_lse(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp, int V, int64_t T, int n_kt,
+k_fwd_lse(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int64_t T, int d, int n_kt,
           int n_splits, int patch_tiles, float2* __restrict__ partials, float* __restrict__ upart, Gate gate) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
@@ -539,20 +569,18 @@ k_fwd_lse(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp, int V, i
   // Consecutive logical ids walk `patch_tiles` token tiles first, then the vocabulary splits: the ~32
   // workgroups resident on one XCD are then patch_tiles token tiles x 32 / patch_tiles splits, which
   // walk their splits in step and share each W block patch_tiles ways (each H block is shared by the
-  // splits of its token tile).  patch_tiles = 1 keeps one token tile's H strip to an XCD: every XCD
-  // then streams all of W once per token tile, which is the better trade only while several H strips
-  // would not fit its L2 (chosen on the host from the strip size).
+  // splits of its token tile).
   int split, nt;
   strip_tile(patch_tiles, L, n_splits, n_tiles, split, nt);
   const int MT = (V + C::BM - 1) / C::BM;
   const int mt_begin = (int)((int64_t)split * MT / n_splits);
   const int mt_end = (int)((int64_t)(split + 1) * MT / n_splits);
   const int64_t n0 = (int64_t)nt * C::BN;
-  const int64_t strip_a = (int64_t)n_kt * (C::STAGE_A / 2), strip_b = (int64_t)n_kt * (C::STAGE_B / 2);
 
-  Mainloop<C> ml;
+  Mainloop<C, ROWS> ml;
   ml.setup();
-  ml.set_b(Hp + nt * strip_b, n_kt);
+  ml.rows_init(d);
+  ml.set_b(H, nt, T, d, n_kt);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / C::WN, wn = wave % C::WN;
@@ -564,18 +592,18 @@ k_fwd_lse(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp, int V, i
 
   f32x16 acc[C::TM][C::TN];
   if (mt_begin < mt_end) {
-    ml.set_a(Wp + mt_begin * strip_a, n_kt);
-    ml.start(smem);
-    if (n_kt > 1) ml.issue(1, smem, 1);
+    ml.set_a(W, mt_begin, V, d, n_kt);
+    ml.start(smem, n_kt);
+    if (n_kt > 1) ml.issue(1, smem, 1, n_kt);
   }
   for (int mt = mt_begin; mt < mt_end; ++mt) {
     const int m0 = mt * C::BM;
     zero_acc<C>(acc);
     ml.template finish<true>(smem, n_kt, acc);
     if (mt + 1 < mt_end) {  // the epilogue below works in registers only: overlap it with the next tile's first loads
-      ml.set_a(Wp + (mt + 1) * strip_a, n_kt);
-      ml.start(smem);
-      if (n_kt > 1) ml.issue(1, smem, 1);
+      ml.set_a(W, mt + 1, V, d, n_kt);
+      ml.start(smem, n_kt);
+      if (n_kt > 1) ml.issue(1, smem, 1, n_kt);
     }
 
     if (m0 + C::BM > V) {  // ragged last vocabulary tile: rows >= V do not exist (their logits are 0, not -inf)
@@ -667,9 +695,9 @@ k_fwd_lse(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp, int V, i
 // Ties go to the smaller index.  Output: one (score, index) pair per token and
 // split (index bit-cast into the pair's second float).
 // ---------------------------------------------------------------------------
-template <class C>
+template <class C, bool ROWS>
 __global__ void __launch_bounds__(C::NT)
-k_fwd_sample(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp, int V, int64_t T, int n_kt, int n_splits,
+k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int64_t T, int d, int n_kt, int n_splits,
              float inv_temperature, uint32_t seed_lo, uint32_t seed_hi, float2* __restrict__ partials) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
@@ -684,11 +712,11 @@ k_fwd_sample(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp, int V
   const int mt_begin = (int)((int64_t)split * MT / n_splits);
   const int mt_end = (int)((int64_t)(split + 1) * MT / n_splits);
   const int64_t n0 = (int64_t)nt * C::BN;
-  const int64_t strip_a = (int64_t)n_kt * (C::STAGE_A / 2), strip_b = (int64_t)n_kt * (C::STAGE_B / 2);
 
-  Mainloop<C> ml;
+  Mainloop<C, ROWS> ml;
   ml.setup();
-  ml.set_b(Hp + nt * strip_b, n_kt);
+  ml.rows_init(d);
+  ml.set_b(H, nt, T, d, n_kt);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / C::WN, wn = wave % C::WN;
@@ -701,18 +729,18 @@ k_fwd_sample(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp, int V
 
   f32x16 acc[C::TM][C::TN];
   if (mt_begin < mt_end) {
-    ml.set_a(Wp + mt_begin * strip_a, n_kt);
-    ml.start(smem);
-    if (n_kt > 1) ml.issue(1, smem, 1);
+    ml.set_a(W, mt_begin, V, d, n_kt);
+    ml.start(smem, n_kt);
+    if (n_kt > 1) ml.issue(1, smem, 1, n_kt);
   }
   for (int mt = mt_begin; mt < mt_end; ++mt) {
     const int m0 = mt * C::BM;
     zero_acc<C>(acc);
     ml.template finish<true>(smem, n_kt, acc);
     if (mt + 1 < mt_end) {
-      ml.set_a(Wp + (mt + 1) * strip_a, n_kt);
-      ml.start(smem);
-      if (n_kt > 1) ml.issue(1, smem, 1);
+      ml.set_a(W, mt + 1, V, d, n_kt);
+      ml.start(smem, n_kt);
+      if (n_kt > 1) ml.issue(1, smem, 1, n_kt);
     }
     const int row0 = m0 + wm * C::TM * 32 + 4 * h;
 #pragma unroll
@@ -807,7 +835,7 @@ k_bwd_dz(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp_panel, int
 
   f32x16 acc[C::TM][C::TN];
   zero_acc<C>(acc);
-  ml.start(smem);
+  ml.start(smem, n_kt);
   ml.finish(smem, n_kt, acc);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -917,7 +945,7 @@ k_sweep(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp_panel, int 
 
   f32x16 acc[C::TM][C::TN];
   zero_acc<C>(acc);
-  ml.start(smem);
+  ml.start(smem, n_kt);
   // the epilogue's per-token references are requested two k-blocks before the end, so that their
   // latency hides behind the last multiplications instead of stalling the epilogue
   const int k_early = n_kt > 2 ? (n_kt - 2) & ~1 : 0;
@@ -1024,7 +1052,7 @@ k_bwd_dh(const bf16_t* __restrict__ WTp, int wt_n_kt, const bf16_t* __restrict__
 
   f32x16 acc[C::TM][C::TN];
   zero_acc<C>(acc);
-  ml.start(smem);
+  ml.start(smem, nk);
   ml.finish(smem, nk, acc);
 
   {
@@ -1118,7 +1146,7 @@ k_bwd_dw(const bf16_t* __restrict__ HTp, const bf16_t* __restrict__ GTp, int t_n
 
   f32x16 acc[C::TM][C::TN];
   zero_acc<C>(acc);
-  ml.start(smem);
+  ml.start(smem, nk);
   ml.finish(smem, nk, acc);
 
   if (accumulate) store_dw_tile<C, true>(acc, dW, d, V, m0, n0);

@@ -20,9 +20,25 @@ namespace oapl {
 typedef TileCfg<4, 2, 2, 6, 2> Cfg;
 static_assert(Cfg::BN == kPackRowsB, "n-side operands of the loss path are packed in blocks of one tile");
 // The sampling kernel carries a running (score, index) pair per column through the main loop and
-// draws Philox blocks in its epilogue: it keeps the 256 x 256 tile (128 accumulators per lane),
-// with H packed in 256-row blocks for it.
+// draws Philox blocks in its epilogue: its largest tile is 256 x 256 (128 accumulators per lane),
+// with H packed in 256-row blocks for it where it reads packed operands.
 typedef TileCfg<4, 2, 2, 4, 2> CfgSample;
+
+// Tiles of the scoring and sampling kernels over row-major operands.  A call of few tokens pays for every padded
+// token column and is bound by reading W once; a call of many is bound by operand delivery, which wants the largest
+// tile.  128 x 64 (48 KB of LDS, three workgroups per CU to keep W streaming through each other's barriers) reads W at
+// 6.0 TB/s for up to 64 tokens at d = 4096, where 256 x 64 reaches 5.0 and the 256 x 256 tile on 64 workgroups 1.1;
+// 128 x 128 (two per CU) serves up to 128 tokens in 260 us against 302 us.  From there on a tile is 256 tall, one per CU,
+// and its width follows from the token count (pick_tile).
+typedef TileCfg<4, 1, 1, 2, 2> Cfg64;
+typedef TileCfg<4, 2, 1, 2, 2> Cfg128;
+typedef CfgSample Cfg256;
+typedef TileCfg<4, 2, 2, 5, 2> Cfg320;
+enum FwdTile { kTile64, kTile128, kTile256, kTile320, kTile384 };
+struct TilePick {
+  FwdTile tile = kTile384;
+  int splits = 1;     // vocabulary ranges: one workgroup per (token tile, range), and the number of partials per token
+};
 
 // Most token rows per backward panel (bf16 path): 32 token tiles, the fastest size measured (the dH
 // contraction then has d / 256 x 32 tiles, whole rounds of 256 workgroups for d a multiple of 2048;
@@ -41,8 +57,10 @@ struct Plan {
   int64_t T = 0;
   int d = 0, V = 0, n_seq = 0, n_groups = 0, dtype = 0;
   bool bwd = false;
-  int n_parts = 0;     // soft-max partials per token
-  int n_parts_s = 0;   // (score, index) partials per token of the sampling kernel
+  bool rows = false;   // the scoring and sampling kernels read W and H where they lie
+  bool packed = false; // ... and packed copies are made (for the gradients' kernels, and for scoring where !rows)
+  TilePick fwd;        // tile and vocabulary splits of the scoring kernel (splits = soft-max partials per token)
+  TilePick smp;        // ... of the sampling kernel (splits = (score, index) partials per token)
   int64_t Tp = 0;      // rows of one backward panel
   int n_buf = 1;       // panel buffers of the single sweep (a ring; one if the batch is one panel)
   size_t size_G = 0, size_GT = 0;   // bytes of one panel buffer of each packed copy
@@ -70,6 +88,52 @@ static int64_t panel_cap(int dtype, int64_t max_panel_rows) {
   return max_panel_rows < Cfg::BN ? Cfg::BN : max_panel_rows / Cfg::BN * Cfg::BN;
 }
 
+// Where reading W and H in place beats packing them first.  Packing moves 4 bytes per weight at ~5.3 TB/s (0.48 ms at
+// d = 4096, V = 151936).  It gains the main loop 3 .. 5 % where rows are whole 128-byte lines (20000 tokens at d = 4096:
+// 18.3 ms packed, 19.2 in place; 8 % at d = 5120) and 10 .. 13 % where they are not (d = 4104): it breaks even near
+// 11000 tokens in the one case and 4500 in the other.
+static bool rows_pay(int64_t T, int d) {
+  if (d % kPackK != 0) return T <= 4096;
+  return T <= 8192;
+}
+
+// Vocabulary splits of the streaming kernels for a tile: one workgroup per (token tile, split), one workgroup per CU
+// at a time.  Takes the count with the least time in the last-finishing CU: rounds of workgroups x tiles each walks,
+// plus a twentieth of a tile per walk.  Short walks cost next to nothing (20000 tokens at d = 4096, patches of eight
+// token tiles: 18.3 / 18.5 / 18.6 ms for walks of 3 / 2 / 1 tiles) while the long ones of neighbouring workgroups
+// drift apart and share less in the L2 (19.6 ms for walks of 26), so the count is free to fill the last round.
+template <class C>
+static TilePick pick_splits(FwdTile tile, int64_t T, int V, double tile_cost = 1.0, double* time_out = nullptr) {
+  const int64_t tiles = (T + C::BN - 1) / C::BN;
+  const int MT = (V + C::BM - 1) / C::BM;
+  const int most = tiles <= 64 ? kNumCU : 64;   // bounds the partials: 12 bytes per token and split
+  TilePick best{tile, 1};
+  double best_time = 1e300;
+  for (int c = 1; c <= most && c <= MT; ++c) {
+    const double rounds = (double)((tiles * c + kNumCU - 1) / kNumCU);
+    const double time = rounds * ((MT + c - 1) / c + 0.05) * tile_cost;
+    if (time < best_time - 1e-9) { best_time = time; best.splits = c; }
+  }
+  if (time_out) *time_out = best_time;
+  return best;
+}
+
+// Tile and splits over row-major operands.  Up to 128 tokens the call is bound by reading W and every 128-row
+// vocabulary tile is a workgroup of its own.  Beyond, the time of one 256-row tile at d = 4096 is 105 / 126 / 150 us
+// for 256 / 320 / 384 columns (it scales with d): the wide tile is the cheapest per column, a narrower one pads fewer
+// columns (777 tokens: 919 us in three 320-wide tiles, 1036 in three of 384, 1029 in four of 256).
+static TilePick pick_tile(int64_t T, int V, bool scoring) {
+  const int MT128 = (V + 127) / 128;
+  if (T <= Cfg64::BN) return TilePick{kTile64, MT128};
+  if (T <= Cfg128::BN) return TilePick{kTile128, MT128};
+  double t256, t320, t384;
+  const TilePick p256 = pick_splits<Cfg256>(kTile256, T, V, 105.0, &t256);
+  if (!scoring) return p256;
+  const TilePick p320 = pick_splits<Cfg320>(kTile320, T, V, 126.0, &t320);
+  const TilePick p384 = pick_splits<Cfg>(kTile384, T, V, 150.0, &t384);
+  return t384 <= t320 && t384 <= t256 ? p384 : t320 <= t256 ? p320 : p256;
+}
+
 // `panel_buffers`: how many panels the single sweep keeps before their gradient contractions run
 // (<= 0: two, the least for a batch of several panels; never more than the batch has panels).
 static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, int dtype, bool bwd,
@@ -89,25 +153,10 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
   if (dtype == OAPL_BF16) {
     const int64_t n_tiles = (T + Cfg::BN - 1) / Cfg::BN;
     const int MT = (V + Cfg::BM - 1) / Cfg::BM;
-    // Vocabulary splits of the streaming kernels: one workgroup per (token tile, split), one
-    // workgroup per CU at a time.  Pick the split count that wastes the least of the last round
-    // of workgroups and of the uneven division of vocabulary tiles, with at least ~8 tiles each.
-    auto pick_splits = [&](int64_t tiles) {
-      const int64_t max_splits = MT / 8 > 1 ? (MT / 8 < 64 ? MT / 8 : 64) : 1;
-      int64_t splits = 1;
-      double best = -1.0;
-      for (int64_t c = 1; c <= max_splits && tiles > 0; ++c) {
-        const int64_t wgs = tiles * c;
-        const double rounds = (double)wgs / kNumCU;
-        const double fill = rounds / (double)((wgs + kNumCU - 1) / kNumCU);      // occupancy of the last round
-        const double even = ((double)MT / c) / (double)((MT + c - 1) / c);       // equal work per workgroup
-        const double score = fill * even;
-        if (score > best + 1e-9) { best = score; splits = c; }
-      }
-      return (int)splits;
-    };
-    p.n_parts = pick_splits(n_tiles);
-    p.n_parts_s = pick_splits((T + CfgSample::BN - 1) / CfgSample::BN);
+    p.rows = rows_pay(T, d);
+    p.packed = bwd || !p.rows;
+    p.fwd = p.rows ? pick_tile(T, V, true) : pick_splits<Cfg>(kTile384, T, V);
+    p.smp = p.rows ? pick_tile(T, V, false) : pick_splits<CfgSample>(kTile256, T, V);
     // Panel size: a multiple of the token tile, at most `cap` rows.  One panel if T fits; otherwise
     // the size (between half the cap and the cap) that costs the fewest rounds of kNumCU workgroups in
     // the dH contraction -- its tiles (d / 256 x panel rows / 384, each K = V long) are few and long, so
@@ -139,15 +188,15 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
     p.n_kt_g = MT * (Cfg::BM / kPackK);              // G strips: whole vocabulary tiles
     p.n_kt_t = (int)(p.Tp / kPackK);                 // strips whose k index is the panel token
   } else {
-    p.n_parts = p.n_parts_s = (V + 63) / 64;
+    p.fwd.splits = p.smp.splits = (V + 63) / 64;
     p.Tp = T < cap ? (T > 0 ? T : 1) : cap;
   }
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += (bytes + 255) / 256 * 256; return at; };
   const size_t Tn = (size_t)(T > 0 ? T : 1);
   p.off_status = take(kStatusWords * 4);
-  p.off_partials = take(Tn * (size_t)(p.n_parts > p.n_parts_s ? p.n_parts : p.n_parts_s) * 8);
-  p.off_upart = take(Tn * (size_t)p.n_parts * 4);
+  p.off_partials = take(Tn * (size_t)(p.fwd.splits > p.smp.splits ? p.fwd.splits : p.smp.splits) * 8);
+  p.off_upart = take(Tn * (size_t)p.fwd.splits * 4);
   p.off_zy = take(Tn * 4);
   p.off_lse2 = take(Tn * 4);
   p.off_diff = take(Tn * 8);
@@ -158,7 +207,7 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
   p.off_cseq = take((size_t)(n_seq > 0 ? n_seq : 1) * 4);
   p.off_vstar = take((size_t)n_groups * 16);
   p.off_gw = take((size_t)((n_seq > 0 ? n_seq : 1) + n_groups) * 8);
-  if (dtype == OAPL_BF16) {
+  if (p.packed) {
     p.off_Wp = take((size_t)p.n_rt_v * p.n_kt_d * kPackBlockBytesA);
     {  // packed H: 384-row blocks, or 256-row blocks for the sampling kernel (whichever is larger)
       const size_t a = (size_t)p.n_rt_T * p.n_kt_d * kPackBlockBytesB;
@@ -236,12 +285,23 @@ static bool allow_big_lds(K kernel, int bytes) {
   return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
 }
 
+template <class C, bool ROWS>
+static bool allow_fwd() {
+  return allow_big_lds(k_fwd_lse<C, false, ROWS>, C::LDS_BYTES) && allow_big_lds(k_fwd_lse<C, true, ROWS>, C::LDS_BYTES);
+}
+template <class C, bool ROWS>
+static bool allow_sample() {
+  return allow_big_lds(k_fwd_sample<C, ROWS>, C::LDS_BYTES);
+}
+
 static bool prepare_kernels() {
   static std::once_flag once;
   static bool ok = false;
   std::call_once(once, [] {
-    ok = allow_big_lds(k_fwd_lse<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_fwd_lse<Cfg, true>, Cfg::LDS_BYTES) &&
-         allow_big_lds(k_fwd_sample<CfgSample>, CfgSample::LDS_BYTES) && allow_big_lds(k_bwd_dz<Cfg>, Cfg::LDS_BYTES) &&
+    ok = allow_fwd<Cfg64, true>() && allow_fwd<Cfg128, true>() && allow_fwd<Cfg256, true>() && allow_fwd<Cfg320, true>() &&
+         allow_fwd<Cfg, true>() && allow_fwd<Cfg, false>() && allow_sample<Cfg64, true>() &&
+         allow_sample<Cfg128, true>() && allow_sample<Cfg256, true>() && allow_sample<CfgSample, false>() &&
+         allow_big_lds(k_bwd_dz<Cfg>, Cfg::LDS_BYTES) &&
          allow_big_lds(k_bwd_dh<Cfg>, Cfg::LDS_BYTES) && allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
          allow_big_lds(k_sweep<Cfg>, Cfg::LDS_BYTES);
   });
@@ -252,6 +312,55 @@ static bool prepare_kernels() {
 // finish.  Writes logprob / lse if wanted, and (for the loss) lse in the
 // kernels' exponent domain plus logprob - logq in double.
 constexpr Gate kNoGate{nullptr, 0};
+
+// Slices of the finishing kernels: at least four partials per thread.
+static int finish_slices(int n_parts) {
+  int s = 1;
+  while (s < 64 && s * 8 <= n_parts) s *= 2;
+  return s;
+}
+
+struct FwdArgs {
+  const bf16_t *W, *H;
+  int V;
+  int64_t T;
+  int d, n_kt;
+  TilePick pick;
+};
+
+// One streaming log-sum-exp pass (the plan's tile; upart != nullptr: with the entropy's partial sums).
+template <class C, bool ROWS>
+static void launch_fwd_lse(const FwdArgs& a, float2* partials, float* upart, hipStream_t st, Gate gate) {
+  const int64_t total = (a.T + C::BN - 1) / C::BN * a.pick.splits;
+  const unsigned grid = (unsigned)round_up(total, 8);
+  // token tiles per XCD patch: eight while a token tile's H strip is at most 3 MiB (384 columns: d <= 4096), else four.
+  // 20000 tokens at d = 4096, walks of 3 tiles: 21.4 / 18.9 / 18.3 / 18.6 ms for patches of 1 / 4 / 8 / 16; 30000 at
+  // d = 5120: 40.4 / 35.8 / 37.3 / 37.2; at d <= 2048 four and eight are equal.
+  const int patch_tiles = (size_t)a.n_kt * C::STAGE_B <= ((size_t)3 << 20) ? 8 : 4;
+  if (upart)
+    k_fwd_lse<C, true, ROWS><<<grid, C::NT, C::LDS_BYTES, st>>>(a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits,
+                                                              patch_tiles, partials, upart, gate);
+  else
+    k_fwd_lse<C, false, ROWS><<<grid, C::NT, C::LDS_BYTES, st>>>(a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits,
+                                                               patch_tiles, partials, nullptr, gate);
+}
+static void launch_fwd_lse(const FwdArgs& a, bool rows, float2* partials, float* upart, hipStream_t st, Gate gate) {
+  if (!rows) return launch_fwd_lse<Cfg, false>(a, partials, upart, st, gate);
+  switch (a.pick.tile) {
+    case kTile64: return launch_fwd_lse<Cfg64, true>(a, partials, upart, st, gate);
+    case kTile128: return launch_fwd_lse<Cfg128, true>(a, partials, upart, st, gate);
+    case kTile256: return launch_fwd_lse<Cfg256, true>(a, partials, upart, st, gate);
+    case kTile320: return launch_fwd_lse<Cfg320, true>(a, partials, upart, st, gate);
+    case kTile384: return launch_fwd_lse<Cfg, true>(a, partials, upart, st, gate);
+  }
+}
+
+template <class C, bool ROWS>
+static void launch_sample(const FwdArgs& a, float inv_t, uint64_t seed, float2* partials, hipStream_t st) {
+  const int64_t total = (a.T + C::BN - 1) / C::BN * a.pick.splits;
+  k_fwd_sample<C, ROWS><<<(unsigned)round_up(total, 8), C::NT, C::LDS_BYTES, st>>>(
+      a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, inv_t, (uint32_t)seed, (uint32_t)(seed >> 32), partials);
+}
 
 // Clears the status header, gathers the sampled tokens' logits and (bf16) packs W and H.
 static int prepare_operands(const Plan& p, const void* H, const void* W, const int32_t* tokens, char* ws,
@@ -264,9 +373,10 @@ static int prepare_operands(const Plan& p, const void* H, const void* W, const i
   if (T == 0) return OAPL_OK;
   if (p.dtype == OAPL_BF16) {
     if (!prepare_kernels()) return OAPL_ERR_HIP;
-    k_gather_logit<bf16_t, float><<<grid1d(T, 4), 256, 0, st>>>((const bf16_t*)H, (const bf16_t*)W, tokens, T, p.d,
+    k_gather_logit<bf16_t, float, 8><<<grid1d(T, 4), 256, 0, st>>>((const bf16_t*)H, (const bf16_t*)W, tokens, T, p.d,
                                                                 p.V, zy, status);
     OAPL_LAUNCH_CHECK();
+    if (!p.packed) return OAPL_OK;
     bf16_t* Wp = (bf16_t*)(ws + p.off_Wp);
     bf16_t* Hp = (bf16_t*)(ws + p.off_Hp);
     k_pack_rows<<<dim3(p.n_kt_d, p.n_rt_v), 256, 0, st>>>((const bf16_t*)W, p.V, p.d, p.d, Wp, p.n_kt_d, Cfg::BM);
@@ -275,8 +385,9 @@ static int prepare_operands(const Plan& p, const void* H, const void* W, const i
                                                                     Cfg::BN);
     OAPL_LAUNCH_CHECK();
   } else {
-    k_gather_logit<float, double><<<grid1d(T, 4), 256, 0, st>>>((const float*)H, (const float*)W, tokens, T, p.d, p.V,
-                                                                zy, status);
+    const bool vec = p.d % 4 == 0 && (((uintptr_t)H | (uintptr_t)W) & 15) == 0;
+    (vec ? k_gather_logit<float, double, 4> : k_gather_logit<float, double, 1>)<<<grid1d(T, 4), 256, 0, st>>>(
+        (const float*)H, (const float*)W, tokens, T, p.d, p.V, zy, status);
     OAPL_LAUNCH_CHECK();
   }
   return OAPL_OK;
@@ -296,35 +407,27 @@ static int forward_scores(const Plan& p, const void* H, const void* W, const int
   const int64_t T = p.T;
   if (T == 0) return OAPL_OK;
   const bool timed = gate.flag == nullptr;
+  const int slices = finish_slices(p.fwd.splits);
 
   if (p.dtype == OAPL_BF16) {
-    const bf16_t* Wp = (const bf16_t*)(ws + p.off_Wp);
-    const bf16_t* Hp = (const bf16_t*)(ws + p.off_Hp);
-    const int64_t n_tiles = (T + Cfg::BN - 1) / Cfg::BN;
-    const int64_t total = n_tiles * p.n_parts;
-    // token tiles per XCD patch: four while a token tile's packed H strip is at most 2 MiB (d <= 2730:
-    // +4 % measured at d = 2048), one beyond that (four strips of 3 MiB thrash the 4 MiB L2: -5 % at d = 4096)
-    const int patch_tiles = (size_t)p.n_kt_d * kPackBlockBytesB <= ((size_t)2 << 20) ? 4 : 1;
+    const FwdArgs args{p.rows ? (const bf16_t*)W : (const bf16_t*)(ws + p.off_Wp),
+                       p.rows ? (const bf16_t*)H : (const bf16_t*)(ws + p.off_Hp), p.V, T, p.d, p.n_kt_d, p.fwd};
     {
       ScopedKernelTimer tm(kFwdLse, st, timed);
-      if (entropy_out)
-        k_fwd_lse<Cfg, true><<<(unsigned)round_up(total, 8), Cfg::NT, Cfg::LDS_BYTES, st>>>(
-            Wp, Hp, p.V, T, p.n_kt_d, p.n_parts, patch_tiles, partials, upart, gate);
-      else
-        k_fwd_lse<Cfg, false><<<(unsigned)round_up(total, 8), Cfg::NT, Cfg::LDS_BYTES, st>>>(
-            Wp, Hp, p.V, T, p.n_kt_d, p.n_parts, patch_tiles, partials, nullptr, gate);
+      launch_fwd_lse(args, p.rows, partials, upart, st, gate);
     }
     OAPL_LAUNCH_CHECK();
-    k_lse_finish<true><<<grid1d(T, 256), 256, 0, st>>>(partials, p.n_parts, T, zy, logq, logprob_out, lse_out, lse2,
-                                                       diff, omp, inv, upart, entropy_out, gate);
+    k_lse_finish<true><<<grid1d(T, 256 / slices), 256, 0, st>>>(partials, p.fwd.splits, T, zy, logq, logprob_out, lse_out,
+                                                                lse2, diff, omp, inv, upart, entropy_out, slices, gate);
     OAPL_LAUNCH_CHECK();
   } else {
     F32Operand A{(const float*)H, p.d, 1}, B{(const float*)W, p.d, 1};
     dim3 grid(grid1d(p.V, 64), grid1d(T, 64));
     k_gemm_f32<<<grid, 256, 0, st>>>(A, B, T, (int64_t)p.V, (int64_t)p.d, EpiLseF32{partials, T, upart});
     OAPL_LAUNCH_CHECK();
-    k_lse_finish<false><<<grid1d(T, 256), 256, 0, st>>>(partials, p.n_parts, T, zy, logq, logprob_out, lse_out, lse2,
-                                                        diff, omp, inv, upart, entropy_out, kNoGate);
+    k_lse_finish<false><<<grid1d(T, 256 / slices), 256, 0, st>>>(partials, p.fwd.splits, T, zy, logq, logprob_out, lse_out,
+                                                                 lse2, diff, omp, inv, upart, entropy_out, slices,
+                                                                 kNoGate);
     OAPL_LAUNCH_CHECK();
   }
   return OAPL_OK;
@@ -459,8 +562,8 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
                                                               kNoGate);
   OAPL_LAUNCH_CHECK();
   // reference exponents: running maximum over the first vocabulary tile, one workgroup per token tile
-  k_fwd_lse<Cfg, false><<<(unsigned)round_up(n_tiles, 8), Cfg::NT, Cfg::LDS_BYTES, st>>>(
-      Wp, Hp, V < Cfg::BM ? V : Cfg::BM, T, p.n_kt_d, 1, 1, sample, nullptr, fast);
+  launch_fwd_lse(FwdArgs{Wp, Hp, V < Cfg::BM ? V : Cfg::BM, T, d, p.n_kt_d, TilePick{kTile384, 1}}, false, sample, nullptr,
+                 st, fast);
   OAPL_LAUNCH_CHECK();
   k_sweep_ref<<<grid1d(T, 256), 256, 0, st>>>(sample, zy, T, ref2);
   OAPL_LAUNCH_CHECK();
@@ -796,31 +899,35 @@ int32_t oapl_sample_tokens(const void* H, const void* W, int64_t T, int32_t d, i
   if (T == 0) return OAPL_OK;
   float2* partials = (float2*)(ws + p.off_partials);
   const float inv_t = 1.0f / temperature;
-  const uint32_t s_lo = (uint32_t)seed, s_hi = (uint32_t)(seed >> 32);
   if (dtype == OAPL_BF16) {
     if (!prepare_kernels()) return OAPL_ERR_HIP;
-    bf16_t* Wp = (bf16_t*)(ws + p.off_Wp);
-    bf16_t* Hp = (bf16_t*)(ws + p.off_Hp);
-    k_pack_rows<<<dim3(p.n_kt_d, p.n_rt_v), 256, 0, st>>>((const bf16_t*)W, V, d, d, Wp, p.n_kt_d, Cfg::BM);
-    OAPL_LAUNCH_CHECK();
-    const int64_t n_tiles = (T + CfgSample::BN - 1) / CfgSample::BN;
-    k_pack_rows<<<dim3(p.n_kt_d, (unsigned)n_tiles), 256, 0, st>>>((const bf16_t*)H, T, d, d, Hp, p.n_kt_d,
-                                                                   CfgSample::BN);
-    OAPL_LAUNCH_CHECK();
-    const int64_t total = n_tiles * p.n_parts_s;
+    FwdArgs args{(const bf16_t*)W, (const bf16_t*)H, V, T, d, p.n_kt_d, p.smp};
+    if (!p.rows) {
+      bf16_t* Wp = (bf16_t*)(ws + p.off_Wp);
+      bf16_t* Hp = (bf16_t*)(ws + p.off_Hp);
+      k_pack_rows<<<dim3(p.n_kt_d, p.n_rt_v), 256, 0, st>>>(args.W, V, d, d, Wp, p.n_kt_d, CfgSample::BM);
+      OAPL_LAUNCH_CHECK();
+      k_pack_rows<<<dim3(p.n_kt_d, grid1d(T, CfgSample::BN)), 256, 0, st>>>(args.H, T, d, d, Hp, p.n_kt_d, CfgSample::BN);
+      OAPL_LAUNCH_CHECK();
+      args.W = Wp;
+      args.H = Hp;
+    }
     {
       ScopedKernelTimer tm(kFwdSample, st);
-      k_fwd_sample<CfgSample><<<(unsigned)round_up(total, 8), CfgSample::NT, CfgSample::LDS_BYTES, st>>>(
-          Wp, Hp, V, T, p.n_kt_d, p.n_parts_s, inv_t, s_lo, s_hi, partials);
+      if (!p.rows) launch_sample<CfgSample, false>(args, inv_t, seed, partials, st);
+      else if (p.smp.tile == kTile64) launch_sample<Cfg64, true>(args, inv_t, seed, partials, st);
+      else if (p.smp.tile == kTile128) launch_sample<Cfg128, true>(args, inv_t, seed, partials, st);
+      else launch_sample<Cfg256, true>(args, inv_t, seed, partials, st);
     }
     OAPL_LAUNCH_CHECK();
   } else {
     F32Operand A{(const float*)H, d, 1}, B{(const float*)W, d, 1};
     dim3 grid(grid1d(V, 64), grid1d(T, 64));
-    k_gemm_f32<<<grid, 256, 0, st>>>(A, B, T, (int64_t)V, (int64_t)d, EpiSampleF32{partials, T, inv_t, s_lo, s_hi});
+    k_gemm_f32<<<grid, 256, 0, st>>>(A, B, T, (int64_t)V, (int64_t)d, EpiSampleF32{partials, T, inv_t, (uint32_t)seed, (uint32_t)(seed >> 32)});
     OAPL_LAUNCH_CHECK();
   }
-  k_sample_finish<<<grid1d(T, 256), 256, 0, st>>>(partials, p.n_parts_s, T, tokens_out, score_out);
+  const int slices = finish_slices(p.smp.splits);
+  k_sample_finish<<<grid1d(T, 256 / slices), 256, 0, st>>>(partials, p.smp.splits, T, tokens_out, score_out, slices);
   OAPL_LAUNCH_CHECK();
   return OAPL_OK;
 }

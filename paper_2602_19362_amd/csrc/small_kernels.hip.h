@@ -26,11 +26,15 @@ __global__ void k_fill_f64(double* p, int64_t n, double v) {
 // z_{t, y_t} = sum_k H[t][k] * W[y_t][k]: one wavefront per token, the gathered
 // W row is read with the index exactly as given (checked against [0, V)).
 // ACC is double for fp32 inputs and float for bf16 inputs (whose products are
-// exact in fp32).
-template <class T, class ACC>
+// exact in fp32).  VEC elements per load: 16 bytes when rows are 16-byte aligned (bf16 always, fp32 if d is a
+// multiple of 4), else one.  Reads 2 rows per token and is bound by the latency of a wavefront's chain of loads:
+// element by element it took 33 us for 777 tokens at d = 4096 (64 loads in a row per lane) and 82 us for 32768 at
+// d = 2048, by 16-byte loads 8.5 and 42 us.
+template <class T, class ACC, int VEC>
 __global__ void __launch_bounds__(256)
 k_gather_logit(const T* __restrict__ H, const T* __restrict__ W, const int32_t* __restrict__ tokens,
                int64_t Ttok, int d, int V, float* __restrict__ zy, int* __restrict__ err) {
+  typedef T vec_t __attribute__((ext_vector_type(VEC)));
   const int lane = threadIdx.x & 63;
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= Ttok) return;
@@ -42,10 +46,15 @@ k_gather_logit(const T* __restrict__ H, const T* __restrict__ W, const int32_t* 
     }
     return;
   }
-  const T* h = H + t * d;
-  const T* w = W + (int64_t)y * d;
+  const vec_t* h = (const vec_t*)(H + t * d);
+  const vec_t* w = (const vec_t*)(W + (int64_t)y * d);
   ACC acc = 0;
-  for (int k = lane; k < d; k += 64) acc += (ACC)to_f32(h[k]) * (ACC)to_f32(w[k]);
+#pragma unroll 4
+  for (int k = lane; k < d / VEC; k += 64) {
+    const vec_t a = h[k], b = w[k];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc += (ACC)to_f32((T)a[e]) * (ACC)to_f32((T)b[e]);
+  }
   acc = wave_sum(acc);
   if (lane == 0) zy[t] = (float)acc;
 }
@@ -56,26 +65,48 @@ k_gather_logit(const T* __restrict__ H, const T* __restrict__ W, const int32_t* 
 // partial u = sum b^(zeta - m) * z.
 // A partial is (m, s) with s = sum b^(zeta - m): LOG2 = true means zeta =
 // z * log2(e), b = 2 (the MFMA kernel's epilogue); false means zeta = z, b = e.
-// Everything after the fp32 partials is done in double.
+// Everything after the fp32 partials is done in double.  A workgroup serves 256 / slices tokens; the partials of a
+// token are taken by `slices` (a power of two <= 64) threads, interleaved, and combined in slice order, so the few
+// tokens of a small call, which come with hundreds of partials each, are not walked by one thread each (777 tokens
+// with 64 partials: 47 us with one slice, 10 us with sixteen).
 template <bool LOG2>
 __global__ void __launch_bounds__(256)
 k_lse_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, const float* __restrict__ zy,
              const float* __restrict__ logq, float* __restrict__ logprob_out, float* __restrict__ lse_out,
              float* __restrict__ lse2_ws, double* __restrict__ diff_ws, float* __restrict__ omp_ws,
              float* __restrict__ inv_omp_ws, const float* __restrict__ upart, float* __restrict__ entropy_out,
-             Gate gate) {
+             int slices, Gate gate) {
+  __shared__ float part_m[256];
+  __shared__ double part_s[256], part_u[256];
   if (gate_closed(gate)) return;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= Ttok) return;
+  const int rows = 256 / slices, col = threadIdx.x % rows, slice = threadIdx.x / rows;
+  const int64_t t = (int64_t)blockIdx.x * rows + col;
   float M = kNegHuge;
-  for (int p = 0; p < n_parts; ++p) M = fmaxf(M, partials[(int64_t)p * Ttok + t].x);
+  if (t < Ttok) {
+#pragma unroll 4
+    for (int p = slice; p < n_parts; p += slices) M = fmaxf(M, partials[(int64_t)p * Ttok + t].x);
+  }
+  part_m[threadIdx.x] = M;
+  __syncthreads();
+  for (int s = 0; s < slices; ++s) M = fmaxf(M, part_m[s * rows + col]);
   double S = 0.0, U = 0.0;
-  for (int p = 0; p < n_parts; ++p) {
-    const float2 a = partials[(int64_t)p * Ttok + t];
-    const double e = (double)a.x - (double)M;
-    const double f = LOG2 ? exp2(e) : exp(e);
-    S += (double)a.y * f;
-    if (entropy_out) U += (double)upart[(int64_t)p * Ttok + t] * f;
+  if (t < Ttok) {
+#pragma unroll 4
+    for (int p = slice; p < n_parts; p += slices) {
+      const float2 a = partials[(int64_t)p * Ttok + t];
+      const double e = (double)a.x - (double)M;
+      const double f = LOG2 ? exp2(e) : exp(e);
+      S += (double)a.y * f;
+      if (entropy_out) U += (double)upart[(int64_t)p * Ttok + t] * f;
+    }
+  }
+  part_s[threadIdx.x] = S;
+  part_u[threadIdx.x] = U;
+  __syncthreads();
+  if (slice != 0 || t >= Ttok) return;
+  for (int s = 1; s < slices; ++s) {
+    S += part_s[s * rows + col];
+    U += part_u[s * rows + col];
   }
   const double lse = LOG2 ? ((double)M + log2(S)) * kLn2 : (double)M + log(S);
   double lp = (double)zy[t] - lse;   // NaN if the token was out of range
@@ -98,16 +129,28 @@ k_lse_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, con
   }
 }
 
-// Picks, per token, the best (score, index) pair over the vocabulary splits (ties to the smaller index).
+// Picks, per token, the best (score, index) pair over the vocabulary splits (ties to the smaller index); slices as
+// in k_lse_finish.
 __global__ void __launch_bounds__(256)
 k_sample_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, int32_t* __restrict__ tokens_out,
-                float* __restrict__ score_out) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= Ttok) return;
+                float* __restrict__ score_out, int slices) {
+  __shared__ float2 part[256];
+  const int rows = 256 / slices, col = threadIdx.x % rows, slice = threadIdx.x / rows;
+  const int64_t t = (int64_t)blockIdx.x * rows + col;
   float best = -__builtin_inff();
   int arg = 0x7FFFFFFF;
-  for (int p = 0; p < n_parts; ++p) {
-    const float2 a = partials[(int64_t)p * Ttok + t];
+  if (t < Ttok) {
+#pragma unroll 4
+    for (int p = slice; p < n_parts; p += slices) {
+      const float2 a = partials[(int64_t)p * Ttok + t];
+      if (better(a.x, __float_as_int(a.y), best, arg)) { best = a.x; arg = __float_as_int(a.y); }
+    }
+  }
+  part[threadIdx.x] = make_float2(best, __int_as_float(arg));
+  __syncthreads();
+  if (slice != 0 || t >= Ttok) return;
+  for (int s = 1; s < slices; ++s) {
+    const float2 a = part[s * rows + col];
     if (better(a.x, __float_as_int(a.y), best, arg)) { best = a.x; arg = __float_as_int(a.y); }
   }
   tokens_out[t] = arg;
