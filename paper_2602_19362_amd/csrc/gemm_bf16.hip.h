@@ -180,18 +180,20 @@ struct Mainloop {
 
   // Starts the direct-to-LDS loads of k-block kt into ring slot STAGE (a literal at the call sites,
   // so the LDS addresses fold to constants once inlined).
+  // ROWS: the row term goes into the per-lane offset, because only that one is sure to be compared with the buffer's
+  // range: a scalar offset past the range (rows of a matrix shorter than the tile) must not decide what is read.
   __device__ __forceinline__ void issue(const int STAGE, lds_char_ptr smem, int kt, int nk) {
     const int v = ROWS && kt + 1 == nk ? vlast : voff;
 #pragma unroll
     for (int i = 0; i < C::NI_A; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          ra, (lds_void_ptr)(smem + STAGE * C::SLOT + (i * C::NW + wave) * 1024), 16, v,
-          ROWS ? kt * C::ROW_BYTES + i * istep : kt * C::STAGE_A + i * C::NW * 1024, 0, 0);
+          ra, (lds_void_ptr)(smem + STAGE * C::SLOT + (i * C::NW + wave) * 1024), 16, ROWS ? v + i * istep : v,
+          ROWS ? kt * C::ROW_BYTES : kt * C::STAGE_A + i * C::NW * 1024, 0, 0);
 #pragma unroll
     for (int i = 0; i < C::NI_B; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rb, (lds_void_ptr)(smem + STAGE * C::SLOT + C::STAGE_A + (i * C::NW + wave) * 1024), 16, v,
-          ROWS ? kt * C::ROW_BYTES + i * istep : kt * C::STAGE_B + i * C::NW * 1024, 0, 0);
+          rb, (lds_void_ptr)(smem + STAGE * C::SLOT + C::STAGE_A + (i * C::NW + wave) * 1024), 16, ROWS ? v + i * istep : v,
+          ROWS ? kt * C::ROW_BYTES : kt * C::STAGE_B + i * C::NW * 1024, 0, 0);
   }
 
   __device__ __forceinline__ void compute(const int STAGE, lds_char_ptr smem, f32x16 (&acc)[C::TM][C::TN]) {
