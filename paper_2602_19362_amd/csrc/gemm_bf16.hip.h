@@ -1022,16 +1022,59 @@ k_sweep(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp_panel, int 
 #endif
 }
 
+// fp32 tile -> out[n][m] (n < n_rows, row pitch d = the m extent), overwritten or added to, straight from the
+// accumulators.
+// A lane owns 4 pieces of 4 consecutive m (16 bytes) of its row n per MFMA block; the four lanes of a
+// quad (four neighbouring rows) trade pieces so that lane q holds piece q of each of the four rows:
+// every load and store then covers whole 128-byte lines (8 lanes per line).  The four old values of
+// an MFMA block are requested together, from clamped (always valid) addresses, before the transpose,
+// so the read-add-write waits for memory once per block, not once per piece (eight at once spill).
+template <class C, bool ACCUMULATE>
+__device__ __forceinline__ void store_f32_tile(const f32x16 (&acc)[C::TM][C::TN], float* __restrict__ out, int d, int n_rows,
+                                               int m0, int n0) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = wave / C::WN, wn = wave % C::WN;
+  const int h = lane >> 5, q = lane & 3;
+#pragma unroll
+  for (int j = 0; j < C::TN; ++j) {
+    const int n_q = n0 + wn * C::TN * 32 + j * 32 + (lane & 28);
+#pragma unroll
+    for (int i = 0; i < C::TM; ++i) {
+      f32x4 piece[4], old[4];
+      const int m = m0 + wm * C::TM * 32 + i * 32 + 8 * q + 4 * h;
+      if (ACCUMULATE) {
+        const int mc = m < d ? m : d - 4;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int nc = n_q + r < n_rows ? n_q + r : n_rows - 1;
+          old[r] = *(const f32x4*)(out + (int64_t)nc * d + mc);
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        piece[c] = f32x4{acc[i][j][4 * c + 0], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2], acc[i][j][4 * c + 3]};
+      quad_transpose(piece);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (m < d && n_q + r < n_rows)
+          *(f32x4*)(out + (int64_t)(n_q + r) * d + m) = ACCUMULATE ? piece[r] + old[r] : piece[r];
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Backward, step 2: dH[t][j] = f_t * sum_v G[t][v] * W[v][j]
 //   A = packed W^T (rows = hidden index j, k = vocabulary), B = Gp (rows = tokens), K = V.
+// A panel of few tokens has few tiles (d / 256 x tokens / 384), each a walk over the whole vocabulary: 1003 tokens at
+// d = 4096 kept 48 of 256 CUs busy for 4.1 ms.  SPLIT: `splits` workgroups share a tile's k-blocks, each writing its
+// fp32 partial sum (whole 128-byte lines) for k_dh_reduce; the host chooses the count (dh_splits).
 // ---------------------------------------------------------------------------
-template <class C>
+template <class C, bool SPLIT>
 __global__ void __launch_bounds__(C::NT)
 k_bwd_dh(const bf16_t* __restrict__ WTp, int wt_n_kt, const bf16_t* __restrict__ Gp, int g_n_kt, int d,
          int64_t n_valid, int nk /* k-blocks to contract: ceil(V / 64) */,
          const float* __restrict__ row_factor /* f_t, panel-local */, bf16_t* __restrict__ dH /* panel's first row */,
-         Gate gate) {
+         int splits, float* __restrict__ part /* [splits][n_valid][d] */, Gate gate) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   lds_char_ptr smem = (lds_char_ptr)smem_raw;
@@ -1039,24 +1082,32 @@ k_bwd_dh(const bf16_t* __restrict__ WTp, int wt_n_kt, const bf16_t* __restrict__
 
   const int MT = (d + C::BM - 1) / C::BM;
   const int NTl = (int)((n_valid + C::BN - 1) / C::BN);
-  const int total = MT * NTl;
+  const int total = MT * NTl * (SPLIT ? splits : 1);
   const int L = xcd_logical_id(blockIdx.x, total);
   if (L >= total) return;
+  // neighbouring ids walk the tiles of one split, so the workgroups of an XCD share its operand blocks
+  const int split = SPLIT ? L / (MT * NTl) : 0;
   int mt, nt;
-  strip_tile<4>(L, MT, NTl, mt, nt);
+  strip_tile<4>(L - split * (MT * NTl), MT, NTl, mt, nt);
   const int m0 = mt * C::BM;
   const int64_t n0 = (int64_t)nt * C::BN;
+  const int k0 = SPLIT ? (int)((int64_t)split * nk / splits) : 0;
+  const int k1 = SPLIT ? (int)((int64_t)(split + 1) * nk / splits) : nk;
 
   Mainloop<C> ml;
   ml.setup();
-  ml.set_a(WTp + (int64_t)mt * wt_n_kt * (C::STAGE_A / 2), wt_n_kt);
-  ml.set_b(Gp + (int64_t)nt * g_n_kt * (C::STAGE_B / 2), g_n_kt);
+  ml.set_a(WTp + ((int64_t)mt * wt_n_kt + k0) * (C::STAGE_A / 2), wt_n_kt - k0);
+  ml.set_b(Gp + ((int64_t)nt * g_n_kt + k0) * (C::STAGE_B / 2), g_n_kt - k0);
 
   f32x16 acc[C::TM][C::TN];
   zero_acc<C>(acc);
-  ml.start(smem, nk);
-  ml.finish(smem, nk, acc);
+  ml.start(smem, k1 - k0);
+  ml.finish(smem, k1 - k0, acc);
 
+  if (SPLIT) {
+    store_f32_tile<C, false>(acc, part + (int64_t)split * n_valid * d, d, (int)n_valid, m0, (int)n0);
+    return;
+  }
   {
     const int lane = threadIdx.x & 63, wn = (threadIdx.x >> 6) % C::WN;
 #pragma unroll
@@ -1077,42 +1128,28 @@ k_bwd_dh(const bf16_t* __restrict__ WTp, int wt_n_kt, const bf16_t* __restrict__
 #endif
 }
 
-// fp32 tile -> dW[n][m] (row pitch d), overwritten or added to, straight from the accumulators.
-// A lane owns 4 pieces of 4 consecutive m (16 bytes) of its row n per MFMA block; the four lanes of a
-// quad (four neighbouring rows) trade pieces so that lane q holds piece q of each of the four rows:
-// every load and store then covers whole 128-byte lines (8 lanes per line).  The four old values of
-// an MFMA block are requested together, from clamped (always valid) addresses, before the transpose,
-// so the read-add-write waits for memory once per block, not once per piece (eight at once spill).
-template <class C, bool ACCUMULATE>
-__device__ __forceinline__ void store_dw_tile(const f32x16 (&acc)[C::TM][C::TN], float* __restrict__ dW, int d, int V,
-                                              int m0, int n0) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / C::WN, wn = wave % C::WN;
-  const int h = lane >> 5, q = lane & 3;
-#pragma unroll
-  for (int j = 0; j < C::TN; ++j) {
-    const int n_q = n0 + wn * C::TN * 32 + j * 32 + (lane & 28);
-#pragma unroll
-    for (int i = 0; i < C::TM; ++i) {
-      f32x4 piece[4], old[4];
-      const int m = m0 + wm * C::TM * 32 + i * 32 + 8 * q + 4 * h;
-      if (ACCUMULATE) {
-        const int mc = m < d ? m : d - 4;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int nc = n_q + r < V ? n_q + r : V - 1;
-          old[r] = *(const f32x4*)(dW + (int64_t)nc * d + mc);
-        }
-      }
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        piece[c] = f32x4{acc[i][j][4 * c + 0], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2], acc[i][j][4 * c + 3]};
-      quad_transpose(piece);
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (m < d && n_q + r < V)
-          *(f32x4*)(dW + (int64_t)(n_q + r) * d + m) = ACCUMULATE ? piece[r] + old[r] : piece[r];
+// dH[n][j] = f_n * (sum of the splits' partial sums, in order): 8 consecutive j per thread.  Bound by memory.
+__global__ void __launch_bounds__(256)
+k_dh_reduce(const float* __restrict__ part, int splits, int64_t n_valid, int d, const float* __restrict__ row_factor,
+            bf16_t* __restrict__ dH, Gate gate) {
+  if (gate_closed(gate)) return;
+  const int64_t total = n_valid * (d / 8), stride = n_valid * d;
+  for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
+    const float* p = part + idx * 8;
+    f32x4 lo = *(const f32x4*)p, hi = *(const f32x4*)(p + 4);
+#pragma unroll 4
+    for (int s = 1; s < splits; ++s) {
+      lo += *(const f32x4*)(p + s * stride);
+      hi += *(const f32x4*)(p + s * stride + 4);
     }
+    const float f = row_factor[idx / (d / 8)];
+    bf16x8 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = (bf16_t)(lo[e] * f);
+      v[4 + e] = (bf16_t)(hi[e] * f);
+    }
+    *(bf16x8*)(dH + idx * 8) = v;
   }
 }
 
@@ -1124,7 +1161,7 @@ __device__ __forceinline__ void store_dw_tile(const f32x16 (&acc)[C::TM][C::TN],
 template <class C>
 __global__ void __launch_bounds__(C::NT)
 k_bwd_dw(const bf16_t* __restrict__ HTp, const bf16_t* __restrict__ GTp, int t_n_kt /* strip pitch of both */, int d,
-         int V, int nk /* k-blocks to contract: panel tokens / 64, rounded up to the tile */,
+         int V, int nk /* k-blocks to contract: ceil(panel tokens / 64) */,
          float* __restrict__ dW, int accumulate, Gate gate) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
@@ -1151,8 +1188,8 @@ k_bwd_dw(const bf16_t* __restrict__ HTp, const bf16_t* __restrict__ GTp, int t_n
   ml.start(smem, nk);
   ml.finish(smem, nk, acc);
 
-  if (accumulate) store_dw_tile<C, true>(acc, dW, d, V, m0, n0);
-  else store_dw_tile<C, false>(acc, dW, d, V, m0, n0);
+  if (accumulate) store_f32_tile<C, true>(acc, dW, d, V, m0, n0);
+  else store_f32_tile<C, false>(acc, dW, d, V, m0, n0);
 #endif
 }
 

@@ -302,7 +302,8 @@ static bool prepare_kernels() {
          allow_fwd<Cfg, true>() && allow_fwd<Cfg, false>() && allow_sample<Cfg64, true>() &&
          allow_sample<Cfg128, true>() && allow_sample<Cfg256, true>() && allow_sample<CfgSample, false>() &&
          allow_big_lds(k_bwd_dz<Cfg>, Cfg::LDS_BYTES) &&
-         allow_big_lds(k_bwd_dh<Cfg>, Cfg::LDS_BYTES) && allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
+         allow_big_lds(k_bwd_dh<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_bwd_dh<Cfg, true>, Cfg::LDS_BYTES) &&
+         allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
          allow_big_lds(k_sweep<Cfg>, Cfg::LDS_BYTES);
   });
   return ok;
@@ -433,6 +434,49 @@ static int forward_scores(const Plan& p, const void* H, const void* W, const int
   return OAPL_OK;
 }
 
+// Workgroups per tile of the dH contraction.  Its tiles are few and long (`nk` k-blocks each, one per CU at a time):
+// the count minimises the time of the last-finishing CU in k-blocks, plus ten per workgroup for filling the ring and
+// the epilogue, plus the partial sums' way through memory (8 bytes per element and split).  Whole loss calls at
+// V = 151936, one workgroup per tile / the count chosen: 1003 tokens, d = 4096 7.79 / 4.65 ms (five splits);
+// 6007 tokens, d = 2048 11.23 / 9.72 ms (two); 30011 tokens at d = 5120, whose last panel has 1211, 114.2 / 111.4 ms.
+static int dh_splits(int64_t tiles, int nk, int64_t nv, int d, size_t scratch) {
+  int best = 1;
+  double best_time = (double)((tiles + kNumCU - 1) / kNumCU) * (nk + 10);
+  for (int s = 2; s <= 64 && s * 4 <= nk && (size_t)s * nv * d * 4 <= scratch; ++s) {
+    const double rounds = (double)((tiles * s + kNumCU - 1) / kNumCU);
+    const double time = rounds * ((nk + s - 1) / s + 10) + 5 + 1.2e-6 * (double)s * nv * d;
+    if (time < best_time - 1e-9) { best_time = time; best = s; }
+  }
+  return best;
+}
+
+// One panel's dH.  `last`: no sweep or recompute of this call follows, so the packed W is dead and holds the partial
+// sums of split tiles (other panels of a long batch are sized to fill the chip as they are).
+static int launch_dh(const Plan& p, const bf16_t* WTp, const bf16_t* G, int64_t nv, const float* factor, bf16_t* dH, bool last,
+                     char* ws, hipStream_t st, Gate gate, bool timed) {
+  const int64_t tiles = (int64_t)p.n_rt_d * ((nv + Cfg::BN - 1) / Cfg::BN);
+  const size_t scratch = last ? (size_t)p.n_rt_v * p.n_kt_d * kPackBlockBytesA : 0;
+  const int splits = dh_splits(tiles, p.n_kt_v, nv, p.d, scratch);
+  float* part = (float*)(ws + p.off_Wp);
+  {
+    ScopedKernelTimer tm(kBwdDh, st, timed);
+    const unsigned grid = (unsigned)round_up(tiles * splits, 8);
+    if (splits > 1)
+      k_bwd_dh<Cfg, true><<<grid, Cfg::NT, Cfg::LDS_BYTES, st>>>(WTp, p.n_kt_v, G, p.n_kt_g, p.d, nv, p.n_kt_v, factor,
+                                                                 dH, splits, part, gate);
+    else
+      k_bwd_dh<Cfg, false><<<grid, Cfg::NT, Cfg::LDS_BYTES, st>>>(WTp, p.n_kt_v, G, p.n_kt_g, p.d, nv, p.n_kt_v,
+                                                                  factor, dH, 1, nullptr, gate);
+  }
+  OAPL_LAUNCH_CHECK();
+  if (splits > 1) {
+    const int64_t blocks = grid1d(nv * (p.d / 8), 256);
+    k_dh_reduce<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, st>>>(part, splits, nv, p.d, factor, dH, gate);
+    OAPL_LAUNCH_CHECK();
+  }
+  return OAPL_OK;
+}
+
 // Steps a8-a10, two-pass form: panel by panel, recompute the soft-max tiles into dZ and run
 // the two gradient contractions.  `wt_packed`: W^T has been packed already by this call.
 static int backward_grads(const Plan& p, const void* H, const void* W, const int32_t* tokens, void* dH, float* dW,
@@ -465,8 +509,8 @@ static int backward_grads(const Plan& p, const void* H, const void* W, const int
     const int64_t strip_d = (int64_t)p.n_kt_d * (kPackBlockBytesB / 2);   // one token tile of packed H
     for (int64_t t0 = 0; t0 < T; t0 += p.Tp) {
       const int64_t nv = (T - t0) < p.Tp ? (T - t0) : p.Tp;
-      const int64_t Kt = round_up(nv, Cfg::BN);
-      const int64_t NTl = Kt / Cfg::BN;
+      const int64_t Kt = round_up(nv, kPackK);
+      const int64_t NTl = (nv + Cfg::BN - 1) / Cfg::BN;
       // (diag(f) H)^T of this panel, packed; token columns in [nv, Kt) come out as zeros
       k_pack_transposed<<<dim3((unsigned)(Kt / kPackK), p.n_rt_d), 256, 0, st>>>(
           (const bf16_t*)H + t0 * d, nv, d, d, coef + t0, HTp, p.n_kt_t, gate);
@@ -478,12 +522,7 @@ static int backward_grads(const Plan& p, const void* H, const void* W, const int
             p.n_kt_t, gate);
       }
       OAPL_LAUNCH_CHECK();
-      {
-        ScopedKernelTimer tm(kBwdDh, st, timed);
-        k_bwd_dh<Cfg><<<(unsigned)round_up(MTd * NTl, 8), Cfg::NT, Cfg::LDS_BYTES, st>>>(
-            WTp, p.n_kt_v, G, p.n_kt_g, d, nv, p.n_kt_v, coef + t0, (bf16_t*)dH + t0 * d, gate);
-      }
-      OAPL_LAUNCH_CHECK();
+      if (int rc = launch_dh(p, WTp, G, nv, coef + t0, (bf16_t*)dH + t0 * d, t0 + p.Tp >= T, ws, st, gate, timed)) return rc;
       {
         ScopedKernelTimer tm(kBwdDw, st, timed);
         k_bwd_dw<Cfg><<<(unsigned)round_up((int64_t)MTd * NTv, kNumCU), Cfg::NT, Cfg::LDS_BYTES, st>>>(
@@ -574,21 +613,15 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
   OAPL_LAUNCH_CHECK();
 
   const int64_t n_panels = (T + p.Tp - 1) / p.Tp;
-  auto gradients = [&](int64_t k) -> int {
+  auto gradients = [&](int64_t k, bool swept) -> int {   // swept: every panel's sweep has been issued
     const int64_t t0 = k * p.Tp;
     const int64_t nv = (T - t0) < p.Tp ? (T - t0) : p.Tp;
-    const int64_t Kt = round_up(nv, Cfg::BN);
-    const int64_t NTl = Kt / Cfg::BN;
+    const int64_t Kt = round_up(nv, kPackK);
     if (int rc = objective(fast, nis)) return rc;
     k_pack_transposed<<<dim3((unsigned)(Kt / kPackK), p.n_rt_d), 256, 0, st>>>(
         (const bf16_t*)H + t0 * d, nv, d, d, coef + t0, HTp, p.n_kt_t, fast);
     OAPL_LAUNCH_CHECK();
-    {
-      ScopedKernelTimer tm(kBwdDh, st);
-      k_bwd_dh<Cfg><<<(unsigned)round_up(MTd * NTl, 8), Cfg::NT, Cfg::LDS_BYTES, st>>>(
-          WTp, p.n_kt_v, Gbuf(k), p.n_kt_g, d, nv, p.n_kt_v, coef + t0, (bf16_t*)dH + t0 * d, fast);
-    }
-    OAPL_LAUNCH_CHECK();
+    if (int rc = launch_dh(p, WTp, Gbuf(k), nv, coef + t0, (bf16_t*)dH + t0 * d, swept, ws, st, fast, true)) return rc;
     {
       ScopedKernelTimer tm(kBwdDw, st);
       k_bwd_dw<Cfg><<<(unsigned)round_up((int64_t)MTd * NTv, kNumCU), Cfg::NT, Cfg::LDS_BYTES, st>>>(
@@ -614,10 +647,10 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
         fast);
     OAPL_LAUNCH_CHECK();
     if (k >= p.n_buf - 1 && p.n_buf > 1)
-      if (int rc = gradients(k - (p.n_buf - 1))) return rc;
+      if (int rc = gradients(k - (p.n_buf - 1), k + 1 == n_panels)) return rc;
   }
   for (int64_t k = n_panels - (p.n_buf > 1 ? p.n_buf - 1 : 1); k < n_panels; ++k)
-    if (int rc = gradients(k)) return rc;
+    if (int rc = gradients(k, true)) return rc;
   return OAPL_OK;
 }
 

@@ -1,0 +1,32 @@
+"""The dH contraction with several workgroups per tile: token counts around the 64-token k-blocks of dW and the token
+tile, ragged hidden sizes and vocabularies, from too few k-blocks to split up to tens of splits, one panel and a ragged
+last panel.  Tolerances as in test_gpu_parity.py."""
+import pytest
+import torch
+
+from tests._util import oracle_full
+from tests.test_gpu_parity import _MODE, _check, _custom_batch, _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("two_pass", [False, True])
+@pytest.mark.parametrize("d,V,lens,cap", [
+    (8, 200, [40, 25], 0),             # 4 k-blocks: one split
+    (264, 1001, [64, 0, 1, 62], 0),    # a ragged second m-tile, two k-blocks of tokens with a ragged tail
+    (72, 9000, [383, 1], 0),           # 141 k-blocks for one tile: many splits, exactly one token tile
+    (520, 20011, [300, 85], 0),        # one token past the tile
+    (136, 5003, [500, 470], 384),      # several panels, the ragged last one split
+])
+def test_split_tiles(d, V, lens, cap, two_pass):
+    print(d, V, lens, cap, two_pass, flush=True)
+    _MODE[0] = "two_pass" if two_pass else "single_sweep"
+    try:
+        b = _custom_batch("bf16", d=d, V=V, lens=lens, n_groups=2 if len(lens) % 2 == 0 else 1, seed=d + V, beta=1.0)
+        res = _run(b, max_panel_rows=cap or None)
+        _check(b, res, oracle_full(b), lp_tol=2e-2, rel_tol=1e-3, g_rtol=2e-2, g_atol_frac=6e-3,
+               fallback=cap > 0 and max(lens) > cap)
+        again = _run(b, max_panel_rows=cap or None)
+        assert torch.equal(res.dH, again.dH) and torch.equal(res.dW, again.dW)
+    finally:
+        _MODE[0] = "single_sweep"
