@@ -103,13 +103,14 @@ static bool rows_pay(int64_t T, int d) {
 // token tiles: 18.3 / 18.5 / 18.6 ms for walks of 3 / 2 / 1 tiles) while the long ones of neighbouring workgroups
 // drift apart and share less in the L2 (19.6 ms for walks of 26), so the count is free to fill the last round.
 template <class C>
-static TilePick pick_splits(FwdTile tile, int64_t T, int V, double tile_cost = 1.0, double* time_out = nullptr) {
+static TilePick pick_splits(FwdTile tile, int64_t T, int V, int max_splits, double tile_cost = 1.0,
+                            double* time_out = nullptr) {
   const int64_t tiles = (T + C::BN - 1) / C::BN;
   const int MT = (V + C::BM - 1) / C::BM;
   const int most = tiles <= 64 ? kNumCU : 64;   // bounds the partials: 12 bytes per token and split
   TilePick best{tile, 1};
   double best_time = 1e300;
-  for (int c = 1; c <= most && c <= MT; ++c) {
+  for (int c = 1; c <= most && c <= MT && c <= max_splits; ++c) {
     const double rounds = (double)((tiles * c + kNumCU - 1) / kNumCU);
     const double time = rounds * ((MT + c - 1) / c + 0.05) * tile_cost;
     if (time < best_time - 1e-9) { best_time = time; best.splits = c; }
@@ -122,22 +123,26 @@ static TilePick pick_splits(FwdTile tile, int64_t T, int V, double tile_cost = 1
 // vocabulary tile is a workgroup of its own.  Beyond, the time of one 256-row tile at d = 4096 is 105 / 126 / 150 us
 // for 256 / 320 / 384 columns (it scales with d): the wide tile is the cheapest per column, a narrower one pads fewer
 // columns (777 tokens: 919 us in three 320-wide tiles, 1036 in three of 384, 1029 in four of 256).
-static TilePick pick_tile(int64_t T, int V, bool scoring) {
+static TilePick pick_tile(int64_t T, int V, int max_splits, bool scoring) {
   const int MT128 = (V + 127) / 128;
-  if (T <= Cfg64::BN) return TilePick{kTile64, MT128};
-  if (T <= Cfg128::BN) return TilePick{kTile128, MT128};
+  const int small = MT128 < max_splits ? MT128 : max_splits;
+  if (T <= Cfg64::BN) return TilePick{kTile64, small};
+  if (T <= Cfg128::BN) return TilePick{kTile128, small};
   double t256, t320, t384;
-  const TilePick p256 = pick_splits<Cfg256>(kTile256, T, V, 105.0, &t256);
+  const TilePick p256 = pick_splits<Cfg256>(kTile256, T, V, max_splits, 105.0, &t256);
   if (!scoring) return p256;
-  const TilePick p320 = pick_splits<Cfg320>(kTile320, T, V, 126.0, &t320);
-  const TilePick p384 = pick_splits<Cfg>(kTile384, T, V, 150.0, &t384);
+  const TilePick p320 = pick_splits<Cfg320>(kTile320, T, V, max_splits, 126.0, &t320);
+  const TilePick p384 = pick_splits<Cfg>(kTile384, T, V, max_splits, 150.0, &t384);
   return t384 <= t320 && t384 <= t256 ? p384 : t320 <= t256 ? p320 : p256;
 }
 
 // `panel_buffers`: how many panels the single sweep keeps before their gradient contractions run
 // (<= 0: two, the least for a batch of several panels; never more than the batch has panels).
+// `max_splits`: most vocabulary splits of the streaming kernels; one gives the smallest workspace (see fit_splits).
+constexpr int kAnySplits = 1 << 30;
 static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, int dtype, bool bwd,
-                      int64_t max_panel_rows = 0, int64_t panel_buffers = 0, int64_t exact_panel_rows = 0) {
+                      int64_t max_panel_rows = 0, int64_t panel_buffers = 0, int64_t exact_panel_rows = 0,
+                      int max_splits = kAnySplits) {
   if (T < 0 || d < 1 || V < 1 || n_seq < 0 || n_groups < 1) return false;
   if (dtype != OAPL_F32 && dtype != OAPL_BF16) return false;
   if (dtype == OAPL_BF16 && (d % 8) != 0) return false;
@@ -155,8 +160,8 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
     const int MT = (V + Cfg::BM - 1) / Cfg::BM;
     p.rows = rows_pay(T, d);
     p.packed = bwd || !p.rows;
-    p.fwd = p.rows ? pick_tile(T, V, true) : pick_splits<Cfg>(kTile384, T, V);
-    p.smp = p.rows ? pick_tile(T, V, false) : pick_splits<CfgSample>(kTile256, T, V);
+    p.fwd = p.rows ? pick_tile(T, V, max_splits, true) : pick_splits<Cfg>(kTile384, T, V, max_splits);
+    p.smp = p.rows ? pick_tile(T, V, max_splits, false) : pick_splits<CfgSample>(kTile256, T, V, max_splits);
     // Panel size: a multiple of the token tile, at most `cap` rows.  One panel if T fits; otherwise
     // the size (between half the cap and the cap) that costs the fewest rounds of kNumCU workgroups in
     // the dH contraction -- its tiles (d / 256 x panel rows / 384, each K = V long) are few and long, so
@@ -195,8 +200,9 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
   auto take = [&](size_t bytes) { size_t at = o; o += (bytes + 255) / 256 * 256; return at; };
   const size_t Tn = (size_t)(T > 0 ? T : 1);
   p.off_status = take(kStatusWords * 4);
-  p.off_partials = take(Tn * (size_t)(p.fwd.splits > p.smp.splits ? p.fwd.splits : p.smp.splits) * 8);
-  p.off_upart = take(Tn * (size_t)p.fwd.splits * 4);
+  // (a call with gradients neither samples nor returns entropies)
+  p.off_partials = take(Tn * (size_t)(bwd || p.fwd.splits > p.smp.splits ? p.fwd.splits : p.smp.splits) * 8);
+  p.off_upart = take(bwd ? 0 : Tn * (size_t)p.fwd.splits * 4);
   p.off_zy = take(Tn * 4);
   p.off_lse2 = take(Tn * 4);
   p.off_diff = take(Tn * 8);
@@ -654,8 +660,18 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
   return OAPL_OK;
 }
 
-static int check_workspace(const void* ws, size_t have, size_t need) {
-  if (ws == nullptr || ((uintptr_t)ws & 255) != 0 || have < need) return OAPL_ERR_WORKSPACE;
+// A plan's partial sums (12 bytes per token and vocabulary split) may be most of a small head's workspace.  They only
+// buy speed: a workspace that is too small for them, but holds one partial per token, is served with that.
+static void fit_splits(Plan& p, size_t have) {
+  Plan q;
+  if (p.total > have && p.dtype == OAPL_BF16 &&
+      make_plan(q, p.T, p.d, p.V, p.n_seq, p.n_groups, p.dtype, p.bwd, 0, 0, 0, 1))
+    p = q;
+}
+
+static int fit_forward_plan(Plan& p, const void* ws, size_t have) {
+  fit_splits(p, have);
+  if (ws == nullptr || ((uintptr_t)ws & 255) != 0 || have < p.total) return OAPL_ERR_WORKSPACE;
   return OAPL_OK;
 }
 
@@ -666,14 +682,16 @@ static int check_workspace(const void* ws, size_t have, size_t need) {
 static int fit_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, int dtype, bool bwd, const void* ws,
                     size_t have) {
   if (!make_plan(p, T, d, V, n_seq, n_groups, dtype, bwd)) return OAPL_ERR_SHAPE;
+  if (!bwd) return fit_forward_plan(p, ws, have);
   if (ws == nullptr || ((uintptr_t)ws & 255) != 0) return OAPL_ERR_WORKSPACE;
-  if (!bwd) return p.total <= have ? OAPL_OK : OAPL_ERR_WORKSPACE;
+  const int max_splits = p.total > have ? 1 : kAnySplits;
+  fit_splits(p, have);
   if (p.total > have) {
     const int64_t step = dtype == OAPL_BF16 ? Cfg::BN : 64;
     bool found = false;
     for (int64_t rows = (p.Tp - 1) / step * step; rows >= step && !found; rows -= step) {
       Plan q;
-      if (make_plan(q, T, d, V, n_seq, n_groups, dtype, bwd, rows) && q.total <= have) {
+      if (make_plan(q, T, d, V, n_seq, n_groups, dtype, bwd, rows, 0, 0, max_splits) && q.total <= have) {
         p = q;
         found = true;
       }
@@ -685,7 +703,7 @@ static int fit_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, i
     const int64_t extra = (int64_t)((have - p.total) / per_buffer);
     if (extra > 0) {
       Plan q;
-      if (make_plan(q, T, d, V, n_seq, n_groups, dtype, bwd, p.Tp, p.n_buf + extra, p.Tp) && q.total <= have) p = q;
+      if (make_plan(q, T, d, V, n_seq, n_groups, dtype, bwd, p.Tp, p.n_buf + extra, p.Tp, max_splits) && q.total <= have) p = q;
     }
   }
   return OAPL_OK;
@@ -909,7 +927,7 @@ int32_t oapl_logprob_fwd(const void* H, const void* W, const int32_t* tokens, in
   if (!make_plan(p, T, d, V, 0, 1, dtype, false)) return OAPL_ERR_SHAPE;
   if (!W) return OAPL_ERR_NULL;
   if (T > 0 && (!H || !tokens || !logprob_out)) return OAPL_ERR_NULL;
-  if (int rc = check_workspace(workspace, workspace_bytes, p.total)) return rc;
+  if (int rc = fit_forward_plan(p, workspace, workspace_bytes)) return rc;
   if (int rc = prepare_operands(p, H, W, tokens, (char*)workspace, (hipStream_t)stream)) return rc;
   return forward_scores(p, H, W, tokens, nullptr, logprob_out, lse_out, entropy_out, (char*)workspace, false,
                         (hipStream_t)stream);
@@ -924,7 +942,7 @@ int32_t oapl_sample_tokens(const void* H, const void* W, int64_t T, int32_t d, i
   if (!W) return OAPL_ERR_NULL;
   if (T > 0 && (!H || !tokens_out)) return OAPL_ERR_NULL;
   if (!(temperature > 0.f) || !isfinite(temperature)) return OAPL_ERR_BETA;
-  if (int rc = check_workspace(workspace, workspace_bytes, p.total)) return rc;
+  if (int rc = fit_forward_plan(p, workspace, workspace_bytes)) return rc;
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
   k_fill_i32<<<1, 64, 0, st>>>((int*)(ws + p.off_status), kStatusWords, 0);
