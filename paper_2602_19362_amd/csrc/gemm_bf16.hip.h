@@ -95,6 +95,14 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_s_barrier();
 }
 
+// Transposing LDS read (see ATR below).  Without the `__restrict__` the compiler takes the read for one that may depend
+// on the direct-to-LDS loads in flight (they fill the other ring slot) and waits for all of them first, which undoes
+// the prefetch: 13.1 ms for a 12288-row dH contraction; the main loop waits for the slot it reads by itself.
+__device__ __forceinline__ bf16x4 lds_read_transposed(const __attribute__((address_space(3))) char* __restrict__ p) {
+  typedef __attribute__((address_space(3))) bf16x4* lds_bf16x4_ptr;
+  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)p);
+}
+
 // ROWS: both operands are read from row-major matrices as the caller holds them (rows of `ld` elements, all of
 // them contracted) instead of from packed copies.  A k-step of one tile is then one 128-byte piece of every row,
 // `ld` apart; rows past the matrix and columns past `ld` read as zeros because their offsets are out of the buffer's
@@ -103,7 +111,13 @@ __device__ __forceinline__ void lds_barrier() {
 // round of workgroups (12288 tokens: 10.68 / 10.67 ms in place / packed at d = 4096, 5.48 / 5.47 at d = 2048), 3 .. 8 %
 // slower in place over several rounds and 12 % slower where row pieces straddle lines (12.11 / 10.79 at d = 4104);
 // rows_pay in oapl_api.hip draws the line.
-template <class C, bool ROWS = false>
+//
+// ATR: the m-side operand is read from a row-major matrix whose ROWS are contracted (element (m, k) at p[k * ld + m]):
+// W as the dH contraction needs it, without a transposed copy.  A k-step of one tile is a 512-byte piece of 64 rows;
+// it lies in LDS as [k][m], and the fragments come out of it by the transposing read (ds_read_b64_tr_b16: of the 16
+// lanes of a group, lane 4e + a points at the four m of column group a in row k + e, and lane i receives column i of
+// the four rows), two reads of 8 bytes in place of one of 16.
+template <class C, bool ROWS = false, bool ATR = false>
 struct Mainloop {
   // 16-byte chunk c of LDS row `row` lives at physical chunk c ^ ((row >> 1) & 7).  The operand
   // fetch of 16 consecutive rows at one logical chunk then touches 16 distinct 16-byte bank groups:
@@ -114,6 +128,9 @@ struct Mainloop {
   int voff;                           // per-lane byte offset of this lane's chunk inside the first 8 rows a wave loads
   int vlast;                          // ROWS: ... in the last k-block (lanes whose chunk lies past the row's end point out of range)
   int istep;                          // ROWS: bytes from one load of a wave to the next (8 * NW rows)
+  const char* at_base;                // ATR: the tile's first column in row 0 of the matrix
+  int64_t at_rows;                    // ... rows (k) from there
+  int at_ld2, at_m0, at_voff;         // ... bytes per row, first column, per-lane byte offset in the first 16 rows of a k-block
   // LDS byte offsets of this lane's operand fragments at k-step 0 of ring slot 0.  K-step ks sits at the
   // same offset with address bits 5..6 flipped by ks (the swizzle is an XOR on the 16-byte chunk index and
   // the k-step is bits 1..2 of that index); deriving it where it is used costs one XOR per operand and
@@ -142,6 +159,24 @@ struct Mainloop {
     const int c0 = lane >> 5;
     rdA0 = rowA * C::ROW_BYTES + ((c0 ^ swz(rowA)) << 4);
     rdB0 = C::STAGE_A + rowB * C::ROW_BYTES + ((c0 ^ swz(rowB)) << 4);
+  }
+
+  // ATR only: the m-side operand of column tile mt in a row-major matrix of R rows of `ld` elements (after setup()).
+  // Chunk c (16 bytes, 32 per row) of LDS row k lives at chunk c ^ ((k & 3) << 2): the four rows and the two halves of
+  // 32 lanes' transposing read then lie on 64 different banks.
+  __device__ __forceinline__ void set_a_transposed(const bf16_t* p, int mt, int64_t R, int ld) {
+    static_assert(!ATR || C::BM == 256, "a k-row of the tile is 512 bytes");
+    at_base = (const char*)(p + mt * C::BM);
+    at_rows = R;
+    at_ld2 = ld * 2;
+    at_m0 = mt * C::BM;
+    const int row = wave * 2 + (lane >> 5);       // one wave-wide load covers 2 rows; load i of a wave 2 * NW rows on
+    static_assert((2 * C::NW) % 4 == 0, "swizzle must repeat from one load of a wave to the next");
+    at_voff = row * at_ld2 + (((lane & 31) ^ ((row & 3) << 2)) << 4);
+    const int e = (lane >> 2) & 3, a = lane & 3, g = lane >> 4, wm = wave / C::WN;
+    const int k = 8 * (g >> 1) + e;
+    const int chunk = wm * C::TM * 4 + 2 * (g & 1) + (a >> 1);   // m / 8 of fragment 0
+    rdA0 = k * (C::BM * 2) + ((chunk ^ (e << 2)) << 4) + ((a & 1) << 3);
   }
 
   // The empty asm keeps the compiler from hoisting the per-k-step addresses out of the loop (back into a table).
@@ -184,8 +219,19 @@ struct Mainloop {
   // range: a scalar offset past the range (rows of a matrix shorter than the tile) must not decide what is read.
   __device__ __forceinline__ void issue(const int STAGE, lds_char_ptr smem, int kt, int nk) {
     const int v = ROWS && kt + 1 == nk ? vlast : voff;
+    if (ATR) {
+      // rows past the matrix lie past its end and read as zeros; columns past `ld` are the next row's: they feed
+      // output rows that are not stored
+      const int64_t left = at_rows - (int64_t)kt * C::BK;
+      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(at_base + (int64_t)kt * C::BK * at_ld2), 0, (int)(left < C::BK ? left : C::BK) * at_ld2 - at_m0 * 2, 0x00020000);
 #pragma unroll
-    for (int i = 0; i < C::NI_A; ++i)
+      for (int i = 0; i < C::NI_A; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_ptr)(smem + STAGE * C::SLOT + (i * C::NW + wave) * 1024), 16,
+                                                 at_voff + i * 2 * C::NW * at_ld2, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < (ATR ? 0 : C::NI_A); ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           ra, (lds_void_ptr)(smem + STAGE * C::SLOT + (i * C::NW + wave) * 1024), 16, ROWS ? v + i * istep : v,
           ROWS ? kt * C::ROW_BYTES : kt * C::STAGE_A + i * C::NW * 1024, 0, 0);
@@ -200,9 +246,18 @@ struct Mainloop {
 #pragma unroll
     for (int ks = 0; ks < C::KSTEPS; ++ks) {
       bf16x8 a[C::TM], b[C::TN];
-      const int ra_ks = fresh(rdA0) ^ (ks << 5), rb_ks = fresh(rdB0) ^ (ks << 5);
+      const int ra_ks = ATR ? fresh(rdA0) : fresh(rdA0) ^ (ks << 5), rb_ks = fresh(rdB0) ^ (ks << 5);
+      if (ATR) {
 #pragma unroll
-      for (int i = 0; i < C::TM; ++i)
+        for (int i = 0; i < C::TM; ++i) {
+          static_assert(!ATR || C::TM <= 2, "fragment i flips chunk bit 2");
+          const lds_char_ptr q = smem + (ra_ks ^ (i << 6)) + STAGE * C::SLOT + ks * 16 * (C::BM * 2);
+          const bf16x4 lo = lds_read_transposed(q), hi = lds_read_transposed(q + 4 * (C::BM * 2));
+          a[i] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < (ATR ? 0 : C::TM); ++i)
         a[i] = *(const __attribute__((address_space(3))) bf16x8*)(smem + STAGE * C::SLOT + ra_ks + i * 32 * C::ROW_BYTES);
 #pragma unroll
       for (int j = 0; j < C::TN; ++j)
@@ -807,11 +862,11 @@ k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, 
 //     Gp   rows = tokens,      k = vocabulary   -> B operand of the dH contraction
 //     GTp  rows = vocabulary,  k = tokens       -> B operand of the dW contraction
 // Entries outside the valid ranges are written as zeros (whole tiles are stored).
-//   A = packed W (M = vocabulary), B = packed H, panel's first token tile (N = tokens).
+//   A = W (M = vocabulary), B = H from the panel's first token (N = tokens), packed or in place.
 // ---------------------------------------------------------------------------
-template <class C>
+template <class C, bool ROWS>
 __global__ void __launch_bounds__(C::NT)
-k_bwd_dz(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp_panel, int V, int64_t n_valid, int n_kt,
+k_bwd_dz(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H_panel, int V, int64_t n_valid, int d, int n_kt,
          const int32_t* __restrict__ tokens, const float* __restrict__ lse2, const float* __restrict__ inv_omp,
          bf16_t* __restrict__ Gp, int g_n_kt, bf16_t* __restrict__ GTp, int gt_n_kt, Gate gate) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -828,12 +883,12 @@ k_bwd_dz(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp_panel, int
   strip_tile<4>(L, MT, NTl, mt, nt);
   const int m0 = mt * C::BM;
   const int64_t n0 = (int64_t)nt * C::BN;
-  const int64_t strip_a = (int64_t)n_kt * (C::STAGE_A / 2), strip_b = (int64_t)n_kt * (C::STAGE_B / 2);
 
-  Mainloop<C> ml;
+  Mainloop<C, ROWS> ml;
   ml.setup();
-  ml.set_a(Wp + mt * strip_a, n_kt);
-  ml.set_b(Hp_panel + nt * strip_b, n_kt);
+  ml.rows_init(d);
+  ml.set_a(W, mt, V, d, n_kt);
+  ml.set_b(H_panel, nt, n_valid, d, n_kt);
 
   f32x16 acc[C::TM][C::TN];
   zero_acc<C>(acc);
@@ -913,9 +968,9 @@ k_bwd_dz(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp_panel, int
 // as the row's largest logit stays within ~2^100 of the reference; k_sweep_finish checks that
 // and otherwise sends the whole call down the two-pass path.
 // ---------------------------------------------------------------------------
-template <class C>
+template <class C, bool ROWS>
 __global__ void __launch_bounds__(C::NT)
-k_sweep(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp_panel, int V, int64_t n_valid, int n_kt,
+k_sweep(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H_panel, int V, int64_t n_valid, int d, int n_kt,
         const float* __restrict__ ref2 /* panel-local */, bf16_t* __restrict__ Gp, int g_n_kt,
         bf16_t* __restrict__ GTp, int gt_n_kt, float* __restrict__ spart /* [MT][ld_s], panel-local */,
         int64_t ld_s, Gate gate) {
@@ -933,12 +988,12 @@ k_sweep(const bf16_t* __restrict__ Wp, const bf16_t* __restrict__ Hp_panel, int 
   strip_tile<4>(L, MT, NTl, mt, nt);
   const int m0 = mt * C::BM;
   const int64_t n0 = (int64_t)nt * C::BN;
-  const int64_t strip_a = (int64_t)n_kt * (C::STAGE_A / 2), strip_b = (int64_t)n_kt * (C::STAGE_B / 2);
 
-  Mainloop<C> ml;
+  Mainloop<C, ROWS> ml;
   ml.setup();
-  ml.set_a(Wp + mt * strip_a, n_kt);
-  ml.set_b(Hp_panel + nt * strip_b, n_kt);
+  ml.rows_init(d);
+  ml.set_a(W, mt, V, d, n_kt);
+  ml.set_b(H_panel, nt, n_valid, d, n_kt);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / C::WN, wn = wave % C::WN;
@@ -1064,14 +1119,15 @@ __device__ __forceinline__ void store_f32_tile(const f32x16 (&acc)[C::TM][C::TN]
 
 // ---------------------------------------------------------------------------
 // Backward, step 2: dH[t][j] = f_t * sum_v G[t][v] * W[v][j]
-//   A = packed W^T (rows = hidden index j, k = vocabulary), B = Gp (rows = tokens), K = V.
+//   A = W^T (rows = hidden index j, k = vocabulary), read from W in place (ATR) or from a packed copy; B = Gp (rows =
+//   tokens), K = V.
 // A panel of few tokens has few tiles (d / 256 x tokens / 384), each a walk over the whole vocabulary: 1003 tokens at
 // d = 4096 kept 48 of 256 CUs busy for 4.1 ms.  SPLIT: `splits` workgroups share a tile's k-blocks, each writing its
 // fp32 partial sum (whole 128-byte lines) for k_dh_reduce; the host chooses the count (dh_splits).
 // ---------------------------------------------------------------------------
-template <class C, bool SPLIT>
+template <class C, bool SPLIT, bool ATR>
 __global__ void __launch_bounds__(C::NT)
-k_bwd_dh(const bf16_t* __restrict__ WTp, int wt_n_kt, const bf16_t* __restrict__ Gp, int g_n_kt, int d,
+k_bwd_dh(const bf16_t* __restrict__ W /* or W^T, packed */, int V, int wt_n_kt, const bf16_t* __restrict__ Gp, int g_n_kt, int d,
          int64_t n_valid, int nk /* k-blocks to contract: ceil(V / 64) */,
          const float* __restrict__ row_factor /* f_t, panel-local */, bf16_t* __restrict__ dH /* panel's first row */,
          int splits, float* __restrict__ part /* [splits][n_valid][d] */, Gate gate) {
@@ -1094,9 +1150,10 @@ k_bwd_dh(const bf16_t* __restrict__ WTp, int wt_n_kt, const bf16_t* __restrict__
   const int k0 = SPLIT ? (int)((int64_t)split * nk / splits) : 0;
   const int k1 = SPLIT ? (int)((int64_t)(split + 1) * nk / splits) : nk;
 
-  Mainloop<C> ml;
+  Mainloop<C, false, ATR> ml;
   ml.setup();
-  ml.set_a(WTp + ((int64_t)mt * wt_n_kt + k0) * (C::STAGE_A / 2), wt_n_kt - k0);
+  if (ATR) ml.set_a_transposed(W + (int64_t)k0 * C::BK * d, mt, V - (int64_t)k0 * C::BK, d);
+  else ml.set_a(W + ((int64_t)mt * wt_n_kt + k0) * (C::STAGE_A / 2), wt_n_kt - k0);
   ml.set_b(Gp + ((int64_t)nt * g_n_kt + k0) * (C::STAGE_B / 2), g_n_kt - k0);
 
   f32x16 acc[C::TM][C::TN];

@@ -34,6 +34,8 @@ typedef TileCfg<4, 1, 1, 2, 2> Cfg64;
 typedef TileCfg<4, 2, 1, 2, 2> Cfg128;
 typedef CfgSample Cfg256;
 typedef TileCfg<4, 2, 2, 5, 2> Cfg320;
+// The sweep's reference exponents: the first 256 vocabulary entries of 64 tokens.
+typedef TileCfg<4, 1, 2, 2, 2> CfgRef;
 enum FwdTile { kTile64, kTile128, kTile256, kTile320, kTile384 };
 struct TilePick {
   FwdTile tile = kTile384;
@@ -57,9 +59,9 @@ struct Plan {
   int64_t T = 0;
   int d = 0, V = 0, n_seq = 0, n_groups = 0, dtype = 0;
   bool bwd = false;
-  bool rows = false;   // the scoring and sampling kernels read W and H where they lie
-  bool packed = false; // ... and packed copies are made (for the gradients' kernels, and for scoring where !rows)
+  bool rows = false;   // the kernels read W and H where they lie; else packed copies (and one of W^T) are made
   TilePick fwd;        // tile and vocabulary splits of the scoring kernel (splits = soft-max partials per token)
+  int splits = 1;      // workgroups per tile of the last panel's dH contraction
   TilePick smp;        // ... of the sampling kernel (splits = (score, index) partials per token)
   int64_t Tp = 0;      // rows of one backward panel
   int n_buf = 1;       // panel buffers of the single sweep (a ring; one if the batch is one panel)
@@ -70,7 +72,7 @@ struct Plan {
   int64_t n_rt_T = 0;  // 384-row token tiles of the whole batch
   size_t off_status = 0, off_partials = 0, off_upart = 0, off_zy = 0, off_lse2 = 0, off_diff = 0, off_coef = 0, off_delta = 0,
          off_cseq = 0, off_vstar = 0, off_gw = 0, off_omp = 0, off_inv = 0, off_Wp = 0, off_Hp = 0, off_WTp = 0, off_HTp = 0,
-         off_G = 0, off_GT = 0, off_ref2 = 0, off_spart = 0, total = 0;
+         off_part = 0, off_G = 0, off_GT = 0, off_ref2 = 0, off_spart = 0, total = 0;
   bool sweep = false;  // single-sweep loss path available (bf16 with backward)
 };
 
@@ -91,7 +93,9 @@ static int64_t panel_cap(int dtype, int64_t max_panel_rows) {
 // Where reading W and H in place beats packing them first.  Packing moves 4 bytes per weight at ~5.3 TB/s (0.48 ms at
 // d = 4096, V = 151936).  It gains the main loop 3 .. 5 % where rows are whole 128-byte lines (20000 tokens at d = 4096:
 // 18.3 ms packed, 19.2 in place; 8 % at d = 5120) and 10 .. 13 % where they are not (d = 4104): it breaks even near
-// 11000 tokens in the one case and 4500 in the other.
+// 11000 tokens in the one case and 4500 in the other.  With gradients there are two copies of W to save (W^T: 0.46 ms)
+// and two contractions that run slower in place (dH of 12288 tokens 11.2 ms against 10.6): about the same line.
+// A loss call of 1003 tokens at d = 4096 takes 4.65 ms packed, 3.64 in place.
 static bool rows_pay(int64_t T, int d) {
   if (d % kPackK != 0) return T <= 4096;
   return T <= 8192;
@@ -136,9 +140,26 @@ static TilePick pick_tile(int64_t T, int V, int max_splits, bool scoring) {
   return t384 <= t320 && t384 <= t256 ? p384 : t320 <= t256 ? p320 : p256;
 }
 
+// Workgroups per tile of the dH contraction.  Its tiles are few and long (`nk` k-blocks each, one per CU at a time):
+// the count minimises the time of the last-finishing CU in k-blocks, plus ten per workgroup for filling the ring and
+// the epilogue, plus the partial sums' way through memory (8 bytes per element and split).  Whole loss calls at
+// V = 151936, one workgroup per tile / the count chosen: 1003 tokens, d = 4096 7.79 / 4.65 ms (five splits);
+// 6007 tokens, d = 2048 11.23 / 9.72 ms (two); 30011 tokens at d = 5120, whose last panel has 1211, 114.2 / 111.4 ms.
+static int dh_splits(int64_t tiles, int nk, int64_t nv, int d, size_t scratch) {
+  int best = 1;
+  double best_time = (double)((tiles + kNumCU - 1) / kNumCU) * (nk + 10);
+  for (int s = 2; s <= 64 && s * 4 <= nk && (size_t)s * nv * d * 4 <= scratch; ++s) {
+    const double rounds = (double)((tiles * s + kNumCU - 1) / kNumCU);
+    const double time = rounds * ((nk + s - 1) / s + 10) + 5 + 1.2e-6 * (double)s * nv * d;
+    if (time < best_time - 1e-9) { best_time = time; best = s; }
+  }
+  return best;
+}
+
 // `panel_buffers`: how many panels the single sweep keeps before their gradient contractions run
 // (<= 0: two, the least for a batch of several panels; never more than the batch has panels).
-// `max_splits`: most vocabulary splits of the streaming kernels; one gives the smallest workspace (see fit_splits).
+// `max_splits`: most vocabulary splits of the streaming kernels; one gives the smallest workspace (see fit_splits): no
+// space that only buys speed.
 constexpr int kAnySplits = 1 << 30;
 static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, int dtype, bool bwd,
                       int64_t max_panel_rows = 0, int64_t panel_buffers = 0, int64_t exact_panel_rows = 0,
@@ -154,12 +175,12 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
   if (dtype == OAPL_F32 && T > (int64_t)65535 * 64) return false;
   if ((int64_t)n_seq * n_groups > kGroupScanLimit) return false;
   const int64_t cap = panel_cap(dtype, max_panel_rows);
+  p = Plan{};
   p.T = T; p.d = d; p.V = V; p.n_seq = n_seq; p.n_groups = n_groups; p.dtype = dtype; p.bwd = bwd;
   if (dtype == OAPL_BF16) {
     const int64_t n_tiles = (T + Cfg::BN - 1) / Cfg::BN;
     const int MT = (V + Cfg::BM - 1) / Cfg::BM;
     p.rows = rows_pay(T, d);
-    p.packed = bwd || !p.rows;
     p.fwd = p.rows ? pick_tile(T, V, max_splits, true) : pick_splits<Cfg>(kTile384, T, V, max_splits);
     p.smp = p.rows ? pick_tile(T, V, max_splits, false) : pick_splits<CfgSample>(kTile256, T, V, max_splits);
     // Panel size: a multiple of the token tile, at most `cap` rows.  One panel if T fits; otherwise
@@ -213,7 +234,7 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
   p.off_cseq = take((size_t)(n_seq > 0 ? n_seq : 1) * 4);
   p.off_vstar = take((size_t)n_groups * 16);
   p.off_gw = take((size_t)((n_seq > 0 ? n_seq : 1) + n_groups) * 8);
-  if (p.packed) {
+  if (dtype == OAPL_BF16 && !p.rows) {
     p.off_Wp = take((size_t)p.n_rt_v * p.n_kt_d * kPackBlockBytesA);
     {  // packed H: 384-row blocks, or 256-row blocks for the sampling kernel (whichever is larger)
       const size_t a = (size_t)p.n_rt_T * p.n_kt_d * kPackBlockBytesB;
@@ -224,7 +245,13 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
   }
   if (bwd) {
     if (dtype == OAPL_BF16) {
-      p.off_WTp = take((size_t)p.n_rt_d * p.n_kt_v * kPackBlockBytesA);
+      // the last panel's partial sums of dH: in the packed copy of W, which is dead by then, or in a space of their own
+      const int64_t last = T > 0 ? T - (T - 1) / p.Tp * p.Tp : 0;
+      const int64_t tiles = (int64_t)p.n_rt_d * ((last + Cfg::BN - 1) / Cfg::BN);
+      if (!p.rows || max_splits > 1)
+        p.splits = dh_splits(tiles, p.n_kt_v, last, d, (size_t)p.n_rt_v * p.n_kt_d * kPackBlockBytesA);
+      p.off_part = p.rows && p.splits > 1 ? take((size_t)p.splits * last * d * 4) : p.off_Wp;
+      if (!p.rows) p.off_WTp = take((size_t)p.n_rt_d * p.n_kt_v * kPackBlockBytesA);
       p.off_HTp = take((size_t)p.n_rt_d * p.n_kt_t * kPackBlockBytesA);
       // Panel buffers, both packed copies.  The single sweep keeps a ring of them: a panel's gradient
       // contractions run once every rollout that touches it is scored, i.e. n_buf - 1 panels later, so
@@ -300,6 +327,11 @@ static bool allow_sample() {
   return allow_big_lds(k_fwd_sample<C, ROWS>, C::LDS_BYTES);
 }
 
+template <bool SPLIT, bool ATR>
+static bool allow_dh() {
+  return allow_big_lds(k_bwd_dh<Cfg, SPLIT, ATR>, Cfg::LDS_BYTES);
+}
+
 static bool prepare_kernels() {
   static std::once_flag once;
   static bool ok = false;
@@ -307,10 +339,12 @@ static bool prepare_kernels() {
     ok = allow_fwd<Cfg64, true>() && allow_fwd<Cfg128, true>() && allow_fwd<Cfg256, true>() && allow_fwd<Cfg320, true>() &&
          allow_fwd<Cfg, true>() && allow_fwd<Cfg, false>() && allow_sample<Cfg64, true>() &&
          allow_sample<Cfg128, true>() && allow_sample<Cfg256, true>() && allow_sample<CfgSample, false>() &&
-         allow_big_lds(k_bwd_dz<Cfg>, Cfg::LDS_BYTES) &&
-         allow_big_lds(k_bwd_dh<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_bwd_dh<Cfg, true>, Cfg::LDS_BYTES) &&
-         allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
-         allow_big_lds(k_sweep<Cfg>, Cfg::LDS_BYTES);
+         allow_big_lds(k_bwd_dz<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_bwd_dz<Cfg, true>, Cfg::LDS_BYTES) &&
+        
+         allow_dh<false, false>() && allow_dh<false, true>() && allow_dh<true, false>() && allow_dh<true, true>() &&
+                 allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
+         allow_big_lds(k_sweep<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_sweep<Cfg, true>, Cfg::LDS_BYTES) &&
+         allow_big_lds(k_fwd_lse<CfgRef, false, true>, CfgRef::LDS_BYTES);
   });
   return ok;
 }
@@ -383,7 +417,7 @@ static int prepare_operands(const Plan& p, const void* H, const void* W, const i
     k_gather_logit<bf16_t, float, 8><<<grid1d(T, 4), 256, 0, st>>>((const bf16_t*)H, (const bf16_t*)W, tokens, T, p.d,
                                                                 p.V, zy, status);
     OAPL_LAUNCH_CHECK();
-    if (!p.packed) return OAPL_OK;
+    if (p.rows) return OAPL_OK;
     bf16_t* Wp = (bf16_t*)(ws + p.off_Wp);
     bf16_t* Hp = (bf16_t*)(ws + p.off_Hp);
     k_pack_rows<<<dim3(p.n_kt_d, p.n_rt_v), 256, 0, st>>>((const bf16_t*)W, p.V, p.d, p.d, Wp, p.n_kt_d, Cfg::BM);
@@ -398,6 +432,17 @@ static int prepare_operands(const Plan& p, const void* H, const void* W, const i
     OAPL_LAUNCH_CHECK();
   }
   return OAPL_OK;
+}
+
+// The operands of the contractions over d, in place or packed by prepare_operands: token row t of H starts at H + t * ld
+// (packed: at a multiple of the token tile).
+struct ContractD {
+  const bf16_t *W, *H;
+  int64_t ld;
+};
+static ContractD contract_d(const Plan& p, const void* H, const void* W, const char* ws) {
+  if (p.rows) return ContractD{(const bf16_t*)W, (const bf16_t*)H, p.d};
+  return ContractD{(const bf16_t*)(ws + p.off_Wp), (const bf16_t*)(ws + p.off_Hp), (int64_t)p.n_kt_d * kPackK};
 }
 
 // (after prepare_operands)
@@ -417,8 +462,8 @@ static int forward_scores(const Plan& p, const void* H, const void* W, const int
   const int slices = finish_slices(p.fwd.splits);
 
   if (p.dtype == OAPL_BF16) {
-    const FwdArgs args{p.rows ? (const bf16_t*)W : (const bf16_t*)(ws + p.off_Wp),
-                       p.rows ? (const bf16_t*)H : (const bf16_t*)(ws + p.off_Hp), p.V, T, p.d, p.n_kt_d, p.fwd};
+    const ContractD x = contract_d(p, H, W, ws);
+    const FwdArgs args{x.W, x.H, p.V, T, p.d, p.n_kt_d, p.fwd};
     {
       ScopedKernelTimer tm(kFwdLse, st, timed);
       launch_fwd_lse(args, p.rows, partials, upart, st, gate);
@@ -440,44 +485,33 @@ static int forward_scores(const Plan& p, const void* H, const void* W, const int
   return OAPL_OK;
 }
 
-// Workgroups per tile of the dH contraction.  Its tiles are few and long (`nk` k-blocks each, one per CU at a time):
-// the count minimises the time of the last-finishing CU in k-blocks, plus ten per workgroup for filling the ring and
-// the epilogue, plus the partial sums' way through memory (8 bytes per element and split).  Whole loss calls at
-// V = 151936, one workgroup per tile / the count chosen: 1003 tokens, d = 4096 7.79 / 4.65 ms (five splits);
-// 6007 tokens, d = 2048 11.23 / 9.72 ms (two); 30011 tokens at d = 5120, whose last panel has 1211, 114.2 / 111.4 ms.
-static int dh_splits(int64_t tiles, int nk, int64_t nv, int d, size_t scratch) {
-  int best = 1;
-  double best_time = (double)((tiles + kNumCU - 1) / kNumCU) * (nk + 10);
-  for (int s = 2; s <= 64 && s * 4 <= nk && (size_t)s * nv * d * 4 <= scratch; ++s) {
-    const double rounds = (double)((tiles * s + kNumCU - 1) / kNumCU);
-    const double time = rounds * ((nk + s - 1) / s + 10) + 5 + 1.2e-6 * (double)s * nv * d;
-    if (time < best_time - 1e-9) { best_time = time; best = s; }
-  }
-  return best;
+template <bool SPLIT, bool ATR>
+static void launch_dh(const Plan& p, const bf16_t* W, const bf16_t* G, int64_t nv, const float* factor, bf16_t* dH, float* part,
+                      hipStream_t st, Gate gate) {
+  const int splits = SPLIT ? p.splits : 1;
+  const int64_t tiles = (int64_t)p.n_rt_d * ((nv + Cfg::BN - 1) / Cfg::BN);
+  k_bwd_dh<Cfg, SPLIT, ATR><<<(unsigned)round_up(tiles * splits, 8), Cfg::NT, Cfg::LDS_BYTES, st>>>(
+      W, p.V, p.n_kt_v, G, p.n_kt_g, p.d, nv, p.n_kt_v, factor, dH, splits, part, gate);
 }
 
-// One panel's dH.  `last`: no sweep or recompute of this call follows, so the packed W is dead and holds the partial
-// sums of split tiles (other panels of a long batch are sized to fill the chip as they are).
-static int launch_dh(const Plan& p, const bf16_t* WTp, const bf16_t* G, int64_t nv, const float* factor, bf16_t* dH, bool last,
+// One panel's dH.  `last`: the batch's last panel (so no sweep or recompute of this call follows); only its tiles are
+// split, and only it has a space for partial sums (the other panels of a long batch are sized to fill the chip as they are).
+static int launch_dh(const Plan& p, const bf16_t* W, const bf16_t* G, int64_t nv, const float* factor, bf16_t* dH, bool last,
                      char* ws, hipStream_t st, Gate gate, bool timed) {
-  const int64_t tiles = (int64_t)p.n_rt_d * ((nv + Cfg::BN - 1) / Cfg::BN);
-  const size_t scratch = last ? (size_t)p.n_rt_v * p.n_kt_d * kPackBlockBytesA : 0;
-  const int splits = dh_splits(tiles, p.n_kt_v, nv, p.d, scratch);
-  float* part = (float*)(ws + p.off_Wp);
+  const bool split = last && p.splits > 1;
+  float* part = split ? (float*)(ws + p.off_part) : nullptr;
+  const bf16_t* A = p.rows ? W : (const bf16_t*)(ws + p.off_WTp);
   {
     ScopedKernelTimer tm(kBwdDh, st, timed);
-    const unsigned grid = (unsigned)round_up(tiles * splits, 8);
-    if (splits > 1)
-      k_bwd_dh<Cfg, true><<<grid, Cfg::NT, Cfg::LDS_BYTES, st>>>(WTp, p.n_kt_v, G, p.n_kt_g, p.d, nv, p.n_kt_v, factor,
-                                                                 dH, splits, part, gate);
-    else
-      k_bwd_dh<Cfg, false><<<grid, Cfg::NT, Cfg::LDS_BYTES, st>>>(WTp, p.n_kt_v, G, p.n_kt_g, p.d, nv, p.n_kt_v,
-                                                                  factor, dH, 1, nullptr, gate);
+    if (split && p.rows) launch_dh<true, true>(p, A, G, nv, factor, dH, part, st, gate);
+    else if (split) launch_dh<true, false>(p, A, G, nv, factor, dH, part, st, gate);
+    else if (p.rows) launch_dh<false, true>(p, A, G, nv, factor, dH, part, st, gate);
+    else launch_dh<false, false>(p, A, G, nv, factor, dH, part, st, gate);
   }
   OAPL_LAUNCH_CHECK();
-  if (splits > 1) {
+  if (split) {
     const int64_t blocks = grid1d(nv * (p.d / 8), 256);
-    k_dh_reduce<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, st>>>(part, splits, nv, p.d, factor, dH, gate);
+    k_dh_reduce<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, st>>>(part, p.splits, nv, p.d, factor, dH, gate);
     OAPL_LAUNCH_CHECK();
   }
   return OAPL_OK;
@@ -499,20 +533,17 @@ static int backward_grads(const Plan& p, const void* H, const void* W, const int
     return OAPL_OK;
   }
   if (p.dtype == OAPL_BF16) {
-    const bf16_t* Wp = (const bf16_t*)(ws + p.off_Wp);   // packed by prepare_operands
-    const bf16_t* Hp = (const bf16_t*)(ws + p.off_Hp);
-    bf16_t* WTp = (bf16_t*)(ws + p.off_WTp);
     bf16_t* HTp = (bf16_t*)(ws + p.off_HTp);
     bf16_t* G = (bf16_t*)(ws + p.off_G);
     bf16_t* GT = (bf16_t*)(ws + p.off_GT);
-    if (!wt_packed) {
-      k_pack_transposed<<<dim3(p.n_kt_v, p.n_rt_d), 256, 0, st>>>((const bf16_t*)W, V, d, d, nullptr, WTp, p.n_kt_v,
-                                                                  gate);
+    if (!wt_packed && !p.rows) {
+      k_pack_transposed<<<dim3(p.n_kt_v, p.n_rt_d), 256, 0, st>>>((const bf16_t*)W, V, d, d, nullptr,
+                                                                  (bf16_t*)(ws + p.off_WTp), p.n_kt_v, gate);
       OAPL_LAUNCH_CHECK();
     }
     const int MTv = p.n_rt_v, MTd = p.n_rt_d;
     const int NTv = (V + Cfg::BN - 1) / Cfg::BN;   // vocabulary tiles on the n side (dW contraction)
-    const int64_t strip_d = (int64_t)p.n_kt_d * (kPackBlockBytesB / 2);   // one token tile of packed H
+    const ContractD x = contract_d(p, H, W, ws);
     for (int64_t t0 = 0; t0 < T; t0 += p.Tp) {
       const int64_t nv = (T - t0) < p.Tp ? (T - t0) : p.Tp;
       const int64_t Kt = round_up(nv, kPackK);
@@ -523,12 +554,12 @@ static int backward_grads(const Plan& p, const void* H, const void* W, const int
       OAPL_LAUNCH_CHECK();
       {
         ScopedKernelTimer tm(kBwdDz, st, timed);
-        k_bwd_dz<Cfg><<<(unsigned)round_up(MTv * NTl, 8), Cfg::NT, Cfg::LDS_BYTES, st>>>(
-            Wp, Hp + (t0 / Cfg::BN) * strip_d, V, nv, p.n_kt_d, tokens + t0, lse2 + t0, inv + t0, G, p.n_kt_g, GT,
-            p.n_kt_t, gate);
+        (p.rows ? k_bwd_dz<Cfg, true> : k_bwd_dz<Cfg, false>)<<<(unsigned)round_up(MTv * NTl, 8), Cfg::NT, Cfg::LDS_BYTES,
+                                                               st>>>(
+            x.W, x.H + t0 * x.ld, V, nv, d, p.n_kt_d, tokens + t0, lse2 + t0, inv + t0, G, p.n_kt_g, GT, p.n_kt_t, gate);
       }
       OAPL_LAUNCH_CHECK();
-      if (int rc = launch_dh(p, WTp, G, nv, coef + t0, (bf16_t*)dH + t0 * d, t0 + p.Tp >= T, ws, st, gate, timed)) return rc;
+      if (int rc = launch_dh(p, (const bf16_t*)W, G, nv, coef + t0, (bf16_t*)dH + t0 * d, t0 + p.Tp >= T, ws, st, gate, timed)) return rc;
       {
         ScopedKernelTimer tm(kBwdDw, st, timed);
         k_bwd_dw<Cfg><<<(unsigned)round_up((int64_t)MTd * NTv, kNumCU), Cfg::NT, Cfg::LDS_BYTES, st>>>(
@@ -581,9 +612,7 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
   const int d = p.d, V = p.V;
   int* flag = (int*)(ws + p.off_status) + kFlagWord;
   const Gate fast{flag, 0};
-  const bf16_t* Wp = (const bf16_t*)(ws + p.off_Wp);
-  const bf16_t* Hp = (const bf16_t*)(ws + p.off_Hp);
-  bf16_t* WTp = (bf16_t*)(ws + p.off_WTp);
+  const ContractD x = contract_d(p, H, W, ws);
   bf16_t* HTp = (bf16_t*)(ws + p.off_HTp);
   auto Gbuf = [&](int64_t k) { return (bf16_t*)(ws + p.off_G + (size_t)(k % p.n_buf) * p.size_G); };
   auto GTbuf = [&](int64_t k) { return (bf16_t*)(ws + p.off_GT + (size_t)(k % p.n_buf) * p.size_GT); };
@@ -596,19 +625,20 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
   const float* coef = (const float*)(ws + p.off_coef);
   const int MTv = p.n_rt_v, MTd = p.n_rt_d;
   const int NTv = (V + Cfg::BN - 1) / Cfg::BN;     // vocabulary tiles on the n side (dW contraction)
-  const int64_t strip_d = (int64_t)p.n_kt_d * (kPackBlockBytesB / 2);   // one token tile of packed H
-  const int64_t n_tiles = (T + Cfg::BN - 1) / Cfg::BN;
 
   // a rollout may span at most n_buf - 1 panels' worth of rows (any length if the batch is one panel)
   k_sweep_plan<<<grid1d(p.n_seq > 0 ? p.n_seq : 1, 256), 256, 0, st>>>(
       seq_offsets, p.n_seq, T, p.n_buf > 1 ? (int64_t)(p.n_buf - 1) * p.Tp : p.Tp, flag);
   OAPL_LAUNCH_CHECK();
-  k_pack_transposed<<<dim3(p.n_kt_v, p.n_rt_d), 256, 0, st>>>((const bf16_t*)W, V, d, d, nullptr, WTp, p.n_kt_v,
-                                                              kNoGate);
-  OAPL_LAUNCH_CHECK();
-  // reference exponents: running maximum over the first vocabulary tile, one workgroup per token tile
-  launch_fwd_lse(FwdArgs{Wp, Hp, V < Cfg::BM ? V : Cfg::BM, T, d, p.n_kt_d, TilePick{kTile384, 1}}, false, sample, nullptr,
-                 st, fast);
+  if (!p.rows) {
+    k_pack_transposed<<<dim3(p.n_kt_v, p.n_rt_d), 256, 0, st>>>((const bf16_t*)W, V, d, d, nullptr,
+                                                                (bf16_t*)(ws + p.off_WTp), p.n_kt_v, kNoGate);
+    OAPL_LAUNCH_CHECK();
+  }
+  // reference exponents: running maximum over the first 256 vocabulary entries, one workgroup per 64 tokens (a walk of
+  // d / 64 k-blocks each, bound by their latency)
+  launch_fwd_lse<CfgRef, true>(FwdArgs{(const bf16_t*)W, (const bf16_t*)H, V < CfgRef::BM ? V : CfgRef::BM, T, d, p.n_kt_d,
+                                       TilePick{}}, sample, nullptr, st, fast);
   OAPL_LAUNCH_CHECK();
   k_sweep_ref<<<grid1d(T, 256), 256, 0, st>>>(sample, zy, T, ref2);
   OAPL_LAUNCH_CHECK();
@@ -619,7 +649,7 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
   OAPL_LAUNCH_CHECK();
 
   const int64_t n_panels = (T + p.Tp - 1) / p.Tp;
-  auto gradients = [&](int64_t k, bool swept) -> int {   // swept: every panel's sweep has been issued
+  auto gradients = [&](int64_t k) -> int {
     const int64_t t0 = k * p.Tp;
     const int64_t nv = (T - t0) < p.Tp ? (T - t0) : p.Tp;
     const int64_t Kt = round_up(nv, kPackK);
@@ -627,7 +657,7 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
     k_pack_transposed<<<dim3((unsigned)(Kt / kPackK), p.n_rt_d), 256, 0, st>>>(
         (const bf16_t*)H + t0 * d, nv, d, d, coef + t0, HTp, p.n_kt_t, fast);
     OAPL_LAUNCH_CHECK();
-    if (int rc = launch_dh(p, WTp, Gbuf(k), nv, coef + t0, (bf16_t*)dH + t0 * d, swept, ws, st, fast, true)) return rc;
+    if (int rc = launch_dh(p, (const bf16_t*)W, Gbuf(k), nv, coef + t0, (bf16_t*)dH + t0 * d, k + 1 == n_panels, ws, st, fast, true)) return rc;
     {
       ScopedKernelTimer tm(kBwdDw, st);
       k_bwd_dw<Cfg><<<(unsigned)round_up((int64_t)MTd * NTv, kNumCU), Cfg::NT, Cfg::LDS_BYTES, st>>>(
@@ -642,8 +672,9 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
     const int64_t NTl = round_up(nv, Cfg::BN) / Cfg::BN;
     {
       ScopedKernelTimer tm(kSweep, st);
-      k_sweep<Cfg><<<(unsigned)round_up(MTv * NTl, 8), Cfg::NT, Cfg::LDS_BYTES, st>>>(
-          Wp, Hp + (t0 / Cfg::BN) * strip_d, V, nv, p.n_kt_d, ref2 + t0, Gbuf(k), p.n_kt_g, GTbuf(k),
+      (p.rows ? k_sweep<Cfg, true> : k_sweep<Cfg, false>)<<<(unsigned)round_up(MTv * NTl, 8), Cfg::NT, Cfg::LDS_BYTES,
+                                                            st>>>(
+          x.W, x.H + t0 * x.ld, V, nv, d, p.n_kt_d, ref2 + t0, Gbuf(k), p.n_kt_g, GTbuf(k),
           p.n_kt_t, spart, p.Tp, fast);
     }
     OAPL_LAUNCH_CHECK();
@@ -653,10 +684,10 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
         fast);
     OAPL_LAUNCH_CHECK();
     if (k >= p.n_buf - 1 && p.n_buf > 1)
-      if (int rc = gradients(k - (p.n_buf - 1), k + 1 == n_panels)) return rc;
+      if (int rc = gradients(k - (p.n_buf - 1))) return rc;
   }
   for (int64_t k = n_panels - (p.n_buf > 1 ? p.n_buf - 1 : 1); k < n_panels; ++k)
-    if (int rc = gradients(k, true)) return rc;
+    if (int rc = gradients(k)) return rc;
   return OAPL_OK;
 }
 
@@ -905,6 +936,9 @@ size_t oapl_workspace_bytes_for(int64_t T, int32_t d, int32_t V, int32_t n_seq, 
   Plan p, full;
   if (!make_plan(p, T, d, V, n_seq, n_groups, dtype, with_backward != 0, max_panel_rows)) return 0;
   if (!make_plan(full, T, d, V, n_seq, n_groups, dtype, with_backward != 0)) return 0;
+  // who asks for less than the library's own panels gets the least that does the work in panels of that size
+  if (p.Tp < full.Tp)
+    make_plan(p, T, d, V, n_seq, n_groups, dtype, with_backward != 0, max_panel_rows, 0, 0, 1);
   // Buffers for the longest rollout, 1 + ceil(len / panel): only at the library's own panel size.  A
   // loss call derives its plan from the byte count alone, and k buffers of a smaller panel could not
   // be told from two buffers of a panel k / 2 times as large (which it prefers: larger panels are faster).

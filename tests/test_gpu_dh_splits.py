@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
     (72, 9000, [383, 1], 0),           # 141 k-blocks for one tile: many splits, exactly one token tile
     (520, 20011, [300, 85], 0),        # one token past the tile
     (136, 5003, [500, 470], 384),      # several panels, the ragged last one split
+    (72, 1001, [4000, 100], 0),        # packed operands: the partial sums lie in the packed copy of W
 ])
 def test_split_tiles(d, V, lens, cap, two_pass):
     print(d, V, lens, cap, two_pass, flush=True)
