@@ -49,11 +49,18 @@ struct TilePick {
 // sweep), never larger panels.
 constexpr int64_t kPanelBf16 = 12288;
 constexpr int64_t kPanelF32 = 4096;    // ... (fp32 path)
+constexpr size_t kPartF32Bytes = (size_t)64 << 20;   // most partial results of an fp32 gradient contraction
 constexpr int64_t kGroupScanLimit = (int64_t)1 << 32;   // n_seq * n_groups: every prompt's wavefront walks all rollouts
 constexpr int kStatusWords = 64;       // 256-byte header
 constexpr int kNumCU = 256;            // MI355X compute units (one workgroup of the dense kernels each: it fills the LDS)
 
 static inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
+
+// Tile and splits of k of an fp32 gradient contraction.
+struct F32Pick {
+  bool large = false;
+  int splits = 1;
+};
 
 struct Plan {
   int64_t T = 0;
@@ -64,6 +71,8 @@ struct Plan {
   int splits = 1;      // workgroups per tile of the last panel's dH contraction
   TilePick smp;        // ... of the sampling kernel (splits = (score, index) partials per token)
   int64_t Tp = 0;      // rows of one backward panel
+  F32Pick f32_dh, f32_dw;   // tile and splits of the fp32 gradient contractions (of the largest panel)
+  int64_t ldz = 0;     // fp32: row pitch of the transposed logits / dZ panel [V][ldz]
   int n_buf = 1;       // panel buffers of the single sweep (a ring; one if the batch is one panel)
   size_t size_G = 0, size_GT = 0;   // bytes of one panel buffer of each packed copy
   // packed-operand geometry (bf16 path): row tiles and k-blocks (strip pitches)
@@ -156,9 +165,29 @@ static int dh_splits(int64_t tiles, int nk, int64_t nv, int d, size_t scratch) {
   return best;
 }
 
+// Tile and splits of an M x N x K fp32 contraction: the least time of the last-finishing CU in clocks.  A tile of 128 x
+// 128 takes 128 clocks per k at the matrix cores' rate, one of 64 x 64 32 (40 with the latency a single workgroup per CU
+// shows), a workgroup 2000 to start and store; partial results cost 8 bytes per element and split at 1700 bytes per
+// clock, and a launch (5000).  `scratch` bounds the partial results.
+static F32Pick pick_f32(int64_t M, int64_t N, int64_t K, int max_splits, size_t scratch) {
+  F32Pick best;
+  double best_time = 1e300;
+  for (int large = 0; large < 2; ++large) {
+    const int64_t tile = large ? F32Large::BM : F32Small::BM, bk = large ? F32Large::BK : F32Small::BK;
+    const int64_t tiles = ((M + tile - 1) / tile) * ((N + tile - 1) / tile);
+    for (int s = 1; s <= 64 && s <= max_splits && (s == 1 || (s * 2 * bk <= K && (size_t)(s * M * N) * 4 <= scratch)); ++s) {
+      const double rounds = (double)((tiles * s + kNumCU - 1) / kNumCU);
+      const double time = rounds * ((double)((K + s - 1) / s) * (large ? 128.0 : 40.0) + 2000.0) +
+                          (s > 1 ? 5000.0 + (double)s * M * N * 8.0 / 1700.0 : 0.0);
+      if (time < best_time - 1e-9) { best_time = time; best.large = large != 0; best.splits = s; }
+    }
+  }
+  return best;
+}
+
 // `panel_buffers`: how many panels the single sweep keeps before their gradient contractions run
 // (<= 0: two, the least for a batch of several panels; never more than the batch has panels).
-// `max_splits`: most vocabulary splits of the streaming kernels; one gives the smallest workspace (see fit_splits): no
+// `max_splits`: most vocabulary splits of the streaming kernels (fp32: splits of the gradient contractions); one gives the smallest workspace (see fit_splits): no
 // space that only buys speed.
 constexpr int kAnySplits = 1 << 30;
 static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, int dtype, bool bwd,
@@ -267,7 +296,13 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
       p.off_ref2 = take(Tn * 4);
       p.off_spart = take((size_t)p.n_rt_v * (size_t)p.Tp * 4);
     } else {
-      p.off_G = take((size_t)p.Tp * V * 4);
+      p.ldz = max_splits > 1 ? round_up(p.Tp, 4) : p.Tp;    // a multiple of 4 floats lets the contractions load 16 bytes
+      p.off_G = take((size_t)p.ldz * V * 4);
+      p.f32_dh = pick_f32(p.Tp, d, V, max_splits, kPartF32Bytes);
+      p.f32_dw = pick_f32(V, d, p.Tp, max_splits, kPartF32Bytes);
+      const size_t dh = p.f32_dh.splits > 1 ? (size_t)p.f32_dh.splits * p.Tp * d * 4 : 0;
+      const size_t dw = p.f32_dw.splits > 1 ? (size_t)p.f32_dw.splits * V * d * 4 : 0;
+      p.off_part = take(dh > dw ? dh : dw);
     }
   }
   p.total = o;
@@ -403,6 +438,48 @@ static void launch_sample(const FwdArgs& a, float inv_t, uint64_t seed, float2* 
       a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, inv_t, (uint32_t)seed, (uint32_t)(seed >> 32), partials);
 }
 
+static F32Operand f32_operand(const void* p, int64_t ld) {
+  return F32Operand{(const float*)p, ld, ld % 4 == 0 && ((uintptr_t)p & 15) == 0};
+}
+
+// Logits of T token rows (transposed: M = vocabulary), in whatever form the epilogue leaves them.  128 x 128 tiles where
+// they give every CU one, else 64 x 128.
+template <class Epi>
+static void launch_logits_f32(const Plan& p, const void* H, const void* W, int64_t T, Epi epi, hipStream_t st) {
+  const F32Operand A = f32_operand(W, p.d), B = f32_operand(H, p.d);
+  const int64_t tiles = (int64_t)grid1d(p.V, F32Large::BM) * grid1d(T, F32Large::BN);
+  if (tiles >= kNumCU)
+    k_gemm_f32<F32Large, true, true><<<dim3(grid1d(p.V, F32Large::BM), grid1d(T, F32Large::BN)), 256, 0, st>>>(
+        A, B, (int64_t)p.V, T, (int64_t)p.d, epi);
+  else
+    k_gemm_f32<F32Flat, true, true><<<dim3(grid1d(p.V, F32Flat::BM), grid1d(T, F32Flat::BN)), 256, 0, st>>>(
+        A, B, (int64_t)p.V, T, (int64_t)p.d, epi);
+}
+
+// out[m][n] (+)= sum_k A(m, k) B(n, k), B and (unless A_KC) A with their rows contiguous.
+template <bool A_KC, class C>
+static void launch_contract_f32(int splits, const F32Operand& A, const F32Operand& B, int64_t M, int64_t N, int64_t K,
+                                float* out, int64_t ld, int accumulate, hipStream_t st) {
+  k_gemm_f32<C, A_KC, false><<<dim3(grid1d(N, C::BN), grid1d(M, C::BM), splits), 256, 0, st>>>(
+      A, B, M, N, K, EpiStoreF32{out, ld, accumulate});
+}
+template <bool A_KC>
+static int contract_f32(const F32Pick& pick, const F32Operand& A, const F32Operand& B, int64_t M, int64_t N, int64_t K, float* out,
+                        float* part, int accumulate, hipStream_t st) {
+  const bool split = pick.splits > 1;
+  float* dst = split ? part : out;
+  const int acc = split ? 0 : accumulate;
+  if (pick.large) launch_contract_f32<A_KC, F32Large>(pick.splits, A, B, M, N, K, dst, N, acc, st);
+  else launch_contract_f32<A_KC, F32Small>(pick.splits, A, B, M, N, K, dst, N, acc, st);
+  OAPL_LAUNCH_CHECK();
+  if (split) {
+    const int64_t blocks = (M * N + 255) / 256;
+    k_reduce_f32<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, st>>>(part, pick.splits, M * N, out, accumulate);
+    OAPL_LAUNCH_CHECK();
+  }
+  return OAPL_OK;
+}
+
 // Clears the status header, gathers the sampled tokens' logits and (bf16) packs W and H.
 static int prepare_operands(const Plan& p, const void* H, const void* W, const int32_t* tokens, char* ws,
                             hipStream_t st) {
@@ -473,9 +550,9 @@ static int forward_scores(const Plan& p, const void* H, const void* W, const int
                                                                 lse2, diff, omp, inv, upart, entropy_out, slices, gate);
     OAPL_LAUNCH_CHECK();
   } else {
-    F32Operand A{(const float*)H, p.d, 1}, B{(const float*)W, p.d, 1};
-    dim3 grid(grid1d(p.V, 64), grid1d(T, 64));
-    k_gemm_f32<<<grid, 256, 0, st>>>(A, B, T, (int64_t)p.V, (int64_t)p.d, EpiLseF32{partials, T, upart});
+    // a batch whose gradient is one panel keeps its logits for it
+    float* zt = keep_for_loss && p.bwd && T <= p.Tp ? (float*)(ws + p.off_G) : nullptr;
+    launch_logits_f32(p, H, W, T, EpiLseF32{partials, T, upart, zt, p.ldz}, st);
     OAPL_LAUNCH_CHECK();
     k_lse_finish<false><<<grid1d(T, 256 / slices), 256, 0, st>>>(partials, p.fwd.splits, T, zy, logq, logprob_out, lse_out,
                                                                  lse2, diff, omp, inv, upart, entropy_out, slices,
@@ -568,29 +645,24 @@ static int backward_grads(const Plan& p, const void* H, const void* W, const int
       OAPL_LAUNCH_CHECK();
     }
   } else {
-    float* dZ = (float*)(ws + p.off_G);
+    float* zt = (float*)(ws + p.off_G);   // dZ^T of a panel
+    float* part = (float*)(ws + p.off_part);
     for (int64_t t0 = 0; t0 < T; t0 += p.Tp) {
       const int64_t nv = (T - t0) < p.Tp ? (T - t0) : p.Tp;
       const float* Hp = (const float*)H + t0 * d;
-      {
-        F32Operand A{Hp, d, 1}, B{(const float*)W, d, 1};
-        dim3 grid(grid1d(V, 64), grid1d(nv, 64));
-        k_gemm_f32<<<grid, 256, 0, st>>>(A, B, nv, (int64_t)V, (int64_t)d,
-                                         EpiDzF32{tokens + t0, lse2 + t0, coef + t0, dZ, (int64_t)V});
-        OAPL_LAUNCH_CHECK();
-      }
-      {  // dH[t][j] = sum_v dZ[t][v] W[v][j]
-        F32Operand A{dZ, V, 1}, B{(const float*)W, 1, d};
-        dim3 grid(grid1d(d, 64), grid1d(nv, 64));
-        k_gemm_f32<<<grid, 256, 0, st>>>(A, B, nv, (int64_t)d, (int64_t)V, EpiStoreF32{(float*)dH + t0 * d, d, 0});
-        OAPL_LAUNCH_CHECK();
-      }
-      {  // dW[v][j] (+)= sum_t dZ[t][v] H[t][j]
-        F32Operand A{dZ, 1, V}, B{Hp, 1, d};
-        dim3 grid(grid1d(d, 64), grid1d(V, 64));
-        k_gemm_f32<<<grid, 256, 0, st>>>(A, B, (int64_t)V, (int64_t)d, nv, EpiStoreF32{dW, d, t0 > 0 ? 1 : 0});
-        OAPL_LAUNCH_CHECK();
-      }
+      if (T <= p.Tp)   // the scoring pass left the logits here
+        k_dz_f32<<<dim3(grid1d(V, kDzRows), grid1d(T, 256)), 256, 0, st>>>(zt, p.ldz, V, T, tokens, lse2, coef);
+      else
+        launch_logits_f32(p, Hp, W, nv, EpiDzF32{tokens + t0, lse2 + t0, coef + t0, zt, p.ldz}, st);
+      OAPL_LAUNCH_CHECK();
+      // dH[t][j] = sum_v dZ[t][v] W[v][j]
+      if (int rc = contract_f32<false>(p.f32_dh, f32_operand(zt, p.ldz), f32_operand(W, d), nv, d, V, (float*)dH + t0 * d, part,
+                                       0, st))
+        return rc;
+      // dW[v][j] (+)= sum_t dZ[t][v] H[t][j]
+      if (int rc = contract_f32<true>(p.f32_dw, f32_operand(zt, p.ldz), f32_operand(Hp, d), V, d, nv, dW, part, t0 > 0 ? 1 : 0,
+                                      st))
+        return rc;
     }
   }
   return OAPL_OK;
@@ -691,13 +763,18 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
   return OAPL_OK;
 }
 
-// A plan's partial sums (12 bytes per token and vocabulary split) may be most of a small head's workspace.  They only
-// buy speed: a workspace that is too small for them, but holds one partial per token, is served with that.
-static void fit_splits(Plan& p, size_t have) {
-  Plan q;
-  if (p.total > have && p.dtype == OAPL_BF16 &&
-      make_plan(q, p.T, p.d, p.V, p.n_seq, p.n_groups, p.dtype, p.bwd, 0, 0, 0, 1))
+// A plan's partial sums (12 bytes per token and vocabulary split; partial results of the gradient contractions) may be
+// most of a small head's workspace.  They only buy speed: a workspace that is too small for them is served with fewer, the
+// least with none.  Returns the limit the plan was made with.
+static int fit_splits(Plan& p, size_t have) {
+  int limit = kAnySplits;
+  for (int fewer : {8, 4, 2, 1}) {
+    Plan q;
+    if (p.total <= have || !make_plan(q, p.T, p.d, p.V, p.n_seq, p.n_groups, p.dtype, p.bwd, 0, 0, 0, fewer)) break;
     p = q;
+    limit = fewer;
+  }
+  return limit;
 }
 
 static int fit_forward_plan(Plan& p, const void* ws, size_t have) {
@@ -715,8 +792,7 @@ static int fit_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, i
   if (!make_plan(p, T, d, V, n_seq, n_groups, dtype, bwd)) return OAPL_ERR_SHAPE;
   if (!bwd) return fit_forward_plan(p, ws, have);
   if (ws == nullptr || ((uintptr_t)ws & 255) != 0) return OAPL_ERR_WORKSPACE;
-  const int max_splits = p.total > have ? 1 : kAnySplits;
-  fit_splits(p, have);
+  const int max_splits = fit_splits(p, have);
   if (p.total > have) {
     const int64_t step = dtype == OAPL_BF16 ? Cfg::BN : 64;
     bool found = false;
@@ -1006,9 +1082,7 @@ int32_t oapl_sample_tokens(const void* H, const void* W, int64_t T, int32_t d, i
     }
     OAPL_LAUNCH_CHECK();
   } else {
-    F32Operand A{(const float*)H, d, 1}, B{(const float*)W, d, 1};
-    dim3 grid(grid1d(V, 64), grid1d(T, 64));
-    k_gemm_f32<<<grid, 256, 0, st>>>(A, B, T, (int64_t)V, (int64_t)d, EpiSampleF32{partials, T, inv_t, (uint32_t)seed, (uint32_t)(seed >> 32)});
+    launch_logits_f32(p, H, W, T, EpiSampleF32{partials, T, inv_t, (uint32_t)seed, (uint32_t)(seed >> 32)}, st);
     OAPL_LAUNCH_CHECK();
   }
   const int slices = finish_slices(p.smp.splits);

@@ -1,0 +1,55 @@
+"""The fp32 path at the edges of its tiles: rows and columns one short of and past 64 and 128, hidden sizes that allow
+16-byte loads and odd ones, k shorter than a stage and split over many workgroups, one panel (logits kept) and several
+(logits computed again), tight workspaces.  Tolerances as in test_gpu_parity.py for fp32 inputs."""
+import pytest
+import torch
+
+from oracle import oapl_oracle as orc
+from paper_2602_19362_amd import oapl
+from tests._util import f64, oracle_full
+from tests.test_gpu_parity import _check, _check_samples, _custom_batch, _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,V,lens,cap", [
+    (1, 1, [1], 0),                    # a single logit
+    (3, 63, [30, 33], 0),
+    (16, 64, [64], 0),
+    (33, 65, [60, 5], 0),              # no 16-byte loads
+    (64, 129, [100, 28], 0),
+    (65, 127, [100, 27], 0),
+    (128, 2049, [120, 9], 0),          # few tiles, long k: many splits
+    (36, 9001, [150, 107], 0),         # 128 x 128 logits tiles
+    (20, 700, [70, 60, 0, 63], 100),   # panels of 100 rows: logits computed again, ragged last panel
+    (21, 700, [70, 60, 0, 62], 64),
+])
+def test_loss(d, V, lens, cap):
+    print(d, V, lens, cap, flush=True)
+    b = _custom_batch("f32", d=d, V=V, lens=lens, n_groups=1, seed=d + V, beta=1.0)
+    ref = oracle_full(b)
+    res = _run(b, max_panel_rows=cap or None)
+    _check(b, res, ref, lp_tol=1e-5, rel_tol=1e-5, g_rtol=1e-4, g_atol_frac=1e-5)
+    again = _run(b, max_panel_rows=cap or None)
+    assert torch.equal(res.dH, again.dH) and torch.equal(res.dW, again.dW)
+    # the least workspace: no partial results, a row pitch that may be odd
+    least = oapl.workspace_bytes_for(b.T, d, V, len(lens), 1, oapl.OAPL_F32, True, 64)[0]
+    res = _run(b, workspace=torch.full((least,), 0xFF, dtype=torch.uint8, device=b.H.device))
+    _check(b, res, ref, lp_tol=1e-5, rel_tol=1e-5, g_rtol=1e-4, g_atol_frac=1e-5)
+
+
+@pytest.mark.parametrize("T,d,V", [(1, 1, 2), (63, 5, 65), (129, 40, 127), (130, 12, 20000)])
+def test_scores_and_samples(T, d, V):
+    print(T, d, V, flush=True)
+    b = _custom_batch("f32", d=d, V=V, lens=[T], n_groups=1, seed=T + V, beta=1.0)
+    lp, lse, ent, _ = oapl.logprob_fwd(b.H, b.W, b.tokens, want_lse=True, want_entropy=True)
+    tok, sc, _ = oapl.sample_tokens(b.H, b.W, 0.7, 5, want_scores=True)
+    torch.cuda.synchronize()
+    H, W = f64(b.H), f64(b.W)
+    z = torch.from_numpy(H @ W.T)
+    ref = torch.logsumexp(z, 1).numpy()
+    y = b.tokens.cpu().numpy()
+    assert abs(f64(lse) - ref).max() <= 1e-5
+    assert abs(f64(lp) - (z.numpy()[range(T), y] - ref)).max() <= 1e-5
+    assert abs(f64(ent) - orc.token_entropy(H, W)).max() <= 1e-5
+    _check_samples(b.H, b.W, 0.7, 5, tok, sc)
