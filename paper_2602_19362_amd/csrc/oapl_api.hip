@@ -298,8 +298,9 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
     } else {
       p.ldz = max_splits > 1 ? round_up(p.Tp, 4) : p.Tp;    // a multiple of 4 floats lets the contractions load 16 bytes
       p.off_G = take((size_t)p.ldz * V * 4);
-      p.f32_dh = pick_f32(p.Tp, d, V, max_splits, kPartF32Bytes);
-      p.f32_dw = pick_f32(V, d, p.Tp, max_splits, kPartF32Bytes);
+      const size_t scratch = T <= p.Tp ? kPartF32Bytes : 0;   // panels of a longer batch are rows enough for whole tiles
+      p.f32_dh = pick_f32(p.Tp, d, V, max_splits, scratch);
+      p.f32_dw = pick_f32(V, d, p.Tp, max_splits, scratch);
       const size_t dh = p.f32_dh.splits > 1 ? (size_t)p.f32_dh.splits * p.Tp * d * 4 : 0;
       const size_t dw = p.f32_dw.splits > 1 ? (size_t)p.f32_dw.splits * V * d * 4 : 0;
       p.off_part = take(dh > dw ? dh : dw);
