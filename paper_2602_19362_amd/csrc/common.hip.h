@@ -37,9 +37,14 @@ constexpr int kErrOffsets = 4;
 constexpr int kErrGroup = 5;
 constexpr int kErrTokenRange = 9;
 
-// First device-side error wins; later ones are dropped.
-__device__ __forceinline__ void record_error(int* flag, int code) {
-  atomicCAS(flag, 0, code);
+// The status header in the workspace.
+constexpr int kStatusWords = 64;   // 256 bytes
+constexpr int kFlagWord = 8;       // selects the two-pass path on the device
+constexpr int kCounterWord = 16;   // workgroups of the objective that are done (last_workgroup)
+
+// A token out of range is reported before anything else; of the other errors the first wins.
+__device__ __forceinline__ void record_token_error(int* flag) {
+  atomicExch(flag, kErrTokenRange);
 }
 // Errors in the batch structure (offsets, group ids) make the loss NaN whatever was recorded
 // first, so they are also kept in the status word behind the first.

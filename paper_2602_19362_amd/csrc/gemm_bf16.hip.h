@@ -613,11 +613,13 @@ __device__ __forceinline__ void strip_tile(int L, int MT, int NTl, int& mt, int&
 template <class C, bool ENT, bool ROWS>
 __global__ void __launch_bounds__(C::NT)
 k_fwd_lse(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int64_t T, int d, int n_kt,
-          int n_splits, int patch_tiles, float2* __restrict__ partials, float* __restrict__ upart, Gate gate) {
+          int n_splits, int patch_tiles, float2* __restrict__ partials, float* __restrict__ upart,
+          int* __restrict__ clear /* a status header to clear, or nullptr */, Gate gate) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   lds_char_ptr smem = (lds_char_ptr)smem_raw;
   if (gate_closed(gate)) return;
+  if (clear != nullptr && blockIdx.x == 0 && threadIdx.x < kStatusWords) clear[threadIdx.x] = 0;
 
   const int n_tiles = (int)((T + C::BN - 1) / C::BN);
   const int total = n_tiles * n_splits;
@@ -956,7 +958,7 @@ k_bwd_dz(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H_panel, int V
 // both the log-sum-exp and the gradient.  The soft-max is written unnormalised
 // against a per-token reference exponent ref2[t] that is known before the pass
 // (an upper-bound-free guess: the largest of a sample of the row's logits, see
-// k_sweep_ref), in the exp2 domain:
+// k_gather_logit), in the exp2 domain:
 //     Pt[t][v] = 2^(z[t][v] * log2(e) - ref2[t])          (bf16, packed twice like G above)
 //     spart[mt][t] = sum over the vocabulary tile mt of Pt[t][v]   (fp32, from the unrounded values)
 // so that, with S_t = sum_mt spart[mt][t]:  lse_t = (ref2[t] + log2 S_t) ln 2  and

@@ -51,7 +51,6 @@ constexpr int64_t kPanelBf16 = 12288;
 constexpr int64_t kPanelF32 = 4096;    // ... (fp32 path)
 constexpr size_t kPartF32Bytes = (size_t)64 << 20;   // most partial results of an fp32 gradient contraction
 constexpr int64_t kGroupScanLimit = (int64_t)1 << 32;   // n_seq * n_groups: every prompt's wavefront walks all rollouts
-constexpr int kStatusWords = 64;       // 256-byte header
 constexpr int kNumCU = 256;            // MI355X compute units (one workgroup of the dense kernels each: it fills the LDS)
 
 static inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
@@ -85,7 +84,6 @@ struct Plan {
   bool sweep = false;  // single-sweep loss path available (bf16 with backward)
 };
 
-constexpr int kFlagWord = 8;   // status word that selects the two-pass path on the device
 // A call this small gains nothing from the sweep's saved pass; it takes the two-pass path, whose one-hot
 // gradient entry is exact rather than exact up to the row-factor correction.
 constexpr int64_t kSweepMinTokens = 64;
@@ -407,7 +405,7 @@ struct FwdArgs {
 
 // One streaming log-sum-exp pass (the plan's tile; upart != nullptr: with the entropy's partial sums).
 template <class C, bool ROWS>
-static void launch_fwd_lse(const FwdArgs& a, float2* partials, float* upart, hipStream_t st, Gate gate) {
+static void launch_fwd_lse(const FwdArgs& a, float2* partials, float* upart, int* clear, hipStream_t st, Gate gate) {
   const int64_t total = (a.T + C::BN - 1) / C::BN * a.pick.splits;
   const unsigned grid = (unsigned)round_up(total, 8);
   // token tiles per XCD patch: eight while a token tile's H strip is at most 3 MiB (384 columns: d <= 4096), else four.
@@ -416,19 +414,20 @@ static void launch_fwd_lse(const FwdArgs& a, float2* partials, float* upart, hip
   const int patch_tiles = (size_t)a.n_kt * C::STAGE_B <= ((size_t)3 << 20) ? 8 : 4;
   if (upart)
     k_fwd_lse<C, true, ROWS><<<grid, C::NT, C::LDS_BYTES, st>>>(a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits,
-                                                              patch_tiles, partials, upart, gate);
+                                                              patch_tiles, partials, upart, clear, gate);
   else
     k_fwd_lse<C, false, ROWS><<<grid, C::NT, C::LDS_BYTES, st>>>(a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits,
-                                                               patch_tiles, partials, nullptr, gate);
+                                                               patch_tiles, partials, nullptr, clear, gate);
 }
-static void launch_fwd_lse(const FwdArgs& a, bool rows, float2* partials, float* upart, hipStream_t st, Gate gate) {
-  if (!rows) return launch_fwd_lse<Cfg, false>(a, partials, upart, st, gate);
+static void launch_fwd_lse(const FwdArgs& a, bool rows, float2* partials, float* upart, int* clear, hipStream_t st,
+                           Gate gate) {
+  if (!rows) return launch_fwd_lse<Cfg, false>(a, partials, upart, clear, st, gate);
   switch (a.pick.tile) {
-    case kTile64: return launch_fwd_lse<Cfg64, true>(a, partials, upart, st, gate);
-    case kTile128: return launch_fwd_lse<Cfg128, true>(a, partials, upart, st, gate);
-    case kTile256: return launch_fwd_lse<Cfg256, true>(a, partials, upart, st, gate);
-    case kTile320: return launch_fwd_lse<Cfg320, true>(a, partials, upart, st, gate);
-    case kTile384: return launch_fwd_lse<Cfg, true>(a, partials, upart, st, gate);
+    case kTile64: return launch_fwd_lse<Cfg64, true>(a, partials, upart, clear, st, gate);
+    case kTile128: return launch_fwd_lse<Cfg128, true>(a, partials, upart, clear, st, gate);
+    case kTile256: return launch_fwd_lse<Cfg256, true>(a, partials, upart, clear, st, gate);
+    case kTile320: return launch_fwd_lse<Cfg320, true>(a, partials, upart, clear, st, gate);
+    case kTile384: return launch_fwd_lse<Cfg, true>(a, partials, upart, clear, st, gate);
   }
 }
 
@@ -481,38 +480,39 @@ static int contract_f32(const F32Pick& pick, const F32Operand& A, const F32Opera
   return OAPL_OK;
 }
 
-// Clears the status header, gathers the sampled tokens' logits and (bf16) packs W and H.
-static int prepare_operands(const Plan& p, const void* H, const void* W, const int32_t* tokens, char* ws,
-                            hipStream_t st) {
-  int* status = (int*)(ws + p.off_status);
-  float* zy = (float*)(ws + p.off_zy);
-  const int64_t T = p.T;
-  k_fill_i32<<<1, 64, 0, st>>>(status, kStatusWords, 0);
+// bf16: packed copies of W and H where the plan wants them.
+static int pack_operands(const Plan& p, const void* H, const void* W, char* ws, hipStream_t st) {
+  if (p.T == 0 || p.dtype != OAPL_BF16) return OAPL_OK;
+  if (!prepare_kernels()) return OAPL_ERR_HIP;
+  if (p.rows) return OAPL_OK;
+  k_pack_rows<<<dim3(p.n_kt_d, p.n_rt_v), 256, 0, st>>>((const bf16_t*)W, p.V, p.d, p.d, (bf16_t*)(ws + p.off_Wp), p.n_kt_d,
+                                                        Cfg::BM);
   OAPL_LAUNCH_CHECK();
-  if (T == 0) return OAPL_OK;
-  if (p.dtype == OAPL_BF16) {
-    if (!prepare_kernels()) return OAPL_ERR_HIP;
-    k_gather_logit<bf16_t, float, 8><<<grid1d(T, 4), 256, 0, st>>>((const bf16_t*)H, (const bf16_t*)W, tokens, T, p.d,
-                                                                p.V, zy, status);
-    OAPL_LAUNCH_CHECK();
-    if (p.rows) return OAPL_OK;
-    bf16_t* Wp = (bf16_t*)(ws + p.off_Wp);
-    bf16_t* Hp = (bf16_t*)(ws + p.off_Hp);
-    k_pack_rows<<<dim3(p.n_kt_d, p.n_rt_v), 256, 0, st>>>((const bf16_t*)W, p.V, p.d, p.d, Wp, p.n_kt_d, Cfg::BM);
-    OAPL_LAUNCH_CHECK();
-    k_pack_rows<<<dim3(p.n_kt_d, (unsigned)p.n_rt_T), 256, 0, st>>>((const bf16_t*)H, T, p.d, p.d, Hp, p.n_kt_d,
-                                                                    Cfg::BN);
-    OAPL_LAUNCH_CHECK();
-  } else {
-    const bool vec = p.d % 4 == 0 && (((uintptr_t)H | (uintptr_t)W) & 15) == 0;
-    (vec ? k_gather_logit<float, double, 4> : k_gather_logit<float, double, 1>)<<<grid1d(T, 4), 256, 0, st>>>(
-        (const float*)H, (const float*)W, tokens, T, p.d, p.V, zy, status);
-    OAPL_LAUNCH_CHECK();
-  }
+  k_pack_rows<<<dim3(p.n_kt_d, (unsigned)p.n_rt_T), 256, 0, st>>>((const bf16_t*)H, p.T, p.d, p.d, (bf16_t*)(ws + p.off_Hp),
+                                                                  p.n_kt_d, Cfg::BN);
+  OAPL_LAUNCH_CHECK();
   return OAPL_OK;
 }
 
-// The operands of the contractions over d, in place or packed by prepare_operands: token row t of H starts at H + t * ld
+// The sampled tokens' logits, and the per-token arrays in `init`.  After the status header has been cleared.
+static int gather_logits(const Plan& p, const void* H, const void* W, const int32_t* tokens, TokenInit init, char* ws,
+                         hipStream_t st) {
+  int* status = (int*)(ws + p.off_status);
+  float* zy = (float*)(ws + p.off_zy);
+  if (p.T == 0) return OAPL_OK;
+  if (p.dtype == OAPL_BF16) {
+    k_gather_logit<bf16_t, float, 8><<<grid1d(p.T, 4), 256, 0, st>>>((const bf16_t*)H, (const bf16_t*)W, tokens, p.T, p.d,
+                                                                     p.V, zy, status, init);
+  } else {
+    const bool vec = p.d % 4 == 0 && (((uintptr_t)H | (uintptr_t)W) & 15) == 0;
+    (vec ? k_gather_logit<float, double, 4> : k_gather_logit<float, double, 1>)<<<grid1d(p.T, 4), 256, 0, st>>>(
+        (const float*)H, (const float*)W, tokens, p.T, p.d, p.V, zy, status, init);
+  }
+  OAPL_LAUNCH_CHECK();
+  return OAPL_OK;
+}
+
+// The operands of the contractions over d, in place or packed by pack_operands: token row t of H starts at H + t * ld
 // (packed: at a multiple of the token tile).
 struct ContractD {
   const bf16_t *W, *H;
@@ -523,43 +523,42 @@ static ContractD contract_d(const Plan& p, const void* H, const void* W, const c
   return ContractD{(const bf16_t*)(ws + p.off_Wp), (const bf16_t*)(ws + p.off_Hp), (int64_t)p.n_kt_d * kPackK};
 }
 
-// (after prepare_operands)
-static int forward_scores(const Plan& p, const void* H, const void* W, const int32_t* tokens, const float* logq,
-                          float* logprob_out, float* lse_out, float* entropy_out, char* ws, bool keep_for_loss,
-                          hipStream_t st, Gate gate = kNoGate) {
-  float2* partials = (float2*)(ws + p.off_partials);
-  float* upart = entropy_out ? (float*)(ws + p.off_upart) : nullptr;
-  float* zy = (float*)(ws + p.off_zy);
-  float* lse2 = keep_for_loss ? (float*)(ws + p.off_lse2) : nullptr;
-  double* diff = keep_for_loss ? (double*)(ws + p.off_diff) : nullptr;
-  float* omp = keep_for_loss ? (float*)(ws + p.off_omp) : nullptr;
-  float* inv = keep_for_loss ? (float*)(ws + p.off_inv) : nullptr;
+// The partial soft-max sums of every token (and the entropy's with `entropy`).  `clear`: a status header to clear.
+static int forward_partials(const Plan& p, const void* H, const void* W, bool entropy, bool keep_logits, int* clear, char* ws,
+                            hipStream_t st, Gate gate) {
   const int64_t T = p.T;
   if (T == 0) return OAPL_OK;
-  const bool timed = gate.flag == nullptr;
-  const int slices = finish_slices(p.fwd.splits);
-
+  float2* partials = (float2*)(ws + p.off_partials);
+  float* upart = entropy ? (float*)(ws + p.off_upart) : nullptr;
   if (p.dtype == OAPL_BF16) {
     const ContractD x = contract_d(p, H, W, ws);
     const FwdArgs args{x.W, x.H, p.V, T, p.d, p.n_kt_d, p.fwd};
-    {
-      ScopedKernelTimer tm(kFwdLse, st, timed);
-      launch_fwd_lse(args, p.rows, partials, upart, st, gate);
-    }
-    OAPL_LAUNCH_CHECK();
-    k_lse_finish<true><<<grid1d(T, 256 / slices), 256, 0, st>>>(partials, p.fwd.splits, T, zy, logq, logprob_out, lse_out,
-                                                                lse2, diff, omp, inv, upart, entropy_out, slices, gate);
-    OAPL_LAUNCH_CHECK();
+    ScopedKernelTimer tm(kFwdLse, st, gate.flag == nullptr);
+    launch_fwd_lse(args, p.rows, partials, upart, clear, st, gate);
   } else {
     // a batch whose gradient is one panel keeps its logits for it
-    float* zt = keep_for_loss && p.bwd && T <= p.Tp ? (float*)(ws + p.off_G) : nullptr;
+    float* zt = keep_logits && T <= p.Tp ? (float*)(ws + p.off_G) : nullptr;
+    if (clear) k_fill_i32<<<1, 64, 0, st>>>(clear, kStatusWords, 0);
     launch_logits_f32(p, H, W, T, EpiLseF32{partials, T, upart, zt, p.ldz}, st);
-    OAPL_LAUNCH_CHECK();
-    k_lse_finish<false><<<grid1d(T, 256 / slices), 256, 0, st>>>(partials, p.fwd.splits, T, zy, logq, logprob_out, lse_out,
-                                                                 lse2, diff, omp, inv, upart, entropy_out, slices,
-                                                                 kNoGate);
-    OAPL_LAUNCH_CHECK();
   }
+  OAPL_LAUNCH_CHECK();
+  return OAPL_OK;
+}
+
+// Log-probs (and lse, entropy) from the partial sums and the sampled tokens' logits; with `logq` also what the objective
+// and the gradients need.
+static int forward_finish(const Plan& p, const float* logq, float* logprob_out, float* lse_out, float* entropy_out, char* ws,
+                          hipStream_t st, Gate gate) {
+  const int64_t T = p.T;
+  if (T == 0) return OAPL_OK;
+  const bool loss = logq != nullptr;
+  const int slices = finish_slices(p.fwd.splits);
+  (p.dtype == OAPL_BF16 ? k_lse_finish<true> : k_lse_finish<false>)<<<grid1d(T, 256 / slices), 256, 0, st>>>(
+      (const float2*)(ws + p.off_partials), p.fwd.splits, T, (const float*)(ws + p.off_zy), logq, logprob_out, lse_out,
+      loss ? (float*)(ws + p.off_lse2) : nullptr, loss ? (double*)(ws + p.off_diff) : nullptr,
+      loss ? (float*)(ws + p.off_omp) : nullptr, loss ? (float*)(ws + p.off_inv) : nullptr,
+      entropy_out ? (const float*)(ws + p.off_upart) : nullptr, entropy_out, slices, gate);
+  OAPL_LAUNCH_CHECK();
   return OAPL_OK;
 }
 
@@ -595,98 +594,120 @@ static int launch_dh(const Plan& p, const bf16_t* W, const bf16_t* G, int64_t nv
   return OAPL_OK;
 }
 
-// Steps a8-a10, two-pass form: panel by panel, recompute the soft-max tiles into dZ and run
-// the two gradient contractions.  `wt_packed`: W^T has been packed already by this call.
+static int pack_wt(const Plan& p, const void* W, char* ws, hipStream_t st, Gate gate) {
+  if (p.rows) return OAPL_OK;
+  k_pack_transposed<<<dim3(p.n_kt_v, p.n_rt_d), 256, 0, st>>>((const bf16_t*)W, p.V, p.d, p.d, nullptr,
+                                                              (bf16_t*)(ws + p.off_WTp), p.n_kt_v, gate);
+  OAPL_LAUNCH_CHECK();
+  return OAPL_OK;
+}
+
+// Step a8, two-pass form: the soft-max tiles of the panel at token t0 recomputed into G and G^T.
+static int recompute_panel(const Plan& p, const void* H, const void* W, const int32_t* tokens, int64_t t0, bf16_t* G, bf16_t* GT,
+                           char* ws, hipStream_t st, Gate gate) {
+  const int64_t nv = (p.T - t0) < p.Tp ? (p.T - t0) : p.Tp;
+  const ContractD x = contract_d(p, H, W, ws);
+  {
+    ScopedKernelTimer tm(kBwdDz, st, gate.flag == nullptr);
+    (p.rows ? k_bwd_dz<Cfg, true> : k_bwd_dz<Cfg, false>)<<<
+        (unsigned)round_up(p.n_rt_v * ((nv + Cfg::BN - 1) / Cfg::BN), 8), Cfg::NT, Cfg::LDS_BYTES, st>>>(
+        x.W, x.H + t0 * x.ld, p.V, nv, p.d, p.n_kt_d, tokens + t0, (const float*)(ws + p.off_lse2) + t0,
+        (const float*)(ws + p.off_inv) + t0, G, p.n_kt_g, GT, p.n_kt_t, gate);
+  }
+  OAPL_LAUNCH_CHECK();
+  return OAPL_OK;
+}
+
+// Steps a9, a10: the two gradient contractions of the panel at token t0 from G and G^T, with coef[t] = the row factor
+// (two-pass form: f_t = c_t (1 - p_y); single sweep: a_t).
+static int panel_gradients(const Plan& p, const void* H, const void* W, int64_t t0, const bf16_t* G, const bf16_t* GT, void* dH,
+                           float* dW, char* ws, hipStream_t st, Gate gate, bool timed) {
+  const int d = p.d, V = p.V;
+  const int64_t nv = (p.T - t0) < p.Tp ? (p.T - t0) : p.Tp;
+  const int kt = (int)((nv + kPackK - 1) / kPackK);
+  const float* coef = (const float*)(ws + p.off_coef) + t0;
+  bf16_t* HTp = (bf16_t*)(ws + p.off_HTp);
+  // (diag(coef) H)^T of this panel, packed; token columns in [nv, 64 kt) come out as zeros
+  k_pack_transposed<<<dim3(kt, p.n_rt_d), 256, 0, st>>>((const bf16_t*)H + t0 * d, nv, d, d, coef, HTp, p.n_kt_t, gate);
+  OAPL_LAUNCH_CHECK();
+  if (int rc = launch_dh(p, (const bf16_t*)W, G, nv, coef, (bf16_t*)dH + t0 * d, t0 + p.Tp >= p.T, ws, st, gate, timed)) return rc;
+  {
+    ScopedKernelTimer tm(kBwdDw, st, timed);
+    const int64_t tiles = (int64_t)p.n_rt_d * ((V + Cfg::BN - 1) / Cfg::BN);
+    k_bwd_dw<Cfg><<<(unsigned)round_up(tiles, kNumCU), Cfg::NT, Cfg::LDS_BYTES, st>>>(HTp, GT, p.n_kt_t, d, V, kt, dW,
+                                                                                    t0 > 0 ? 1 : 0, gate);
+  }
+  OAPL_LAUNCH_CHECK();
+  return OAPL_OK;
+}
+
+// Steps a8-a10, two-pass form, panel by panel, from log-sum-exps and token coefficients.  `wt_packed`: W^T has been packed
+// already by this call.
 static int backward_grads(const Plan& p, const void* H, const void* W, const int32_t* tokens, void* dH, float* dW,
-                          char* ws, hipStream_t st, Gate gate = kNoGate, bool wt_packed = false) {
+                          char* ws, hipStream_t st, Gate gate, bool wt_packed) {
   const int64_t T = p.T;
   const int d = p.d, V = p.V;
-  const float* lse2 = (const float*)(ws + p.off_lse2);
-  const float* coef = (const float*)(ws + p.off_coef);  // bf16: f_t = c_t (1 - p_y); fp32: c_t
-  const float* inv = (const float*)(ws + p.off_inv);
-  const bool timed = gate.flag == nullptr;
   if (T == 0) {
     k_fill_f32<<<1024, 256, 0, st>>>(dW, (int64_t)V * d, 0.f, gate);
     OAPL_LAUNCH_CHECK();
     return OAPL_OK;
   }
   if (p.dtype == OAPL_BF16) {
-    bf16_t* HTp = (bf16_t*)(ws + p.off_HTp);
     bf16_t* G = (bf16_t*)(ws + p.off_G);
     bf16_t* GT = (bf16_t*)(ws + p.off_GT);
-    if (!wt_packed && !p.rows) {
-      k_pack_transposed<<<dim3(p.n_kt_v, p.n_rt_d), 256, 0, st>>>((const bf16_t*)W, V, d, d, nullptr,
-                                                                  (bf16_t*)(ws + p.off_WTp), p.n_kt_v, gate);
-      OAPL_LAUNCH_CHECK();
-    }
-    const int MTv = p.n_rt_v, MTd = p.n_rt_d;
-    const int NTv = (V + Cfg::BN - 1) / Cfg::BN;   // vocabulary tiles on the n side (dW contraction)
-    const ContractD x = contract_d(p, H, W, ws);
+    if (!wt_packed)
+      if (int rc = pack_wt(p, W, ws, st, gate)) return rc;
     for (int64_t t0 = 0; t0 < T; t0 += p.Tp) {
-      const int64_t nv = (T - t0) < p.Tp ? (T - t0) : p.Tp;
-      const int64_t Kt = round_up(nv, kPackK);
-      const int64_t NTl = (nv + Cfg::BN - 1) / Cfg::BN;
-      // (diag(f) H)^T of this panel, packed; token columns in [nv, Kt) come out as zeros
-      k_pack_transposed<<<dim3((unsigned)(Kt / kPackK), p.n_rt_d), 256, 0, st>>>(
-          (const bf16_t*)H + t0 * d, nv, d, d, coef + t0, HTp, p.n_kt_t, gate);
-      OAPL_LAUNCH_CHECK();
-      {
-        ScopedKernelTimer tm(kBwdDz, st, timed);
-        (p.rows ? k_bwd_dz<Cfg, true> : k_bwd_dz<Cfg, false>)<<<(unsigned)round_up(MTv * NTl, 8), Cfg::NT, Cfg::LDS_BYTES,
-                                                               st>>>(
-            x.W, x.H + t0 * x.ld, V, nv, d, p.n_kt_d, tokens + t0, lse2 + t0, inv + t0, G, p.n_kt_g, GT, p.n_kt_t, gate);
-      }
-      OAPL_LAUNCH_CHECK();
-      if (int rc = launch_dh(p, (const bf16_t*)W, G, nv, coef + t0, (bf16_t*)dH + t0 * d, t0 + p.Tp >= T, ws, st, gate, timed)) return rc;
-      {
-        ScopedKernelTimer tm(kBwdDw, st, timed);
-        k_bwd_dw<Cfg><<<(unsigned)round_up((int64_t)MTd * NTv, kNumCU), Cfg::NT, Cfg::LDS_BYTES, st>>>(
-            HTp, GT, p.n_kt_t, d, V, (int)(Kt / kPackK), dW, t0 > 0 ? 1 : 0, gate);
-      }
-      OAPL_LAUNCH_CHECK();
+      if (int rc = recompute_panel(p, H, W, tokens, t0, G, GT, ws, st, gate)) return rc;
+      if (int rc = panel_gradients(p, H, W, t0, G, GT, dH, dW, ws, st, gate, gate.flag == nullptr)) return rc;
     }
-  } else {
-    float* zt = (float*)(ws + p.off_G);   // dZ^T of a panel
-    float* part = (float*)(ws + p.off_part);
-    for (int64_t t0 = 0; t0 < T; t0 += p.Tp) {
-      const int64_t nv = (T - t0) < p.Tp ? (T - t0) : p.Tp;
-      const float* Hp = (const float*)H + t0 * d;
-      if (T <= p.Tp)   // the scoring pass left the logits here
-        k_dz_f32<<<dim3(grid1d(V, kDzRows), grid1d(T, 256)), 256, 0, st>>>(zt, p.ldz, V, T, tokens, lse2, coef);
-      else
-        launch_logits_f32(p, Hp, W, nv, EpiDzF32{tokens + t0, lse2 + t0, coef + t0, zt, p.ldz}, st);
-      OAPL_LAUNCH_CHECK();
-      // dH[t][j] = sum_v dZ[t][v] W[v][j]
-      if (int rc = contract_f32<false>(p.f32_dh, f32_operand(zt, p.ldz), f32_operand(W, d), nv, d, V, (float*)dH + t0 * d, part,
-                                       0, st))
-        return rc;
-      // dW[v][j] (+)= sum_t dZ[t][v] H[t][j]
-      if (int rc = contract_f32<true>(p.f32_dw, f32_operand(zt, p.ldz), f32_operand(Hp, d), V, d, nv, dW, part, t0 > 0 ? 1 : 0,
-                                      st))
-        return rc;
-    }
+    return OAPL_OK;
+  }
+  float* zt = (float*)(ws + p.off_G);   // dZ^T of a panel
+  float* part = (float*)(ws + p.off_part);
+  const float* lse = (const float*)(ws + p.off_lse2);
+  const float* coef = (const float*)(ws + p.off_coef);
+  for (int64_t t0 = 0; t0 < T; t0 += p.Tp) {
+    const int64_t nv = (T - t0) < p.Tp ? (T - t0) : p.Tp;
+    const float* Hp = (const float*)H + t0 * d;
+    if (T <= p.Tp)   // the scoring pass left the logits here
+      k_dz_f32<<<dim3(grid1d(V, kDzRows), grid1d(T, 256)), 256, 0, st>>>(zt, p.ldz, V, T, tokens, lse, coef);
+    else
+      launch_logits_f32(p, Hp, W, nv, EpiDzF32{tokens + t0, lse + t0, coef + t0, zt, p.ldz}, st);
+    OAPL_LAUNCH_CHECK();
+    // dH[t][j] = sum_v dZ[t][v] W[v][j]
+    if (int rc = contract_f32<false>(p.f32_dh, f32_operand(zt, p.ldz), f32_operand(W, d), nv, d, V, (float*)dH + t0 * d, part,
+                                     0, st))
+      return rc;
+    // dW[v][j] (+)= sum_t dZ[t][v] H[t][j]
+    if (int rc = contract_f32<true>(p.f32_dw, f32_operand(zt, p.ldz), f32_operand(Hp, d), V, d, nv, dW, part, t0 > 0 ? 1 : 0,
+                                    st))
+      return rc;
   }
   return OAPL_OK;
 }
 
+// A rollout may span at most n_buf - 1 panels' worth of rows on the single sweep (any length if the batch is one panel).
+static int64_t sweep_longest(const Plan& p) { return p.n_buf > 1 ? (int64_t)(p.n_buf - 1) * p.Tp : p.Tp; }
+
 // Steps a1-a3 and a8-a10 in ONE pass over the logits (bf16, T > 0).  Per panel of token rows:
 // k_sweep writes the unnormalised soft-max panel and its row sums, k_sweep_finish turns the sums
-// into log-probs; the objective's O(T) kernels (`objective`, which must fill coef[t] = c_t * nis[t]
-// for every token whose rollout is complete and may run any number of times) then give the row
+// into log-probs; the objective (`objective(gate, factors)`, which must fill coef[t] = c_t * factor[t]
+// for every token whose rollout is complete and may run any number of times) then gives the row
 // factors, and the two gradient contractions consume the panel.  A rollout may straddle a panel
 // boundary, so a panel's contractions run after the NEXT panel's sweep (two panel buffers); by
 // then every rollout that touches it is complete, because no rollout is longer than a panel
-// (k_sweep_plan raises the fallback flag otherwise).  All kernels here run only while the flag is 0.
+// (sweep_plan raises the fallback flag otherwise).  What the sweep does runs only while the flag is 0, and the
+// two-pass schedule behind it only if it is not.  A batch of one panel shares the objective and the contractions between
+// the two: its fallback is the scoring pass and the recompute alone (three closed launches in place of nine).
 template <class Objective>
 static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t* tokens, const float* logq,
-                      const int64_t* seq_offsets, float* logprob_out, void* dH, float* dW, char* ws, hipStream_t st,
-                      Objective&& objective) {
+                      float* logprob_out, void* dH, float* dW, char* ws, hipStream_t st, Objective&& objective) {
   const int64_t T = p.T;
   const int d = p.d, V = p.V;
   int* flag = (int*)(ws + p.off_status) + kFlagWord;
-  const Gate fast{flag, 0};
+  const Gate fast{flag, 0}, slow{flag, 1};
   const ContractD x = contract_d(p, H, W, ws);
-  bf16_t* HTp = (bf16_t*)(ws + p.off_HTp);
   auto Gbuf = [&](int64_t k) { return (bf16_t*)(ws + p.off_G + (size_t)(k % p.n_buf) * p.size_G); };
   auto GTbuf = [&](int64_t k) { return (bf16_t*)(ws + p.off_GT + (size_t)(k % p.n_buf) * p.size_GT); };
   float2* sample = (float2*)(ws + p.off_partials);
@@ -695,73 +716,73 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
   float* spart = (float*)(ws + p.off_spart);
   double* diff = (double*)(ws + p.off_diff);
   float* nis = (float*)(ws + p.off_inv);
-  const float* coef = (const float*)(ws + p.off_coef);
-  const int MTv = p.n_rt_v, MTd = p.n_rt_d;
-  const int NTv = (V + Cfg::BN - 1) / Cfg::BN;     // vocabulary tiles on the n side (dW contraction)
+  const float* omp = (const float*)(ws + p.off_omp);
 
-  // a rollout may span at most n_buf - 1 panels' worth of rows (any length if the batch is one panel)
-  k_sweep_plan<<<grid1d(p.n_seq > 0 ? p.n_seq : 1, 256), 256, 0, st>>>(
-      seq_offsets, p.n_seq, T, p.n_buf > 1 ? (int64_t)(p.n_buf - 1) * p.Tp : p.Tp, flag);
-  OAPL_LAUNCH_CHECK();
-  if (!p.rows) {
-    k_pack_transposed<<<dim3(p.n_kt_v, p.n_rt_d), 256, 0, st>>>((const bf16_t*)W, V, d, d, nullptr,
-                                                                (bf16_t*)(ws + p.off_WTp), p.n_kt_v, kNoGate);
-    OAPL_LAUNCH_CHECK();
-  }
+  if (int rc = pack_wt(p, W, ws, st, kNoGate)) return rc;
   // reference exponents: running maximum over the first 256 vocabulary entries, one workgroup per 64 tokens (a walk of
   // d / 64 k-blocks each, bound by their latency)
   launch_fwd_lse<CfgRef, true>(FwdArgs{(const bf16_t*)W, (const bf16_t*)H, V < CfgRef::BM ? V : CfgRef::BM, T, d, p.n_kt_d,
-                                       TilePick{}}, sample, nullptr, st, fast);
+                                       TilePick{}}, sample, nullptr, nullptr, st, fast);
   OAPL_LAUNCH_CHECK();
-  k_sweep_ref<<<grid1d(T, 256), 256, 0, st>>>(sample, zy, T, ref2);
-  OAPL_LAUNCH_CHECK();
-  // rows not swept yet must read as "no contribution" in the objective's kernels
-  k_fill_f64<<<grid1d(T, 256 * 8), 256, 0, st>>>(diff, T, 0.0);
-  OAPL_LAUNCH_CHECK();
-  k_fill_f32<<<grid1d(T, 256 * 8), 256, 0, st>>>(nis, T, 0.f);
-  OAPL_LAUNCH_CHECK();
+  if (int rc = gather_logits(p, H, W, tokens, TokenInit{(float*)(ws + p.off_coef), sample, ref2, diff, nis}, ws, st)) return rc;
 
-  const int64_t n_panels = (T + p.Tp - 1) / p.Tp;
-  auto gradients = [&](int64_t k) -> int {
+  auto sweep = [&](int64_t k) -> int {
     const int64_t t0 = k * p.Tp;
     const int64_t nv = (T - t0) < p.Tp ? (T - t0) : p.Tp;
-    const int64_t Kt = round_up(nv, kPackK);
-    if (int rc = objective(fast, nis)) return rc;
-    k_pack_transposed<<<dim3((unsigned)(Kt / kPackK), p.n_rt_d), 256, 0, st>>>(
-        (const bf16_t*)H + t0 * d, nv, d, d, coef + t0, HTp, p.n_kt_t, fast);
-    OAPL_LAUNCH_CHECK();
-    if (int rc = launch_dh(p, (const bf16_t*)W, Gbuf(k), nv, coef + t0, (bf16_t*)dH + t0 * d, k + 1 == n_panels, ws, st, fast, true)) return rc;
-    {
-      ScopedKernelTimer tm(kBwdDw, st);
-      k_bwd_dw<Cfg><<<(unsigned)round_up((int64_t)MTd * NTv, kNumCU), Cfg::NT, Cfg::LDS_BYTES, st>>>(
-          HTp, GTbuf(k), p.n_kt_t, d, V, (int)(Kt / kPackK), dW, k > 0 ? 1 : 0, fast);
-    }
-    OAPL_LAUNCH_CHECK();
-    return OAPL_OK;
-  };
-  for (int64_t k = 0; k < n_panels; ++k) {
-    const int64_t t0 = k * p.Tp;
-    const int64_t nv = (T - t0) < p.Tp ? (T - t0) : p.Tp;
-    const int64_t NTl = round_up(nv, Cfg::BN) / Cfg::BN;
     {
       ScopedKernelTimer tm(kSweep, st);
-      (p.rows ? k_sweep<Cfg, true> : k_sweep<Cfg, false>)<<<(unsigned)round_up(MTv * NTl, 8), Cfg::NT, Cfg::LDS_BYTES,
-                                                            st>>>(
-          x.W, x.H + t0 * x.ld, V, nv, d, p.n_kt_d, ref2 + t0, Gbuf(k), p.n_kt_g, GTbuf(k),
-          p.n_kt_t, spart, p.Tp, fast);
+      (p.rows ? k_sweep<Cfg, true> : k_sweep<Cfg, false>)<<<
+          (unsigned)round_up(p.n_rt_v * ((nv + Cfg::BN - 1) / Cfg::BN), 8), Cfg::NT, Cfg::LDS_BYTES, st>>>(
+          x.W, x.H + t0 * x.ld, V, nv, d, p.n_kt_d, ref2 + t0, Gbuf(k), p.n_kt_g, GTbuf(k), p.n_kt_t, spart, p.Tp, fast);
     }
     OAPL_LAUNCH_CHECK();
     k_sweep_finish<<<grid1d(nv, kFinishRows), kFinishSlices * kFinishRows, 0, st>>>(
-        spart, MTv, p.Tp, nv, ref2 + t0, zy + t0, logq + t0, tokens + t0, V,
+        spart, p.n_rt_v, p.Tp, nv, ref2 + t0, zy + t0, logq + t0, tokens + t0, V,
         logprob_out ? logprob_out + t0 : nullptr, diff + t0, nis + t0, Gbuf(k), p.n_kt_g, GTbuf(k), p.n_kt_t, flag,
         fast);
     OAPL_LAUNCH_CHECK();
-    if (k >= p.n_buf - 1 && p.n_buf > 1)
+    return OAPL_OK;
+  };
+
+  const int64_t n_panels = (T + p.Tp - 1) / p.Tp;
+  if (n_panels == 1) {
+    if (int rc = sweep(0)) return rc;
+    if (int rc = forward_partials(p, H, W, false, false, nullptr, ws, st, slow)) return rc;
+    if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, ws, st, slow)) return rc;
+    if (int rc = objective(kNoGate, TokenFactor{nis, omp, flag})) return rc;
+    if (int rc = recompute_panel(p, H, W, tokens, 0, Gbuf(0), GTbuf(0), ws, st, slow)) return rc;
+    return panel_gradients(p, H, W, 0, Gbuf(0), GTbuf(0), dH, dW, ws, st, kNoGate, true);
+  }
+
+  auto gradients = [&](int64_t k) -> int {
+    if (int rc = objective(fast, TokenFactor{nis, nullptr, nullptr})) return rc;
+    return panel_gradients(p, H, W, k * p.Tp, Gbuf(k), GTbuf(k), dH, dW, ws, st, fast, true);
+  };
+  for (int64_t k = 0; k < n_panels; ++k) {
+    if (int rc = sweep(k)) return rc;
+    if (k >= p.n_buf - 1)
       if (int rc = gradients(k - (p.n_buf - 1))) return rc;
   }
-  for (int64_t k = n_panels - (p.n_buf > 1 ? p.n_buf - 1 : 1); k < n_panels; ++k)
+  for (int64_t k = n_panels - (p.n_buf - 1); k < n_panels; ++k)
     if (int rc = gradients(k)) return rc;
-  return OAPL_OK;
+  if (int rc = forward_partials(p, H, W, false, false, nullptr, ws, st, slow)) return rc;
+  if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, ws, st, slow)) return rc;
+  if (int rc = objective(slow, TokenFactor{omp, nullptr, nullptr})) return rc;
+  return backward_grads(p, H, W, tokens, dH, dW, ws, st, slow, true);
+}
+
+// The two-pass schedule (and the scoring alone, without gradients).
+template <class Objective>
+static int two_pass_path(const Plan& p, const void* H, const void* W, const int32_t* tokens, const float* logq,
+                         float* logprob_out, void* dH, float* dW, char* ws, hipStream_t st, Objective&& objective) {
+  float* coef = p.bwd ? (float*)(ws + p.off_coef) : nullptr;
+  if (int rc = gather_logits(p, H, W, tokens, TokenInit{coef, nullptr, nullptr, nullptr, nullptr}, ws, st)) return rc;
+  if (int rc = forward_partials(p, H, W, false, p.bwd, nullptr, ws, st, kNoGate)) return rc;
+  if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, ws, st, kNoGate)) return rc;
+  const float* factor = p.bwd && p.dtype == OAPL_BF16 ? (const float*)(ws + p.off_omp) : nullptr;
+  if (int rc = objective(kNoGate, TokenFactor{factor, nullptr, nullptr})) return rc;
+  if (!p.bwd) return OAPL_OK;
+  return backward_grads(p, H, W, tokens, dH, dW, ws, st, kNoGate, false);
 }
 
 // A plan's partial sums (12 bytes per token and vocabulary split; partial results of the gradient contractions) may be
@@ -817,6 +838,13 @@ static int fit_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, i
   return OAPL_OK;
 }
 
+// One workgroup takes a call's first steps while it has at most a few thousand (rollout, prompt) pairs to look at.
+static bool begin_in_one_launch(int n_seq, int n_groups) { return (int64_t)n_seq * n_groups + n_seq + n_groups <= 8192; }
+static unsigned begin_grid(int n_seq, int n_groups) {
+  const unsigned a = grid1d(n_groups, 4), b = grid1d(n_seq > 0 ? n_seq : 1, 256);
+  return a > b ? a : b;
+}
+
 static int loss_impl(const void* H, const void* W, const int32_t* tokens, const float* logq,
                      const int64_t* seq_offsets, const float* rewards, const int32_t* group_ids, int64_t T, int32_t d,
                      int32_t V, int32_t n_seq, int32_t n_groups, int32_t dtype, float beta_value, float beta_loss,
@@ -841,51 +869,32 @@ static int loss_impl(const void* H, const void* W, const int32_t* tokens, const 
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
   int* status = (int*)(ws + p.off_status);
-  double* Delta = (double*)(ws + p.off_delta);
-  float* cseq = (float*)(ws + p.off_cseq);
-  float* coef = (float*)(ws + p.off_coef);
+  double* vstar = (double*)(ws + p.off_vstar);
+  const bool sweep = p.sweep && T >= kSweepMinTokens && !(flags & OAPL_FLAG_TWO_PASS);
+  const int64_t longest = sweep ? sweep_longest(p) : -1;
 
-  // Steps a4-a7 from logprob - logq [T]: per-rollout sums, Eq. 2, Eq. 3, token coefficients
-  // coef[t] = c_t * factor[t] (factor = NULL: c_t itself).
-  auto objective = [&](Gate gate, const float* factor) -> int {
-    if (n_seq > 0) {
-      k_segmented_sum<double><<<n_seq, 256, 0, st>>>((const double*)(ws + p.off_diff), seq_offsets, n_seq, T, Delta,
-                                                     gate);
-      OAPL_LAUNCH_CHECK();
-    }
-    k_residual_loss<<<1, 256, 0, st>>>(Delta, rewards, group_ids, seq_offsets, n_seq, n_groups, T,
-                                       (double)beta_loss, (double)loss_scale, (const double*)(ws + p.off_vstar), cseq,
-                                       loss_out, seq_logratio_out, status, gate);
+  // the status header, the sweep's length check, and Eq. 2, which needs the rewards only
+  const bool one = begin_in_one_launch(n_seq, n_groups);
+  if (!one) k_fill_i32<<<1, 64, 0, st>>>(status, kStatusWords, 0);
+  k_oapl_begin<<<one ? 1 : begin_grid(n_seq, n_groups), 256, 0, st>>>(rewards, group_ids, seq_offsets, n_seq, n_groups, T,
+                                                                      longest, (double)beta_value, vstar, vstar_out, status,
+                                                                      one ? 1 : 0);
+  OAPL_LAUNCH_CHECK();
+  if (int rc = pack_operands(p, H, W, ws, st)) return rc;
+
+  // Steps a4, a6, a7 from logprob - logq [T]
+  auto objective = [&](Gate gate, TokenFactor factors) -> int {
+    k_oapl_objective<<<n_seq > 0 ? n_seq : 1, 256, 0, st>>>(
+        (const double*)(ws + p.off_diff), rewards, group_ids, seq_offsets, n_seq, n_groups, T, (double)beta_loss,
+        (double)loss_scale, vstar, factors, (double*)(ws + p.off_delta), bwd && T > 0 ? (float*)(ws + p.off_coef) : nullptr,
+        loss_out, seq_logratio_out, status, gate);
     OAPL_LAUNCH_CHECK();
-    if (bwd && T > 0) {
-      k_fill_f32<<<grid1d(T, 256 * 8), 256, 0, st>>>(coef, T, 0.f, gate);
-      OAPL_LAUNCH_CHECK();
-      if (n_seq > 0) {
-        k_token_coefficients<<<n_seq, 256, 0, st>>>(cseq, seq_offsets, n_seq, T, factor, coef, gate);
-        OAPL_LAUNCH_CHECK();
-      }
-    }
     return OAPL_OK;
   };
-
-  if (int rc = prepare_operands(p, H, W, tokens, ws, st)) return rc;
-  // Eq. 2 needs the rewards only: one wavefront per prompt, before anything is scored
-  k_group_value<<<grid1d(n_groups, 4), 256, 0, st>>>(rewards, group_ids, n_seq, n_groups, (double)beta_value,
-                                                     (double*)(ws + p.off_vstar), vstar_out, status, kNoGate);
-  OAPL_LAUNCH_CHECK();
-  // bf16 with gradients: one sweep over the logits; the two-pass path behind it runs only if the
+  // bf16 with gradients: one sweep over the logits; the two-pass schedule behind it runs only if the
   // sweep's preconditions fail on this call's data (decided on the device, in stream order)
-  const bool sweep = bwd && T >= kSweepMinTokens && p.sweep && !(flags & OAPL_FLAG_TWO_PASS);
-  Gate slow = kNoGate;
-  if (sweep) {
-    if (int rc = sweep_path(p, H, W, tokens, logq, seq_offsets, logprob_out, dH, dW, ws, st, objective)) return rc;
-    slow = Gate{status + kFlagWord, 1};
-  }
-  if (int rc = forward_scores(p, H, W, tokens, logq, logprob_out, nullptr, nullptr, ws, true, st, slow)) return rc;
-  const float* factor = (bwd && p.dtype == OAPL_BF16) ? (const float*)(ws + p.off_omp) : nullptr;
-  if (int rc = objective(slow, factor)) return rc;
-  if (!bwd) return OAPL_OK;
-  return backward_grads(p, H, W, tokens, dH, dW, ws, st, slow, sweep);
+  if (sweep) return sweep_path(p, H, W, tokens, logq, logprob_out, dH, dW, ws, st, objective);
+  return two_pass_path(p, H, W, tokens, logq, logprob_out, dH, dW, ws, st, objective);
 }
 
 // The paper's baseline objective on the same fused head (Sec. 2): scores, group advantages,
@@ -913,44 +922,35 @@ static int grpo_impl(const void* H, const void* W, const int32_t* tokens, const 
   float* adv = (float*)(ws + p.off_cseq);
   double* gstat = (double*)(ws + p.off_vstar);          // [2 n_groups]: mean, std
   double* wseq = (double*)(ws + p.off_gw);              // [n_seq + n_groups]
-  double* seqterm = (double*)(ws + p.off_delta);
-  float* coef = (float*)(ws + p.off_coef);
+  double* gsize = wseq + (n_seq > 0 ? n_seq : 1);
+  const bool sweep = p.sweep && T >= kSweepMinTokens && !(flags & OAPL_FLAG_TWO_PASS);
+  const int64_t longest = sweep ? sweep_longest(p) : -1;
 
-  auto objective = [&](Gate gate, const float* factor) -> int {
-    if (T > 0) {
-      k_fill_f32<<<grid1d(T, 256 * 8), 256, 0, st>>>(coef, T, 0.f, gate);
-      OAPL_LAUNCH_CHECK();
-    }
-    if (n_seq > 0) {
-      k_grpo_tokens<<<n_seq, 256, 0, st>>>((const double*)(ws + p.off_diff), logq, logp_old, seq_offsets, n_seq, T,
-                                           adv, wseq, (double)clip_eps, factor, coef, seqterm, gate);
-      OAPL_LAUNCH_CHECK();
-    }
-    k_grpo_loss<<<1, 256, 0, st>>>(seqterm, n_seq, status, loss_out, gate);
+  auto begin = [&](unsigned grid, int steps) {
+    k_grpo_begin<<<grid, 256, 0, st>>>(rewards, group_ids, seq_offsets, n_seq, n_groups, T, longest, (double)adv_eps,
+                                       (double)loss_scale, gstat, gstat + n_groups, gsize, adv, wseq, adv_out, status, steps);
+  };
+  if (begin_in_one_launch(n_seq, n_groups)) {
+    begin(1, 3);
+  } else {
+    k_fill_i32<<<1, 64, 0, st>>>(status, kStatusWords, 0);
+    OAPL_LAUNCH_CHECK();
+    begin(begin_grid(n_seq, n_groups), 1);
+    OAPL_LAUNCH_CHECK();
+    begin(grid1d(n_seq > 0 ? n_seq : 1, 256), 2);
+  }
+  OAPL_LAUNCH_CHECK();
+  if (int rc = pack_operands(p, H, W, ws, st)) return rc;
+
+  auto objective = [&](Gate gate, TokenFactor factors) -> int {
+    k_grpo_objective<<<n_seq > 0 ? n_seq : 1, 256, 0, st>>>(
+        (const double*)(ws + p.off_diff), logq, logp_old, seq_offsets, n_seq, T, adv, wseq, (double)clip_eps, factors,
+        bwd && T > 0 ? (float*)(ws + p.off_coef) : nullptr, (double*)(ws + p.off_delta), loss_out, status, gate);
     OAPL_LAUNCH_CHECK();
     return OAPL_OK;
   };
-
-  if (int rc = prepare_operands(p, H, W, tokens, ws, st)) return rc;
-  k_grpo_group_stats<<<grid1d(n_groups, 4), 256, 0, st>>>(rewards, group_ids, n_seq, n_groups, gstat,
-                                                          gstat + n_groups, wseq + (n_seq > 0 ? n_seq : 1), status,
-                                                          kNoGate);
-  OAPL_LAUNCH_CHECK();
-  k_grpo_advantage<<<grid1d(n_seq > 0 ? n_seq : 1, 256), 256, 0, st>>>(
-      rewards, group_ids, seq_offsets, n_seq, n_groups, T, (double)adv_eps, (double)loss_scale, gstat,
-      gstat + n_groups, wseq + (n_seq > 0 ? n_seq : 1), adv, wseq, adv_out, status, kNoGate);
-  OAPL_LAUNCH_CHECK();
-  const bool sweep = bwd && T >= kSweepMinTokens && p.sweep && !(flags & OAPL_FLAG_TWO_PASS);
-  Gate slow = kNoGate;
-  if (sweep) {
-    if (int rc = sweep_path(p, H, W, tokens, logq, seq_offsets, logprob_out, dH, dW, ws, st, objective)) return rc;
-    slow = Gate{status + kFlagWord, 1};
-  }
-  if (int rc = forward_scores(p, H, W, tokens, logq, logprob_out, nullptr, nullptr, ws, true, st, slow)) return rc;
-  const float* factor = (bwd && p.dtype == OAPL_BF16) ? (const float*)(ws + p.off_omp) : nullptr;
-  if (int rc = objective(slow, factor)) return rc;
-  if (!bwd) return OAPL_OK;
-  return backward_grads(p, H, W, tokens, dH, dW, ws, st, slow, sweep);
+  if (sweep) return sweep_path(p, H, W, tokens, logq, logprob_out, dH, dW, ws, st, objective);
+  return two_pass_path(p, H, W, tokens, logq, logprob_out, dH, dW, ws, st, objective);
 }
 
 // Scratch of the entry point that allocates nothing: every GPU the library runs on holds its own
@@ -1039,9 +1039,18 @@ int32_t oapl_logprob_fwd(const void* H, const void* W, const int32_t* tokens, in
   if (!W) return OAPL_ERR_NULL;
   if (T > 0 && (!H || !tokens || !logprob_out)) return OAPL_ERR_NULL;
   if (int rc = fit_forward_plan(p, workspace, workspace_bytes)) return rc;
-  if (int rc = prepare_operands(p, H, W, tokens, (char*)workspace, (hipStream_t)stream)) return rc;
-  return forward_scores(p, H, W, tokens, nullptr, logprob_out, lse_out, entropy_out, (char*)workspace, false,
-                        (hipStream_t)stream);
+  hipStream_t st = (hipStream_t)stream;
+  char* ws = (char*)workspace;
+  int* status = (int*)(ws + p.off_status);
+  if (T == 0) {
+    k_fill_i32<<<1, 64, 0, st>>>(status, kStatusWords, 0);
+    OAPL_LAUNCH_CHECK();
+    return OAPL_OK;
+  }
+  if (int rc = pack_operands(p, H, W, ws, st)) return rc;
+  if (int rc = forward_partials(p, H, W, entropy_out != nullptr, false, status, ws, st, kNoGate)) return rc;
+  if (int rc = gather_logits(p, H, W, tokens, TokenInit{}, ws, st)) return rc;
+  return forward_finish(p, nullptr, logprob_out, lse_out, entropy_out, ws, st, kNoGate);
 }
 
 int32_t oapl_sample_tokens(const void* H, const void* W, int64_t T, int32_t d, int32_t V, int32_t dtype,
@@ -1056,9 +1065,12 @@ int32_t oapl_sample_tokens(const void* H, const void* W, int64_t T, int32_t d, i
   if (int rc = fit_forward_plan(p, workspace, workspace_bytes)) return rc;
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
-  k_fill_i32<<<1, 64, 0, st>>>((int*)(ws + p.off_status), kStatusWords, 0);
-  OAPL_LAUNCH_CHECK();
-  if (T == 0) return OAPL_OK;
+  int* status = (int*)(ws + p.off_status);
+  if (T == 0) {
+    k_fill_i32<<<1, 64, 0, st>>>(status, kStatusWords, 0);
+    OAPL_LAUNCH_CHECK();
+    return OAPL_OK;
+  }
   float2* partials = (float2*)(ws + p.off_partials);
   const float inv_t = 1.0f / temperature;
   if (dtype == OAPL_BF16) {
@@ -1087,7 +1099,7 @@ int32_t oapl_sample_tokens(const void* H, const void* W, int64_t T, int32_t d, i
     OAPL_LAUNCH_CHECK();
   }
   const int slices = finish_slices(p.smp.splits);
-  k_sample_finish<<<grid1d(T, 256 / slices), 256, 0, st>>>(partials, p.smp.splits, T, tokens_out, score_out, slices);
+  k_sample_finish<<<grid1d(T, 256 / slices), 256, 0, st>>>(partials, p.smp.splits, T, tokens_out, score_out, slices, status);
   OAPL_LAUNCH_CHECK();
   return OAPL_OK;
 }
@@ -1147,7 +1159,7 @@ int32_t oapl_segmented_sum_f32(const float* x, const int64_t* seq_offsets, int32
   if (n_seq < 0) return OAPL_ERR_SHAPE;
   if (n_seq == 0) return OAPL_OK;
   if (!x || !seq_offsets || !out) return OAPL_ERR_NULL;
-  k_segmented_sum<float><<<n_seq, 256, 0, (hipStream_t)stream>>>(x, seq_offsets, n_seq, -1, out);
+  k_segmented_sum<float><<<n_seq, 256, 0, (hipStream_t)stream>>>(x, seq_offsets, n_seq, out);
   OAPL_LAUNCH_CHECK();
   return OAPL_OK;
 }

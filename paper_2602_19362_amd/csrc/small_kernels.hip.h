@@ -15,11 +15,8 @@ __device__ __forceinline__ float to_f32(bf16_t x) { return (float)x; }
 __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
-__global__ void k_fill_f32(float* p, int64_t n, float v, Gate gate = Gate{nullptr, 0}) {
+__global__ void k_fill_f32(float* p, int64_t n, float v, Gate gate) {
   if (gate_closed(gate)) return;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
-}
-__global__ void k_fill_f64(double* p, int64_t n, double v) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
@@ -30,19 +27,44 @@ __global__ void k_fill_f64(double* p, int64_t n, double v) {
 // multiple of 4), else one.  Reads 2 rows per token and is bound by the latency of a wavefront's chain of loads:
 // element by element it took 33 us for 777 tokens at d = 4096 (64 loads in a row per lane) and 82 us for 32768 at
 // d = 2048, by 16-byte loads 8.5 and 42 us.
+//
+// It also prepares the other per-token arrays of a loss call, where those are given: coef[t] = 0 (a token that malformed
+// offsets leave out keeps it); for the single sweep the reference exponent ref2[t] of k_sweep, and "no contribution yet"
+// for a row that is not swept: diff[t] = 0, nis[t] = 0.  The reference is the largest logit among a sample of the row (its
+// first 256 vocabulary entries, whose running maximum `sample` carries in .x, and the sampled token's own logit) plus a
+// margin, in the exp2 domain.  Some entry of the row then equals 2^-margin, so S_t >= 2^-margin, and entries down to
+// 2^-(126 - margin) of the row's largest stay normal bf16 numbers.
+constexpr float kSweepMargin = 40.f;
+constexpr float kSweepLimit = 1.2676506e30f;   // 2^100: largest S_t the single sweep accepts
+struct TokenInit {
+  float* coef;            // or nullptr
+  const float2* sample;   // or nullptr: no single sweep
+  float* ref2;
+  double* diff;
+  float* nis;
+};
 template <class T, class ACC, int VEC>
 __global__ void __launch_bounds__(256)
 k_gather_logit(const T* __restrict__ H, const T* __restrict__ W, const int32_t* __restrict__ tokens,
-               int64_t Ttok, int d, int V, float* __restrict__ zy, int* __restrict__ err) {
+               int64_t Ttok, int d, int V, float* __restrict__ zy, int* __restrict__ err, TokenInit init) {
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
   const int lane = threadIdx.x & 63;
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= Ttok) return;
   const int y = tokens[t];
+  auto finish = [&](float z) {
+    zy[t] = z;
+    if (init.coef) init.coef[t] = 0.f;
+    if (init.sample) {
+      init.ref2[t] = fmaxf(init.sample[t].x, z * kLog2e) + kSweepMargin;    // fmaxf drops a NaN (token out of range)
+      init.diff[t] = 0.0;
+      init.nis[t] = 0.f;
+    }
+  };
   if (y < 0 || y >= V) {
     if (lane == 0) {
-      record_error(err, kErrTokenRange);
-      zy[t] = __builtin_nanf("");
+      record_token_error(err);
+      finish(__builtin_nanf(""));
     }
     return;
   }
@@ -56,7 +78,7 @@ k_gather_logit(const T* __restrict__ H, const T* __restrict__ W, const int32_t* 
     for (int e = 0; e < VEC; ++e) acc += (ACC)to_f32((T)a[e]) * (ACC)to_f32((T)b[e]);
   }
   acc = wave_sum(acc);
-  if (lane == 0) zy[t] = (float)acc;
+  if (lane == 0) finish((float)acc);
 }
 
 // Merges the per-split soft-max partials of each token and finishes
@@ -133,7 +155,8 @@ k_lse_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, con
 // in k_lse_finish.
 __global__ void __launch_bounds__(256)
 k_sample_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, int32_t* __restrict__ tokens_out,
-                float* __restrict__ score_out, int slices) {
+                float* __restrict__ score_out, int slices, int* __restrict__ status) {
+  if (blockIdx.x == 0 && threadIdx.x < kStatusWords) status[threadIdx.x] = 0;   // nothing in a sampling call can set one
   __shared__ float2 part[256];
   const int rows = 256 / slices, col = threadIdx.x % rows, slice = threadIdx.x / rows;
   const int64_t t = (int64_t)blockIdx.x * rows + col;
@@ -157,32 +180,52 @@ k_sample_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, 
   if (score_out) score_out[t] = best;
 }
 
+// Sum over the 256 threads of a workgroup, valid in every thread: wavefront shuffles, then the 4 wave totals in order.
+__device__ __forceinline__ double block_sum(double v) {
+  __shared__ double wsum[4];
+  v = wave_sum(v);
+  __syncthreads();      // wsum may still be read for an earlier sum
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
+}
+
+// Token range of rollout s, clamped to [0, limit] so that malformed offsets cannot reach past a buffer.
+__device__ __forceinline__ void token_range(const int64_t* off, int s, int64_t limit, int64_t& a, int64_t& b) {
+  a = off[s];
+  b = off[s + 1];
+  a = a < 0 ? 0 : (a > limit ? limit : a);
+  b = b < a ? a : (b > limit ? limit : b);
+}
+
+// The last of `n` workgroups to get here returns true and sees what the others wrote before (their plain stores too).
+// The counter is back at zero afterwards.
+__device__ __forceinline__ bool last_workgroup(int* counter, int n) {
+  __shared__ int last;
+  __threadfence();
+  __syncthreads();
+  if (threadIdx.x == 0) last = atomicInc((unsigned*)counter, (unsigned)(n - 1)) == (unsigned)(n - 1);
+  __syncthreads();
+  if (last) __threadfence();
+  return last != 0;
+}
+
 // out[s] = sum_{t in [off[s], off[s+1])} x[t] in double: one workgroup per
-// rollout, each thread a strided partial in a fixed order, wavefront shuffle
-// reduction, then the 4 wave totals in order.  Bit-reproducible.  Offsets are
-// clamped to [0, limit] (limit < 0: only to a >= 0, b >= a) so malformed input
-// cannot read below the buffer or, with a limit, past it.
+// rollout, each thread a strided partial in a fixed order, then block_sum.
+// Bit-reproducible.  Offsets are clamped to a >= 0, b >= a, so malformed input
+// cannot read below the buffer.
 template <class T>
 __global__ void __launch_bounds__(256)
-k_segmented_sum(const T* __restrict__ x, const int64_t* __restrict__ off, int n_seq, int64_t limit,
-                double* __restrict__ out, Gate gate = Gate{nullptr, 0}) {
-  __shared__ double wsum[4];
-  if (gate_closed(gate)) return;
+k_segmented_sum(const T* __restrict__ x, const int64_t* __restrict__ off, int n_seq, double* __restrict__ out) {
   const int s = blockIdx.x;
   if (s >= n_seq) return;
   int64_t a = off[s], b = off[s + 1];
   a = a < 0 ? 0 : a;
   b = b < a ? a : b;
-  if (limit >= 0) {
-    a = a > limit ? limit : a;
-    b = b > limit ? limit : b;
-  }
   double acc = 0.0;
   for (int64_t t = a + threadIdx.x; t < b; t += 256) acc += (double)x[t];
-  acc = wave_sum(acc);
-  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) out[s] = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
+  acc = block_sum(acc);
+  if (threadIdx.x == 0) out[s] = acc;
 }
 
 // Butterfly reductions over a wavefront: every lane ends with the same value, combined in a
@@ -203,120 +246,80 @@ __device__ __forceinline__ int wave_allsum(int v) {
   return v;
 }
 
-// Group value estimate, one wavefront per prompt (4 prompts per workgroup):
+// ---------------------------------------------------------------------------
+// What a loss call does before anything is scored.  Each step is a function of (worker, workers): one workgroup takes them
+// all in one launch where rollouts and prompts are few (a launch costs a small call 2 .. 4 us), else each has a grid.
+// ---------------------------------------------------------------------------
+
+// Group value estimate, one wavefront per prompt:
 //   V*_g = beta_v ln( (1/G_g) sum_{s in g} exp(r_s / beta_v) )            Eq. 2
 //        = m_g + beta_v ln( (1/G_g) sum exp((r_s - m_g) / beta_v) ),  m_g = max_{s in g} r_s
 // (same value; the shift keeps exp() in range for small beta and makes all-equal rewards return
 // exactly r).  Group ids come in any order, so the wavefront walks the rollouts lane-strided and
 // keeps those of its prompt: lane-local partial max / count / sum in rollout order, then shuffle
 // butterflies.  A prompt without rollouts gets NaN and records the group error.
-__global__ void __launch_bounds__(256)
-k_group_value(const float* __restrict__ rewards, const int32_t* __restrict__ gid, int n_seq, int n_groups,
-              double beta_v, double* __restrict__ vstar_ws, float* __restrict__ vstar_out, int* __restrict__ err,
-              Gate gate) {
-  if (gate_closed(gate)) return;
+__device__ __forceinline__ void group_value(int wave, int waves, const float* __restrict__ rewards,
+                                            const int32_t* __restrict__ gid, int n_seq, int n_groups, double beta_v,
+                                            double* __restrict__ vstar_ws, float* __restrict__ vstar_out, int* err) {
   const int lane = threadIdx.x & 63;
-  const int g = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (g >= n_groups) return;
-  double m = -1.0e300;
-  int cnt = 0;
-  for (int s = lane; s < n_seq; s += 64)
-    if (gid[s] == g) { m = fmax(m, (double)rewards[s]); ++cnt; }
-  m = wave_allmax(m);
-  cnt = wave_allsum(cnt);
-  double v;
-  if (cnt == 0) {
-    if (lane == 0) record_batch_error(err, kErrGroup);
-    v = __builtin_nan("");
-  } else {
-    double sum = 0.0;
+  for (int g = wave; g < n_groups; g += waves) {
+    double m = -1.0e300;
+    int cnt = 0;
     for (int s = lane; s < n_seq; s += 64)
-      if (gid[s] == g) sum += exp(((double)rewards[s] - m) / beta_v);
-    sum = wave_allsum(sum);
-    v = m + beta_v * log(sum / (double)cnt);
-  }
-  if (lane == 0) {
-    vstar_ws[g] = v;
-    if (vstar_out) vstar_out[g] = (float)v;
-  }
-}
-
-// Residuals and loss (one workgroup walks the rollouts; fixed summation order):
-//   delta_s = beta_l Delta_s - (r_s - V*_{g(s)})
-//   loss    = scale sum_s delta_s^2                                           Eq. 3
-//   cseq_s  = scale 2 beta_l delta_s      (d loss / d ln pi(y_t) for every token of s)
-// Also validates offsets and group ids; on a violation (or an empty prompt found by
-// k_group_value, whose V* is NaN) the loss is NaN and the status word is set.
-__global__ void __launch_bounds__(256)
-k_residual_loss(const double* __restrict__ Delta, const float* __restrict__ rewards,
-                const int32_t* __restrict__ gid, const int64_t* __restrict__ off, int n_seq, int n_groups,
-                int64_t Ttok, double beta_l, double scale, const double* __restrict__ vstar_ws,
-                float* __restrict__ cseq, float* __restrict__ loss_out, float* __restrict__ seq_logratio_out,
-                int* __restrict__ err, Gate gate) {
-  __shared__ double wsum[4];
-  __shared__ int bad;
-  if (gate_closed(gate)) return;
-  const int tid = threadIdx.x;
-  if (tid == 0) bad = (off[0] != 0 || off[n_seq] != Ttok) ? kErrOffsets : 0;
-  __syncthreads();
-  double acc = 0.0;
-  for (int s = tid; s < n_seq; s += 256) {
-    if (off[s + 1] < off[s]) atomicCAS(&bad, 0, kErrOffsets);
-    const int g = gid[s];
-    const bool g_ok = g >= 0 && g < n_groups;
-    if (!g_ok) atomicCAS(&bad, 0, kErrGroup);
-    const double v = g_ok ? vstar_ws[g] : __builtin_nan("");
-    const double delta = beta_l * Delta[s] - ((double)rewards[s] - v);
-    cseq[s] = (float)(scale * 2.0 * beta_l * delta);
-    if (seq_logratio_out) seq_logratio_out[s] = (float)Delta[s];
-    acc += delta * delta;
-  }
-  acc = wave_sum(acc);
-  if ((tid & 63) == 0) wsum[tid >> 6] = acc;
-  __syncthreads();
-  if (tid == 0) {
-    double loss = scale * (((wsum[0] + wsum[1]) + wsum[2]) + wsum[3]);
-    if (bad) record_batch_error(err, bad);
-    if (batch_error(err)) loss = __builtin_nan("");
-    loss_out[0] = (float)loss;
+      if (gid[s] == g) { m = fmax(m, (double)rewards[s]); ++cnt; }
+    m = wave_allmax(m);
+    cnt = wave_allsum(cnt);
+    double v;
+    if (cnt == 0) {
+      if (lane == 0) record_batch_error(err, kErrGroup);
+      v = __builtin_nan("");
+    } else {
+      double sum = 0.0;
+      for (int s = lane; s < n_seq; s += 64)
+        if (gid[s] == g) sum += exp(((double)rewards[s] - m) / beta_v);
+      sum = wave_allsum(sum);
+      v = m + beta_v * log(sum / (double)cnt);
+    }
+    if (lane == 0) {
+      vstar_ws[g] = v;
+      if (vstar_out) vstar_out[g] = (float)v;
+    }
   }
 }
 
 // GRPO baseline (Sec. 2, the displayed GRPO objective), group step, one wavefront per prompt:
 // mean and population standard deviation of the prompt's rewards and its size G_g (kept behind
 // the per-rollout weights).  A prompt without rollouts gets NaN and records the group error.
-__global__ void __launch_bounds__(256)
-k_grpo_group_stats(const float* __restrict__ rewards, const int32_t* __restrict__ gid, int n_seq, int n_groups,
-                   double* __restrict__ gmean, double* __restrict__ gstd, double* __restrict__ gsize,
-                   int* __restrict__ err, Gate gate) {
-  if (gate_closed(gate)) return;
+__device__ __forceinline__ void grpo_group_stats(int wave, int waves, const float* __restrict__ rewards,
+                                                 const int32_t* __restrict__ gid, int n_seq, int n_groups,
+                                                 double* gmean, double* gstd, double* gsize, int* err) {
   const int lane = threadIdx.x & 63;
-  const int g = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (g >= n_groups) return;
-  double sum = 0.0;
-  int cnt = 0;
-  for (int s = lane; s < n_seq; s += 64)
-    if (gid[s] == g) { sum += (double)rewards[s]; ++cnt; }
-  sum = wave_allsum(sum);
-  cnt = wave_allsum(cnt);
-  if (cnt == 0) {
-    if (lane == 0) {
-      record_batch_error(err, kErrGroup);
-      gmean[g] = __builtin_nan("");
-      gstd[g] = __builtin_nan("");
-      gsize[g] = 0.0;
+  for (int g = wave; g < n_groups; g += waves) {
+    double sum = 0.0;
+    int cnt = 0;
+    for (int s = lane; s < n_seq; s += 64)
+      if (gid[s] == g) { sum += (double)rewards[s]; ++cnt; }
+    sum = wave_allsum(sum);
+    cnt = wave_allsum(cnt);
+    if (cnt == 0) {
+      if (lane == 0) {
+        record_batch_error(err, kErrGroup);
+        gmean[g] = __builtin_nan("");
+        gstd[g] = __builtin_nan("");
+        gsize[g] = 0.0;
+      }
+      continue;
     }
-    return;
-  }
-  const double mean = sum / cnt;
-  double var = 0.0;
-  for (int s = lane; s < n_seq; s += 64)
-    if (gid[s] == g) { const double dlt = (double)rewards[s] - mean; var += dlt * dlt; }
-  var = wave_allsum(var);
-  if (lane == 0) {
-    gmean[g] = mean;
-    gstd[g] = sqrt(var / cnt);
-    gsize[g] = (double)cnt;
+    const double mean = sum / cnt;
+    double var = 0.0;
+    for (int s = lane; s < n_seq; s += 64)
+      if (gid[s] == g) { const double dlt = (double)rewards[s] - mean; var += dlt * dlt; }
+    var = wave_allsum(var);
+    if (lane == 0) {
+      gmean[g] = mean;
+      gstd[g] = sqrt(var / cnt);
+      gsize[g] = (double)cnt;
+    }
   }
 }
 
@@ -324,15 +327,14 @@ k_grpo_group_stats(const float* __restrict__ rewards, const int32_t* __restrict_
 //   A_s = (r_s - mean_g r) / (std_g r + adv_eps)
 // and the weight w_s = scale / (G_g |y_s|) of rollout s (0 for an empty rollout).  Validates
 // offsets and group ids like the OAPL kernel and records the status.
-__global__ void __launch_bounds__(256)
-k_grpo_advantage(const float* __restrict__ rewards, const int32_t* __restrict__ gid, const int64_t* __restrict__ off,
-                 int n_seq, int n_groups, int64_t Ttok, double adv_eps, double scale,
-                 const double* __restrict__ gmean, const double* __restrict__ gstd, const double* __restrict__ gsize,
-                 float* __restrict__ adv, double* __restrict__ wseq, float* __restrict__ adv_out,
-                 int* __restrict__ err, Gate gate) {
-  if (gate_closed(gate)) return;
-  if (blockIdx.x == 0 && threadIdx.x == 0 && (off[0] != 0 || off[n_seq] != Ttok)) record_batch_error(err, kErrOffsets);
-  for (int s = blockIdx.x * 256 + threadIdx.x; s < n_seq; s += gridDim.x * 256) {
+__device__ __forceinline__ void grpo_advantage(int thread, int threads, const float* __restrict__ rewards,
+                                               const int32_t* __restrict__ gid, const int64_t* __restrict__ off,
+                                               int n_seq, int n_groups, int64_t Ttok, double adv_eps, double scale,
+                                               const double* gmean, const double* gstd, const double* gsize,
+                                               float* __restrict__ adv, double* __restrict__ wseq,
+                                               float* __restrict__ adv_out, int* err) {
+  if (thread == 0 && (off[0] != 0 || off[n_seq] != Ttok)) record_batch_error(err, kErrOffsets);
+  for (int s = thread; s < n_seq; s += threads) {
     if (off[s + 1] < off[s]) record_batch_error(err, kErrOffsets);
     const int g = gid[s];
     const bool ok = g >= 0 && g < n_groups;
@@ -345,104 +347,167 @@ k_grpo_advantage(const float* __restrict__ rewards, const int32_t* __restrict__ 
   }
 }
 
-// GRPO, token step: one workgroup per rollout.  With r_t = pi / pi_old and IS_t = pi_old / pi_vllm,
-//   term_t = IS_t min(r_t A, clip(r_t, 1 - eps, 1 + eps) A),   d term_t / d ln pi(y_t) = IS_t r_t A if unclipped else 0,
-// it writes the loss gradient coefficient c_t = -w_s d term_t (times factor[t] if given) and the
-// rollout's loss share -w_s sum_t term_t (double, fixed order).  lp comes as diff = lp - logq in double.
-__global__ void __launch_bounds__(256)
-k_grpo_tokens(const double* __restrict__ diff, const float* __restrict__ logq, const float* __restrict__ logp_old,
-              const int64_t* __restrict__ off, int n_seq, int64_t Ttok, const float* __restrict__ adv,
-              const double* __restrict__ wseq, double clip_eps, const float* __restrict__ factor,
-              float* __restrict__ coef, double* __restrict__ seqterm, Gate gate) {
-  __shared__ double wsum[4];
-  if (gate_closed(gate)) return;
-  const int s = blockIdx.x;
-  if (s >= n_seq) return;
-  int64_t a = off[s], b = off[s + 1];
-  a = a < 0 ? 0 : (a > Ttok ? Ttok : a);
-  b = b < a ? a : (b > Ttok ? Ttok : b);
-  const double A = (double)adv[s], w = wseq[s];
-  double acc = 0.0;
-  for (int64_t t = a + threadIdx.x; t < b; t += 256) {
-    const double q = (double)logq[t], lo = (double)logp_old[t];
-    const double lp = diff[t] + q;
-    const double r = exp(lp - lo), is = exp(lo - q);
-    const double unclipped = r * A;
-    const double rc = r < 1.0 - clip_eps ? 1.0 - clip_eps : (r > 1.0 + clip_eps ? 1.0 + clip_eps : r);
-    const double clipped = rc * A;
-    acc += is * (unclipped <= clipped ? unclipped : clipped);
-    const double g = unclipped <= clipped ? -w * is * unclipped : 0.0;
-    coef[t] = (float)(factor ? g * (double)factor[t] : g);
-  }
-  acc = wave_sum(acc);
-  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) seqterm[s] = -w * (((wsum[0] + wsum[1]) + wsum[2]) + wsum[3]);
-}
-
-// loss = sum_s seqterm[s] (one workgroup, fixed order), NaN if an offsets / group error was recorded.
-__global__ void __launch_bounds__(256)
-k_grpo_loss(const double* __restrict__ seqterm, int n_seq, const int* __restrict__ err,
-            float* __restrict__ loss_out, Gate gate) {
-  __shared__ double wsum[4];
-  if (gate_closed(gate)) return;
-  double acc = 0.0;
-  for (int s = threadIdx.x; s < n_seq; s += 256) acc += seqterm[s];
-  acc = wave_sum(acc);
-  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double loss = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
-    if (batch_error(err)) loss = __builtin_nan("");
-    loss_out[0] = (float)loss;
-  }
-}
-
-// coef[t] = cseq[s(t)] (times factor[t] if given): one workgroup per rollout
-// writes its token range (clamped to [0, T], so malformed offsets cannot write
-// out of bounds).
-__global__ void __launch_bounds__(256)
-k_token_coefficients(const float* __restrict__ cseq, const int64_t* __restrict__ off, int n_seq, int64_t Ttok,
-                     const float* __restrict__ factor, float* __restrict__ coef, Gate gate) {
-  if (gate_closed(gate)) return;
-  const int s = blockIdx.x;
-  if (s >= n_seq) return;
-  int64_t a = off[s], b = off[s + 1];
-  a = a < 0 ? 0 : (a > Ttok ? Ttok : a);
-  b = b < a ? a : (b > Ttok ? Ttok : b);
-  const float c = cseq[s];
-  for (int64_t t = a + threadIdx.x; t < b; t += 256) coef[t] = factor ? c * factor[t] : c;
-}
-
-// ---------------------------------------------------------------------------
-// Helpers of the single-sweep loss path (see k_sweep).
-// ---------------------------------------------------------------------------
-
 // The single-sweep path finishes a panel of token rows before it knows the later panels, so a
-// rollout must end at most one panel after it starts: any rollout longer than `panel_rows`
+// rollout must end at most one panel after it starts: any rollout longer than `longest`
 // (or malformed offsets) raises the flag that sends the call down the two-pass path instead.
-__global__ void __launch_bounds__(256)
-k_sweep_plan(const int64_t* __restrict__ off, int n_seq, int64_t Ttok, int64_t panel_rows, int* __restrict__ flag) {
-  bool bad = threadIdx.x == 0 && blockIdx.x == 0 && (off[0] != 0 || off[n_seq] != Ttok);
-  for (int s = blockIdx.x * 256 + threadIdx.x; s < n_seq; s += gridDim.x * 256) {
+// longest < 0: the call does not try the single sweep.
+__device__ __forceinline__ void sweep_plan(int thread, int threads, const int64_t* __restrict__ off, int n_seq,
+                                           int64_t Ttok, int64_t longest, int* flag) {
+  if (longest < 0) return;
+  bool bad = thread == 0 && (off[0] != 0 || off[n_seq] != Ttok);
+  for (int s = thread; s < n_seq; s += threads) {
     const int64_t len = off[s + 1] - off[s];
-    bad |= len < 0 || len > panel_rows;
+    bad |= len < 0 || len > longest;
   }
   if (bad) atomicCAS(flag, 0, 1);
 }
 
-// Reference exponent of a token row for k_sweep: the largest logit among a sample of the row
-// (the first vocabulary tile, whose running maximum `sample` carries in .x, and the sampled
-// token's own logit) plus a margin, in the exp2 domain.  Some entry of the row then equals
-// 2^-margin, so S_t >= 2^-margin, and entries down to 2^-(126 - margin) of the row's largest
-// stay normal bf16 numbers.
-constexpr float kSweepMargin = 40.f;
-constexpr float kSweepLimit = 1.2676506e30f;   // 2^100: largest S_t the single sweep accepts
+// Clears the status header; every later use of it by this workgroup comes after the clear.
+__device__ __forceinline__ void clear_status(int* status) {
+  if (threadIdx.x < kStatusWords) __hip_atomic_store(status + threadIdx.x, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __threadfence();
+  __syncthreads();
+}
+
+// `all`: one workgroup does everything, status header included; else a grid after a launch that cleared the header.
 __global__ void __launch_bounds__(256)
-k_sweep_ref(const float2* __restrict__ sample, const float* __restrict__ zy, int64_t Ttok, float* __restrict__ ref2) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= Ttok) return;
-  ref2[t] = fmaxf(sample[t].x, zy[t] * kLog2e) + kSweepMargin;    // fmaxf drops a NaN zy (token out of range)
+k_oapl_begin(const float* __restrict__ rewards, const int32_t* __restrict__ gid, const int64_t* __restrict__ off, int n_seq,
+             int n_groups, int64_t Ttok, int64_t longest, double beta_v, double* __restrict__ vstar_ws,
+             float* __restrict__ vstar_out, int* status, int all) {
+  if (all) clear_status(status);
+  sweep_plan(blockIdx.x * 256 + threadIdx.x, gridDim.x * 256, off, n_seq, Ttok, longest, status + kFlagWord);
+  group_value(blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, rewards, gid, n_seq, n_groups, beta_v, vstar_ws, vstar_out,
+              status);
+}
+
+// Steps: 1 = plan and group statistics, 2 = advantages, 3 = both (one workgroup, status header included).
+__global__ void __launch_bounds__(256)
+k_grpo_begin(const float* __restrict__ rewards, const int32_t* __restrict__ gid, const int64_t* __restrict__ off, int n_seq,
+             int n_groups, int64_t Ttok, int64_t longest, double adv_eps, double scale, double* gmean, double* gstd,
+             double* gsize, float* __restrict__ adv, double* __restrict__ wseq, float* __restrict__ adv_out, int* status,
+             int steps) {
+  if (steps == 3) clear_status(status);
+  if (steps & 1) {
+    sweep_plan(blockIdx.x * 256 + threadIdx.x, gridDim.x * 256, off, n_seq, Ttok, longest, status + kFlagWord);
+    grpo_group_stats(blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, rewards, gid, n_seq, n_groups, gmean, gstd, gsize,
+                     status);
+  }
+  if (steps == 3) {
+    __threadfence();
+    __syncthreads();
+  }
+  if (steps & 2)
+    grpo_advantage(blockIdx.x * 256 + threadIdx.x, gridDim.x * 256, rewards, gid, off, n_seq, n_groups, Ttok, adv_eps, scale,
+                   gmean, gstd, gsize, adv, wseq, adv_out, status);
+}
+
+// ---------------------------------------------------------------------------
+// The objective, from diff = logprob - logq: one workgroup per rollout (at least one), the loss by the last to finish.
+// It may run any number of times in a call; rows not scored yet have diff = 0.
+// ---------------------------------------------------------------------------
+
+// The factor that goes into a token's coefficient: `fast` unless the call's flag says that the two-pass schedule served
+// it, then `slow`; either may be nullptr (no factor), and so may `flag` (fast).
+struct TokenFactor {
+  const float *fast, *slow;
+  const int* flag;
+};
+__device__ __forceinline__ const float* token_factor(const TokenFactor f) {
+  return f.flag != nullptr && *f.flag != 0 ? f.slow : f.fast;
+}
+
+// Steps a4, a6, a7: per rollout
+//   Delta_s = sum_t diff[t]     (double, fixed order)
+//   delta_s = beta_l Delta_s - (r_s - V*_{g(s)})
+//   coef[t] = scale 2 beta_l delta_s (times the factor)      = d loss / d ln pi(y_t) for every token of s
+// and  loss = scale sum_s delta_s^2   (Eq. 3; one workgroup walks the rollouts, fixed summation order).
+// Also validates offsets and group ids; on a violation (or an empty prompt found by
+// group_value, whose V* is NaN) the loss is NaN and the status word is set.
+__global__ void __launch_bounds__(256)
+k_oapl_objective(const double* __restrict__ diff, const float* __restrict__ rewards, const int32_t* __restrict__ gid,
+                 const int64_t* __restrict__ off, int n_seq, int n_groups, int64_t Ttok, double beta_l, double scale,
+                 const double* __restrict__ vstar_ws, TokenFactor factors, double* Delta, float* __restrict__ coef,
+                 float* __restrict__ loss_out, float* __restrict__ seq_logratio_out, int* status, Gate gate) {
+  __shared__ int bad;
+  if (gate_closed(gate)) return;
+  const int tid = threadIdx.x, s0 = blockIdx.x;
+  auto residual = [&](int s, double sum) {
+    const int g = gid[s];
+    const double v = g >= 0 && g < n_groups ? vstar_ws[g] : __builtin_nan("");
+    return beta_l * sum - ((double)rewards[s] - v);
+  };
+  if (s0 < n_seq) {
+    int64_t a, b;
+    token_range(off, s0, Ttok, a, b);
+    double acc = 0.0;
+    for (int64_t t = a + tid; t < b; t += 256) acc += diff[t];
+    acc = block_sum(acc);
+    if (coef) {
+      const float* factor = token_factor(factors);
+      const float c = (float)(scale * 2.0 * beta_l * residual(s0, acc));
+      for (int64_t t = a + tid; t < b; t += 256) coef[t] = factor ? c * factor[t] : c;
+    }
+    if (tid == 0) {
+      __hip_atomic_store(Delta + s0, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (seq_logratio_out) seq_logratio_out[s0] = (float)acc;
+    }
+  }
+  if (!last_workgroup(status + kCounterWord, gridDim.x)) return;
+  if (tid == 0) bad = (off[0] != 0 || off[n_seq] != Ttok) ? kErrOffsets : 0;
+  __syncthreads();
+  double acc = 0.0;
+  for (int s = tid; s < n_seq; s += 256) {
+    if (off[s + 1] < off[s]) atomicCAS(&bad, 0, kErrOffsets);
+    if (gid[s] < 0 || gid[s] >= n_groups) atomicCAS(&bad, 0, kErrGroup);
+    const double delta = residual(s, __hip_atomic_load(Delta + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    acc += delta * delta;
+  }
+  acc = block_sum(acc);
+  if (tid == 0) {
+    double loss = scale * acc;
+    if (bad) record_batch_error(status, bad);
+    if (batch_error(status)) loss = __builtin_nan("");
+    loss_out[0] = (float)loss;
+  }
+}
+
+// GRPO, token step.  With r_t = pi / pi_old and IS_t = pi_old / pi_vllm,
+//   term_t = IS_t min(r_t A, clip(r_t, 1 - eps, 1 + eps) A),   d term_t / d ln pi(y_t) = IS_t r_t A if unclipped else 0,
+// it writes the loss gradient coefficient c_t = -w_s d term_t (times the factor) and the rollout's
+// loss share -w_s sum_t term_t (double, fixed order); loss = sum of the shares, NaN if an offsets / group error was
+// recorded.  lp comes as diff = lp - logq in double.
+__global__ void __launch_bounds__(256)
+k_grpo_objective(const double* __restrict__ diff, const float* __restrict__ logq, const float* __restrict__ logp_old,
+                 const int64_t* __restrict__ off, int n_seq, int64_t Ttok, const float* __restrict__ adv,
+                 const double* __restrict__ wseq, double clip_eps, TokenFactor factors, float* __restrict__ coef,
+                 double* seqterm, float* __restrict__ loss_out, int* status, Gate gate) {
+  if (gate_closed(gate)) return;
+  const int tid = threadIdx.x, s0 = blockIdx.x;
+  if (s0 < n_seq) {
+    int64_t a, b;
+    token_range(off, s0, Ttok, a, b);
+    const float* factor = token_factor(factors);
+    const double A = (double)adv[s0], w = wseq[s0];
+    double acc = 0.0;
+    for (int64_t t = a + tid; t < b; t += 256) {
+      const double q = (double)logq[t], lo = (double)logp_old[t];
+      const double lp = diff[t] + q;
+      const double r = exp(lp - lo), is = exp(lo - q);
+      const double unclipped = r * A;
+      const double rc = r < 1.0 - clip_eps ? 1.0 - clip_eps : (r > 1.0 + clip_eps ? 1.0 + clip_eps : r);
+      const double clipped = rc * A;
+      acc += is * (unclipped <= clipped ? unclipped : clipped);
+      const double g = unclipped <= clipped ? -w * is * unclipped : 0.0;
+      if (coef) coef[t] = (float)(factor ? g * (double)factor[t] : g);
+    }
+    acc = block_sum(acc);
+    if (tid == 0) __hip_atomic_store(seqterm + s0, -w * acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (!last_workgroup(status + kCounterWord, gridDim.x)) return;
+  double acc = 0.0;
+  for (int s = tid; s < n_seq; s += 256) acc += __hip_atomic_load(seqterm + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  acc = block_sum(acc);
+  if (tid == 0) loss_out[0] = batch_error(status) ? __builtin_nanf("") : (float)acc;
 }
 
 // Finishes one panel of the single sweep.  Per token row (panel-local index n, global t0 + n):
