@@ -44,7 +44,8 @@
 namespace oapl {
 
 
-template <int WM_, int WN_, int TM_, int TN_, int NS_>
+// PACK_B_: rows per block of the n-side operands where they are packed (0: one tile), a multiple of the tile's.
+template <int WM_, int WN_, int TM_, int TN_, int NS_, int PACK_B_ = 0>
 struct TileCfg {
   static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_;
   static constexpr int NW = WM * WN;            // waves per workgroup
@@ -57,6 +58,9 @@ struct TileCfg {
   static constexpr int ROW_BYTES = kPackRowBytes;
   static constexpr int STAGE_A = BM * ROW_BYTES;   // one stage of the m-side operand
   static constexpr int STAGE_B = BN * ROW_BYTES;   // ... of the n-side operand
+  static constexpr int PACK_A = kPackRowsA, PACK_B = PACK_B_ ? PACK_B_ : BN;
+  static constexpr int PITCH_A = PACK_A * ROW_BYTES, PITCH_B = PACK_B * ROW_BYTES;   // bytes of one packed block
+  static_assert(PACK_A % BM == 0 && PACK_B % BN == 0, "a tile lies in one block");
   static constexpr int SLOT = STAGE_A + STAGE_B;   // one ring slot: the m-side block, then the n-side block
   static constexpr int MAIN_BYTES = NS * (STAGE_A + STAGE_B);
   static constexpr int NI_A = BM / (8 * NW);    // direct loads per wave and stage (8 rows each), m-side operand
@@ -130,7 +134,7 @@ struct Mainloop {
   int istep;                          // ROWS: bytes from one load of a wave to the next (8 * NW rows)
   const char* at_base;                // ATR: the tile's first column in row 0 of the matrix
   int64_t at_rows;                    // ... rows (k) from there
-  int at_ld2, at_m0, at_voff;         // ... bytes per row, first column, per-lane byte offset in the first 16 rows of a k-block
+  int at_ld2, at_m0, at_voff;         // ... bytes per row, first column, per-lane byte offset of a wave's first load of a k-block
   // LDS byte offsets of this lane's operand fragments at k-step 0 of ring slot 0.  K-step ks sits at the
   // same offset with address bits 5..6 flipped by ks (the swizzle is an XOR on the 16-byte chunk index and
   // the k-step is bits 1..2 of that index); deriving it where it is used costs one XOR per operand and
@@ -162,17 +166,19 @@ struct Mainloop {
   }
 
   // ATR only: the m-side operand of column tile mt in a row-major matrix of R rows of `ld` elements (after setup()).
-  // Chunk c (16 bytes, 32 per row) of LDS row k lives at chunk c ^ ((k & 3) << 2): the four rows and the two halves of
+  // Chunk c (16 bytes, BM / 8 per row) of LDS row k lives at chunk c ^ ((k & 3) << 2): the four rows and the two halves of
   // 32 lanes' transposing read then lie on 64 different banks.
   __device__ __forceinline__ void set_a_transposed(const bf16_t* p, int mt, int64_t R, int ld) {
-    static_assert(!ATR || C::BM == 256, "a k-row of the tile is 512 bytes");
+    // one wave-wide load covers RPL rows of LPR lanes; load i of a wave is NW * RPL rows further on
+    constexpr int LPR = C::BM / 8, RPL = 64 / LPR;
+    static_assert(!ATR || (C::NW * RPL) % 4 == 0, "swizzle must repeat from one load of a wave to the next");
+    static_assert(!ATR || C::NI_A * C::NW * RPL == C::BK, "the loads cover the block");
     at_base = (const char*)(p + mt * C::BM);
     at_rows = R;
     at_ld2 = ld * 2;
     at_m0 = mt * C::BM;
-    const int row = wave * 2 + (lane >> 5);       // one wave-wide load covers 2 rows; load i of a wave 2 * NW rows on
-    static_assert((2 * C::NW) % 4 == 0, "swizzle must repeat from one load of a wave to the next");
-    at_voff = row * at_ld2 + (((lane & 31) ^ ((row & 3) << 2)) << 4);
+    const int row = wave * RPL + lane / LPR;
+    at_voff = row * at_ld2 + (((lane % LPR) ^ ((row & 3) << 2)) << 4);
     const int e = (lane >> 2) & 3, a = lane & 3, g = lane >> 4, wm = wave / C::WN;
     const int k = 8 * (g >> 1) + e;
     const int chunk = wm * C::TM * 4 + 2 * (g & 1) + (a >> 1);   // m / 8 of fragment 0
@@ -197,20 +203,24 @@ struct Mainloop {
   __device__ __forceinline__ void set_a(const bf16_t* p, int64_t rt, int64_t R, int ld, int n_kt) {
     const int64_t left = R - rt * C::BM;
     if (ROWS) ra = __builtin_amdgcn_make_buffer_rsrc((void*)(p + rt * C::BM * ld), 0, (int)(left < C::BM ? left : C::BM) * ld * 2, 0x00020000);
-    else set_a(p + rt * n_kt * (C::STAGE_A / 2), n_kt);
+    else set_a_packed(p, rt * C::BM, n_kt, 0);
   }
   __device__ __forceinline__ void set_b(const bf16_t* p, int64_t rt, int64_t R, int ld, int n_kt) {
     const int64_t left = R - rt * C::BN;
     if (ROWS) rb = __builtin_amdgcn_make_buffer_rsrc((void*)(p + rt * C::BN * ld), 0, (int)(left < C::BN ? left : C::BN) * ld * 2, 0x00020000);
-    else set_b(p + rt * n_kt * (C::STAGE_B / 2), n_kt);
+    else set_b_packed(p, rt * C::BN, n_kt, 0);
   }
 
-  // Operand = one row-tile strip of a packed matrix: n_kt consecutive blocks of 32 KiB (A) / 48 KiB (B).
-  __device__ __forceinline__ void set_a(const bf16_t* strip, int n_kt) {
-    ra = __builtin_amdgcn_make_buffer_rsrc((void*)strip, 0, n_kt * C::STAGE_A, 0x00020000);
+  // Operand = rows row0 .. of a packed matrix with n_kt k-blocks per strip, from k-block k0 on.
+  __device__ __forceinline__ void set_a_packed(const bf16_t* p, int64_t row0, int n_kt, int k0) {
+    const int in_block = (int)(row0 % C::PACK_A) * C::ROW_BYTES;
+    ra = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)p + (row0 / C::PACK_A * n_kt + k0) * C::PITCH_A + in_block), 0,
+                                           (n_kt - k0) * C::PITCH_A - in_block, 0x00020000);
   }
-  __device__ __forceinline__ void set_b(const bf16_t* strip, int n_kt) {
-    rb = __builtin_amdgcn_make_buffer_rsrc((void*)strip, 0, n_kt * C::STAGE_B, 0x00020000);
+  __device__ __forceinline__ void set_b_packed(const bf16_t* p, int64_t row0, int n_kt, int k0) {
+    const int in_block = (int)(row0 % C::PACK_B) * C::ROW_BYTES;
+    rb = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)p + (row0 / C::PACK_B * n_kt + k0) * C::PITCH_B + in_block), 0,
+                                           (n_kt - k0) * C::PITCH_B - in_block, 0x00020000);
   }
 
   // Starts the direct-to-LDS loads of k-block kt into ring slot STAGE (a literal at the call sites,
@@ -228,18 +238,18 @@ struct Mainloop {
 #pragma unroll
       for (int i = 0; i < C::NI_A; ++i)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_ptr)(smem + STAGE * C::SLOT + (i * C::NW + wave) * 1024), 16,
-                                                 at_voff + i * 2 * C::NW * at_ld2, 0, 0, 0);
+                                                 at_voff + i * (C::NW * 64 / (C::BM / 8)) * at_ld2, 0, 0, 0);
     }
 #pragma unroll
     for (int i = 0; i < (ATR ? 0 : C::NI_A); ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           ra, (lds_void_ptr)(smem + STAGE * C::SLOT + (i * C::NW + wave) * 1024), 16, ROWS ? v + i * istep : v,
-          ROWS ? kt * C::ROW_BYTES : kt * C::STAGE_A + i * C::NW * 1024, 0, 0);
+          ROWS ? kt * C::ROW_BYTES : kt * C::PITCH_A + i * C::NW * 1024, 0, 0);
 #pragma unroll
     for (int i = 0; i < C::NI_B; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           rb, (lds_void_ptr)(smem + STAGE * C::SLOT + C::STAGE_A + (i * C::NW + wave) * 1024), 16, ROWS ? v + i * istep : v,
-          ROWS ? kt * C::ROW_BYTES : kt * C::STAGE_B + i * C::NW * 1024, 0, 0);
+          ROWS ? kt * C::ROW_BYTES : kt * C::PITCH_B + i * C::NW * 1024, 0, 0);
   }
 
   __device__ __forceinline__ void compute(const int STAGE, lds_char_ptr smem, f32x16 (&acc)[C::TM][C::TN]) {
@@ -504,15 +514,17 @@ __device__ __forceinline__ void quad_transpose(V4 (&p)[4]) {
 // request over the kernel, where a request can carry 64).  So the four lanes of a quad, which hold four
 // neighbouring rows, transpose their pieces first: lane q then holds piece q of each of the four
 // rows, and every store instruction writes whole lines, 8 lanes per line (+2.7 % on the sweep).
-// Destroys pk.  `strip` is block (n-tile, 0) of the destination, kb0 the first k-block (m0 / 64).
+// Destroys pk.  `dst` is the destination matrix, n_kt its strip pitch in k-blocks, n0 the tile's first row, kb0 the first
+// k-block (m0 / 64).
 template <class C>
-__device__ __forceinline__ void store_nm_packed_direct(uint32_t (&pk)[C::TM][C::TN][8], bf16_t* strip, int kb0) {
+__device__ __forceinline__ void store_nm_packed_direct(uint32_t (&pk)[C::TM][C::TN][8], bf16_t* dst, int n_kt, int64_t n0, int kb0) {
   static_assert(C::TM == 2 && C::TM * 32 == kPackK, "a wave row spans exactly one packed k-block: 4 pieces of 16 bytes per lane");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / C::WN, wn = wave % C::WN;
   const int h = lane >> 5, q = lane & 3;
   // piece q of a row sits at byte (q >> 1) * 64 + 32 h + 16 (q & 1) of its 128-byte line
-  char* base = (char*)strip + (int64_t)(kb0 + wm) * C::STAGE_B + (q >> 1) * 64 + 32 * h + 16 * (q & 1);
+  char* base = (char*)dst + (n0 / C::PACK_B * n_kt + kb0 + wm) * C::PITCH_B + (n0 % C::PACK_B) * kPackRowBytes +
+               (q >> 1) * 64 + 32 * h + 16 * (q & 1);
 #pragma unroll
   for (int j = 0; j < C::TN; ++j) {
     u32x4 piece[4];
@@ -563,7 +575,7 @@ __device__ __forceinline__ void stage_mn_pk(lds_char_ptr smem, const uint32_t (&
 }
 
 // Chunk i staged by stage_mn_pk -> packed n-side matrix whose rows are the m index (global row
-// m0 + ..., blocks of BN rows) and whose k index is n; n_kt is the destination's strip pitch in
+// m0 + ..., blocks of PACK_B rows) and whose k index is n; n_kt is the destination's strip pitch in
 // k-blocks, kb0 the first k-block (n0 / 64).
 template <class C>
 __device__ __forceinline__ void store_mn_pk_packed(lds_char_ptr smem, bf16_t* base, int n_kt, int m0, int kb0, int i) {
@@ -571,9 +583,9 @@ __device__ __forceinline__ void store_mn_pk_packed(lds_char_ptr smem, bf16_t* ba
   for (int idx = threadIdx.x; idx < C::WM * 32 * CH; idx += C::NT) {
     const int m_l = idx / CH, ch = idx % CH;
     const int m = m0 + (m_l >> 5) * (C::TM * 32) + i * 32 + (m_l & 31);
-    const int blk = m / C::BN, r = m - blk * C::BN;
+    const int blk = m / C::PACK_B, r = m - blk * C::PACK_B;
     const u32x4 v = *(const __attribute__((address_space(3))) u32x4*)(smem + m_l * C::PITCH_MN + ch * 16);
-    char* dst = (char*)base + ((int64_t)blk * n_kt + kb0 + (ch >> 3)) * C::STAGE_B;
+    char* dst = (char*)base + ((int64_t)blk * n_kt + kb0 + (ch >> 3)) * C::PITCH_B;
     *(u32x4*)(dst + r * kPackRowBytes + (ch & 7) * 16) = v;
   }
 }
@@ -1075,7 +1087,7 @@ k_sweep(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H_panel, int V,
   }
   // Gp: rows = tokens (n), k = vocabulary (m), straight from the registers (last: it consumes pk,
   // and its stores drain after the workgroup has gone)
-  store_nm_packed_direct<C>(pk, Gp + (int64_t)nt * g_n_kt * (C::STAGE_B / 2), m0 / kPackK);
+  store_nm_packed_direct<C>(pk, Gp, g_n_kt, n0, m0 / kPackK);
 #endif
 }
 
@@ -1155,8 +1167,8 @@ k_bwd_dh(const bf16_t* __restrict__ W /* or W^T, packed */, int V, int wt_n_kt, 
   Mainloop<C, false, ATR> ml;
   ml.setup();
   if (ATR) ml.set_a_transposed(W + (int64_t)k0 * C::BK * d, mt, V - (int64_t)k0 * C::BK, d);
-  else ml.set_a(W + ((int64_t)mt * wt_n_kt + k0) * (C::STAGE_A / 2), wt_n_kt - k0);
-  ml.set_b(Gp + ((int64_t)nt * g_n_kt + k0) * (C::STAGE_B / 2), g_n_kt - k0);
+  else ml.set_a_packed(W, m0, wt_n_kt, k0);
+  ml.set_b_packed(Gp, n0, g_n_kt, k0);
 
   f32x16 acc[C::TM][C::TN];
   zero_acc<C>(acc);
@@ -1239,8 +1251,8 @@ k_bwd_dw(const bf16_t* __restrict__ HTp, const bf16_t* __restrict__ GTp, int t_n
 
   Mainloop<C> ml;
   ml.setup();
-  ml.set_a(HTp + (int64_t)mt * t_n_kt * (C::STAGE_A / 2), t_n_kt);
-  ml.set_b(GTp + (int64_t)nt * t_n_kt * (C::STAGE_B / 2), t_n_kt);
+  ml.set_a_packed(HTp, m0, t_n_kt, 0);
+  ml.set_b_packed(GTp, n0, t_n_kt, 0);
 
   f32x16 acc[C::TM][C::TN];
   zero_acc<C>(acc);

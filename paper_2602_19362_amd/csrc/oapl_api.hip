@@ -19,6 +19,9 @@ namespace oapl {
 // SIMD; operands in a ring of 2 LDS stages (160 KB, the whole LDS of a CU).
 typedef TileCfg<4, 2, 2, 6, 2> Cfg;
 static_assert(Cfg::BN == kPackRowsB, "n-side operands of the loss path are packed in blocks of one tile");
+// Where tiles of that size are too few to fill the chip (small heads and hidden sizes): 128 x 128, two workgroups per CU,
+// on the same packed blocks.
+typedef TileCfg<2, 2, 2, 2, 2, kPackRowsB> CfgSmall;
 // The sampling kernel carries a running (score, index) pair per column through the main loop and
 // draws Philox blocks in its epilogue: its largest tile is 256 x 256 (128 accumulators per lane),
 // with H packed in 256-row blocks for it where it reads packed operands.
@@ -49,11 +52,18 @@ struct TilePick {
 // sweep), never larger panels.
 constexpr int64_t kPanelBf16 = 12288;
 constexpr int64_t kPanelF32 = 4096;    // ... (fp32 path)
+constexpr size_t kPartDhBytes = (size_t)32 << 20;    // partial sums of dH that a plan may have whatever the size of W
 constexpr size_t kPartF32Bytes = (size_t)64 << 20;   // most partial results of an fp32 gradient contraction
 constexpr int64_t kGroupScanLimit = (int64_t)1 << 32;   // n_seq * n_groups: every prompt's wavefront walks all rollouts
 constexpr int kNumCU = 256;            // MI355X compute units (one workgroup of the dense kernels each: it fills the LDS)
 
 static inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
+
+// Tile of the last panel's dH contraction, and workgroups per tile.
+struct DhPick {
+  bool small = false;
+  int splits = 1;
+};
 
 // Tile and splits of k of an fp32 gradient contraction.
 struct F32Pick {
@@ -67,7 +77,9 @@ struct Plan {
   bool bwd = false;
   bool rows = false;   // the kernels read W and H where they lie; else packed copies (and one of W^T) are made
   TilePick fwd;        // tile and vocabulary splits of the scoring kernel (splits = soft-max partials per token)
-  int splits = 1;      // workgroups per tile of the last panel's dH contraction
+  bool small_sweep = false, small_dw = false;   // 128 x 128 tiles (one panel, operands in place)
+  int n_vt = 0;        // vocabulary tiles of the sweep: row sums per token
+  DhPick dh;           // the last panel's dH contraction
   TilePick smp;        // ... of the sampling kernel (splits = (score, index) partials per token)
   int64_t Tp = 0;      // rows of one backward panel
   F32Pick f32_dh, f32_dw;   // tile and splits of the fp32 gradient contractions (of the largest panel)
@@ -147,18 +159,48 @@ static TilePick pick_tile(int64_t T, int V, int max_splits, bool scoring) {
   return t384 <= t320 && t384 <= t256 ? p384 : t320 <= t256 ? p320 : p256;
 }
 
-// Workgroups per tile of the dH contraction.  Its tiles are few and long (`nk` k-blocks each, one per CU at a time):
-// the count minimises the time of the last-finishing CU in k-blocks, plus ten per workgroup for filling the ring and
-// the epilogue, plus the partial sums' way through memory (8 bytes per element and split).  Whole loss calls at
+// Time of `tiles` tiles with nk k-blocks each, in k-blocks of a 256 x 384 tile (1.5 .. 2 us): rounds of workgroups, with
+// some k-blocks each for filling the ring and the epilogue.  128 x 128 tiles run two per CU; what a pair of their k-blocks
+// costs depends on how the kernel's operands reach the LDS (packed blocks least, a transposed read of W most):
+//   d = 4096, small / large tiles   V = 8192, 1000 tokens   V = 32000, 1000   V = 151936, 300 / 1000
+//   sweep                            73 / 121 us             309 / 293         528 / 470, 1368 / 1132
+//   dH                               90 /  75                392 / 238         588 / 355, 1381 / 1048
+//   dW                               77 / 100                381 / 302         874 / 700, 1877 / 1284
+// and at d = 256, V = 1544, 1000 tokens 14 / 25, 11 / 20, 17 / 36 us.
+struct SmallRate {
+  double pair, alone;   // a k-block of two workgroups of one CU; of one that has it to itself
+  int start;
+};
+constexpr SmallRate kSmallSweep{0.7, 0.45, 5}, kSmallDh{0.95, 0.5, 5}, kSmallDw{0.48, 0.4, 8};
+static double large_time(int64_t tiles, int nk) { return (double)((tiles + kNumCU - 1) / kNumCU) * (nk + 10); }
+static double small_time(const SmallRate& r, int64_t tiles, int nk) {
+  const int64_t full = tiles / (2 * kNumCU), rest = tiles - full * 2 * kNumCU;
+  return ((double)full * r.pair + (rest > kNumCU ? r.pair : rest > 0 ? r.alone : 0.0)) * (nk + r.start);
+}
+template <class C>
+static int64_t tile_count(int64_t M, int64_t N) {
+  return ((M + C::BM - 1) / C::BM) * ((N + C::BN - 1) / C::BN);
+}
+// An M x N contraction of nk k-blocks is faster in small tiles.
+static bool small_tiles_pay(const SmallRate& r, int64_t M, int64_t N, int nk) {
+  return small_time(r, tile_count<CfgSmall>(M, N), nk) < large_time(tile_count<Cfg>(M, N), nk);
+}
+
+// Tile and workgroups per tile of the dH contraction of nv tokens.  Its tiles are few and long (`nk` k-blocks each): the
+// pick minimises their time plus the partial sums' way through memory (8 bytes per element and split).  Whole loss calls at
 // V = 151936, one workgroup per tile / the count chosen: 1003 tokens, d = 4096 7.79 / 4.65 ms (five splits);
 // 6007 tokens, d = 2048 11.23 / 9.72 ms (two); 30011 tokens at d = 5120, whose last panel has 1211, 114.2 / 111.4 ms.
-static int dh_splits(int64_t tiles, int nk, int64_t nv, int d, size_t scratch) {
-  int best = 1;
-  double best_time = (double)((tiles + kNumCU - 1) / kNumCU) * (nk + 10);
-  for (int s = 2; s <= 64 && s * 4 <= nk && (size_t)s * nv * d * 4 <= scratch; ++s) {
-    const double rounds = (double)((tiles * s + kNumCU - 1) / kNumCU);
-    const double time = rounds * ((nk + s - 1) / s + 10) + 5 + 1.2e-6 * (double)s * nv * d;
-    if (time < best_time - 1e-9) { best_time = time; best = s; }
+static DhPick pick_dh(int64_t nv, int d, int nk, bool allow_small, size_t scratch) {
+  DhPick best;
+  double best_time = 1e300;
+  for (int small = 0; small <= (allow_small ? 1 : 0); ++small) {
+    const int64_t tiles = small ? tile_count<CfgSmall>(d, nv) : tile_count<Cfg>(d, nv);
+    for (int s = 1; s <= 64 && (s == 1 || (s * 4 <= nk && (size_t)s * nv * d * 4 <= scratch)); ++s) {
+      const int k = (nk + s - 1) / s;
+      const double time = (small ? small_time(kSmallDh, tiles * s, k) : large_time(tiles * s, k)) +
+                          (s > 1 ? 5 + 1.2e-6 * (double)s * nv * d : 0.0);
+      if (time < best_time - 1e-9) { best_time = time; best.small = small != 0; best.splits = s; }
+    }
   }
   return best;
 }
@@ -274,10 +316,14 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
     if (dtype == OAPL_BF16) {
       // the last panel's partial sums of dH: in the packed copy of W, which is dead by then, or in a space of their own
       const int64_t last = T > 0 ? T - (T - 1) / p.Tp * p.Tp : 0;
-      const int64_t tiles = (int64_t)p.n_rt_d * ((last + Cfg::BN - 1) / Cfg::BN);
-      if (!p.rows || max_splits > 1)
-        p.splits = dh_splits(tiles, p.n_kt_v, last, d, (size_t)p.n_rt_v * p.n_kt_d * kPackBlockBytesA);
-      p.off_part = p.rows && p.splits > 1 ? take((size_t)p.splits * last * d * 4) : p.off_Wp;
+      const size_t packed_w = (size_t)p.n_rt_v * p.n_kt_d * kPackBlockBytesA;
+      const bool lean = max_splits == 1;
+      if (!p.rows) p.dh = pick_dh(last, d, p.n_kt_v, false, packed_w);
+      else p.dh = pick_dh(last, d, p.n_kt_v, true, lean ? 0 : (packed_w > kPartDhBytes ? packed_w : kPartDhBytes));
+      p.off_part = p.rows && p.dh.splits > 1 ? take((size_t)p.dh.splits * last * d * 4) : p.off_Wp;
+      p.small_sweep = p.rows && T <= p.Tp && !lean && small_tiles_pay(kSmallSweep, V, T, p.n_kt_d);
+      p.small_dw = p.rows && T <= p.Tp && small_tiles_pay(kSmallDw, d, V, (int)((T + kPackK - 1) / kPackK));
+      p.n_vt = p.small_sweep ? (V + CfgSmall::BM - 1) / CfgSmall::BM : p.n_rt_v;
       if (!p.rows) p.off_WTp = take((size_t)p.n_rt_d * p.n_kt_v * kPackBlockBytesA);
       p.off_HTp = take((size_t)p.n_rt_d * p.n_kt_t * kPackBlockBytesA);
       // Panel buffers, both packed copies.  The single sweep keeps a ring of them: a panel's gradient
@@ -292,7 +338,7 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
       // single-sweep path: reference exponents and per-vocabulary-tile row sums of one panel
       p.sweep = true;
       p.off_ref2 = take(Tn * 4);
-      p.off_spart = take((size_t)p.n_rt_v * (size_t)p.Tp * 4);
+      p.off_spart = take((size_t)p.n_vt * (size_t)p.Tp * 4);
     } else {
       p.ldz = max_splits > 1 ? round_up(p.Tp, 4) : p.Tp;    // a multiple of 4 floats lets the contractions load 16 bytes
       p.off_G = take((size_t)p.ldz * V * 4);
@@ -361,9 +407,9 @@ static bool allow_sample() {
   return allow_big_lds(k_fwd_sample<C, ROWS>, C::LDS_BYTES);
 }
 
-template <bool SPLIT, bool ATR>
+template <class C, bool SPLIT, bool ATR>
 static bool allow_dh() {
-  return allow_big_lds(k_bwd_dh<Cfg, SPLIT, ATR>, Cfg::LDS_BYTES);
+  return allow_big_lds(k_bwd_dh<C, SPLIT, ATR>, C::LDS_BYTES);
 }
 
 static bool prepare_kernels() {
@@ -375,7 +421,9 @@ static bool prepare_kernels() {
          allow_sample<Cfg128, true>() && allow_sample<Cfg256, true>() && allow_sample<CfgSample, false>() &&
          allow_big_lds(k_bwd_dz<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_bwd_dz<Cfg, true>, Cfg::LDS_BYTES) &&
         
-         allow_dh<false, false>() && allow_dh<false, true>() && allow_dh<true, false>() && allow_dh<true, true>() &&
+         allow_dh<Cfg, false, false>() && allow_dh<Cfg, false, true>() && allow_dh<Cfg, true, false>() &&
+         allow_dh<Cfg, true, true>() && allow_dh<CfgSmall, false, true>() && allow_dh<CfgSmall, true, true>() &&
+         allow_big_lds(k_bwd_dw<CfgSmall>, CfgSmall::LDS_BYTES) && allow_big_lds(k_sweep<CfgSmall, true>, CfgSmall::LDS_BYTES) &&
                  allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
          allow_big_lds(k_sweep<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_sweep<Cfg, true>, Cfg::LDS_BYTES) &&
          allow_big_lds(k_fwd_lse<CfgRef, false, true>, CfgRef::LDS_BYTES);
@@ -562,12 +610,11 @@ static int forward_finish(const Plan& p, const float* logq, float* logprob_out, 
   return OAPL_OK;
 }
 
-template <bool SPLIT, bool ATR>
+template <class C, bool SPLIT, bool ATR>
 static void launch_dh(const Plan& p, const bf16_t* W, const bf16_t* G, int64_t nv, const float* factor, bf16_t* dH, float* part,
                       hipStream_t st, Gate gate) {
-  const int splits = SPLIT ? p.splits : 1;
-  const int64_t tiles = (int64_t)p.n_rt_d * ((nv + Cfg::BN - 1) / Cfg::BN);
-  k_bwd_dh<Cfg, SPLIT, ATR><<<(unsigned)round_up(tiles * splits, 8), Cfg::NT, Cfg::LDS_BYTES, st>>>(
+  const int splits = SPLIT ? p.dh.splits : 1;
+  k_bwd_dh<C, SPLIT, ATR><<<(unsigned)round_up(tile_count<C>(p.d, nv) * splits, 8), C::NT, C::LDS_BYTES, st>>>(
       W, p.V, p.n_kt_v, G, p.n_kt_g, p.d, nv, p.n_kt_v, factor, dH, splits, part, gate);
 }
 
@@ -575,23 +622,39 @@ static void launch_dh(const Plan& p, const bf16_t* W, const bf16_t* G, int64_t n
 // split, and only it has a space for partial sums (the other panels of a long batch are sized to fill the chip as they are).
 static int launch_dh(const Plan& p, const bf16_t* W, const bf16_t* G, int64_t nv, const float* factor, bf16_t* dH, bool last,
                      char* ws, hipStream_t st, Gate gate, bool timed) {
-  const bool split = last && p.splits > 1;
+  const bool split = last && p.dh.splits > 1, small = last && p.dh.small;
   float* part = split ? (float*)(ws + p.off_part) : nullptr;
   const bf16_t* A = p.rows ? W : (const bf16_t*)(ws + p.off_WTp);
   {
     ScopedKernelTimer tm(kBwdDh, st, timed);
-    if (split && p.rows) launch_dh<true, true>(p, A, G, nv, factor, dH, part, st, gate);
-    else if (split) launch_dh<true, false>(p, A, G, nv, factor, dH, part, st, gate);
-    else if (p.rows) launch_dh<false, true>(p, A, G, nv, factor, dH, part, st, gate);
-    else launch_dh<false, false>(p, A, G, nv, factor, dH, part, st, gate);
+    if (split && small) launch_dh<CfgSmall, true, true>(p, A, G, nv, factor, dH, part, st, gate);
+    else if (small) launch_dh<CfgSmall, false, true>(p, A, G, nv, factor, dH, part, st, gate);
+    else if (split && p.rows) launch_dh<Cfg, true, true>(p, A, G, nv, factor, dH, part, st, gate);
+    else if (split) launch_dh<Cfg, true, false>(p, A, G, nv, factor, dH, part, st, gate);
+    else if (p.rows) launch_dh<Cfg, false, true>(p, A, G, nv, factor, dH, part, st, gate);
+    else launch_dh<Cfg, false, false>(p, A, G, nv, factor, dH, part, st, gate);
   }
   OAPL_LAUNCH_CHECK();
   if (split) {
     const int64_t blocks = grid1d(nv * (p.d / 8), 256);
-    k_dh_reduce<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, st>>>(part, p.splits, nv, p.d, factor, dH, gate);
+    k_dh_reduce<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, st>>>(part, p.dh.splits, nv, p.d, factor, dH, gate);
     OAPL_LAUNCH_CHECK();
   }
   return OAPL_OK;
+}
+
+template <class C>
+static void launch_dw(const Plan& p, const bf16_t* HTp, const bf16_t* GT, int kt, float* dW, int accumulate, hipStream_t st,
+                      Gate gate) {
+  k_bwd_dw<C><<<(unsigned)round_up(tile_count<C>(p.d, p.V), kNumCU), C::NT, C::LDS_BYTES, st>>>(HTp, GT, p.n_kt_t, p.d, p.V, kt,
+                                                                                             dW, accumulate, gate);
+}
+
+template <class C, bool ROWS>
+static void launch_sweep(const Plan& p, const bf16_t* W, const bf16_t* H, int64_t nv, const float* ref2, bf16_t* G, bf16_t* GT,
+                         float* spart, hipStream_t st, Gate gate) {
+  k_sweep<C, ROWS><<<(unsigned)round_up(tile_count<C>(p.V, nv), 8), C::NT, C::LDS_BYTES, st>>>(
+      W, H, p.V, nv, p.d, p.n_kt_d, ref2, G, p.n_kt_g, GT, p.n_kt_t, spart, p.Tp, gate);
 }
 
 static int pack_wt(const Plan& p, const void* W, char* ws, hipStream_t st, Gate gate) {
@@ -622,7 +685,7 @@ static int recompute_panel(const Plan& p, const void* H, const void* W, const in
 // (two-pass form: f_t = c_t (1 - p_y); single sweep: a_t).
 static int panel_gradients(const Plan& p, const void* H, const void* W, int64_t t0, const bf16_t* G, const bf16_t* GT, void* dH,
                            float* dW, char* ws, hipStream_t st, Gate gate, bool timed) {
-  const int d = p.d, V = p.V;
+  const int d = p.d;
   const int64_t nv = (p.T - t0) < p.Tp ? (p.T - t0) : p.Tp;
   const int kt = (int)((nv + kPackK - 1) / kPackK);
   const float* coef = (const float*)(ws + p.off_coef) + t0;
@@ -633,9 +696,8 @@ static int panel_gradients(const Plan& p, const void* H, const void* W, int64_t 
   if (int rc = launch_dh(p, (const bf16_t*)W, G, nv, coef, (bf16_t*)dH + t0 * d, t0 + p.Tp >= p.T, ws, st, gate, timed)) return rc;
   {
     ScopedKernelTimer tm(kBwdDw, st, timed);
-    const int64_t tiles = (int64_t)p.n_rt_d * ((V + Cfg::BN - 1) / Cfg::BN);
-    k_bwd_dw<Cfg><<<(unsigned)round_up(tiles, kNumCU), Cfg::NT, Cfg::LDS_BYTES, st>>>(HTp, GT, p.n_kt_t, d, V, kt, dW,
-                                                                                    t0 > 0 ? 1 : 0, gate);
+    if (p.small_dw) launch_dw<CfgSmall>(p, HTp, GT, kt, dW, 0, st, gate);
+    else launch_dw<Cfg>(p, HTp, GT, kt, dW, t0 > 0 ? 1 : 0, st, gate);
   }
   OAPL_LAUNCH_CHECK();
   return OAPL_OK;
@@ -731,13 +793,14 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
     const int64_t nv = (T - t0) < p.Tp ? (T - t0) : p.Tp;
     {
       ScopedKernelTimer tm(kSweep, st);
-      (p.rows ? k_sweep<Cfg, true> : k_sweep<Cfg, false>)<<<
-          (unsigned)round_up(p.n_rt_v * ((nv + Cfg::BN - 1) / Cfg::BN), 8), Cfg::NT, Cfg::LDS_BYTES, st>>>(
-          x.W, x.H + t0 * x.ld, V, nv, d, p.n_kt_d, ref2 + t0, Gbuf(k), p.n_kt_g, GTbuf(k), p.n_kt_t, spart, p.Tp, fast);
+      const bf16_t* Ht = x.H + t0 * x.ld;
+      if (p.small_sweep) launch_sweep<CfgSmall, true>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
+      else if (p.rows) launch_sweep<Cfg, true>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
+      else launch_sweep<Cfg, false>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
     }
     OAPL_LAUNCH_CHECK();
     k_sweep_finish<<<grid1d(nv, kFinishRows), kFinishSlices * kFinishRows, 0, st>>>(
-        spart, p.n_rt_v, p.Tp, nv, ref2 + t0, zy + t0, logq + t0, tokens + t0, V,
+        spart, p.n_vt, p.Tp, nv, ref2 + t0, zy + t0, logq + t0, tokens + t0, V,
         logprob_out ? logprob_out + t0 : nullptr, diff + t0, nis + t0, Gbuf(k), p.n_kt_g, GTbuf(k), p.n_kt_t, flag,
         fast);
     OAPL_LAUNCH_CHECK();
