@@ -813,25 +813,37 @@ k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, 
       ml.start(smem, n_kt);
       if (n_kt > 1) ml.issue(1, smem, 1, n_kt);
     }
-    const int row0 = m0 + wm * C::TM * 32 + 4 * h;
-#pragma unroll
-    for (int j = 0; j < C::TN; ++j) {
-      const int64_t t = n0 + wn * C::TN * 32 + j * 32 + (lane & 31);
-      const uint32_t t_lo = (uint32_t)t, t_hi = (uint32_t)(t >> 32);
+    if (m0 + C::BM > V) {  // ragged last vocabulary tile: a logit of -inf is never drawn
+      const int row = m0 + wm * C::TM * 32 + 4 * h;
 #pragma unroll
       for (int i = 0; i < C::TM; ++i)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int v0 = row0 + i * 32 + 8 * q;          // multiple of 4: one Philox block
+        for (int r = 0; r < 16; ++r)
+          if (row + acc_row(i, r) >= V) {
+#pragma unroll
+            for (int j = 0; j < C::TN; ++j) acc[i][j][r] = -__builtin_inff();
+          }
+    }
+    // Rows outside, tokens inside: the first two Philox rounds multiply words that depend on the row block or on the token
+    // alone, and are shared over the other.
+    const int row0 = m0 + wm * C::TM * 32 + 4 * h;
+#pragma unroll
+    for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int v0 = row0 + i * 32 + 8 * q;          // multiple of 4: one Philox block
+#pragma unroll
+        for (int j = 0; j < C::TN; ++j) {
+          const int64_t t = n0 + wn * C::TN * 32 + j * 32 + (lane & 31);
           uint32_t x[4];
-          philox4x32_10((uint32_t)(v0 >> 2), t_lo, t_hi, 0u, seed_lo, seed_hi, x);
+          philox4x32_10((uint32_t)(v0 >> 2), (uint32_t)t, (uint32_t)(t >> 32), 0u, seed_lo, seed_hi, x);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const float sc = __builtin_fmaf(acc[i][j][4 * q + e], inv_temperature, gumbel_from_bits(x[e]));
-            if (v0 + e < V && sc > best[j]) { best[j] = sc; arg[j] = v0 + e; }   // indices rise: strict > keeps the smallest
+            if (sc > best[j]) { best[j] = sc; arg[j] = v0 + e; }   // indices rise: strict > keeps the smallest
           }
         }
-    }
+      }
   }
 
   // merge the two lane halves, then the WM waves stacked along the vocabulary (through LDS)
