@@ -78,7 +78,7 @@ struct TileCfg {
   static constexpr int LDS_BYTES =
       MAIN_BYTES > STAGE_NM ? (MAIN_BYTES > STAGE_MN ? MAIN_BYTES : STAGE_MN)
                             : (STAGE_NM > STAGE_MN ? STAGE_NM : STAGE_MN);
-  static_assert(NS == 2, "ring size");
+  static_assert(NS == 2 || NS == 4, "ring size");
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "block rows must split over waves");
   static_assert(RED_BYTES + RED_BYTES / 2 <= LDS_BYTES, "reduction scratch must fit");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of one CU");
@@ -283,29 +283,68 @@ struct Mainloop {
     }
   }
 
+  // Ring of four (128 x 128 tiles that have a CU to themselves, the reference pass): such a workgroup waits for the
+  // latency of its loads as much as for operand bytes, so three blocks are in flight instead of one.  Loss calls of 100
+  // tokens, ring of two / four: d = 4096, V = 32000 419 / 380 us (dH 62 / 49), V = 8192 174 / 160, V = 151936 1267 / 1241.
+  //
   // One k-block of the pipeline in ring slot S (a literal at the call sites): wait until the block's
   // loads have landed, barrier (which also tells that every wave is done with the other slot),
   // refill the other slot with the next block, multiply.  Branches are wave-uniform and touch no
   // accumulator.
   __device__ __forceinline__ void step(const int S, lds_char_ptr smem, int kt, int nk, f32x16 (&acc)[C::TM][C::TN]) {
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    __syncthreads();
-    if (kt + 1 < nk) issue(S ^ 1, smem, kt + 1, nk);
+    if (C::NS == 2) {
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+      __syncthreads();
+      if (kt + 1 < nk) issue(S ^ 1, smem, kt + 1, nk);
+    } else {
+      // Blocks kt + 1 and kt + 2 stay in flight (loads issued later than block kt's by someone else only make the wait
+      // stricter).  __syncthreads() would wait for them, so the barrier is a bare one; this wave's LDS reads of the slot
+      // that is refilled next are done (lgkmcnt), and the compiler keeps memory accesses on their side of it.
+      constexpr int L = C::NI_A + C::NI_B;
+      if (kt + 2 < nk) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * L) & ~0x0F00);
+      else if (kt + 1 < nk) __builtin_amdgcn_s_waitcnt(vmcnt_imm(L) & ~0x0F00);
+      else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0) & ~0x0F00);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      if (kt + 3 < nk) issue((S + 3) & 3, smem, kt + 3, nk);
+    }
     compute(S, smem, acc);
   }
 
-  // Starts a tile: k-block 0 into slot 0.  Every wave must be past its last LDS read of the
+  // Starts a tile: k-block 0 into slot 0 (ring of four: blocks 0 .. 2).  Every wave must be past its last LDS read of the
   // previous tile (finish() ends with a barrier).
-  __device__ __forceinline__ void start(lds_char_ptr smem, int nk) { issue(0, smem, 0, nk); }
+  __device__ __forceinline__ void start(lds_char_ptr smem, int nk) {
+    issue(0, smem, 0, nk);
+    if (C::NS == 4 && nk > 1) issue(1, smem, 1, nk);
+    if (C::NS == 4 && nk > 2) issue(2, smem, 2, nk);
+  }
+  // ... and block 1 into slot 1 of a ring of two, for steps<true>.
+  __device__ __forceinline__ void start_preload(lds_char_ptr smem, int nk) {
+    start(smem, nk);
+    if (C::NS == 2 && nk > 1) issue(1, smem, 1, nk);
+  }
 
-  // k-blocks [k0, k1) of a tile with nk k-blocks in all (k0 even, after start() or an earlier steps()).
-  // PRELOADED (with k0 = 0): k-block 1 was issued beforehand as well (start(), then issue(1, smem, 1) if the tile
-  // has two blocks), by a caller whose work between two tiles leaves the LDS alone.  The first block then issues
+  // k-blocks [k0, k1) of a tile with nk k-blocks in all (k0 a multiple of NS, after start() or an earlier steps()).
+  // PRELOADED (ring of two, k0 = 0): k-block 1 was issued beforehand as well (start_preload()), by a caller whose work between two tiles leaves the LDS alone.  The first block then issues
   // nothing.  It waits for both blocks: waiting for the first alone (vmcnt = the second block's loads, and a bare
   // s_barrier, since __syncthreads() waits for every outstanding load itself) measured no different.
   template <bool PRELOADED = false>
   __device__ __forceinline__ void steps(lds_char_ptr smem, int k0, int k1, int nk, f32x16 (&acc)[C::TM][C::TN]) {
     int kt = k0;
+    if (C::NS == 4) {
+      for (; kt + 4 <= k1; kt += 4) {
+        step(0, smem, kt, nk, acc);
+        step(1, smem, kt + 1, nk, acc);
+        step(2, smem, kt + 2, nk, acc);
+        step(3, smem, kt + 3, nk, acc);
+      }
+      if (kt < k1) step(0, smem, kt, nk, acc);
+      if (kt + 1 < k1) step(1, smem, kt + 1, nk, acc);
+      if (kt + 2 < k1) step(2, smem, kt + 2, nk, acc);
+      return;
+    }
     if (PRELOADED) {
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
       __syncthreads();
@@ -664,8 +703,7 @@ k_fwd_lse(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int
   f32x16 acc[C::TM][C::TN];
   if (mt_begin < mt_end) {
     ml.set_a(W, mt_begin, V, d, n_kt);
-    ml.start(smem, n_kt);
-    if (n_kt > 1) ml.issue(1, smem, 1, n_kt);
+    ml.start_preload(smem, n_kt);
   }
   for (int mt = mt_begin; mt < mt_end; ++mt) {
     const int m0 = mt * C::BM;
@@ -673,8 +711,7 @@ k_fwd_lse(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int
     ml.template finish<true>(smem, n_kt, acc);
     if (mt + 1 < mt_end) {  // the epilogue below works in registers only: overlap it with the next tile's first loads
       ml.set_a(W, mt + 1, V, d, n_kt);
-      ml.start(smem, n_kt);
-      if (n_kt > 1) ml.issue(1, smem, 1, n_kt);
+      ml.start_preload(smem, n_kt);
     }
 
     if (m0 + C::BM > V) {  // ragged last vocabulary tile: rows >= V do not exist (their logits are 0, not -inf)
@@ -801,8 +838,7 @@ k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, 
   f32x16 acc[C::TM][C::TN];
   if (mt_begin < mt_end) {
     ml.set_a(W, mt_begin, V, d, n_kt);
-    ml.start(smem, n_kt);
-    if (n_kt > 1) ml.issue(1, smem, 1, n_kt);
+    ml.start_preload(smem, n_kt);
   }
   for (int mt = mt_begin; mt < mt_end; ++mt) {
     const int m0 = mt * C::BM;
@@ -810,8 +846,7 @@ k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, 
     ml.template finish<true>(smem, n_kt, acc);
     if (mt + 1 < mt_end) {
       ml.set_a(W, mt + 1, V, d, n_kt);
-      ml.start(smem, n_kt);
-      if (n_kt > 1) ml.issue(1, smem, 1, n_kt);
+      ml.start_preload(smem, n_kt);
     }
     if (m0 + C::BM > V) {  // ragged last vocabulary tile: a logit of -inf is never drawn
       const int row = m0 + wm * C::TM * 32 + 4 * h;
@@ -1031,7 +1066,7 @@ k_sweep(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H_panel, int V,
   ml.start(smem, n_kt);
   // the epilogue's per-token references are requested two k-blocks before the end, so that their
   // latency hides behind the last multiplications instead of stalling the epilogue
-  const int k_early = n_kt > 2 ? (n_kt - 2) & ~1 : 0;
+  const int k_early = n_kt > C::NS ? (n_kt - 2) & ~(C::NS - 1) : 0;
   ml.steps(smem, 0, k_early, n_kt, acc);
   float r2v[C::TN];
 #pragma unroll

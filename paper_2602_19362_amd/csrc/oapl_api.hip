@@ -22,6 +22,8 @@ static_assert(Cfg::BN == kPackRowsB, "n-side operands of the loss path are packe
 // Where tiles of that size are too few to fill the chip (small heads and hidden sizes): 128 x 128, two workgroups per CU,
 // on the same packed blocks.
 typedef TileCfg<2, 2, 2, 2, 2, kPackRowsB> CfgSmall;
+// ... and, where there are no more of them than CUs, with a ring of four stages.
+typedef TileCfg<2, 2, 2, 2, 4, kPackRowsB> CfgDeep;
 // The sampling kernel carries a running (score, index) pair per column through the main loop and
 // draws Philox blocks in its epilogue: its largest tile is 256 x 256 (128 accumulators per lane),
 // with H packed in 256-row blocks for it where it reads packed operands.
@@ -38,7 +40,7 @@ typedef TileCfg<4, 2, 1, 2, 2> Cfg128;
 typedef CfgSample Cfg256;
 typedef TileCfg<4, 2, 2, 5, 2> Cfg320;
 // The sweep's reference exponents: the first 256 vocabulary entries of 64 tokens.
-typedef TileCfg<4, 1, 2, 2, 2> CfgRef;
+typedef TileCfg<4, 1, 2, 2, 4> CfgRef;
 enum FwdTile { kTile64, kTile128, kTile256, kTile320, kTile384 };
 struct TilePick {
   FwdTile tile = kTile384;
@@ -423,6 +425,8 @@ static bool prepare_kernels() {
         
          allow_dh<Cfg, false, false>() && allow_dh<Cfg, false, true>() && allow_dh<Cfg, true, false>() &&
          allow_dh<Cfg, true, true>() && allow_dh<CfgSmall, false, true>() && allow_dh<CfgSmall, true, true>() &&
+         allow_dh<CfgDeep, false, true>() && allow_dh<CfgDeep, true, true>() && allow_big_lds(k_bwd_dw<CfgDeep>, CfgDeep::LDS_BYTES) &&
+         allow_big_lds(k_sweep<CfgDeep, true>, CfgDeep::LDS_BYTES) &&
          allow_big_lds(k_bwd_dw<CfgSmall>, CfgSmall::LDS_BYTES) && allow_big_lds(k_sweep<CfgSmall, true>, CfgSmall::LDS_BYTES) &&
                  allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
          allow_big_lds(k_sweep<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_sweep<Cfg, true>, Cfg::LDS_BYTES) &&
@@ -627,7 +631,10 @@ static int launch_dh(const Plan& p, const bf16_t* W, const bf16_t* G, int64_t nv
   const bf16_t* A = p.rows ? W : (const bf16_t*)(ws + p.off_WTp);
   {
     ScopedKernelTimer tm(kBwdDh, st, timed);
-    if (split && small) launch_dh<CfgSmall, true, true>(p, A, G, nv, factor, dH, part, st, gate);
+    const bool deep = small && tile_count<CfgDeep>(p.d, nv) * p.dh.splits <= kNumCU;
+    if (split && deep) launch_dh<CfgDeep, true, true>(p, A, G, nv, factor, dH, part, st, gate);
+    else if (deep) launch_dh<CfgDeep, false, true>(p, A, G, nv, factor, dH, part, st, gate);
+    else if (split && small) launch_dh<CfgSmall, true, true>(p, A, G, nv, factor, dH, part, st, gate);
     else if (small) launch_dh<CfgSmall, false, true>(p, A, G, nv, factor, dH, part, st, gate);
     else if (split && p.rows) launch_dh<Cfg, true, true>(p, A, G, nv, factor, dH, part, st, gate);
     else if (split) launch_dh<Cfg, true, false>(p, A, G, nv, factor, dH, part, st, gate);
@@ -696,7 +703,8 @@ static int panel_gradients(const Plan& p, const void* H, const void* W, int64_t 
   if (int rc = launch_dh(p, (const bf16_t*)W, G, nv, coef, (bf16_t*)dH + t0 * d, t0 + p.Tp >= p.T, ws, st, gate, timed)) return rc;
   {
     ScopedKernelTimer tm(kBwdDw, st, timed);
-    if (p.small_dw) launch_dw<CfgSmall>(p, HTp, GT, kt, dW, 0, st, gate);
+    if (p.small_dw && tile_count<CfgDeep>(d, p.V) <= kNumCU) launch_dw<CfgDeep>(p, HTp, GT, kt, dW, 0, st, gate);
+    else if (p.small_dw) launch_dw<CfgSmall>(p, HTp, GT, kt, dW, 0, st, gate);
     else launch_dw<Cfg>(p, HTp, GT, kt, dW, t0 > 0 ? 1 : 0, st, gate);
   }
   OAPL_LAUNCH_CHECK();
@@ -794,7 +802,9 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
     {
       ScopedKernelTimer tm(kSweep, st);
       const bf16_t* Ht = x.H + t0 * x.ld;
-      if (p.small_sweep) launch_sweep<CfgSmall, true>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
+      if (p.small_sweep && tile_count<CfgDeep>(V, nv) <= kNumCU)
+        launch_sweep<CfgDeep, true>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
+      else if (p.small_sweep) launch_sweep<CfgSmall, true>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
       else if (p.rows) launch_sweep<Cfg, true>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
       else launch_sweep<Cfg, false>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
     }
