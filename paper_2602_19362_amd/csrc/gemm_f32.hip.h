@@ -283,9 +283,10 @@ struct EpiDzF32 {
   }
 };
 
-// ... or in place from the logits the scoring pass kept: 256 tokens x 16 vocabulary rows per workgroup.  Bound by memory
+// ... or in place from the logits the scoring pass kept: 256 tokens x 4 vocabulary rows per workgroup (sixteen rows took
+// 8 us for 256 x 1024 logits, a chain of loads on a quarter of the chip).  Bound by memory
 // (8 bytes per logit): 20 us for 1501 x 8192, a tenth of computing them again at d = 768.
-constexpr int kDzRows = 16;
+constexpr int kDzRows = 4;
 __global__ void __launch_bounds__(256)
 k_dz_f32(float* __restrict__ zt, int64_t ldz, int V, int64_t T, const int32_t* __restrict__ tokens,
          const float* __restrict__ lse, const float* __restrict__ coef) {
@@ -294,12 +295,13 @@ k_dz_f32(float* __restrict__ zt, int64_t ldz, int V, int64_t T, const int32_t* _
   const float c = coef[t], l = lse[t];
   const int y = tokens[t];
   const int v0 = blockIdx.x * kDzRows;
-#pragma unroll 8
+  float z[kDzRows];
+#pragma unroll
   for (int i = 0; i < kDzRows; ++i)
-    if (v0 + i < V) {
-      float* p = zt + (int64_t)(v0 + i) * ldz + t;
-      *p = dz_f32(*p, v0 + i, y, c, l);
-    }
+    if (v0 + i < V) z[i] = zt[(int64_t)(v0 + i) * ldz + t];
+#pragma unroll
+  for (int i = 0; i < kDzRows; ++i)
+    if (v0 + i < V) zt[(int64_t)(v0 + i) * ldz + t] = dz_f32(z[i], v0 + i, y, c, l);
 }
 
 // Plain store, or read-add-store, of the tile into C[m][n]; with several splits of k each writes its own [M][N] copy.

@@ -431,20 +431,21 @@ k_oapl_objective(const double* __restrict__ diff, const float* __restrict__ rewa
   __shared__ int bad;
   if (gate_closed(gate)) return;
   const int tid = threadIdx.x, s0 = blockIdx.x;
-  auto residual = [&](int s, double sum) {
+  auto advantage = [&](int s) {      // r_s - V*
     const int g = gid[s];
-    const double v = g >= 0 && g < n_groups ? vstar_ws[g] : __builtin_nan("");
-    return beta_l * sum - ((double)rewards[s] - v);
+    return (double)rewards[s] - (g >= 0 && g < n_groups ? vstar_ws[g] : __builtin_nan(""));
   };
   if (s0 < n_seq) {
+    // requested before the sum that they are combined with
+    const double adv = advantage(s0);
+    const float* factor = token_factor(factors);
     int64_t a, b;
     token_range(off, s0, Ttok, a, b);
     double acc = 0.0;
     for (int64_t t = a + tid; t < b; t += 256) acc += diff[t];
     acc = block_sum(acc);
     if (coef) {
-      const float* factor = token_factor(factors);
-      const float c = (float)(scale * 2.0 * beta_l * residual(s0, acc));
+      const float c = (float)(scale * 2.0 * beta_l * (beta_l * acc - adv));
       for (int64_t t = a + tid; t < b; t += 256) coef[t] = factor ? c * factor[t] : c;
     }
     if (tid == 0) {
@@ -452,6 +453,8 @@ k_oapl_objective(const double* __restrict__ diff, const float* __restrict__ rewa
       if (seq_logratio_out) seq_logratio_out[s0] = (float)acc;
     }
   }
+  // the last workgroup's first 256 rollouts: requested before the hand-over, which then costs one round trip less
+  const double adv0 = tid < n_seq ? advantage(tid) : 0.0;
   if (!last_workgroup(status + kCounterWord, gridDim.x)) return;
   if (tid == 0) bad = (off[0] != 0 || off[n_seq] != Ttok) ? kErrOffsets : 0;
   __syncthreads();
@@ -459,7 +462,7 @@ k_oapl_objective(const double* __restrict__ diff, const float* __restrict__ rewa
   for (int s = tid; s < n_seq; s += 256) {
     if (off[s + 1] < off[s]) atomicCAS(&bad, 0, kErrOffsets);
     if (gid[s] < 0 || gid[s] >= n_groups) atomicCAS(&bad, 0, kErrGroup);
-    const double delta = residual(s, __hip_atomic_load(Delta + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const double delta = beta_l * __hip_atomic_load(Delta + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - (s == tid ? adv0 : advantage(s));
     acc += delta * delta;
   }
   acc = block_sum(acc);
