@@ -65,7 +65,7 @@ typedef enum {
 } oapl_status;
 
 typedef enum {
-  OAPL_F32 = 0,  /* H, W, dH are float; plain fp32 FMA arithmetic */
+  OAPL_F32 = 0,  /* H, W, dH are float; fp32 products and sums (matrix cores) */
   OAPL_BF16 = 1  /* H, W, dH are bfloat16 (raw uint16 bit patterns); MFMA with fp32 accumulation */
 } oapl_dtype;
 
@@ -118,8 +118,10 @@ size_t oapl_workspace_bytes(int64_t T, int32_t d, int32_t V, int32_t n_seq,
  * A loss call derives its plan from workspace_bytes alone: the library's panel
  * size if two buffers of it fit, else the largest panel that does
  * (OAPL_ERR_WORKSPACE if not even a one-tile panel fits); then as many buffers
- * as fit.  Results do not depend on the plan beyond rounding (summation order
- * of dW over panels).
+ * as fit.  Space that only buys speed (partial sums of split contractions) is
+ * given up before the panel is made smaller; a plan asked for with panels
+ * smaller than the library's own has none.  Results do not depend on the plan
+ * beyond rounding (summation order of dW over panels and of split sums).
  */
 size_t oapl_workspace_bytes_for(int64_t T, int32_t d, int32_t V, int32_t n_seq,
                                 int32_t n_groups, int32_t dtype, int32_t with_backward,

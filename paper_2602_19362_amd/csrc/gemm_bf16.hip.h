@@ -9,6 +9,9 @@
 // each a 64 x 192 patch (192 accumulator registers per lane).  The tile is as
 // large as registers and LDS allow: operand delivery from L2 is what the loop
 // waits for, and 256 x 384 needs 17 % fewer operand bytes per flop than 256 x 256.
+// Calls too small to fill the chip with such tiles take smaller ones of the same
+// loop, and calls of few tokens read the caller's matrices in place (Mainloop's ROWS
+// and ATR); oapl_api.hip has the rules.
 //
 // Operand layout in HBM ("packed"): a matrix with R rows and K columns is
 // stored as blocks of RB rows x 64 columns (RB = 256 for the m-side operand,
