@@ -443,7 +443,7 @@ constexpr Gate kNoGate{nullptr, 0};
 // Slices of the finishing kernels: at least four partials per thread.
 static int finish_slices(int n_parts) {
   int s = 1;
-  while (s < 64 && s * 8 <= n_parts) s *= 2;
+  while (s < 256 && s * 8 <= n_parts) s *= 2;
   return s;
 }
 

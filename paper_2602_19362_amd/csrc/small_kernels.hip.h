@@ -88,7 +88,7 @@ k_gather_logit(const T* __restrict__ H, const T* __restrict__ W, const int32_t* 
 // A partial is (m, s) with s = sum b^(zeta - m): LOG2 = true means zeta =
 // z * log2(e), b = 2 (the MFMA kernel's epilogue); false means zeta = z, b = e.
 // Everything after the fp32 partials is done in double.  A workgroup serves 256 / slices tokens; the partials of a
-// token are taken by `slices` (a power of two <= 64) threads, interleaved, and combined in slice order, so the few
+// token are taken by `slices` (a power of two <= 256) threads, interleaved, and combined pairwise, so the few
 // tokens of a small call, which come with hundreds of partials each, are not walked by one thread each (777 tokens
 // with 64 partials: 47 us with one slice, 10 us with sixteen).
 template <bool LOG2>
@@ -105,15 +105,19 @@ k_lse_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, con
   const int64_t t = (int64_t)blockIdx.x * rows + col;
   float M = kNegHuge;
   if (t < Ttok) {
-#pragma unroll 4
+#pragma unroll 8
     for (int p = slice; p < n_parts; p += slices) M = fmaxf(M, partials[(int64_t)p * Ttok + t].x);
   }
   part_m[threadIdx.x] = M;
+  for (int half = slices / 2; half > 0; half /= 2) {
+    __syncthreads();
+    if (slice < half) part_m[threadIdx.x] = M = fmaxf(M, part_m[threadIdx.x + half * rows]);
+  }
   __syncthreads();
-  for (int s = 0; s < slices; ++s) M = fmaxf(M, part_m[s * rows + col]);
+  M = part_m[col];
   double S = 0.0, U = 0.0;
   if (t < Ttok) {
-#pragma unroll 4
+#pragma unroll 8
     for (int p = slice; p < n_parts; p += slices) {
       const float2 a = partials[(int64_t)p * Ttok + t];
       const double e = (double)a.x - (double)M;
@@ -124,12 +128,14 @@ k_lse_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, con
   }
   part_s[threadIdx.x] = S;
   part_u[threadIdx.x] = U;
-  __syncthreads();
-  if (slice != 0 || t >= Ttok) return;
-  for (int s = 1; s < slices; ++s) {
-    S += part_s[s * rows + col];
-    U += part_u[s * rows + col];
+  for (int half = slices / 2; half > 0; half /= 2) {
+    __syncthreads();
+    if (slice < half) {
+      part_s[threadIdx.x] = S += part_s[threadIdx.x + half * rows];
+      part_u[threadIdx.x] = U += part_u[threadIdx.x + half * rows];
+    }
   }
+  if (slice != 0 || t >= Ttok) return;
   const double lse = LOG2 ? ((double)M + log2(S)) * kLn2 : (double)M + log(S);
   double lp = (double)zy[t] - lse;   // NaN if the token was out of range
   if (lp > 0.0) lp = 0.0;            // the gathered logit is rounded separately from the sum
@@ -163,19 +169,22 @@ k_sample_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, 
   float best = -__builtin_inff();
   int arg = 0x7FFFFFFF;
   if (t < Ttok) {
-#pragma unroll 4
+#pragma unroll 8
     for (int p = slice; p < n_parts; p += slices) {
       const float2 a = partials[(int64_t)p * Ttok + t];
       if (better(a.x, __float_as_int(a.y), best, arg)) { best = a.x; arg = __float_as_int(a.y); }
     }
   }
   part[threadIdx.x] = make_float2(best, __int_as_float(arg));
-  __syncthreads();
-  if (slice != 0 || t >= Ttok) return;
-  for (int s = 1; s < slices; ++s) {
-    const float2 a = part[s * rows + col];
-    if (better(a.x, __float_as_int(a.y), best, arg)) { best = a.x; arg = __float_as_int(a.y); }
+  for (int half = slices / 2; half > 0; half /= 2) {
+    __syncthreads();
+    if (slice < half) {
+      const float2 a = part[threadIdx.x + half * rows];
+      if (better(a.x, __float_as_int(a.y), best, arg)) { best = a.x; arg = __float_as_int(a.y); }
+      part[threadIdx.x] = make_float2(best, __int_as_float(arg));
+    }
   }
+  if (slice != 0 || t >= Ttok) return;
   tokens_out[t] = arg;
   if (score_out) score_out[t] = best;
 }
@@ -520,7 +529,9 @@ k_grpo_objective(const double* __restrict__ diff, const float* __restrict__ logq
 // and patches the sampled token's entry of the unnormalised soft-max panel, in both packed
 // copies, to  Pt[y] - S = -S (1 - p_y)  (computed from expm1 so it is accurate when p_y -> 1).
 // Rows whose sum left the accepted range raise the fallback flag.
-constexpr int kFinishSlices = 8;
+// 32 slices, four loads each in flight: with 8 slices, one load after the other, a panel of 1003 tokens (594 tiles) took
+// 36 us and one of 12288 40 us; now 9 and 13 us.
+constexpr int kFinishSlices = 32;
 constexpr int kFinishRows = 32;      // token rows per workgroup of kFinishSlices * kFinishRows threads
 __global__ void __launch_bounds__(kFinishSlices * kFinishRows)
 k_sweep_finish(const float* __restrict__ spart, int n_vt, int64_t ld_s, int64_t n_valid,
@@ -536,8 +547,10 @@ k_sweep_finish(const float* __restrict__ spart, int n_vt, int64_t ld_s, int64_t 
   const int col = threadIdx.x % kFinishRows, slice = threadIdx.x / kFinishRows;
   const int64_t n = (int64_t)blockIdx.x * kFinishRows + col;
   double acc = 0.0;
-  if (n < n_valid)
+  if (n < n_valid) {
+#pragma unroll 4
     for (int mt = slice; mt < n_vt; mt += kFinishSlices) acc += (double)spart[(int64_t)mt * ld_s + n];
+  }
   part[slice][col] = acc;
   __syncthreads();
   if (slice != 0 || n >= n_valid) return;
