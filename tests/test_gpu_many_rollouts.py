@@ -1,0 +1,27 @@
+"""Batches with more rollouts and prompts than one workgroup looks at in a call's first launch, more rollouts than the
+objective's last workgroup has threads, and short or empty rollouts; the sizes just below that line too.  Tolerances as in
+test_gpu_parity.py."""
+import pytest
+import torch
+
+from tests._util import oracle_full
+from tests.test_gpu_parity import _check, _custom_batch, _grpo, _grpo_check, _grpo_inputs, _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_seq,n_groups", [(255, 15), (256, 16), (257, 1), (400, 40), (900, 9)])
+def test_losses(dtype, n_seq, n_groups):
+    print(dtype, n_seq, n_groups, flush=True)
+    n_seq = n_seq // n_groups * n_groups
+    b = _custom_batch(dtype, d=64, V=300, lens=[i % 4 for i in range(n_seq)], n_groups=n_groups, seed=n_seq, beta=1.0)
+    tol = (2e-2, 1e-3, 2e-2, 6e-3) if dtype == "bf16" else (1e-5, 1e-5, 1e-4, 1e-5)
+    res = _run(b)
+    _check(b, res, oracle_full(b), *tol)
+    again = _run(b)
+    assert torch.equal(res.loss, again.loss) and torch.equal(res.dW, again.dW)
+    logq, logp_old = _grpo_inputs(b, n_seq)
+    res = _grpo(b.H, b.W, b.tokens, logq, logp_old, b.seq_offsets, b.rewards, b.group_ids, n_groups)
+    torch.cuda.synchronize()
+    _grpo_check(b, logq, logp_old, res, *tol)
