@@ -913,9 +913,11 @@ static int fit_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, i
 
 // One workgroup takes a call's first steps while it has at most a few thousand (rollout, prompt) pairs to look at.
 static bool begin_in_one_launch(int n_seq, int n_groups) { return (int64_t)n_seq * n_groups + n_seq + n_groups <= 8192; }
+// ... else workgroups of 256 rollouts and four prompts each, at most 65536: the steps walk on from there, and thread indices
+// stay far below 2^31.
 static unsigned begin_grid(int n_seq, int n_groups) {
-  const unsigned a = grid1d(n_groups, 4), b = grid1d(n_seq > 0 ? n_seq : 1, 256);
-  return a > b ? a : b;
+  const unsigned a = grid1d(n_groups, 4), b = grid1d(n_seq > 0 ? n_seq : 1, 256), most = 1u << 16;
+  return a > most || b > most ? most : (a > b ? a : b);
 }
 
 static int loss_impl(const void* H, const void* W, const int32_t* tokens, const float* logq,
@@ -1010,7 +1012,7 @@ static int grpo_impl(const void* H, const void* W, const int32_t* tokens, const 
     OAPL_LAUNCH_CHECK();
     begin(begin_grid(n_seq, n_groups), 1);
     OAPL_LAUNCH_CHECK();
-    begin(grid1d(n_seq > 0 ? n_seq : 1, 256), 2);
+    begin(begin_grid(n_seq, 1), 2);
   }
   OAPL_LAUNCH_CHECK();
   if (int rc = pack_operands(p, H, W, ws, st)) return rc;

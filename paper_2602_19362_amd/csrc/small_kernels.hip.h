@@ -258,6 +258,7 @@ __device__ __forceinline__ int wave_allsum(int v) {
 // ---------------------------------------------------------------------------
 // What a loss call does before anything is scored.  Each step is a function of (worker, workers): one workgroup takes them
 // all in one launch where rollouts and prompts are few (a launch costs a small call 2 .. 4 us), else each has a grid.
+// Indices are 64 bits: rollouts and prompts may number 2^31 - 1, and a step past the last one must not wrap.
 // ---------------------------------------------------------------------------
 
 // Group value estimate, one wavefront per prompt:
@@ -267,14 +268,14 @@ __device__ __forceinline__ int wave_allsum(int v) {
 // exactly r).  Group ids come in any order, so the wavefront walks the rollouts lane-strided and
 // keeps those of its prompt: lane-local partial max / count / sum in rollout order, then shuffle
 // butterflies.  A prompt without rollouts gets NaN and records the group error.
-__device__ __forceinline__ void group_value(int wave, int waves, const float* __restrict__ rewards,
+__device__ __forceinline__ void group_value(int64_t wave, int64_t waves, const float* __restrict__ rewards,
                                             const int32_t* __restrict__ gid, int n_seq, int n_groups, double beta_v,
                                             double* __restrict__ vstar_ws, float* __restrict__ vstar_out, int* err) {
   const int lane = threadIdx.x & 63;
-  for (int g = wave; g < n_groups; g += waves) {
+  for (int64_t g = wave; g < n_groups; g += waves) {
     double m = -1.0e300;
     int cnt = 0;
-    for (int s = lane; s < n_seq; s += 64)
+    for (int64_t s = lane; s < n_seq; s += 64)
       if (gid[s] == g) { m = fmax(m, (double)rewards[s]); ++cnt; }
     m = wave_allmax(m);
     cnt = wave_allsum(cnt);
@@ -284,7 +285,7 @@ __device__ __forceinline__ void group_value(int wave, int waves, const float* __
       v = __builtin_nan("");
     } else {
       double sum = 0.0;
-      for (int s = lane; s < n_seq; s += 64)
+      for (int64_t s = lane; s < n_seq; s += 64)
         if (gid[s] == g) sum += exp(((double)rewards[s] - m) / beta_v);
       sum = wave_allsum(sum);
       v = m + beta_v * log(sum / (double)cnt);
@@ -299,14 +300,14 @@ __device__ __forceinline__ void group_value(int wave, int waves, const float* __
 // GRPO baseline (Sec. 2, the displayed GRPO objective), group step, one wavefront per prompt:
 // mean and population standard deviation of the prompt's rewards and its size G_g (kept behind
 // the per-rollout weights).  A prompt without rollouts gets NaN and records the group error.
-__device__ __forceinline__ void grpo_group_stats(int wave, int waves, const float* __restrict__ rewards,
+__device__ __forceinline__ void grpo_group_stats(int64_t wave, int64_t waves, const float* __restrict__ rewards,
                                                  const int32_t* __restrict__ gid, int n_seq, int n_groups,
                                                  double* gmean, double* gstd, double* gsize, int* err) {
   const int lane = threadIdx.x & 63;
-  for (int g = wave; g < n_groups; g += waves) {
+  for (int64_t g = wave; g < n_groups; g += waves) {
     double sum = 0.0;
     int cnt = 0;
-    for (int s = lane; s < n_seq; s += 64)
+    for (int64_t s = lane; s < n_seq; s += 64)
       if (gid[s] == g) { sum += (double)rewards[s]; ++cnt; }
     sum = wave_allsum(sum);
     cnt = wave_allsum(cnt);
@@ -321,7 +322,7 @@ __device__ __forceinline__ void grpo_group_stats(int wave, int waves, const floa
     }
     const double mean = sum / cnt;
     double var = 0.0;
-    for (int s = lane; s < n_seq; s += 64)
+    for (int64_t s = lane; s < n_seq; s += 64)
       if (gid[s] == g) { const double dlt = (double)rewards[s] - mean; var += dlt * dlt; }
     var = wave_allsum(var);
     if (lane == 0) {
@@ -336,14 +337,14 @@ __device__ __forceinline__ void grpo_group_stats(int wave, int waves, const floa
 //   A_s = (r_s - mean_g r) / (std_g r + adv_eps)
 // and the weight w_s = scale / (G_g |y_s|) of rollout s (0 for an empty rollout).  Validates
 // offsets and group ids like the OAPL kernel and records the status.
-__device__ __forceinline__ void grpo_advantage(int thread, int threads, const float* __restrict__ rewards,
+__device__ __forceinline__ void grpo_advantage(int64_t thread, int64_t threads, const float* __restrict__ rewards,
                                                const int32_t* __restrict__ gid, const int64_t* __restrict__ off,
                                                int n_seq, int n_groups, int64_t Ttok, double adv_eps, double scale,
                                                const double* gmean, const double* gstd, const double* gsize,
                                                float* __restrict__ adv, double* __restrict__ wseq,
                                                float* __restrict__ adv_out, int* err) {
   if (thread == 0 && (off[0] != 0 || off[n_seq] != Ttok)) record_batch_error(err, kErrOffsets);
-  for (int s = thread; s < n_seq; s += threads) {
+  for (int64_t s = thread; s < n_seq; s += threads) {
     if (off[s + 1] < off[s]) record_batch_error(err, kErrOffsets);
     const int g = gid[s];
     const bool ok = g >= 0 && g < n_groups;
@@ -360,11 +361,11 @@ __device__ __forceinline__ void grpo_advantage(int thread, int threads, const fl
 // rollout must end at most one panel after it starts: any rollout longer than `longest`
 // (or malformed offsets) raises the flag that sends the call down the two-pass path instead.
 // longest < 0: the call does not try the single sweep.
-__device__ __forceinline__ void sweep_plan(int thread, int threads, const int64_t* __restrict__ off, int n_seq,
+__device__ __forceinline__ void sweep_plan(int64_t thread, int64_t threads, const int64_t* __restrict__ off, int n_seq,
                                            int64_t Ttok, int64_t longest, int* flag) {
   if (longest < 0) return;
   bool bad = thread == 0 && (off[0] != 0 || off[n_seq] != Ttok);
-  for (int s = thread; s < n_seq; s += threads) {
+  for (int64_t s = thread; s < n_seq; s += threads) {
     const int64_t len = off[s + 1] - off[s];
     bad |= len < 0 || len > longest;
   }
