@@ -1,6 +1,8 @@
 """The fp32 path at the edges of its tiles: rows and columns one short of and past 64 and 128, hidden sizes that allow
 16-byte loads and odd ones, k shorter than a stage and split over many workgroups, one panel (logits kept) and several
 (logits computed again), tight workspaces.  Tolerances as in test_gpu_parity.py for fp32 inputs."""
+import math
+
 import pytest
 import torch
 
@@ -53,3 +55,18 @@ def test_scores_and_samples(T, d, V):
     assert abs(f64(lp) - (z.numpy()[range(T), y] - ref)).max() <= 1e-5
     assert abs(f64(ent) - orc.token_entropy(H, W)).max() <= 1e-5
     _check_samples(b.H, b.W, 0.7, 5, tok, sc)
+
+
+def test_entropy_of_equal_logits():
+    """All rows of W alike: a token's logits are one number z whatever its rounding, and its entropy is ln V.  In sums of z
+    taken as quads and then pairwise only 3z and 4z round (1.75 x 2^-24 of |z|, doublings are exact; exp(0) = 1, the rest is
+    double), plus half an ulp of the result.  A running sum over 32 rows is off by several times that."""
+    T, d, V = 1000, 8, 640
+    g = torch.Generator(device="cuda:0").manual_seed(3)
+    H = 30 * torch.randn(T, d, generator=g, device="cuda:0")
+    W = torch.randn(1, d, generator=g, device="cuda:0").expand(V, d).contiguous()
+    lp, ent, _ = oapl.logprob_fwd(H, W, torch.zeros(T, dtype=torch.int32, device="cuda:0"), want_entropy=True)
+    z = (H.double() @ W[0].double()).abs().cpu().numpy()
+    err = abs(f64(ent) - math.log(V))
+    assert z.max() > 100
+    assert (err <= 2.0 ** -24 * (1.75 * 1.0001 * z + math.log(V))).all()
