@@ -25,6 +25,10 @@
  *     the default stream).  No entry point synchronises with the host except
  *     oapl_read_device_status.
  *   - Inputs are never modified; outputs are fully overwritten.
+ *   - H and W may start at any element.  OAPL_BF16 operands that are not 16-byte
+ *     aligned are copied into the workspace first where the kernels would read
+ *     them in place (up to 8192 tokens); oapl_workspace_bytes has room for that,
+ *     and a call on aligned operands does with 2 V d + 2 T d bytes less.
  *   - `workspace` must hold at least oapl_workspace_bytes(...) bytes for the
  *     same sizes, aligned to 256 bytes (the loss calls also accept less or more,
  *     see oapl_workspace_bytes_for).  Its contents are scratch.  Two calls
@@ -101,7 +105,9 @@ size_t oapl_workspace_bytes(int64_t T, int32_t d, int32_t V, int32_t n_seq,
  *   - the panel size.  oapl_workspace_bytes uses the library's own (at most
  *     12288 rows for OAPL_BF16 -- the fastest measured -- and 4096 for
  *     OAPL_F32); max_panel_rows caps it lower (rounded down to whole 384-row
- *     tiles for OAPL_BF16, at least one tile; <= 0 or larger = the library's);
+ *     tiles for OAPL_BF16, at least one tile; <= 0 or larger = the library's).
+ *     Less than one tile asks for the least workspace there is: one-tile panels,
+ *     and no room for copies of OAPL_BF16 operands that are not 16-byte aligned;
  *   - the number of panel buffers (OAPL_BF16).  The single sweep finishes a
  *     panel's gradients only when every rollout touching it is scored, so it
  *     keeps a ring of panels: 1 + ceil(longest rollout / panel rows) buffers

@@ -17,6 +17,13 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
+// 16 bytes of a caller's bf16 matrix, which may start at any element.
+__device__ __forceinline__ u32x4 load_any16(const bf16_t* p) {
+  u32x4 v;
+  __builtin_memcpy(&v, p, sizeof(v));
+  return v;
+}
+
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr double kLn2 = 0.6931471805599453094;
 // "minus infinity" that survives (m - m) without producing NaN.

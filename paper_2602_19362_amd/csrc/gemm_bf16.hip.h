@@ -1318,6 +1318,13 @@ k_bwd_dw(const bf16_t* __restrict__ HTp, const bf16_t* __restrict__ GTp, int t_n
 // Packing of row-major matrices into the block layout the main loop reads.
 // ---------------------------------------------------------------------------
 
+// Aligned copy of a matrix that starts at any element: `pieces` of 16 bytes.  Bound by memory.
+__global__ void __launch_bounds__(256)
+k_copy_aligned(const bf16_t* __restrict__ src, int64_t pieces, bf16_t* __restrict__ dst) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < pieces; i += (int64_t)gridDim.x * 256)
+    ((u32x4*)dst)[i] = load_any16(src + i * 8);
+}
+
 // dst = packed(src), src [R, K] row-major with leading dimension ld (K and ld multiples of 8),
 // in blocks of `rb` rows (256 for an m-side operand, 384 for an n-side operand).  One workgroup
 // per block; blocks in [0, n_rt) x [0, n_kt); everything outside [0, R) x [0, K) is written as zero.
@@ -1331,13 +1338,13 @@ k_pack_rows(const bf16_t* __restrict__ src, int64_t R, int K, int64_t ld, bf16_t
     const int64_t r = rt * rb + row;
     const int k = kt * kPackK + c * 8;
     u32x4 v = {0u, 0u, 0u, 0u};
-    if (r < R && k < K) v = *(const u32x4*)(src + r * ld + k);
+    if (r < R && k < K) v = load_any16(src + r * ld + k);
     *(u32x4*)(out + row * 128 + c * 16) = v;
   }
 }
 
 // dst = packed(S^T), an m-side operand (256-row blocks), where S [R, Ccols] is row-major (ld; Ccols and ld
-// multiples of 8, rows 16-byte aligned) and optionally row-scaled:
+// multiples of 8) and optionally row-scaled:
 // dst row j (a column of S), k index r (a row of S): dst(j, r) = bf16(S[r][j] * scale[r]).
 // One workgroup per destination block (jt, kt): it reads S[kt*64 .. +64][jt*256 .. +256] in 16-byte
 // pieces (8 columns of one row), four consecutive rows per thread, turns each 4 x 8 patch into eight
@@ -1365,7 +1372,7 @@ k_pack_transposed(const bf16_t* __restrict__ src, int64_t R, int Ccols, int64_t 
       const int64_t r = r0 + 4 * rq + k;
       row[k] = u32x4{0u, 0u, 0u, 0u};
       if (r < R && j < Ccols) {
-        row[k] = *(const u32x4*)(src + r * ld + j);
+        row[k] = load_any16(src + r * ld + j);
         if (scale != nullptr) {
           const float sc = scale[r];
 #pragma unroll

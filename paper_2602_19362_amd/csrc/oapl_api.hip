@@ -39,8 +39,8 @@ typedef TileCfg<4, 1, 1, 2, 2> Cfg64;
 typedef TileCfg<4, 2, 1, 2, 2> Cfg128;
 typedef CfgSample Cfg256;
 typedef TileCfg<4, 2, 2, 5, 2> Cfg320;
-// The sweep's reference exponents: the first 256 vocabulary entries of 64 tokens.
-typedef TileCfg<4, 1, 2, 2, 4> CfgRef;
+// The sweep's reference exponents: the first 256 vocabulary entries of 64 tokens (a sixth of a packed block of H).
+typedef TileCfg<4, 1, 2, 2, 4, kPackRowsB> CfgRef;
 enum FwdTile { kTile64, kTile128, kTile256, kTile320, kTile384 };
 struct TilePick {
   FwdTile tile = kTile384;
@@ -78,6 +78,7 @@ struct Plan {
   int d = 0, V = 0, n_seq = 0, n_groups = 0, dtype = 0;
   bool bwd = false;
   bool rows = false;   // the kernels read W and H where they lie; else packed copies (and one of W^T) are made
+  unsigned unaligned = 0;   // ... but these (Unaligned) are copied to an aligned place first
   TilePick fwd;        // tile and vocabulary splits of the scoring kernel (splits = soft-max partials per token)
   bool small_sweep = false, small_dw = false;   // 128 x 128 tiles (one panel, operands in place)
   int n_vt = 0;        // vocabulary tiles of the sweep: row sums per token
@@ -93,7 +94,7 @@ struct Plan {
   int n_rb_v = 0;      // 384-row blocks of a matrix whose rows are the vocabulary (G^T)
   int64_t n_rt_T = 0;  // 384-row token tiles of the whole batch
   size_t off_status = 0, off_partials = 0, off_upart = 0, off_zy = 0, off_lse2 = 0, off_diff = 0, off_coef = 0, off_delta = 0,
-         off_cseq = 0, off_vstar = 0, off_gw = 0, off_omp = 0, off_inv = 0, off_Wp = 0, off_Hp = 0, off_WTp = 0, off_HTp = 0,
+         off_cseq = 0, off_vstar = 0, off_gw = 0, off_omp = 0, off_inv = 0, off_Wp = 0, off_Hp = 0, off_Wc = 0, off_Hc = 0, off_WTp = 0, off_HTp = 0,
          off_part = 0, off_G = 0, off_GT = 0, off_ref2 = 0, off_spart = 0, total = 0;
   bool sweep = false;  // single-sweep loss path available (bf16 with backward)
 };
@@ -227,12 +228,22 @@ static F32Pick pick_f32(int64_t M, int64_t N, int64_t K, int max_splits, size_t 
   return best;
 }
 
+// bf16 operands that are not 16-byte aligned.  The 16-byte direct-to-LDS loads of the in-place kernels want that; the packing
+// and gathering kernels use ordinary loads, which take any address.  Such an operand is copied first and the call goes on
+// as any other (W at d = 4096, V = 151936: 0.46 ms; sampling 64 tokens takes 0.69 ms, 1.68 when it packed every operand).
+enum Unaligned { kUnalignedW = 1, kUnalignedH = 2, kUnalignedAny = 3 };
+static unsigned unaligned_operands(int dtype, const void* H, const void* W) {
+  if (dtype != OAPL_BF16) return 0;
+  return (((uintptr_t)W & 15) != 0 ? kUnalignedW : 0) | (((uintptr_t)H & 15) != 0 ? kUnalignedH : 0);
+}
+
+// `unaligned`: which operands the plan has copies of (Unaligned; the workspace sizes that the library reports have both).
 // `panel_buffers`: how many panels the single sweep keeps before their gradient contractions run
 // (<= 0: two, the least for a batch of several panels; never more than the batch has panels).
 // `max_splits`: most vocabulary splits of the streaming kernels (fp32: splits of the gradient contractions); one gives the smallest workspace (see fit_splits): no
 // space that only buys speed.
 constexpr int kAnySplits = 1 << 30;
-static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, int dtype, bool bwd,
+static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, int dtype, bool bwd, unsigned unaligned,
                       int64_t max_panel_rows = 0, int64_t panel_buffers = 0, int64_t exact_panel_rows = 0,
                       int max_splits = kAnySplits) {
   if (T < 0 || d < 1 || V < 1 || n_seq < 0 || n_groups < 1) return false;
@@ -252,6 +263,7 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
     const int64_t n_tiles = (T + Cfg::BN - 1) / Cfg::BN;
     const int MT = (V + Cfg::BM - 1) / Cfg::BM;
     p.rows = rows_pay(T, d);
+    p.unaligned = p.rows ? unaligned : 0;
     p.fwd = p.rows ? pick_tile(T, V, max_splits, true) : pick_splits<Cfg>(kTile384, T, V, max_splits);
     p.smp = p.rows ? pick_tile(T, V, max_splits, false) : pick_splits<CfgSample>(kTile256, T, V, max_splits);
     // Panel size: a multiple of the token tile, at most `cap` rows.  One panel if T fits; otherwise
@@ -314,6 +326,8 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
       p.off_Hp = take(a > b ? a : b);
     }
   }
+  if (p.unaligned & kUnalignedW) p.off_Wc = take((size_t)V * d * 2);
+  if (p.unaligned & kUnalignedH) p.off_Hc = take(Tn * d * 2);
   if (bwd) {
     if (dtype == OAPL_BF16) {
       // the last panel's partial sums of dH: in the packed copy of W, which is dead by then, or in a space of their own
@@ -430,7 +444,8 @@ static bool prepare_kernels() {
          allow_big_lds(k_bwd_dw<CfgSmall>, CfgSmall::LDS_BYTES) && allow_big_lds(k_sweep<CfgSmall, true>, CfgSmall::LDS_BYTES) &&
                  allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
          allow_big_lds(k_sweep<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_sweep<Cfg, true>, Cfg::LDS_BYTES) &&
-         allow_big_lds(k_fwd_lse<CfgRef, false, true>, CfgRef::LDS_BYTES);
+         allow_big_lds(k_fwd_lse<CfgRef, false, true>, CfgRef::LDS_BYTES) &&
+         allow_big_lds(k_fwd_lse<CfgRef, false, false>, CfgRef::LDS_BYTES);
   });
   return ok;
 }
@@ -532,11 +547,25 @@ static int contract_f32(const F32Pick& pick, const F32Operand& A, const F32Opera
   return OAPL_OK;
 }
 
-// bf16: packed copies of W and H where the plan wants them.
-static int pack_operands(const Plan& p, const void* H, const void* W, char* ws, hipStream_t st) {
+// Aligned copies of the operands that the plan has copies of, which the call uses from here on.
+static int copy_unaligned(const Plan& p, const void*& H, const void*& W, char* ws, hipStream_t st) {
+  auto copy = [&](const void*& m, int64_t elements, size_t off) {
+    const int64_t pieces = elements / 8;
+    k_copy_aligned<<<(unsigned)(pieces < 256 * 65536 ? grid1d(pieces, 256) : 65536), 256, 0, st>>>((const bf16_t*)m, pieces,
+                                                                                                (bf16_t*)(ws + off));
+    m = ws + off;
+  };
+  if (p.unaligned & kUnalignedW) copy(W, (int64_t)p.V * p.d, p.off_Wc);
+  if (p.unaligned & kUnalignedH) copy(H, p.T * p.d, p.off_Hc);
+  OAPL_LAUNCH_CHECK();
+  return OAPL_OK;
+}
+
+// bf16: packed or aligned copies of W and H where the plan wants them.
+static int pack_operands(const Plan& p, const void*& H, const void*& W, char* ws, hipStream_t st) {
   if (p.T == 0 || p.dtype != OAPL_BF16) return OAPL_OK;
   if (!prepare_kernels()) return OAPL_ERR_HIP;
-  if (p.rows) return OAPL_OK;
+  if (p.rows) return copy_unaligned(p, H, W, ws, st);
   k_pack_rows<<<dim3(p.n_kt_d, p.n_rt_v), 256, 0, st>>>((const bf16_t*)W, p.V, p.d, p.d, (bf16_t*)(ws + p.off_Wp), p.n_kt_d,
                                                         Cfg::BM);
   OAPL_LAUNCH_CHECK();
@@ -791,8 +820,9 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
   if (int rc = pack_wt(p, W, ws, st, kNoGate)) return rc;
   // reference exponents: running maximum over the first 256 vocabulary entries, one workgroup per 64 tokens (a walk of
   // d / 64 k-blocks each, bound by their latency)
-  launch_fwd_lse<CfgRef, true>(FwdArgs{(const bf16_t*)W, (const bf16_t*)H, V < CfgRef::BM ? V : CfgRef::BM, T, d, p.n_kt_d,
-                                       TilePick{}}, sample, nullptr, nullptr, st, fast);
+  const FwdArgs ref{x.W, x.H, V < CfgRef::BM ? V : CfgRef::BM, T, d, p.n_kt_d, TilePick{}};
+  if (p.rows) launch_fwd_lse<CfgRef, true>(ref, sample, nullptr, nullptr, st, fast);
+  else launch_fwd_lse<CfgRef, false>(ref, sample, nullptr, nullptr, st, fast);
   OAPL_LAUNCH_CHECK();
   if (int rc = gather_logits(p, H, W, tokens, TokenInit{(float*)(ws + p.off_coef), sample, ref2, diff, nis}, ws, st)) return rc;
 
@@ -865,7 +895,7 @@ static int fit_splits(Plan& p, size_t have) {
   int limit = kAnySplits;
   for (int fewer : {8, 4, 2, 1}) {
     Plan q;
-    if (p.total <= have || !make_plan(q, p.T, p.d, p.V, p.n_seq, p.n_groups, p.dtype, p.bwd, 0, 0, 0, fewer)) break;
+    if (p.total <= have || !make_plan(q, p.T, p.d, p.V, p.n_seq, p.n_groups, p.dtype, p.bwd, p.unaligned, 0, 0, 0, fewer)) break;
     p = q;
     limit = fewer;
   }
@@ -882,9 +912,9 @@ static int fit_forward_plan(Plan& p, const void* ws, size_t have) {
 // the default panel (the fastest) if two buffers of it fit, else the largest that does.  Then as
 // many panel buffers as fit (and the batch has panels): they decide how long a rollout the single
 // sweep serves, not how fast it runs.
-static int fit_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, int dtype, bool bwd, const void* ws,
-                    size_t have) {
-  if (!make_plan(p, T, d, V, n_seq, n_groups, dtype, bwd)) return OAPL_ERR_SHAPE;
+static int fit_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, int dtype, bool bwd, unsigned unaligned,
+                    const void* ws, size_t have) {
+  if (!make_plan(p, T, d, V, n_seq, n_groups, dtype, bwd, unaligned)) return OAPL_ERR_SHAPE;
   if (!bwd) return fit_forward_plan(p, ws, have);
   if (ws == nullptr || ((uintptr_t)ws & 255) != 0) return OAPL_ERR_WORKSPACE;
   const int max_splits = fit_splits(p, have);
@@ -893,7 +923,7 @@ static int fit_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, i
     bool found = false;
     for (int64_t rows = (p.Tp - 1) / step * step; rows >= step && !found; rows -= step) {
       Plan q;
-      if (make_plan(q, T, d, V, n_seq, n_groups, dtype, bwd, rows, 0, 0, max_splits) && q.total <= have) {
+      if (make_plan(q, T, d, V, n_seq, n_groups, dtype, bwd, unaligned, rows, 0, 0, max_splits) && q.total <= have) {
         p = q;
         found = true;
       }
@@ -905,7 +935,9 @@ static int fit_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, i
     const int64_t extra = (int64_t)((have - p.total) / per_buffer);
     if (extra > 0) {
       Plan q;
-      if (make_plan(q, T, d, V, n_seq, n_groups, dtype, bwd, p.Tp, p.n_buf + extra, p.Tp, max_splits) && q.total <= have) p = q;
+      if (make_plan(q, T, d, V, n_seq, n_groups, dtype, bwd, unaligned, p.Tp, p.n_buf + extra, p.Tp, max_splits) &&
+          q.total <= have)
+        p = q;
     }
   }
   return OAPL_OK;
@@ -930,7 +962,8 @@ static int loss_impl(const void* H, const void* W, const int32_t* tokens, const 
   if (flags & ~(uint32_t)OAPL_FLAG_TWO_PASS) return OAPL_ERR_SHAPE;
   const bool bwd = (dH != nullptr) || (dW != nullptr);
   Plan p;
-  if (!make_plan(p, T, d, V, n_seq, n_groups, dtype, bwd)) return OAPL_ERR_SHAPE;
+  const unsigned unaligned = unaligned_operands(dtype, H, W);
+  if (!make_plan(p, T, d, V, n_seq, n_groups, dtype, bwd, unaligned)) return OAPL_ERR_SHAPE;
   // gradients come as a pair; an empty batch has no dH rows, so its pointer may be NULL
   if (!W || !seq_offsets || !loss_out || (bwd && (!dW || (T > 0 && !dH)))) return OAPL_ERR_NULL;
   if (T > 0 && (!H || !tokens || !logq)) return OAPL_ERR_NULL;
@@ -938,7 +971,7 @@ static int loss_impl(const void* H, const void* W, const int32_t* tokens, const 
   if (!(beta_value > 0.f) || !(beta_loss > 0.f) || !isfinite(beta_value) || !isfinite(beta_loss) ||
       !isfinite(loss_scale))
     return OAPL_ERR_BETA;
-  if (int rc = fit_plan(p, T, d, V, n_seq, n_groups, dtype, bwd, workspace, workspace_bytes)) return rc;
+  if (int rc = fit_plan(p, T, d, V, n_seq, n_groups, dtype, bwd, unaligned, workspace, workspace_bytes)) return rc;
   if (checks_only) return OAPL_OK;
 
   hipStream_t st = (hipStream_t)stream;
@@ -983,13 +1016,14 @@ static int grpo_impl(const void* H, const void* W, const int32_t* tokens, const 
   if (flags & ~(uint32_t)OAPL_FLAG_TWO_PASS) return OAPL_ERR_SHAPE;
   const bool bwd = (dH != nullptr) || (dW != nullptr);
   Plan p;
-  if (!make_plan(p, T, d, V, n_seq, n_groups, dtype, bwd)) return OAPL_ERR_SHAPE;
+  const unsigned unaligned = unaligned_operands(dtype, H, W);
+  if (!make_plan(p, T, d, V, n_seq, n_groups, dtype, bwd, unaligned)) return OAPL_ERR_SHAPE;
   if (!W || !seq_offsets || !loss_out || (bwd && (!dW || (T > 0 && !dH)))) return OAPL_ERR_NULL;
   if (T > 0 && (!H || !tokens || !logq || !logp_old)) return OAPL_ERR_NULL;
   if (n_seq > 0 && (!rewards || !group_ids)) return OAPL_ERR_NULL;
   if (!(clip_eps >= 0.f) || !(clip_eps < 1.f) || !(adv_eps >= 0.f) || !isfinite(adv_eps) || !isfinite(loss_scale))
     return OAPL_ERR_BETA;
-  if (int rc = fit_plan(p, T, d, V, n_seq, n_groups, dtype, bwd, workspace, workspace_bytes)) return rc;
+  if (int rc = fit_plan(p, T, d, V, n_seq, n_groups, dtype, bwd, unaligned, workspace, workspace_bytes)) return rc;
 
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
@@ -1078,7 +1112,7 @@ const char* oapl_status_string(int32_t status) {
 size_t oapl_workspace_bytes(int64_t T, int32_t d, int32_t V, int32_t n_seq, int32_t n_groups, int32_t dtype,
                             int32_t with_backward) {
   Plan p;
-  if (!make_plan(p, T, d, V, n_seq, n_groups, dtype, with_backward != 0)) return 0;
+  if (!make_plan(p, T, d, V, n_seq, n_groups, dtype, with_backward != 0, kUnalignedAny)) return 0;
   return p.total;
 }
 
@@ -1086,18 +1120,20 @@ size_t oapl_workspace_bytes_for(int64_t T, int32_t d, int32_t V, int32_t n_seq, 
                                 int32_t with_backward, int64_t max_panel_rows, int64_t max_rollout_len,
                                 int64_t* panel_rows_out, int32_t* panel_buffers_out) {
   Plan p, full;
-  if (!make_plan(p, T, d, V, n_seq, n_groups, dtype, with_backward != 0, max_panel_rows)) return 0;
-  if (!make_plan(full, T, d, V, n_seq, n_groups, dtype, with_backward != 0)) return 0;
+  // fewer rows than a tile ask for the least workspace there is: no room for copies of operands that are not aligned
+  const unsigned copies = max_panel_rows > 0 && max_panel_rows < Cfg::BN ? 0 : kUnalignedAny;
+  if (!make_plan(p, T, d, V, n_seq, n_groups, dtype, with_backward != 0, copies, max_panel_rows)) return 0;
+  if (!make_plan(full, T, d, V, n_seq, n_groups, dtype, with_backward != 0, copies)) return 0;
   // who asks for less than the library's own panels gets the least that does the work in panels of that size
   if (p.Tp < full.Tp)
-    make_plan(p, T, d, V, n_seq, n_groups, dtype, with_backward != 0, max_panel_rows, 0, 0, 1);
+    make_plan(p, T, d, V, n_seq, n_groups, dtype, with_backward != 0, copies, max_panel_rows, 0, 0, 1);
   // Buffers for the longest rollout, 1 + ceil(len / panel): only at the library's own panel size.  A
   // loss call derives its plan from the byte count alone, and k buffers of a smaller panel could not
   // be told from two buffers of a panel k / 2 times as large (which it prefers: larger panels are faster).
   if (max_rollout_len > p.Tp && p.n_buf >= 2 && p.Tp == full.Tp) {
     const int64_t want = 1 + (max_rollout_len + p.Tp - 1) / p.Tp;
     Plan q;
-    if (!make_plan(q, T, d, V, n_seq, n_groups, dtype, with_backward != 0, p.Tp, want, p.Tp)) return 0;
+    if (!make_plan(q, T, d, V, n_seq, n_groups, dtype, with_backward != 0, copies, p.Tp, want, p.Tp)) return 0;
     p = q;
   }
   if (panel_rows_out) *panel_rows_out = p.Tp;
@@ -1110,7 +1146,7 @@ int32_t oapl_logprob_fwd(const void* H, const void* W, const int32_t* tokens, in
                          size_t workspace_bytes, void* stream) {
   if (dtype != OAPL_F32 && dtype != OAPL_BF16) return OAPL_ERR_DTYPE;
   Plan p;
-  if (!make_plan(p, T, d, V, 0, 1, dtype, false)) return OAPL_ERR_SHAPE;
+  if (!make_plan(p, T, d, V, 0, 1, dtype, false, unaligned_operands(dtype, H, W))) return OAPL_ERR_SHAPE;
   if (!W) return OAPL_ERR_NULL;
   if (T > 0 && (!H || !tokens || !logprob_out)) return OAPL_ERR_NULL;
   if (int rc = fit_forward_plan(p, workspace, workspace_bytes)) return rc;
@@ -1133,7 +1169,7 @@ int32_t oapl_sample_tokens(const void* H, const void* W, int64_t T, int32_t d, i
                            size_t workspace_bytes, void* stream) {
   if (dtype != OAPL_F32 && dtype != OAPL_BF16) return OAPL_ERR_DTYPE;
   Plan p;
-  if (!make_plan(p, T, d, V, 0, 1, dtype, false)) return OAPL_ERR_SHAPE;
+  if (!make_plan(p, T, d, V, 0, 1, dtype, false, unaligned_operands(dtype, H, W))) return OAPL_ERR_SHAPE;
   if (!W) return OAPL_ERR_NULL;
   if (T > 0 && (!H || !tokens_out)) return OAPL_ERR_NULL;
   if (!(temperature > 0.f) || !isfinite(temperature)) return OAPL_ERR_BETA;
@@ -1150,6 +1186,7 @@ int32_t oapl_sample_tokens(const void* H, const void* W, int64_t T, int32_t d, i
   const float inv_t = 1.0f / temperature;
   if (dtype == OAPL_BF16) {
     if (!prepare_kernels()) return OAPL_ERR_HIP;
+    if (int rc = copy_unaligned(p, H, W, ws, st)) return rc;
     FwdArgs args{(const bf16_t*)W, (const bf16_t*)H, V, T, d, p.n_kt_d, p.smp};
     if (!p.rows) {
       bf16_t* Wp = (bf16_t*)(ws + p.off_Wp);

@@ -23,8 +23,8 @@ __global__ void k_fill_f32(float* p, int64_t n, float v, Gate gate) {
 // z_{t, y_t} = sum_k H[t][k] * W[y_t][k]: one wavefront per token, the gathered
 // W row is read with the index exactly as given (checked against [0, V)).
 // ACC is double for fp32 inputs and float for bf16 inputs (whose products are
-// exact in fp32).  VEC elements per load: 16 bytes when rows are 16-byte aligned (bf16 always, fp32 if d is a
-// multiple of 4), else one.  Reads 2 rows per token and is bound by the latency of a wavefront's chain of loads:
+// exact in fp32).  VEC elements per load: 16 bytes, or one for fp32 rows that are not
+// 16-byte aligned.  Reads 2 rows per token and is bound by the latency of a wavefront's chain of loads:
 // element by element it took 33 us for 777 tokens at d = 4096 (64 loads in a row per lane) and 82 us for 32768 at
 // d = 2048, by 16-byte loads 8.5 and 42 us.
 //
@@ -47,7 +47,7 @@ template <class T, class ACC, int VEC>
 __global__ void __launch_bounds__(256)
 k_gather_logit(const T* __restrict__ H, const T* __restrict__ W, const int32_t* __restrict__ tokens,
                int64_t Ttok, int d, int V, float* __restrict__ zy, int* __restrict__ err, TokenInit init) {
-  typedef T vec_t __attribute__((ext_vector_type(VEC)));
+  typedef T vec_t __attribute__((ext_vector_type(VEC), aligned(sizeof(T))));   // bf16 rows may start at any element
   const int lane = threadIdx.x & 63;
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= Ttok) return;

@@ -9,9 +9,18 @@
 int main() {
   char line[256];
   while (std::fgets(line, sizeof line, stdin)) {
-    int n_seq = 0, n_groups = 0;
+    int n_seq = 0, n_groups = 0, d = 0, V = 0, dtype = 0, bwd = 0;
+    long long T = 0, cap = 0, have = 0;
+    unsigned unaligned = 0;
     if (std::sscanf(line, "begin %d %d", &n_seq, &n_groups) == 2) {
       std::printf("one=%d grid=%u\n", begin_in_one_launch(n_seq, n_groups) ? 1 : 0, begin_grid(n_seq, n_groups));
+    } else if (std::sscanf(line, "plan %lld %d %d %d %d %lld %u %lld", &T, &d, &V, &dtype, &bwd, &cap, &unaligned, &have) == 8) {
+      // the plan of a call of one rollout on `have` bytes (< 0: what the library asks for with panels of `cap` rows)
+      if (have < 0) have = (long long)oapl_workspace_bytes_for(T, d, V, 1, 1, dtype, bwd, cap, 0, nullptr, nullptr);
+      Plan p;
+      const int rc = fit_plan(p, T, d, V, 1, 1, dtype, bwd != 0, unaligned, (void*)(uintptr_t)256, (size_t)have);
+      std::printf("rc=%d have=%lld total=%lld rows=%d copies=%u panel=%lld buffers=%d\n", rc, have, (long long)p.total,
+                  p.rows ? 1 : 0, p.unaligned, (long long)p.Tp, p.n_buf);
     } else {
       std::printf("unknown query\n");
       return 1;

@@ -1,4 +1,5 @@
 """The library's host decisions, host side only: launch grids and plans."""
+from paper_2602_19362_amd import oapl
 from tests._plan import ask
 
 INT_MAX = 2 ** 31 - 1
@@ -14,3 +15,17 @@ def test_first_launch_indices_fit_32_bits():
         assert 1 <= a["grid"] * 256 <= INT_MAX, (n_seq, n_groups, a)
         if max(n_seq, 64 * n_groups) <= 1 << 22:
             assert a["grid"] * 256 >= n_seq and a["grid"] * 4 >= n_groups, (n_seq, n_groups, a)
+
+
+def test_operands_that_are_not_aligned_have_room_for_an_aligned_copy():
+    """The kernels that read bf16 W and H in place want them 16-byte aligned: a call whose operands are not copies them
+    first, within the workspace the library asks for; one whose operands are needs no such space."""
+    for T, d, V in [(1, 8, 8), (64, 4096, 151936), (777, 2048, 3000), (8192, 64, 1000), (4000, 72, 5003), (0, 64, 100)]:
+        for bwd in (0, 1):
+            nbytes = oapl.workspace_bytes(T, d, V, 1, 1, oapl.OAPL_BF16, bool(bwd))
+            plans = ask([f"plan {T} {d} {V} 1 {bwd} 0 {u} -1" for u in range(4)])
+            assert [(p["rc"], p["rows"], p["copies"], p["have"]) for p in plans] == [(0, 1, u, nbytes) for u in range(4)]
+            assert nbytes >= plans[0]["total"] + 2 * V * d + 2 * T * d
+    # packed operands are copies already, and fp32 takes any address
+    for q in ("plan 8193 64 1000 1 1 0 3 -1", "plan 4097 72 1000 1 1 0 3 -1", "plan 300 72 1000 0 1 0 0 -1"):
+        assert ask([q])[0]["copies"] == 0
