@@ -93,7 +93,7 @@ struct Plan {
   int n_rt_v = 0, n_rt_d = 0, n_kt_d = 0, n_kt_v = 0, n_kt_g = 0, n_kt_t = 0;
   int n_rb_v = 0;      // 384-row blocks of a matrix whose rows are the vocabulary (G^T)
   int64_t n_rt_T = 0;  // 384-row token tiles of the whole batch
-  size_t off_status = 0, off_partials = 0, off_upart = 0, off_zy = 0, off_lse2 = 0, off_diff = 0, off_coef = 0, off_delta = 0,
+  size_t off_status = 0, off_partials = 0, off_fwd_partials = 0, off_upart = 0, off_zy = 0, off_lse2 = 0, off_diff = 0, off_coef = 0, off_delta = 0,
          off_cseq = 0, off_vstar = 0, off_gw = 0, off_omp = 0, off_inv = 0, off_Wp = 0, off_Hp = 0, off_Wc = 0, off_Hc = 0, off_WTp = 0, off_HTp = 0,
          off_part = 0, off_G = 0, off_GT = 0, off_ref2 = 0, off_spart = 0, total = 0;
   bool sweep = false;  // single-sweep loss path available (bf16 with backward)
@@ -160,6 +160,10 @@ static TilePick pick_tile(int64_t T, int V, int max_splits, bool scoring) {
   const TilePick p320 = pick_splits<Cfg320>(kTile320, T, V, max_splits, 126.0, &t320);
   const TilePick p384 = pick_splits<Cfg>(kTile384, T, V, max_splits, 150.0, &t384);
   return t384 <= t320 && t384 <= t256 ? p384 : t320 <= t256 ? p320 : p256;
+}
+
+static TilePick pick_fwd(bool rows, int64_t T, int V, int max_splits) {
+  return rows ? pick_tile(T, V, max_splits, true) : pick_splits<Cfg>(kTile384, T, V, max_splits);
 }
 
 // Time of `tiles` tiles with nk k-blocks each, in k-blocks of a 256 x 384 tile (1.5 .. 2 us): rounds of workgroups, with
@@ -240,8 +244,8 @@ static unsigned unaligned_operands(int dtype, const void* H, const void* W) {
 // `unaligned`: which operands the plan has copies of (Unaligned; the workspace sizes that the library reports have both).
 // `panel_buffers`: how many panels the single sweep keeps before their gradient contractions run
 // (<= 0: two, the least for a batch of several panels; never more than the batch has panels).
-// `max_splits`: most vocabulary splits of the streaming kernels (fp32: splits of the gradient contractions); one gives the smallest workspace (see fit_splits): no
-// space that only buys speed.
+// `max_splits`: most vocabulary splits of the streaming kernels of a call without gradients, most splits of k of the gradient
+// contractions of one with gradients.  One gives the smallest workspace (see fit_splits).
 constexpr int kAnySplits = 1 << 30;
 static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, int dtype, bool bwd, unsigned unaligned,
                       int64_t max_panel_rows = 0, int64_t panel_buffers = 0, int64_t exact_panel_rows = 0,
@@ -264,7 +268,7 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
     const int MT = (V + Cfg::BM - 1) / Cfg::BM;
     p.rows = rows_pay(T, d);
     p.unaligned = p.rows ? unaligned : 0;
-    p.fwd = p.rows ? pick_tile(T, V, max_splits, true) : pick_splits<Cfg>(kTile384, T, V, max_splits);
+    if (!bwd) p.fwd = pick_fwd(p.rows, T, V, max_splits);
     p.smp = p.rows ? pick_tile(T, V, max_splits, false) : pick_splits<CfgSample>(kTile256, T, V, max_splits);
     // Panel size: a multiple of the token tile, at most `cap` rows.  One panel if T fits; otherwise
     // the size (between half the cap and the cap) that costs the fewest rounds of kNumCU workgroups in
@@ -304,8 +308,10 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
   auto take = [&](size_t bytes) { size_t at = o; o += (bytes + 255) / 256 * 256; return at; };
   const size_t Tn = (size_t)(T > 0 ? T : 1);
   p.off_status = take(kStatusWords * 4);
-  // (a call with gradients neither samples nor returns entropies)
+  // (a call with gradients neither samples nor returns entropies; its bf16 scoring pass, which comes before a panel is filled
+  // or after all are consumed, has its partials in the panel buffers, see below)
   p.off_partials = take(Tn * (size_t)(bwd || p.fwd.splits > p.smp.splits ? p.fwd.splits : p.smp.splits) * 8);
+  p.off_fwd_partials = p.off_partials;
   p.off_upart = take(bwd ? 0 : Tn * (size_t)p.fwd.splits * 4);
   p.off_zy = take(Tn * 4);
   p.off_lse2 = take(Tn * 4);
@@ -351,6 +357,11 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
       p.size_GT = ((size_t)p.n_rb_v * p.n_kt_t * kPackBlockBytesB + 255) / 256 * 256;
       p.off_G = take(p.size_G * p.n_buf);
       p.off_GT = take(p.size_GT * p.n_buf);
+      // as many vocabulary splits as that space takes, so small panels do not leave the scoring pass short of workgroups
+      // (two passes over 16411 tokens at d = 4096 in panels of 6144: 66 ms, 113 ms with one split)
+      const size_t room = (p.size_G + p.size_GT) * p.n_buf / (Tn * 8);
+      p.fwd = pick_fwd(p.rows, T, V, room < (size_t)kAnySplits ? (room > 1 ? (int)room : 1) : kAnySplits);
+      if (p.fwd.splits > 1) p.off_fwd_partials = p.off_G;
       // single-sweep path: reference exponents and per-vocabulary-tile row sums of one panel
       p.sweep = true;
       p.off_ref2 = take(Tn * 4);
@@ -609,7 +620,7 @@ static int forward_partials(const Plan& p, const void* H, const void* W, bool en
                             hipStream_t st, Gate gate) {
   const int64_t T = p.T;
   if (T == 0) return OAPL_OK;
-  float2* partials = (float2*)(ws + p.off_partials);
+  float2* partials = (float2*)(ws + p.off_fwd_partials);
   float* upart = entropy ? (float*)(ws + p.off_upart) : nullptr;
   if (p.dtype == OAPL_BF16) {
     const ContractD x = contract_d(p, H, W, ws);
@@ -635,7 +646,7 @@ static int forward_finish(const Plan& p, const float* logq, float* logprob_out, 
   const bool loss = logq != nullptr;
   const int slices = finish_slices(p.fwd.splits);
   (p.dtype == OAPL_BF16 ? k_lse_finish<true> : k_lse_finish<false>)<<<grid1d(T, 256 / slices), 256, 0, st>>>(
-      (const float2*)(ws + p.off_partials), p.fwd.splits, T, (const float*)(ws + p.off_zy), logq, logprob_out, lse_out,
+      (const float2*)(ws + p.off_fwd_partials), p.fwd.splits, T, (const float*)(ws + p.off_zy), logq, logprob_out, lse_out,
       loss ? (float*)(ws + p.off_lse2) : nullptr, loss ? (double*)(ws + p.off_diff) : nullptr,
       loss ? (float*)(ws + p.off_omp) : nullptr, loss ? (float*)(ws + p.off_inv) : nullptr,
       entropy_out ? (const float*)(ws + p.off_upart) : nullptr, entropy_out, slices, gate);
@@ -892,12 +903,27 @@ static int two_pass_path(const Plan& p, const void* H, const void* W, const int3
 // most of a small head's workspace.  They only buy speed: a workspace that is too small for them is served with fewer, the
 // least with none.  Returns the limit the plan was made with.
 static int fit_splits(Plan& p, size_t have) {
-  int limit = kAnySplits;
-  for (int fewer : {8, 4, 2, 1}) {
+  auto fewer = [&](int limit) {
     Plan q;
-    if (p.total <= have || !make_plan(q, p.T, p.d, p.V, p.n_seq, p.n_groups, p.dtype, p.bwd, p.unaligned, 0, 0, 0, fewer)) break;
+    if (!make_plan(q, p.T, p.d, p.V, p.n_seq, p.n_groups, p.dtype, p.bwd, p.unaligned, 0, 0, 0, limit)) return false;
     p = q;
-    limit = fewer;
+    return true;
+  };
+  int limit = kAnySplits;
+  if (p.bwd) {
+    for (int next : {8, 4, 2, 1}) {
+      if (p.total <= have || !fewer(next)) break;
+      limit = next;
+    }
+  } else if (p.dtype == OAPL_BF16) {
+    // a split less frees 12 bytes per token at most
+    while (p.total > have && limit > 1) {
+      const int64_t now = p.fwd.splits > p.smp.splits ? p.fwd.splits : p.smp.splits, per = (p.T > 0 ? p.T : 1) * 12;
+      const int64_t left = now - ((int64_t)(p.total - have) + per - 1) / per;
+      const int next = (int)(left < 1 ? 1 : left < now ? left : now - 1);
+      if (!fewer(next)) break;
+      limit = next;
+    }
   }
   return limit;
 }

@@ -19,8 +19,9 @@ int main() {
       if (have < 0) have = (long long)oapl_workspace_bytes_for(T, d, V, 1, 1, dtype, bwd, cap, 0, nullptr, nullptr);
       Plan p;
       const int rc = fit_plan(p, T, d, V, 1, 1, dtype, bwd != 0, unaligned, (void*)(uintptr_t)256, (size_t)have);
-      std::printf("rc=%d have=%lld total=%lld rows=%d copies=%u panel=%lld buffers=%d\n", rc, have, (long long)p.total,
-                  p.rows ? 1 : 0, p.unaligned, (long long)p.Tp, p.n_buf);
+      std::printf("rc=%d have=%lld total=%lld rows=%d copies=%u panel=%lld buffers=%d fwd_tile=%d fwd_splits=%d "
+                  "smp_splits=%d\n", rc, have, (long long)p.total, p.rows ? 1 : 0, p.unaligned, (long long)p.Tp, p.n_buf,
+                  (int)p.fwd.tile, p.fwd.splits, p.smp.splits);
     } else {
       std::printf("unknown query\n");
       return 1;

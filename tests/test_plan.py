@@ -29,3 +29,25 @@ def test_operands_that_are_not_aligned_have_room_for_an_aligned_copy():
     # packed operands are copies already, and fp32 takes any address
     for q in ("plan 8193 64 1000 1 1 0 3 -1", "plan 4097 72 1000 1 1 0 3 -1", "plan 300 72 1000 0 1 0 0 -1"):
         assert ask([q])[0]["copies"] == 0
+
+
+def test_small_panels_leave_the_scoring_pass_its_workgroups():
+    """The two-pass schedule's scoring pass covers the whole batch whatever the panels: a cap on the panel does not cut its
+    vocabulary splits (its partial sums have the panel buffers for their space)."""
+    for T, d, V, cap in [(16411, 4096, 151936, 6144), (16411, 4096, 151936, 384), (30011, 5120, 151936, 6144),
+                         (3000, 4096, 151936, 384), (3000, 1024, 32000, 768), (1000, 72, 9001, 1), (140897, 4096, 151936, 768)]:
+        full, capped = ask([f"plan {T} {d} {V} 1 1 {c} 0 -1" for c in (0, cap)])
+        assert capped["rc"] == 0 and capped["panel"] < full["panel"] and capped["have"] < full["have"]
+        assert (capped["fwd_tile"], capped["fwd_splits"]) == (full["fwd_tile"], full["fwd_splits"])
+
+
+def test_a_few_missing_bytes_cost_a_few_splits():
+    """Scoring and sampling of few tokens, where a workgroup is a split, on less than the workspace asked for."""
+    for T, d, V in [(64, 4096, 151936), (1, 8, 60000), (120, 2048, 151936)]:
+        full = ask([f"plan {T} {d} {V} 1 0 0 0 -1"])[0]
+        splits = max(full["fwd_splits"], full["smp_splits"])
+        for part in (0.99, 0.75, 0.5, 0.1):
+            have = int(full["total"] - (1 - part) * splits * T * 12)
+            p = ask([f"plan {T} {d} {V} 1 0 0 0 {have}"])[0]
+            assert p["rc"] == 0 and p["total"] <= have
+            assert min(p["fwd_splits"], p["smp_splits"]) >= part * splits - 512 / T - 2, (T, part, full, p)
