@@ -520,13 +520,16 @@ static F32Operand f32_operand(const void* p, int64_t ld) {
   return F32Operand{(const float*)p, ld, ld % 4 == 0 && ((uintptr_t)p & 15) == 0};
 }
 
-// Logits of T token rows (transposed: M = vocabulary), in whatever form the epilogue leaves them.  128 x 128 tiles where
-// they give every CU one, else 64 x 128.
+// 128 x 128 tiles of the logits where they give every CU one, else 64 x 128.
+static bool logits_large_f32(int V, int64_t T) {
+  return (int64_t)grid1d(V, F32Large::BM) * grid1d(T, F32Large::BN) >= kNumCU;
+}
+
+// Logits of T token rows (transposed: M = vocabulary), in whatever form the epilogue leaves them.
 template <class Epi>
 static void launch_logits_f32(const Plan& p, const void* H, const void* W, int64_t T, Epi epi, hipStream_t st) {
   const F32Operand A = f32_operand(W, p.d), B = f32_operand(H, p.d);
-  const int64_t tiles = (int64_t)grid1d(p.V, F32Large::BM) * grid1d(T, F32Large::BN);
-  if (tiles >= kNumCU)
+  if (logits_large_f32(p.V, T))
     k_gemm_f32<F32Large, true, true><<<dim3(grid1d(p.V, F32Large::BM), grid1d(T, F32Large::BN)), 256, 0, st>>>(
         A, B, (int64_t)p.V, T, (int64_t)p.d, epi);
   else

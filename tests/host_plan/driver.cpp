@@ -6,6 +6,11 @@
 
 #include "../../paper_2602_19362_amd/csrc/oapl_api.hip"
 
+// workgroups of a contraction with an M x N result (one split of k)
+static long long groups(bool small, int64_t M, int64_t N) {
+  return (long long)(small ? tile_count<CfgSmall>(M, N) : tile_count<Cfg>(M, N));
+}
+
 int main() {
   char line[256];
   while (std::fgets(line, sizeof line, stdin)) {
@@ -19,9 +24,17 @@ int main() {
       if (have < 0) have = (long long)oapl_workspace_bytes_for(T, d, V, 1, 1, dtype, bwd, cap, 0, nullptr, nullptr);
       Plan p;
       const int rc = fit_plan(p, T, d, V, 1, 1, dtype, bwd != 0, unaligned, (void*)(uintptr_t)256, (size_t)have);
-      std::printf("rc=%d have=%lld total=%lld rows=%d copies=%u panel=%lld buffers=%d fwd_tile=%d fwd_splits=%d "
-                  "smp_splits=%d\n", rc, have, (long long)p.total, p.rows ? 1 : 0, p.unaligned, (long long)p.Tp, p.n_buf,
-                  (int)p.fwd.tile, p.fwd.splits, p.smp.splits);
+      std::printf("rc=%d have=%lld total=%lld rows=%d copies=%u panel=%lld buffers=%d fwd_tile=%d fwd_splits=%d smp_splits=%d",
+                  rc, have, (long long)p.total, p.rows ? 1 : 0, p.unaligned, (long long)p.Tp, p.n_buf, (int)p.fwd.tile,
+                  p.fwd.splits, p.smp.splits);
+      const int64_t last = T > 0 ? T - (T - 1) / p.Tp * p.Tp : 0;   // rows of the last panel
+      if (dtype == OAPL_BF16)
+        std::printf(" small_sweep=%d small_dw=%d dh_small=%d dh_splits=%d sweep_groups=%lld dw_groups=%lld dh_groups=%lld\n",
+                    p.small_sweep, p.small_dw, p.dh.small, p.dh.splits, groups(p.small_sweep, V, last),
+                    groups(p.small_dw, d, V), groups(p.dh.small, d, last) * p.dh.splits);
+      else
+        std::printf(" logits_large=%d dh_large=%d dh_splits=%d dw_large=%d dw_splits=%d\n",
+                    logits_large_f32(V, T < p.Tp ? T : p.Tp), p.f32_dh.large, p.f32_dh.splits, p.f32_dw.large, p.f32_dw.splits);
     } else {
       std::printf("unknown query\n");
       return 1;

@@ -1,6 +1,7 @@
 """The fp32 path at the edges of its tiles: rows and columns one short of and past 64 and 128, hidden sizes that allow
 16-byte loads and odd ones, k shorter than a stage and split over many workgroups, one panel (logits kept) and several
-(logits computed again), tight workspaces.  Tolerances as in test_gpu_parity.py for fp32 inputs."""
+(logits computed again), tight workspaces; 64 x 64 and 128 x 128 tiles, split and not, in each contraction.  Tolerances as
+in test_gpu_parity.py for fp32 inputs; test_plan.py checks that the plan of each case is the one named here."""
 import math
 
 import pytest
@@ -14,18 +15,32 @@ from tests.test_gpu_parity import _check, _check_samples, _custom_batch, _run
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d,V,lens,cap", [
-    (1, 1, [1], 0),                    # a single logit
-    (3, 63, [30, 33], 0),
-    (16, 64, [64], 0),
-    (33, 65, [60, 5], 0),              # no 16-byte loads
-    (64, 129, [100, 28], 0),
-    (65, 127, [100, 27], 0),
-    (128, 2049, [120, 9], 0),          # few tiles, long k: many splits
-    (36, 9001, [150, 107], 0),         # 128 x 128 logits tiles
-    (20, 700, [70, 60, 0, 63], 100),   # panels of 100 rows: logits computed again, ragged last panel
-    (21, 700, [70, 60, 0, 62], 64),
-])
+CASES = [   # d, V, rollout lengths, panel cap, what the plan has to say
+    (1, 1, [1], 0, {}),                    # a single logit
+    (3, 63, [30, 33], 0, {}),
+    (16, 64, [64], 0, {}),
+    (33, 65, [60, 5], 0, {}),              # no 16-byte loads
+    (64, 129, [100, 28], 0, {}),
+    (65, 127, [100, 27], 0, {}),
+    (128, 2049, [120, 9], 0, dict(dh_large=0, dh_splits=32)),      # few tiles, long k: many splits
+    (36, 9001, [150, 107], 0, dict(logits_large=0, dh_splits=51)),   # not quite enough tokens for 128 x 128 logits tiles
+    (37, 9001, [150, 150, 150, 63], 0, dict(logits_large=1)),      # one token past a tile
+    (768, 8192, [150] * 10 + [1], 0, dict(logits_large=1, dh_large=1, dh_splits=7, dw_large=1, dw_splits=2)),
+    (767, 8191, [150] * 10 + [1], 0, dict(logits_large=1, dh_large=1, dh_splits=7, dw_large=1, dw_splits=2)),
+    (67, 994, [150] * 18 + [68], 0, dict(dh_large=1, dh_splits=11, dw_large=0, dw_splits=8)),
+    (72, 4200, [150] * 4 + [107], 0, dict(dh_large=0, dw_large=1, dw_splits=7)),
+    (726, 104, [150] * 18 + [71], 0, dict(dh_large=1, dh_splits=1)),
+    (71, 17140, [40, 31], 0, dict(dh_splits=64, dw_large=1, dw_splits=1)),
+    # panels of 64 rows (what a workspace for 100 serves): logits computed again, ragged last panel
+    (20, 700, [70, 60, 0, 63], 100, dict(panel=64)),
+    (21, 700, [70, 60, 0, 62], 64, dict(panel=64)),
+    (155, 11026, [60, 35], 73, dict(panel=64, dw_large=1)),        # 128 x 128 tiles of a dW that is added to
+    (9, 899, [150] * 30 + [21], 0, dict(panel=4096, logits_large=1)),
+    (531, 125, [150] * 31 + [44], 0, dict(panel=4096, dh_large=1, dh_splits=1)),
+]
+
+
+@pytest.mark.parametrize("d,V,lens,cap", [c[:4] for c in CASES])
 def test_loss(d, V, lens, cap):
     print(d, V, lens, cap, flush=True)
     b = _custom_batch("f32", d=d, V=V, lens=lens, n_groups=1, seed=d + V, beta=1.0)

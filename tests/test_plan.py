@@ -1,5 +1,8 @@
 """The library's host decisions, host side only: launch grids and plans."""
+import pytest
+
 from paper_2602_19362_amd import oapl
+from tests import test_gpu_dh_splits, test_gpu_f32_tiles, test_gpu_small_tiles
 from tests._plan import ask
 
 INT_MAX = 2 ** 31 - 1
@@ -51,3 +54,15 @@ def test_a_few_missing_bytes_cost_a_few_splits():
             p = ask([f"plan {T} {d} {V} 1 0 0 0 {have}"])[0]
             assert p["rc"] == 0 and p["total"] <= have
             assert min(p["fwd_splits"], p["smp_splits"]) >= part * splits - 512 / T - 2, (T, part, full, p)
+
+
+@pytest.mark.parametrize("dtype,cases", [
+    (oapl.OAPL_BF16, [(sum(lens), d, V, cap, want) for d, V, lens, cap, want in test_gpu_dh_splits.CASES]),
+    (oapl.OAPL_BF16, [(T, d, V, 0, want) for d, V, T, want in test_gpu_small_tiles.CASES]),
+    (oapl.OAPL_F32, [(sum(lens), d, V, cap, want) for d, V, lens, cap, want in test_gpu_f32_tiles.CASES])],
+    ids=["dh_splits", "small_tiles", "f32_tiles"])
+def test_gpu_cases_have_the_plans_they_name(dtype, cases):
+    """A change of the time models must not empty the GPU tests of the kernels they are there for."""
+    plans = ask([f"plan {T} {d} {V} {dtype} 1 {cap} 0 -1" for T, d, V, cap, _ in cases])
+    for (T, d, V, cap, want), plan in zip(cases, plans):
+        assert plan["rc"] == 0 and {k: plan[k] for k in want} == want, (T, d, V, cap, plan)
