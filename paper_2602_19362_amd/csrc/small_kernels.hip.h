@@ -412,9 +412,12 @@ k_grpo_begin(const float* __restrict__ rewards, const int32_t* __restrict__ gid,
 }
 
 // ---------------------------------------------------------------------------
-// The objective, from diff = logprob - logq: one workgroup per rollout (at least one), the loss by the last to finish.
-// It may run any number of times in a call; rows not scored yet have diff = 0.
+// The objective, from diff = logprob - logq: one workgroup per rollout (at least one), the loss by the last of few to finish
+// or, where rollouts are many, in a launch of its own (objective_steps in oapl_api.hip).  It may run any number of times in a
+// call; rows not scored yet have diff = 0.
 // ---------------------------------------------------------------------------
+
+enum ObjectiveSteps { kRollouts = 1, kLoss = 2 };   // a launch does one of them, or both with the hand-over between them
 
 // The factor that goes into a token's coefficient: `fast` unless the call's flag says that the two-pass schedule served
 // it, then `slow`; either may be nullptr (no factor), and so may `flag` (fast).
@@ -437,7 +440,7 @@ __global__ void __launch_bounds__(256)
 k_oapl_objective(const double* __restrict__ diff, const float* __restrict__ rewards, const int32_t* __restrict__ gid,
                  const int64_t* __restrict__ off, int n_seq, int n_groups, int64_t Ttok, double beta_l, double scale,
                  const double* __restrict__ vstar_ws, TokenFactor factors, double* Delta, float* __restrict__ coef,
-                 float* __restrict__ loss_out, float* __restrict__ seq_logratio_out, int* status, Gate gate) {
+                 float* __restrict__ loss_out, float* __restrict__ seq_logratio_out, int* status, int steps, Gate gate) {
   __shared__ int bad;
   if (gate_closed(gate)) return;
   const int tid = threadIdx.x, s0 = blockIdx.x;
@@ -445,7 +448,7 @@ k_oapl_objective(const double* __restrict__ diff, const float* __restrict__ rewa
     const int g = gid[s];
     return (double)rewards[s] - (g >= 0 && g < n_groups ? vstar_ws[g] : __builtin_nan(""));
   };
-  if (s0 < n_seq) {
+  if ((steps & kRollouts) && s0 < n_seq) {
     // requested before the sum that they are combined with
     const double adv = advantage(s0);
     const float* factor = token_factor(factors);
@@ -463,9 +466,10 @@ k_oapl_objective(const double* __restrict__ diff, const float* __restrict__ rewa
       if (seq_logratio_out) seq_logratio_out[s0] = (float)acc;
     }
   }
+  if (!(steps & kLoss)) return;
   // the last workgroup's first 256 rollouts: requested before the hand-over, which then costs one round trip less
   const double adv0 = tid < n_seq ? advantage(tid) : 0.0;
-  if (!last_workgroup(status + kCounterWord, gridDim.x)) return;
+  if ((steps & kRollouts) && !last_workgroup(status + kCounterWord, gridDim.x)) return;
   if (tid == 0) bad = (off[0] != 0 || off[n_seq] != Ttok) ? kErrOffsets : 0;
   __syncthreads();
   double acc = 0.0;
@@ -493,10 +497,10 @@ __global__ void __launch_bounds__(256)
 k_grpo_objective(const double* __restrict__ diff, const float* __restrict__ logq, const float* __restrict__ logp_old,
                  const int64_t* __restrict__ off, int n_seq, int64_t Ttok, const float* __restrict__ adv,
                  const double* __restrict__ wseq, double clip_eps, TokenFactor factors, float* __restrict__ coef,
-                 double* seqterm, float* __restrict__ loss_out, int* status, Gate gate) {
+                 double* seqterm, float* __restrict__ loss_out, int* status, int steps, Gate gate) {
   if (gate_closed(gate)) return;
   const int tid = threadIdx.x, s0 = blockIdx.x;
-  if (s0 < n_seq) {
+  if ((steps & kRollouts) && s0 < n_seq) {
     int64_t a, b;
     token_range(off, s0, Ttok, a, b);
     const float* factor = token_factor(factors);
@@ -516,7 +520,7 @@ k_grpo_objective(const double* __restrict__ diff, const float* __restrict__ logq
     acc = block_sum(acc);
     if (tid == 0) __hip_atomic_store(seqterm + s0, -w * acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (!last_workgroup(status + kCounterWord, gridDim.x)) return;
+  if (!(steps & kLoss) || ((steps & kRollouts) && !last_workgroup(status + kCounterWord, gridDim.x))) return;
   double acc = 0.0;
   for (int s = tid; s < n_seq; s += 256) acc += __hip_atomic_load(seqterm + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   acc = block_sum(acc);

@@ -19,6 +19,13 @@ int main() {
     unsigned unaligned = 0;
     if (std::sscanf(line, "begin %d %d", &n_seq, &n_groups) == 2) {
       std::printf("one=%d grid=%u\n", begin_in_one_launch(n_seq, n_groups) ? 1 : 0, begin_grid(n_seq, n_groups));
+    } else if (std::sscanf(line, "objective %d", &n_seq) == 1) {
+      // the first launch of the objective: workgroups, and how many of them hand over to the last one
+      unsigned first = 0, hand_over = 0;
+      objective_steps(n_seq, [&](unsigned grid, int steps) {
+        if (first == 0) { first = grid; hand_over = steps == (kRollouts | kLoss) ? grid : 0; }
+      });
+      std::printf("grid=%u hand_over=%u\n", first, hand_over);
     } else if (std::sscanf(line, "plan %lld %d %d %d %d %lld %u %lld", &T, &d, &V, &dtype, &bwd, &cap, &unaligned, &have) == 8) {
       // the plan of a call of one rollout on `have` bytes (< 0: what the library asks for with panels of `cap` rows)
       if (have < 0) have = (long long)oapl_workspace_bytes_for(T, d, V, 1, 1, dtype, bwd, cap, 0, nullptr, nullptr);

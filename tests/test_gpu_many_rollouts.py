@@ -1,6 +1,6 @@
 """Batches with more rollouts and prompts than one workgroup looks at in a call's first launch, more rollouts than the
-objective's last workgroup has threads, and short or empty rollouts; the sizes just below that line too.  Tolerances as in
-test_gpu_parity.py."""
+objective takes in one launch and than the workgroup that adds up the loss has threads, and short or empty rollouts; the
+sizes just below each line too.  Tolerances as in test_gpu_parity.py."""
 import pytest
 import torch
 
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("n_seq,n_groups", [(255, 15), (256, 16), (257, 1), (400, 40), (900, 9)])
+@pytest.mark.parametrize("n_seq,n_groups", [(32, 4), (33, 3), (255, 15), (256, 16), (257, 1), (400, 40), (900, 9)])
 def test_losses(dtype, n_seq, n_groups):
     print(dtype, n_seq, n_groups, flush=True)
     n_seq = n_seq // n_groups * n_groups
@@ -22,6 +22,9 @@ def test_losses(dtype, n_seq, n_groups):
     _check(b, res, oracle_full(b), *tol)
     again = _run(b)
     assert torch.equal(res.loss, again.loss) and torch.equal(res.dW, again.dW)
+    # the loss once more, from its parts: NaN-free and fixed whatever the launches
+    delta = b.beta * res.seq_logratio.double() - (b.rewards.double() - res.vstar.double()[b.group_ids.long()])
+    assert abs((delta ** 2).sum().item() / res.loss.item() - 1) <= 1e-5
     logq, logp_old = _grpo_inputs(b, n_seq)
     res = _grpo(b.H, b.W, b.tokens, logq, logp_old, b.seq_offsets, b.rewards, b.group_ids, n_groups)
     torch.cuda.synchronize()

@@ -20,6 +20,13 @@ def test_first_launch_indices_fit_32_bits():
             assert a["grid"] * 256 >= n_seq and a["grid"] * 4 >= n_groups, (n_seq, n_groups, a)
 
 
+def test_few_workgroups_hand_the_loss_over():
+    """A hand-over costs a fence and a counter per rollout (2048 rollouts: 134 us against 13 in two launches)."""
+    sizes = [0, 1, 8, 32, 33, 64, 2048]
+    for n, a in zip(sizes, ask([f"objective {n}" for n in sizes])):
+        assert a["grid"] == max(n, 1) and a["hand_over"] <= 32
+
+
 def test_operands_that_are_not_aligned_have_room_for_an_aligned_copy():
     """The kernels that read bf16 W and H in place want them 16-byte aligned: a call whose operands are not copies them
     first, within the workspace the library asks for; one whose operands are needs no such space."""
