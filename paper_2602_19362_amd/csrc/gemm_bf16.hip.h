@@ -1187,7 +1187,8 @@ __device__ __forceinline__ void store_f32_tile(const f32x16 (&acc)[C::TM][C::TN]
 //   tokens), K = V.
 // A panel of few tokens has few tiles (d / 256 x tokens / 384), each a walk over the whole vocabulary: 1003 tokens at
 // d = 4096 kept 48 of 256 CUs busy for 4.1 ms.  SPLIT: `splits` workgroups share a tile's k-blocks, each writing its
-// fp32 partial sum (whole 128-byte lines) for k_dh_reduce; the host chooses the count (dh_splits).
+// fp32 partial sum (whole 128-byte lines) for k_dh_reduce; the host chooses the count (pick_dh in
+// oapl_api.hip).
 // ---------------------------------------------------------------------------
 template <class C, bool SPLIT, bool ATR>
 __global__ void __launch_bounds__(C::NT)

@@ -446,17 +446,16 @@ static bool prepare_kernels() {
     ok = allow_fwd<Cfg64, true>() && allow_fwd<Cfg128, true>() && allow_fwd<Cfg256, true>() && allow_fwd<Cfg320, true>() &&
          allow_fwd<Cfg, true>() && allow_fwd<Cfg, false>() && allow_sample<Cfg64, true>() &&
          allow_sample<Cfg128, true>() && allow_sample<Cfg256, true>() && allow_sample<CfgSample, false>() &&
-         allow_big_lds(k_bwd_dz<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_bwd_dz<Cfg, true>, Cfg::LDS_BYTES) &&
-        
-         allow_dh<Cfg, false, false>() && allow_dh<Cfg, false, true>() && allow_dh<Cfg, true, false>() &&
-         allow_dh<Cfg, true, true>() && allow_dh<CfgSmall, false, true>() && allow_dh<CfgSmall, true, true>() &&
-         allow_dh<CfgDeep, false, true>() && allow_dh<CfgDeep, true, true>() && allow_big_lds(k_bwd_dw<CfgDeep>, CfgDeep::LDS_BYTES) &&
-         allow_big_lds(k_sweep<CfgDeep, true>, CfgDeep::LDS_BYTES) &&
-         allow_big_lds(k_bwd_dw<CfgSmall>, CfgSmall::LDS_BYTES) && allow_big_lds(k_sweep<CfgSmall, true>, CfgSmall::LDS_BYTES) &&
-                 allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
-         allow_big_lds(k_sweep<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_sweep<Cfg, true>, Cfg::LDS_BYTES) &&
          allow_big_lds(k_fwd_lse<CfgRef, false, true>, CfgRef::LDS_BYTES) &&
-         allow_big_lds(k_fwd_lse<CfgRef, false, false>, CfgRef::LDS_BYTES);
+         allow_big_lds(k_fwd_lse<CfgRef, false, false>, CfgRef::LDS_BYTES) &&
+         allow_big_lds(k_bwd_dz<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_bwd_dz<Cfg, true>, Cfg::LDS_BYTES) &&
+         allow_big_lds(k_sweep<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_sweep<Cfg, true>, Cfg::LDS_BYTES) &&
+         allow_big_lds(k_sweep<CfgSmall, true>, CfgSmall::LDS_BYTES) &&
+         allow_big_lds(k_sweep<CfgDeep, true>, CfgDeep::LDS_BYTES) && allow_dh<Cfg, false, false>() &&
+         allow_dh<Cfg, false, true>() && allow_dh<Cfg, true, false>() && allow_dh<Cfg, true, true>() &&
+         allow_dh<CfgSmall, false, true>() && allow_dh<CfgSmall, true, true>() && allow_dh<CfgDeep, false, true>() &&
+         allow_dh<CfgDeep, true, true>() && allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
+         allow_big_lds(k_bwd_dw<CfgSmall>, CfgSmall::LDS_BYTES) && allow_big_lds(k_bwd_dw<CfgDeep>, CfgDeep::LDS_BYTES);
   });
   return ok;
 }
@@ -481,21 +480,22 @@ struct FwdArgs {
   TilePick pick;
 };
 
-// One streaming log-sum-exp pass (the plan's tile; upart != nullptr: with the entropy's partial sums).
-template <class C, bool ROWS>
-static void launch_fwd_lse(const FwdArgs& a, float2* partials, float* upart, int* clear, hipStream_t st, Gate gate) {
+// One streaming log-sum-exp pass (the plan's tile; ENT: with the entropy's partial sums in upart).
+template <class C, bool ENT, bool ROWS>
+static void launch_fwd_lse_kernel(const FwdArgs& a, float2* partials, float* upart, int* clear, hipStream_t st, Gate gate) {
   const int64_t total = (a.T + C::BN - 1) / C::BN * a.pick.splits;
   const unsigned grid = (unsigned)round_up(total, 8);
   // token tiles per XCD patch: eight while a token tile's H strip is at most 3 MiB (384 columns: d <= 4096), else four.
   // 20000 tokens at d = 4096, walks of 3 tiles: 21.4 / 18.9 / 18.3 / 18.6 ms for patches of 1 / 4 / 8 / 16; 30000 at
   // d = 5120: 40.4 / 35.8 / 37.3 / 37.2; at d <= 2048 four and eight are equal.
   const int patch_tiles = (size_t)a.n_kt * C::STAGE_B <= ((size_t)3 << 20) ? 8 : 4;
-  if (upart)
-    k_fwd_lse<C, true, ROWS><<<grid, C::NT, C::LDS_BYTES, st>>>(a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits,
-                                                              patch_tiles, partials, upart, clear, gate);
-  else
-    k_fwd_lse<C, false, ROWS><<<grid, C::NT, C::LDS_BYTES, st>>>(a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits,
-                                                               patch_tiles, partials, nullptr, clear, gate);
+  k_fwd_lse<C, ENT, ROWS><<<grid, C::NT, C::LDS_BYTES, st>>>(a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, patch_tiles,
+                                                           partials, upart, clear, gate);
+}
+template <class C, bool ROWS>
+static void launch_fwd_lse(const FwdArgs& a, float2* partials, float* upart, int* clear, hipStream_t st, Gate gate) {
+  if (upart) launch_fwd_lse_kernel<C, true, ROWS>(a, partials, upart, clear, st, gate);
+  else launch_fwd_lse_kernel<C, false, ROWS>(a, partials, nullptr, clear, st, gate);
 }
 static void launch_fwd_lse(const FwdArgs& a, bool rows, float2* partials, float* upart, int* clear, hipStream_t st,
                            Gate gate) {
@@ -835,8 +835,8 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
   // reference exponents: running maximum over the first 256 vocabulary entries, one workgroup per 64 tokens (a walk of
   // d / 64 k-blocks each, bound by their latency)
   const FwdArgs ref{x.W, x.H, V < CfgRef::BM ? V : CfgRef::BM, T, d, p.n_kt_d, TilePick{}};
-  if (p.rows) launch_fwd_lse<CfgRef, true>(ref, sample, nullptr, nullptr, st, fast);
-  else launch_fwd_lse<CfgRef, false>(ref, sample, nullptr, nullptr, st, fast);
+  if (p.rows) launch_fwd_lse_kernel<CfgRef, false, true>(ref, sample, nullptr, nullptr, st, fast);
+  else launch_fwd_lse_kernel<CfgRef, false, false>(ref, sample, nullptr, nullptr, st, fast);
   OAPL_LAUNCH_CHECK();
   if (int rc = gather_logits(p, H, W, tokens, TokenInit{(float*)(ws + p.off_coef), sample, ref2, diff, nis}, ws, st)) return rc;
 
