@@ -93,8 +93,9 @@ struct Plan {
   int n_rt_v = 0, n_rt_d = 0, n_kt_d = 0, n_kt_v = 0, n_kt_g = 0, n_kt_t = 0;
   int n_rb_v = 0;      // 384-row blocks of a matrix whose rows are the vocabulary (G^T)
   int64_t n_rt_T = 0;  // 384-row token tiles of the whole batch
-  size_t off_status = 0, off_partials = 0, off_fwd_partials = 0, off_upart = 0, off_zy = 0, off_lse2 = 0, off_diff = 0, off_coef = 0, off_delta = 0,
-         off_cseq = 0, off_vstar = 0, off_gw = 0, off_omp = 0, off_inv = 0, off_Wp = 0, off_Hp = 0, off_Wc = 0, off_Hc = 0, off_WTp = 0, off_HTp = 0,
+  size_t off_status = 0, off_partials = 0, off_fwd_partials = 0, off_upart = 0, off_zy = 0, off_lse2 = 0, off_diff = 0,
+         off_coef = 0, off_delta = 0, off_cseq = 0, off_vstar = 0, off_gw = 0, off_omp = 0, off_inv = 0, off_Wp = 0,
+         off_Hp = 0, off_Wc = 0, off_Hc = 0, off_WTp = 0, off_HTp = 0,
          off_part = 0, off_G = 0, off_GT = 0, off_ref2 = 0, off_spart = 0, total = 0;
   bool sweep = false;  // single-sweep loss path available (bf16 with backward)
 };

@@ -22,11 +22,10 @@ __global__ void k_fill_f32(float* p, int64_t n, float v, Gate gate) {
 
 // z_{t, y_t} = sum_k H[t][k] * W[y_t][k]: one wavefront per token, the gathered
 // W row is read with the index exactly as given (checked against [0, V)).
-// ACC is double for fp32 inputs and float for bf16 inputs (whose products are
-// exact in fp32).  VEC elements per load: 16 bytes, or one for fp32 rows that are not
-// 16-byte aligned.  Reads 2 rows per token and is bound by the latency of a wavefront's chain of loads:
-// element by element it took 33 us for 777 tokens at d = 4096 (64 loads in a row per lane) and 82 us for 32768 at
-// d = 2048, by 16-byte loads 8.5 and 42 us.
+// ACC is double for fp32 inputs and float for bf16 inputs (whose products are exact in fp32).  VEC elements per load: 16
+// bytes, or one for fp32 rows that are not 16-byte aligned.  Reads 2 rows per token and is bound by the latency of a
+// wavefront's chain of loads: element by element it took 33 us for 777 tokens at d = 4096 (64 loads in a row per lane) and
+// 82 us for 32768 at d = 2048, by 16-byte loads 8.5 and 42 us.
 //
 // It also prepares the other per-token arrays of a loss call, where those are given: coef[t] = 0 (a token that malformed
 // offsets leave out keeps it); for the single sweep the reference exponent ref2[t] of k_sweep, and "no contribution yet"
