@@ -145,6 +145,15 @@ def _workspace(nbytes: int, device, workspace: Optional[torch.Tensor]) -> torch.
     return workspace
 
 
+def _panel_rows(H: torch.Tensor, W: torch.Tensor, max_panel_rows: Optional[int]) -> Optional[int]:
+    """The panel cap to size a loss call's workspace for: less than a bf16 tile asks for the least workspace, which has no
+    room for the copies that operands off 16-byte alignment need, so for those it is a whole tile."""
+    if max_panel_rows is not None and 0 < max_panel_rows < 384 and H.dtype == torch.bfloat16 \
+            and (H.data_ptr() | W.data_ptr()) % 16:
+        return 384
+    return max_panel_rows
+
+
 def read_device_status(workspace: torch.Tensor) -> int:
     out = ctypes.c_int32(0)
     rc = lib().oapl_read_device_status(workspace.data_ptr(), _stream(workspace.device), ctypes.byref(out))
@@ -255,7 +264,7 @@ def loss_fwd_bwd(H, W, tokens, logq, seq_offsets, rewards, group_ids, n_groups: 
             or group_ids.shape != (n_seq,):
         raise ValueError("shape mismatch between the inputs")
     dev = H.device
-    nbytes = workspace_bytes(T, d, V, n_seq, n_groups, dt, backward, max_panel_rows, max_rollout_len)
+    nbytes = workspace_bytes(T, d, V, n_seq, n_groups, dt, backward, _panel_rows(H, W, max_panel_rows), max_rollout_len)
     if nbytes == 0:
         raise OaplError(2, "oapl_workspace_bytes")
     ws = _workspace(nbytes, dev, workspace)
@@ -341,7 +350,7 @@ def grpo_loss_fwd_bwd(H, W, tokens, logq, logp_old, seq_offsets, rewards, group_
             or seq_offsets.shape != (n_seq + 1,) or group_ids.shape != (n_seq,):
         raise ValueError("shape mismatch between the inputs")
     dev = H.device
-    nbytes = workspace_bytes(T, d, V, n_seq, n_groups, dt, backward, max_panel_rows, max_rollout_len)
+    nbytes = workspace_bytes(T, d, V, n_seq, n_groups, dt, backward, _panel_rows(H, W, max_panel_rows), max_rollout_len)
     if nbytes == 0:
         raise OaplError(2, "oapl_workspace_bytes")
     ws = _workspace(nbytes, dev, workspace)

@@ -18,9 +18,10 @@ def _at(t, elements):
     return view
 
 
-# in place with small tiles, dH split, one and several panels; packed (ragged rows above 4096 tokens; above 8192)
+# in place with small tiles, dH split, one and several panels, the least workspace asked for; packed (ragged rows above 4096 tokens; above 8192)
 @pytest.mark.parametrize("two_pass", [False, True])
 @pytest.mark.parametrize("d,V,lens,cap", [(72, 1003, [40, 20], 0), (264, 1544, [300, 0, 85], 0), (128, 9000, [500, 470], 384),
+                                          (128, 9000, [500, 470], 1),
                                           (72, 300, [4000, 100], 0), (64, 300, [8000, 200], 0)])
 def test_losses(d, V, lens, cap, two_pass):
     print(d, V, lens, cap, two_pass, flush=True)
