@@ -2,7 +2,7 @@
 //
 // One main loop serves all dense steps of the path.  It computes a
 // 256 x 384 tile of  C[m][n] = sum_k A[m][k] * B[n][k]  with both operands
-// k-contiguous, fp32 accumulation in v_mfma_f32_32x32x16_bf16, operands
+// k-contiguous, fp32 accumulation in v_mfma_f32_16x16x32_bf16, operands
 // streamed L2 -> LDS by direct-to-LDS buffer loads (no VGPR staging) into a
 // two-stage, XOR-swizzled LDS ring that fills the CU's 160 KB, 8 wavefronts
 // (two per SIMD, so one wavefront's waits are covered by the other's MFMAs),
@@ -12,6 +12,13 @@
 // Calls too small to fill the chip with such tiles take smaller ones of the same
 // loop, and calls of few tokens read the caller's matrices in place (Mainloop's ROWS
 // and ATR); oapl_api.hip has the rules.
+//
+// Two things bound the loop: the power the part may draw, which sets its clock, and the loads.  Multiplications alone, on
+// registers, run at 1.79 GHz in the 32 x 32 x 16 shape and at 2.09 GHz in the 16 x 16 x 32 one (8.39 / 7.18 ms for 12288 x
+// 4096 x 151936), which moves fewer accumulator bytes per flop.  And a wave that issues its ten loads of a block in one go waits
+// until the memory pipeline has taken them; given out two at a time between the multiplications they cost it nothing.
+// dH of 12288 tokens at d = 4096, same box: 10.82 ms 32 x 32 with the loads in one go, 10.23 ms 16 x 16, 9.75 ms
+// with the loads spread (dW 11.14 / 10.50 / 10.23, logits 11.91 / 11.41 / 10.86 ms).
 //
 // Operand layout in HBM ("packed"): a matrix with R rows and K columns is
 // stored as blocks of RB rows x 64 columns (RB = 256 for the m-side operand,
@@ -24,18 +31,17 @@
 // are packed once per call by k_pack_rows / k_pack_transposed; the kernels
 // that produce intermediate operands write them packed directly.
 //
-// In the accumulator of a 32x32 MFMA block a lane owns ONE column n (lane%32)
-// and 16 rows m: m = 8*(r/4) + 4*(lane/32) + r%4 for register r.  Every
-// epilogue is built around that:
+// In the accumulator of a 16x16 MFMA block a lane owns ONE column n (lane%16)
+// and 4 consecutive rows m = 4*(lane/16) + r.  Every epilogue is built around that:
 //   * forward (logits^T tile, M = vocabulary, N = tokens): the soft-max
-//     reduction over the vocabulary is lane-local, so the streaming max / sum
-//     needs no cross-lane traffic until the very end;
+//     reduction over the vocabulary is lane-local but for its last step, across
+//     the four groups of 16 lanes (reduce4);
 //   * outputs with m contiguous (G[t][v], dH[t][j], dW[v][j]) get 4
 //     consecutive m per lane.
 //
 // The bodies of the tile kernels are compiled in the device pass only (__HIP_DEVICE_COMPILE__).
-// They use instructions that gfx950 alone has (16-byte direct-to-LDS loads, the 32x32x16 bf16
-// MFMA, v_permlane32_swap).  The host pass needs nothing but the signatures, for its launch stubs;
+// They use instructions that gfx950 alone has (16-byte direct-to-LDS loads, the 16x16x32 bf16
+// MFMA, v_permlane16/32_swap).  The host pass needs nothing but the signatures, for its launch stubs;
 // it checks builtins against a generic target, keeps its complaints about device code to itself,
 // and has been seen to drop a kernel's launch stub, or to refuse a launch as "no matching
 // function", after an unrelated edit of the main loop.
@@ -47,17 +53,21 @@
 namespace oapl {
 
 
+// WM x WN wavefronts, each MB x NB blocks of 16 x 16.
 // PACK_B_: rows per block of the n-side operands where they are packed (0: one tile), a multiple of the tile's.
-template <int WM_, int WN_, int TM_, int TN_, int NS_, int PACK_B_ = 0>
+// EARLY_: a block's loads go out in one go, for walks that wait for memory rather than for the multiplications.
+template <int WM_, int WN_, int MB_, int NB_, int NS_, int PACK_B_ = 0, bool EARLY_ = false>
 struct TileCfg {
-  static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_;
+  static constexpr int WM = WM_, WN = WN_, MB = MB_, NB = NB_;
+  static constexpr bool EARLY = EARLY_;
   static constexpr int NW = WM * WN;            // waves per workgroup
   static constexpr int NT = NW * 64;            // threads per workgroup
-  static constexpr int BM = WM * TM * 32;
-  static constexpr int BN = WN * TN * 32;
+  static constexpr int WROWS = MB * 16, WCOLS = NB * 16;   // one wavefront's patch
+  static constexpr int BM = WM * WROWS;
+  static constexpr int BN = WN * WCOLS;
   static constexpr int BK = kPackK;             // k-extent of one LDS stage
   static constexpr int NS = NS_;                // LDS stages in the ring
-  static constexpr int KSTEPS = BK / 16;        // MFMA k-steps per stage
+  static constexpr int KSTEPS = BK / 32;        // MFMA k-steps per stage
   static constexpr int ROW_BYTES = kPackRowBytes;
   static constexpr int STAGE_A = BM * ROW_BYTES;   // one stage of the m-side operand
   static constexpr int STAGE_B = BN * ROW_BYTES;   // ... of the n-side operand
@@ -68,13 +78,13 @@ struct TileCfg {
   static constexpr int MAIN_BYTES = NS * (STAGE_A + STAGE_B);
   static constexpr int NI_A = BM / (8 * NW);    // direct loads per wave and stage (8 rows each), m-side operand
   static constexpr int NI_B = BN / (8 * NW);    // ... n-side operand
-  // bf16 staging tiles used by epilogues (16 B of padding per row).  A whole tile does not fit
-  // the LDS, so epilogues stage it in chunks: [n][m] by wave column (BN / WN rows of n at a
-  // time), [m][n] by pairs of wave rows (BM / MN_CHUNKS rows of m at a time).
+  // bf16 staging tiles used by epilogues, rows padded so that a write instruction's lanes spread over the banks.  A whole
+  // tile does not fit the LDS, so epilogues stage it in chunks: [n][m] by wave column (BN / WN rows of n at a
+  // time), [m][n] by pairs of MFMA block rows (32 rows of every wave row at a time).
   static constexpr int PITCH_NM = BM * 2 + 16;  // tile stored [n][m]
-  static constexpr int PITCH_MN = BN * 2 + 16;  // tile stored [m][n]
+  static constexpr int PITCH_MN = BN * 2 + 32;  // tile stored [m][n]
   static constexpr int NM_CHUNKS = WN, NM_ROWS = BN / WN;
-  static constexpr int MN_CHUNKS = BM >= 128 ? BM / 128 : 1, MN_ROWS = BM / MN_CHUNKS;
+  static constexpr int MN_CHUNKS = MB / 2, MN_ROWS = WM * 32;
   static constexpr int STAGE_NM = NM_ROWS * PITCH_NM;
   static constexpr int STAGE_MN = MN_ROWS * PITCH_MN;
   static constexpr int RED_BYTES = WM * BN * 8;
@@ -124,6 +134,13 @@ __device__ __forceinline__ bf16x4 lds_read_transposed(const __attribute__((addre
 // it lies in LDS as [k][m], and the fragments come out of it by the transposing read (ds_read_b64_tr_b16: of the 16
 // lanes of a group, lane 4e + a points at the four m of column group a in row k + e, and lane i receives column i of
 // the four rows), two reads of 8 bytes in place of one of 16.
+//
+// The multiplications are inline assembly because only there can an accumulator be tied to its register: given the builtin, the
+// register allocator gives results new registers and spills around them (3.5 times as slow).  The price is that the compiler
+// does not know what an MFMA leaves behind: a vector instruction may not read or overwrite its result for 8 wait states, nor
+// an MFMA read what a vector instruction wrote less than 2 before.  Fragments come straight from LDS reads, and every step
+// ends with settle(), through which all accumulators pass; tests/test_mfma_hazards.py looks for what slips through in the
+// built library.
 template <class C, bool ROWS = false, bool ATR = false>
 struct Mainloop {
   // 16-byte chunk c of LDS row `row` lives at physical chunk c ^ ((row >> 1) & 7).  The operand
@@ -138,10 +155,9 @@ struct Mainloop {
   const char* at_base;                // ATR: the tile's first column in row 0 of the matrix
   int64_t at_rows;                    // ... rows (k) from there
   int at_ld2, at_m0, at_voff;         // ... bytes per row, first column, per-lane byte offset of a wave's first load of a k-block
-  // LDS byte offsets of this lane's operand fragments at k-step 0 of ring slot 0.  K-step ks sits at the
-  // same offset with address bits 5..6 flipped by ks (the swizzle is an XOR on the 16-byte chunk index and
-  // the k-step is bits 1..2 of that index); deriving it where it is used costs one XOR per operand and
-  // k-step and saves six registers over a table.
+  // LDS byte offsets of this lane's operand fragments at k-step 0 of ring slot 0.  K-step 1 sits at the
+  // same offset with address bit 6 flipped (the swizzle is an XOR on the 16-byte chunk index and
+  // the k-step is bit 2 of that index).
   int rdA0, rdB0;
   int wave, lane;
 
@@ -160,32 +176,33 @@ struct Mainloop {
       const int row = wave * 8 + (lane >> 3);
       voff = row * C::ROW_BYTES + (((lane & 7) ^ swz(row)) << 4);
     }
-    const int rowA = wm * C::TM * 32 + (lane & 31);
-    const int rowB = wn * C::TN * 32 + (lane & 31);
-    static_assert(C::KSTEPS == 4, "k-step index = chunk bits 1..2");
-    const int c0 = lane >> 5;
+    const int rowA = wm * C::WROWS + (lane & 15);
+    const int rowB = wn * C::WCOLS + (lane & 15);
+    static_assert(C::KSTEPS == 2, "k-step index = chunk bit 2");
+    const int c0 = lane >> 4;
     rdA0 = rowA * C::ROW_BYTES + ((c0 ^ swz(rowA)) << 4);
     rdB0 = C::STAGE_A + rowB * C::ROW_BYTES + ((c0 ^ swz(rowB)) << 4);
   }
 
   // ATR only: the m-side operand of column tile mt in a row-major matrix of R rows of `ld` elements (after setup()).
-  // Chunk c (16 bytes, BM / 8 per row) of LDS row k lives at chunk c ^ ((k & 3) << 2): the four rows and the two halves of
-  // 32 lanes' transposing read then lie on 64 different banks.
+  // Chunk c (16 bytes, BM / 8 per row) of LDS row k lives at chunk c ^ at_swz(k): the eight rows of 32 lanes' transposing
+  // read, 32 bytes each, then lie on 64 different banks.
+  static __device__ __forceinline__ int at_swz(int k) { return ((k & 3) | ((k & 8) >> 1)) << 1; }
   __device__ __forceinline__ void set_a_transposed(const bf16_t* p, int mt, int64_t R, int ld) {
     // one wave-wide load covers RPL rows of LPR lanes; load i of a wave is NW * RPL rows further on
     constexpr int LPR = C::BM / 8, RPL = 64 / LPR;
-    static_assert(!ATR || (C::NW * RPL) % 4 == 0, "swizzle must repeat from one load of a wave to the next");
+    static_assert(!ATR || (C::NW * RPL) % 16 == 0, "swizzle must repeat from one load of a wave to the next");
     static_assert(!ATR || C::NI_A * C::NW * RPL == C::BK, "the loads cover the block");
     at_base = (const char*)(p + mt * C::BM);
     at_rows = R;
     at_ld2 = ld * 2;
     at_m0 = mt * C::BM;
     const int row = wave * RPL + lane / LPR;
-    at_voff = row * at_ld2 + (((lane % LPR) ^ ((row & 3) << 2)) << 4);
+    at_voff = row * at_ld2 + (((lane % LPR) ^ at_swz(row)) << 4);
     const int e = (lane >> 2) & 3, a = lane & 3, g = lane >> 4, wm = wave / C::WN;
-    const int k = 8 * (g >> 1) + e;
-    const int chunk = wm * C::TM * 4 + 2 * (g & 1) + (a >> 1);   // m / 8 of fragment 0
-    rdA0 = k * (C::BM * 2) + ((chunk ^ (e << 2)) << 4) + ((a & 1) << 3);
+    const int k = 8 * g + e;
+    const int chunk = wm * C::MB * 2 + (a >> 1);   // m / 8 of fragment 0
+    rdA0 = k * (C::BM * 2) + ((chunk ^ at_swz(k)) << 4) + ((a & 1) << 3);
   }
 
   // The empty asm keeps the compiler from hoisting the per-k-step addresses out of the loop (back into a table).
@@ -226,64 +243,107 @@ struct Mainloop {
                                            (n_kt - k0) * C::PITCH_B - in_block, 0x00020000);
   }
 
-  // Starts the direct-to-LDS loads of k-block kt into ring slot STAGE (a literal at the call sites,
-  // so the LDS addresses fold to constants once inlined).
+  // Per-lane offset of the loads of k-block kt: past the buffer's range, so that nothing is read and zeros are
+  // written, for a block past the last.
+  __device__ __forceinline__ int load_voff(int kt, int nk) const {
+    const int inside = ATR ? 0 : ROWS && kt + 1 == nk ? vlast : voff;
+    return kt < nk ? inside : (int)0x80000000u;
+  }
+  // Starts direct-to-LDS load i (of NI_A + NI_B) of k-block kt into ring slot STAGE (a literal at the call sites,
+  // so the LDS addresses fold to constants once inlined), v = load_voff(kt, nk).
   // ROWS: the row term goes into the per-lane offset, because only that one is sure to be compared with the buffer's
   // range: a scalar offset past the range (rows of a matrix shorter than the tile) must not decide what is read.
-  __device__ __forceinline__ void issue(const int STAGE, lds_char_ptr smem, int kt, int nk) {
-    const int v = ROWS && kt + 1 == nk ? vlast : voff;
-    if (ATR) {
-      // rows past the matrix lie past its end and read as zeros; columns past `ld` are the next row's: they feed
-      // output rows that are not stored
-      const int64_t left = at_rows - (int64_t)kt * C::BK;
-      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-          (void*)(at_base + (int64_t)kt * C::BK * at_ld2), 0, (int)(left < C::BK ? left : C::BK) * at_ld2 - at_m0 * 2, 0x00020000);
-#pragma unroll
-      for (int i = 0; i < C::NI_A; ++i)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_ptr)(smem + STAGE * C::SLOT + (i * C::NW + wave) * 1024), 16,
-                                                 at_voff + i * (C::NW * 64 / (C::BM / 8)) * at_ld2, 0, 0, 0);
+  __device__ __forceinline__ void issue_one(const int STAGE, lds_char_ptr smem, int v, int kt, int nk, const int i) {
+    if (i < C::NI_A) {
+      const lds_void_ptr dst = (lds_void_ptr)(smem + STAGE * C::SLOT + (i * C::NW + wave) * 1024);
+      if (ATR) {
+        // rows past the matrix lie past its end and read as zeros; columns past `ld` are the next row's: they feed
+        // output rows that are not stored
+        const int kc = kt < nk ? kt : nk - 1;
+        const int64_t left = at_rows - (int64_t)kc * C::BK;
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(at_base + (int64_t)kc * C::BK * at_ld2), 0, (int)(left < C::BK ? left : C::BK) * at_ld2 - at_m0 * 2, 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, (v < 0 ? v : at_voff) + i * (C::NW * 64 / (C::BM / 8)) * at_ld2, 0, 0, 0);
+      } else {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, dst, 16, ROWS ? v + i * istep : v,
+                                                 ROWS ? kt * C::ROW_BYTES : kt * C::PITCH_A + i * C::NW * 1024, 0, 0);
+      }
+    } else if (i < C::NI_A + C::NI_B) {
+      const int b = i - C::NI_A;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rb, (lds_void_ptr)(smem + STAGE * C::SLOT + C::STAGE_A + (b * C::NW + wave) * 1024), 16,
+          ATR ? (v < 0 ? v : voff) : ROWS ? v + b * istep : v,
+          ROWS ? kt * C::ROW_BYTES : kt * C::PITCH_B + b * C::NW * 1024, 0, 0);
     }
+  }
+  // ... all loads of the block.
+  __device__ __forceinline__ void issue(const int STAGE, lds_char_ptr smem, int kt, int nk) {
+    const int v = load_voff(kt, nk);
 #pragma unroll
-    for (int i = 0; i < (ATR ? 0 : C::NI_A); ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          ra, (lds_void_ptr)(smem + STAGE * C::SLOT + (i * C::NW + wave) * 1024), 16, ROWS ? v + i * istep : v,
-          ROWS ? kt * C::ROW_BYTES : kt * C::PITCH_A + i * C::NW * 1024, 0, 0);
-#pragma unroll
-    for (int i = 0; i < C::NI_B; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rb, (lds_void_ptr)(smem + STAGE * C::SLOT + C::STAGE_A + (i * C::NW + wave) * 1024), 16, ROWS ? v + i * istep : v,
-          ROWS ? kt * C::ROW_BYTES : kt * C::PITCH_B + i * C::NW * 1024, 0, 0);
+    for (int i = 0; i < C::NI_A + C::NI_B; ++i) issue_one(STAGE, smem, v, kt, nk, i);
   }
 
-  __device__ __forceinline__ void compute(const int STAGE, lds_char_ptr smem, f32x16 (&acc)[C::TM][C::TN]) {
+  // Two loads are given out per group of multiplications, from the second group on, where the patch is large enough.
+  static constexpr int kLoads = C::NI_A + C::NI_B;
+  static constexpr int kGroups = C::KSTEPS * ((C::NB + 1) / 2);
+  static constexpr bool kSpread = C::NS == 2 && C::MB * C::NB >= 32 && !C::EARLY && 2 * (kGroups - 1) >= kLoads;
+
+  static __device__ __forceinline__ void mfma(f32x4& c, const bf16x8 a, const bf16x8 b) {
+    asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+  }
+  // The last multiplications' results are there (8 wait states) before any other instruction sees the accumulators.
+  static __device__ __forceinline__ void settle(f32x4 (&acc)[C::MB][C::NB]) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 7" : "+v"(acc[0][0]));
+#pragma unroll
+    for (int i = 0; i < C::MB; ++i)
+#pragma unroll
+      for (int j = 0; j < C::NB; ++j) asm volatile("" : "+v"(acc[i][j]));
+  }
+
+  // Multiplies the block in ring slot STAGE; with LOAD also starts the loads of block kt_load into slot LSTAGE on the way.
+  // A k-step's m-side fragments stay in registers, n-side fragments come two at a time, requested one group of
+  // multiplications ahead (the scheduler moves a group's reads up between the previous group's multiplications, no
+  // further: that is what the barriers are for).
+  template <bool LOAD>
+  __device__ __forceinline__ void compute(const int STAGE, lds_char_ptr smem, f32x4 (&acc)[C::MB][C::NB], const int LSTAGE = 0,
+                                          int kt_load = 0, int nk = 0) {
+    const int v = LOAD ? load_voff(kt_load, nk) : 0;
 #pragma unroll
     for (int ks = 0; ks < C::KSTEPS; ++ks) {
-      bf16x8 a[C::TM], b[C::TN];
-      const int ra_ks = ATR ? fresh(rdA0) : fresh(rdA0) ^ (ks << 5), rb_ks = fresh(rdB0) ^ (ks << 5);
-      if (ATR) {
+      bf16x8 a[C::MB];
+      const int ra_ks = ATR ? fresh(rdA0) : fresh(rdA0) ^ (ks << 6), rb_ks = fresh(rdB0) ^ (ks << 6);
 #pragma unroll
-        for (int i = 0; i < C::TM; ++i) {
-          static_assert(!ATR || C::TM <= 2, "fragment i flips chunk bit 2");
-          const lds_char_ptr q = smem + (ra_ks ^ (i << 6)) + STAGE * C::SLOT + ks * 16 * (C::BM * 2);
+      for (int i = 0; i < C::MB; ++i) {
+        if (ATR) {
+          static_assert(!ATR || C::MB == 4, "fragment i flips chunk bits 1..2");
+          const lds_char_ptr q = smem + (ra_ks ^ (i << 5)) + STAGE * C::SLOT + ks * 32 * (C::BM * 2);
           const bf16x4 lo = lds_read_transposed(q), hi = lds_read_transposed(q + 4 * (C::BM * 2));
           a[i] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        } else {
+          a[i] = *(const __attribute__((address_space(3))) bf16x8*)(smem + STAGE * C::SLOT + ra_ks + i * 16 * C::ROW_BYTES);
         }
       }
 #pragma unroll
-      for (int i = 0; i < (ATR ? 0 : C::TM); ++i)
-        a[i] = *(const __attribute__((address_space(3))) bf16x8*)(smem + STAGE * C::SLOT + ra_ks + i * 32 * C::ROW_BYTES);
+      for (int j0 = 0; j0 < C::NB; j0 += 2) {
+        const int w = C::NB - j0 < 2 ? 1 : 2;
+        bf16x8 b[2];
 #pragma unroll
-      for (int j = 0; j < C::TN; ++j)
-        b[j] = *(const __attribute__((address_space(3))) bf16x8*)(smem + STAGE * C::SLOT + rb_ks + j * 32 * C::ROW_BYTES);
-      // all reads of a k-step are issued before its first multiplication; the scheduler then overlaps
-      // them with the previous k-step's last multiplications instead of starting every k-step by waiting
-      __builtin_amdgcn_sched_barrier(0);
+        for (int j = 0; j < w; ++j)
+          b[j] = *(const __attribute__((address_space(3))) bf16x8*)(smem + STAGE * C::SLOT + rb_ks + (j0 + j) * 16 * C::ROW_BYTES);
+        const int group = ks * ((C::NB + 1) / 2) + j0 / 2;
+        if (LOAD && group > 0) {
+          issue_one(LSTAGE, smem, v, kt_load, nk, 2 * (group - 1));
+          issue_one(LSTAGE, smem, v, kt_load, nk, 2 * (group - 1) + 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < C::TM; ++i)
+        for (int i = 0; i < C::MB; ++i)
 #pragma unroll
-        for (int j = 0; j < C::TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < w; ++j) mfma(acc[i][j0 + j], a[i], b[j]);
+      }
     }
+    settle(acc);
   }
 
   // Ring of four (128 x 128 tiles that have a CU to themselves, the reference pass): such a workgroup waits for the
@@ -294,10 +354,15 @@ struct Mainloop {
   // loads have landed, barrier (which also tells that every wave is done with the other slot),
   // refill the other slot with the next block, multiply.  Branches are wave-uniform and touch no
   // accumulator.
-  __device__ __forceinline__ void step(const int S, lds_char_ptr smem, int kt, int nk, f32x16 (&acc)[C::TM][C::TN]) {
+  __device__ __forceinline__ void step(const int S, lds_char_ptr smem, int kt, int nk, f32x4 (&acc)[C::MB][C::NB]) {
     if (C::NS == 2) {
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
       __syncthreads();
+      if (kSpread) {
+        // past the last block the loads find nothing (load_voff); finish() waits for them all the same
+        compute<true>(S, smem, acc, S ^ 1, kt + 1, nk);
+        return;
+      }
       if (kt + 1 < nk) issue(S ^ 1, smem, kt + 1, nk);
     } else {
       // Blocks kt + 1 and kt + 2 stay in flight (loads issued later than block kt's by someone else only make the wait
@@ -313,7 +378,7 @@ struct Mainloop {
       __builtin_amdgcn_sched_barrier(0);
       if (kt + 3 < nk) issue((S + 3) & 3, smem, kt + 3, nk);
     }
-    compute(S, smem, acc);
+    compute<false>(S, smem, acc);
   }
 
   // Starts a tile: k-block 0 into slot 0 (ring of four: blocks 0 .. 2).  Every wave must be past its last LDS read of the
@@ -334,7 +399,7 @@ struct Mainloop {
   // nothing.  It waits for both blocks: waiting for the first alone (vmcnt = the second block's loads, and a bare
   // s_barrier, since __syncthreads() waits for every outstanding load itself) measured no different.
   template <bool PRELOADED = false>
-  __device__ __forceinline__ void steps(lds_char_ptr smem, int k0, int k1, int nk, f32x16 (&acc)[C::TM][C::TN]) {
+  __device__ __forceinline__ void steps(lds_char_ptr smem, int k0, int k1, int nk, f32x4 (&acc)[C::MB][C::NB]) {
     int kt = k0;
     if (C::NS == 4) {
       for (; kt + 4 <= k1; kt += 4) {
@@ -351,7 +416,7 @@ struct Mainloop {
     if (PRELOADED) {
       __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
       __syncthreads();
-      compute(0, smem, acc);
+      compute<false>(0, smem, acc);
       kt = 1;
       if (kt < k1) {
         step(1, smem, 1, nk, acc);
@@ -366,27 +431,81 @@ struct Mainloop {
   }
 
   // acc += A_tile * B_tile^T over k-blocks [0, nk) after start().  Ends with a barrier: on return
-  // every wave is done reading LDS, so the caller may reuse it (or start() the next tile) at once.
+  // every wave is done reading LDS and every load into it has landed, so the caller may reuse it (or start() the next
+  // tile) at once.
   template <bool PRELOADED = false>
-  __device__ __forceinline__ void finish(lds_char_ptr smem, int nk, f32x16 (&acc)[C::TM][C::TN]) {
+  __device__ __forceinline__ void finish(lds_char_ptr smem, int nk, f32x4 (&acc)[C::MB][C::NB]) {
     steps<PRELOADED>(smem, 0, nk, nk, acc);
+    drain();
+  }
+  // ... the end of it, for a caller of steps().
+  static __device__ __forceinline__ void drain() {
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __syncthreads();
   }
 };
 
 template <class C>
-__device__ __forceinline__ void zero_acc(f32x16 (&acc)[C::TM][C::TN]) {
+__device__ __forceinline__ void zero_acc(f32x4 (&acc)[C::MB][C::NB]) {
 #pragma unroll
-  for (int i = 0; i < C::TM; ++i)
+  for (int i = 0; i < C::MB; ++i)
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < C::NB; ++j) {
+      acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      asm volatile("" : "+v"(acc[i][j]));     // here, and not in front of the multiplication that adds to it
+    }
 }
 
-// Row offset (within the wave's 32*TM rows, before the lane-half term) of
-// accumulator register r of m-block i.
-__device__ __forceinline__ constexpr int acc_row(int i, int r) { return i * 32 + 8 * (r >> 2) + (r & 3); }
+// Where a lane stands in its wavefront's patch: accumulator register r of block (i, j) is row 16 i + 4 g + r, column 16 j + c.
+template <class C>
+struct Lane {
+  int wm, wn, g, c;
+  __device__ __forceinline__ Lane() {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    wm = wave / C::WN;
+    wn = wave % C::WN;
+    g = lane >> 4;
+    c = lane & 15;
+  }
+  __device__ __forceinline__ int row0() const { return wm * C::WROWS + 4 * g; }    // in the tile: row of (i = 0, r = 0)
+  __device__ __forceinline__ int col0() const { return wn * C::WCOLS + c; }        // ... column of j = 0
+};
+
+// Rows past `rows` of a tile whose row of (i = 0, r = 0) is row0 take the value v.
+template <class C>
+__device__ __forceinline__ void fill_rows_past(f32x4 (&acc)[C::MB][C::NB], int row0, int rows, float v) {
+#pragma unroll
+  for (int i = 0; i < C::MB; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (row0 + 16 * i + r >= rows) {
+#pragma unroll
+        for (int j = 0; j < C::NB; ++j) acc[i][j][r] = v;
+      }
+}
+
+// Reduction over the four groups of 16 lanes, four columns at a time: group g ends with column g's result.  A swap hands
+// one half of the lanes the other column's partial results, so three swaps and three operations serve four columns.
+template <class Op>
+__device__ __forceinline__ float reduce4(const float (&x)[4], Op op) {
+  auto swap32 = [&](float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return op(__uint_as_float(r[0]), __uint_as_float(r[1]));    // lower half: a over both halves; upper half: b
+  };
+  const float p = swap32(x[0], x[2]), q = swap32(x[1], x[3]);
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(p), __float_as_uint(q), false, false);
+  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+// ... and back: x[k] = what group k holds in y.
+__device__ __forceinline__ void spread4(float y, float (&x)[4]) {
+  const uint32_t u = __float_as_uint(y);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);      // groups 0, 0, 2, 2 and 1, 1, 3, 3
+  const auto e = __builtin_amdgcn_permlane32_swap(r[0], r[0], false, false), o = __builtin_amdgcn_permlane32_swap(r[1], r[1], false, false);
+  x[0] = __uint_as_float(e[0]);
+  x[1] = __uint_as_float(o[0]);
+  x[2] = __uint_as_float(e[1]);
+  x[3] = __uint_as_float(o[1]);
+}
 
 // ---------------------------------------------------------------------------
 // bf16 staging of an accumulator tile through LDS for 16-byte coalesced stores.
@@ -398,27 +517,17 @@ __device__ __forceinline__ constexpr int acc_row(int i, int r) { return i * 32 +
 // LDS chunk [n][m] (n = the BN / WN columns of wave column `chunk`): each lane of those waves
 // writes 4 consecutive m (8 bytes) per step.
 template <class C>
-__device__ __forceinline__ void stage_nm(lds_char_ptr smem, const f32x16 (&acc)[C::TM][C::TN], int chunk) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / C::WN, wn = wave % C::WN;
-  const int h = lane >> 5;
-  if (wn != chunk) return;
+__device__ __forceinline__ void stage_nm(lds_char_ptr smem, const f32x4 (&acc)[C::MB][C::NB], int chunk) {
+  const Lane<C> at;
+  if (at.wn != chunk) return;
 #pragma unroll
-  for (int j = 0; j < C::TN; ++j) {
-    const int n_l = j * 32 + (lane & 31);
+  for (int j = 0; j < C::NB; ++j)
 #pragma unroll
-    for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int m_l = wm * C::TM * 32 + i * 32 + 8 * q + 4 * h;
-        bf16x4 v;
-        v[0] = (bf16_t)acc[i][j][4 * q + 0];
-        v[1] = (bf16_t)acc[i][j][4 * q + 1];
-        v[2] = (bf16_t)acc[i][j][4 * q + 2];
-        v[3] = (bf16_t)acc[i][j][4 * q + 3];
-        *(__attribute__((address_space(3))) bf16x4*)(smem + n_l * C::PITCH_NM + m_l * 2) = v;
-      }
-  }
+    for (int i = 0; i < C::MB; ++i) {
+      const f32x4 x = acc[i][j];
+      *(__attribute__((address_space(3))) bf16x4*)(smem + (j * 16 + at.c) * C::PITCH_NM + (at.row0() + 16 * i) * 2) =
+          bf16x4{(bf16_t)x[0], (bf16_t)x[1], (bf16_t)x[2], (bf16_t)x[3]};
+    }
 }
 
 // Staged chunk -> out[n][m] (row pitch ldo elements, pointer at the tile origin):
@@ -437,199 +546,93 @@ __device__ __forceinline__ void store_nm(lds_char_ptr smem, bf16_t* out, int64_t
   }
 }
 
-// Staged chunk [n][m] -> packed n-side matrix whose rows are the n index and whose k index is m:
-// `strip` is block (n-tile, 0) of the destination, kb0 the first k-block (m0 / 64).  Whole rows are
-// written (the packed buffers are padded to whole tiles; padding must be zeros).
-template <class C>
-__device__ __forceinline__ void store_nm_packed(lds_char_ptr smem, bf16_t* strip, int kb0, int chunk) {
-  constexpr int CH = C::BM / 8;
-  char* dst = (char*)strip + (int64_t)kb0 * C::STAGE_B;
-  for (int idx = threadIdx.x; idx < C::NM_ROWS * CH; idx += C::NT) {
-    const int n_l = idx / CH, ch = idx % CH;
-    const int n = chunk * C::NM_ROWS + n_l;
-    const u32x4 v = *(const __attribute__((address_space(3))) u32x4*)(smem + n_l * C::PITCH_NM + ch * 16);
-    *(u32x4*)(dst + (ch >> 3) * C::STAGE_B + n * kPackRowBytes + (ch & 7) * 16) = v;
-  }
-}
-
-// LDS chunk [m][n] (m = the BM / MN_CHUNKS rows of wave rows chunk * WM / MN_CHUNKS ...): 2-byte
-// writes, consecutive lanes write consecutive n.
-template <class C>
-__device__ __forceinline__ void stage_mn(lds_char_ptr smem, const f32x16 (&acc)[C::TM][C::TN], int chunk) {
-  constexpr int WPC = C::WM / C::MN_CHUNKS;   // wave rows per chunk
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / C::WN, wn = wave % C::WN;
-  const int h = lane >> 5;
-  if (wm / WPC != chunk) return;
-#pragma unroll
-  for (int j = 0; j < C::TN; ++j) {
-    const int n_l = wn * C::TN * 32 + j * 32 + (lane & 31);
-#pragma unroll
-    for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m_l = (wm % WPC) * C::TM * 32 + acc_row(i, r) + 4 * h;
-        *(__attribute__((address_space(3))) bf16_t*)(smem + m_l * C::PITCH_MN + n_l * 2) = (bf16_t)acc[i][j][r];
-      }
-  }
-}
-
-// Staged chunk [m][n] -> packed n-side matrix whose rows are the m index (global row m0 + ...,
-// blocks of BN rows) and whose k index is n: `base` is the destination matrix, n_kt its strip
-// pitch in k-blocks, kb0 the first k-block (n0 / 64).
-template <class C>
-__device__ __forceinline__ void store_mn_packed(lds_char_ptr smem, bf16_t* base, int n_kt, int m0, int kb0, int chunk) {
-  constexpr int CH = C::BN / 8;
-  for (int idx = threadIdx.x; idx < C::MN_ROWS * CH; idx += C::NT) {
-    const int m_l = idx / CH, ch = idx % CH;
-    const int m = m0 + chunk * C::MN_ROWS + m_l;
-    const int blk = m / C::BN, r = m - blk * C::BN;
-    const u32x4 v = *(const __attribute__((address_space(3))) u32x4*)(smem + m_l * C::PITCH_MN + ch * 16);
-    char* dst = (char*)base + ((int64_t)blk * n_kt + kb0 + (ch >> 3)) * C::STAGE_B;
-    *(u32x4*)(dst + r * kPackRowBytes + (ch & 7) * 16) = v;
-  }
-}
-
-// Both packed copies of a finished tile: rows = n (tokens) with k = m, and rows = m with k = n.
-template <class C>
-__device__ __forceinline__ void store_tile_both_ways(lds_char_ptr smem, const f32x16 (&acc)[C::TM][C::TN],
-                                                     bf16_t* Gp_strip, int m0, bf16_t* GTp, int gt_n_kt, int64_t n0) {
-#pragma unroll 1
-  for (int c = 0; c < C::NM_CHUNKS; ++c) {
-    stage_nm<C>(smem, acc, c);
-    __syncthreads();
-    store_nm_packed<C>(smem, Gp_strip, m0 / kPackK, c);
-    __syncthreads();
-  }
-#pragma unroll 1
-  for (int c = 0; c < C::MN_CHUNKS; ++c) {
-    stage_mn<C>(smem, acc, c);
-    __syncthreads();
-    store_mn_packed<C>(smem, GTp, gt_n_kt, m0, (int)(n0 / kPackK), c);
-    __syncthreads();
-  }
-}
-
 // ---------------------------------------------------------------------------
-// The same two packed copies from a tile already rounded to bf16 pairs:
-// pk[i][j][p] holds rows acc_row(i, 2p) and acc_row(i, 2p) + 1 (low / high half) of column j.
-// Half the registers of the fp32 tile, so nothing spills around the stores.
+// Two packed copies of a tile rounded to bf16 pairs: pk[i][j][p] holds rows 2p and 2p + 1 (low / high half) of the lane's
+// four in block (i, j).  Half the registers of the fp32 tile, so nothing spills around the stores.
 // ---------------------------------------------------------------------------
 
-// 4 x 4 transpose of 16-byte pieces across the four lanes of a quad: lane q hands its piece c to
-// lane c and ends up holding, as piece r, what lane r held as piece q.  Two butterfly steps
-// (partner lane ^ 1, then lane ^ 2), each a select, a quad-permute DPP move and two selects per
-// exchanged piece.  All four lanes of the quad must be active.
-template <int CTRL, class V4>
-__device__ __forceinline__ V4 quad_xchg(const V4 v) {
-  V4 r;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const auto x = v[e];   // a copy: a vector element is not an object whose bytes can be reinterpreted in place
-    r[e] = __builtin_bit_cast(decltype(x), __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
-  }
-  return r;
-}
-template <class V4>
-__device__ __forceinline__ void quad_transpose(V4 (&p)[4]) {
-  const bool b0 = (threadIdx.x & 1) != 0, b1 = (threadIdx.x & 2) != 0;
-#pragma unroll
-  for (int c = 0; c < 4; c += 2) {       // lane bit 0 <-> piece bit 0
-    const V4 r = quad_xchg<0xB1 /* quad_perm 1,0,3,2 */>(b0 ? p[c] : p[c + 1]);
-    p[c] = b0 ? r : p[c];
-    p[c + 1] = b0 ? p[c + 1] : r;
-  }
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {          // lane bit 1 <-> piece bit 1
-    const V4 r = quad_xchg<0x4E /* quad_perm 2,3,0,1 */>(b1 ? p[c] : p[c + 2]);
-    p[c] = b1 ? r : p[c];
-    p[c + 2] = b1 ? p[c + 2] : r;
-  }
-}
-
-// Copy with rows = n, k = m, straight from registers.  A lane owns 4 consecutive m (8 bytes) of its
-// row n per (i, q) and the other lane half owns the 8 bytes next to them.  The halves first trade
-// registers (v_permlane32_swap: the lower half hands over its pieces q = 2, 3 and receives the
-// upper half's q = 0, 1), after which each lane holds two 16-byte pieces per MFMA block row i, four
-// in all: with its other half, the whole 128-byte line of row n in this k-block.  Stored as they are,
-// every store instruction would scatter 16-byte pieces over 32 lines (measured: 43 bytes per write
-// request over the kernel, where a request can carry 64).  So the four lanes of a quad, which hold four
-// neighbouring rows, transpose their pieces first: lane q then holds piece q of each of the four
-// rows, and every store instruction writes whole lines, 8 lanes per line (+2.7 % on the sweep).
-// Destroys pk.  `dst` is the destination matrix, n_kt its strip pitch in k-blocks, n0 the tile's first row, kb0 the first
+// Copy with rows = n, k = m, straight from registers.  A lane owns 4 consecutive m (8 bytes) of its row n per block; the
+// groups trade registers between two block rows (v_permlane16_swap), after which a lane holds a 16-byte piece of its row and
+// the four lanes of a row 64 bytes, as much as a write request carries.  Stored in 16-byte pieces all over the lines, the
+// sweep's write requests averaged 43 bytes and the kernel took 2.7 % longer.
+// `dst` is the destination matrix, n_kt its strip pitch in k-blocks, n0 the tile's first row, kb0 the first
 // k-block (m0 / 64).
 template <class C>
-__device__ __forceinline__ void store_nm_packed_direct(uint32_t (&pk)[C::TM][C::TN][8], bf16_t* dst, int n_kt, int64_t n0, int kb0) {
-  static_assert(C::TM == 2 && C::TM * 32 == kPackK, "a wave row spans exactly one packed k-block: 4 pieces of 16 bytes per lane");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / C::WN, wn = wave % C::WN;
-  const int h = lane >> 5, q = lane & 3;
-  // piece q of a row sits at byte (q >> 1) * 64 + 32 h + 16 (q & 1) of its 128-byte line
-  char* base = (char*)dst + (n0 / C::PACK_B * n_kt + kb0 + wm) * C::PITCH_B + (n0 % C::PACK_B) * kPackRowBytes +
-               (q >> 1) * 64 + 32 * h + 16 * (q & 1);
+__device__ __forceinline__ void store_nm_packed_direct(const uint32_t (&pk)[C::MB][C::NB][2], bf16_t* dst, int n_kt, int64_t n0, int kb0) {
+  static_assert(C::WROWS == kPackK, "a wave row spans exactly one packed k-block");
+  const Lane<C> at;
+  // the piece of block rows 2q, 2q + 1 sits at byte 64 q + 32 (g & 1) + 16 (g >> 1) of its row's 128-byte line
+  char* base = (char*)dst + (n0 / C::PACK_B * n_kt + kb0 + at.wm) * C::PITCH_B + (n0 % C::PACK_B + at.col0()) * kPackRowBytes +
+               32 * (at.g & 1) + 16 * (at.g >> 1);
 #pragma unroll
-  for (int j = 0; j < C::TN; ++j) {
-    u32x4 piece[4];
+  for (int j = 0; j < C::NB; ++j)
 #pragma unroll
-    for (int i = 0; i < C::TM; ++i) {
-      uint32_t a[4], b[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const auto r = __builtin_amdgcn_permlane32_swap(pk[i][j][e], pk[i][j][e + 4], false, false);
-        a[e] = r[0];
-        b[e] = r[1];
-      }
-      piece[2 * i] = u32x4{a[0], a[1], b[0], b[1]};
-      piece[2 * i + 1] = u32x4{a[2], a[3], b[2], b[3]};
+    for (int q = 0; q < C::MB / 2; ++q) {
+      const auto lo = __builtin_amdgcn_permlane16_swap(pk[2 * q][j][0], pk[2 * q + 1][j][0], false, false);
+      const auto hi = __builtin_amdgcn_permlane16_swap(pk[2 * q][j][1], pk[2 * q + 1][j][1], false, false);
+      *(u32x4*)(base + j * 16 * kPackRowBytes + 64 * q) = u32x4{lo[0], hi[0], lo[1], hi[1]};
     }
-    // the four lanes of a quad hold four neighbouring rows: after the transpose lane q holds piece q of
-    // each of them, and every store instruction writes whole 128-byte lines (8 lanes per line)
-    quad_transpose(piece);
-    const int n_q = wn * C::TN * 32 + j * 32 + (lane & 28);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) *(u32x4*)(base + (n_q + r) * kPackRowBytes) = piece[r];
-  }
 }
 
-// LDS chunk [m][n] from the packed pairs: chunk i holds MFMA block row i of every wave row (32 rows
+// LDS chunk [m][n] from the packed pairs: chunk q holds MFMA block rows 2q and 2q + 1 of every wave row (32 rows
 // each, WM * 32 rows in all), so all waves stage at once.  Neighbouring lanes (columns n, n + 1) swap
 // halves so that each lane writes 4 bytes: the even lane row m (its own low half, the neighbour's
 // low half), the odd lane row m + 1 (the neighbour's high half, its own high half).
 template <class C>
-__device__ __forceinline__ void stage_mn_pk(lds_char_ptr smem, const uint32_t (&pk)[C::TM][C::TN][8], const int i) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / C::WN, wn = wave % C::WN;
-  const int h = lane >> 5, odd = lane & 1;
+__device__ __forceinline__ void stage_mn_pk(lds_char_ptr smem, const uint32_t (&pk)[C::MB][C::NB][2], const int q) {
+  const Lane<C> at;
+  const int odd = at.c & 1;
   // v_perm_b32 picks bytes from {neighbour (4..7), own (0..3)}
   const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+  const lds_char_ptr base = smem + (at.wm * 32 + 4 * at.g + odd) * C::PITCH_MN + (at.col0() - odd) * 2;
 #pragma unroll
-  for (int j = 0; j < C::TN; ++j) {
-    const int n_l = wn * C::TN * 32 + j * 32 + (lane & 31) - odd;
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      const uint32_t own = pk[i][j][p];
-      const uint32_t nbr = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, true);
-      const uint32_t w = __builtin_amdgcn_perm(nbr, own, sel);
-      const int m_l = wm * 32 + acc_row(0, 2 * p) + 4 * h + odd;
-      *(__attribute__((address_space(3))) uint32_t*)(smem + m_l * C::PITCH_MN + n_l * 2) = w;
-    }
-  }
+    for (int j = 0; j < C::NB; ++j)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const uint32_t own = pk[2 * q + i][j][p];
+        const uint32_t nbr = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, true);
+        *(__attribute__((address_space(3))) uint32_t*)(base + (16 * i + 2 * p) * C::PITCH_MN + j * 32) =
+            __builtin_amdgcn_perm(nbr, own, sel);
+      }
 }
 
-// Chunk i staged by stage_mn_pk -> packed n-side matrix whose rows are the m index (global row
+// Chunk q staged by stage_mn_pk -> packed n-side matrix whose rows are the m index (global row
 // m0 + ..., blocks of PACK_B rows) and whose k index is n; n_kt is the destination's strip pitch in
 // k-blocks, kb0 the first k-block (n0 / 64).
 template <class C>
-__device__ __forceinline__ void store_mn_pk_packed(lds_char_ptr smem, bf16_t* base, int n_kt, int m0, int kb0, int i) {
+__device__ __forceinline__ void store_mn_pk_packed(lds_char_ptr smem, bf16_t* base, int n_kt, int m0, int kb0, int q) {
   constexpr int CH = C::BN / 8;
-  for (int idx = threadIdx.x; idx < C::WM * 32 * CH; idx += C::NT) {
+  for (int idx = threadIdx.x; idx < C::MN_ROWS * CH; idx += C::NT) {
     const int m_l = idx / CH, ch = idx % CH;
-    const int m = m0 + (m_l >> 5) * (C::TM * 32) + i * 32 + (m_l & 31);
+    const int m = m0 + (m_l >> 5) * C::WROWS + q * 32 + (m_l & 31);
     const int blk = m / C::PACK_B, r = m - blk * C::PACK_B;
     const u32x4 v = *(const __attribute__((address_space(3))) u32x4*)(smem + m_l * C::PITCH_MN + ch * 16);
     char* dst = (char*)base + ((int64_t)blk * n_kt + kb0 + (ch >> 3)) * C::PITCH_B;
     *(u32x4*)(dst + r * kPackRowBytes + (ch & 7) * 16) = v;
   }
+}
+
+// Both packed copies of a tile: rows = vocabulary (m) with k = tokens (n), through LDS, two MFMA block rows of every wave at a
+// time, then rows = tokens with k = vocabulary, whose stores drain after the workgroup has gone.
+template <class C>
+__device__ __forceinline__ void store_both_copies(lds_char_ptr smem, const uint32_t (&pk)[C::MB][C::NB][2], bf16_t* Gp, int g_n_kt,
+                                                  bf16_t* GTp, int gt_n_kt, int m0, int64_t n0) {
+  static_assert(C::STAGE_MN <= C::LDS_BYTES, "staging chunk must fit");
+#pragma unroll
+  for (int q = 0; q < C::MN_CHUNKS; ++q) {
+    if (q > 0) lds_barrier();
+    stage_mn_pk<C>(smem, pk, q);
+    lds_barrier();
+    store_mn_pk_packed<C>(smem, GTp, gt_n_kt, m0, (int)(n0 / kPackK), q);
+  }
+  store_nm_packed_direct<C>(pk, Gp, g_n_kt, n0, m0 / kPackK);
+}
+
+__device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
+  const bf16x2 v = {(bf16_t)lo, (bf16_t)hi};
+  return __builtin_bit_cast(uint32_t, v);
 }
 
 // Tile coordinates for a logical workgroup id: tiles are walked in strips of
@@ -695,15 +698,14 @@ k_fwd_lse(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int
   ml.rows_init(d);
   ml.set_b(H, nt, T, d, n_kt);
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / C::WN, wn = wave % C::WN;
-  const int h = lane >> 5;
-
-  float m2[C::TN], s[C::TN], u[C::TN];
+  const Lane<C> at;
+  // the running values of column 16 (4 q + g) + c are lane group g's: a quarter of the columns per lane
+  constexpr int Q = (C::NB + 3) / 4;
+  float m2[Q], s[Q], u[Q];
 #pragma unroll
-  for (int j = 0; j < C::TN; ++j) { m2[j] = kNegHuge; s[j] = 0.f; u[j] = 0.f; }
+  for (int q = 0; q < Q; ++q) { m2[q] = kNegHuge; s[q] = 0.f; u[q] = 0.f; }
 
-  f32x16 acc[C::TM][C::TN];
+  f32x4 acc[C::MB][C::NB];
   if (mt_begin < mt_end) {
     ml.set_a(W, mt_begin, V, d, n_kt);
     ml.start_preload(smem, n_kt);
@@ -717,63 +719,58 @@ k_fwd_lse(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int
       ml.start_preload(smem, n_kt);
     }
 
-    if (m0 + C::BM > V) {  // ragged last vocabulary tile: rows >= V do not exist (their logits are 0, not -inf)
-      const int row0 = m0 + wm * C::TM * 32 + 4 * h;
+    // ragged last vocabulary tile: rows >= V do not exist (their logits are 0, not -inf)
+    if (m0 + C::BM > V) fill_rows_past<C>(acc, m0 + at.row0(), V, -__builtin_inff());
 #pragma unroll
-      for (int i = 0; i < C::TM; ++i)
+    for (int q = 0; q < Q; ++q) {
+      float x[4];
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (row0 + acc_row(i, r) >= V) {
+      for (int k = 0; k < 4; ++k) {
+        x[k] = -__builtin_inff();
+        if (4 * q + k < C::NB) {
 #pragma unroll
-            for (int j = 0; j < C::TN; ++j) acc[i][j][r] = -__builtin_inff();
-          }
-    }
+          for (int i = 0; i < C::MB; ++i)
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j) {
-      float mx = -__builtin_inff();
-#pragma unroll
-      for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[i][j][r]);
-      const float mnew = fmaxf(m2[j], mx * kLog2e);
-      float sum = 0.f, usum = 0.f;
-#pragma unroll
-      for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r], kLog2e, -mnew));
-          sum += e;
-          // masked rows hold -inf with e = 0: keep their product out (0 * inf)
-          if (ENT) usum = __builtin_fmaf(e, e > 0.f ? acc[i][j][r] : 0.f, usum);
+            for (int r = 0; r < 4; ++r) x[k] = fmaxf(x[k], acc[i][4 * q + k][r]);
         }
-      const float scale = __builtin_amdgcn_exp2f(m2[j] - mnew);
-      s[j] = s[j] * scale + sum;
-      if (ENT) u[j] = u[j] * scale + usum;
-      m2[j] = mnew;
+      }
+      const float mnew = fmaxf(m2[q], reduce4(x, [](float a, float b) { return fmaxf(a, b); }) * kLog2e);
+      float ref[4], us[4];
+      spread4(mnew, ref);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        x[k] = us[k] = 0.f;
+        if (4 * q + k < C::NB) {
+#pragma unroll
+          for (int i = 0; i < C::MB; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float z = acc[i][4 * q + k][r], e = __builtin_amdgcn_exp2f(__builtin_fmaf(z, kLog2e, -ref[k]));
+              x[k] += e;
+              // masked rows hold -inf with e = 0: keep their product out (0 * inf)
+              if (ENT) us[k] = __builtin_fmaf(e, e > 0.f ? z : 0.f, us[k]);
+            }
+        }
+      }
+      const auto add = [](float a, float b) { return a + b; };
+      const float scale = __builtin_amdgcn_exp2f(m2[q] - mnew);
+      s[q] = s[q] * scale + reduce4(x, add);
+      if (ENT) u[q] = u[q] * scale + reduce4(us, add);
+      m2[q] = mnew;
     }
   }
 
-  // merge the two lane halves (same token, different vocabulary rows) ...
-#pragma unroll
-  for (int j = 0; j < C::TN; ++j) {
-    const float mo = __shfl_xor(m2[j], 32, 64), so = __shfl_xor(s[j], 32, 64);
-    const float M = fmaxf(m2[j], mo);
-    const float fa = __builtin_amdgcn_exp2f(m2[j] - M), fb = __builtin_amdgcn_exp2f(mo - M);
-    s[j] = s[j] * fa + so * fb;
-    if (ENT) u[j] = u[j] * fa + __shfl_xor(u[j], 32, 64) * fb;
-    m2[j] = M;
-  }
-  // ... then the WM waves stacked along the vocabulary, through LDS.
+  // merge the WM waves stacked along the vocabulary, through LDS.
   typedef float f32x2 __attribute__((ext_vector_type(2)));
   __attribute__((address_space(3))) f32x2* red = (__attribute__((address_space(3))) f32x2*)smem;
   __attribute__((address_space(3))) float* red_u = (__attribute__((address_space(3))) float*)(smem + C::RED_BYTES);
-  if (h == 0) {
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j) {
-      red[wm * C::BN + wn * C::TN * 32 + j * 32 + lane] = f32x2{m2[j], s[j]};
-      if (ENT) red_u[wm * C::BN + wn * C::TN * 32 + j * 32 + lane] = u[j];
+  for (int q = 0; q < Q; ++q)
+    if (4 * q + at.g < C::NB) {
+      const int n_l = at.wm * C::BN + at.col0() + (4 * q + at.g) * 16;
+      red[n_l] = f32x2{m2[q], s[q]};
+      if (ENT) red_u[n_l] = u[q];
     }
-  }
   __syncthreads();
   for (int n_l = threadIdx.x; n_l < C::BN; n_l += C::NT) {
     if (n0 + n_l < T) {
@@ -829,16 +826,13 @@ k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, 
   ml.rows_init(d);
   ml.set_b(H, nt, T, d, n_kt);
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / C::WN, wn = wave % C::WN;
-  const int h = lane >> 5;
-
-  float best[C::TN];
-  int arg[C::TN];
+  const Lane<C> at;
+  float best[C::NB];
+  int arg[C::NB];
 #pragma unroll
-  for (int j = 0; j < C::TN; ++j) { best[j] = -__builtin_inff(); arg[j] = 0x7FFFFFFF; }
+  for (int j = 0; j < C::NB; ++j) { best[j] = -__builtin_inff(); arg[j] = 0x7FFFFFFF; }
 
-  f32x16 acc[C::TM][C::TN];
+  f32x4 acc[C::MB][C::NB];
   if (mt_begin < mt_end) {
     ml.set_a(W, mt_begin, V, d, n_kt);
     ml.start_preload(smem, n_kt);
@@ -851,52 +845,41 @@ k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, 
       ml.set_a(W, mt + 1, V, d, n_kt);
       ml.start_preload(smem, n_kt);
     }
-    if (m0 + C::BM > V) {  // ragged last vocabulary tile: a logit of -inf is never drawn
-      const int row = m0 + wm * C::TM * 32 + 4 * h;
-#pragma unroll
-      for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (row + acc_row(i, r) >= V) {
-#pragma unroll
-            for (int j = 0; j < C::TN; ++j) acc[i][j][r] = -__builtin_inff();
-          }
-    }
+    // ragged last vocabulary tile: a logit of -inf is never drawn
+    if (m0 + C::BM > V) fill_rows_past<C>(acc, m0 + at.row0(), V, -__builtin_inff());
     // Rows outside, tokens inside: the first two Philox rounds multiply words that depend on the row block or on the token
     // alone, and are shared over the other.
-    const int row0 = m0 + wm * C::TM * 32 + 4 * h;
 #pragma unroll
-    for (int i = 0; i < C::TM; ++i)
+    for (int i = 0; i < C::MB; ++i) {
+      const int v0 = m0 + at.row0() + i * 16;          // multiple of 4: one Philox block
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int v0 = row0 + i * 32 + 8 * q;          // multiple of 4: one Philox block
+      for (int j = 0; j < C::NB; ++j) {
+        const int64_t t = n0 + at.col0() + j * 16;
+        uint32_t x[4];
+        philox4x32_10((uint32_t)(v0 >> 2), (uint32_t)t, (uint32_t)(t >> 32), 0u, seed_lo, seed_hi, x);
 #pragma unroll
-        for (int j = 0; j < C::TN; ++j) {
-          const int64_t t = n0 + wn * C::TN * 32 + j * 32 + (lane & 31);
-          uint32_t x[4];
-          philox4x32_10((uint32_t)(v0 >> 2), (uint32_t)t, (uint32_t)(t >> 32), 0u, seed_lo, seed_hi, x);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float sc = __builtin_fmaf(acc[i][j][4 * q + e], inv_temperature, gumbel_from_bits(x[e]));
-            if (sc > best[j]) { best[j] = sc; arg[j] = v0 + e; }   // indices rise: strict > keeps the smallest
-          }
+        for (int e = 0; e < 4; ++e) {
+          const float sc = __builtin_fmaf(acc[i][j][e], inv_temperature, gumbel_from_bits(x[e]));
+          if (sc > best[j]) { best[j] = sc; arg[j] = v0 + e; }   // indices rise: strict > keeps the smallest
         }
       }
+    }
   }
 
-  // merge the two lane halves, then the WM waves stacked along the vocabulary (through LDS)
+  // merge the four lane groups, then the WM waves stacked along the vocabulary (through LDS)
 #pragma unroll
-  for (int j = 0; j < C::TN; ++j) {
-    const float so = __shfl_xor(best[j], 32, 64);
-    const int io = __shfl_xor(arg[j], 32, 64);
-    if (better(so, io, best[j], arg[j])) { best[j] = so; arg[j] = io; }
-  }
+  for (int j = 0; j < C::NB; ++j)
+#pragma unroll
+    for (int o = 16; o < 64; o *= 2) {
+      const float so = __shfl_xor(best[j], o, 64);
+      const int io = __shfl_xor(arg[j], o, 64);
+      if (better(so, io, best[j], arg[j])) { best[j] = so; arg[j] = io; }
+    }
   typedef float f32x2 __attribute__((ext_vector_type(2)));
   __attribute__((address_space(3))) f32x2* red = (__attribute__((address_space(3))) f32x2*)smem;
-  if (h == 0) {
+  if (at.g == 0) {
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j)
-      red[wm * C::BN + wn * C::TN * 32 + j * 32 + lane] = f32x2{best[j], __int_as_float(arg[j])};
+    for (int j = 0; j < C::NB; ++j) red[at.wm * C::BN + at.col0() + j * 16] = f32x2{best[j], __int_as_float(arg[j])};
   }
   __syncthreads();
   for (int n_l = threadIdx.x; n_l < C::BN; n_l += C::NT) {
@@ -954,64 +937,35 @@ k_bwd_dz(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H_panel, int V
   ml.set_a(W, mt, V, d, n_kt);
   ml.set_b(H_panel, nt, n_valid, d, n_kt);
 
-  f32x16 acc[C::TM][C::TN];
+  f32x4 acc[C::MB][C::NB];
   zero_acc<C>(acc);
   ml.start(smem, n_kt);
   ml.finish(smem, n_kt, acc);
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / C::WN, wn = wave % C::WN;
-  const int h = lane >> 5;
-  const int wave_row0 = m0 + wm * C::TM * 32;      // first vocabulary row of this wave
-  const int row0 = wave_row0 + 4 * h;              // ... of this lane
-
-  bool any_hit = false;
-  float ninv[C::TN], l2[C::TN];   // -1 / (1 - p_y), lse in the exp2 domain
-  int ytok[C::TN];
+  const Lane<C> at;
+  const int row0 = m0 + at.row0();                 // first vocabulary row of this lane
+  uint32_t pk[C::MB][C::NB][2];
 #pragma unroll
-  for (int j = 0; j < C::TN; ++j) {
-    const int64_t n = n0 + wn * C::TN * 32 + j * 32 + (lane & 31);
+  for (int j = 0; j < C::NB; ++j) {
+    const int64_t n = n0 + at.col0() + j * 16;
     const bool ok = n < n_valid;
-    ninv[j] = ok ? -inv_omp[n] : 0.f;
-    l2[j] = ok ? lse2[n] : 0.f;
-    ytok[j] = ok ? tokens[n] : -1;
-    any_hit |= (unsigned)(ytok[j] - wave_row0) < (unsigned)(C::TM * 32);
-  }
+    const float ninv = ok ? -inv_omp[n] : 0.f, l2 = ok ? lse2[n] : 0.f;    // -1 / (1 - p_y), lse in the exp2 domain
+    const int rel = ok ? tokens[n] - row0 : -1;                            // the one-hot term's row
 #pragma unroll
-  for (int j = 0; j < C::TN; ++j)
+    for (int i = 0; i < C::MB; ++i) {
+      float x[4];
 #pragma unroll
-    for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r], kLog2e, -l2[j]));
-        acc[i][j][r] = p * ninv[j];
+      for (int r = 0; r < 4; ++r) {
+        x[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r], kLog2e, -l2)) * ninv;
+        if (rel == 16 * i + r) x[r] = ninv != 0.f ? 1.f : 0.f;
+        if (row0 + 16 * i + r >= V) x[r] = 0.f;     // rows past the vocabulary carry exp2(0 - lse2) garbage
       }
-  // the one-hot term: at most one element per token over the whole vocabulary,
-  // so only waves whose row range contains a sampled token look for it
-  if (__builtin_amdgcn_ballot_w64(any_hit) != 0) {
-#pragma unroll
-    for (int j = 0; j < C::TN; ++j) {
-      const int rel = ytok[j] - row0;
-#pragma unroll
-      for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (rel == acc_row(i, r)) acc[i][j][r] = ninv[j] != 0.f ? 1.f : 0.f;
+      pk[i][j][0] = bf16_pair(x[0], x[1]);
+      pk[i][j][1] = bf16_pair(x[2], x[3]);
     }
   }
-  if (m0 + C::BM > V) {  // rows past the vocabulary carry exp2(0 - lse2) garbage: clear them
-#pragma unroll
-    for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (row0 + acc_row(i, r) >= V) {
-#pragma unroll
-          for (int j = 0; j < C::TN; ++j) acc[i][j][r] = 0.f;
-        }
-  }
-
   // Gp: rows = tokens (n), k = vocabulary (m);  GTp: rows = vocabulary (m), k = tokens (n)
-  store_tile_both_ways<C>(smem, acc, Gp + (int64_t)nt * g_n_kt * (C::STAGE_B / 2), m0, GTp, gt_n_kt, n0);
+  store_both_copies<C>(smem, pk, Gp, g_n_kt, GTp, gt_n_kt, m0, n0);
 #endif
 }
 
@@ -1059,63 +1013,53 @@ k_sweep(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H_panel, int V,
   ml.set_a(W, mt, V, d, n_kt);
   ml.set_b(H_panel, nt, n_valid, d, n_kt);
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / C::WN, wn = wave % C::WN;
-  const int h = lane >> 5;
-  const int row0 = m0 + wm * C::TM * 32 + 4 * h;   // first vocabulary row of this lane
-
-  f32x16 acc[C::TM][C::TN];
+  const Lane<C> at;
+  f32x4 acc[C::MB][C::NB];
   zero_acc<C>(acc);
   ml.start(smem, n_kt);
   // the epilogue's per-token references are requested two k-blocks before the end, so that their
   // latency hides behind the last multiplications instead of stalling the epilogue
   const int k_early = n_kt > C::NS ? (n_kt - 2) & ~(C::NS - 1) : 0;
   ml.steps(smem, 0, k_early, n_kt, acc);
-  float r2v[C::TN];
+  float r2v[C::NB];
 #pragma unroll
-  for (int j = 0; j < C::TN; ++j) {
-    const int64_t n = n0 + wn * C::TN * 32 + j * 32 + (lane & 31);
+  for (int j = 0; j < C::NB; ++j) {
+    const int64_t n = n0 + at.col0() + j * 16;
     // token columns past the panel: reference +inf, every entry 2^(-inf) = 0
     r2v[j] = n < n_valid ? ref2[n] : __builtin_inff();
   }
   ml.steps(smem, k_early, n_kt, n_kt, acc);
-  __syncthreads();
+  ml.drain();
 
-  if (m0 + C::BM > V) {  // ragged last vocabulary tile: rows >= V do not exist (2^(-inf) = 0 below)
+  // ragged last vocabulary tile: rows >= V do not exist (2^(-inf) = 0 below)
+  if (m0 + C::BM > V) fill_rows_past<C>(acc, m0 + at.row0(), V, -__builtin_inff());
+  float csum[(C::NB + 3) / 4];    // columns 16 (4 q + g) + c, as in k_fwd_lse
+  uint32_t pk[C::MB][C::NB][2];   // the tile as bf16 pairs
 #pragma unroll
-    for (int i = 0; i < C::TM; ++i)
+  for (int q = 0; q < (C::NB + 3) / 4; ++q) {
+    float x[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (row0 + acc_row(i, r) >= V) {
+    for (int k = 0; k < 4; ++k) {
+      const int j = 4 * q + k;
+      if (j >= C::NB) continue;
 #pragma unroll
-          for (int j = 0; j < C::TN; ++j) acc[i][j][r] = -__builtin_inff();
+      for (int i = 0; i < C::MB; ++i)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][2 * p], kLog2e, -r2v[j]));
+          const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][2 * p + 1], kLog2e, -r2v[j]));
+          x[k] += e0;
+          x[k] += e1;
+          pk[i][j][p] = bf16_pair(e0, e1);
         }
-  }
-  float csum[C::TN];
-  uint32_t pk[C::TM][C::TN][8];   // the tile as bf16 pairs: rows acc_row(i, 2p), +1
-#pragma unroll
-  for (int j = 0; j < C::TN; ++j) {
-    const float r2 = r2v[j];
-    float sum = 0.f;
-#pragma unroll
-    for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-      for (int p = 0; p < 8; ++p) {
-        const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][2 * p], kLog2e, -r2));
-        const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][2 * p + 1], kLog2e, -r2));
-        sum += e0;
-        sum += e1;
-        const bf16x2 v = {(bf16_t)e0, (bf16_t)e1};
-        pk[i][j][p] = __builtin_bit_cast(uint32_t, v);
-      }
-    csum[j] = sum + __shfl_xor(sum, 32, 64);     // the two lane halves hold the same token
+    }
+    csum[q] = reduce4(x, [](float a, float b) { return a + b; });
   }
   // row sums: the WM waves stacked along the vocabulary, through LDS, in a fixed order
   __attribute__((address_space(3))) float* red = (__attribute__((address_space(3))) float*)smem;
-  if (h == 0) {
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j) red[wm * C::BN + wn * C::TN * 32 + j * 32 + lane] = csum[j];
-  }
+  for (int q = 0; q < (C::NB + 3) / 4; ++q)
+    if (4 * q + at.g < C::NB) red[at.wm * C::BN + at.col0() + (4 * q + at.g) * 16] = csum[q];
   lds_barrier();
   for (int n_l = threadIdx.x; n_l < C::BN; n_l += C::NT) {
     if (n0 + n_l < n_valid) {
@@ -1126,57 +1070,53 @@ k_sweep(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H_panel, int V,
     }
   }
   lds_barrier();
-  // GTp: rows = vocabulary (m), k = tokens (n), through LDS, one MFMA block row of every wave at a time
-  static_assert(C::WM * 32 * C::PITCH_MN <= C::LDS_BYTES, "staging chunk must fit");
-#pragma unroll
-  for (int i = 0; i < C::TM; ++i) {
-    if (i > 0) lds_barrier();
-    stage_mn_pk<C>(smem, pk, i);
-    lds_barrier();
-    store_mn_pk_packed<C>(smem, GTp, gt_n_kt, m0, (int)(n0 / kPackK), i);
-  }
-  // Gp: rows = tokens (n), k = vocabulary (m), straight from the registers (last: it consumes pk,
-  // and its stores drain after the workgroup has gone)
-  store_nm_packed_direct<C>(pk, Gp, g_n_kt, n0, m0 / kPackK);
+  store_both_copies<C>(smem, pk, Gp, g_n_kt, GTp, gt_n_kt, m0, n0);
 #endif
 }
 
+// 16 bytes of the neighbouring lane (lane ^ 1, which must be active).
+__device__ __forceinline__ f32x4 neighbour(const f32x4 v) {
+  f32x4 r;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float x = v[e];   // a copy: a vector element is not an object whose bytes can be reinterpreted in place
+    r[e] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, true));
+  }
+  return r;
+}
+
 // fp32 tile -> out[n][m] (n < n_rows, row pitch d = the m extent), overwritten or added to, straight from the
-// accumulators.
-// A lane owns 4 pieces of 4 consecutive m (16 bytes) of its row n per MFMA block; the four lanes of a
-// quad (four neighbouring rows) trade pieces so that lane q holds piece q of each of the four rows:
-// every load and store then covers whole 128-byte lines (8 lanes per line).  The four old values of
-// an MFMA block are requested together, from clamped (always valid) addresses, before the transpose,
-// so the read-add-write waits for memory once per block, not once per piece (eight at once spill).
+// accumulators.  A lane owns 16 bytes of its row n per block, the four groups 64 bytes; neighbouring lanes (rows n, n + 1)
+// trade pieces of two block rows, so that the even lane holds block row 2q of both rows, the odd one block row 2q + 1, and
+// every load and store covers whole 128-byte lines.  The old values of a block column are requested together,
+// from clamped (always valid) addresses, so the read-add-write waits for memory once per column, not once per piece.
 template <class C, bool ACCUMULATE>
-__device__ __forceinline__ void store_f32_tile(const f32x16 (&acc)[C::TM][C::TN], float* __restrict__ out, int d, int n_rows,
+__device__ __forceinline__ void store_f32_tile(const f32x4 (&acc)[C::MB][C::NB], float* __restrict__ out, int d, int n_rows,
                                                int m0, int n0) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / C::WN, wn = wave % C::WN;
-  const int h = lane >> 5, q = lane & 3;
+  const Lane<C> at;
+  const bool odd = (at.c & 1) != 0;
+  const int m = m0 + at.row0() + (odd ? 16 : 0);
 #pragma unroll
-  for (int j = 0; j < C::TN; ++j) {
-    const int n_q = n0 + wn * C::TN * 32 + j * 32 + (lane & 28);
+  for (int j = 0; j < C::NB; ++j) {
+    const int n = n0 + at.col0() + j * 16 - (odd ? 1 : 0);    // the even row; both lanes store it and the next
+    f32x4 old[C::MB];
+    if (ACCUMULATE) {
 #pragma unroll
-    for (int i = 0; i < C::TM; ++i) {
-      f32x4 piece[4], old[4];
-      const int m = m0 + wm * C::TM * 32 + i * 32 + 8 * q + 4 * h;
-      if (ACCUMULATE) {
-        const int mc = m < d ? m : d - 4;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int nc = n_q + r < n_rows ? n_q + r : n_rows - 1;
-          old[r] = *(const f32x4*)(out + (int64_t)nc * d + mc);
-        }
+      for (int i = 0; i < C::MB; ++i) {
+        const int mi = m + 32 * (i / 2), ni = n + (i & 1);
+        old[i] = *(const f32x4*)(out + (int64_t)(ni < n_rows ? ni : n_rows - 1) * d + (mi < d ? mi : d - 4));
       }
+    }
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        piece[c] = f32x4{acc[i][j][4 * c + 0], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2], acc[i][j][4 * c + 3]};
-      quad_transpose(piece);
+    for (int i = 0; i < C::MB; i += 2) {
+      const f32x4 lo = acc[i][j], hi = acc[i + 1][j];
+      const f32x4 got = neighbour(odd ? lo : hi);
+      const f32x4 piece[2] = {odd ? got : lo, odd ? hi : got};
+      const int mi = m + 16 * i;
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (m < d && n_q + r < n_rows)
-          *(f32x4*)(out + (int64_t)(n_q + r) * d + m) = ACCUMULATE ? piece[r] + old[r] : piece[r];
+      for (int r = 0; r < 2; ++r)
+        if (mi < d && n + r < n_rows)
+          *(f32x4*)(out + (int64_t)(n + r) * d + mi) = ACCUMULATE ? piece[r] + old[i + r] : piece[r];
     }
   }
 }
@@ -1221,7 +1161,7 @@ k_bwd_dh(const bf16_t* __restrict__ W /* or W^T, packed */, int V, int wt_n_kt, 
   else ml.set_a_packed(W, m0, wt_n_kt, k0);
   ml.set_b_packed(Gp, n0, g_n_kt, k0);
 
-  f32x16 acc[C::TM][C::TN];
+  f32x4 acc[C::MB][C::NB];
   zero_acc<C>(acc);
   ml.start(smem, k1 - k0);
   ml.finish(smem, k1 - k0, acc);
@@ -1230,15 +1170,13 @@ k_bwd_dh(const bf16_t* __restrict__ W /* or W^T, packed */, int V, int wt_n_kt, 
     store_f32_tile<C, false>(acc, part + (int64_t)split * n_valid * d, d, (int)n_valid, m0, (int)n0);
     return;
   }
-  {
-    const int lane = threadIdx.x & 63, wn = (threadIdx.x >> 6) % C::WN;
+  const Lane<C> at;
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j) {
-      const int64_t n = n0 + wn * C::TN * 32 + j * 32 + (lane & 31);
-      const float f = n < n_valid ? row_factor[n] : 0.f;
+  for (int j = 0; j < C::NB; ++j) {
+    const int64_t n = n0 + at.col0() + j * 16;
+    const float f = n < n_valid ? row_factor[n] : 0.f;
 #pragma unroll
-      for (int i = 0; i < C::TM; ++i) acc[i][j] *= f;
-    }
+    for (int i = 0; i < C::MB; ++i) acc[i][j] *= f;
   }
 #pragma unroll 1
   for (int c = 0; c < C::NM_CHUNKS; ++c) {
@@ -1305,7 +1243,7 @@ k_bwd_dw(const bf16_t* __restrict__ HTp, const bf16_t* __restrict__ GTp, int t_n
   ml.set_a_packed(HTp, m0, t_n_kt, 0);
   ml.set_b_packed(GTp, n0, t_n_kt, 0);
 
-  f32x16 acc[C::TM][C::TN];
+  f32x4 acc[C::MB][C::NB];
   zero_acc<C>(acc);
   ml.start(smem, nk);
   ml.finish(smem, nk, acc);

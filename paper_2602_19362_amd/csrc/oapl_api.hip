@@ -15,19 +15,19 @@
 namespace oapl {
 
 // 256 x 384 x 64 tiles, 8 wavefronts in a 4 x 2 grid, each a 64 x 192 patch
-// (2 x 6 MFMA blocks, 192 accumulator registers per lane), two wavefronts per
+// (4 x 12 MFMA blocks, 192 accumulator registers per lane), two wavefronts per
 // SIMD; operands in a ring of 2 LDS stages (160 KB, the whole LDS of a CU).
-typedef TileCfg<4, 2, 2, 6, 2> Cfg;
+typedef TileCfg<4, 2, 4, 12, 2> Cfg;
 static_assert(Cfg::BN == kPackRowsB, "n-side operands of the loss path are packed in blocks of one tile");
 // Where tiles of that size are too few to fill the chip (small heads and hidden sizes): 128 x 128, two workgroups per CU,
 // on the same packed blocks.
-typedef TileCfg<2, 2, 2, 2, 2, kPackRowsB> CfgSmall;
+typedef TileCfg<2, 2, 4, 4, 2, kPackRowsB> CfgSmall;
 // ... and, where there are no more of them than CUs, with a ring of four stages.
-typedef TileCfg<2, 2, 2, 2, 4, kPackRowsB> CfgDeep;
+typedef TileCfg<2, 2, 4, 4, 4, kPackRowsB> CfgDeep;
 // The sampling kernel carries a running (score, index) pair per column through the main loop and
 // draws Philox blocks in its epilogue: its largest tile is 256 x 256 (128 accumulators per lane),
 // with H packed in 256-row blocks for it where it reads packed operands.
-typedef TileCfg<4, 2, 2, 4, 2> CfgSample;
+typedef TileCfg<4, 2, 4, 8, 2> CfgSample;
 
 // Tiles of the scoring and sampling kernels over row-major operands.  A call of few tokens pays for every padded
 // token column and is bound by reading W once; a call of many is bound by operand delivery, which wants the largest
@@ -35,12 +35,17 @@ typedef TileCfg<4, 2, 2, 4, 2> CfgSample;
 // 6.0 TB/s for up to 64 tokens at d = 4096, where 256 x 64 reaches 5.0 and the 256 x 256 tile on 64 workgroups 1.1;
 // 128 x 128 (two per CU) serves up to 128 tokens in 260 us against 302 us.  From there on a tile is 256 tall, one per CU,
 // and its width follows from the token count (pick_tile).
-typedef TileCfg<4, 1, 1, 2, 2> Cfg64;
-typedef TileCfg<4, 2, 1, 2, 2> Cfg128;
+typedef TileCfg<4, 1, 2, 4, 2> Cfg64;
+typedef TileCfg<4, 2, 2, 4, 2> Cfg128;
 typedef CfgSample Cfg256;
-typedef TileCfg<4, 2, 2, 5, 2> Cfg320;
+// ... up to two token tiles wait for W to arrive: their loads go out as early as they can (scoring / sampling, loads early and
+// spread, d = 2048: 200 tokens 178 / 188, 197 / 205 us; 500 281 / 285, 318 / 323; d = 4096: 1000 994 / 988, 1102 / 1111;
+// sampling 4000 4116 / 3904).
+typedef TileCfg<4, 2, 4, 8, 2, 0, true> Cfg256Early;
+constexpr int64_t kEarlyTokens = 2 * Cfg256Early::BN;
+typedef TileCfg<4, 2, 4, 10, 2> Cfg320;
 // The sweep's reference exponents: the first 256 vocabulary entries of 64 tokens (a sixth of a packed block of H).
-typedef TileCfg<4, 1, 2, 2, 4, kPackRowsB> CfgRef;
+typedef TileCfg<4, 1, 4, 4, 4, kPackRowsB> CfgRef;
 enum FwdTile { kTile64, kTile128, kTile256, kTile320, kTile384 };
 struct TilePick {
   FwdTile tile = kTile384;
@@ -444,9 +449,9 @@ static bool prepare_kernels() {
   static std::once_flag once;
   static bool ok = false;
   std::call_once(once, [] {
-    ok = allow_fwd<Cfg64, true>() && allow_fwd<Cfg128, true>() && allow_fwd<Cfg256, true>() && allow_fwd<Cfg320, true>() &&
+    ok = allow_fwd<Cfg64, true>() && allow_fwd<Cfg128, true>() && allow_fwd<Cfg256, true>() && allow_fwd<Cfg256Early, true>() && allow_fwd<Cfg320, true>() &&
          allow_fwd<Cfg, true>() && allow_fwd<Cfg, false>() && allow_sample<Cfg64, true>() &&
-         allow_sample<Cfg128, true>() && allow_sample<Cfg256, true>() && allow_sample<CfgSample, false>() &&
+         allow_sample<Cfg128, true>() && allow_sample<Cfg256, true>() && allow_sample<Cfg256Early, true>() && allow_sample<CfgSample, false>() &&
          allow_big_lds(k_fwd_lse<CfgRef, false, true>, CfgRef::LDS_BYTES) &&
          allow_big_lds(k_fwd_lse<CfgRef, false, false>, CfgRef::LDS_BYTES) &&
          allow_big_lds(k_bwd_dz<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_bwd_dz<Cfg, true>, Cfg::LDS_BYTES) &&
@@ -504,7 +509,9 @@ static void launch_fwd_lse(const FwdArgs& a, bool rows, float2* partials, float*
   switch (a.pick.tile) {
     case kTile64: return launch_fwd_lse<Cfg64, true>(a, partials, upart, clear, st, gate);
     case kTile128: return launch_fwd_lse<Cfg128, true>(a, partials, upart, clear, st, gate);
-    case kTile256: return launch_fwd_lse<Cfg256, true>(a, partials, upart, clear, st, gate);
+    case kTile256:
+      if (a.T <= kEarlyTokens) return launch_fwd_lse<Cfg256Early, true>(a, partials, upart, clear, st, gate);
+      return launch_fwd_lse<Cfg256, true>(a, partials, upart, clear, st, gate);
     case kTile320: return launch_fwd_lse<Cfg320, true>(a, partials, upart, clear, st, gate);
     case kTile384: return launch_fwd_lse<Cfg, true>(a, partials, upart, clear, st, gate);
   }
@@ -1249,6 +1256,7 @@ int32_t oapl_sample_tokens(const void* H, const void* W, int64_t T, int32_t d, i
       if (!p.rows) launch_sample<CfgSample, false>(args, inv_t, seed, partials, st);
       else if (p.smp.tile == kTile64) launch_sample<Cfg64, true>(args, inv_t, seed, partials, st);
       else if (p.smp.tile == kTile128) launch_sample<Cfg128, true>(args, inv_t, seed, partials, st);
+      else if (T <= kEarlyTokens) launch_sample<Cfg256Early, true>(args, inv_t, seed, partials, st);
       else launch_sample<Cfg256, true>(args, inv_t, seed, partials, st);
     }
     OAPL_LAUNCH_CHECK();
