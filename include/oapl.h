@@ -342,7 +342,8 @@ int32_t oapl_read_path_taken(const void* workspace, void* stream, int32_t* two_p
  * dense bf16 kernels: 0 = LM-head contraction fused with the streaming
  * log-sum-exp (forward-only scoring, and pass one of the two-pass loss),
  * 1 = soft-max recompute producing the logit gradient (pass two of the two-pass loss),
- * 2 = the dH contraction, 3 = the dW contraction, 4 = the sampling kernel,
+ * 2 = the dH contraction, 3 = the dW contraction (in small calls both are one
+ * launch, which counts as 3), 4 = the sampling kernel,
  * 5 = the single sweep (contraction + unnormalised soft-max panel + row sums).  After
  * oapl_timing_enable(1), every launch of these kernels is bracketed by a pair
  * of HIP events recorded on the launch stream; oapl_timing_read waits for the

@@ -1130,21 +1130,31 @@ __device__ __forceinline__ void store_f32_tile(const f32x4 (&acc)[C::MB][C::NB],
 // fp32 partial sum (whole 128-byte lines) for k_dh_reduce; the host chooses the count (pick_dh in
 // oapl_api.hip).
 // ---------------------------------------------------------------------------
-template <class C, bool SPLIT, bool ATR>
-__global__ void __launch_bounds__(C::NT)
-k_bwd_dh(const bf16_t* __restrict__ W /* or W^T, packed */, int V, int wt_n_kt, const bf16_t* __restrict__ Gp, int g_n_kt, int d,
-         int64_t n_valid, int nk /* k-blocks to contract: ceil(V / 64) */,
-         const float* __restrict__ row_factor /* f_t, panel-local */, bf16_t* __restrict__ dH /* panel's first row */,
-         int splits, float* __restrict__ part /* [splits][n_valid][d] */, Gate gate) {
+struct DhArgs {
+  const bf16_t* W;          // or W^T, packed
+  int V, wt_n_kt;
+  const bf16_t* Gp;
+  int g_n_kt, d;
+  int64_t n_valid;
+  int nk;                   // k-blocks to contract: ceil(V / 64)
+  const float* row_factor;  // f_t, panel-local
+  bf16_t* dH;               // panel's first row
+  int splits;
+  float* part;              // [splits][n_valid][d]
+};
 #if defined(__HIP_DEVICE_COMPILE__)
-  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
-  lds_char_ptr smem = (lds_char_ptr)smem_raw;
-  if (gate_closed(gate)) return;
-
+template <class C, bool SPLIT, bool ATR>
+__device__ __forceinline__ void dh_tile(const DhArgs& args, int bid, lds_char_ptr smem) {
+  const bf16_t* __restrict__ W = args.W;
+  const bf16_t* __restrict__ Gp = args.Gp;
+  const float* __restrict__ row_factor = args.row_factor;
+  bf16_t* __restrict__ dH = args.dH;
+  const int V = args.V, d = args.d, nk = args.nk, splits = args.splits;
+  const int64_t n_valid = args.n_valid;
   const int MT = (d + C::BM - 1) / C::BM;
   const int NTl = (int)((n_valid + C::BN - 1) / C::BN);
   const int total = MT * NTl * (SPLIT ? splits : 1);
-  const int L = xcd_logical_id(blockIdx.x, total);
+  const int L = xcd_logical_id(bid, total);
   if (L >= total) return;
   // neighbouring ids walk the tiles of one split, so the workgroups of an XCD share its operand blocks
   const int split = SPLIT ? L / (MT * NTl) : 0;
@@ -1158,8 +1168,8 @@ k_bwd_dh(const bf16_t* __restrict__ W /* or W^T, packed */, int V, int wt_n_kt, 
   Mainloop<C, false, ATR> ml;
   ml.setup();
   if (ATR) ml.set_a_transposed(W + (int64_t)k0 * C::BK * d, mt, V - (int64_t)k0 * C::BK, d);
-  else ml.set_a_packed(W, m0, wt_n_kt, k0);
-  ml.set_b_packed(Gp, n0, g_n_kt, k0);
+  else ml.set_a_packed(W, m0, args.wt_n_kt, k0);
+  ml.set_b_packed(Gp, n0, args.g_n_kt, k0);
 
   f32x4 acc[C::MB][C::NB];
   zero_acc<C>(acc);
@@ -1167,7 +1177,7 @@ k_bwd_dh(const bf16_t* __restrict__ W /* or W^T, packed */, int V, int wt_n_kt, 
   ml.finish(smem, k1 - k0, acc);
 
   if (SPLIT) {
-    store_f32_tile<C, false>(acc, part + (int64_t)split * n_valid * d, d, (int)n_valid, m0, (int)n0);
+    store_f32_tile<C, false>(acc, args.part + (int64_t)split * n_valid * d, d, (int)n_valid, m0, (int)n0);
     return;
   }
   const Lane<C> at;
@@ -1185,6 +1195,14 @@ k_bwd_dh(const bf16_t* __restrict__ W /* or W^T, packed */, int V, int wt_n_kt, 
     store_nm<C>(smem, dH + n0 * d + m0, d, n_valid - n0, (int64_t)d - m0, c);
     __syncthreads();
   }
+}
+#endif
+template <class C, bool SPLIT, bool ATR>
+__global__ void __launch_bounds__(C::NT) k_bwd_dh(DhArgs args, Gate gate) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+  if (gate_closed(gate)) return;
+  dh_tile<C, SPLIT, ATR>(args, blockIdx.x, (lds_char_ptr)smem_raw);
 #endif
 }
 
@@ -1218,20 +1236,24 @@ k_dh_reduce(const float* __restrict__ part, int splits, int64_t n_valid, int d, 
 //   A = packed (diag(f) H)^T (rows = hidden index j, k = panel tokens), B = GTp (rows = vocabulary).
 // fp32 output written straight from the accumulators: 4 consecutive j per lane.
 // ---------------------------------------------------------------------------
-template <class C>
-__global__ void __launch_bounds__(C::NT)
-k_bwd_dw(const bf16_t* __restrict__ HTp, const bf16_t* __restrict__ GTp, int t_n_kt /* strip pitch of both */, int d,
-         int V, int nk /* k-blocks to contract: ceil(panel tokens / 64) */,
-         float* __restrict__ dW, int accumulate, Gate gate) {
+struct DwArgs {
+  const bf16_t *HTp, *GTp;
+  int t_n_kt;               // strip pitch of both
+  int d, V, nk;             // k-blocks to contract: ceil(panel tokens / 64)
+  float* dW;
+  int accumulate;
+};
 #if defined(__HIP_DEVICE_COMPILE__)
-  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
-  lds_char_ptr smem = (lds_char_ptr)smem_raw;
-  if (gate_closed(gate)) return;
-
+template <class C>
+__device__ __forceinline__ void dw_tile(const DwArgs& args, int bid, lds_char_ptr smem) {
+  const bf16_t* __restrict__ HTp = args.HTp;
+  const bf16_t* __restrict__ GTp = args.GTp;
+  float* __restrict__ dW = args.dW;
+  const int d = args.d, V = args.V, nk = args.nk, t_n_kt = args.t_n_kt;
   const int MT = (d + C::BM - 1) / C::BM;
   const int NTl = (V + C::BN - 1) / C::BN;
   const int total = MT * NTl;
-  const int L = xcd_round_major_id(blockIdx.x);   // launched in whole rounds of 256 workgroups
+  const int L = xcd_round_major_id(bid);   // launched in whole rounds of 256 workgroups
   if (L >= total) return;
   int mt, nt;
   strip_tile<4>(L, MT, NTl, mt, nt);
@@ -1248,8 +1270,32 @@ k_bwd_dw(const bf16_t* __restrict__ HTp, const bf16_t* __restrict__ GTp, int t_n
   ml.start(smem, nk);
   ml.finish(smem, nk, acc);
 
-  if (accumulate) store_f32_tile<C, true>(acc, dW, d, V, m0, n0);
+  if (args.accumulate) store_f32_tile<C, true>(acc, dW, d, V, m0, n0);
   else store_f32_tile<C, false>(acc, dW, d, V, m0, n0);
+}
+#endif
+template <class C>
+__global__ void __launch_bounds__(C::NT) k_bwd_dw(DwArgs args, Gate gate) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+  if (gate_closed(gate)) return;
+  dw_tile<C>(args, blockIdx.x, (lds_char_ptr)smem_raw);
+#endif
+}
+
+// Steps 2 and 3 of a small batch (one panel, 128 x 128 tiles, operands in place) in one launch: the first n_dh (a multiple of
+// 8) workgroups are dH's, the others dW's.  Neither fills the chip and they do not depend on each other: 1000 tokens
+// at d = 256, V = 1544 28.3 us in two launches, 21.8 in one (whole call 71.6 / 67); 700 at d = 128, V = 300 21.4 / 13.4
+// (53.9 / 48.3).  256 x 384 tiles gain nothing from it (V = 151936, d = 4096, 1003 tokens: 2166 / 2185 us; with longer dH walks
+// beside dW's tiles 2221, 300 tokens 1007 / 1286): the two kinds of tile share no operands in the L2.
+template <class C, bool SPLIT>
+__global__ void __launch_bounds__(C::NT) k_bwd_grads(DhArgs dh, int n_dh, DwArgs dw, Gate gate) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+  lds_char_ptr smem = (lds_char_ptr)smem_raw;
+  if (gate_closed(gate)) return;
+  if ((int)blockIdx.x < n_dh) dh_tile<C, SPLIT, true>(dh, blockIdx.x, smem);
+  else dw_tile<C>(dw, blockIdx.x - n_dh, smem);
 #endif
 }
 

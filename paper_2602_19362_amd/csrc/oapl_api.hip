@@ -88,6 +88,7 @@ struct Plan {
   bool small_sweep = false, small_dw = false;   // 128 x 128 tiles (one panel, operands in place)
   int n_vt = 0;        // vocabulary tiles of the sweep: row sums per token
   DhPick dh;           // the last panel's dH contraction
+  bool grads_fused = false;   // ... shares its launch with dW's (both in 128 x 128 tiles)
   TilePick smp;        // ... of the sampling kernel (splits = (score, index) partials per token)
   int64_t Tp = 0;      // rows of one backward panel
   F32Pick f32_dh, f32_dw;   // tile and splits of the fp32 gradient contractions (of the largest panel)
@@ -346,11 +347,13 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
       const int64_t last = T > 0 ? T - (T - 1) / p.Tp * p.Tp : 0;
       const size_t packed_w = (size_t)p.n_rt_v * p.n_kt_d * kPackBlockBytesA;
       const bool lean = max_splits == 1;
+      const size_t part_bytes = lean ? 0 : (packed_w > kPartDhBytes ? packed_w : kPartDhBytes);
       if (!p.rows) p.dh = pick_dh(last, d, p.n_kt_v, false, packed_w);
-      else p.dh = pick_dh(last, d, p.n_kt_v, true, lean ? 0 : (packed_w > kPartDhBytes ? packed_w : kPartDhBytes));
+      else p.dh = pick_dh(last, d, p.n_kt_v, true, part_bytes);
+      p.small_dw = p.rows && T <= p.Tp && small_tiles_pay(kSmallDw, d, V, (int)((T + kPackK - 1) / kPackK));
+      p.grads_fused = p.small_dw && p.dh.small;
       p.off_part = p.rows && p.dh.splits > 1 ? take((size_t)p.dh.splits * last * d * 4) : p.off_Wp;
       p.small_sweep = p.rows && T <= p.Tp && !lean && small_tiles_pay(kSmallSweep, V, T, p.n_kt_d);
-      p.small_dw = p.rows && T <= p.Tp && small_tiles_pay(kSmallDw, d, V, (int)((T + kPackK - 1) / kPackK));
       p.n_vt = p.small_sweep ? (V + CfgSmall::BM - 1) / CfgSmall::BM : p.n_rt_v;
       if (!p.rows) p.off_WTp = take((size_t)p.n_rt_d * p.n_kt_v * kPackBlockBytesA);
       p.off_HTp = take((size_t)p.n_rt_d * p.n_kt_t * kPackBlockBytesA);
@@ -440,9 +443,14 @@ static bool allow_sample() {
   return allow_big_lds(k_fwd_sample<C, ROWS>, C::LDS_BYTES);
 }
 
-template <class C, bool SPLIT, bool ATR>
+template <class C, bool ATR>
 static bool allow_dh() {
-  return allow_big_lds(k_bwd_dh<C, SPLIT, ATR>, C::LDS_BYTES);
+  return allow_big_lds(k_bwd_dh<C, false, ATR>, C::LDS_BYTES) && allow_big_lds(k_bwd_dh<C, true, ATR>, C::LDS_BYTES);
+}
+template <class C>
+static bool allow_grads() {
+  return allow_big_lds(k_bwd_dw<C>, C::LDS_BYTES) && allow_big_lds(k_bwd_grads<C, false>, C::LDS_BYTES) &&
+         allow_big_lds(k_bwd_grads<C, true>, C::LDS_BYTES);
 }
 
 static bool prepare_kernels() {
@@ -457,11 +465,9 @@ static bool prepare_kernels() {
          allow_big_lds(k_bwd_dz<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_bwd_dz<Cfg, true>, Cfg::LDS_BYTES) &&
          allow_big_lds(k_sweep<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_sweep<Cfg, true>, Cfg::LDS_BYTES) &&
          allow_big_lds(k_sweep<CfgSmall, true>, CfgSmall::LDS_BYTES) &&
-         allow_big_lds(k_sweep<CfgDeep, true>, CfgDeep::LDS_BYTES) && allow_dh<Cfg, false, false>() &&
-         allow_dh<Cfg, false, true>() && allow_dh<Cfg, true, false>() && allow_dh<Cfg, true, true>() &&
-         allow_dh<CfgSmall, false, true>() && allow_dh<CfgSmall, true, true>() && allow_dh<CfgDeep, false, true>() &&
-         allow_dh<CfgDeep, true, true>() && allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
-         allow_big_lds(k_bwd_dw<CfgSmall>, CfgSmall::LDS_BYTES) && allow_big_lds(k_bwd_dw<CfgDeep>, CfgDeep::LDS_BYTES);
+         allow_big_lds(k_sweep<CfgDeep, true>, CfgDeep::LDS_BYTES) && allow_dh<Cfg, false>() && allow_dh<Cfg, true>() &&
+         allow_dh<CfgSmall, true>() && allow_dh<CfgDeep, true>() && allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
+         allow_grads<CfgSmall>() && allow_grads<CfgDeep>();
   });
   return ok;
 }
@@ -666,46 +672,61 @@ static int forward_finish(const Plan& p, const float* logq, float* logprob_out, 
 }
 
 template <class C, bool SPLIT, bool ATR>
-static void launch_dh(const Plan& p, const bf16_t* W, const bf16_t* G, int64_t nv, const float* factor, bf16_t* dH, float* part,
-                      hipStream_t st, Gate gate) {
-  const int splits = SPLIT ? p.dh.splits : 1;
-  k_bwd_dh<C, SPLIT, ATR><<<(unsigned)round_up(tile_count<C>(p.d, nv) * splits, 8), C::NT, C::LDS_BYTES, st>>>(
-      W, p.V, p.n_kt_v, G, p.n_kt_g, p.d, nv, p.n_kt_v, factor, dH, splits, part, gate);
+static void launch_dh(const DhArgs& args, hipStream_t st, Gate gate) {
+  const unsigned grid = (unsigned)round_up(tile_count<C>(args.d, args.n_valid) * (SPLIT ? args.splits : 1), 8);
+  k_bwd_dh<C, SPLIT, ATR><<<grid, C::NT, C::LDS_BYTES, st>>>(args, gate);
+}
+template <class C, bool ATR>
+static void launch_dh(const DhArgs& args, bool split, hipStream_t st, Gate gate) {
+  if (split) launch_dh<C, true, ATR>(args, st, gate);
+  else launch_dh<C, false, ATR>(args, st, gate);
+}
+template <class C>
+static void launch_dw(const DwArgs& args, hipStream_t st, Gate gate) {
+  k_bwd_dw<C><<<(unsigned)round_up(tile_count<C>(args.d, args.V), kNumCU), C::NT, C::LDS_BYTES, st>>>(args, gate);
+}
+template <class C>
+static void launch_grads(const DhArgs& dh, bool split, const DwArgs& dw, hipStream_t st, Gate gate) {
+  const unsigned n_dh = (unsigned)round_up(tile_count<C>(dh.d, dh.n_valid) * (split ? dh.splits : 1), 8);
+  const unsigned grid = n_dh + (unsigned)round_up(tile_count<C>(dw.d, dw.V), kNumCU);
+  if (split) k_bwd_grads<C, true><<<grid, C::NT, C::LDS_BYTES, st>>>(dh, (int)n_dh, dw, gate);
+  else k_bwd_grads<C, false><<<grid, C::NT, C::LDS_BYTES, st>>>(dh, (int)n_dh, dw, gate);
 }
 
-// One panel's dH.  `last`: the batch's last panel (so no sweep or recompute of this call follows); only its tiles are
-// split, and only it has a space for partial sums (the other panels of a long batch are sized to fill the chip as they are).
-static int launch_dh(const Plan& p, const bf16_t* W, const bf16_t* G, int64_t nv, const float* factor, bf16_t* dH, bool last,
-                     char* ws, hipStream_t st, Gate gate, bool timed) {
+// One panel's dH and dW.  Only the tiles of the batch's last panel are split, and only it has a space for partial sums (no
+// sweep or recompute of the call follows; the other panels of a long batch are sized to fill the chip as they are).
+static int launch_gradients(const Plan& p, DhArgs dh, const DwArgs& dw, bool last, char* ws, hipStream_t st, Gate gate, bool timed) {
   const bool split = last && p.dh.splits > 1, small = last && p.dh.small;
-  float* part = split ? (float*)(ws + p.off_part) : nullptr;
-  const bf16_t* A = p.rows ? W : (const bf16_t*)(ws + p.off_WTp);
-  {
-    ScopedKernelTimer tm(kBwdDh, st, timed);
-    const bool deep = small && tile_count<CfgDeep>(p.d, nv) * p.dh.splits <= kNumCU;
-    if (split && deep) launch_dh<CfgDeep, true, true>(p, A, G, nv, factor, dH, part, st, gate);
-    else if (deep) launch_dh<CfgDeep, false, true>(p, A, G, nv, factor, dH, part, st, gate);
-    else if (split && small) launch_dh<CfgSmall, true, true>(p, A, G, nv, factor, dH, part, st, gate);
-    else if (small) launch_dh<CfgSmall, false, true>(p, A, G, nv, factor, dH, part, st, gate);
-    else if (split && p.rows) launch_dh<Cfg, true, true>(p, A, G, nv, factor, dH, part, st, gate);
-    else if (split) launch_dh<Cfg, true, false>(p, A, G, nv, factor, dH, part, st, gate);
-    else if (p.rows) launch_dh<Cfg, false, true>(p, A, G, nv, factor, dH, part, st, gate);
-    else launch_dh<Cfg, false, false>(p, A, G, nv, factor, dH, part, st, gate);
+  dh.splits = split ? p.dh.splits : 1;
+  dh.part = split ? (float*)(ws + p.off_part) : nullptr;
+  const int64_t dh_groups = small ? tile_count<CfgDeep>(p.d, dh.n_valid) * dh.splits : 0;
+  const int64_t dw_groups = p.small_dw ? tile_count<CfgDeep>(p.d, p.V) : 0;
+  if (p.grads_fused) {
+    ScopedKernelTimer tm(kBwdDw, st, timed);
+    if (dh_groups + dw_groups <= kNumCU) launch_grads<CfgDeep>(dh, split, dw, st, gate);
+    else launch_grads<CfgSmall>(dh, split, dw, st, gate);
+  } else {
+    {
+      ScopedKernelTimer tm(kBwdDh, st, timed);
+      if (small && dh_groups <= kNumCU) launch_dh<CfgDeep, true>(dh, split, st, gate);
+      else if (small) launch_dh<CfgSmall, true>(dh, split, st, gate);
+      else if (p.rows) launch_dh<Cfg, true>(dh, split, st, gate);
+      else launch_dh<Cfg, false>(dh, split, st, gate);
+    }
+    OAPL_LAUNCH_CHECK();
+    ScopedKernelTimer tm(kBwdDw, st, timed);
+    if (p.small_dw && dw_groups <= kNumCU) launch_dw<CfgDeep>(dw, st, gate);
+    else if (p.small_dw) launch_dw<CfgSmall>(dw, st, gate);
+    else launch_dw<Cfg>(dw, st, gate);
   }
   OAPL_LAUNCH_CHECK();
   if (split) {
-    const int64_t blocks = grid1d(nv * (p.d / 8), 256);
-    k_dh_reduce<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, st>>>(part, p.dh.splits, nv, p.d, factor, dH, gate);
+    const int64_t blocks = grid1d(dh.n_valid * (p.d / 8), 256);
+    k_dh_reduce<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, st>>>(dh.part, dh.splits, dh.n_valid, p.d, dh.row_factor,
+                                                                        dh.dH, gate);
     OAPL_LAUNCH_CHECK();
   }
   return OAPL_OK;
-}
-
-template <class C>
-static void launch_dw(const Plan& p, const bf16_t* HTp, const bf16_t* GT, int kt, float* dW, int accumulate, hipStream_t st,
-                      Gate gate) {
-  k_bwd_dw<C><<<(unsigned)round_up(tile_count<C>(p.d, p.V), kNumCU), C::NT, C::LDS_BYTES, st>>>(HTp, GT, p.n_kt_t, p.d, p.V, kt,
-                                                                                             dW, accumulate, gate);
 }
 
 template <class C, bool ROWS>
@@ -751,15 +772,10 @@ static int panel_gradients(const Plan& p, const void* H, const void* W, int64_t 
   // (diag(coef) H)^T of this panel, packed; token columns in [nv, 64 kt) come out as zeros
   k_pack_transposed<<<dim3(kt, p.n_rt_d), 256, 0, st>>>((const bf16_t*)H + t0 * d, nv, d, d, coef, HTp, p.n_kt_t, gate);
   OAPL_LAUNCH_CHECK();
-  if (int rc = launch_dh(p, (const bf16_t*)W, G, nv, coef, (bf16_t*)dH + t0 * d, t0 + p.Tp >= p.T, ws, st, gate, timed)) return rc;
-  {
-    ScopedKernelTimer tm(kBwdDw, st, timed);
-    if (p.small_dw && tile_count<CfgDeep>(d, p.V) <= kNumCU) launch_dw<CfgDeep>(p, HTp, GT, kt, dW, 0, st, gate);
-    else if (p.small_dw) launch_dw<CfgSmall>(p, HTp, GT, kt, dW, 0, st, gate);
-    else launch_dw<Cfg>(p, HTp, GT, kt, dW, t0 > 0 ? 1 : 0, st, gate);
-  }
-  OAPL_LAUNCH_CHECK();
-  return OAPL_OK;
+  const DhArgs dh{p.rows ? (const bf16_t*)W : (const bf16_t*)(ws + p.off_WTp), p.V, p.n_kt_v, G, p.n_kt_g, d, nv, p.n_kt_v, coef,
+                  (bf16_t*)dH + t0 * d, 1, nullptr};
+  const DwArgs dw{HTp, GT, p.n_kt_t, d, p.V, kt, dW, t0 > 0 ? 1 : 0};
+  return launch_gradients(p, dh, dw, t0 + p.Tp >= p.T, ws, st, gate, timed);
 }
 
 // Steps a8-a10, two-pass form, panel by panel, from log-sum-exps and token coefficients.  `wt_packed`: W^T has been packed
