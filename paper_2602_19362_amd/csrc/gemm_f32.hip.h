@@ -16,6 +16,7 @@
 
 #include "common.hip.h"
 #include "rng.hip.h"
+#include "small_kernels.hip.h"
 
 namespace oapl {
 
@@ -31,6 +32,8 @@ struct F32Cfg {
   static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, BK = BK_;
   static constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
   static_assert(WM * WN == 4 && BK % 8 == 0, "256 threads, whole groups of eight k");
+  // workgroups that the registers must leave room for on a CU: as many as the LDS does
+  static constexpr int kPerCU = BM * BN >= 128 * 128 ? 4 : 2;
 };
 typedef F32Cfg<2, 2, 2, 2, 16> F32Large;   // 128 x 128, 40 KB of LDS
 typedef F32Cfg<2, 2, 1, 1, 32> F32Small;   // 64 x 64, 36 KB
@@ -84,21 +87,29 @@ struct F32Stage {
 // Row inside a 32 x 32 block of accumulator register r, before the lane-half term 4 * (lane / 32); the column is lane % 32.
 __device__ __forceinline__ constexpr int f32_acc_row(int r) { return 8 * (r >> 2) + (r & 3); }
 
-// Grid: x and y = row and column tiles in the order the epilogue names (y holds at most 65535), z = splits of k in whole
-// stages.
+// LDS of a tile: two stages of each operand.
+template <class C, bool A_KC>
+constexpr int f32_lds_a() { return 2 * F32Stage<C::BM, C::BK, A_KC>::FLOATS; }
+template <class C, bool B_KC>
+constexpr int f32_lds_b() { return 2 * F32Stage<C::BN, C::BK, B_KC>::FLOATS; }
+constexpr int larger(int a, int b) { return a > b ? a : b; }
+
+// Tile at block (bx, by, bz): x and y = row and column tiles in the order the epilogue names, z = one of `nz` splits of k in
+// whole stages.
 template <class C, bool A_KC, bool B_KC, class Epi>
-__global__ void __launch_bounds__(256, 2)   // two workgroups per CU at least: one's products cover the other's stage turn
-k_gemm_f32(F32Operand A, F32Operand B, int64_t M, int64_t N, int64_t K, Epi epi) {
+__device__ __forceinline__ void gemm_f32_tile(const F32Operand& A, const F32Operand& B, int64_t M, int64_t N, int64_t K, const Epi& epi,
+                                              unsigned bx, unsigned by, unsigned bz, unsigned nz, float* lds_a, float* lds_b) {
   typedef F32Stage<C::BM, C::BK, A_KC> SA;
   typedef F32Stage<C::BN, C::BK, B_KC> SB;
-  __shared__ __attribute__((aligned(16))) float As[2][SA::FLOATS], Bs[2][SB::FLOATS];
+  float (*As)[SA::FLOATS] = (float (*)[SA::FLOATS])lds_a;
+  float (*Bs)[SB::FLOATS] = (float (*)[SB::FLOATS])lds_b;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
   const int wm = wave / C::WN, wn = wave % C::WN;
-  const int64_t m0 = (int64_t)(Epi::kRowsOnX ? blockIdx.x : blockIdx.y) * C::BM;
-  const int64_t n0 = (int64_t)(Epi::kRowsOnX ? blockIdx.y : blockIdx.x) * C::BN;
+  const int64_t m0 = (int64_t)(Epi::kRowsOnX ? bx : by) * C::BM;
+  const int64_t n0 = (int64_t)(Epi::kRowsOnX ? by : bx) * C::BN;
   const int64_t stages = (K + C::BK - 1) / C::BK;
-  const int64_t kb = stages * blockIdx.z / gridDim.z * C::BK;
-  int64_t ke = stages * (blockIdx.z + 1) / gridDim.z * C::BK;
+  const int64_t kb = stages * bz / nz * C::BK;
+  int64_t ke = stages * (bz + 1) / nz * C::BK;
   ke = ke < K ? ke : K;
 
   f32x16 acc[C::TM][C::TN];
@@ -147,7 +158,15 @@ k_gemm_f32(F32Operand A, F32Operand B, int64_t M, int64_t N, int64_t K, Epi epi)
     __syncthreads();
     cur ^= 1;
   }
-  epi.template store<C::TM, C::TN>(acc, m0 + wm * C::TM * 32, n0 + wn * C::TN * 32 + (lane & 31), half, M, N);
+  epi.template store<C::TM, C::TN>(acc, m0 + wm * C::TM * 32, n0 + wn * C::TN * 32 + (lane & 31), half, M, N, bz);
+}
+
+// Grid as gemm_f32_tile's block (y holds at most 65535).  Two workgroups per CU at least: one's products cover the other's
+// stage turn.
+template <class C, bool A_KC, bool B_KC, class Epi>
+__global__ void __launch_bounds__(256, 2) k_gemm_f32(F32Operand A, F32Operand B, int64_t M, int64_t N, int64_t K, Epi epi) {
+  __shared__ __attribute__((aligned(16))) float As[f32_lds_a<C, A_KC>()], Bs[f32_lds_b<C, B_KC>()];
+  gemm_f32_tile<C, A_KC, B_KC>(A, B, M, N, K, epi, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z, As, Bs);
 }
 
 // The epilogues get a wavefront's accumulators, its first row and the lane's first column.
@@ -163,7 +182,7 @@ struct EpiLseF32 {
   float* zt;      // or nullptr
   int64_t ldz;
   template <int TM, int TN>
-  __device__ void store(f32x16 (&acc)[TM][TN], int64_t m, int64_t n, int half, int64_t M, int64_t N) const {
+  __device__ void store(f32x16 (&acc)[TM][TN], int64_t m, int64_t n, int half, int64_t M, int64_t N, unsigned split) const {
     static_assert(TM == 2, "a partial is 64 vocabulary rows");
     if (m >= M) return;
     const int left = (int)(M - m < 64 ? M - m : 64) - 4 * half;   // this lane's rows r with row(r) >= left do not exist
@@ -234,7 +253,7 @@ struct EpiSampleF32 {
   float inv_temperature;
   uint32_t seed_lo, seed_hi;
   template <int TM, int TN>
-  __device__ void store(f32x16 (&acc)[TM][TN], int64_t m, int64_t n, int half, int64_t M, int64_t N) const {
+  __device__ void store(f32x16 (&acc)[TM][TN], int64_t m, int64_t n, int half, int64_t M, int64_t N, unsigned split) const {
     static_assert(TM == 2, "a partial is 64 vocabulary rows");
     if (m >= M) return;
 #pragma unroll
@@ -275,7 +294,7 @@ struct EpiDzF32 {
   float* zt;
   int64_t ldz;
   template <int TM, int TN>
-  __device__ void store(f32x16 (&acc)[TM][TN], int64_t m, int64_t n, int half, int64_t M, int64_t N) const {
+  __device__ void store(f32x16 (&acc)[TM][TN], int64_t m, int64_t n, int half, int64_t M, int64_t N, unsigned split) const {
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int64_t t = n + j * 32;
@@ -323,8 +342,8 @@ struct EpiStoreF32 {
   int64_t ld;
   int accumulate;
   template <int TM, int TN>
-  __device__ void store(f32x16 (&acc)[TM][TN], int64_t m, int64_t n, int half, int64_t M, int64_t N) const {
-    float* out = C + (int64_t)blockIdx.z * M * N;
+  __device__ void store(f32x16 (&acc)[TM][TN], int64_t m, int64_t n, int half, int64_t M, int64_t N, unsigned split) const {
+    float* out = C + (int64_t)split * M * N;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -340,15 +359,66 @@ struct EpiStoreF32 {
   }
 };
 
-// out (+)= the splits' partial results, in order.
-__global__ void __launch_bounds__(256)
-k_reduce_f32(const float* __restrict__ part, int splits, int64_t n, float* __restrict__ out, int accumulate) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    float a = accumulate ? out[i] : 0.f;
+// out = the splits' partial results, in order, of two contractions (n = 0: there is only one).
+struct F32Reduction {
+  const float* part;
+  int splits;
+  int64_t n;
+  float* out;
+};
+__global__ void __launch_bounds__(256) k_reduce_f32(F32Reduction a, F32Reduction b) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.n + b.n; i += (int64_t)gridDim.x * 256) {
+    const bool first = i < a.n;
+    const float* part = first ? a.part + i : b.part + (i - a.n);
+    const int splits = first ? a.splits : b.splits;
+    const int64_t n = first ? a.n : b.n;
+    float sum = 0.f;
 #pragma unroll 8
-    for (int s = 0; s < splits; ++s) a += part[(int64_t)s * n + i];
-    out[i] = a;
+    for (int s = 0; s < splits; ++s) sum += part[(int64_t)s * n];
+    (first ? a.out + i : b.out + (i - a.n))[0] = sum;
   }
+}
+
+// The first launch of a loss call of few tokens: what the call begins with (workgroup 0), the sampled tokens' logits (four per
+// workgroup) and the logits' tiles.  None needs the others, and a launch costs such a call 3 .. 5 us.
+template <class C, class Epi, class Begin, int VEC>
+__global__ void __launch_bounds__(256, 2)
+k_scores_f32(Begin begin, const int32_t* __restrict__ tokens, float* __restrict__ zy, TokenInit init, F32Operand W, F32Operand H,
+             int V, int64_t T, int d, Epi epi) {
+  __shared__ __attribute__((aligned(16))) float As[f32_lds_a<C, true>()], Bs[f32_lds_b<C, true>()];
+  int64_t b = blockIdx.x;
+  if (b == 0) return begin.run(0, 1, kPlan | kRest);
+  b -= 1;
+  const int64_t n_gather = (T + 3) / 4, rows = (V + C::BM - 1) / C::BM;
+  if (b < n_gather)
+    return gather_logit<float, double, VEC>(b * 4 + (threadIdx.x >> 6), H.p, W.p, tokens, T, d, V, zy, nullptr, init);
+  b -= n_gather;
+  gemm_f32_tile<C, true, true>(W, H, (int64_t)V, T, (int64_t)d, epi, b % rows, b / rows, 0, 1, As, Bs);
+}
+
+// One contraction with its splits; `grid` = (columns, rows, splits) of tiles.
+struct F32Contraction {
+  F32Operand A, B;
+  int64_t M, N, K;
+  float* out;      // [splits][M][N]
+  int nx, ny, splits;
+};
+// dH (rows of dZ^T contiguous) and dW (k contiguous) of a batch of one panel in one launch: neither fills the chip to
+// the end, and they do not depend on each other.
+template <class CH, class CW>
+__global__ void __launch_bounds__(256, larger(CH::kPerCU, CW::kPerCU)) k_grads_f32(F32Contraction dh, F32Contraction dw) {
+  __shared__ __attribute__((aligned(16))) float As[larger(f32_lds_a<CH, false>(), f32_lds_a<CW, true>())],
+      Bs[larger(f32_lds_b<CH, false>(), f32_lds_b<CW, false>())];
+  const int64_t n_dh = (int64_t)dh.nx * dh.ny * dh.splits;
+  int64_t i = blockIdx.x;
+  if (i < n_dh) {
+    gemm_f32_tile<CH, false, false>(dh.A, dh.B, dh.M, dh.N, dh.K, EpiStoreF32{dh.out, dh.N, 0}, i % dh.nx, i / dh.nx % dh.ny,
+                                    (unsigned)(i / ((int64_t)dh.nx * dh.ny)), dh.splits, As, Bs);
+    return;
+  }
+  i -= n_dh;
+  gemm_f32_tile<CW, true, false>(dw.A, dw.B, dw.M, dw.N, dw.K, EpiStoreF32{dw.out, dw.N, 0}, i % dw.nx, i / dw.nx % dw.ny,
+                                 (unsigned)(i / ((int64_t)dw.nx * dw.ny)), dw.splits, As, Bs);
 }
 
 }  // namespace oapl

@@ -88,7 +88,7 @@ struct Plan {
   bool small_sweep = false, small_dw = false;   // 128 x 128 tiles (one panel, operands in place)
   int n_vt = 0;        // vocabulary tiles of the sweep: row sums per token
   DhPick dh;           // the last panel's dH contraction
-  bool grads_fused = false;   // ... shares its launch with dW's (both in 128 x 128 tiles)
+  bool grads_fused = false;   // ... shares its launch with dW's (bf16: both in 128 x 128 tiles; fp32: few workgroups)
   TilePick smp;        // ... of the sampling kernel (splits = (score, index) partials per token)
   int64_t Tp = 0;      // rows of one backward panel
   F32Pick f32_dh, f32_dw;   // tile and splits of the fp32 gradient contractions (of the largest panel)
@@ -102,7 +102,7 @@ struct Plan {
   size_t off_status = 0, off_partials = 0, off_fwd_partials = 0, off_upart = 0, off_zy = 0, off_lse2 = 0, off_diff = 0,
          off_coef = 0, off_delta = 0, off_cseq = 0, off_vstar = 0, off_gw = 0, off_omp = 0, off_inv = 0, off_Wp = 0,
          off_Hp = 0, off_Wc = 0, off_Hc = 0, off_WTp = 0, off_HTp = 0,
-         off_part = 0, off_G = 0, off_GT = 0, off_ref2 = 0, off_spart = 0, total = 0;
+         off_part = 0, off_part_dw = 0, off_G = 0, off_GT = 0, off_ref2 = 0, off_spart = 0, total = 0;
   bool sweep = false;  // single-sweep loss path available (bf16 with backward)
 };
 
@@ -239,6 +239,15 @@ static F32Pick pick_f32(int64_t M, int64_t N, int64_t K, int max_splits, size_t 
   return best;
 }
 
+static int64_t f32_groups(const F32Pick& pick, int64_t M, int64_t N) {
+  const int64_t tile = pick.large ? F32Large::BM : F32Small::BM;
+  return ((M + tile - 1) / tile) * ((N + tile - 1) / tile) * pick.splits;
+}
+// fp32 gradient contractions share a launch up to this many workgroups, three per CU, which is what the registers of 128 x 128
+// tiles leave room for.  Whole calls, two launches / one: 256 tokens at d = 64, V = 1024 (128 workgroups) 40 / 37 us; 700, 300,
+// 3000 (455) 104 / 96; 1501, 768, 8192 (1272) 585 / 609.
+constexpr int64_t kSharedGroupsF32 = 3 * kNumCU;
+
 // bf16 operands that are not 16-byte aligned.  The 16-byte direct-to-LDS loads of the in-place kernels want that; the packing
 // and gathering kernels use ordinary loads, which take any address.  Such an operand is copied first and the call goes on
 // as any other (W at d = 4096, V = 151936: 0.46 ms; sampling 64 tokens takes 0.69 ms, 1.68 when it packed every operand).
@@ -252,7 +261,8 @@ static unsigned unaligned_operands(int dtype, const void* H, const void* W) {
 // `panel_buffers`: how many panels the single sweep keeps before their gradient contractions run
 // (<= 0: two, the least for a batch of several panels; never more than the batch has panels).
 // `max_splits`: most vocabulary splits of the streaming kernels of a call without gradients, most splits of k of the gradient
-// contractions of one with gradients.  One gives the smallest workspace (see fit_splits).
+// contractions of one with gradients.  One gives the smallest workspace (see fit_splits); short of kAnySplits the fp32
+// gradient contractions have one space for partial results between them, and a launch each.
 constexpr int kAnySplits = 1 << 30;
 static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, int dtype, bool bwd, unsigned unaligned,
                       int64_t max_panel_rows = 0, int64_t panel_buffers = 0, int64_t exact_panel_rows = 0,
@@ -383,7 +393,15 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
       p.f32_dw = pick_f32(V, d, p.Tp, max_splits, scratch);
       const size_t dh = p.f32_dh.splits > 1 ? (size_t)p.f32_dh.splits * p.Tp * d * 4 : 0;
       const size_t dw = p.f32_dw.splits > 1 ? (size_t)p.f32_dw.splits * V * d * 4 : 0;
-      p.off_part = take(dh > dw ? dh : dw);
+      // few workgroups share a launch, and then both have their partial results at once
+      p.grads_fused = T > 0 && T <= p.Tp && max_splits == kAnySplits &&
+                      f32_groups(p.f32_dh, T, d) + f32_groups(p.f32_dw, V, d) <= kSharedGroupsF32;
+      if (p.grads_fused) {
+        p.off_part = take(dh);
+        p.off_part_dw = take(dw);
+      } else {
+        p.off_part = p.off_part_dw = take(dh > dw ? dh : dw);
+      }
     }
   }
   p.total = o;
@@ -551,27 +569,62 @@ static void launch_logits_f32(const Plan& p, const void* H, const void* W, int64
         A, B, (int64_t)p.V, T, (int64_t)p.d, epi);
 }
 
+// ... in the launch that a loss call of few tokens starts with (k_scores_f32).
+template <class C, class Begin>
+static void launch_scores_f32(const Plan& p, const Begin& begin, const void* H, const void* W, const int32_t* tokens, float* zy,
+                              const TokenInit& init, const EpiLseF32& epi, hipStream_t st) {
+  const F32Operand A = f32_operand(W, p.d), B = f32_operand(H, p.d);
+  const unsigned grid = 1 + grid1d(p.T, 4) + grid1d(p.V, C::BM) * grid1d(p.T, C::BN);
+  if (A.vec && B.vec) k_scores_f32<C, EpiLseF32, Begin, 4><<<grid, 256, 0, st>>>(begin, tokens, zy, init, A, B, p.V, p.T, p.d, epi);
+  else k_scores_f32<C, EpiLseF32, Begin, 1><<<grid, 256, 0, st>>>(begin, tokens, zy, init, A, B, p.V, p.T, p.d, epi);
+}
+
 // out[m][n] (+)= sum_k A(m, k) B(n, k), B and (unless A_KC) A with their rows contiguous.
-template <bool A_KC, class C>
-static void launch_contract_f32(int splits, const F32Operand& A, const F32Operand& B, int64_t M, int64_t N, int64_t K,
-                                float* out, int64_t ld, int accumulate, hipStream_t st) {
-  k_gemm_f32<C, A_KC, false><<<dim3(grid1d(N, C::BN), grid1d(M, C::BM), splits), 256, 0, st>>>(
-      A, B, M, N, K, EpiStoreF32{out, ld, accumulate});
+static F32Contraction contraction_f32(const F32Pick& pick, const F32Operand& A, const F32Operand& B, int64_t M, int64_t N, int64_t K,
+                                      float* out) {
+  const int tile = pick.large ? F32Large::BM : F32Small::BM;
+  return F32Contraction{A, B, M, N, K, out, (int)grid1d(N, tile), (int)grid1d(M, tile), pick.splits};
 }
 template <bool A_KC>
-static int contract_f32(const F32Pick& pick, const F32Operand& A, const F32Operand& B, int64_t M, int64_t N, int64_t K, float* out,
-                        float* part, int accumulate, hipStream_t st) {
-  const bool split = pick.splits > 1;
-  float* dst = split ? part : out;
-  const int acc = split ? 0 : accumulate;
-  if (pick.large) launch_contract_f32<A_KC, F32Large>(pick.splits, A, B, M, N, K, dst, N, acc, st);
-  else launch_contract_f32<A_KC, F32Small>(pick.splits, A, B, M, N, K, dst, N, acc, st);
-  OAPL_LAUNCH_CHECK();
-  if (split) {
-    const int64_t blocks = (M * N + 255) / 256;
-    k_reduce_f32<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, st>>>(part, pick.splits, M * N, out, accumulate);
+static void launch_contract_f32(bool large, const F32Contraction& c, int accumulate, hipStream_t st) {
+  const EpiStoreF32 epi{c.out, c.N, accumulate};
+  const dim3 grid(c.nx, c.ny, c.splits);
+  if (large) k_gemm_f32<F32Large, A_KC, false><<<grid, 256, 0, st>>>(c.A, c.B, c.M, c.N, c.K, epi);
+  else k_gemm_f32<F32Small, A_KC, false><<<grid, 256, 0, st>>>(c.A, c.B, c.M, c.N, c.K, epi);
+}
+
+// Both gradient contractions of a batch of one panel, and the sums of what was split.
+static int grads_f32(const Plan& p, const void* H, const void* W, const float* zt, float* dH, float* dW, char* ws, hipStream_t st) {
+  float* part_dh = p.f32_dh.splits > 1 ? (float*)(ws + p.off_part) : nullptr;
+  float* part_dw = p.f32_dw.splits > 1 ? (float*)(ws + p.off_part_dw) : nullptr;
+  // dH[t][j] = sum_v dZ[t][v] W[v][j],  dW[v][j] = sum_t dZ[t][v] H[t][j]
+  const F32Contraction dh = contraction_f32(p.f32_dh, f32_operand(zt, p.ldz), f32_operand(W, p.d), p.T, p.d, p.V, part_dh ? part_dh : dH);
+  const F32Contraction dw = contraction_f32(p.f32_dw, f32_operand(zt, p.ldz), f32_operand(H, p.d), p.V, p.d, p.T, part_dw ? part_dw : dW);
+  const F32Reduction a{part_dh, dh.splits, part_dh ? dh.M * dh.N : 0, dH}, b{part_dw, dw.splits, part_dw ? dw.M * dw.N : 0, dW};
+  const F32Reduction none{nullptr, 0, 0, nullptr};
+  auto reduce = [&](const F32Reduction& x, const F32Reduction& y) {
+    const int64_t blocks = (x.n + y.n + 255) / 256;
+    if (blocks > 0) k_reduce_f32<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, st>>>(x, y);
+  };
+  if (!p.grads_fused) {
+    launch_contract_f32<false>(p.f32_dh.large, dh, 0, st);
     OAPL_LAUNCH_CHECK();
+    reduce(a, none);      // before the other's partial results, which have the same space
+    OAPL_LAUNCH_CHECK();
+    launch_contract_f32<true>(p.f32_dw.large, dw, 0, st);
+    OAPL_LAUNCH_CHECK();
+    reduce(b, none);
+    OAPL_LAUNCH_CHECK();
+    return OAPL_OK;
   }
+  const unsigned grid = (unsigned)((int64_t)dh.nx * dh.ny * dh.splits + (int64_t)dw.nx * dw.ny * dw.splits);
+  if (p.f32_dh.large && p.f32_dw.large) k_grads_f32<F32Large, F32Large><<<grid, 256, 0, st>>>(dh, dw);
+  else if (p.f32_dh.large) k_grads_f32<F32Large, F32Small><<<grid, 256, 0, st>>>(dh, dw);
+  else if (p.f32_dw.large) k_grads_f32<F32Small, F32Large><<<grid, 256, 0, st>>>(dh, dw);
+  else k_grads_f32<F32Small, F32Small><<<grid, 256, 0, st>>>(dh, dw);
+  OAPL_LAUNCH_CHECK();
+  reduce(a, b);
+  OAPL_LAUNCH_CHECK();
   return OAPL_OK;
 }
 
@@ -655,9 +708,9 @@ static int forward_partials(const Plan& p, const void* H, const void* W, bool en
 }
 
 // Log-probs (and lse, entropy) from the partial sums and the sampled tokens' logits; with `logq` also what the objective
-// and the gradients need.
-static int forward_finish(const Plan& p, const float* logq, float* logprob_out, float* lse_out, float* entropy_out, char* ws,
-                          hipStream_t st, Gate gate) {
+// and the gradients need.  `check_tokens`: the tokens, if the gather before left it to this launch to report those out of range.
+static int forward_finish(const Plan& p, const float* logq, float* logprob_out, float* lse_out, float* entropy_out,
+                          const int32_t* check_tokens, char* ws, hipStream_t st, Gate gate) {
   const int64_t T = p.T;
   if (T == 0) return OAPL_OK;
   const bool loss = logq != nullptr;
@@ -666,7 +719,8 @@ static int forward_finish(const Plan& p, const float* logq, float* logprob_out, 
       (const float2*)(ws + p.off_fwd_partials), p.fwd.splits, T, (const float*)(ws + p.off_zy), logq, logprob_out, lse_out,
       loss ? (float*)(ws + p.off_lse2) : nullptr, loss ? (double*)(ws + p.off_diff) : nullptr,
       loss ? (float*)(ws + p.off_omp) : nullptr, loss ? (float*)(ws + p.off_inv) : nullptr,
-      entropy_out ? (const float*)(ws + p.off_upart) : nullptr, entropy_out, slices, gate);
+      entropy_out ? (const float*)(ws + p.off_upart) : nullptr, entropy_out, slices, check_tokens, p.V,
+      (int*)(ws + p.off_status), gate);
   OAPL_LAUNCH_CHECK();
   return OAPL_OK;
 }
@@ -801,31 +855,59 @@ static int backward_grads(const Plan& p, const void* H, const void* W, const int
     return OAPL_OK;
   }
   float* zt = (float*)(ws + p.off_G);   // dZ^T of a panel
-  float* part = (float*)(ws + p.off_part);
   const float* lse = (const float*)(ws + p.off_lse2);
   const float* coef = (const float*)(ws + p.off_coef);
+  if (T <= p.Tp) {   // the scoring pass left the logits here
+    k_dz_f32<<<dim3(grid1d(V, kDzRows), grid1d(T, 256)), 256, 0, st>>>(zt, p.ldz, V, T, tokens, lse, coef);
+    OAPL_LAUNCH_CHECK();
+    return grads_f32(p, H, W, zt, (float*)dH, dW, ws, st);
+  }
   for (int64_t t0 = 0; t0 < T; t0 += p.Tp) {
     const int64_t nv = (T - t0) < p.Tp ? (T - t0) : p.Tp;
     const float* Hp = (const float*)H + t0 * d;
-    if (T <= p.Tp)   // the scoring pass left the logits here
-      k_dz_f32<<<dim3(grid1d(V, kDzRows), grid1d(T, 256)), 256, 0, st>>>(zt, p.ldz, V, T, tokens, lse, coef);
-    else
-      launch_logits_f32(p, Hp, W, nv, EpiDzF32{tokens + t0, lse + t0, coef + t0, zt, p.ldz}, st);
+    launch_logits_f32(p, Hp, W, nv, EpiDzF32{tokens + t0, lse + t0, coef + t0, zt, p.ldz}, st);
     OAPL_LAUNCH_CHECK();
     // dH[t][j] = sum_v dZ[t][v] W[v][j]
-    if (int rc = contract_f32<false>(p.f32_dh, f32_operand(zt, p.ldz), f32_operand(W, d), nv, d, V, (float*)dH + t0 * d, part,
-                                     0, st))
-      return rc;
+    launch_contract_f32<false>(p.f32_dh.large, contraction_f32(p.f32_dh, f32_operand(zt, p.ldz), f32_operand(W, d), nv, d, V,
+                                                               (float*)dH + t0 * d), 0, st);
+    OAPL_LAUNCH_CHECK();
     // dW[v][j] (+)= sum_t dZ[t][v] H[t][j]
-    if (int rc = contract_f32<true>(p.f32_dw, f32_operand(zt, p.ldz), f32_operand(Hp, d), V, d, nv, dW, part, t0 > 0 ? 1 : 0,
-                                    st))
-      return rc;
+    launch_contract_f32<true>(p.f32_dw.large, contraction_f32(p.f32_dw, f32_operand(zt, p.ldz), f32_operand(Hp, d), V, d, nv, dW),
+                              t0 > 0 ? 1 : 0, st);
+    OAPL_LAUNCH_CHECK();
   }
   return OAPL_OK;
 }
 
 // A rollout may span at most n_buf - 1 panels' worth of rows on the single sweep (any length if the batch is one panel).
 static int64_t sweep_longest(const Plan& p) { return p.n_buf > 1 ? (int64_t)(p.n_buf - 1) * p.Tp : p.Tp; }
+
+// One workgroup takes a call's first steps while it has at most a few thousand (rollout, prompt) pairs to look at.
+static bool begin_in_one_launch(int n_seq, int n_groups) { return (int64_t)n_seq * n_groups + n_seq + n_groups <= 8192; }
+// ... else workgroups of 256 rollouts and four prompts each, at most 65536: the steps walk on from there, and thread indices
+// stay far below 2^31.
+static unsigned begin_grid(int n_seq, int n_groups) {
+  const unsigned a = grid1d(n_groups, 4), b = grid1d(n_seq > 0 ? n_seq : 1, 256), most = 1u << 16;
+  return a > most || b > most ? most : (a > b ? a : b);
+}
+
+// A call's beginning: the status header, the sweep's length check, and what needs the rewards only.
+template <class Begin>
+static int launch_begin(const Begin& begin, hipStream_t st) {
+  if (begin_in_one_launch(begin.n_seq, begin.n_groups)) {
+    k_begin<<<1, 256, 0, st>>>(begin, kPlan | kRest);
+  } else {
+    k_fill_i32<<<1, 64, 0, st>>>(begin.status, kStatusWords, 0);
+    OAPL_LAUNCH_CHECK();
+    k_begin<<<begin_grid(begin.n_seq, begin.n_groups), 256, 0, st>>>(begin, kPlan);
+    if (Begin::kHasRest) {
+      OAPL_LAUNCH_CHECK();
+      k_begin<<<begin_grid(begin.n_seq, 1), 256, 0, st>>>(begin, kRest);
+    }
+  }
+  OAPL_LAUNCH_CHECK();
+  return OAPL_OK;
+}
 
 // Steps a1-a3 and a8-a10 in ONE pass over the logits (bf16, T > 0).  Per panel of token rows:
 // k_sweep writes the unnormalised soft-max panel and its row sums, k_sweep_finish turns the sums
@@ -837,8 +919,8 @@ static int64_t sweep_longest(const Plan& p) { return p.n_buf > 1 ? (int64_t)(p.n
 // (sweep_plan raises the fallback flag otherwise).  What the sweep does runs only while the flag is 0, and the
 // two-pass schedule behind it only if it is not.  A batch of one panel shares the objective and the contractions between
 // the two: its fallback is the scoring pass and the recompute alone (three closed launches in place of nine).
-template <class Objective>
-static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t* tokens, const float* logq,
+template <class Begin, class Objective>
+static int sweep_path(const Plan& p, const Begin& begin, const void* H, const void* W, const int32_t* tokens, const float* logq,
                       float* logprob_out, void* dH, float* dW, char* ws, hipStream_t st, Objective&& objective) {
   const int64_t T = p.T;
   const int d = p.d, V = p.V;
@@ -855,6 +937,7 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
   float* nis = (float*)(ws + p.off_inv);
   const float* omp = (const float*)(ws + p.off_omp);
 
+  if (int rc = launch_begin(begin, st)) return rc;
   if (int rc = pack_wt(p, W, ws, st, kNoGate)) return rc;
   // reference exponents: running maximum over the first 256 vocabulary entries, one workgroup per 64 tokens (a walk of
   // d / 64 k-blocks each, bound by their latency)
@@ -889,7 +972,7 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
   if (n_panels == 1) {
     if (int rc = sweep(0)) return rc;
     if (int rc = forward_partials(p, H, W, false, false, nullptr, ws, st, slow)) return rc;
-    if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, ws, st, slow)) return rc;
+    if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, nullptr, ws, st, slow)) return rc;
     if (int rc = objective(kNoGate, TokenFactor{nis, omp, flag})) return rc;
     if (int rc = recompute_panel(p, H, W, tokens, 0, Gbuf(0), GTbuf(0), ws, st, slow)) return rc;
     return panel_gradients(p, H, W, 0, Gbuf(0), GTbuf(0), dH, dW, ws, st, kNoGate, true);
@@ -907,19 +990,35 @@ static int sweep_path(const Plan& p, const void* H, const void* W, const int32_t
   for (int64_t k = n_panels - (p.n_buf - 1); k < n_panels; ++k)
     if (int rc = gradients(k)) return rc;
   if (int rc = forward_partials(p, H, W, false, false, nullptr, ws, st, slow)) return rc;
-  if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, ws, st, slow)) return rc;
+  if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, nullptr, ws, st, slow)) return rc;
   if (int rc = objective(slow, TokenFactor{omp, nullptr, nullptr})) return rc;
   return backward_grads(p, H, W, tokens, dH, dW, ws, st, slow, true);
 }
 
+// fp32 calls whose logits do not give every CU a 128 x 128 tile start with one launch (k_scores_f32; 256 tokens at d = 64,
+// V = 1024: three launches of 3.6, 2.7 and 8.2 us before).  Where they do, workgroups in front of them unbalance the chip (1501 tokens,
+// d = 768, V = 8192, three tiles per CU: whole call 586 us apart, 639 together).
+static bool scores_in_one_launch_f32(const Plan& p, int n_seq, int n_groups) {
+  return p.dtype == OAPL_F32 && p.T > 0 && p.T <= kPanelF32 && !logits_large_f32(p.V, p.T) && begin_in_one_launch(n_seq, n_groups);
+}
+
 // The two-pass schedule (and the scoring alone, without gradients).
-template <class Objective>
-static int two_pass_path(const Plan& p, const void* H, const void* W, const int32_t* tokens, const float* logq,
+template <class Begin, class Objective>
+static int two_pass_path(const Plan& p, const Begin& begin, const void* H, const void* W, const int32_t* tokens, const float* logq,
                          float* logprob_out, void* dH, float* dW, char* ws, hipStream_t st, Objective&& objective) {
-  float* coef = p.bwd ? (float*)(ws + p.off_coef) : nullptr;
-  if (int rc = gather_logits(p, H, W, tokens, TokenInit{coef, nullptr, nullptr, nullptr, nullptr}, ws, st)) return rc;
-  if (int rc = forward_partials(p, H, W, false, p.bwd, nullptr, ws, st, kNoGate)) return rc;
-  if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, ws, st, kNoGate)) return rc;
+  const int64_t T = p.T;
+  const TokenInit init{p.bwd ? (float*)(ws + p.off_coef) : nullptr, nullptr, nullptr, nullptr, nullptr};
+  const bool one = scores_in_one_launch_f32(p, begin.n_seq, begin.n_groups);
+  if (one) {
+    const EpiLseF32 epi{(float2*)(ws + p.off_fwd_partials), T, nullptr, p.bwd && T <= p.Tp ? (float*)(ws + p.off_G) : nullptr, p.ldz};
+    launch_scores_f32<F32Flat>(p, begin, H, W, tokens, (float*)(ws + p.off_zy), init, epi, st);
+    OAPL_LAUNCH_CHECK();
+  } else {
+    if (int rc = launch_begin(begin, st)) return rc;
+    if (int rc = gather_logits(p, H, W, tokens, init, ws, st)) return rc;
+    if (int rc = forward_partials(p, H, W, false, p.bwd, nullptr, ws, st, kNoGate)) return rc;
+  }
+  if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, one ? tokens : nullptr, ws, st, kNoGate)) return rc;
   const float* factor = p.bwd && p.dtype == OAPL_BF16 ? (const float*)(ws + p.off_omp) : nullptr;
   if (int rc = objective(kNoGate, TokenFactor{factor, nullptr, nullptr})) return rc;
   if (!p.bwd) return OAPL_OK;
@@ -938,7 +1037,7 @@ static int fit_splits(Plan& p, size_t have) {
   };
   int limit = kAnySplits;
   if (p.bwd) {
-    for (int next : {8, 4, 2, 1}) {
+    for (int next : {kAnySplits - 1, 8, 4, 2, 1}) {
       if (p.total <= have || !fewer(next)) break;
       limit = next;
     }
@@ -996,15 +1095,6 @@ static int fit_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, i
   return OAPL_OK;
 }
 
-// One workgroup takes a call's first steps while it has at most a few thousand (rollout, prompt) pairs to look at.
-static bool begin_in_one_launch(int n_seq, int n_groups) { return (int64_t)n_seq * n_groups + n_seq + n_groups <= 8192; }
-// ... else workgroups of 256 rollouts and four prompts each, at most 65536: the steps walk on from there, and thread indices
-// stay far below 2^31.
-static unsigned begin_grid(int n_seq, int n_groups) {
-  const unsigned a = grid1d(n_groups, 4), b = grid1d(n_seq > 0 ? n_seq : 1, 256), most = 1u << 16;
-  return a > most || b > most ? most : (a > b ? a : b);
-}
-
 // Runs the objective's launch(grid, steps) once with both steps, or once with each.  The hand-over costs a fence and a counter
 // for every rollout: whole calls in one launch / two, 1000 tokens at d = 256, V = 1544: 72.5 / 72.1 us for 8 rollouts, 76.6 /
 // 73.3 for 64, 88.7 / 73.7 for 256, 138.6 / 78.6 for 1024; fp32, 256 tokens, d = 64, V = 1024, where the host's launches are
@@ -1050,13 +1140,7 @@ static int loss_impl(const void* H, const void* W, const int32_t* tokens, const 
   const bool sweep = p.sweep && T >= kSweepMinTokens && !(flags & OAPL_FLAG_TWO_PASS);
   const int64_t longest = sweep ? sweep_longest(p) : -1;
 
-  // the status header, the sweep's length check, and Eq. 2, which needs the rewards only
-  const bool one = begin_in_one_launch(n_seq, n_groups);
-  if (!one) k_fill_i32<<<1, 64, 0, st>>>(status, kStatusWords, 0);
-  k_oapl_begin<<<one ? 1 : begin_grid(n_seq, n_groups), 256, 0, st>>>(rewards, group_ids, seq_offsets, n_seq, n_groups, T,
-                                                                      longest, (double)beta_value, vstar, vstar_out, status,
-                                                                      one ? 1 : 0);
-  OAPL_LAUNCH_CHECK();
+  const OaplBegin begin{rewards, group_ids, seq_offsets, n_seq, n_groups, T, longest, (double)beta_value, vstar, vstar_out, status};
   if (int rc = pack_operands(p, H, W, ws, st)) return rc;
 
   // Steps a4, a6, a7 from logprob - logq [T]
@@ -1070,8 +1154,8 @@ static int loss_impl(const void* H, const void* W, const int32_t* tokens, const 
   };
   // bf16 with gradients: one sweep over the logits; the two-pass schedule behind it runs only if the
   // sweep's preconditions fail on this call's data (decided on the device, in stream order)
-  if (sweep) return sweep_path(p, H, W, tokens, logq, logprob_out, dH, dW, ws, st, objective);
-  return two_pass_path(p, H, W, tokens, logq, logprob_out, dH, dW, ws, st, objective);
+  if (sweep) return sweep_path(p, begin, H, W, tokens, logq, logprob_out, dH, dW, ws, st, objective);
+  return two_pass_path(p, begin, H, W, tokens, logq, logprob_out, dH, dW, ws, st, objective);
 }
 
 // The paper's baseline objective on the same fused head (Sec. 2): scores, group advantages,
@@ -1104,20 +1188,8 @@ static int grpo_impl(const void* H, const void* W, const int32_t* tokens, const 
   const bool sweep = p.sweep && T >= kSweepMinTokens && !(flags & OAPL_FLAG_TWO_PASS);
   const int64_t longest = sweep ? sweep_longest(p) : -1;
 
-  auto begin = [&](unsigned grid, int steps) {
-    k_grpo_begin<<<grid, 256, 0, st>>>(rewards, group_ids, seq_offsets, n_seq, n_groups, T, longest, (double)adv_eps,
-                                       (double)loss_scale, gstat, gstat + n_groups, gsize, adv, wseq, adv_out, status, steps);
-  };
-  if (begin_in_one_launch(n_seq, n_groups)) {
-    begin(1, 3);
-  } else {
-    k_fill_i32<<<1, 64, 0, st>>>(status, kStatusWords, 0);
-    OAPL_LAUNCH_CHECK();
-    begin(begin_grid(n_seq, n_groups), 1);
-    OAPL_LAUNCH_CHECK();
-    begin(begin_grid(n_seq, 1), 2);
-  }
-  OAPL_LAUNCH_CHECK();
+  const GrpoBegin begin{rewards, group_ids, seq_offsets, n_seq, n_groups, T, longest, (double)adv_eps, (double)loss_scale, gstat,
+                        gstat + n_groups, gsize, adv, wseq, adv_out, status};
   if (int rc = pack_operands(p, H, W, ws, st)) return rc;
 
   auto objective = [&](Gate gate, TokenFactor factors) -> int {
@@ -1127,8 +1199,8 @@ static int grpo_impl(const void* H, const void* W, const int32_t* tokens, const 
           bwd && T > 0 ? (float*)(ws + p.off_coef) : nullptr, (double*)(ws + p.off_delta), loss_out, status, steps, gate);
     });
   };
-  if (sweep) return sweep_path(p, H, W, tokens, logq, logprob_out, dH, dW, ws, st, objective);
-  return two_pass_path(p, H, W, tokens, logq, logprob_out, dH, dW, ws, st, objective);
+  if (sweep) return sweep_path(p, begin, H, W, tokens, logq, logprob_out, dH, dW, ws, st, objective);
+  return two_pass_path(p, begin, H, W, tokens, logq, logprob_out, dH, dW, ws, st, objective);
 }
 
 // Scratch of the entry point that allocates nothing: every GPU the library runs on holds its own
@@ -1230,7 +1302,7 @@ int32_t oapl_logprob_fwd(const void* H, const void* W, const int32_t* tokens, in
   if (int rc = pack_operands(p, H, W, ws, st)) return rc;
   if (int rc = forward_partials(p, H, W, entropy_out != nullptr, false, status, ws, st, kNoGate)) return rc;
   if (int rc = gather_logits(p, H, W, tokens, TokenInit{}, ws, st)) return rc;
-  return forward_finish(p, nullptr, logprob_out, lse_out, entropy_out, ws, st, kNoGate);
+  return forward_finish(p, nullptr, logprob_out, lse_out, entropy_out, nullptr, ws, st, kNoGate);
 }
 
 int32_t oapl_sample_tokens(const void* H, const void* W, int64_t T, int32_t d, int32_t V, int32_t dtype,

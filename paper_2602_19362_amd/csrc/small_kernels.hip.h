@@ -42,13 +42,14 @@ struct TokenInit {
   double* diff;
   float* nis;
 };
+// `err` == nullptr: a token out of range is recorded by a later launch (k_lse_finish), for the status header is being cleared
+// by this one.
 template <class T, class ACC, int VEC>
-__global__ void __launch_bounds__(256)
-k_gather_logit(const T* __restrict__ H, const T* __restrict__ W, const int32_t* __restrict__ tokens,
-               int64_t Ttok, int d, int V, float* __restrict__ zy, int* __restrict__ err, TokenInit init) {
+__device__ __forceinline__ void gather_logit(int64_t t /* of this wavefront */, const T* __restrict__ H, const T* __restrict__ W,
+                                             const int32_t* __restrict__ tokens, int64_t Ttok, int d, int V,
+                                             float* __restrict__ zy, int* __restrict__ err, const TokenInit& init) {
   typedef T vec_t __attribute__((ext_vector_type(VEC), aligned(sizeof(T))));   // bf16 rows may start at any element
   const int lane = threadIdx.x & 63;
-  const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= Ttok) return;
   const int y = tokens[t];
   auto finish = [&](float z) {
@@ -62,7 +63,7 @@ k_gather_logit(const T* __restrict__ H, const T* __restrict__ W, const int32_t* 
   };
   if (y < 0 || y >= V) {
     if (lane == 0) {
-      record_token_error(err);
+      if (err) record_token_error(err);
       finish(__builtin_nanf(""));
     }
     return;
@@ -78,6 +79,12 @@ k_gather_logit(const T* __restrict__ H, const T* __restrict__ W, const int32_t* 
   }
   acc = wave_sum(acc);
   if (lane == 0) finish((float)acc);
+}
+template <class T, class ACC, int VEC>
+__global__ void __launch_bounds__(256)
+k_gather_logit(const T* __restrict__ H, const T* __restrict__ W, const int32_t* __restrict__ tokens,
+               int64_t Ttok, int d, int V, float* __restrict__ zy, int* __restrict__ err, TokenInit init) {
+  gather_logit<T, ACC, VEC>((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), H, W, tokens, Ttok, d, V, zy, err, init);
 }
 
 // Merges the per-split soft-max partials of each token and finishes
@@ -96,7 +103,7 @@ k_lse_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, con
              const float* __restrict__ logq, float* __restrict__ logprob_out, float* __restrict__ lse_out,
              float* __restrict__ lse2_ws, double* __restrict__ diff_ws, float* __restrict__ omp_ws,
              float* __restrict__ inv_omp_ws, const float* __restrict__ upart, float* __restrict__ entropy_out,
-             int slices, Gate gate) {
+             int slices, const int32_t* __restrict__ tokens /* to check, or nullptr */, int V, int* __restrict__ err, Gate gate) {
   __shared__ float part_m[256];
   __shared__ double part_s[256], part_u[256];
   if (gate_closed(gate)) return;
@@ -135,6 +142,7 @@ k_lse_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, con
     }
   }
   if (slice != 0 || t >= Ttok) return;
+  if (tokens && (tokens[t] < 0 || tokens[t] >= V)) record_token_error(err);
   const double lse = LOG2 ? ((double)M + log2(S)) * kLn2 : (double)M + log(S);
   double lp = (double)zy[t] - lse;   // NaN if the token was out of range
   if (lp > 0.0) lp = 0.0;            // the gathered logit is rounded separately from the sum
@@ -378,36 +386,60 @@ __device__ __forceinline__ void clear_status(int* status) {
   __syncthreads();
 }
 
-// `all`: one workgroup does everything, status header included; else a grid after a launch that cleared the header.
-__global__ void __launch_bounds__(256)
-k_oapl_begin(const float* __restrict__ rewards, const int32_t* __restrict__ gid, const int64_t* __restrict__ off, int n_seq,
-             int n_groups, int64_t Ttok, int64_t longest, double beta_v, double* __restrict__ vstar_ws,
-             float* __restrict__ vstar_out, int* status, int all) {
-  if (all) clear_status(status);
-  sweep_plan(blockIdx.x * 256 + threadIdx.x, gridDim.x * 256, off, n_seq, Ttok, longest, status + kFlagWord);
-  group_value(blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, rewards, gid, n_seq, n_groups, beta_v, vstar_ws, vstar_out,
-              status);
-}
+// Steps of a call's beginning as (block, blocks) of 256 threads.  kPlan: after a clear header, the sweep's length check and
+// what prompts need; kRest: what needs the prompts' results; both: one workgroup, status header included.
+enum BeginSteps { kPlan = 1, kRest = 2 };
 
-// Steps: 1 = plan and group statistics, 2 = advantages, 3 = both (one workgroup, status header included).
-__global__ void __launch_bounds__(256)
-k_grpo_begin(const float* __restrict__ rewards, const int32_t* __restrict__ gid, const int64_t* __restrict__ off, int n_seq,
-             int n_groups, int64_t Ttok, int64_t longest, double adv_eps, double scale, double* gmean, double* gstd,
-             double* gsize, float* __restrict__ adv, double* __restrict__ wseq, float* __restrict__ adv_out, int* status,
-             int steps) {
-  if (steps == 3) clear_status(status);
-  if (steps & 1) {
-    sweep_plan(blockIdx.x * 256 + threadIdx.x, gridDim.x * 256, off, n_seq, Ttok, longest, status + kFlagWord);
-    grpo_group_stats(blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, rewards, gid, n_seq, n_groups, gmean, gstd, gsize,
-                     status);
+struct OaplBegin {
+  const float* rewards;
+  const int32_t* gid;
+  const int64_t* off;
+  int n_seq, n_groups;
+  int64_t Ttok, longest;
+  double beta_v;
+  double* vstar_ws;
+  float* vstar_out;
+  int* status;
+  static constexpr bool kHasRest = false;
+  __device__ __forceinline__ void run(int64_t block, int64_t blocks, int steps) const {
+    if (steps == (kPlan | kRest)) clear_status(status);
+    sweep_plan(block * 256 + threadIdx.x, blocks * 256, off, n_seq, Ttok, longest, status + kFlagWord);
+    group_value(block * 4 + (threadIdx.x >> 6), blocks * 4, rewards, gid, n_seq, n_groups, beta_v, vstar_ws, vstar_out, status);
   }
-  if (steps == 3) {
-    __threadfence();
-    __syncthreads();
+};
+
+struct GrpoBegin {
+  const float* rewards;
+  const int32_t* gid;
+  const int64_t* off;
+  int n_seq, n_groups;
+  int64_t Ttok, longest;
+  double adv_eps, scale;
+  double *gmean, *gstd, *gsize;
+  float* adv;
+  double* wseq;
+  float* adv_out;
+  int* status;
+  static constexpr bool kHasRest = true;
+  __device__ __forceinline__ void run(int64_t block, int64_t blocks, int steps) const {
+    if (steps == (kPlan | kRest)) clear_status(status);
+    if (steps & kPlan) {
+      sweep_plan(block * 256 + threadIdx.x, blocks * 256, off, n_seq, Ttok, longest, status + kFlagWord);
+      grpo_group_stats(block * 4 + (threadIdx.x >> 6), blocks * 4, rewards, gid, n_seq, n_groups, gmean, gstd, gsize, status);
+    }
+    if (steps == (kPlan | kRest)) {
+      __threadfence();
+      __syncthreads();
+    }
+    if (steps & kRest)
+      grpo_advantage(block * 256 + threadIdx.x, blocks * 256, rewards, gid, off, n_seq, n_groups, Ttok, adv_eps, scale, gmean,
+                     gstd, gsize, adv, wseq, adv_out, status);
   }
-  if (steps & 2)
-    grpo_advantage(blockIdx.x * 256 + threadIdx.x, gridDim.x * 256, rewards, gid, off, n_seq, n_groups, Ttok, adv_eps, scale,
-                   gmean, gstd, gsize, adv, wseq, adv_out, status);
+};
+
+template <class Begin>
+__global__ void __launch_bounds__(256) k_begin(Begin begin, int steps) {
+  begin.run(blockIdx.x, gridDim.x, steps);
 }
 
 // ---------------------------------------------------------------------------
