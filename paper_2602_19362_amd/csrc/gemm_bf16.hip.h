@@ -49,6 +49,7 @@
 
 #include "common.hip.h"
 #include "rng.hip.h"
+#include "small_kernels.hip.h"
 
 namespace oapl {
 
@@ -896,6 +897,86 @@ k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, 
 #endif
 }
 
+// dst = packed(S^T), an m-side operand (256-row blocks), where S [R, Ccols] is row-major (ld; Ccols and ld
+// multiples of 8) and optionally row-scaled:
+// dst row j (a column of S), k index r (a row of S): dst(j, r) = bf16(S[r][j] * scale[r]).
+// One workgroup per destination block (jt, kt): it reads S[kt*64 .. +64][jt*256 .. +256] in 16-byte
+// pieces (8 columns of one row), four consecutive rows per thread, turns each 4 x 8 patch into eight
+// 8-byte column pieces (4 rows of one column) and parks them in LDS as [row quad][column]; a
+// destination chunk (8 consecutive r of one j, 16 bytes) is then two 8-byte LDS reads.
+// Blocks in [0, n_jt) x [0, n_kt); zero outside [0, Ccols) x [0, R).
+struct PackTransposed {
+  const bf16_t* src;
+  int64_t R;
+  int Ccols;
+  int64_t ld;
+  const float* scale;
+  bf16_t* dst;
+  int n_kt;          // strip pitch of dst
+  // bytes per row quad: 256 columns x 8 bytes; +16 keeps the reads below off each other's banks
+  static constexpr int kPitch = kPackRowsA * 8 + 16;
+  static constexpr int kLds = (kPackK / 4) * kPitch;
+};
+// Block (kt, jt) by the 256 threads `tid` of a workgroup, all of whose threads come here.
+__device__ __forceinline__ void pack_transposed_block(const PackTransposed& p, int kt, int jt, int tid, char* tile) {
+  const bf16_t* __restrict__ src = p.src;
+  const int64_t R = p.R, ld = p.ld;
+  const int Ccols = p.Ccols;
+  constexpr int kPitch = PackTransposed::kPitch;
+  const int64_t r0 = (int64_t)kt * kPackK;
+  const int j0 = jt * kPackRowsA;
+  const int cc = tid & 31;                // 8-column piece of the 256 columns
+#pragma unroll
+  for (int pass = 0; pass < 2; ++pass) {
+    const int rq = (tid >> 5) + 8 * pass;   // row quad 0 .. 15
+    const int j = j0 + cc * 8;
+    u32x4 row[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t r = r0 + 4 * rq + k;
+      row[k] = u32x4{0u, 0u, 0u, 0u};
+      if (r < R && j < Ccols) {
+        row[k] = load_any16(src + r * ld + j);
+        if (p.scale != nullptr) {
+          const float sc = p.scale[r];
+#pragma unroll
+          for (int m = 0; m < 4; ++m) {
+            // a copy: a vector element is not an object whose bytes can be reinterpreted in place
+            const uint32_t x = row[k][m];
+            const bf16x2 v = __builtin_bit_cast(bf16x2, x);
+            const bf16x2 w = {(bf16_t)((float)v[0] * sc), (bf16_t)((float)v[1] * sc)};
+            row[k][m] = __builtin_bit_cast(uint32_t, w);
+          }
+        }
+      }
+    }
+    // dword m of a row holds columns 2m (low half) and 2m + 1 (high half)
+    char* out = tile + rq * kPitch + cc * 64;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const uint32_t a0 = row[0][m], a1 = row[1][m], a2 = row[2][m], a3 = row[3][m];
+      const u32x4 piece = {(a0 & 0xFFFFu) | (a1 << 16), (a2 & 0xFFFFu) | (a3 << 16),        // column 2m: rows 0..3
+                           (a0 >> 16) | (a1 & 0xFFFF0000u), (a2 >> 16) | (a3 & 0xFFFF0000u)};  // column 2m + 1
+      *(u32x4*)(out + m * 16) = piece;
+    }
+  }
+  __syncthreads();
+  char* outb = (char*)p.dst + ((int64_t)jt * p.n_kt + kt) * (int64_t)kPackBlockBytesA;
+#pragma unroll
+  for (int it = 0; it < 8; ++it) {
+    const int idx = it * 256 + tid;
+    const int rowj = idx >> 3, c = idx & 7;                 // destination row (j), 8 consecutive k = row quads 2c, 2c + 1
+    const u32x2 lo = *(const u32x2*)(tile + (2 * c) * kPitch + rowj * 8);
+    const u32x2 hi = *(const u32x2*)(tile + (2 * c + 1) * kPitch + rowj * 8);
+    *(u32x4*)(outb + rowj * 128 + c * 16) = u32x4{lo[0], lo[1], hi[0], hi[1]};
+  }
+}
+__global__ void __launch_bounds__(256) k_pack_transposed(PackTransposed p, Gate gate) {
+  __shared__ __attribute__((aligned(16))) char tile[PackTransposed::kLds];
+  if (gate_closed(gate)) return;
+  pack_transposed_block(p, blockIdx.x, blockIdx.y, threadIdx.x, tile);
+}
+
 // ---------------------------------------------------------------------------
 // Backward, step 1: recompute a logits^T tile and turn it into the gradient
 // with respect to the logits.  With p = softmax(z_t) and f_t = c_t (1 - p_{t,y_t}),
@@ -911,20 +992,30 @@ k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, 
 // Entries outside the valid ranges are written as zeros (whole tiles are stored).
 //   A = W (M = vocabulary), B = H from the panel's first token (N = tokens), packed or in place.
 // ---------------------------------------------------------------------------
+// In a small call the transposed rows that the next launch wants come along (`n_pack` workgroups in front, two blocks each): the
+// recompute is closed in nearly every call, and a launch of its own that does nothing costs 3 us.
 template <class C, bool ROWS>
 __global__ void __launch_bounds__(C::NT)
 k_bwd_dz(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H_panel, int V, int64_t n_valid, int d, int n_kt,
          const int32_t* __restrict__ tokens, const float* __restrict__ lse2, const float* __restrict__ inv_omp,
-         bf16_t* __restrict__ Gp, int g_n_kt, bf16_t* __restrict__ GTp, int gt_n_kt, Gate gate) {
+         bf16_t* __restrict__ Gp, int g_n_kt, bf16_t* __restrict__ GTp, int gt_n_kt, Gate gate, int n_pack, PackTransposed pack,
+         int pack_kt, int pack_blocks) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   lds_char_ptr smem = (lds_char_ptr)smem_raw;
+  static_assert(C::NT == 512 && 2 * PackTransposed::kLds <= C::LDS_BYTES, "two blocks per workgroup");
+  if ((int)blockIdx.x < n_pack) {
+    const int half = threadIdx.x >> 8, i = 2 * blockIdx.x + half;
+    const int block = i < pack_blocks ? i : pack_blocks - 1;     // an odd one out is written twice, with the same values
+    pack_transposed_block(pack, block % pack_kt, block / pack_kt, threadIdx.x & 255, smem_raw + half * PackTransposed::kLds);
+    return;
+  }
   if (gate_closed(gate)) return;
 
   const int MT = (V + C::BM - 1) / C::BM;
   const int NTl = (int)((n_valid + C::BN - 1) / C::BN);
   const int total = MT * NTl;
-  const int L = xcd_logical_id(blockIdx.x, total);
+  const int L = xcd_logical_id(blockIdx.x - n_pack, total);
   if (L >= total) return;
   int mt, nt;
   strip_tile<4>(L, MT, NTl, mt, nt);
@@ -966,6 +1057,97 @@ k_bwd_dz(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H_panel, int V
   }
   // Gp: rows = tokens (n), k = vocabulary (m);  GTp: rows = vocabulary (m), k = tokens (n)
   store_both_copies<C>(smem, pk, Gp, g_n_kt, GTp, gt_n_kt, m0, n0);
+#endif
+}
+
+// The first launch of a single sweep over operands in place: what the call begins with (workgroup 0), and per 64 tokens the
+// reference exponents of k_sweep (the largest logit among the first 256 vocabulary entries and the sampled token's own, which
+// is gathered here) with the per-token arrays of TokenInit.  Three launches otherwise; see sweep_begins_in_one_launch in
+// oapl_api.hip.
+template <class C, class Begin>
+__global__ void __launch_bounds__(C::NT)
+k_sweep_begin(Begin begin, const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int64_t T, int d, int n_kt,
+              const int32_t* __restrict__ tokens, float* __restrict__ zy, TokenInit init) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+  lds_char_ptr smem = (lds_char_ptr)smem_raw;
+  static_assert(C::NT == 256, "begin's steps are for 256 threads");
+  if (blockIdx.x == 0) return begin.run(0, 1, kPlan | kRest);
+  const int64_t nt = blockIdx.x - 1, n0 = nt * C::BN;
+
+  Mainloop<C, true> ml;
+  ml.setup();
+  ml.rows_init(d);
+  ml.set_b(H, nt, T, d, n_kt);
+  ml.set_a(W, 0, V, d, n_kt);
+  const Lane<C> at;
+  constexpr int kShare = C::BN / C::NW;      // tokens per wavefront; lane i has the i-th one's
+  static_assert(kShare == 16, "four rounds of four tokens");
+  const int64_t t_lane = n0 + at.wm * kShare + at.c;
+  const int tok = tokens[t_lane < T ? t_lane : T - 1];
+  f32x4 acc[C::MB][C::NB];
+  zero_acc<C>(acc);
+  ml.start(smem, n_kt);
+  ml.finish(smem, n_kt, acc);
+
+  if (C::BM > V) fill_rows_past<C>(acc, at.row0(), V, -__builtin_inff());
+  static_assert(C::NB == 4 && C::WN == 1, "four columns per lane");
+  float x[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    x[k] = -__builtin_inff();
+#pragma unroll
+    for (int i = 0; i < C::MB; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x[k] = fmaxf(x[k], acc[i][k][r]);
+  }
+  __attribute__((address_space(3))) float* red = (__attribute__((address_space(3))) float*)smem;
+  red[at.wm * C::BN + at.g * 16 + at.c] = reduce4(x, [](float a, float b) { return fmaxf(a, b); });
+  __syncthreads();
+  // each wavefront's 16 tokens, four at a time with 16 lanes each, the next four's first pieces on their way meanwhile
+  const int pieces = d / 8;
+  auto row = [&](int q) { return at.wm * kShare + q * 4 + at.g; };
+  int y[kShare / 4];
+#pragma unroll
+  for (int q = 0; q < kShare / 4; ++q) y[q] = __shfl(tok, q * 4 + at.g, 64);
+  auto load = [&](const int q, int e, bf16x8& h, bf16x8& w) {
+    const int64_t t = n0 + row(q) < T ? n0 + row(q) : T - 1;
+    const int p = e < pieces ? e : pieces - 1;
+    h = *(const bf16x8*)(H + t * d + p * 8);
+    w = *(const bf16x8*)(W + (int64_t)(y[q] < 0 || y[q] >= V ? 0 : y[q]) * d + p * 8);
+  };
+  constexpr int kAhead = 2;      // pieces per lane: rows of up to 256 elements are all under way at once
+  bf16x8 h[kShare / 4][kAhead], w[kShare / 4][kAhead];
+#pragma unroll
+  for (int q = 0; q < kShare / 4; ++q)
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) load(q, at.c + 16 * k, h[q][k], w[q][k]);
+#pragma unroll
+  for (int q = 0; q < kShare / 4; ++q) {
+    float z = 0.f;
+    auto add = [&](const bf16x8& x, const bf16x8& y, bool there) {
+      if (!there) return;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) z += (float)x[i] * (float)y[i];
+    };
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) add(h[q][k], w[q][k], at.c + 16 * k < pieces);
+#pragma unroll 4
+    for (int e = at.c + 16 * kAhead; e < pieces; e += 16) {
+      bf16x8 a, b;
+      load(q, e, a, b);
+      add(a, b, true);
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o /= 2) z += __shfl_xor(z, o, 64);
+    const int64_t t = n0 + row(q);
+    if (at.c != 0 || t >= T) continue;
+    float largest = kNegHuge;
+#pragma unroll
+    for (int i = 0; i < C::WM; ++i) largest = fmaxf(largest, red[i * C::BN + row(q)] * kLog2e);
+    // a token out of range is recorded by k_sweep_finish
+    init_token(init, t, y[q] >= 0 && y[q] < V ? z : __builtin_nanf(""), largest, zy);
+  }
 #endif
 }
 
@@ -1325,71 +1507,6 @@ k_pack_rows(const bf16_t* __restrict__ src, int64_t R, int K, int64_t ld, bf16_t
     u32x4 v = {0u, 0u, 0u, 0u};
     if (r < R && k < K) v = load_any16(src + r * ld + k);
     *(u32x4*)(out + row * 128 + c * 16) = v;
-  }
-}
-
-// dst = packed(S^T), an m-side operand (256-row blocks), where S [R, Ccols] is row-major (ld; Ccols and ld
-// multiples of 8) and optionally row-scaled:
-// dst row j (a column of S), k index r (a row of S): dst(j, r) = bf16(S[r][j] * scale[r]).
-// One workgroup per destination block (jt, kt): it reads S[kt*64 .. +64][jt*256 .. +256] in 16-byte
-// pieces (8 columns of one row), four consecutive rows per thread, turns each 4 x 8 patch into eight
-// 8-byte column pieces (4 rows of one column) and parks them in LDS as [row quad][column]; a
-// destination chunk (8 consecutive r of one j, 16 bytes) is then two 8-byte LDS reads.
-// Blocks in [0, n_jt) x [0, n_kt); zero outside [0, Ccols) x [0, R).
-__global__ void __launch_bounds__(256)
-k_pack_transposed(const bf16_t* __restrict__ src, int64_t R, int Ccols, int64_t ld, const float* __restrict__ scale,
-                  bf16_t* __restrict__ dst, int n_kt, Gate gate) {
-  // bytes per row quad: 256 columns x 8 bytes; +16 keeps the reads below off each other's banks
-  constexpr int kPitch = kPackRowsA * 8 + 16;
-  __shared__ __attribute__((aligned(16))) char tile[(kPackK / 4) * kPitch];
-  if (gate_closed(gate)) return;
-  const int kt = blockIdx.x, jt = blockIdx.y;
-  const int64_t r0 = (int64_t)kt * kPackK;
-  const int j0 = jt * kPackRowsA;
-  const int cc = threadIdx.x & 31;                // 8-column piece of the 256 columns
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int rq = (threadIdx.x >> 5) + 8 * pass;   // row quad 0 .. 15
-    const int j = j0 + cc * 8;
-    u32x4 row[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int64_t r = r0 + 4 * rq + k;
-      row[k] = u32x4{0u, 0u, 0u, 0u};
-      if (r < R && j < Ccols) {
-        row[k] = load_any16(src + r * ld + j);
-        if (scale != nullptr) {
-          const float sc = scale[r];
-#pragma unroll
-          for (int m = 0; m < 4; ++m) {
-            // a copy: a vector element is not an object whose bytes can be reinterpreted in place
-            const uint32_t x = row[k][m];
-            const bf16x2 v = __builtin_bit_cast(bf16x2, x);
-            const bf16x2 w = {(bf16_t)((float)v[0] * sc), (bf16_t)((float)v[1] * sc)};
-            row[k][m] = __builtin_bit_cast(uint32_t, w);
-          }
-        }
-      }
-    }
-    // dword m of a row holds columns 2m (low half) and 2m + 1 (high half)
-    char* out = tile + rq * kPitch + cc * 64;
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      const uint32_t a0 = row[0][m], a1 = row[1][m], a2 = row[2][m], a3 = row[3][m];
-      const u32x4 piece = {(a0 & 0xFFFFu) | (a1 << 16), (a2 & 0xFFFFu) | (a3 << 16),        // column 2m: rows 0..3
-                           (a0 >> 16) | (a1 & 0xFFFF0000u), (a2 >> 16) | (a3 & 0xFFFF0000u)};  // column 2m + 1
-      *(u32x4*)(out + m * 16) = piece;
-    }
-  }
-  __syncthreads();
-  char* outb = (char*)dst + ((int64_t)jt * n_kt + kt) * (int64_t)kPackBlockBytesA;
-#pragma unroll
-  for (int it = 0; it < 8; ++it) {
-    const int idx = it * 256 + threadIdx.x;
-    const int rowj = idx >> 3, c = idx & 7;                 // destination row (j), 8 consecutive k = row quads 2c, 2c + 1
-    const u32x2 lo = *(const u32x2*)(tile + (2 * c) * kPitch + rowj * 8);
-    const u32x2 hi = *(const u32x2*)(tile + (2 * c + 1) * kPitch + rowj * 8);
-    *(u32x4*)(outb + rowj * 128 + c * 16) = u32x4{lo[0], lo[1], hi[0], hi[1]};
   }
 }
 

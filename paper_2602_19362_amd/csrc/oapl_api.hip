@@ -19,6 +19,9 @@ namespace oapl {
 // SIMD; operands in a ring of 2 LDS stages (160 KB, the whole LDS of a CU).
 typedef TileCfg<4, 2, 4, 12, 2> Cfg;
 static_assert(Cfg::BN == kPackRowsB, "n-side operands of the loss path are packed in blocks of one tile");
+// ... with each block's loads in one go, for a sweep of one token tile or whose tiles are there all at once: it waits for W to
+// arrive (300 tokens at d = 2048, V = 32000, 125 tiles: 84 us, 87 .. 91 spread; 380 at d = 4096, V = 151936: 464 / 469).
+typedef TileCfg<4, 2, 4, 12, 2, 0, true> CfgEarly;
 // Where tiles of that size are too few to fill the chip (small heads and hidden sizes): 128 x 128, two workgroups per CU,
 // on the same packed blocks.
 typedef TileCfg<2, 2, 4, 4, 2, kPackRowsB> CfgSmall;
@@ -362,6 +365,8 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
       else p.dh = pick_dh(last, d, p.n_kt_v, true, part_bytes);
       p.small_dw = p.rows && T <= p.Tp && small_tiles_pay(kSmallDw, d, V, (int)((T + kPackK - 1) / kPackK));
       p.grads_fused = p.small_dw && p.dh.small;
+      // beside dW's walks, dH's need not be split while they are not much longer: no partial sums, and a launch less
+      if (p.grads_fused && p.n_kt_v <= 2 * (int)((T + kPackK - 1) / kPackK)) p.dh.splits = 1;
       p.off_part = p.rows && p.dh.splits > 1 ? take((size_t)p.dh.splits * last * d * 4) : p.off_Wp;
       p.small_sweep = p.rows && T <= p.Tp && !lean && small_tiles_pay(kSmallSweep, V, T, p.n_kt_d);
       p.n_vt = p.small_sweep ? (V + CfgSmall::BM - 1) / CfgSmall::BM : p.n_rt_v;
@@ -480,8 +485,11 @@ static bool prepare_kernels() {
          allow_sample<Cfg128, true>() && allow_sample<Cfg256, true>() && allow_sample<Cfg256Early, true>() && allow_sample<CfgSample, false>() &&
          allow_big_lds(k_fwd_lse<CfgRef, false, true>, CfgRef::LDS_BYTES) &&
          allow_big_lds(k_fwd_lse<CfgRef, false, false>, CfgRef::LDS_BYTES) &&
+         allow_big_lds(k_sweep_begin<CfgRef, OaplBegin>, CfgRef::LDS_BYTES) &&
+         allow_big_lds(k_sweep_begin<CfgRef, GrpoBegin>, CfgRef::LDS_BYTES) &&
          allow_big_lds(k_bwd_dz<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_bwd_dz<Cfg, true>, Cfg::LDS_BYTES) &&
          allow_big_lds(k_sweep<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_sweep<Cfg, true>, Cfg::LDS_BYTES) &&
+         allow_big_lds(k_sweep<CfgEarly, true>, CfgEarly::LDS_BYTES) &&
          allow_big_lds(k_sweep<CfgSmall, true>, CfgSmall::LDS_BYTES) &&
          allow_big_lds(k_sweep<CfgDeep, true>, CfgDeep::LDS_BYTES) && allow_dh<Cfg, false>() && allow_dh<Cfg, true>() &&
          allow_dh<CfgSmall, true>() && allow_dh<CfgDeep, true>() && allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
@@ -755,31 +763,40 @@ static int launch_gradients(const Plan& p, DhArgs dh, const DwArgs& dw, bool las
   dh.part = split ? (float*)(ws + p.off_part) : nullptr;
   const int64_t dh_groups = small ? tile_count<CfgDeep>(p.d, dh.n_valid) * dh.splits : 0;
   const int64_t dw_groups = p.small_dw ? tile_count<CfgDeep>(p.d, p.V) : 0;
+  auto reduce = [&] {     // before anything else has pushed the partial sums out of the caches (11 us; 21 behind dW's stores)
+    if (!split) return;
+    const int64_t blocks = grid1d(dh.n_valid * (p.d / 8), 256);
+    k_dh_reduce<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, st>>>(dh.part, dh.splits, dh.n_valid, p.d, dh.row_factor,
+                                                                        dh.dH, gate);
+  };
   if (p.grads_fused) {
-    ScopedKernelTimer tm(kBwdDw, st, timed);
-    if (dh_groups + dw_groups <= kNumCU) launch_grads<CfgDeep>(dh, split, dw, st, gate);
-    else launch_grads<CfgSmall>(dh, split, dw, st, gate);
-  } else {
     {
-      ScopedKernelTimer tm(kBwdDh, st, timed);
-      if (small && dh_groups <= kNumCU) launch_dh<CfgDeep, true>(dh, split, st, gate);
-      else if (small) launch_dh<CfgSmall, true>(dh, split, st, gate);
-      else if (p.rows) launch_dh<Cfg, true>(dh, split, st, gate);
-      else launch_dh<Cfg, false>(dh, split, st, gate);
+      ScopedKernelTimer tm(kBwdDw, st, timed);
+      if (dh_groups + dw_groups <= kNumCU) launch_grads<CfgDeep>(dh, split, dw, st, gate);
+      else launch_grads<CfgSmall>(dh, split, dw, st, gate);
     }
     OAPL_LAUNCH_CHECK();
+    reduce();
+    OAPL_LAUNCH_CHECK();
+    return OAPL_OK;
+  }
+  {
+    ScopedKernelTimer tm(kBwdDh, st, timed);
+    if (small && dh_groups <= kNumCU) launch_dh<CfgDeep, true>(dh, split, st, gate);
+    else if (small) launch_dh<CfgSmall, true>(dh, split, st, gate);
+    else if (p.rows) launch_dh<Cfg, true>(dh, split, st, gate);
+    else launch_dh<Cfg, false>(dh, split, st, gate);
+  }
+  OAPL_LAUNCH_CHECK();
+  reduce();
+  OAPL_LAUNCH_CHECK();
+  {
     ScopedKernelTimer tm(kBwdDw, st, timed);
     if (p.small_dw && dw_groups <= kNumCU) launch_dw<CfgDeep>(dw, st, gate);
     else if (p.small_dw) launch_dw<CfgSmall>(dw, st, gate);
     else launch_dw<Cfg>(dw, st, gate);
   }
   OAPL_LAUNCH_CHECK();
-  if (split) {
-    const int64_t blocks = grid1d(dh.n_valid * (p.d / 8), 256);
-    k_dh_reduce<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, st>>>(dh.part, dh.splits, dh.n_valid, p.d, dh.row_factor,
-                                                                        dh.dH, gate);
-    OAPL_LAUNCH_CHECK();
-  }
   return OAPL_OK;
 }
 
@@ -792,39 +809,47 @@ static void launch_sweep(const Plan& p, const bf16_t* W, const bf16_t* H, int64_
 
 static int pack_wt(const Plan& p, const void* W, char* ws, hipStream_t st, Gate gate) {
   if (p.rows) return OAPL_OK;
-  k_pack_transposed<<<dim3(p.n_kt_v, p.n_rt_d), 256, 0, st>>>((const bf16_t*)W, p.V, p.d, p.d, nullptr,
-                                                              (bf16_t*)(ws + p.off_WTp), p.n_kt_v, gate);
+  k_pack_transposed<<<dim3(p.n_kt_v, p.n_rt_d), 256, 0, st>>>(
+      PackTransposed{(const bf16_t*)W, p.V, p.d, p.d, nullptr, (bf16_t*)(ws + p.off_WTp), p.n_kt_v}, gate);
   OAPL_LAUNCH_CHECK();
   return OAPL_OK;
 }
 
-// Step a8, two-pass form: the soft-max tiles of the panel at token t0 recomputed into G and G^T.
+// (diag(coef) H)^T of the panel at token t0, packed; token columns in [nv, 64 kt) come out as zeros
+static PackTransposed scaled_rows(const Plan& p, const void* H, int64_t t0, char* ws) {
+  const int64_t nv = (p.T - t0) < p.Tp ? (p.T - t0) : p.Tp;
+  return PackTransposed{(const bf16_t*)H + t0 * p.d, nv, p.d, p.d, (const float*)(ws + p.off_coef) + t0, (bf16_t*)(ws + p.off_HTp),
+                        p.n_kt_t};
+}
+
+// Step a8, two-pass form: the soft-max tiles of the panel at token t0 recomputed into G and G^T.  `pack`: the launch makes the
+// panel's scaled_rows too, whatever the gate says.
 static int recompute_panel(const Plan& p, const void* H, const void* W, const int32_t* tokens, int64_t t0, bf16_t* G, bf16_t* GT,
-                           char* ws, hipStream_t st, Gate gate) {
+                           char* ws, hipStream_t st, Gate gate, bool pack = false) {
   const int64_t nv = (p.T - t0) < p.Tp ? (p.T - t0) : p.Tp;
   const ContractD x = contract_d(p, H, W, ws);
+  const int kt = (int)((nv + kPackK - 1) / kPackK), blocks = kt * p.n_rt_d, n_pack = pack ? (blocks + 1) / 2 : 0;
   {
     ScopedKernelTimer tm(kBwdDz, st, gate.flag == nullptr);
     (p.rows ? k_bwd_dz<Cfg, true> : k_bwd_dz<Cfg, false>)<<<
-        (unsigned)round_up(p.n_rt_v * ((nv + Cfg::BN - 1) / Cfg::BN), 8), Cfg::NT, Cfg::LDS_BYTES, st>>>(
+        (unsigned)(n_pack + round_up(p.n_rt_v * ((nv + Cfg::BN - 1) / Cfg::BN), 8)), Cfg::NT, Cfg::LDS_BYTES, st>>>(
         x.W, x.H + t0 * x.ld, p.V, nv, p.d, p.n_kt_d, tokens + t0, (const float*)(ws + p.off_lse2) + t0,
-        (const float*)(ws + p.off_inv) + t0, G, p.n_kt_g, GT, p.n_kt_t, gate);
+        (const float*)(ws + p.off_inv) + t0, G, p.n_kt_g, GT, p.n_kt_t, gate, n_pack, scaled_rows(p, H, t0, ws), kt, blocks);
   }
   OAPL_LAUNCH_CHECK();
   return OAPL_OK;
 }
 
 // Steps a9, a10: the two gradient contractions of the panel at token t0 from G and G^T, with coef[t] = the row factor
-// (two-pass form: f_t = c_t (1 - p_y); single sweep: a_t).
+// (two-pass form: f_t = c_t (1 - p_y); single sweep: a_t).  `packed`: an earlier launch made scaled_rows.
 static int panel_gradients(const Plan& p, const void* H, const void* W, int64_t t0, const bf16_t* G, const bf16_t* GT, void* dH,
-                           float* dW, char* ws, hipStream_t st, Gate gate, bool timed) {
+                           float* dW, char* ws, hipStream_t st, Gate gate, bool timed, bool packed = false) {
   const int d = p.d;
   const int64_t nv = (p.T - t0) < p.Tp ? (p.T - t0) : p.Tp;
   const int kt = (int)((nv + kPackK - 1) / kPackK);
   const float* coef = (const float*)(ws + p.off_coef) + t0;
   bf16_t* HTp = (bf16_t*)(ws + p.off_HTp);
-  // (diag(coef) H)^T of this panel, packed; token columns in [nv, 64 kt) come out as zeros
-  k_pack_transposed<<<dim3(kt, p.n_rt_d), 256, 0, st>>>((const bf16_t*)H + t0 * d, nv, d, d, coef, HTp, p.n_kt_t, gate);
+  if (!packed) k_pack_transposed<<<dim3(kt, p.n_rt_d), 256, 0, st>>>(scaled_rows(p, H, t0, ws), gate);
   OAPL_LAUNCH_CHECK();
   const DhArgs dh{p.rows ? (const bf16_t*)W : (const bf16_t*)(ws + p.off_WTp), p.V, p.n_kt_v, G, p.n_kt_g, d, nv, p.n_kt_v, coef,
                   (bf16_t*)dH + t0 * d, 1, nullptr};
@@ -909,6 +934,14 @@ static int launch_begin(const Begin& begin, hipStream_t st) {
   return OAPL_OK;
 }
 
+// The sweep's beginning, reference pass and gather in one launch (k_sweep_begin), 1000 tokens at d = 256, V = 1544: whole call 58
+// us, 67 in three.  Sixteen sampled logits per wavefront cost more than a launch of their own once rows are long
+// (in four rounds of whole wavefronts 500 tokens at d = 1024 lost 1.5 %, 300 at d = 4096 3 %).
+constexpr int kOneLaunchHidden = 1024;
+static bool sweep_begins_in_one_launch(const Plan& p, int n_seq, int n_groups) {
+  return p.rows && p.d <= kOneLaunchHidden && begin_in_one_launch(n_seq, n_groups);
+}
+
 // Steps a1-a3 and a8-a10 in ONE pass over the logits (bf16, T > 0).  Per panel of token rows:
 // k_sweep writes the unnormalised soft-max panel and its row sums, k_sweep_finish turns the sums
 // into log-probs; the objective (`objective(gate, factors)`, which must fill coef[t] = c_t * factor[t]
@@ -937,15 +970,23 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
   float* nis = (float*)(ws + p.off_inv);
   const float* omp = (const float*)(ws + p.off_omp);
 
-  if (int rc = launch_begin(begin, st)) return rc;
-  if (int rc = pack_wt(p, W, ws, st, kNoGate)) return rc;
-  // reference exponents: running maximum over the first 256 vocabulary entries, one workgroup per 64 tokens (a walk of
-  // d / 64 k-blocks each, bound by their latency)
-  const FwdArgs ref{x.W, x.H, V < CfgRef::BM ? V : CfgRef::BM, T, d, p.n_kt_d, TilePick{}};
-  if (p.rows) launch_fwd_lse_kernel<CfgRef, false, true>(ref, sample, nullptr, nullptr, st, fast);
-  else launch_fwd_lse_kernel<CfgRef, false, false>(ref, sample, nullptr, nullptr, st, fast);
-  OAPL_LAUNCH_CHECK();
-  if (int rc = gather_logits(p, H, W, tokens, TokenInit{(float*)(ws + p.off_coef), sample, ref2, diff, nis}, ws, st)) return rc;
+  const TokenInit init{(float*)(ws + p.off_coef), sample, ref2, diff, nis};
+  const bool one = sweep_begins_in_one_launch(p, begin.n_seq, begin.n_groups);
+  if (one) {
+    k_sweep_begin<CfgRef><<<1 + grid1d(T, CfgRef::BN), CfgRef::NT, CfgRef::LDS_BYTES, st>>>(begin, x.W, x.H, V, T, d, p.n_kt_d,
+                                                                                         tokens, (float*)(ws + p.off_zy), init);
+    OAPL_LAUNCH_CHECK();
+  } else {
+    if (int rc = launch_begin(begin, st)) return rc;
+    if (int rc = pack_wt(p, W, ws, st, kNoGate)) return rc;
+    // reference exponents: running maximum over the first 256 vocabulary entries, one workgroup per 64 tokens (a walk of
+    // d / 64 k-blocks each, bound by their latency)
+    const FwdArgs ref{x.W, x.H, V < CfgRef::BM ? V : CfgRef::BM, T, d, p.n_kt_d, TilePick{}};
+    if (p.rows) launch_fwd_lse_kernel<CfgRef, false, true>(ref, sample, nullptr, nullptr, st, fast);
+    else launch_fwd_lse_kernel<CfgRef, false, false>(ref, sample, nullptr, nullptr, st, fast);
+    OAPL_LAUNCH_CHECK();
+    if (int rc = gather_logits(p, H, W, tokens, init, ws, st)) return rc;
+  }
 
   auto sweep = [&](int64_t k) -> int {
     const int64_t t0 = k * p.Tp;
@@ -955,6 +996,8 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
       const bf16_t* Ht = x.H + t0 * x.ld;
       if (p.small_sweep && tile_count<CfgDeep>(V, nv) <= kNumCU)
         launch_sweep<CfgDeep, true>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
+      else if (!p.small_sweep && p.rows && (nv <= Cfg::BN || tile_count<Cfg>(V, nv) <= kNumCU))
+        launch_sweep<CfgEarly, true>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
       else if (p.small_sweep) launch_sweep<CfgSmall, true>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
       else if (p.rows) launch_sweep<Cfg, true>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
       else launch_sweep<Cfg, false>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
@@ -962,7 +1005,7 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
     OAPL_LAUNCH_CHECK();
     k_sweep_finish<<<grid1d(nv, kFinishRows), kFinishSlices * kFinishRows, 0, st>>>(
         spart, p.n_vt, p.Tp, nv, ref2 + t0, zy + t0, logq + t0, tokens + t0, V,
-        logprob_out ? logprob_out + t0 : nullptr, diff + t0, nis + t0, Gbuf(k), p.n_kt_g, GTbuf(k), p.n_kt_t, flag,
+        logprob_out ? logprob_out + t0 : nullptr, diff + t0, nis + t0, Gbuf(k), p.n_kt_g, GTbuf(k), p.n_kt_t, (int*)(ws + p.off_status),
         fast);
     OAPL_LAUNCH_CHECK();
     return OAPL_OK;
@@ -972,10 +1015,10 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
   if (n_panels == 1) {
     if (int rc = sweep(0)) return rc;
     if (int rc = forward_partials(p, H, W, false, false, nullptr, ws, st, slow)) return rc;
-    if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, nullptr, ws, st, slow)) return rc;
+    if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, one ? tokens : nullptr, ws, st, slow)) return rc;
     if (int rc = objective(kNoGate, TokenFactor{nis, omp, flag})) return rc;
-    if (int rc = recompute_panel(p, H, W, tokens, 0, Gbuf(0), GTbuf(0), ws, st, slow)) return rc;
-    return panel_gradients(p, H, W, 0, Gbuf(0), GTbuf(0), dH, dW, ws, st, kNoGate, true);
+    if (int rc = recompute_panel(p, H, W, tokens, 0, Gbuf(0), GTbuf(0), ws, st, slow, p.grads_fused)) return rc;
+    return panel_gradients(p, H, W, 0, Gbuf(0), GTbuf(0), dH, dW, ws, st, kNoGate, true, p.grads_fused);
   }
 
   auto gradients = [&](int64_t k) -> int {

@@ -37,11 +37,21 @@ constexpr float kSweepMargin = 40.f;
 constexpr float kSweepLimit = 1.2676506e30f;   // 2^100: largest S_t the single sweep accepts
 struct TokenInit {
   float* coef;            // or nullptr
-  const float2* sample;   // or nullptr: no single sweep
-  float* ref2;
+  const float2* sample;   // or nullptr
+  float* ref2;            // or nullptr: no single sweep
   double* diff;
   float* nis;
 };
+// What a token of a call gets with its logit z; `largest`: of the sample's logits, in the exp2 domain.
+__device__ __forceinline__ void init_token(const TokenInit& init, int64_t t, float z, float largest, float* __restrict__ zy) {
+  zy[t] = z;
+  if (init.coef) init.coef[t] = 0.f;
+  if (init.ref2) {
+    init.ref2[t] = fmaxf(largest, z * kLog2e) + kSweepMargin;    // fmaxf drops a NaN (token out of range)
+    init.diff[t] = 0.0;
+    init.nis[t] = 0.f;
+  }
+}
 // `err` == nullptr: a token out of range is recorded by a later launch (k_lse_finish), for the status header is being cleared
 // by this one.
 template <class T, class ACC, int VEC>
@@ -52,15 +62,7 @@ __device__ __forceinline__ void gather_logit(int64_t t /* of this wavefront */, 
   const int lane = threadIdx.x & 63;
   if (t >= Ttok) return;
   const int y = tokens[t];
-  auto finish = [&](float z) {
-    zy[t] = z;
-    if (init.coef) init.coef[t] = 0.f;
-    if (init.sample) {
-      init.ref2[t] = fmaxf(init.sample[t].x, z * kLog2e) + kSweepMargin;    // fmaxf drops a NaN (token out of range)
-      init.diff[t] = 0.0;
-      init.nis[t] = 0.f;
-    }
-  };
+  auto finish = [&](float z) { init_token(init, t, z, init.sample ? init.sample[t].x : 0.f, zy); };
   if (y < 0 || y >= V) {
     if (lane == 0) {
       if (err) record_token_error(err);
@@ -574,7 +576,7 @@ k_sweep_finish(const float* __restrict__ spart, int n_vt, int64_t ld_s, int64_t 
                const float* __restrict__ ref2, const float* __restrict__ zy, const float* __restrict__ logq,
                const int32_t* __restrict__ tokens, int V, float* __restrict__ logprob_out,
                double* __restrict__ diff, float* __restrict__ nis, bf16_t* __restrict__ Gp, int g_n_kt,
-               bf16_t* __restrict__ GTp, int gt_n_kt, int* __restrict__ flag, Gate gate) {
+               bf16_t* __restrict__ GTp, int gt_n_kt, int* __restrict__ status, Gate gate) {
   if (gate_closed(gate)) return;
   // kFinishRows token rows per workgroup; the tile sums of a row are added in kFinishSlices interleaved slices
   // (slice s takes tiles s, s + kFinishSlices, ...), then the slices in order: a fixed order, and
@@ -593,7 +595,7 @@ k_sweep_finish(const float* __restrict__ spart, int n_vt, int64_t ld_s, int64_t 
   double S = part[0][col];
 #pragma unroll
   for (int s = 1; s < kFinishSlices; ++s) S += part[s][col];
-  if (!(S <= (double)kSweepLimit)) atomicCAS(flag, 0, 1);     // also catches inf and NaN
+  if (!(S <= (double)kSweepLimit)) atomicCAS(status + kFlagWord, 0, 1);     // also catches inf and NaN
   const double lse = ((double)ref2[n] + log2(S)) * kLn2;
   double lp = (double)zy[n] - lse;     // NaN if the token was out of range
   if (lp > 0.0) lp = 0.0;
@@ -616,6 +618,7 @@ k_sweep_finish(const float* __restrict__ spart, int n_vt, int64_t ld_s, int64_t 
     Gp[(nb * g_n_kt + (y >> 6)) * blk + nr * kPackK + (y & 63)] = patch;
     GTp[((int64_t)yb * gt_n_kt + (n >> 6)) * blk + (int64_t)yr * kPackK + (n & 63)] = patch;
   }
+  if (y < 0 || y >= V) record_token_error(status);
   nis[n] = (float)row_factor;
 }
 
