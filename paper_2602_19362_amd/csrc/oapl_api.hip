@@ -156,9 +156,10 @@ static TilePick pick_splits(FwdTile tile, int64_t T, int V, int max_splits, doub
 }
 
 // Tile and splits over row-major operands.  Up to 128 tokens the call is bound by reading W and every 128-row
-// vocabulary tile is a workgroup of its own.  Beyond, the time of one 256-row tile at d = 4096 is 105 / 126 / 150 us
-// for 256 / 320 / 384 columns (it scales with d): the wide tile is the cheapest per column, a narrower one pads fewer
-// columns (777 tokens: 919 us in three 320-wide tiles, 1036 in three of 384, 1029 in four of 256).
+// vocabulary tile is a workgroup of its own.  Beyond, the time of one 256-row tile at d = 4096 was 105 / 126 / 150 us
+// for 256 / 320 / 384 columns when it was taken (it scales with d, and all three are 7 % shorter now): the wide tile is the
+// cheapest per column, a narrower one pads fewer
+// columns (777 tokens, then: 919 us in three 320-wide tiles, 1036 in three of 384, 1029 in four of 256; now 840).
 static TilePick pick_tile(int64_t T, int V, int max_splits, bool scoring) {
   const int MT128 = (V + 127) / 128;
   const int small = MT128 < max_splits ? MT128 : max_splits;
