@@ -78,7 +78,8 @@ struct TileCfg {
   static constexpr int SLOT = STAGE_A + STAGE_B;   // one ring slot: the m-side block, then the n-side block
   static constexpr int MAIN_BYTES = NS * (STAGE_A + STAGE_B);
   static constexpr int NI_A = BM / (8 * NW);    // direct loads per wave and stage (8 rows each), m-side operand
-  static constexpr int NI_B = BN / (8 * NW);    // ... n-side operand
+  static constexpr int NI_B = (BN / 8 + NW - 1) / NW;   // ... n-side operand
+  static constexpr int LAST_B = BN / 8 % NW;    // waves that take part in the last of them (0: all)
   // bf16 staging tiles used by epilogues, rows padded so that a write instruction's lanes spread over the banks.  A whole
   // tile does not fit the LDS, so epilogues stage it in chunks: [n][m] by wave column (BN / WN rows of n at a
   // time), [m][n] by pairs of MFMA block rows (32 rows of every wave row at a time).
@@ -93,7 +94,7 @@ struct TileCfg {
       MAIN_BYTES > STAGE_NM ? (MAIN_BYTES > STAGE_MN ? MAIN_BYTES : STAGE_MN)
                             : (STAGE_NM > STAGE_MN ? STAGE_NM : STAGE_MN);
   static_assert(NS == 2 || NS == 4, "ring size");
-  static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "block rows must split over waves");
+  static_assert(BM % (8 * NW) == 0 && (LAST_B == 0 || NS == 2), "a ring of four counts every wave's loads");
   static_assert(RED_BYTES + RED_BYTES / 2 <= LDS_BYTES, "reduction scratch must fit");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of one CU");
 };
@@ -271,6 +272,7 @@ struct Mainloop {
       }
     } else if (i < C::NI_A + C::NI_B) {
       const int b = i - C::NI_A;
+      if (C::LAST_B != 0 && b == C::NI_B - 1 && wave >= C::LAST_B) return;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           rb, (lds_void_ptr)(smem + STAGE * C::SLOT + C::STAGE_A + (b * C::NW + wave) * 1024), 16,
           ATR ? (v < 0 ? v : voff) : ROWS ? v + b * istep : v,

@@ -46,10 +46,14 @@ typedef CfgSample Cfg256;
 // sampling 4000 4116 / 3904).
 typedef TileCfg<4, 2, 4, 8, 2, 0, true> Cfg256Early;
 constexpr int64_t kEarlyTokens = 2 * Cfg256Early::BN;
+// Odd widths: the n-side block is 4.5 or 5.5 loads per wave, the last of them half of the waves'.  The 352-wide kernel has a
+// register too few (8 B of scratch, outside the k loop).
+typedef TileCfg<4, 2, 4, 9, 2> Cfg288;
 typedef TileCfg<4, 2, 4, 10, 2> Cfg320;
+typedef TileCfg<4, 2, 4, 11, 2> Cfg352;
 // The sweep's reference exponents: the first 256 vocabulary entries of 64 tokens (a sixth of a packed block of H).
 typedef TileCfg<4, 1, 4, 4, 4, kPackRowsB> CfgRef;
-enum FwdTile { kTile64, kTile128, kTile256, kTile320, kTile384 };
+enum FwdTile { kTile64, kTile128, kTile256, kTile320, kTile384, kTile288, kTile352 };
 struct TilePick {
   FwdTile tile = kTile384;
   int splits = 1;     // vocabulary ranges: one workgroup per (token tile, range), and the number of partials per token
@@ -156,21 +160,26 @@ static TilePick pick_splits(FwdTile tile, int64_t T, int V, int max_splits, doub
 }
 
 // Tile and splits over row-major operands.  Up to 128 tokens the call is bound by reading W and every 128-row
-// vocabulary tile is a workgroup of its own.  Beyond, the time of one 256-row tile at d = 4096 was 105 / 126 / 150 us
-// for 256 / 320 / 384 columns when it was taken (it scales with d, and all three are 7 % shorter now): the wide tile is the
-// cheapest per column, a narrower one pads fewer
-// columns (777 tokens, then: 919 us in three 320-wide tiles, 1036 in three of 384, 1029 in four of 256; now 840).
+// vocabulary tile is a workgroup of its own.  Beyond, the time of one 256-row tile at d = 4096 is in the ratio of 105 / 115.5 /
+// 126 / 138 / 150 for 256 / 288 / 320 / 352 / 384 columns (it scales with d): the wide tile is the cheapest per column, a narrower one
+// pads fewer columns.  256, 320 and 384 alone / all five: 350 tokens at d = 4096 433 / 403 us, 700 725 / 674, 777 825 / 779, 1003 996 /
+// 941, 1400 1412 / 1292, 2500 and more the same.
 static TilePick pick_tile(int64_t T, int V, int max_splits, bool scoring) {
   const int MT128 = (V + 127) / 128;
   const int small = MT128 < max_splits ? MT128 : max_splits;
   if (T <= Cfg64::BN) return TilePick{kTile64, small};
   if (T <= Cfg128::BN) return TilePick{kTile128, small};
-  double t256, t320, t384;
-  const TilePick p256 = pick_splits<Cfg256>(kTile256, T, V, max_splits, 105.0, &t256);
-  if (!scoring) return p256;
-  const TilePick p320 = pick_splits<Cfg320>(kTile320, T, V, max_splits, 126.0, &t320);
-  const TilePick p384 = pick_splits<Cfg>(kTile384, T, V, max_splits, 150.0, &t384);
-  return t384 <= t320 && t384 <= t256 ? p384 : t320 <= t256 ? p320 : p256;
+  double best_time, time;
+  TilePick best = pick_splits<Cfg256>(kTile256, T, V, max_splits, 105.0, &best_time);
+  if (!scoring) return best;
+  auto consider = [&](const TilePick& pick) {     // ties go to the wider tile
+    if (time <= best_time) { best = pick; best_time = time; }
+  };
+  consider(pick_splits<Cfg288>(kTile288, T, V, max_splits, 115.5, &time));
+  consider(pick_splits<Cfg320>(kTile320, T, V, max_splits, 126.0, &time));
+  consider(pick_splits<Cfg352>(kTile352, T, V, max_splits, 138.0, &time));
+  consider(pick_splits<Cfg>(kTile384, T, V, max_splits, 150.0, &time));
+  return best;
 }
 
 static TilePick pick_fwd(bool rows, int64_t T, int V, int max_splits) {
@@ -481,7 +490,8 @@ static bool prepare_kernels() {
   static std::once_flag once;
   static bool ok = false;
   std::call_once(once, [] {
-    ok = allow_fwd<Cfg64, true>() && allow_fwd<Cfg128, true>() && allow_fwd<Cfg256, true>() && allow_fwd<Cfg256Early, true>() && allow_fwd<Cfg320, true>() &&
+    ok = allow_fwd<Cfg64, true>() && allow_fwd<Cfg128, true>() && allow_fwd<Cfg256, true>() && allow_fwd<Cfg256Early, true>() &&
+         allow_fwd<Cfg288, true>() && allow_fwd<Cfg320, true>() && allow_fwd<Cfg352, true>() &&
          allow_fwd<Cfg, true>() && allow_fwd<Cfg, false>() && allow_sample<Cfg64, true>() &&
          allow_sample<Cfg128, true>() && allow_sample<Cfg256, true>() && allow_sample<Cfg256Early, true>() && allow_sample<CfgSample, false>() &&
          allow_big_lds(k_fwd_lse<CfgRef, false, true>, CfgRef::LDS_BYTES) &&
@@ -545,7 +555,9 @@ static void launch_fwd_lse(const FwdArgs& a, bool rows, float2* partials, float*
     case kTile256:
       if (a.T <= kEarlyTokens) return launch_fwd_lse<Cfg256Early, true>(a, partials, upart, clear, st, gate);
       return launch_fwd_lse<Cfg256, true>(a, partials, upart, clear, st, gate);
+    case kTile288: return launch_fwd_lse<Cfg288, true>(a, partials, upart, clear, st, gate);
     case kTile320: return launch_fwd_lse<Cfg320, true>(a, partials, upart, clear, st, gate);
+    case kTile352: return launch_fwd_lse<Cfg352, true>(a, partials, upart, clear, st, gate);
     case kTile384: return launch_fwd_lse<Cfg, true>(a, partials, upart, clear, st, gate);
   }
 }

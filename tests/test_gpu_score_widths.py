@@ -1,0 +1,36 @@
+"""Scoring in tiles of every width (288 and 352 columns are loads that only half of the wavefronts take part in): token counts at
+the edges of one, two and three tiles, with and without ragged k-blocks, and both sides of the line up to which loads
+go out early.  test_plan.py checks that each case takes the tile named here."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oapl_oracle as orc
+from paper_2602_19362_amd import oapl
+from tests._util import f64
+from tests.test_gpu_parity import _custom_batch
+
+pytestmark = pytest.mark.gpu
+
+V = 60000
+CASES = [(257, 288), (288, 288), (289, 320), (321, 352), (352, 352), (353, 384), (385, 256), (512, 256), (513, 288), (576, 288),
+         (650, 352), (704, 352), (864, 288), (1056, 352)]     # tokens, tile width
+
+
+@pytest.mark.parametrize("d", [64, 72])
+@pytest.mark.parametrize("T", [c[0] for c in CASES])
+def test_scores(T, d):
+    print(T, d, flush=True)
+    b = _custom_batch("bf16", d=d, V=V, lens=[T], n_groups=1, seed=T + d, beta=1.0)
+    lp, lse, ent, ws = oapl.logprob_fwd(b.H, b.W, b.tokens, want_lse=True, want_entropy=True)
+    assert oapl.read_device_status(ws) == 0
+    plain, _ = oapl.logprob_fwd(b.H, b.W, b.tokens)
+    assert torch.equal(lp, plain)
+    rows = np.unique(np.concatenate([np.arange(0, T, 7), np.arange(T - 40, T)]))     # every lane column, the last tile's edge
+    rt = torch.from_numpy(rows).to(b.H.device)
+    H, W = f64(b.H[rt]), f64(b.W)
+    z = H @ W.T
+    ref = np.log(np.exp(z - z.max(1, keepdims=True)).sum(1)) + z.max(1)
+    assert np.abs(f64(lse[rt]) - ref).max() <= 1e-4      # fp32 sums of exact products over d <= 72, V = 60000
+    assert np.abs(f64(lp[rt]) - (z[np.arange(rows.size), b.tokens[rt].cpu().numpy()] - ref)).max() <= 1e-4
+    assert np.abs(f64(ent[rt]) - orc.token_entropy(H, W)).max() <= 2e-3

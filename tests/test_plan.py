@@ -2,7 +2,7 @@
 import pytest
 
 from paper_2602_19362_amd import oapl
-from tests import test_gpu_dh_splits, test_gpu_f32_tiles, test_gpu_small_tiles
+from tests import test_gpu_dh_splits, test_gpu_f32_tiles, test_gpu_score_widths, test_gpu_small_tiles
 from tests._plan import ask
 
 INT_MAX = 2 ** 31 - 1
@@ -73,3 +73,11 @@ def test_gpu_cases_have_the_plans_they_name(dtype, cases):
     plans = ask([f"plan {T} {d} {V} {dtype} 1 {cap} 0 -1" for T, d, V, cap, _ in cases])
     for (T, d, V, cap, want), plan in zip(cases, plans):
         assert plan["rc"] == 0 and {k: plan[k] for k in want} == want, (T, d, V, cap, plan)
+
+
+def test_scoring_tiles_are_as_wide_as_the_tokens_need():
+    """The widths that the GPU test of the scoring tiles names."""
+    width = {2: 256, 3: 320, 4: 384, 5: 288, 6: 352}       # FwdTile
+    for d in (64, 72):
+        plans = ask([f"plan {T} {d} {test_gpu_score_widths.V} 1 0 0 0 -1" for T, _ in test_gpu_score_widths.CASES])
+        assert [width[p["fwd_tile"]] for p in plans] == [w for _, w in test_gpu_score_widths.CASES]
