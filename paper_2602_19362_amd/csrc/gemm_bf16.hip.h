@@ -1147,7 +1147,7 @@ k_sweep_begin(Begin begin, const bf16_t* __restrict__ W, const bf16_t* __restric
     float largest = kNegHuge;
 #pragma unroll
     for (int i = 0; i < C::WM; ++i) largest = fmaxf(largest, red[i * C::BN + row(q)] * kLog2e);
-    // a token out of range is recorded by k_sweep_finish
+    // a token out of range is recorded by k_sweep_finish, or by the fallback where that is closed
     init_token(init, t, y[q] >= 0 && y[q] < V ? z : __builtin_nanf(""), largest, zy);
   }
 #endif

@@ -985,6 +985,9 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
 
   const TokenInit init{(float*)(ws + p.off_coef), sample, ref2, diff, nis};
   const bool one = sweep_begins_in_one_launch(p, begin.n_seq, begin.n_groups);
+  // k_sweep_begin leaves tokens out of range to k_sweep_finish, which is closed for the panels behind a raised flag (for all, if it
+  // was raised at the beginning): the fallback, which that flag opens, then looks at every token
+  const int32_t* check = one ? tokens : nullptr;
   if (one) {
     k_sweep_begin<CfgRef><<<1 + grid1d(T, CfgRef::BN), CfgRef::NT, CfgRef::LDS_BYTES, st>>>(begin, x.W, x.H, V, T, d, p.n_kt_d,
                                                                                          tokens, (float*)(ws + p.off_zy), init);
@@ -1028,7 +1031,7 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
   if (n_panels == 1) {
     if (int rc = sweep(0)) return rc;
     if (int rc = forward_partials(p, H, W, false, false, nullptr, ws, st, slow)) return rc;
-    if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, one ? tokens : nullptr, ws, st, slow)) return rc;
+    if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, check, ws, st, slow)) return rc;
     if (int rc = objective(kNoGate, TokenFactor{nis, omp, flag})) return rc;
     if (int rc = recompute_panel(p, H, W, tokens, 0, Gbuf(0), GTbuf(0), ws, st, slow, p.grads_fused)) return rc;
     return panel_gradients(p, H, W, 0, Gbuf(0), GTbuf(0), dH, dW, ws, st, kNoGate, true, p.grads_fused);
@@ -1046,7 +1049,7 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
   for (int64_t k = n_panels - (p.n_buf - 1); k < n_panels; ++k)
     if (int rc = gradients(k)) return rc;
   if (int rc = forward_partials(p, H, W, false, false, nullptr, ws, st, slow)) return rc;
-  if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, nullptr, ws, st, slow)) return rc;
+  if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, check, ws, st, slow)) return rc;
   if (int rc = objective(slow, TokenFactor{omp, nullptr, nullptr})) return rc;
   return backward_grads(p, H, W, tokens, dH, dW, ws, st, slow, true);
 }

@@ -52,3 +52,35 @@ def test_calls(dtype, d, T, V):
 def test_sweeps_on_both_sides_of_early_loads(T):
     b = _custom_batch("bf16", d=512, V=40000, lens=[T - 100, 100], n_groups=1, seed=T, beta=1.0)
     _check(b, _run(b), oracle_full(b), lp_tol=2e-2, rel_tol=1e-3, g_rtol=2e-2, g_atol_frac=6e-3)
+
+
+# Several panels (384 rows each, two buffers), the call's beginning in one launch.  Whatever closes the sweep, and wherever the bad
+# token lies, somebody reports it: an open k_sweep_finish or the fallback.
+@pytest.mark.parametrize("objective", ["oapl", "grpo"])
+@pytest.mark.parametrize("at", [5, 400, 999])                                   # first, middle and last panel
+@pytest.mark.parametrize("closed_by", ["nothing", "rollout", "offsets", "range"])
+def test_bad_token_in_several_panels(closed_by, at, objective):
+    print(closed_by, at, objective, flush=True)
+    d, V, T = 256, 1544, 1000
+    b = _custom_batch("bf16", d=d, V=V, lens=[700, 300] if closed_by == "rollout" else [300, 350, 250, 100], n_groups=2, seed=at,
+                      beta=1.0)
+    if closed_by == "range":       # a row of the first panel whose largest logit is 300 nats above all that the sweep samples
+        b.tokens = (b.tokens % 1500).to(torch.int32)
+        b.W[1520] = (b.H[10].float() * (300.0 / float((b.H[10].float() ** 2).sum()))).bfloat16()
+    ref = oracle_full(b, backward=False)["logprob"]
+    bad, off = b.tokens.clone(), b.seq_offsets.clone()
+    bad[at] = V
+    if closed_by == "offsets":
+        off[0] = 1
+    args = (b.H, b.W, bad, b.logq)
+    rest = (off, b.rewards, b.group_ids, b.n_groups)
+    _, rows, buffers = oapl.workspace_bytes_for(T, d, V, b.rewards.shape[0], b.n_groups, oapl.OAPL_BF16, True, 384)
+    assert (rows, buffers) == (384, 2)
+    if objective == "oapl":
+        res = oapl.loss_fwd_bwd(*args, *rest, b.beta, max_panel_rows=384)
+    else:
+        res = oapl.grpo_loss_fwd_bwd(*args, (b.logq + 0.01).contiguous(), *rest, max_panel_rows=384)
+    assert oapl.took_two_passes(res.workspace) == (closed_by != "nothing")
+    assert oapl.read_device_status(res.workspace) == 9
+    lp = f64(res.logprob)
+    assert np.isnan(lp[at]) and np.abs(np.delete(lp - ref, at)).max() <= 2e-2
