@@ -1124,22 +1124,30 @@ k_sweep_begin(Begin begin, const bf16_t* __restrict__ W, const bf16_t* __restric
   for (int q = 0; q < kShare / 4; ++q)
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) load(q, at.c + 16 * k, h[q][k], w[q][k]);
+  // Summed in the order of gather_logit, to the bit: lane c does the work of its lanes c, c + 16, c + 32 and c + 48, one sum each.
+  // One sum of all a lane's pieces, a chain of 64 products at d = 1024, moved the last bit of the logit, with it the reference
+  // exponent and the bf16 roundings of the whole panel row: gradients of 7749 tokens (V = 151936) 1e-4 from gather_logit's.
 #pragma unroll
   for (int q = 0; q < kShare / 4; ++q) {
-    float z = 0.f;
-    auto add = [&](const bf16x8& x, const bf16x8& y, bool there) {
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+    auto add = [&](const int m, const bf16x8& x, const bf16x8& y, bool there) {
       if (!there) return;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) z += (float)x[i] * (float)y[i];
+      for (int i = 0; i < 8; ++i) part[m] += (float)x[i] * (float)y[i];
     };
 #pragma unroll
-    for (int k = 0; k < kAhead; ++k) add(h[q][k], w[q][k], at.c + 16 * k < pieces);
-#pragma unroll 4
-    for (int e = at.c + 16 * kAhead; e < pieces; e += 16) {
-      bf16x8 a, b;
-      load(q, e, a, b);
-      add(a, b, true);
+    for (int k = 0; k < kAhead; ++k) add(k, h[q][k], w[q][k], at.c + 16 * k < pieces);
+    for (int k0 = 16 * kAhead; k0 < pieces; k0 += 64) {
+      const bool more = k0 + 32 < pieces;
+      bf16x8 a[4], b[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (k < 2 || more) load(q, at.c + k0 + 16 * k, a[k], b[k]);     // past the row's end its last piece
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (k < 2 || more) add((kAhead + k) & 3, a[k], b[k], at.c + k0 + 16 * k < pieces);
     }
+    float z = (part[0] + part[2]) + (part[1] + part[3]);
 #pragma unroll
     for (int o = 8; o > 0; o /= 2) z += __shfl_xor(z, o, 64);
     const int64_t t = n0 + row(q);

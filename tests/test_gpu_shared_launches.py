@@ -84,3 +84,21 @@ def test_bad_token_in_several_panels(closed_by, at, objective):
     assert oapl.read_device_status(res.workspace) == 9
     lp = f64(res.logprob)
     assert np.isnan(lp[at]) and np.abs(np.delete(lp - ref, at)).max() <= 2e-2
+
+
+@pytest.mark.parametrize("d,V", [(8, 300), (128, 300), (136, 700), (512, 1500), (520, 257), (1016, 1500), (1024, 1500)])
+def test_sampled_logit_is_the_gathers_to_the_bit(d, V):
+    """A sampled token's logit is summed in one order, whichever launch takes it: log-probs do not depend on the number of
+    rollouts and prompts (200 x 60 are too many for a beginning in one launch), nor on a bit of it."""
+    T = 1000
+    few = _custom_batch("bf16", d=d, V=V, lens=[600, 400], n_groups=2, seed=d, beta=1.0)
+    few.H[::3] += 20 * few.W[few.tokens[::3].long()]        # sampled tokens from unlikely to near-certain
+    n = 200
+    off = torch.arange(n + 1, device=few.H.device, dtype=torch.int64) * (T // n)
+    gid = (torch.arange(n, device=few.H.device) % 60).to(torch.int32)
+    rewards = torch.ones(n, device=few.H.device)
+    a = oapl.loss_fwd_bwd(few.H, few.W, few.tokens, few.logq, few.seq_offsets, few.rewards, few.group_ids, 2, 1.0)
+    m = oapl.loss_fwd_bwd(few.H, few.W, few.tokens, few.logq, off, rewards, gid, 60, 1.0)
+    assert oapl.read_device_status(a.workspace) == oapl.read_device_status(m.workspace) == 0
+    assert not oapl.took_two_passes(a.workspace) and not oapl.took_two_passes(m.workspace)
+    assert torch.equal(a.logprob, m.logprob)
