@@ -140,9 +140,9 @@ __device__ __forceinline__ bf16x4 lds_read_transposed(const __attribute__((addre
 // The multiplications are inline assembly because only there can an accumulator be tied to its register: given the builtin, the
 // register allocator gives results new registers and spills around them (3.5 times as slow).  The price is that the compiler
 // does not know what an MFMA leaves behind: a vector instruction may not read or overwrite its result for 8 wait states, nor
-// an MFMA read what a vector instruction wrote less than 2 before.  Fragments come straight from LDS reads, and every step
-// ends with settle(), through which all accumulators pass; tests/test_mfma_hazards.py looks for what slips through in the
-// built library.
+// an MFMA read what a vector instruction wrote less than 2 before.  The first is in the code: every step ends with settle(),
+// which all accumulators pass through.  The second holds because fragments come straight from LDS reads and zero_acc comes well
+// before the first multiplication; tests/test_mfma_hazards.py reads the built library for both.
 template <class C, bool ROWS = false, bool ATR = false>
 struct Mainloop {
   // 16-byte chunk c of LDS row `row` lives at physical chunk c ^ ((row >> 1) & 7).  The operand
@@ -294,14 +294,35 @@ struct Mainloop {
   static __device__ __forceinline__ void mfma(f32x4& c, const bf16x8 a, const bf16x8 b) {
     asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
   }
-  // The last multiplications' results are there (8 wait states) before any other instruction sees the accumulators.
+  // The last multiplications' results are there (8 wait states) before any other instruction sees the accumulators: the wait states
+  // are one statement that every accumulator goes into and comes out of, so that the order is in the data.  Several statements
+  // chained through an accumulator cost a wait state per link, which the compiler puts between them.
   static __device__ __forceinline__ void settle(f32x4 (&acc)[C::MB][C::NB]) {
     __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_nop 7" : "+v"(acc[0][0]));
-#pragma unroll
-    for (int i = 0; i < C::MB; ++i)
-#pragma unroll
-      for (int j = 0; j < C::NB; ++j) asm volatile("" : "+v"(acc[i][j]));
+#define OAPL_COLUMN(j) "+v"(acc[0][j]), "+v"(acc[1][j]), "+v"(acc[2][j]), "+v"(acc[3][j])
+#define OAPL_COLUMNS_4 OAPL_COLUMN(0), OAPL_COLUMN(1), OAPL_COLUMN(2), OAPL_COLUMN(3)
+#define OAPL_COLUMNS_8 OAPL_COLUMNS_4, OAPL_COLUMN(4), OAPL_COLUMN(5), OAPL_COLUMN(6), OAPL_COLUMN(7)
+#define OAPL_COLUMNS_9 OAPL_COLUMNS_8, OAPL_COLUMN(8)
+#define OAPL_COLUMNS_10 OAPL_COLUMNS_9, OAPL_COLUMN(9)
+#define OAPL_COLUMNS_11 OAPL_COLUMNS_10, OAPL_COLUMN(10)
+#define OAPL_COLUMNS_12 OAPL_COLUMNS_11, OAPL_COLUMN(11)
+    if constexpr (C::MB == 2 && C::NB == 4)
+      asm volatile("s_nop 7" : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]), "+v"(acc[1][0]), "+v"(acc[1][1]),
+                               "+v"(acc[1][2]), "+v"(acc[1][3]));
+    else if constexpr (C::NB == 4) asm volatile("s_nop 7" : OAPL_COLUMNS_4);
+    else if constexpr (C::NB == 8) asm volatile("s_nop 7" : OAPL_COLUMNS_8);
+    else if constexpr (C::NB == 9) asm volatile("s_nop 7" : OAPL_COLUMNS_9);
+    else if constexpr (C::NB == 10) asm volatile("s_nop 7" : OAPL_COLUMNS_10);
+    else if constexpr (C::NB == 11) asm volatile("s_nop 7" : OAPL_COLUMNS_11);
+    else asm volatile("s_nop 7" : OAPL_COLUMNS_12);
+#undef OAPL_COLUMN
+#undef OAPL_COLUMNS_4
+#undef OAPL_COLUMNS_8
+#undef OAPL_COLUMNS_9
+#undef OAPL_COLUMNS_10
+#undef OAPL_COLUMNS_11
+#undef OAPL_COLUMNS_12
+    static_assert(C::MB == 4 || (C::MB == 2 && C::NB == 4), "operands of the statement above");
   }
 
   // Multiplies the block in ring slot STAGE; with LOAD also starts the loads of block kt_load into slot LSTAGE on the way.
