@@ -76,8 +76,9 @@ def test_gpu_cases_have_the_plans_they_name(dtype, cases):
 
 
 def test_scoring_tiles_are_as_wide_as_the_tokens_need():
-    """The widths that the GPU test of the scoring tiles names."""
+    """The widths that the GPU test of the scoring tiles names, and 256 columns with loads early and spread among them."""
     width = {2: 256, 3: 320, 4: 384, 5: 288, 6: 352}       # FwdTile
-    for d in (64, 72):
+    for d in test_gpu_score_widths.HIDDEN:
         plans = ask([f"plan {T} {d} {test_gpu_score_widths.V} 1 0 0 0 -1" for T, _ in test_gpu_score_widths.CASES])
         assert [width[p["fwd_tile"]] for p in plans] == [w for _, w in test_gpu_score_widths.CASES]
+        assert {p["fwd_early"] for p in plans if p["fwd_tile"] == 2} == {0, 1}
