@@ -92,7 +92,7 @@ __device__ __forceinline__ double wave_sum(double v) {
 // through one contiguous range of logical ids, so neighbouring tiles (which
 // share operand panels) meet in the same L2.  `total` need not be a multiple
 // of 8: launch round_up(total, 8) workgroups and drop ids >= total.
-__device__ __forceinline__ int xcd_logical_id(int bid, int total) {
+__host__ __device__ __forceinline__ int xcd_logical_id(int bid, int total) {
   const int per = (total + 7) >> 3;
   return (bid & 7) * per + (bid >> 3);
 }

@@ -1458,16 +1458,14 @@ struct DwArgs {
 };
 #if defined(__HIP_DEVICE_COMPILE__)
 template <class C>
-__device__ __forceinline__ void dw_tile(const DwArgs& args, int bid, lds_char_ptr smem) {
+__device__ __forceinline__ void dw_tile(const DwArgs& args, int L /* tile */, lds_char_ptr smem) {
   const bf16_t* __restrict__ HTp = args.HTp;
   const bf16_t* __restrict__ GTp = args.GTp;
   float* __restrict__ dW = args.dW;
   const int d = args.d, V = args.V, nk = args.nk, t_n_kt = args.t_n_kt;
   const int MT = (d + C::BM - 1) / C::BM;
   const int NTl = (V + C::BN - 1) / C::BN;
-  const int total = MT * NTl;
-  const int L = xcd_round_major_id(bid);   // launched in whole rounds of 256 workgroups
-  if (L >= total) return;
+  if (L >= MT * NTl) return;
   int mt, nt;
   strip_tile<4>(L, MT, NTl, mt, nt);
   const int m0 = mt * C::BM;
@@ -1492,7 +1490,7 @@ __global__ void __launch_bounds__(C::NT) k_bwd_dw(DwArgs args, Gate gate) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   if (gate_closed(gate)) return;
-  dw_tile<C>(args, blockIdx.x, (lds_char_ptr)smem_raw);
+  dw_tile<C>(args, xcd_round_major_id(blockIdx.x), (lds_char_ptr)smem_raw);   // launched in whole rounds of 256 workgroups
 #endif
 }
 
@@ -1501,14 +1499,18 @@ __global__ void __launch_bounds__(C::NT) k_bwd_dw(DwArgs args, Gate gate) {
 // at d = 256, V = 1544 28.3 us in two launches, 21.8 in one (whole call 71.6 / 67); 700 at d = 128, V = 300 21.4 / 13.4
 // (53.9 / 48.3).  256 x 384 tiles gain nothing from it (V = 151936, d = 4096, 1003 tokens: 2166 / 2185 us; with longer dH walks
 // beside dW's tiles 2221, 300 tokens 1007 / 1286): the two kinds of tile share no operands in the L2.
+// dW's tiles (n_dw) are spread evenly over the XCDs: in rounds of 256, 32 to an XCD, as a launch of its own walks them, the few
+// tiles of such a batch all land on the first XCDs and wait there behind dH's workgroups (rounds / even, the launch: 4335 tokens at
+// d = 64, V = 3951, 34 + 31 tiles, 79 / 44 us; 8000 at d = 256, V = 8000 152 / 94; 1000 at d = 256, V = 1544 23.2 / 21.7).
+__host__ __device__ __forceinline__ int shared_dw_tile(int workgroup, int n_dw) { return xcd_logical_id(workgroup, n_dw); }
 template <class C, bool SPLIT>
-__global__ void __launch_bounds__(C::NT) k_bwd_grads(DhArgs dh, int n_dh, DwArgs dw, Gate gate) {
+__global__ void __launch_bounds__(C::NT) k_bwd_grads(DhArgs dh, int n_dh, DwArgs dw, int n_dw, Gate gate) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   lds_char_ptr smem = (lds_char_ptr)smem_raw;
   if (gate_closed(gate)) return;
   if ((int)blockIdx.x < n_dh) dh_tile<C, SPLIT, true>(dh, blockIdx.x, smem);
-  else dw_tile<C>(dw, blockIdx.x - n_dh, smem);
+  else dw_tile<C>(dw, shared_dw_tile(blockIdx.x - n_dh, n_dw), smem);
 #endif
 }
 

@@ -763,9 +763,10 @@ static void launch_dw(const DwArgs& args, hipStream_t st, Gate gate) {
 template <class C>
 static void launch_grads(const DhArgs& dh, bool split, const DwArgs& dw, hipStream_t st, Gate gate) {
   const unsigned n_dh = (unsigned)round_up(tile_count<C>(dh.d, dh.n_valid) * (split ? dh.splits : 1), 8);
-  const unsigned grid = n_dh + (unsigned)round_up(tile_count<C>(dw.d, dw.V), kNumCU);
-  if (split) k_bwd_grads<C, true><<<grid, C::NT, C::LDS_BYTES, st>>>(dh, (int)n_dh, dw, gate);
-  else k_bwd_grads<C, false><<<grid, C::NT, C::LDS_BYTES, st>>>(dh, (int)n_dh, dw, gate);
+  const int n_dw = (int)tile_count<C>(dw.d, dw.V);
+  const unsigned grid = n_dh + (unsigned)round_up(n_dw, 8);
+  if (split) k_bwd_grads<C, true><<<grid, C::NT, C::LDS_BYTES, st>>>(dh, (int)n_dh, dw, n_dw, gate);
+  else k_bwd_grads<C, false><<<grid, C::NT, C::LDS_BYTES, st>>>(dh, (int)n_dh, dw, n_dw, gate);
 }
 
 // One panel's dH and dW.  Only the tiles of the batch's last panel are split, and only it has a space for partial sums (no

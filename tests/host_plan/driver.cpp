@@ -26,6 +26,18 @@ int main() {
         if (first == 0) { first = grid; hand_over = steps == (kRollouts | kLoss) ? grid : 0; }
       });
       std::printf("grid=%u hand_over=%u\n", first, hand_over);
+    } else if (std::sscanf(line, "shared_dw %d %d", &d, &V) == 2) {
+      // dW's workgroups in the launch that they share with dH's: tiles, tiles taken once, most tiles on one of the 8 XCDs
+      const int n = (int)tile_count<CfgSmall>(d, V);
+      std::vector<int> taken(n, 0);
+      int on[8] = {}, once = 0, most = 0;
+      for (int b = 0; b < (int)round_up(n, 8); ++b) {
+        const int tile = shared_dw_tile(b, n);
+        if (tile < n) { ++taken[tile]; ++on[b & 7]; }
+      }
+      for (int t : taken) once += t == 1;
+      for (int x : on) most = x > most ? x : most;
+      std::printf("tiles=%d once=%d most=%d\n", n, once, most);
     } else if (std::sscanf(line, "plan %lld %d %d %d %d %lld %u %lld", &T, &d, &V, &dtype, &bwd, &cap, &unaligned, &have) == 8) {
       // the plan of a call of one rollout on `have` bytes (< 0: what the library asks for with panels of `cap` rows)
       if (have < 0) have = (long long)oapl_workspace_bytes_for(T, d, V, 1, 1, dtype, bwd, cap, 0, nullptr, nullptr);

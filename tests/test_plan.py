@@ -82,3 +82,10 @@ def test_scoring_tiles_are_as_wide_as_the_tokens_need():
         plans = ask([f"plan {T} {d} {test_gpu_score_widths.V} 1 0 0 0 -1" for T, _ in test_gpu_score_widths.CASES])
         assert [width[p["fwd_tile"]] for p in plans] == [w for _, w in test_gpu_score_widths.CASES]
         assert {p["fwd_early"] for p in plans if p["fwd_tile"] == 2} == {0, 1}
+
+
+@pytest.mark.parametrize("d, V", [(64, 300), (64, 3951), (256, 1544), (256, 15000), (512, 3884), (1024, 2162), (1024, 8192)])
+def test_a_shared_launch_spreads_dw_over_the_dies(d, V):
+    """Each of dW's tiles once, no XCD with more than its eighth of them."""
+    a = ask([f"shared_dw {d} {V}"])[0]
+    assert a["once"] == a["tiles"] and a["most"] == (a["tiles"] + 7) // 8
