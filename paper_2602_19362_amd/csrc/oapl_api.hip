@@ -232,6 +232,12 @@ static DhPick pick_dh(int64_t nv, int d, int nk, bool allow_small, size_t scratc
   return best;
 }
 
+// In a launch that dH shares with dW, dH's walks (nk_v k-blocks) need no split while they end with dW's (nk_t), which saves the partial
+// sums and a launch.  Whole calls split / not, us, d = 256 unless named: nk_v and nk_t 21, 27 63.7 / 60.4; 53, 107 131 / 121; 32, 32
+// (d = 512) 77 / 74; 25, 16 55.4 / 57.4; 29, 17 (d = 80) 51.6 / 57.4; 46, 24 63 / 76; 75, 71 111 / 110; 92, 77 128 / 131; 126, 113
+// 196 / 184; 144, 125 267 / 247; 166, 112 285 / 297; 235, 125 363 / 439.
+static bool dh_hides_behind_dw(int nk_v, int nk_t) { return nk_v <= nk_t + nk_t / 8 + 2; }
+
 // Tile and splits of an M x N x K fp32 contraction: the least time of the last-finishing CU in clocks.  A tile of 128 x
 // 128 takes 128 clocks per k at the matrix cores' rate, one of 64 x 64 32 (40 with the latency a single workgroup per CU
 // shows), a workgroup 2000 to start and store; partial results cost 8 bytes per element and split at 1700 bytes per
@@ -375,8 +381,7 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
       else p.dh = pick_dh(last, d, p.n_kt_v, true, part_bytes);
       p.small_dw = p.rows && T <= p.Tp && small_tiles_pay(kSmallDw, d, V, (int)((T + kPackK - 1) / kPackK));
       p.grads_fused = p.small_dw && p.dh.small;
-      // beside dW's walks, dH's need not be split while they are not much longer: no partial sums, and a launch less
-      if (p.grads_fused && p.n_kt_v <= 2 * (int)((T + kPackK - 1) / kPackK)) p.dh.splits = 1;
+      if (p.grads_fused && dh_hides_behind_dw(p.n_kt_v, (int)((T + kPackK - 1) / kPackK))) p.dh.splits = 1;
       p.off_part = p.rows && p.dh.splits > 1 ? take((size_t)p.dh.splits * last * d * 4) : p.off_Wp;
       p.small_sweep = p.rows && T <= p.Tp && !lean && small_tiles_pay(kSmallSweep, V, T, p.n_kt_d);
       p.n_vt = p.small_sweep ? (V + CfgSmall::BM - 1) / CfgSmall::BM : p.n_rt_v;

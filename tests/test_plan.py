@@ -89,3 +89,12 @@ def test_a_shared_launch_spreads_dw_over_the_dies(d, V):
     """Each of dW's tiles once, no XCD with more than its eighth of them."""
     a = ask([f"shared_dw {d} {V}"])[0]
     assert a["once"] == a["tiles"] and a["most"] == (a["tiles"] + 7) // 8
+
+
+@pytest.mark.parametrize("T, d, V, split", [
+    (1, 8, 1, False), (64, 64, 192, False), (1000, 256, 1280, False), (1000, 256, 1344, True),
+    (3000, 256, 1544, False), (2000, 512, 2000, False), (8000, 256, 9088, False), (8000, 256, 9152, True), (8000, 256, 15000, True)])
+def test_dh_is_split_where_its_walk_outlasts_dws(T, d, V, split):
+    """In the launch that both share, on both sides of the line."""
+    p = ask([f"plan {T} {d} {V} 1 1 0 0 -1"])[0]
+    assert p["rc"] == 0 and p["dh_small"] and p["small_dw"] and (p["dh_splits"] > 1) == split
