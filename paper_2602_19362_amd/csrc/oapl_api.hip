@@ -41,11 +41,14 @@ typedef TileCfg<4, 2, 4, 8, 2> CfgSample;
 typedef TileCfg<4, 1, 2, 4, 2> Cfg64;
 typedef TileCfg<4, 2, 2, 4, 2> Cfg128;
 typedef CfgSample Cfg256;
-// ... up to two token tiles wait for W to arrive: their loads go out as early as they can (scoring / sampling, loads early and
-// spread, d = 2048: 200 tokens 178 / 188, 197 / 205 us; 500 281 / 285, 318 / 323; d = 4096: 1000 994 / 988, 1102 / 1111;
-// sampling 4000 4116 / 3904).
+// ... up to two token tiles over a W that the memory-side cache cannot hold wait for it to arrive: their loads go out as early as
+// they can.  Early / spread, 200, 400 and 512 tokens: d = 4096, V = 48000 (375 MiB) sampling -5, -8, -5 %, scoring -5, -5, -4 %;
+// d = 2048, V = 100000 (391 MiB) -5, -5, -2 and -5, -4, -4 %; V = 151936 -4, -3, -1 and -4, -2, -2 %.  Where the cache holds it
+// (W the same from call to call): d = 4096, V = 3000 +8 %; d = 2048, V = 8000 +6 .. +8 %; d = 1024, V = 48000 0 .. +6 %.
 typedef TileCfg<4, 2, 4, 8, 2, 0, true> Cfg256Early;
-constexpr int64_t kEarlyTokens = 2 * Cfg256Early::BN;
+static bool early_pays(int64_t T, int V, int d) {
+  return T <= 2 * Cfg256Early::BN && (int64_t)V * d * 2 > (int64_t)256 << 20;
+}
 // Odd widths: the n-side block is 4.5 or 5.5 loads per wave, the last of them half of the waves'.  The 352-wide kernel has a
 // register too few (8 B of scratch, outside the k loop).
 typedef TileCfg<4, 2, 4, 9, 2> Cfg288;
@@ -558,7 +561,7 @@ static void launch_fwd_lse(const FwdArgs& a, bool rows, float2* partials, float*
     case kTile64: return launch_fwd_lse<Cfg64, true>(a, partials, upart, clear, st, gate);
     case kTile128: return launch_fwd_lse<Cfg128, true>(a, partials, upart, clear, st, gate);
     case kTile256:
-      if (a.T <= kEarlyTokens) return launch_fwd_lse<Cfg256Early, true>(a, partials, upart, clear, st, gate);
+      if (early_pays(a.T, a.V, a.d)) return launch_fwd_lse<Cfg256Early, true>(a, partials, upart, clear, st, gate);
       return launch_fwd_lse<Cfg256, true>(a, partials, upart, clear, st, gate);
     case kTile288: return launch_fwd_lse<Cfg288, true>(a, partials, upart, clear, st, gate);
     case kTile320: return launch_fwd_lse<Cfg320, true>(a, partials, upart, clear, st, gate);
@@ -1409,7 +1412,7 @@ int32_t oapl_sample_tokens(const void* H, const void* W, int64_t T, int32_t d, i
       if (!p.rows) launch_sample<CfgSample, false>(args, inv_t, seed, partials, st);
       else if (p.smp.tile == kTile64) launch_sample<Cfg64, true>(args, inv_t, seed, partials, st);
       else if (p.smp.tile == kTile128) launch_sample<Cfg128, true>(args, inv_t, seed, partials, st);
-      else if (T <= kEarlyTokens) launch_sample<Cfg256Early, true>(args, inv_t, seed, partials, st);
+      else if (early_pays(T, V, d)) launch_sample<Cfg256Early, true>(args, inv_t, seed, partials, st);
       else launch_sample<Cfg256, true>(args, inv_t, seed, partials, st);
     }
     OAPL_LAUNCH_CHECK();

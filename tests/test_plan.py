@@ -76,12 +76,24 @@ def test_gpu_cases_have_the_plans_they_name(dtype, cases):
 
 
 def test_scoring_tiles_are_as_wide_as_the_tokens_need():
-    """The widths that the GPU test of the scoring tiles names, and 256 columns with loads early and spread among them."""
+    """The widths that the GPU test of the scoring tiles names."""
     width = {2: 256, 3: 320, 4: 384, 5: 288, 6: 352}       # FwdTile
     for d in test_gpu_score_widths.HIDDEN:
         plans = ask([f"plan {T} {d} {test_gpu_score_widths.V} 1 0 0 0 -1" for T, _ in test_gpu_score_widths.CASES])
         assert [width[p["fwd_tile"]] for p in plans] == [w for _, w in test_gpu_score_widths.CASES]
-        assert {p["fwd_early"] for p in plans if p["fwd_tile"] == 2} == {0, 1}
+
+
+def test_loads_go_out_early_where_w_comes_from_memory():
+    """256-wide tiles of up to 512 tokens, over a W that is larger than the memory-side cache."""
+    def early(T, d, V):
+        return ask([f"plan {T} {d} {V} 1 0 0 0 -1"])[0]["fwd_early"]
+    cases = test_gpu_score_widths
+    assert [early(T, d, cases.V) for T, d in cases.EARLY] == [1, 1, 1, 0]
+    assert not any(early(T, d, cases.V) for T, _ in cases.CASES for d in cases.HIDDEN)
+    # calls on small heads: 8 .. 9 % slower with early loads
+    assert [early(T, d, V) for T, d, V in [(192, 2048, 5500), (507, 1024, 351), (410, 2048, 2100), (200, 4096, 32000)]] == [0] * 4
+    assert early(200, 4096, 32769) == early(200, 2048, 151936) == 1
+
 
 
 @pytest.mark.parametrize("d, V", [(64, 300), (64, 3951), (256, 1544), (256, 15000), (512, 3884), (1024, 2162), (1024, 8192)])
