@@ -325,6 +325,30 @@ struct Mainloop {
     static_assert(C::MB == 4 || (C::MB == 2 && C::NB == 4), "operands of the statement above");
   }
 
+  // Patches of up to eight blocks (64 and 128 tokens): all fragments of the block are requested before its first multiplication, for
+  // eight multiplications of a k-step do not cover the next one's reads (sampling 128 tokens at d = 1024, V = 8081 16.7 / 15.8 us,
+  // scoring 50 at d = 2048, V = 922 21.3 / 20.8; at V = 151936 the same; 128 x 128 tiles, sixteen blocks, +1 .. +2 us).
+  static constexpr bool kWhole = !ATR && C::MB * C::NB <= 8;
+  __device__ __forceinline__ void compute_whole(const int STAGE, lds_char_ptr smem, f32x4 (&acc)[C::MB][C::NB]) {
+    bf16x8 a[C::KSTEPS][C::MB], b[C::KSTEPS][C::NB];
+#pragma unroll
+    for (int ks = 0; ks < C::KSTEPS; ++ks) {
+      const lds_char_ptr pa = smem + STAGE * C::SLOT + (fresh(rdA0) ^ (ks << 6)), pb = smem + STAGE * C::SLOT + (fresh(rdB0) ^ (ks << 6));
+#pragma unroll
+      for (int i = 0; i < C::MB; ++i) a[ks][i] = *(const __attribute__((address_space(3))) bf16x8*)(pa + i * 16 * C::ROW_BYTES);
+#pragma unroll
+      for (int j = 0; j < C::NB; ++j) b[ks][j] = *(const __attribute__((address_space(3))) bf16x8*)(pb + j * 16 * C::ROW_BYTES);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < C::KSTEPS; ++ks)
+#pragma unroll
+      for (int i = 0; i < C::MB; ++i)
+#pragma unroll
+        for (int j = 0; j < C::NB; ++j) mfma(acc[i][j], a[ks][i], b[ks][j]);
+    settle(acc);
+  }
+
   // Multiplies the block in ring slot STAGE; with LOAD also starts the loads of block kt_load into slot LSTAGE on the way.
   // A k-step's m-side fragments stay in registers, n-side fragments come two at a time, requested one group of
   // multiplications ahead (the scheduler moves a group's reads up between the previous group's multiplications, no
@@ -332,6 +356,7 @@ struct Mainloop {
   template <bool LOAD>
   __device__ __forceinline__ void compute(const int STAGE, lds_char_ptr smem, f32x4 (&acc)[C::MB][C::NB], const int LSTAGE = 0,
                                           int kt_load = 0, int nk = 0) {
+    if constexpr (kWhole) return compute_whole(STAGE, smem, acc);
     const int v = LOAD ? load_voff(kt_load, nk) : 0;
 #pragma unroll
     for (int ks = 0; ks < C::KSTEPS; ++ks) {
