@@ -238,12 +238,14 @@ def main():
     hw_tflops = tokens_per_s * flop_unit * n_executed / 1e12
 
     # Each dense kernel executes 2*V*d flop per token it processes; over the
-    # timed steps every kernel sees every token once per step.
+    # timed steps every kernel sees every token once per step.  Small calls run dH
+    # and dW as one launch, which is recorded as k_bwd_dw.
     kernels = {}
     for name, (ms, n) in kt.items():
         if n == 0:
             continue
-        tf = flop_unit * T * args.steps / (ms * 1e-3) / 1e12
+        both = name == "k_bwd_dw" and kt["k_bwd_dh"][1] == 0
+        tf = flop_unit * (2 if both else 1) * T * args.steps / (ms * 1e-3) / 1e12
         kernels[name] = {"launches": n, "avg_ms": ms / n, "tflops": tf, "frac": tf / PEAK_BF16_TFLOPS}
     dom = max(kernels, key=lambda k: kernels[k]["avg_ms"] * kernels[k]["launches"]) if kernels else None
     roofline = None

@@ -15,10 +15,10 @@
 //
 // Two things bound the loop: the power the part may draw, which sets its clock, and the loads.  Multiplications alone, on
 // registers, run at 1.79 GHz in the 32 x 32 x 16 shape and at 2.09 GHz in the 16 x 16 x 32 one (8.39 / 7.18 ms for 12288 x
-// 4096 x 151936), which moves fewer accumulator bytes per flop.  And a wave that issues its ten loads of a block in one go waits
-// until the memory pipeline has taken them; given out two at a time between the multiplications they cost it nothing.
-// dH of 12288 tokens at d = 4096, same box: 10.82 ms 32 x 32 with the loads in one go, 10.23 ms 16 x 16, 9.75 ms
-// with the loads spread (dW 11.14 / 10.50 / 10.23, logits 11.91 / 11.41 / 10.86 ms).
+// 4096 x 151936), which moves fewer accumulator bytes per flop. And a wave that issues its ten loads of a block in one go waits
+// until the memory pipeline has taken them; given out two at a time between the multiplications they cost it nothing. dH of
+// 12288 tokens at d = 4096, same box: 10.82 ms 32 x 32 with the loads in one go, 10.23 ms 16 x 16, 9.75 ms with the loads
+// spread (dW 11.14 / 10.50 / 10.23, logits 11.91 / 11.41 / 10.86 ms).
 //
 // Operand layout in HBM ("packed"): a matrix with R rows and K columns is
 // stored as blocks of RB rows x 64 columns (RB = 256 for the m-side operand,
@@ -126,10 +126,9 @@ __device__ __forceinline__ bf16x4 lds_read_transposed(const __attribute__((addre
 // them contracted) instead of from packed copies.  A k-step of one tile is then one 128-byte piece of every row,
 // `ld` apart; rows past the matrix and columns past `ld` read as zeros because their offsets are out of the buffer's
 // range, so edges still need no padding.  Packing W costs a pass over it, more than the whole contraction of a few
-// hundred tokens (0.48 ms at d = 4096, V = 151936); the loop runs at the same rate from either layout in a single
-// round of workgroups (12288 tokens: 10.68 / 10.67 ms in place / packed at d = 4096, 5.48 / 5.47 at d = 2048), 3 .. 8 %
-// slower in place over several rounds and 12 % slower where row pieces straddle lines (12.11 / 10.79 at d = 4104);
-// rows_pay in oapl_api.hip draws the line.
+// hundred tokens (0.48 ms at d = 4096, V = 151936).  The loop itself is 0 .. 4 % slower in place where rows are whole 128-byte
+// lines (12288 tokens: sweep 11.37 / 11.28 ms in place / packed, dH, whose operand is transposed too, 10.48 / 10.06) and 12 %
+// slower where row pieces straddle lines (d = 4104); rows_pay in oapl_api.hip draws the line.
 //
 // ATR: the m-side operand is read from a row-major matrix whose ROWS are contracted (element (m, k) at p[k * ld + m]):
 // W as the dH contraction needs it, without a transposed copy.  A k-step of one tile is a 512-byte piece of 64 rows;
@@ -152,7 +151,7 @@ struct Mainloop {
 
   __amdgpu_buffer_rsrc_t ra, rb;
   int voff;                           // per-lane byte offset of this lane's chunk inside the first 8 rows a wave loads
-  int vlast;                          // ROWS: ... in the last k-block (lanes whose chunk lies past the row's end point out of range)
+  int vlast;                          // ROWS: ... in the last k-block (out of range where the chunk lies past the row's end)
   int istep;                          // ROWS: bytes from one load of a wave to the next (8 * NW rows)
   const char* at_base;                // ATR: the tile's first column in row 0 of the matrix
   int64_t at_rows;                    // ... rows (k) from there
@@ -224,12 +223,14 @@ struct Mainloop {
   // Operand tile `rt` (BM / BN rows) of a matrix of R rows, row-major or packed as ROWS says.
   __device__ __forceinline__ void set_a(const bf16_t* p, int64_t rt, int64_t R, int ld, int n_kt) {
     const int64_t left = R - rt * C::BM;
-    if (ROWS) ra = __builtin_amdgcn_make_buffer_rsrc((void*)(p + rt * C::BM * ld), 0, (int)(left < C::BM ? left : C::BM) * ld * 2, 0x00020000);
+    const int bytes = (int)(left < C::BM ? left : C::BM) * ld * 2;
+    if (ROWS) ra = __builtin_amdgcn_make_buffer_rsrc((void*)(p + rt * C::BM * ld), 0, bytes, 0x00020000);
     else set_a_packed(p, rt * C::BM, n_kt, 0);
   }
   __device__ __forceinline__ void set_b(const bf16_t* p, int64_t rt, int64_t R, int ld, int n_kt) {
     const int64_t left = R - rt * C::BN;
-    if (ROWS) rb = __builtin_amdgcn_make_buffer_rsrc((void*)(p + rt * C::BN * ld), 0, (int)(left < C::BN ? left : C::BN) * ld * 2, 0x00020000);
+    const int bytes = (int)(left < C::BN ? left : C::BN) * ld * 2;
+    if (ROWS) rb = __builtin_amdgcn_make_buffer_rsrc((void*)(p + rt * C::BN * ld), 0, bytes, 0x00020000);
     else set_b_packed(p, rt * C::BN, n_kt, 0);
   }
 
@@ -263,9 +264,10 @@ struct Mainloop {
         // output rows that are not stored
         const int kc = kt < nk ? kt : nk - 1;
         const int64_t left = at_rows - (int64_t)kc * C::BK;
-        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-            (void*)(at_base + (int64_t)kc * C::BK * at_ld2), 0, (int)(left < C::BK ? left : C::BK) * at_ld2 - at_m0 * 2, 0x00020000);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, (v < 0 ? v : at_voff) + i * (C::NW * 64 / (C::BM / 8)) * at_ld2, 0, 0, 0);
+        const int bytes = (int)(left < C::BK ? left : C::BK) * at_ld2 - at_m0 * 2;
+        const __amdgpu_buffer_rsrc_t r =
+            __builtin_amdgcn_make_buffer_rsrc((void*)(at_base + (int64_t)kc * C::BK * at_ld2), 0, bytes, 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, (v < 0 ? v : at_voff) + i * (C::NW * 512 / C::BM) * at_ld2, 0, 0, 0);
       } else {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, dst, 16, ROWS ? v + i * istep : v,
                                                  ROWS ? kt * C::ROW_BYTES : kt * C::PITCH_A + i * C::NW * 1024, 0, 0);
@@ -294,9 +296,9 @@ struct Mainloop {
   static __device__ __forceinline__ void mfma(f32x4& c, const bf16x8 a, const bf16x8 b) {
     asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
   }
-  // The last multiplications' results are there (8 wait states) before any other instruction sees the accumulators: the wait states
-  // are one statement that every accumulator goes into and comes out of, so that the order is in the data.  Several statements
-  // chained through an accumulator cost a wait state per link, which the compiler puts between them.
+  // The last multiplications' results are there (8 wait states) before any other instruction sees the accumulators: the wait
+  // states are one statement that every accumulator goes into and comes out of, so that the order is in the data. Several
+  // statements chained through an accumulator cost a wait state per link, which the compiler puts between them.
   static __device__ __forceinline__ void settle(f32x4 (&acc)[C::MB][C::NB]) {
     __builtin_amdgcn_sched_barrier(0);
 #define OAPL_COLUMN(j) "+v"(acc[0][j]), "+v"(acc[1][j]), "+v"(acc[2][j]), "+v"(acc[3][j])
@@ -307,8 +309,8 @@ struct Mainloop {
 #define OAPL_COLUMNS_11 OAPL_COLUMNS_10, OAPL_COLUMN(10)
 #define OAPL_COLUMNS_12 OAPL_COLUMNS_11, OAPL_COLUMN(11)
     if constexpr (C::MB == 2 && C::NB == 4)
-      asm volatile("s_nop 7" : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]), "+v"(acc[1][0]), "+v"(acc[1][1]),
-                               "+v"(acc[1][2]), "+v"(acc[1][3]));
+      asm volatile("s_nop 7" : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]),
+                               "+v"(acc[1][0]), "+v"(acc[1][1]), "+v"(acc[1][2]), "+v"(acc[1][3]));
     else if constexpr (C::NB == 4) asm volatile("s_nop 7" : OAPL_COLUMNS_4);
     else if constexpr (C::NB == 8) asm volatile("s_nop 7" : OAPL_COLUMNS_8);
     else if constexpr (C::NB == 9) asm volatile("s_nop 7" : OAPL_COLUMNS_9);
@@ -325,15 +327,17 @@ struct Mainloop {
     static_assert(C::MB == 4 || (C::MB == 2 && C::NB == 4), "operands of the statement above");
   }
 
-  // Patches of up to eight blocks (64 and 128 tokens): all fragments of the block are requested before its first multiplication, for
-  // eight multiplications of a k-step do not cover the next one's reads (sampling 128 tokens at d = 1024, V = 8081 16.7 / 15.8 us,
-  // scoring 50 at d = 2048, V = 922 21.3 / 20.8; at V = 151936 the same; 128 x 128 tiles, sixteen blocks, +1 .. +2 us).
+  // Patches of up to eight blocks (64 and 128 tokens): all fragments of the block are requested before its first
+  // multiplication, for eight multiplications of a k-step do not cover the next one's reads (sampling 128 tokens at d = 1024, V
+  // = 8081 16.7 / 15.8 us, scoring 50 at d = 2048, V = 922 21.3 / 20.8; at V = 151936 the same; 128 x 128 tiles, sixteen
+  // blocks, +1 .. +2 us).
   static constexpr bool kWhole = !ATR && C::MB * C::NB <= 8;
   __device__ __forceinline__ void compute_whole(const int STAGE, lds_char_ptr smem, f32x4 (&acc)[C::MB][C::NB]) {
     bf16x8 a[C::KSTEPS][C::MB], b[C::KSTEPS][C::NB];
 #pragma unroll
     for (int ks = 0; ks < C::KSTEPS; ++ks) {
-      const lds_char_ptr pa = smem + STAGE * C::SLOT + (fresh(rdA0) ^ (ks << 6)), pb = smem + STAGE * C::SLOT + (fresh(rdB0) ^ (ks << 6));
+      const lds_char_ptr pa = smem + STAGE * C::SLOT + (fresh(rdA0) ^ (ks << 6));
+      const lds_char_ptr pb = smem + STAGE * C::SLOT + (fresh(rdB0) ^ (ks << 6));
 #pragma unroll
       for (int i = 0; i < C::MB; ++i) a[ks][i] = *(const __attribute__((address_space(3))) bf16x8*)(pa + i * 16 * C::ROW_BYTES);
 #pragma unroll
@@ -379,7 +383,8 @@ struct Mainloop {
         bf16x8 b[2];
 #pragma unroll
         for (int j = 0; j < w; ++j)
-          b[j] = *(const __attribute__((address_space(3))) bf16x8*)(smem + STAGE * C::SLOT + rb_ks + (j0 + j) * 16 * C::ROW_BYTES);
+          b[j] = *(const __attribute__((address_space(3))) bf16x8*)(smem + STAGE * C::SLOT + rb_ks +
+                                                                    (j0 + j) * 16 * C::ROW_BYTES);
         const int group = ks * ((C::NB + 1) / 2) + j0 / 2;
         if (LOAD && group > 0) {
           issue_one(LSTAGE, smem, v, kt_load, nk, 2 * (group - 1));
@@ -397,7 +402,8 @@ struct Mainloop {
 
   // Ring of four (128 x 128 tiles that have a CU to themselves, the reference pass): such a workgroup waits for the
   // latency of its loads as much as for operand bytes, so three blocks are in flight instead of one.  Loss calls of 100
-  // tokens, ring of two / four: d = 4096, V = 32000 419 / 380 us (dH 62 / 49), V = 8192 174 / 160, V = 151936 1267 / 1241.
+  // tokens, ring of two / four: d = 4096, V = 32000 361 / 349 us, V = 8192 152 / 149, V = 151936 1168 / 1169; 1000 tokens at d
+  // = 256, V = 1544 and 300 at d = 1024, V = 8192 the same.
   //
   // One k-block of the pipeline in ring slot S (a literal at the call sites): wait until the block's
   // loads have landed, barrier (which also tells that every wave is done with the other slot),
@@ -444,9 +450,10 @@ struct Mainloop {
   }
 
   // k-blocks [k0, k1) of a tile with nk k-blocks in all (k0 a multiple of NS, after start() or an earlier steps()).
-  // PRELOADED (ring of two, k0 = 0): k-block 1 was issued beforehand as well (start_preload()), by a caller whose work between two tiles leaves the LDS alone.  The first block then issues
-  // nothing.  It waits for both blocks: waiting for the first alone (vmcnt = the second block's loads, and a bare
-  // s_barrier, since __syncthreads() waits for every outstanding load itself) measured no different.
+  // PRELOADED (ring of two, k0 = 0): k-block 1 was issued beforehand as well (start_preload()), by a caller whose work between
+  // two tiles leaves the LDS alone. The first block then issues nothing. It waits for both blocks: waiting for the first alone
+  // (vmcnt = the second block's loads, and a bare s_barrier, since __syncthreads() waits for every outstanding load itself)
+  // measured no different.
   template <bool PRELOADED = false>
   __device__ __forceinline__ void steps(lds_char_ptr smem, int k0, int k1, int nk, f32x4 (&acc)[C::MB][C::NB]) {
     int kt = k0;
@@ -549,7 +556,8 @@ __device__ __forceinline__ float reduce4(const float (&x)[4], Op op) {
 __device__ __forceinline__ void spread4(float y, float (&x)[4]) {
   const uint32_t u = __float_as_uint(y);
   const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);      // groups 0, 0, 2, 2 and 1, 1, 3, 3
-  const auto e = __builtin_amdgcn_permlane32_swap(r[0], r[0], false, false), o = __builtin_amdgcn_permlane32_swap(r[1], r[1], false, false);
+  const auto e = __builtin_amdgcn_permlane32_swap(r[0], r[0], false, false);
+  const auto o = __builtin_amdgcn_permlane32_swap(r[1], r[1], false, false);
   x[0] = __uint_as_float(e[0]);
   x[1] = __uint_as_float(o[0]);
   x[2] = __uint_as_float(e[1]);
@@ -607,7 +615,8 @@ __device__ __forceinline__ void store_nm(lds_char_ptr smem, bf16_t* out, int64_t
 // `dst` is the destination matrix, n_kt its strip pitch in k-blocks, n0 the tile's first row, kb0 the first
 // k-block (m0 / 64).
 template <class C>
-__device__ __forceinline__ void store_nm_packed_direct(const uint32_t (&pk)[C::MB][C::NB][2], bf16_t* dst, int n_kt, int64_t n0, int kb0) {
+__device__ __forceinline__ void store_nm_packed_direct(const uint32_t (&pk)[C::MB][C::NB][2], bf16_t* dst, int n_kt, int64_t n0,
+                                                       int kb0) {
   static_assert(C::WROWS == kPackK, "a wave row spans exactly one packed k-block");
   const Lane<C> at;
   // the piece of block rows 2q, 2q + 1 sits at byte 64 q + 32 (g & 1) + 16 (g >> 1) of its row's 128-byte line
@@ -666,8 +675,8 @@ __device__ __forceinline__ void store_mn_pk_packed(lds_char_ptr smem, bf16_t* ba
 // Both packed copies of a tile: rows = vocabulary (m) with k = tokens (n), through LDS, two MFMA block rows of every wave at a
 // time, then rows = tokens with k = vocabulary, whose stores drain after the workgroup has gone.
 template <class C>
-__device__ __forceinline__ void store_both_copies(lds_char_ptr smem, const uint32_t (&pk)[C::MB][C::NB][2], bf16_t* Gp, int g_n_kt,
-                                                  bf16_t* GTp, int gt_n_kt, int m0, int64_t n0) {
+__device__ __forceinline__ void store_both_copies(lds_char_ptr smem, const uint32_t (&pk)[C::MB][C::NB][2], bf16_t* Gp,
+                                                  int g_n_kt, bf16_t* GTp, int gt_n_kt, int m0, int64_t n0) {
   static_assert(C::STAGE_MN <= C::LDS_BYTES, "staging chunk must fit");
 #pragma unroll
   for (int q = 0; q < C::MN_CHUNKS; ++q) {
@@ -688,8 +697,8 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
 // SN tiles along n, m fastest within a strip row, so that the ~32 workgroups
 // resident on one XCD form a (32 / SN) x SN patch and share operand panels.
 // The kernels use SN = 4: an 8 x 4 patch of 256 x 384 tiles needs 8 x 32 KB +
-// 4 x 48 KB of operands per k-step, the least for 32 tiles (measured +1.5 %
-// over 4 x 8, and 8 % over 2 x 16).
+// 4 x 48 KB of operands per k-step, the least for 32 tiles (sweep / dH / dW of 12288 tokens at d = 4096, V = 151936: 11.28 /
+// 10.06 / 10.45 ms; SN = 8 11.31 / 10.22 / 10.57; SN = 2 11.60 / 10.10 / 10.53).
 __device__ __forceinline__ void strip_tile(const int SN, int L, int MT, int NTl, int& mt, int& nt) {
   const int per_strip = SN * MT;
   const int strip = L / per_strip;
@@ -1040,8 +1049,8 @@ __global__ void __launch_bounds__(256) k_pack_transposed(PackTransposed p, Gate 
 // Entries outside the valid ranges are written as zeros (whole tiles are stored).
 //   A = W (M = vocabulary), B = H from the panel's first token (N = tokens), packed or in place.
 // ---------------------------------------------------------------------------
-// In a small call the transposed rows that the next launch wants come along (`n_pack` workgroups in front, two blocks each): the
-// recompute is closed in nearly every call, and a launch of its own that does nothing costs 3 us.
+// In a small call the transposed rows that the next launch wants come along (`n_pack` workgroups in front, two blocks each):
+// the recompute is closed in nearly every call, and a launch of its own that does nothing costs 3 us.
 template <class C, bool ROWS>
 __global__ void __launch_bounds__(C::NT)
 k_bwd_dz(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H_panel, int V, int64_t n_valid, int d, int n_kt,
@@ -1170,9 +1179,10 @@ k_sweep_begin(Begin begin, const bf16_t* __restrict__ W, const bf16_t* __restric
   for (int q = 0; q < kShare / 4; ++q)
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) load(q, at.c + 16 * k, h[q][k], w[q][k]);
-  // Summed in the order of gather_logit, to the bit: lane c does the work of its lanes c, c + 16, c + 32 and c + 48, one sum each.
-  // One sum of all a lane's pieces, a chain of 64 products at d = 1024, moved the last bit of the logit, with it the reference
-  // exponent and the bf16 roundings of the whole panel row: gradients of 7749 tokens (V = 151936) 1e-4 from gather_logit's.
+  // Summed in the order of gather_logit, to the bit: lane c does the work of its lanes c, c + 16, c + 32 and c + 48, one sum
+  // each. One sum of all a lane's pieces, a chain of 64 products at d = 1024, moved the last bit of the logit, with it the
+  // reference exponent and the bf16 roundings of the whole panel row: gradients of 7749 tokens (V = 151936) 1e-4 from
+  // gather_logit's.
 #pragma unroll
   for (int q = 0; q < kShare / 4; ++q) {
     float part[4] = {0.f, 0.f, 0.f, 0.f};
@@ -1519,15 +1529,17 @@ __global__ void __launch_bounds__(C::NT) k_bwd_dw(DwArgs args, Gate gate) {
 #endif
 }
 
-// Steps 2 and 3 of a small batch (one panel, 128 x 128 tiles, operands in place) in one launch: the first n_dh (a multiple of
-// 8) workgroups are dH's, the others dW's.  Neither fills the chip and they do not depend on each other: 1000 tokens
-// at d = 256, V = 1544 28.3 us in two launches, 21.8 in one (whole call 71.6 / 67); 700 at d = 128, V = 300 21.4 / 13.4
-// (53.9 / 48.3).  256 x 384 tiles gain nothing from it (V = 151936, d = 4096, 1003 tokens: 2166 / 2185 us; with longer dH walks
-// beside dW's tiles 2221, 300 tokens 1007 / 1286): the two kinds of tile share no operands in the L2.
-// dW's tiles (n_dw) are spread evenly over the XCDs: in rounds of 256, 32 to an XCD, as a launch of its own walks them, the few
-// tiles of such a batch all land on the first XCDs and wait there behind dH's workgroups (rounds / even, the launch: 4335 tokens at
-// d = 64, V = 3951, 34 + 31 tiles, 79 / 44 us; 8000 at d = 256, V = 8000 152 / 94; 1000 at d = 256, V = 1544 23.2 / 21.7).
+// dW's tiles (n_dw) in the launch that it shares with dH (k_bwd_grads) are spread evenly over the XCDs: in rounds of 256, 32 to
+// an XCD, as a launch of its own walks them, the few tiles of such a batch all land on the first XCDs and wait there behind
+// dH's workgroups (rounds / even, the launch: 4335 tokens at d = 64, V = 3951, 34 + 31 tiles, 79 / 44 us; 8000 at d = 256,
+// V = 8000 152 / 94; 1000 at d = 256, V = 1544 23.2 / 21.7).
 __host__ __device__ __forceinline__ int shared_dw_tile(int workgroup, int n_dw) { return xcd_logical_id(workgroup, n_dw); }
+
+// Steps 2 and 3 of a small batch (one panel, 128 x 128 tiles, operands in place) in one launch: the first n_dh (a multiple of
+// 8) workgroups are dH's, the others dW's.  Neither fills the chip and they do not depend on each other: whole calls in two
+// launches / one, 1000 tokens at d = 256, V = 1544 66 / 53 us; 700 at d = 128, V = 300 48 / 39; 1000 at d = 1024, V = 8192
+// 118 / 106.  256 x 384 tiles gain nothing from it (V = 151936, d = 4096, 1003 tokens: 2166 / 2185 us; with longer dH walks
+// beside dW's tiles 2221, 300 tokens 1007 / 1286): the two kinds of tile share no operands in the L2.
 template <class C, bool SPLIT>
 __global__ void __launch_bounds__(C::NT) k_bwd_grads(DhArgs dh, int n_dh, DwArgs dw, int n_dw, Gate gate) {
 #if defined(__HIP_DEVICE_COMPILE__)

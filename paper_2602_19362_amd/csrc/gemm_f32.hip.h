@@ -33,7 +33,8 @@ struct F32Cfg {
   static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, BK = BK_;
   static constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
   static_assert(WM * WN == 4 && BK % 8 == 0, "256 threads, whole groups of eight k");
-  // workgroups that the registers must leave room for on a CU: as many as the LDS does
+  // workgroups that the registers of a shared launch must leave room for on a CU: of the large tile four, as many as the LDS
+  // does (left alone it takes 130 registers and leaves room for three); the small one's 81 leave that room unasked
   static constexpr int kPerCU = BM * BN >= 128 * 128 ? 4 : 2;
 };
 typedef F32Cfg<2, 2, 2, 2, 16> F32Large;   // 128 x 128, 40 KB of LDS
@@ -98,8 +99,9 @@ constexpr int larger(int a, int b) { return a > b ? a : b; }
 // Tile at block (bx, by, bz): x and y = row and column tiles in the order the epilogue names, z = one of `nz` splits of k in
 // whole stages.
 template <class C, bool A_KC, bool B_KC, class Epi>
-__device__ __forceinline__ void gemm_f32_tile(const F32Operand& A, const F32Operand& B, int64_t M, int64_t N, int64_t K, const Epi& epi,
-                                              unsigned bx, unsigned by, unsigned bz, unsigned nz, float* lds_a, float* lds_b) {
+__device__ __forceinline__ void gemm_f32_tile(const F32Operand& A, const F32Operand& B, int64_t M, int64_t N, int64_t K,
+                                              const Epi& epi, unsigned bx, unsigned by, unsigned bz, unsigned nz,
+                                              float* lds_a, float* lds_b) {
   typedef F32Stage<C::BM, C::BK, A_KC> SA;
   typedef F32Stage<C::BN, C::BK, B_KC> SB;
   float (*As)[SA::FLOATS] = (float (*)[SA::FLOATS])lds_a;

@@ -34,17 +34,17 @@ typedef TileCfg<4, 2, 4, 8, 2> CfgSample;
 
 // Tiles of the scoring and sampling kernels over row-major operands.  A call of few tokens pays for every padded
 // token column and is bound by reading W once; a call of many is bound by operand delivery, which wants the largest
-// tile.  128 x 64 (48 KB of LDS, three workgroups per CU to keep W streaming through each other's barriers) reads W at
-// 6.0 TB/s for up to 64 tokens at d = 4096, where 256 x 64 reaches 5.0 and the 256 x 256 tile on 64 workgroups 1.1;
-// 128 x 128 (two per CU) serves up to 128 tokens in 260 us against 302 us.  From there on a tile is 256 tall, one per CU,
+// tile.  128 x 64 (48 KB of LDS, three workgroups per CU to keep W streaming through each other's barriers) reads W at 5.8 TB/s
+// for up to 64 tokens at d = 4096, V = 151936: sampling 215 us, in tiles of 256 x 64 249, of 128 x 128 255, of 256 x 256 307.
+// 128 x 128 (two per CU) serves up to 128 tokens in 277 us against 325.  From there on a tile is 256 tall, one per CU,
 // and its width follows from the token count (pick_tile).
 typedef TileCfg<4, 1, 2, 4, 2> Cfg64;
 typedef TileCfg<4, 2, 2, 4, 2> Cfg128;
 typedef CfgSample Cfg256;
-// ... up to two token tiles over a W that the memory-side cache cannot hold wait for it to arrive: their loads go out as early as
-// they can.  Early / spread, 200, 400 and 512 tokens: d = 4096, V = 48000 (375 MiB) sampling -5, -8, -5 %, scoring -5, -5, -4 %;
-// d = 2048, V = 100000 (391 MiB) -5, -5, -2 and -5, -4, -4 %; V = 151936 -4, -3, -1 and -4, -2, -2 %.  Where the cache holds it
-// (W the same from call to call): d = 4096, V = 3000 +8 %; d = 2048, V = 8000 +6 .. +8 %; d = 1024, V = 48000 0 .. +6 %.
+// ... up to two token tiles over a W that the memory-side cache cannot hold wait for it to arrive: their loads go out as early
+// as they can. Early / spread, 200, 400 and 512 tokens: d = 4096, V = 48000 (375 MiB) sampling -5, -8, -5 %, scoring -5, -5, -4
+// %; d = 2048, V = 100000 (391 MiB) -5, -5, -2 and -5, -4, -4 %; V = 151936 -4, -3, -1 and -4, -2, -2 %. Where the cache holds
+// it (W the same from call to call): d = 4096, V = 3000 +8 %; d = 2048, V = 8000 +6 .. +8 %; d = 1024, V = 48000 0 .. +6 %.
 typedef TileCfg<4, 2, 4, 8, 2, 0, true> Cfg256Early;
 static bool early_pays(int64_t T, int V, int d) {
   return T <= 2 * Cfg256Early::BN && (int64_t)V * d * 2 > (int64_t)256 << 20;
@@ -130,11 +130,11 @@ static int64_t panel_cap(int dtype, int64_t max_panel_rows) {
 }
 
 // Where reading W and H in place beats packing them first.  Packing moves 4 bytes per weight at ~5.3 TB/s (0.48 ms at
-// d = 4096, V = 151936).  It gains the main loop 3 .. 5 % where rows are whole 128-byte lines (20000 tokens at d = 4096:
-// 18.3 ms packed, 19.2 in place; 8 % at d = 5120) and 10 .. 13 % where they are not (d = 4104): it breaks even near
-// 11000 tokens in the one case and 4500 in the other.  With gradients there are two copies of W to save (W^T: 0.46 ms)
-// and two contractions that run slower in place (dH of 12288 tokens 11.2 ms against 10.6): about the same line.
-// A loss call of 1003 tokens at d = 4096 takes 4.65 ms packed, 3.64 in place.
+// d = 4096, V = 151936; with gradients there are two copies of W to save, W^T: 0.46 ms). Scoring in place / packed, ms: rows of
+// whole 128-byte lines, d = 4096, 4000 tokens 3.54 / 4.03, 8000 7.15 / 7.45, 11000 9.91 / 10.13, 20000 17.93 / 17.94; others, d
+// = 4104, 2000 2.15 / 2.47, 4000 4.04 / 4.09, 6000 6.23 / 5.77. Loss calls at d = 4096: 1003 tokens 3.47 / 4.42, 4000 11.86 /
+// 12.70, 8000 22.4 / 23.0, 12288 32.5 / 33.0; d = 4104, 4000 12.7 / 13.1. (Between 8192 and about 20000 tokens packing costs
+// whole-line rows up to 2 %: the line is older than the present main loop.)
 static bool rows_pay(int64_t T, int d) {
   if (d % kPackK != 0) return T <= 4096;
   return T <= 8192;
@@ -143,8 +143,8 @@ static bool rows_pay(int64_t T, int d) {
 // Vocabulary splits of the streaming kernels for a tile: one workgroup per (token tile, split), one workgroup per CU
 // at a time.  Takes the count with the least time in the last-finishing CU: rounds of workgroups x tiles each walks,
 // plus a twentieth of a tile per walk.  Short walks cost next to nothing (20000 tokens at d = 4096, patches of eight
-// token tiles: 18.3 / 18.5 / 18.6 ms for walks of 3 / 2 / 1 tiles) while the long ones of neighbouring workgroups
-// drift apart and share less in the L2 (19.6 ms for walks of 26), so the count is free to fill the last round.
+// token tiles: 18.1 / 18.2 / 18.6 ms for walks of 3 / 2 / 1 tiles) while the long ones of neighbouring workgroups
+// drift apart and share less in the L2 (18.4 / 19.0 ms for walks of 6 / 26), so the count is free to fill the last round.
 template <class C>
 static TilePick pick_splits(FwdTile tile, int64_t T, int V, int max_splits, double tile_cost = 1.0,
                             double* time_out = nullptr) {
@@ -164,9 +164,9 @@ static TilePick pick_splits(FwdTile tile, int64_t T, int V, int max_splits, doub
 
 // Tile and splits over row-major operands.  Up to 128 tokens the call is bound by reading W and every 128-row
 // vocabulary tile is a workgroup of its own.  Beyond, the time of one 256-row tile at d = 4096 is in the ratio of 105 / 115.5 /
-// 126 / 138 / 150 for 256 / 288 / 320 / 352 / 384 columns (it scales with d): the wide tile is the cheapest per column, a narrower one
-// pads fewer columns.  256, 320 and 384 alone / all five: 350 tokens at d = 4096 433 / 403 us, 700 725 / 674, 777 825 / 779, 1003 996 /
-// 941, 1400 1412 / 1292, 2500 and more the same.
+// 126 / 138 / 150 for 256 / 288 / 320 / 352 / 384 columns (it scales with d): the wide tile is the cheapest per column, a
+// narrower one pads fewer columns. 256, 320 and 384 alone / all five: 350 tokens at d = 4096 433 / 403 us, 700 725 / 674, 777
+// 825 / 779, 1003 996 / 941, 1400 1412 / 1292, 2500 and more the same.
 static TilePick pick_tile(int64_t T, int V, int max_splits, bool scoring) {
   const int MT128 = (V + 127) / 128;
   const int small = MT128 < max_splits ? MT128 : max_splits;
@@ -193,10 +193,13 @@ static TilePick pick_fwd(bool rows, int64_t T, int V, int max_splits) {
 // some k-blocks each for filling the ring and the epilogue.  128 x 128 tiles run two per CU; what a pair of their k-blocks
 // costs depends on how the kernel's operands reach the LDS (packed blocks least, a transposed read of W most):
 //   d = 4096, small / large tiles   V = 8192, 1000 tokens   V = 32000, 1000   V = 151936, 300 / 1000
-//   sweep                            73 / 121 us             309 / 293         528 / 470, 1368 / 1132
-//   dH                               90 /  75                392 / 238         588 / 355, 1381 / 1048
-//   dW                               77 / 100                381 / 302         874 / 700, 1877 / 1284
-// and at d = 256, V = 1544, 1000 tokens 14 / 25, 11 / 20, 17 / 36 us.
+//   sweep                            67 / 138 us             304 / 294         512 / 483, 1330 / 1103
+//   dH                               93 /  77                316 / 234         577 / 352, 1383 / 1034
+//   dW                               77 /  97                350 / 284         877 / 694, 1710 / 1223
+// and at d = 256, V = 1544, 1000 tokens 14 / 29, 12 / 22, 17 / 36 us (launches of their own; dH and dW of small tiles share
+// one, 16 us). Against the best of five fixed choices over 47 shapes the chosen call is within 4 % but for four: 1000 tokens at
+// d = 1024, V = 32000 (339 us, all in small tiles 294), 3000 at d = 4096, V = 1544 (240 / 223) and V = 8192 (668 / 625), 100 at
+// d = 4096, V = 32000 (354 / 332): the rates do not know the launch that dH and dW of small tiles share.
 struct SmallRate {
   double pair, alone;   // a k-block of two workgroups of one CU; of one that has it to itself
   int start;
@@ -218,8 +221,8 @@ static bool small_tiles_pay(const SmallRate& r, int64_t M, int64_t N, int nk) {
 
 // Tile and workgroups per tile of the dH contraction of nv tokens.  Its tiles are few and long (`nk` k-blocks each): the
 // pick minimises their time plus the partial sums' way through memory (8 bytes per element and split).  Whole loss calls at
-// V = 151936, one workgroup per tile / the count chosen: 1003 tokens, d = 4096 7.79 / 4.65 ms (five splits);
-// 6007 tokens, d = 2048 11.23 / 9.72 ms (two); 30011 tokens at d = 5120, whose last panel has 1211, 114.2 / 111.4 ms.
+// V = 151936, one workgroup per tile / the count chosen: 1003 tokens, d = 4096 3.99 / 3.47 ms (five splits);
+// 6007 tokens, d = 2048 10.77 / 8.80 ms (two); 30011 tokens at d = 5120, whose last panel has 1211, 107.3 / 104.6 ms.
 static DhPick pick_dh(int64_t nv, int d, int nk, bool allow_small, size_t scratch) {
   DhPick best;
   double best_time = 1e300;
@@ -235,10 +238,10 @@ static DhPick pick_dh(int64_t nv, int d, int nk, bool allow_small, size_t scratc
   return best;
 }
 
-// In a launch that dH shares with dW, dH's walks (nk_v k-blocks) need no split while they end with dW's (nk_t), which saves the partial
-// sums and a launch.  Whole calls split / not, us, d = 256 unless named: nk_v and nk_t 21, 27 63.7 / 60.4; 53, 107 131 / 121; 32, 32
-// (d = 512) 77 / 74; 25, 16 55.4 / 57.4; 29, 17 (d = 80) 51.6 / 57.4; 46, 24 63 / 76; 75, 71 111 / 110; 92, 77 128 / 131; 126, 113
-// 196 / 184; 144, 125 267 / 247; 166, 112 285 / 297; 235, 125 363 / 439.
+// In a launch that dH shares with dW, dH's walks (nk_v k-blocks) need no split while they end with dW's (nk_t), which saves the
+// partial sums and a launch. Whole calls split / not, us, d = 256 unless named: nk_v and nk_t 21, 27 63.7 / 60.4; 53, 107 131 /
+// 121; 32, 32 (d = 512) 77 / 74; 25, 16 55.4 / 57.4; 29, 17 (d = 80) 51.6 / 57.4; 46, 24 63 / 76; 75, 71 111 / 110; 92, 77 128
+// / 131; 126, 113 196 / 184; 144, 125 267 / 247; 166, 112 285 / 297; 235, 125 363 / 439.
 static bool dh_hides_behind_dw(int nk_v, int nk_t) { return nk_v <= nk_t + nk_t / 8 + 2; }
 
 // Tile and splits of an M x N x K fp32 contraction: the least time of the last-finishing CU in clocks.  A tile of 128 x
@@ -265,9 +268,9 @@ static int64_t f32_groups(const F32Pick& pick, int64_t M, int64_t N) {
   const int64_t tile = pick.large ? F32Large::BM : F32Small::BM;
   return ((M + tile - 1) / tile) * ((N + tile - 1) / tile) * pick.splits;
 }
-// fp32 gradient contractions share a launch up to this many workgroups, three per CU, which is what the registers of 128 x 128
-// tiles leave room for.  Whole calls, two launches / one: 256 tokens at d = 64, V = 1024 (128 workgroups) 40 / 37 us; 700, 300,
-// 3000 (455) 104 / 96; 1501, 768, 8192 (1272) 585 / 609.
+// fp32 gradient contractions share a launch up to this many workgroups.  Whole calls, two launches / one: 256 tokens at d = 64,
+// V = 1024 (128 workgroups) 40 / 37 us; 700, 300, 3000 (455) 104 / 96; 1501, 768, 8192 (1272) 585 / 609. Where between the last
+// two the line lies has not been measured.
 constexpr int64_t kSharedGroupsF32 = 3 * kNumCU;
 
 // bf16 operands that are not 16-byte aligned.  The 16-byte direct-to-LDS loads of the in-place kernels want that; the packing
@@ -501,7 +504,8 @@ static bool prepare_kernels() {
     ok = allow_fwd<Cfg64, true>() && allow_fwd<Cfg128, true>() && allow_fwd<Cfg256, true>() && allow_fwd<Cfg256Early, true>() &&
          allow_fwd<Cfg288, true>() && allow_fwd<Cfg320, true>() && allow_fwd<Cfg352, true>() &&
          allow_fwd<Cfg, true>() && allow_fwd<Cfg, false>() && allow_sample<Cfg64, true>() &&
-         allow_sample<Cfg128, true>() && allow_sample<Cfg256, true>() && allow_sample<Cfg256Early, true>() && allow_sample<CfgSample, false>() &&
+         allow_sample<Cfg128, true>() && allow_sample<Cfg256, true>() && allow_sample<Cfg256Early, true>() &&
+         allow_sample<CfgSample, false>() &&
          allow_big_lds(k_fwd_lse<CfgRef, false, true>, CfgRef::LDS_BYTES) &&
          allow_big_lds(k_fwd_lse<CfgRef, false, false>, CfgRef::LDS_BYTES) &&
          allow_big_lds(k_sweep_begin<CfgRef, OaplBegin>, CfgRef::LDS_BYTES) &&
@@ -543,8 +547,8 @@ static void launch_fwd_lse_kernel(const FwdArgs& a, float2* partials, float* upa
   const int64_t total = (a.T + C::BN - 1) / C::BN * a.pick.splits;
   const unsigned grid = (unsigned)round_up(total, 8);
   // token tiles per XCD patch: eight while a token tile's H strip is at most 3 MiB (384 columns: d <= 4096), else four.
-  // 20000 tokens at d = 4096, walks of 3 tiles: 21.4 / 18.9 / 18.3 / 18.6 ms for patches of 1 / 4 / 8 / 16; 30000 at
-  // d = 5120: 40.4 / 35.8 / 37.3 / 37.2; at d <= 2048 four and eight are equal.
+  // 20000 tokens at d = 4096, walks of 3 tiles: 20.2 / 18.2 / 18.1 / 18.4 ms for patches of 1 / 4 / 8 / 16; 30000 at
+  // d = 5120: 36.7 / 34.5 / 35.5 / 35.7; 20000 at d = 2048 10.19 / 9.15 / 9.18 / 9.28.
   const int patch_tiles = (size_t)a.n_kt * C::STAGE_B <= ((size_t)3 << 20) ? 8 : 4;
   k_fwd_lse<C, ENT, ROWS><<<grid, C::NT, C::LDS_BYTES, st>>>(a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, patch_tiles,
                                                            partials, upart, clear, gate);
@@ -604,13 +608,14 @@ static void launch_scores_f32(const Plan& p, const Begin& begin, const void* H, 
                               const TokenInit& init, const EpiLseF32& epi, hipStream_t st) {
   const F32Operand A = f32_operand(W, p.d), B = f32_operand(H, p.d);
   const unsigned grid = 1 + grid1d(p.T, 4) + grid1d(p.V, C::BM) * grid1d(p.T, C::BN);
-  if (A.vec && B.vec) k_scores_f32<C, EpiLseF32, Begin, 4><<<grid, 256, 0, st>>>(begin, tokens, zy, init, A, B, p.V, p.T, p.d, epi);
+  if (A.vec && B.vec)
+    k_scores_f32<C, EpiLseF32, Begin, 4><<<grid, 256, 0, st>>>(begin, tokens, zy, init, A, B, p.V, p.T, p.d, epi);
   else k_scores_f32<C, EpiLseF32, Begin, 1><<<grid, 256, 0, st>>>(begin, tokens, zy, init, A, B, p.V, p.T, p.d, epi);
 }
 
 // out[m][n] (+)= sum_k A(m, k) B(n, k), B and (unless A_KC) A with their rows contiguous.
-static F32Contraction contraction_f32(const F32Pick& pick, const F32Operand& A, const F32Operand& B, int64_t M, int64_t N, int64_t K,
-                                      float* out) {
+static F32Contraction contraction_f32(const F32Pick& pick, const F32Operand& A, const F32Operand& B, int64_t M, int64_t N,
+                                      int64_t K, float* out) {
   const int tile = pick.large ? F32Large::BM : F32Small::BM;
   return F32Contraction{A, B, M, N, K, out, (int)grid1d(N, tile), (int)grid1d(M, tile), pick.splits};
 }
@@ -623,12 +628,14 @@ static void launch_contract_f32(bool large, const F32Contraction& c, int accumul
 }
 
 // Both gradient contractions of a batch of one panel, and the sums of what was split.
-static int grads_f32(const Plan& p, const void* H, const void* W, const float* zt, float* dH, float* dW, char* ws, hipStream_t st) {
+static int grads_f32(const Plan& p, const void* H, const void* W, const float* zt, float* dH, float* dW, char* ws,
+                     hipStream_t st) {
   float* part_dh = p.f32_dh.splits > 1 ? (float*)(ws + p.off_part) : nullptr;
   float* part_dw = p.f32_dw.splits > 1 ? (float*)(ws + p.off_part_dw) : nullptr;
   // dH[t][j] = sum_v dZ[t][v] W[v][j],  dW[v][j] = sum_t dZ[t][v] H[t][j]
-  const F32Contraction dh = contraction_f32(p.f32_dh, f32_operand(zt, p.ldz), f32_operand(W, p.d), p.T, p.d, p.V, part_dh ? part_dh : dH);
-  const F32Contraction dw = contraction_f32(p.f32_dw, f32_operand(zt, p.ldz), f32_operand(H, p.d), p.V, p.d, p.T, part_dw ? part_dw : dW);
+  const F32Operand z = f32_operand(zt, p.ldz);
+  const F32Contraction dh = contraction_f32(p.f32_dh, z, f32_operand(W, p.d), p.T, p.d, p.V, part_dh ? part_dh : dH);
+  const F32Contraction dw = contraction_f32(p.f32_dw, z, f32_operand(H, p.d), p.V, p.d, p.T, part_dw ? part_dw : dW);
   const F32Reduction a{part_dh, dh.splits, part_dh ? dh.M * dh.N : 0, dH}, b{part_dw, dw.splits, part_dw ? dw.M * dw.N : 0, dW};
   const F32Reduction none{nullptr, 0, 0, nullptr};
   auto reduce = [&](const F32Reduction& x, const F32Reduction& y) {
@@ -737,7 +744,7 @@ static int forward_partials(const Plan& p, const void* H, const void* W, bool en
 }
 
 // Log-probs (and lse, entropy) from the partial sums and the sampled tokens' logits; with `logq` also what the objective
-// and the gradients need.  `check_tokens`: the tokens, if the gather before left it to this launch to report those out of range.
+// and the gradients need. `check_tokens`: the tokens, if the gather before left it to this launch to report those out of range.
 static int forward_finish(const Plan& p, const float* logq, float* logprob_out, float* lse_out, float* entropy_out,
                           const int32_t* check_tokens, char* ws, hipStream_t st, Gate gate) {
   const int64_t T = p.T;
@@ -779,7 +786,8 @@ static void launch_grads(const DhArgs& dh, bool split, const DwArgs& dw, hipStre
 
 // One panel's dH and dW.  Only the tiles of the batch's last panel are split, and only it has a space for partial sums (no
 // sweep or recompute of the call follows; the other panels of a long batch are sized to fill the chip as they are).
-static int launch_gradients(const Plan& p, DhArgs dh, const DwArgs& dw, bool last, char* ws, hipStream_t st, Gate gate, bool timed) {
+static int launch_gradients(const Plan& p, DhArgs dh, const DwArgs& dw, bool last, char* ws, hipStream_t st, Gate gate,
+                            bool timed) {
   const bool split = last && p.dh.splits > 1, small = last && p.dh.small;
   dh.splits = split ? p.dh.splits : 1;
   dh.part = split ? (float*)(ws + p.off_part) : nullptr;
@@ -840,8 +848,8 @@ static int pack_wt(const Plan& p, const void* W, char* ws, hipStream_t st, Gate 
 // (diag(coef) H)^T of the panel at token t0, packed; token columns in [nv, 64 kt) come out as zeros
 static PackTransposed scaled_rows(const Plan& p, const void* H, int64_t t0, char* ws) {
   const int64_t nv = (p.T - t0) < p.Tp ? (p.T - t0) : p.Tp;
-  return PackTransposed{(const bf16_t*)H + t0 * p.d, nv, p.d, p.d, (const float*)(ws + p.off_coef) + t0, (bf16_t*)(ws + p.off_HTp),
-                        p.n_kt_t};
+  return PackTransposed{(const bf16_t*)H + t0 * p.d, nv, p.d, p.d, (const float*)(ws + p.off_coef) + t0,
+                        (bf16_t*)(ws + p.off_HTp), p.n_kt_t};
 }
 
 // Step a8, two-pass form: the soft-max tiles of the panel at token t0 recomputed into G and G^T.  `pack`: the launch makes the
@@ -956,9 +964,10 @@ static int launch_begin(const Begin& begin, hipStream_t st) {
   return OAPL_OK;
 }
 
-// The sweep's beginning, reference pass and gather in one launch (k_sweep_begin), 1000 tokens at d = 256, V = 1544: whole call 58
-// us, 67 in three.  Sixteen sampled logits per wavefront cost more than a launch of their own once rows are long
-// (in four rounds of whole wavefronts 500 tokens at d = 1024 lost 1.5 %, 300 at d = 4096 3 %).
+// The sweep's beginning, reference pass and gather in one launch (k_sweep_begin), whole calls in one / three, us: 1000 tokens
+// at d = 256, V = 1544 53 / 59; d = 1024: 1000, V = 8000 104 / 106, 8000 463 / 466. Sixteen sampled logits per wavefront cost
+// more than a launch of their own once rows are long: 1000 at d = 2048, V = 8000 168 / 165, 300 at d = 4096, V = 151936 1593 /
+// 1579.
 constexpr int kOneLaunchHidden = 1024;
 static bool sweep_begins_in_one_launch(const Plan& p, int n_seq, int n_groups) {
   return p.rows && p.d <= kOneLaunchHidden && begin_in_one_launch(n_seq, n_groups);
@@ -994,8 +1003,8 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
 
   const TokenInit init{(float*)(ws + p.off_coef), sample, ref2, diff, nis};
   const bool one = sweep_begins_in_one_launch(p, begin.n_seq, begin.n_groups);
-  // k_sweep_begin leaves tokens out of range to k_sweep_finish, which is closed for the panels behind a raised flag (for all, if it
-  // was raised at the beginning): the fallback, which that flag opens, then looks at every token
+  // k_sweep_begin leaves tokens out of range to k_sweep_finish, which is closed for the panels behind a raised flag (for all,
+  // if it was raised at the beginning): the fallback, which that flag opens, then looks at every token
   const int32_t* check = one ? tokens : nullptr;
   if (one) {
     k_sweep_begin<CfgRef><<<1 + grid1d(T, CfgRef::BN), CfgRef::NT, CfgRef::LDS_BYTES, st>>>(begin, x.W, x.H, V, T, d, p.n_kt_d,
@@ -1030,8 +1039,8 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
     OAPL_LAUNCH_CHECK();
     k_sweep_finish<<<grid1d(nv, kFinishRows), kFinishSlices * kFinishRows, 0, st>>>(
         spart, p.n_vt, p.Tp, nv, ref2 + t0, zy + t0, logq + t0, tokens + t0, V,
-        logprob_out ? logprob_out + t0 : nullptr, diff + t0, nis + t0, Gbuf(k), p.n_kt_g, GTbuf(k), p.n_kt_t, (int*)(ws + p.off_status),
-        fast);
+        logprob_out ? logprob_out + t0 : nullptr, diff + t0, nis + t0, Gbuf(k), p.n_kt_g, GTbuf(k), p.n_kt_t,
+        (int*)(ws + p.off_status), fast);
     OAPL_LAUNCH_CHECK();
     return OAPL_OK;
   };
@@ -1064,21 +1073,24 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
 }
 
 // fp32 calls whose logits do not give every CU a 128 x 128 tile start with one launch (k_scores_f32; 256 tokens at d = 64,
-// V = 1024: three launches of 3.6, 2.7 and 8.2 us before).  Where they do, workgroups in front of them unbalance the chip (1501 tokens,
-// d = 768, V = 8192, three tiles per CU: whole call 586 us apart, 639 together).
+// V = 1024: three launches of 3.6, 2.7 and 8.2 us before). Where they do, workgroups in front of them unbalance the chip (1501
+// tokens, d = 768, V = 8192, three tiles per CU: whole call 586 us apart, 639 together).
 static bool scores_in_one_launch_f32(const Plan& p, int n_seq, int n_groups) {
-  return p.dtype == OAPL_F32 && p.T > 0 && p.T <= kPanelF32 && !logits_large_f32(p.V, p.T) && begin_in_one_launch(n_seq, n_groups);
+  return p.dtype == OAPL_F32 && p.T > 0 && p.T <= kPanelF32 && !logits_large_f32(p.V, p.T) &&
+         begin_in_one_launch(n_seq, n_groups);
 }
 
 // The two-pass schedule (and the scoring alone, without gradients).
 template <class Begin, class Objective>
-static int two_pass_path(const Plan& p, const Begin& begin, const void* H, const void* W, const int32_t* tokens, const float* logq,
-                         float* logprob_out, void* dH, float* dW, char* ws, hipStream_t st, Objective&& objective) {
+static int two_pass_path(const Plan& p, const Begin& begin, const void* H, const void* W, const int32_t* tokens,
+                         const float* logq, float* logprob_out, void* dH, float* dW, char* ws, hipStream_t st,
+                         Objective&& objective) {
   const int64_t T = p.T;
   const TokenInit init{p.bwd ? (float*)(ws + p.off_coef) : nullptr, nullptr, nullptr, nullptr, nullptr};
   const bool one = scores_in_one_launch_f32(p, begin.n_seq, begin.n_groups);
   if (one) {
-    const EpiLseF32 epi{(float2*)(ws + p.off_fwd_partials), T, nullptr, p.bwd && T <= p.Tp ? (float*)(ws + p.off_G) : nullptr, p.ldz};
+    float* zt = p.bwd && T <= p.Tp ? (float*)(ws + p.off_G) : nullptr;
+    const EpiLseF32 epi{(float2*)(ws + p.off_fwd_partials), T, nullptr, zt, p.ldz};
     launch_scores_f32<F32Flat>(p, begin, H, W, tokens, (float*)(ws + p.off_zy), init, epi, st);
     OAPL_LAUNCH_CHECK();
   } else {
@@ -1164,9 +1176,9 @@ static int fit_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups, i
 }
 
 // Runs the objective's launch(grid, steps) once with both steps, or once with each.  The hand-over costs a fence and a counter
-// for every rollout: whole calls in one launch / two, 1000 tokens at d = 256, V = 1544: 72.5 / 72.1 us for 8 rollouts, 76.6 /
-// 73.3 for 64, 88.7 / 73.7 for 256, 138.6 / 78.6 for 1024; fp32, 256 tokens, d = 64, V = 1024, where the host's launches are
-// what the call waits for: 50 / 54 us up to 64.
+// for every rollout: whole calls in one launch / two, 1000 tokens at d = 256, V = 1544: 55.3 / 55.7 us for 8 rollouts, 55.5 /
+// 54.8 for 32, 57.4 / 54.7 for 64, 69 / 55 for 256, 119 / 60 for 1024; fp32, 256 tokens, d = 64, V = 1024, where the host's
+// launches are what the call waits for: 34.4 / 37.5 for 8, 36.1 / 37.6 for 64, 46 / 38 for 256.
 constexpr int kOneLaunchRollouts = 32;
 template <class Launch>
 static int objective_steps(int n_seq, Launch&& launch) {
@@ -1208,7 +1220,8 @@ static int loss_impl(const void* H, const void* W, const int32_t* tokens, const 
   const bool sweep = p.sweep && T >= kSweepMinTokens && !(flags & OAPL_FLAG_TWO_PASS);
   const int64_t longest = sweep ? sweep_longest(p) : -1;
 
-  const OaplBegin begin{rewards, group_ids, seq_offsets, n_seq, n_groups, T, longest, (double)beta_value, vstar, vstar_out, status};
+  const OaplBegin begin{rewards, group_ids, seq_offsets, n_seq, n_groups, T,
+                        longest, (double)beta_value, vstar, vstar_out, status};
   if (int rc = pack_operands(p, H, W, ws, st)) return rc;
 
   // Steps a4, a6, a7 from logprob - logq [T]

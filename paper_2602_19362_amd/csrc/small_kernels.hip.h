@@ -509,7 +509,8 @@ k_oapl_objective(const double* __restrict__ diff, const float* __restrict__ rewa
   for (int s = tid; s < n_seq; s += 256) {
     if (off[s + 1] < off[s]) atomicCAS(&bad, 0, kErrOffsets);
     if (gid[s] < 0 || gid[s] >= n_groups) atomicCAS(&bad, 0, kErrGroup);
-    const double delta = beta_l * __hip_atomic_load(Delta + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - (s == tid ? adv0 : advantage(s));
+    const double sum = __hip_atomic_load(Delta + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const double delta = beta_l * sum - (s == tid ? adv0 : advantage(s));
     acc += delta * delta;
   }
   acc = block_sum(acc);

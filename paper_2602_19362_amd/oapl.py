@@ -396,7 +396,8 @@ def timing_enable(on: bool) -> None:
 
 
 def timing_read():
-    """{kernel name: (total milliseconds, launches)} since timing was enabled."""
+    """{kernel name: (total milliseconds, launches)} since timing was enabled.  In small calls dH and dW are one launch, which
+    counts as k_bwd_dw; k_bwd_dh then has none."""
     out = {}
     for i, name in enumerate(DENSE_KERNELS):
         ms = ctypes.c_double(0.0)
