@@ -103,7 +103,7 @@ size_t oapl_workspace_bytes(int64_t T, int32_t d, int32_t V, int32_t n_seq,
  * and nearly all of the workspace is panel storage: panel rows x V x 4 bytes
  * per panel buffer.  Two things can be chosen:
  *   - the panel size.  oapl_workspace_bytes uses the library's own (at most
- *     12288 rows for OAPL_BF16 -- the fastest measured -- and 4096 for
+ *     12288 rows for OAPL_BF16 -- larger ones gain nothing -- and 4096 for
  *     OAPL_F32); max_panel_rows caps it lower (rounded down to whole 384-row
  *     tiles for OAPL_BF16, at least one tile; <= 0 or larger = the library's).
  *     Less than one tile asks for the least workspace there is: one-tile panels,

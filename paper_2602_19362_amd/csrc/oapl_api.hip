@@ -62,9 +62,9 @@ struct TilePick {
   int splits = 1;     // vocabulary ranges: one workgroup per (token tile, range), and the number of partials per token
 };
 
-// Most token rows per backward panel (bf16 path): 32 token tiles, the fastest size measured (the dH
-// contraction then has d / 256 x 32 tiles, whole rounds of 256 workgroups for d a multiple of 2048;
-// larger panels run 2 .. 3 % slower, smaller ones pay more for the read-add-write of dW).  A smaller
+// Most token rows per backward panel (bf16 path): 32 token tiles, for which the dH contraction has d / 256 x 32 tiles, whole
+// rounds of 256 workgroups for d a multiple of 2048.  140897 tokens at d = 4096, V = 151936: 368.5 ms; panels of 6144 rows, which
+// pay more for the read-add-write of dW, 377; of 24576 367, at twice the memory.  A smaller
 // workspace makes panels smaller; a larger one buys more panel buffers (longer rollouts on the single
 // sweep), never larger panels.
 constexpr int64_t kPanelBf16 = 12288;
@@ -403,7 +403,7 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
       p.off_G = take(p.size_G * p.n_buf);
       p.off_GT = take(p.size_GT * p.n_buf);
       // as many vocabulary splits as that space takes, so small panels do not leave the scoring pass short of workgroups
-      // (two passes over 16411 tokens at d = 4096 in panels of 6144: 66 ms, 113 ms with one split)
+      // (two passes over 16411 tokens at d = 4096 in panels of 6144, with the 32 x 32 x 16 loop: 66 ms, 113 ms with one split)
       const size_t room = (p.size_G + p.size_GT) * p.n_buf / (Tn * 8);
       p.fwd = pick_fwd(p.rows, T, V, room < (size_t)kAnySplits ? (room > 1 ? (int)room : 1) : kAnySplits);
       if (p.fwd.splits > 1) p.off_fwd_partials = p.off_G;
