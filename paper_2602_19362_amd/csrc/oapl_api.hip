@@ -197,7 +197,7 @@ static TilePick pick_fwd(bool rows, int64_t T, int V, int max_splits) {
 //   dH                               93 /  77                316 / 234         577 / 352, 1383 / 1034
 //   dW                               77 /  97                350 / 284         877 / 694, 1710 / 1223
 // and at d = 256, V = 1544, 1000 tokens 14 / 29, 12 / 22, 17 / 36 us (launches of their own; dH and dW of small tiles share
-// one, 16 us). Against the best of five fixed choices over 47 shapes the chosen call is within 4 % but for four: 1000 tokens at
+// one, 16 us). Against the best of five fixed choices over 44 shapes the chosen call is within 4 % but for four: 1000 tokens at
 // d = 1024, V = 32000 (339 us, all in small tiles 294), 3000 at d = 4096, V = 1544 (240 / 223) and V = 8192 (668 / 625), 100 at
 // d = 4096, V = 32000 (354 / 332): the rates do not know the launch that dH and dW of small tiles share.
 struct SmallRate {
