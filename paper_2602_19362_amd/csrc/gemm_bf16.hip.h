@@ -332,6 +332,7 @@ struct Mainloop {
   // = 8081 16.7 / 15.8 us, scoring 50 at d = 2048, V = 922 21.3 / 20.8; at V = 151936 the same; 128 x 128 tiles, sixteen
   // blocks, +1 .. +2 us).
   static constexpr bool kWhole = !ATR && C::MB * C::NB <= 8;
+  static_assert(!kWhole || !kSpread, "compute_whole gives out no loads");
   __device__ __forceinline__ void compute_whole(const int STAGE, lds_char_ptr smem, f32x4 (&acc)[C::MB][C::NB]) {
     bf16x8 a[C::KSTEPS][C::MB], b[C::KSTEPS][C::NB];
 #pragma unroll

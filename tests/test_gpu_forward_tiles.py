@@ -29,7 +29,7 @@ def _check(T, d, V, rows):
     z = H @ W.T
     ref_lse = np.log(np.exp(z - z.max(1, keepdims=True)).sum(1)) + z.max(1)
     ref_lp = z[np.arange(r.size), b.tokens[rt].cpu().numpy()] - ref_lse
-    assert np.abs(f64(lse[rt]) - ref_lse).max() <= 1e-4      # fp32 sums of exact products over d <= 200, V <= 60000
+    assert np.abs(f64(lse[rt]) - ref_lse).max() <= 1e-4      # fp32 sums of exact products over d <= 1024, V <= 60000
     assert np.abs(f64(lp[rt]) - ref_lp).max() <= 1e-4
     assert np.abs(f64(ent[rt]) - orc.token_entropy(H, W)).max() <= 2e-3
     _check_samples(b.H, b.W, 0.9, 77, tok, sc, rows=r)
@@ -39,6 +39,12 @@ def _check(T, d, V, rows):
 def test_small_token_counts(V):
     for T, d in ((1, 8), (2, 72), (63, 128), (64, 200), (65, 64), (127, 72), (128, 64), (129, 136), (256, 64), (257, 72)):
         _check(T, d, V, 300)
+
+
+# the 64- and 128-token tiles, which hold a whole block's fragments, over three and more k-blocks, a ragged last one among them
+@pytest.mark.parametrize("T,d", [(1, 192), (33, 200), (64, 320), (65, 192), (100, 328), (128, 200), (128, 1024)])
+def test_small_tiles_over_many_blocks(T, d):
+    _check(T, d, 700, 300)
 
 
 # 256-, 320- and 384-wide tiles: which one is taken depends on how the tiles divide over 256 compute units
