@@ -57,10 +57,13 @@ namespace oapl {
 // WM x WN wavefronts, each MB x NB blocks of 16 x 16.
 // PACK_B_: rows per block of the n-side operands where they are packed (0: one tile), a multiple of the tile's.
 // EARLY_: a block's loads go out in one go, for walks that wait for memory rather than for the multiplications.
-template <int WM_, int WN_, int MB_, int NB_, int NS_, int PACK_B_ = 0, bool EARLY_ = false>
+// ONCE_: the m-side operand is read once in the whole launch and its lines pass the caches by (non-temporal loads); a walk may start
+// at any k-block.
+template <int WM_, int WN_, int MB_, int NB_, int NS_, int PACK_B_ = 0, bool EARLY_ = false, bool ONCE_ = false>
 struct TileCfg {
   static constexpr int WM = WM_, WN = WN_, MB = MB_, NB = NB_;
   static constexpr bool EARLY = EARLY_;
+  static constexpr bool ONCE = ONCE_;
   static constexpr int NW = WM * WN;            // waves per workgroup
   static constexpr int NT = NW * 64;            // threads per workgroup
   static constexpr int WROWS = MB * 16, WCOLS = NB * 16;   // one wavefront's patch
@@ -72,7 +75,7 @@ struct TileCfg {
   static constexpr int ROW_BYTES = kPackRowBytes;
   static constexpr int STAGE_A = BM * ROW_BYTES;   // one stage of the m-side operand
   static constexpr int STAGE_B = BN * ROW_BYTES;   // ... of the n-side operand
-  static constexpr int PACK_A = kPackRowsA, PACK_B = PACK_B_ ? PACK_B_ : BN;
+  static constexpr int PACK_A = BM > kPackRowsA ? BM : kPackRowsA, PACK_B = PACK_B_ ? PACK_B_ : BN;   // (taller tiles read in place only)
   static constexpr int PITCH_A = PACK_A * ROW_BYTES, PITCH_B = PACK_B * ROW_BYTES;   // bytes of one packed block
   static_assert(PACK_A % BM == 0 && PACK_B % BN == 0, "a tile lies in one block");
   static constexpr int SLOT = STAGE_A + STAGE_B;   // one ring slot: the m-side block, then the n-side block
@@ -153,6 +156,7 @@ struct Mainloop {
   int voff;                           // per-lane byte offset of this lane's chunk inside the first 8 rows a wave loads
   int vlast;                          // ROWS: ... in the last k-block (out of range where the chunk lies past the row's end)
   int istep;                          // ROWS: bytes from one load of a wave to the next (8 * NW rows)
+  int first;                          // ONCE: the k-block that a walk starts with, and wraps around to behind the last
   const char* at_base;                // ATR: the tile's first column in row 0 of the matrix
   int64_t at_rows;                    // ... rows (k) from there
   int at_ld2, at_m0, at_voff;         // ... bytes per row, first column, per-lane byte offset of a wave's first load of a k-block
@@ -220,13 +224,15 @@ struct Mainloop {
     vlast = ((ld - 1) & ~(C::BK - 1)) + c * 8 < ld ? voff : (int)0x80000000u;
     istep = 8 * C::NW * ld * 2;
   }
-  // Operand tile `rt` (BM / BN rows) of a matrix of R rows, row-major or packed as ROWS says.
-  __device__ __forceinline__ void set_a(const bf16_t* p, int64_t rt, int64_t R, int ld, int n_kt) {
-    const int64_t left = R - rt * C::BM;
+  // m-side operand from row r0 of a matrix, rows from `end` on (at most BM further) as zeros: row-major or, with r0 at a
+  // multiple of BM, packed as ROWS says.
+  __device__ __forceinline__ void set_a(const bf16_t* p, int64_t r0, int64_t end, int ld, int n_kt) {
+    const int64_t left = end - r0;
     const int bytes = (int)(left < C::BM ? left : C::BM) * ld * 2;
-    if (ROWS) ra = __builtin_amdgcn_make_buffer_rsrc((void*)(p + rt * C::BM * ld), 0, bytes, 0x00020000);
-    else set_a_packed(p, rt * C::BM, n_kt, 0);
+    if (ROWS) ra = __builtin_amdgcn_make_buffer_rsrc((void*)(p + r0 * ld), 0, bytes, 0x00020000);
+    else set_a_packed(p, r0, n_kt, 0);
   }
+  // n-side operand tile `rt` (BN rows) of a matrix of R rows.
   __device__ __forceinline__ void set_b(const bf16_t* p, int64_t rt, int64_t R, int ld, int n_kt) {
     const int64_t left = R - rt * C::BN;
     const int bytes = (int)(left < C::BN ? left : C::BN) * ld * 2;
@@ -249,8 +255,13 @@ struct Mainloop {
   // Per-lane offset of the loads of k-block kt: past the buffer's range, so that nothing is read and zeros are
   // written, for a block past the last.
   __device__ __forceinline__ int load_voff(int kt, int nk) const {
-    const int inside = ATR ? 0 : ROWS && kt + 1 == nk ? vlast : voff;
+    const int inside = ATR ? 0 : ROWS && block(kt, nk) + 1 == nk ? vlast : voff;
     return kt < nk ? inside : (int)0x80000000u;
+  }
+  // The k-block that a walk takes at its step kt.
+  __device__ __forceinline__ int block(int kt, int nk) const {
+    if (!C::ONCE) return kt;
+    return kt + first < nk ? kt + first : kt + first - nk;
   }
   // Starts direct-to-LDS load i (of NI_A + NI_B) of k-block kt into ring slot STAGE (a literal at the call sites,
   // so the LDS addresses fold to constants once inlined), v = load_voff(kt, nk).
@@ -270,7 +281,7 @@ struct Mainloop {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, (v < 0 ? v : at_voff) + i * (C::NW * 512 / C::BM) * at_ld2, 0, 0, 0);
       } else {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, dst, 16, ROWS ? v + i * istep : v,
-                                                 ROWS ? kt * C::ROW_BYTES : kt * C::PITCH_A + i * C::NW * 1024, 0, 0);
+                                                 ROWS ? block(kt, nk) * C::ROW_BYTES : kt * C::PITCH_A + i * C::NW * 1024, 0, C::ONCE ? 2 : 0 /* non-temporal */);
       }
     } else if (i < C::NI_A + C::NI_B) {
       const int b = i - C::NI_A;
@@ -278,7 +289,7 @@ struct Mainloop {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           rb, (lds_void_ptr)(smem + STAGE * C::SLOT + C::STAGE_A + (b * C::NW + wave) * 1024), 16,
           ATR ? (v < 0 ? v : voff) : ROWS ? v + b * istep : v,
-          ROWS ? kt * C::ROW_BYTES : kt * C::PITCH_B + b * C::NW * 1024, 0, 0);
+          ROWS ? block(kt, nk) * C::ROW_BYTES : kt * C::PITCH_B + b * C::NW * 1024, 0, 0);
     }
   }
   // ... all loads of the block.
@@ -302,6 +313,8 @@ struct Mainloop {
   static __device__ __forceinline__ void settle(f32x4 (&acc)[C::MB][C::NB]) {
     __builtin_amdgcn_sched_barrier(0);
 #define OAPL_COLUMN(j) "+v"(acc[0][j]), "+v"(acc[1][j]), "+v"(acc[2][j]), "+v"(acc[3][j])
+#define OAPL_ROW_4 "+v"(acc[4][0]), "+v"(acc[4][1]), "+v"(acc[4][2]), "+v"(acc[4][3]), "+v"(acc[4][4]), "+v"(acc[4][5]), \
+                   "+v"(acc[4][6]), "+v"(acc[4][7])
 #define OAPL_COLUMNS_4 OAPL_COLUMN(0), OAPL_COLUMN(1), OAPL_COLUMN(2), OAPL_COLUMN(3)
 #define OAPL_COLUMNS_8 OAPL_COLUMNS_4, OAPL_COLUMN(4), OAPL_COLUMN(5), OAPL_COLUMN(6), OAPL_COLUMN(7)
 #define OAPL_COLUMNS_9 OAPL_COLUMNS_8, OAPL_COLUMN(8)
@@ -312,19 +325,21 @@ struct Mainloop {
       asm volatile("s_nop 7" : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]),
                                "+v"(acc[1][0]), "+v"(acc[1][1]), "+v"(acc[1][2]), "+v"(acc[1][3]));
     else if constexpr (C::NB == 4) asm volatile("s_nop 7" : OAPL_COLUMNS_4);
+    else if constexpr (C::MB == 5) asm volatile("s_nop 7" : OAPL_COLUMNS_8, OAPL_ROW_4);
     else if constexpr (C::NB == 8) asm volatile("s_nop 7" : OAPL_COLUMNS_8);
     else if constexpr (C::NB == 9) asm volatile("s_nop 7" : OAPL_COLUMNS_9);
     else if constexpr (C::NB == 10) asm volatile("s_nop 7" : OAPL_COLUMNS_10);
     else if constexpr (C::NB == 11) asm volatile("s_nop 7" : OAPL_COLUMNS_11);
     else asm volatile("s_nop 7" : OAPL_COLUMNS_12);
 #undef OAPL_COLUMN
+#undef OAPL_ROW_4
 #undef OAPL_COLUMNS_4
 #undef OAPL_COLUMNS_8
 #undef OAPL_COLUMNS_9
 #undef OAPL_COLUMNS_10
 #undef OAPL_COLUMNS_11
 #undef OAPL_COLUMNS_12
-    static_assert(C::MB == 4 || (C::MB == 2 && C::NB == 4), "operands of the statement above");
+    static_assert(C::MB == 4 || (C::MB == 2 && C::NB == 4) || (C::MB == 5 && C::NB == 8), "operands of the statement above");
   }
 
   // Patches of up to eight blocks (64 and 128 tokens): all fragments of the block are requested before its first
@@ -713,6 +728,29 @@ __device__ __forceinline__ void strip_tile(int L, int MT, int NTl, int& mt, int&
   strip_tile(SN, L, MT, NTl, mt, nt);
 }
 
+// The vocabulary rows that a workgroup of the streaming kernels walks, tiles of `h` rows from r0 to r1.  Split `split` of
+// n_splits: whole tiles, or (balanced, operands in place) the same number of rows to within 16 for everyone, in tiles of equal
+// height.  A launch that waits for W to arrive takes as long as the workgroup with the most rows: whole tiles of 256 at V =
+// 151936 are two for some CUs and three for others.  The rows that a lower tile leaves out are not read.
+struct RowWalk {
+  int r0, r1, h;
+};
+template <class C>
+__host__ __device__ __forceinline__ RowWalk row_walk(int V, int split, int n_splits, int balanced) {
+  const int unit = balanced ? 16 : C::BM, units = (V + unit - 1) / unit;
+  const int r0 = (int)((int64_t)split * units / n_splits) * unit, end = (int)((int64_t)(split + 1) * units / n_splits) * unit;
+  const int r1 = end < V ? end : V;
+  if (!balanced) return RowWalk{r0, r1, C::BM};
+  const int tiles = (r1 - r0 + C::BM - 1) / C::BM;
+  return RowWalk{r0, r1, tiles > 0 ? ((r1 - r0 + tiles - 1) / tiles + 15) / 16 * 16 : C::BM};
+}
+
+// Where rows are a multiple of 4 KiB apart, what workgroups in step with each other request (a 128-byte piece of every row, all at
+// the same k) lies on few of the memory's channels, so each starts its walk over k at another block: scoring 16 tokens at d = 2048,
+// V = 151936 137 / 103 us, at d = 6144, V = 60000 169 / 129, 8192 190 / 163, at d = 4096, V = 151936 210 / 203. Other pitches
+// gain nothing (d = 1024 .. 7168: -2 .. +2 %) and keep the plain order.
+__device__ __forceinline__ int first_block(int split, int d, int n_kt) { return d % 2048 == 0 ? split % n_kt : 0; }
+
 // ---------------------------------------------------------------------------
 // Forward: logits^T tiles with a streaming (online) log-sum-exp over the
 // vocabulary.  The T x V logits never leave registers.
@@ -729,7 +767,7 @@ __device__ __forceinline__ void strip_tile(int L, int MT, int NTl, int& mt, int&
 template <class C, bool ENT, bool ROWS>
 __global__ void __launch_bounds__(C::NT)
 k_fwd_lse(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int64_t T, int d, int n_kt,
-          int n_splits, int patch_tiles, float2* __restrict__ partials, float* __restrict__ upart,
+          int n_splits, int balanced, int patch_tiles, float2* __restrict__ partials, float* __restrict__ upart,
           int* __restrict__ clear /* a status header to clear, or nullptr */, Gate gate) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
@@ -747,14 +785,13 @@ k_fwd_lse(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int
   // splits of its token tile).
   int split, nt;
   strip_tile(patch_tiles, L, n_splits, n_tiles, split, nt);
-  const int MT = (V + C::BM - 1) / C::BM;
-  const int mt_begin = (int)((int64_t)split * MT / n_splits);
-  const int mt_end = (int)((int64_t)(split + 1) * MT / n_splits);
+  const RowWalk walk = row_walk<C>(V, split, n_splits, balanced);
   const int64_t n0 = (int64_t)nt * C::BN;
 
   Mainloop<C, ROWS> ml;
   ml.setup();
   ml.rows_init(d);
+  ml.first = first_block(split, d, n_kt);
   ml.set_b(H, nt, T, d, n_kt);
 
   const Lane<C> at;
@@ -765,21 +802,22 @@ k_fwd_lse(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int
   for (int q = 0; q < Q; ++q) { m2[q] = kNegHuge; s[q] = 0.f; u[q] = 0.f; }
 
   f32x4 acc[C::MB][C::NB];
-  if (mt_begin < mt_end) {
-    ml.set_a(W, mt_begin, V, d, n_kt);
+  auto set_tile = [&](int m0) { ml.set_a(W, m0, m0 + walk.h < walk.r1 ? m0 + walk.h : walk.r1, d, n_kt); };
+  if (walk.r0 < walk.r1) {
+    set_tile(walk.r0);
     ml.start_preload(smem, n_kt);
   }
-  for (int mt = mt_begin; mt < mt_end; ++mt) {
-    const int m0 = mt * C::BM;
+  for (int m0 = walk.r0; m0 < walk.r1; m0 += walk.h) {
+    const int end = m0 + walk.h < walk.r1 ? m0 + walk.h : walk.r1;
     zero_acc<C>(acc);
     ml.template finish<true>(smem, n_kt, acc);
-    if (mt + 1 < mt_end) {  // the epilogue below works in registers only: overlap it with the next tile's first loads
-      ml.set_a(W, mt + 1, V, d, n_kt);
+    if (end < walk.r1) {  // the epilogue below works in registers only: overlap it with the next tile's first loads
+      set_tile(end);
       ml.start_preload(smem, n_kt);
     }
 
-    // ragged last vocabulary tile: rows >= V do not exist (their logits are 0, not -inf)
-    if (m0 + C::BM > V) fill_rows_past<C>(acc, m0 + at.row0(), V, -__builtin_inff());
+    // a lower tile, the ragged last one among them: rows from its end on do not exist (their logits are 0, not -inf)
+    if (m0 + C::BM > end) fill_rows_past<C>(acc, m0 + at.row0(), end, -__builtin_inff());
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       float x[4];
@@ -865,7 +903,7 @@ k_fwd_lse(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int
 template <class C, bool ROWS>
 __global__ void __launch_bounds__(C::NT)
 k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int64_t T, int d, int n_kt, int n_splits,
-             float inv_temperature, uint32_t seed_lo, uint32_t seed_hi, float2* __restrict__ partials) {
+             int balanced, float inv_temperature, uint32_t seed_lo, uint32_t seed_hi, float2* __restrict__ partials) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   lds_char_ptr smem = (lds_char_ptr)smem_raw;
@@ -875,14 +913,13 @@ k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, 
   const int L = xcd_logical_id(blockIdx.x, total);
   if (L >= total) return;
   const int nt = L / n_splits, split = L % n_splits;
-  const int MT = (V + C::BM - 1) / C::BM;
-  const int mt_begin = (int)((int64_t)split * MT / n_splits);
-  const int mt_end = (int)((int64_t)(split + 1) * MT / n_splits);
+  const RowWalk walk = row_walk<C>(V, split, n_splits, balanced);
   const int64_t n0 = (int64_t)nt * C::BN;
 
   Mainloop<C, ROWS> ml;
   ml.setup();
   ml.rows_init(d);
+  ml.first = first_block(split, d, n_kt);
   ml.set_b(H, nt, T, d, n_kt);
 
   const Lane<C> at;
@@ -892,20 +929,21 @@ k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, 
   for (int j = 0; j < C::NB; ++j) { best[j] = -__builtin_inff(); arg[j] = 0x7FFFFFFF; }
 
   f32x4 acc[C::MB][C::NB];
-  if (mt_begin < mt_end) {
-    ml.set_a(W, mt_begin, V, d, n_kt);
+  auto set_tile = [&](int m0) { ml.set_a(W, m0, m0 + walk.h < walk.r1 ? m0 + walk.h : walk.r1, d, n_kt); };
+  if (walk.r0 < walk.r1) {
+    set_tile(walk.r0);
     ml.start_preload(smem, n_kt);
   }
-  for (int mt = mt_begin; mt < mt_end; ++mt) {
-    const int m0 = mt * C::BM;
+  for (int m0 = walk.r0; m0 < walk.r1; m0 += walk.h) {
+    const int end = m0 + walk.h < walk.r1 ? m0 + walk.h : walk.r1;
     zero_acc<C>(acc);
     ml.template finish<true>(smem, n_kt, acc);
-    if (mt + 1 < mt_end) {
-      ml.set_a(W, mt + 1, V, d, n_kt);
+    if (end < walk.r1) {
+      set_tile(end);
       ml.start_preload(smem, n_kt);
     }
-    // ragged last vocabulary tile: a logit of -inf is never drawn
-    if (m0 + C::BM > V) fill_rows_past<C>(acc, m0 + at.row0(), V, -__builtin_inff());
+    // a lower tile, the ragged last one among them: a logit of -inf is never drawn
+    if (m0 + C::BM > end) fill_rows_past<C>(acc, m0 + at.row0(), end, -__builtin_inff());
     // Rows outside, tokens inside: the first two Philox rounds multiply words that depend on the row block or on the token
     // alone, and are shared over the other.
 #pragma unroll
@@ -1083,7 +1121,7 @@ k_bwd_dz(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H_panel, int V
   Mainloop<C, ROWS> ml;
   ml.setup();
   ml.rows_init(d);
-  ml.set_a(W, mt, V, d, n_kt);
+  ml.set_a(W, m0, V, d, n_kt);
   ml.set_b(H_panel, nt, n_valid, d, n_kt);
 
   f32x4 acc[C::MB][C::NB];
@@ -1259,7 +1297,7 @@ k_sweep(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H_panel, int V,
   Mainloop<C, ROWS> ml;
   ml.setup();
   ml.rows_init(d);
-  ml.set_a(W, mt, V, d, n_kt);
+  ml.set_a(W, m0, V, d, n_kt);
   ml.set_b(H_panel, nt, n_valid, d, n_kt);
 
   const Lane<C> at;

@@ -34,13 +34,14 @@ typedef TileCfg<4, 2, 4, 8, 2> CfgSample;
 
 // Tiles of the scoring and sampling kernels over row-major operands.  A call of few tokens pays for every padded
 // token column and is bound by reading W once; a call of many is bound by operand delivery, which wants the largest
-// tile.  128 x 64 (48 KB of LDS, three workgroups per CU to keep W streaming through each other's barriers) reads W at 5.8 TB/s
-// for up to 64 tokens at d = 4096, V = 151936: sampling 215 us, in tiles of 256 x 64 249, of 128 x 128 255, of 256 x 256 307.
-// 128 x 128 (two per CU) serves up to 128 tokens in 277 us against 325.  From there on a tile is 256 tall, one per CU,
-// and its width follows from the token count (pick_tile).
+// tile.  128 x 64 (48 KB of LDS, three workgroups per CU to keep W streaming through each other's barriers) serves up to 64 tokens,
+// 128 x 128 (two per CU) up to 128.  From there on a tile is one per CU and 256 tall, and its width follows from the token count
+// (pick_tile); up to 256 tokens it may be 320 tall instead, where that divides the rows of a CU into fewer or better filled
+// tiles (V = 151936, 594 rows per CU: two tiles of 297 in place of three of 198).
 typedef TileCfg<4, 1, 2, 4, 2> Cfg64;
 typedef TileCfg<4, 2, 2, 4, 2> Cfg128;
 typedef CfgSample Cfg256;
+typedef TileCfg<4, 2, 5, 8, 2> Cfg256Tall;
 // ... up to two token tiles over a W that the memory-side cache cannot hold wait for it to arrive: their loads go out as early
 // as they can. Early / spread, 200, 400 and 512 tokens: d = 4096, V = 48000 (375 MiB) sampling -5, -8, -5 %, scoring -5, -5, -4
 // %; d = 2048, V = 100000 (391 MiB) -5, -5, -2 and -5, -4, -4 %; V = 151936 -4, -3, -1 and -4, -2, -2 %. Where the cache holds
@@ -48,6 +49,20 @@ typedef CfgSample Cfg256;
 typedef TileCfg<4, 2, 4, 8, 2, 0, true> Cfg256Early;
 static bool early_pays(int64_t T, int V, int d) {
   return T <= 2 * Cfg256Early::BN && (int64_t)V * d * 2 > (int64_t)256 << 20;
+}
+// ... and one token tile reads W once: non-temporal loads, which this card delivers at 7.1 TB/s where others reach 6.3, and, rows
+// a multiple of 4 KiB apart, each workgroup's walk over k from another block on (TileCfg's ONCE).  With equally many rows
+// for every workgroup (row_walk), scoring before / now at V = 151936, us: d = 4096 16 tokens 238 / 202, 64 231 / 214, 128
+// 283 / 260, 192 340 / 286, 256 348 / 300 (sampling 227 / 197, 225 / 211, 283 / 264, 348 / 310, 358 / 323); d = 2048 16 tokens 153 /
+// 107, 128 180 / 142, 256 203 / 164; d = 5120 286 / 255, 388 / 371, 458 / 390.  Rows that are not whole 128-byte lines would be
+// fetched twice (d = 3000, V = 60000: +12 .. +20 %), and a W that mostly survives in the memory-side cache from call to
+// call is better left there (264 MiB +3 .. +10 %, 297 MiB -4 .. -16 %, 305 MiB -4 .. -11 %).
+typedef TileCfg<4, 1, 2, 4, 2, 0, false, true> Cfg64Once;
+typedef TileCfg<4, 2, 2, 4, 2, 0, false, true> Cfg128Once;
+typedef TileCfg<4, 2, 4, 8, 2, 0, true, true> Cfg256Once;
+typedef TileCfg<4, 2, 5, 8, 2, 0, true, true> Cfg256TallOnce;
+static bool once_pays(int64_t T, int V, int d) {
+  return T <= Cfg256Once::BN && d % kPackK == 0 && (int64_t)V * d * 2 > (int64_t)288 << 20;
 }
 // Odd widths: the n-side block is 4.5 or 5.5 loads per wave, the last of them half of the waves'.  The 352-wide kernel has a
 // register too few (8 B of scratch, outside the k loop).
@@ -60,6 +75,8 @@ enum FwdTile { kTile64, kTile128, kTile256, kTile320, kTile384, kTile288, kTile3
 struct TilePick {
   FwdTile tile = kTile384;
   int splits = 1;     // vocabulary ranges: one workgroup per (token tile, range), and the number of partials per token
+  bool balanced = false;   // ranges of equally many rows instead of whole tiles (row_walk)
+  bool tall = false;       // 256 columns: 320 rows in place of 256
 };
 
 // Most token rows per backward panel (bf16 path): 32 token tiles, for which the dH contraction has d / 256 x 32 tiles, whole
@@ -162,16 +179,24 @@ static TilePick pick_splits(FwdTile tile, int64_t T, int V, int max_splits, doub
   return best;
 }
 
-// Tile and splits over row-major operands.  Up to 128 tokens the call is bound by reading W and every 128-row
-// vocabulary tile is a workgroup of its own.  Beyond, the time of one 256-row tile at d = 4096 is in the ratio of 105 / 115.5 /
+// Tile and splits over row-major operands.  Up to 256 tokens the call is bound by reading W, and as many workgroups as the CUs
+// hold at once share its rows evenly. Beyond, the time of one 256-row tile at d = 4096 is in the ratio of 105 / 115.5 /
 // 126 / 138 / 150 for 256 / 288 / 320 / 352 / 384 columns (it scales with d): the wide tile is the cheapest per column, a
 // narrower one pads fewer columns. 256, 320 and 384 alone / all five: 350 tokens at d = 4096 433 / 403 us, 700 725 / 674, 777
 // 825 / 779, 1003 996 / 941, 1400 1412 / 1292, 2500 and more the same.
 static TilePick pick_tile(int64_t T, int V, int max_splits, bool scoring) {
-  const int MT128 = (V + 127) / 128;
-  const int small = MT128 < max_splits ? MT128 : max_splits;
-  if (T <= Cfg64::BN) return TilePick{kTile64, small};
-  if (T <= Cfg128::BN) return TilePick{kTile128, small};
+  auto workgroups = [&](int per_cu, int rows) {      // at most one per tile of `rows` rows
+    const int tiles = (V + rows - 1) / rows, most = per_cu * kNumCU < max_splits ? per_cu * kNumCU : max_splits;
+    return tiles < most ? tiles : most;
+  };
+  if (T <= Cfg64::BN) return TilePick{kTile64, workgroups(3, Cfg64::BM), true};
+  if (T <= Cfg128::BN) return TilePick{kTile128, workgroups(2, Cfg128::BM), true};
+  if (T <= Cfg256::BN) {
+    // the least tile rows: of 256, or of 320 where they are fewer
+    const int splits = workgroups(1, Cfg256::BM), rows = (int)round_up((V + splits - 1) / splits, 16);
+    const int flat = (rows + Cfg256::BM - 1) / Cfg256::BM, tall = (rows + Cfg256Tall::BM - 1) / Cfg256Tall::BM;
+    return TilePick{kTile256, splits, true, tall * Cfg256Tall::BM < flat * Cfg256::BM};
+  }
   double best_time, time;
   TilePick best = pick_splits<Cfg256>(kTile256, T, V, max_splits, 105.0, &best_time);
   if (!scoring) return best;
@@ -501,7 +526,10 @@ static bool prepare_kernels() {
   static std::once_flag once;
   static bool ok = false;
   std::call_once(once, [] {
-    ok = allow_fwd<Cfg64, true>() && allow_fwd<Cfg128, true>() && allow_fwd<Cfg256, true>() && allow_fwd<Cfg256Early, true>() &&
+    ok = allow_fwd<Cfg64Once, true>() && allow_fwd<Cfg128Once, true>() && allow_fwd<Cfg256Once, true>() &&
+         allow_fwd<Cfg256Tall, true>() && allow_fwd<Cfg256TallOnce, true>() && allow_sample<Cfg64Once, true>() &&
+         allow_sample<Cfg128Once, true>() && allow_sample<Cfg256Once, true>() && allow_sample<Cfg256Tall, true>() &&
+         allow_sample<Cfg256TallOnce, true>() && allow_fwd<Cfg64, true>() && allow_fwd<Cfg128, true>() && allow_fwd<Cfg256, true>() && allow_fwd<Cfg256Early, true>() &&
          allow_fwd<Cfg288, true>() && allow_fwd<Cfg320, true>() && allow_fwd<Cfg352, true>() &&
          allow_fwd<Cfg, true>() && allow_fwd<Cfg, false>() && allow_sample<Cfg64, true>() &&
          allow_sample<Cfg128, true>() && allow_sample<Cfg256, true>() && allow_sample<Cfg256Early, true>() &&
@@ -550,7 +578,7 @@ static void launch_fwd_lse_kernel(const FwdArgs& a, float2* partials, float* upa
   // 20000 tokens at d = 4096, walks of 3 tiles: 20.2 / 18.2 / 18.1 / 18.4 ms for patches of 1 / 4 / 8 / 16; 30000 at
   // d = 5120: 36.7 / 34.5 / 35.5 / 35.7; 20000 at d = 2048 10.19 / 9.15 / 9.18 / 9.28.
   const int patch_tiles = (size_t)a.n_kt * C::STAGE_B <= ((size_t)3 << 20) ? 8 : 4;
-  k_fwd_lse<C, ENT, ROWS><<<grid, C::NT, C::LDS_BYTES, st>>>(a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, patch_tiles,
+  k_fwd_lse<C, ENT, ROWS><<<grid, C::NT, C::LDS_BYTES, st>>>(a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, a.pick.balanced, patch_tiles,
                                                            partials, upart, clear, gate);
 }
 template <class C, bool ROWS>
@@ -561,10 +589,18 @@ static void launch_fwd_lse(const FwdArgs& a, float2* partials, float* upart, int
 static void launch_fwd_lse(const FwdArgs& a, bool rows, float2* partials, float* upart, int* clear, hipStream_t st,
                            Gate gate) {
   if (!rows) return launch_fwd_lse<Cfg, false>(a, partials, upart, clear, st, gate);
+  const bool once = once_pays(a.T, a.V, a.d);
   switch (a.pick.tile) {
-    case kTile64: return launch_fwd_lse<Cfg64, true>(a, partials, upart, clear, st, gate);
-    case kTile128: return launch_fwd_lse<Cfg128, true>(a, partials, upart, clear, st, gate);
+    case kTile64:
+      if (once) return launch_fwd_lse<Cfg64Once, true>(a, partials, upart, clear, st, gate);
+      return launch_fwd_lse<Cfg64, true>(a, partials, upart, clear, st, gate);
+    case kTile128:
+      if (once) return launch_fwd_lse<Cfg128Once, true>(a, partials, upart, clear, st, gate);
+      return launch_fwd_lse<Cfg128, true>(a, partials, upart, clear, st, gate);
     case kTile256:
+      if (a.pick.tall && once) return launch_fwd_lse<Cfg256TallOnce, true>(a, partials, upart, clear, st, gate);
+      if (a.pick.tall) return launch_fwd_lse<Cfg256Tall, true>(a, partials, upart, clear, st, gate);
+      if (once) return launch_fwd_lse<Cfg256Once, true>(a, partials, upart, clear, st, gate);
       if (early_pays(a.T, a.V, a.d)) return launch_fwd_lse<Cfg256Early, true>(a, partials, upart, clear, st, gate);
       return launch_fwd_lse<Cfg256, true>(a, partials, upart, clear, st, gate);
     case kTile288: return launch_fwd_lse<Cfg288, true>(a, partials, upart, clear, st, gate);
@@ -578,7 +614,7 @@ template <class C, bool ROWS>
 static void launch_sample(const FwdArgs& a, float inv_t, uint64_t seed, float2* partials, hipStream_t st) {
   const int64_t total = (a.T + C::BN - 1) / C::BN * a.pick.splits;
   k_fwd_sample<C, ROWS><<<(unsigned)round_up(total, 8), C::NT, C::LDS_BYTES, st>>>(
-      a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, inv_t, (uint32_t)seed, (uint32_t)(seed >> 32), partials);
+      a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, a.pick.balanced, inv_t, (uint32_t)seed, (uint32_t)(seed >> 32), partials);
 }
 
 static F32Operand f32_operand(const void* p, int64_t ld) {
@@ -1422,9 +1458,15 @@ int32_t oapl_sample_tokens(const void* H, const void* W, int64_t T, int32_t d, i
     }
     {
       ScopedKernelTimer tm(kFwdSample, st);
+      const bool once = once_pays(T, V, d);
       if (!p.rows) launch_sample<CfgSample, false>(args, inv_t, seed, partials, st);
+      else if (p.smp.tile == kTile64 && once) launch_sample<Cfg64Once, true>(args, inv_t, seed, partials, st);
       else if (p.smp.tile == kTile64) launch_sample<Cfg64, true>(args, inv_t, seed, partials, st);
+      else if (p.smp.tile == kTile128 && once) launch_sample<Cfg128Once, true>(args, inv_t, seed, partials, st);
       else if (p.smp.tile == kTile128) launch_sample<Cfg128, true>(args, inv_t, seed, partials, st);
+      else if (p.smp.tall && once) launch_sample<Cfg256TallOnce, true>(args, inv_t, seed, partials, st);
+      else if (p.smp.tall) launch_sample<Cfg256Tall, true>(args, inv_t, seed, partials, st);
+      else if (once) launch_sample<Cfg256Once, true>(args, inv_t, seed, partials, st);
       else if (early_pays(T, V, d)) launch_sample<Cfg256Early, true>(args, inv_t, seed, partials, st);
       else launch_sample<Cfg256, true>(args, inv_t, seed, partials, st);
     }

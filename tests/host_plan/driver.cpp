@@ -38,6 +38,20 @@ int main() {
       for (int t : taken) once += t == 1;
       for (int x : on) most = x > most ? x : most;
       std::printf("tiles=%d once=%d most=%d\n", n, once, most);
+    } else if (std::sscanf(line, "walks %d %d %d", &V, &n_seq, &n_groups) == 3) {
+      // n_seq balanced ranges of V rows in tiles of 128, 256 or 320 rows: gaps between them, tiles that are empty or too high,
+      // rows of the longest and the shortest
+      int at = 0, wrong = 0, most = 0, least = V;
+      for (int k = 0; k < n_seq; ++k) {
+        const RowWalk w = n_groups == 128 ? row_walk<Cfg128>(V, k, n_seq, 1) : n_groups == 256 ? row_walk<Cfg256>(V, k, n_seq, 1)
+                                                                                               : row_walk<Cfg256Tall>(V, k, n_seq, 1);
+        wrong += w.r0 != at || w.r0 % 16 != 0 || w.h < 1 || w.h > n_groups || w.h % 16 != 0;
+        wrong += w.r0 >= w.r1 || (w.r1 - w.r0 + w.h - 1) / w.h != (w.r1 - w.r0 + n_groups - 1) / n_groups;
+        at = w.r1;
+        most = w.r1 - w.r0 > most ? w.r1 - w.r0 : most;
+        least = w.r1 - w.r0 < least ? w.r1 - w.r0 : least;
+      }
+      std::printf("wrong=%d end=%d most=%d least=%d\n", wrong, at, most, least);
     } else if (std::sscanf(line, "plan %lld %d %d %d %d %lld %u %lld", &T, &d, &V, &dtype, &bwd, &cap, &unaligned, &have) == 8) {
       // the plan of a call of one rollout on `have` bytes (< 0: what the library asks for with panels of `cap` rows)
       if (have < 0) have = (long long)oapl_workspace_bytes_for(T, d, V, 1, 1, dtype, bwd, cap, 0, nullptr, nullptr);

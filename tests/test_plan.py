@@ -110,3 +110,13 @@ def test_dh_is_split_where_its_walk_outlasts_dws(T, d, V, split):
     """In the launch that both share, on both sides of the line."""
     p = ask([f"plan {T} {d} {V} 1 1 0 0 -1"])[0]
     assert p["rc"] == 0 and p["dh_small"] and p["small_dw"] and (p["dh_splits"] > 1) == split
+
+
+@pytest.mark.parametrize("rows", [128, 256, 320])
+@pytest.mark.parametrize("V", [1, 16, 127, 300, 5003, 32000, 60000, 151936, 2 ** 21])
+def test_balanced_walks_cover_the_vocabulary(V, rows):
+    """Every row once, in as few tiles as its workgroup needs, and no workgroup with over 32 rows more than another."""
+    for per_cu in (1, 2, 3):
+        n = min(per_cu * 256, (V + rows - 1) // rows)
+        a = ask([f"walks {V} {n} {rows}"])[0]
+        assert a["wrong"] == 0 and a["end"] == V and a["most"] - a["least"] <= 32
