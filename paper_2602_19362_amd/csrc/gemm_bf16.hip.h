@@ -256,7 +256,8 @@ struct Mainloop {
   // written, for a block past the last.
   __device__ __forceinline__ int load_voff(int kt, int nk) const {
     const int inside = ATR ? 0 : ROWS && block(kt, nk) + 1 == nk ? vlast : voff;
-    return kt < nk ? inside : (int)0x80000000u;
+    const int v = kt < nk ? inside : (int)0x80000000u;
+    return ROWS ? fresh(v) : v;
   }
   // The k-block that a walk takes at its step kt.
   __device__ __forceinline__ int block(int kt, int nk) const {
@@ -567,6 +568,25 @@ __device__ __forceinline__ float reduce4(const float (&x)[4], Op op) {
   const float p = swap32(x[0], x[2]), q = swap32(x[1], x[3]);
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(p), __float_as_uint(q), false, false);
   return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+// ... of (score, index) pairs, the better of which stays.
+__device__ __forceinline__ void reduce4_better(const float (&x)[4], const int (&i)[4], float& score, int& index) {
+  auto pick = [](float sa, int ia, float sb, int ib, float& so, int& io) {
+    const bool first = better(sa, ia, sb, ib);
+    so = first ? sa : sb;
+    io = first ? ia : ib;
+  };
+  float p[2];
+  int pi[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[k]), __float_as_uint(x[k + 2]), false, false);
+    const auto ri = __builtin_amdgcn_permlane32_swap((uint32_t)i[k], (uint32_t)i[k + 2], false, false);
+    pick(__uint_as_float(r[0]), (int)ri[0], __uint_as_float(r[1]), (int)ri[1], p[k], pi[k]);
+  }
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(p[0]), __float_as_uint(p[1]), false, false);
+  const auto ri = __builtin_amdgcn_permlane16_swap((uint32_t)pi[0], (uint32_t)pi[1], false, false);
+  pick(__uint_as_float(r[0]), (int)ri[0], __uint_as_float(r[1]), (int)ri[1], score, index);
 }
 // ... and back: x[k] = what group k holds in y.
 __device__ __forceinline__ void spread4(float y, float (&x)[4]) {
@@ -903,7 +923,7 @@ k_fwd_lse(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int
 template <class C, bool ROWS>
 __global__ void __launch_bounds__(C::NT)
 k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int64_t T, int d, int n_kt, int n_splits,
-             int balanced, float inv_temperature, uint32_t seed_lo, uint32_t seed_hi, float2* __restrict__ partials) {
+             int balanced, int patch_tiles, float inv_temperature, uint32_t seed_lo, uint32_t seed_hi, float2* __restrict__ partials) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   lds_char_ptr smem = (lds_char_ptr)smem_raw;
@@ -912,7 +932,8 @@ k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, 
   const int total = n_tiles * n_splits;
   const int L = xcd_logical_id(blockIdx.x, total);
   if (L >= total) return;
-  const int nt = L / n_splits, split = L % n_splits;
+  int split, nt;
+  strip_tile(patch_tiles, L, n_splits, n_tiles, split, nt);     // as in k_fwd_lse
   const RowWalk walk = row_walk<C>(V, split, n_splits, balanced);
   const int64_t n0 = (int64_t)nt * C::BN;
 
@@ -923,10 +944,12 @@ k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, 
   ml.set_b(H, nt, T, d, n_kt);
 
   const Lane<C> at;
-  float best[C::NB];
-  int arg[C::NB];
+  // the running best of column 16 (4 q + g) + c is lane group g's, as in k_fwd_lse
+  constexpr int Q = (C::NB + 3) / 4;
+  float best[Q];
+  int arg[Q];
 #pragma unroll
-  for (int j = 0; j < C::NB; ++j) { best[j] = -__builtin_inff(); arg[j] = 0x7FFFFFFF; }
+  for (int q = 0; q < Q; ++q) { best[q] = -__builtin_inff(); arg[q] = 0x7FFFFFFF; }
 
   f32x4 acc[C::MB][C::NB];
   auto set_tile = [&](int m0) { ml.set_a(W, m0, m0 + walk.h < walk.r1 ? m0 + walk.h : walk.r1, d, n_kt); };
@@ -944,40 +967,45 @@ k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, 
     }
     // a lower tile, the ragged last one among them: a logit of -inf is never drawn
     if (m0 + C::BM > end) fill_rows_past<C>(acc, m0 + at.row0(), end, -__builtin_inff());
-    // Rows outside, tokens inside: the first two Philox rounds multiply words that depend on the row block or on the token
-    // alone, and are shared over the other.
+    // Four tokens at a time, rows outside: the first two Philox rounds multiply words that depend on the row block or on the
+    // token alone, and are shared over the other.  (The column made anew for every tile: what depends on the token alone would be
+    // carried through the main loop otherwise, in registers that it does not have.)
+    const uint32_t t0 = Mainloop<C, ROWS>::fresh((int)n0 + at.col0());     // bf16 calls have fewer than 2^32 tokens
 #pragma unroll
-    for (int i = 0; i < C::MB; ++i) {
-      const int v0 = m0 + at.row0() + i * 16;          // multiple of 4: one Philox block
+    for (int q = 0; q < Q; ++q) {
+      float top[4];
+      int where[4];
 #pragma unroll
-      for (int j = 0; j < C::NB; ++j) {
-        const int64_t t = n0 + at.col0() + j * 16;
-        uint32_t x[4];
-        philox4x32_10((uint32_t)(v0 >> 2), (uint32_t)t, (uint32_t)(t >> 32), 0u, seed_lo, seed_hi, x);
+      for (int k = 0; k < 4; ++k) { top[k] = -__builtin_inff(); where[k] = 0x7FFFFFFF; }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float sc = __builtin_fmaf(acc[i][j][e], inv_temperature, gumbel_from_bits(x[e]));
-          if (sc > best[j]) { best[j] = sc; arg[j] = v0 + e; }   // indices rise: strict > keeps the smallest
+      for (int i = 0; i < C::MB; ++i) {
+        const int v0 = m0 + at.row0() + i * 16;          // multiple of 4: one Philox block
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int j = 4 * q + k;
+          if (j >= C::NB) continue;
+          uint32_t x[4];
+          philox4x32_10((uint32_t)(v0 >> 2), t0 + j * 16, 0u, 0u, seed_lo, seed_hi, x);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float sc = __builtin_fmaf(acc[i][j][e], inv_temperature, gumbel_from_bits(x[e]));
+            if (sc > top[k]) { top[k] = sc; where[k] = v0 + e; }   // indices rise: strict > keeps the smallest
+          }
         }
       }
+      float sc;
+      int v;
+      reduce4_better(top, where, sc, v);
+      if (sc > best[q]) { best[q] = sc; arg[q] = v; }     // ... from tile to tile too
     }
   }
 
-  // merge the four lane groups, then the WM waves stacked along the vocabulary (through LDS)
-#pragma unroll
-  for (int j = 0; j < C::NB; ++j)
-#pragma unroll
-    for (int o = 16; o < 64; o *= 2) {
-      const float so = __shfl_xor(best[j], o, 64);
-      const int io = __shfl_xor(arg[j], o, 64);
-      if (better(so, io, best[j], arg[j])) { best[j] = so; arg[j] = io; }
-    }
+  // merge the WM waves stacked along the vocabulary, through LDS
   typedef float f32x2 __attribute__((ext_vector_type(2)));
   __attribute__((address_space(3))) f32x2* red = (__attribute__((address_space(3))) f32x2*)smem;
-  if (at.g == 0) {
 #pragma unroll
-    for (int j = 0; j < C::NB; ++j) red[at.wm * C::BN + at.col0() + j * 16] = f32x2{best[j], __int_as_float(arg[j])};
-  }
+  for (int q = 0; q < Q; ++q)
+    if (4 * q + at.g < C::NB) red[at.wm * C::BN + at.col0() + (4 * q + at.g) * 16] = f32x2{best[q], __int_as_float(arg[q])};
   __syncthreads();
   for (int n_l = threadIdx.x; n_l < C::BN; n_l += C::NT) {
     if (n0 + n_l < T) {

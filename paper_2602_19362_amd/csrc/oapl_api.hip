@@ -27,11 +27,6 @@ typedef TileCfg<4, 2, 4, 12, 2, 0, true> CfgEarly;
 typedef TileCfg<2, 2, 4, 4, 2, kPackRowsB> CfgSmall;
 // ... and, where there are no more of them than CUs, with a ring of four stages.
 typedef TileCfg<2, 2, 4, 4, 4, kPackRowsB> CfgDeep;
-// The sampling kernel carries a running (score, index) pair per column through the main loop and
-// draws Philox blocks in its epilogue: its largest tile is 256 x 256 (128 accumulators per lane),
-// with H packed in 256-row blocks for it where it reads packed operands.
-typedef TileCfg<4, 2, 4, 8, 2> CfgSample;
-
 // Tiles of the scoring and sampling kernels over row-major operands.  A call of few tokens pays for every padded
 // token column and is bound by reading W once; a call of many is bound by operand delivery, which wants the largest
 // tile.  128 x 64 (48 KB of LDS, three workgroups per CU to keep W streaming through each other's barriers) serves up to 64 tokens,
@@ -40,7 +35,7 @@ typedef TileCfg<4, 2, 4, 8, 2> CfgSample;
 // tiles (V = 151936, 594 rows per CU: two tiles of 297 in place of three of 198).
 typedef TileCfg<4, 1, 2, 4, 2> Cfg64;
 typedef TileCfg<4, 2, 2, 4, 2> Cfg128;
-typedef CfgSample Cfg256;
+typedef TileCfg<4, 2, 4, 8, 2> Cfg256;
 typedef TileCfg<4, 2, 5, 8, 2> Cfg256Tall;
 // ... up to two token tiles over a W that the memory-side cache cannot hold wait for it to arrive: their loads go out as early
 // as they can. Early / spread, 200, 400 and 512 tokens: d = 4096, V = 48000 (375 MiB) sampling -5, -8, -5 %, scoring -5, -5, -4
@@ -64,8 +59,7 @@ typedef TileCfg<4, 2, 5, 8, 2, 0, true, true> Cfg256TallOnce;
 static bool once_pays(int64_t T, int V, int d) {
   return T <= Cfg256Once::BN && d % kPackK == 0 && (int64_t)V * d * 2 > (int64_t)288 << 20;
 }
-// Odd widths: the n-side block is 4.5 or 5.5 loads per wave, the last of them half of the waves'.  The 352-wide kernel has a
-// register too few (8 B of scratch, outside the k loop).
+// Odd widths: the n-side block is 4.5 or 5.5 loads per wave, the last of them half of the waves'.
 typedef TileCfg<4, 2, 4, 9, 2> Cfg288;
 typedef TileCfg<4, 2, 4, 10, 2> Cfg320;
 typedef TileCfg<4, 2, 4, 11, 2> Cfg352;
@@ -180,11 +174,17 @@ static TilePick pick_splits(FwdTile tile, int64_t T, int V, int max_splits, doub
 }
 
 // Tile and splits over row-major operands.  Up to 256 tokens the call is bound by reading W, and as many workgroups as the CUs
-// hold at once share its rows evenly. Beyond, the time of one 256-row tile at d = 4096 is in the ratio of 105 / 115.5 /
-// 126 / 138 / 150 for 256 / 288 / 320 / 352 / 384 columns (it scales with d): the wide tile is the cheapest per column, a
-// narrower one pads fewer columns. 256, 320 and 384 alone / all five: 350 tokens at d = 4096 433 / 403 us, 700 725 / 674, 777
-// 825 / 779, 1003 996 / 941, 1400 1412 / 1292, 2500 and more the same.
-static TilePick pick_tile(int64_t T, int V, int max_splits, bool scoring) {
+// hold at once share its rows evenly. Beyond, the wide tile is the cheapest per column and a narrower one pads fewer columns: the
+// time of one 256-row tile of 256 / 288 / 320 / 352 / 384 columns is in the ratio of kScoreCost (it scales with d), in sampling,
+// whose epilogue draws for every logit, of kSampleCost (8064 tokens, all rounds full, d = 4096 101 / 116 / 133 / 139 / 155 us, d =
+// 2048 55 / 63 / 71 / 75 / 85). Scoring with 256, 320 and 384 alone / all five: 350 tokens at d = 4096 433 / 403 us, 700 725 / 674,
+// 777 825 / 779, 1003 996 / 941, 1400 1412 / 1292, 2500 and more the same.  Sampling with 256 alone / all five, V = 151936: d = 4096, 300
+// tokens 563 / 396 us, 384 551 / 460, 600 775 / 656, 1003 1106 / 1009; d = 2048 292 / 230, 303 / 267, 421 / 364, 586 / 550.
+struct TileCosts {
+  double w256, w288, w320, w352, w384;
+};
+constexpr TileCosts kScoreCost{105.0, 115.5, 126.0, 138.0, 150.0}, kSampleCost{100.0, 115.0, 128.0, 137.0, 152.0};
+static TilePick pick_tile(int64_t T, int V, int max_splits, const TileCosts& cost) {
   auto workgroups = [&](int per_cu, int rows) {      // at most one per tile of `rows` rows
     const int tiles = (V + rows - 1) / rows, most = per_cu * kNumCU < max_splits ? per_cu * kNumCU : max_splits;
     return tiles < most ? tiles : most;
@@ -198,20 +198,29 @@ static TilePick pick_tile(int64_t T, int V, int max_splits, bool scoring) {
     return TilePick{kTile256, splits, true, tall * Cfg256Tall::BM < flat * Cfg256::BM};
   }
   double best_time, time;
-  TilePick best = pick_splits<Cfg256>(kTile256, T, V, max_splits, 105.0, &best_time);
-  if (!scoring) return best;
+  TilePick best = pick_splits<Cfg256>(kTile256, T, V, max_splits, cost.w256, &best_time);
   auto consider = [&](const TilePick& pick) {     // ties go to the wider tile
     if (time <= best_time) { best = pick; best_time = time; }
   };
-  consider(pick_splits<Cfg288>(kTile288, T, V, max_splits, 115.5, &time));
-  consider(pick_splits<Cfg320>(kTile320, T, V, max_splits, 126.0, &time));
-  consider(pick_splits<Cfg352>(kTile352, T, V, max_splits, 138.0, &time));
-  consider(pick_splits<Cfg>(kTile384, T, V, max_splits, 150.0, &time));
+  consider(pick_splits<Cfg288>(kTile288, T, V, max_splits, cost.w288, &time));
+  consider(pick_splits<Cfg320>(kTile320, T, V, max_splits, cost.w320, &time));
+  consider(pick_splits<Cfg352>(kTile352, T, V, max_splits, cost.w352, &time));
+  consider(pick_splits<Cfg>(kTile384, T, V, max_splits, cost.w384, &time));
   return best;
 }
 
 static TilePick pick_fwd(bool rows, int64_t T, int V, int max_splits) {
-  return rows ? pick_tile(T, V, max_splits, true) : pick_splits<Cfg>(kTile384, T, V, max_splits);
+  return rows ? pick_tile(T, V, max_splits, kScoreCost) : pick_splits<Cfg>(kTile384, T, V, max_splits);
+}
+
+// ... of the sampling kernel: over packed operands 256 or 384 columns (V = 151936, 256 alone / both: 12288 tokens at d = 4096 12.7 /
+// 11.3 ms, 32768 35.5 / 31.9; 16384 at d = 2048 8.16 in tiles of 256, 8.54 in tiles of 384).
+static TilePick pick_sample(bool rows, int64_t T, int V, int max_splits) {
+  if (rows) return pick_tile(T, V, max_splits, kSampleCost);
+  double narrow_time, wide_time;
+  const TilePick narrow = pick_splits<Cfg256>(kTile256, T, V, max_splits, kSampleCost.w256, &narrow_time);
+  const TilePick wide = pick_splits<Cfg>(kTile384, T, V, max_splits, kSampleCost.w384, &wide_time);
+  return narrow_time < wide_time ? narrow : wide;
 }
 
 // Time of `tiles` tiles with nk k-blocks each, in k-blocks of a 256 x 384 tile (1.5 .. 2 us): rounds of workgroups, with
@@ -336,7 +345,7 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
     p.rows = rows_pay(T, d);
     p.unaligned = p.rows ? unaligned : 0;
     if (!bwd) p.fwd = pick_fwd(p.rows, T, V, max_splits);
-    p.smp = p.rows ? pick_tile(T, V, max_splits, false) : pick_splits<CfgSample>(kTile256, T, V, max_splits);
+    p.smp = pick_sample(p.rows, T, V, max_splits);
     // Panel size: a multiple of the token tile, at most `cap` rows.  One panel if T fits; otherwise
     // the size (between half the cap and the cap) that costs the fewest rounds of kNumCU workgroups in
     // the dH contraction -- its tiles (d / 256 x panel rows / 384, each K = V long) are few and long, so
@@ -392,10 +401,10 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
   p.off_gw = take((size_t)((n_seq > 0 ? n_seq : 1) + n_groups) * 8);
   if (dtype == OAPL_BF16 && !p.rows) {
     p.off_Wp = take((size_t)p.n_rt_v * p.n_kt_d * kPackBlockBytesA);
-    {  // packed H: 384-row blocks, or 256-row blocks for the sampling kernel (whichever is larger)
+    {  // packed H: blocks of 384 rows, or of 256 for sampling in tiles of 256 columns (whichever is larger)
       const size_t a = (size_t)p.n_rt_T * p.n_kt_d * kPackBlockBytesB;
-      const size_t b = (size_t)((T + CfgSample::BN - 1) / CfgSample::BN > 0 ? (T + CfgSample::BN - 1) / CfgSample::BN : 1) *
-                       p.n_kt_d * CfgSample::STAGE_B;
+      const size_t b = (size_t)((T + Cfg256::BN - 1) / Cfg256::BN > 0 ? (T + Cfg256::BN - 1) / Cfg256::BN : 1) * p.n_kt_d *
+                       Cfg256::STAGE_B;
       p.off_Hp = take(a > b ? a : b);
     }
   }
@@ -533,7 +542,8 @@ static bool prepare_kernels() {
          allow_fwd<Cfg288, true>() && allow_fwd<Cfg320, true>() && allow_fwd<Cfg352, true>() &&
          allow_fwd<Cfg, true>() && allow_fwd<Cfg, false>() && allow_sample<Cfg64, true>() &&
          allow_sample<Cfg128, true>() && allow_sample<Cfg256, true>() && allow_sample<Cfg256Early, true>() &&
-         allow_sample<CfgSample, false>() &&
+         allow_sample<Cfg288, true>() && allow_sample<Cfg320, true>() && allow_sample<Cfg352, true>() &&
+         allow_sample<Cfg, true>() && allow_sample<Cfg256, false>() && allow_sample<Cfg, false>() &&
          allow_big_lds(k_fwd_lse<CfgRef, false, true>, CfgRef::LDS_BYTES) &&
          allow_big_lds(k_fwd_lse<CfgRef, false, false>, CfgRef::LDS_BYTES) &&
          allow_big_lds(k_sweep_begin<CfgRef, OaplBegin>, CfgRef::LDS_BYTES) &&
@@ -569,16 +579,18 @@ struct FwdArgs {
   TilePick pick;
 };
 
+// Token tiles per XCD patch of the streaming kernels: eight while a token tile's H strip is at most 3 MiB (384 columns: d <=
+// 4096), else four. Scoring 20000 tokens at d = 4096, walks of 3 tiles: 20.2 / 18.2 / 18.1 / 18.4 ms for patches of 1 / 4 / 8 / 16;
+// 30000 at d = 5120: 36.7 / 34.5 / 35.5 / 35.7; 20000 at d = 2048 10.19 / 9.15 / 9.18 / 9.28.
+template <class C>
+static int patch_tiles(int n_kt) { return (size_t)n_kt * C::STAGE_B <= ((size_t)3 << 20) ? 8 : 4; }
+
 // One streaming log-sum-exp pass (the plan's tile; ENT: with the entropy's partial sums in upart).
 template <class C, bool ENT, bool ROWS>
 static void launch_fwd_lse_kernel(const FwdArgs& a, float2* partials, float* upart, int* clear, hipStream_t st, Gate gate) {
   const int64_t total = (a.T + C::BN - 1) / C::BN * a.pick.splits;
   const unsigned grid = (unsigned)round_up(total, 8);
-  // token tiles per XCD patch: eight while a token tile's H strip is at most 3 MiB (384 columns: d <= 4096), else four.
-  // 20000 tokens at d = 4096, walks of 3 tiles: 20.2 / 18.2 / 18.1 / 18.4 ms for patches of 1 / 4 / 8 / 16; 30000 at
-  // d = 5120: 36.7 / 34.5 / 35.5 / 35.7; 20000 at d = 2048 10.19 / 9.15 / 9.18 / 9.28.
-  const int patch_tiles = (size_t)a.n_kt * C::STAGE_B <= ((size_t)3 << 20) ? 8 : 4;
-  k_fwd_lse<C, ENT, ROWS><<<grid, C::NT, C::LDS_BYTES, st>>>(a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, a.pick.balanced, patch_tiles,
+  k_fwd_lse<C, ENT, ROWS><<<grid, C::NT, C::LDS_BYTES, st>>>(a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, a.pick.balanced, patch_tiles<C>(a.n_kt),
                                                            partials, upart, clear, gate);
 }
 template <class C, bool ROWS>
@@ -610,11 +622,38 @@ static void launch_fwd_lse(const FwdArgs& a, bool rows, float2* partials, float*
   }
 }
 
+// ... of the sampling kernel: patches of 1 / 4 / 8 token tiles, V = 151936, us: d = 4096, 1003 tokens 1010 / 993 / 990, 4096 3904 / 3835 /
+// 3830, 6144 6170 / 5982 / 6064; d = 2048 554 / 551 / 542, 2115 / 2106 / 2086, 3339 / 3187 / 3291, 8192 4086 / 4044 / 4106.
+constexpr int kSamplePatch = 4;
 template <class C, bool ROWS>
 static void launch_sample(const FwdArgs& a, float inv_t, uint64_t seed, float2* partials, hipStream_t st) {
   const int64_t total = (a.T + C::BN - 1) / C::BN * a.pick.splits;
   k_fwd_sample<C, ROWS><<<(unsigned)round_up(total, 8), C::NT, C::LDS_BYTES, st>>>(
-      a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, a.pick.balanced, inv_t, (uint32_t)seed, (uint32_t)(seed >> 32), partials);
+      a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, a.pick.balanced, kSamplePatch, inv_t, (uint32_t)seed, (uint32_t)(seed >> 32), partials);
+}
+
+static void launch_sample(const FwdArgs& a, bool rows, float inv_t, uint64_t seed, float2* partials, hipStream_t st) {
+  if (!rows && a.pick.tile == kTile256) return launch_sample<Cfg256, false>(a, inv_t, seed, partials, st);
+  if (!rows) return launch_sample<Cfg, false>(a, inv_t, seed, partials, st);
+  const bool once = once_pays(a.T, a.V, a.d);
+  switch (a.pick.tile) {
+    case kTile64:
+      if (once) return launch_sample<Cfg64Once, true>(a, inv_t, seed, partials, st);
+      return launch_sample<Cfg64, true>(a, inv_t, seed, partials, st);
+    case kTile128:
+      if (once) return launch_sample<Cfg128Once, true>(a, inv_t, seed, partials, st);
+      return launch_sample<Cfg128, true>(a, inv_t, seed, partials, st);
+    case kTile256:
+      if (a.pick.tall && once) return launch_sample<Cfg256TallOnce, true>(a, inv_t, seed, partials, st);
+      if (a.pick.tall) return launch_sample<Cfg256Tall, true>(a, inv_t, seed, partials, st);
+      if (once) return launch_sample<Cfg256Once, true>(a, inv_t, seed, partials, st);
+      if (early_pays(a.T, a.V, a.d)) return launch_sample<Cfg256Early, true>(a, inv_t, seed, partials, st);
+      return launch_sample<Cfg256, true>(a, inv_t, seed, partials, st);
+    case kTile288: return launch_sample<Cfg288, true>(a, inv_t, seed, partials, st);
+    case kTile320: return launch_sample<Cfg320, true>(a, inv_t, seed, partials, st);
+    case kTile352: return launch_sample<Cfg352, true>(a, inv_t, seed, partials, st);
+    case kTile384: return launch_sample<Cfg, true>(a, inv_t, seed, partials, st);
+  }
 }
 
 static F32Operand f32_operand(const void* p, int64_t ld) {
@@ -1449,26 +1488,17 @@ int32_t oapl_sample_tokens(const void* H, const void* W, int64_t T, int32_t d, i
     if (!p.rows) {
       bf16_t* Wp = (bf16_t*)(ws + p.off_Wp);
       bf16_t* Hp = (bf16_t*)(ws + p.off_Hp);
-      k_pack_rows<<<dim3(p.n_kt_d, p.n_rt_v), 256, 0, st>>>(args.W, V, d, d, Wp, p.n_kt_d, CfgSample::BM);
+      k_pack_rows<<<dim3(p.n_kt_d, p.n_rt_v), 256, 0, st>>>(args.W, V, d, d, Wp, p.n_kt_d, Cfg::BM);
       OAPL_LAUNCH_CHECK();
-      k_pack_rows<<<dim3(p.n_kt_d, grid1d(T, CfgSample::BN)), 256, 0, st>>>(args.H, T, d, d, Hp, p.n_kt_d, CfgSample::BN);
+      const int rb = p.smp.tile == kTile256 ? Cfg256::BN : Cfg::BN;
+      k_pack_rows<<<dim3(p.n_kt_d, grid1d(T, rb)), 256, 0, st>>>(args.H, T, d, d, Hp, p.n_kt_d, rb);
       OAPL_LAUNCH_CHECK();
       args.W = Wp;
       args.H = Hp;
     }
     {
       ScopedKernelTimer tm(kFwdSample, st);
-      const bool once = once_pays(T, V, d);
-      if (!p.rows) launch_sample<CfgSample, false>(args, inv_t, seed, partials, st);
-      else if (p.smp.tile == kTile64 && once) launch_sample<Cfg64Once, true>(args, inv_t, seed, partials, st);
-      else if (p.smp.tile == kTile64) launch_sample<Cfg64, true>(args, inv_t, seed, partials, st);
-      else if (p.smp.tile == kTile128 && once) launch_sample<Cfg128Once, true>(args, inv_t, seed, partials, st);
-      else if (p.smp.tile == kTile128) launch_sample<Cfg128, true>(args, inv_t, seed, partials, st);
-      else if (p.smp.tall && once) launch_sample<Cfg256TallOnce, true>(args, inv_t, seed, partials, st);
-      else if (p.smp.tall) launch_sample<Cfg256Tall, true>(args, inv_t, seed, partials, st);
-      else if (once) launch_sample<Cfg256Once, true>(args, inv_t, seed, partials, st);
-      else if (early_pays(T, V, d)) launch_sample<Cfg256Early, true>(args, inv_t, seed, partials, st);
-      else launch_sample<Cfg256, true>(args, inv_t, seed, partials, st);
+      launch_sample(args, p.rows, inv_t, seed, partials, st);
     }
     OAPL_LAUNCH_CHECK();
   } else {

@@ -2,7 +2,7 @@
 import pytest
 
 from paper_2602_19362_amd import oapl
-from tests import test_gpu_dh_splits, test_gpu_f32_tiles, test_gpu_score_widths, test_gpu_small_tiles
+from tests import test_gpu_dh_splits, test_gpu_f32_tiles, test_gpu_sample_widths, test_gpu_score_widths, test_gpu_small_tiles
 from tests._plan import ask
 
 INT_MAX = 2 ** 31 - 1
@@ -120,3 +120,12 @@ def test_balanced_walks_cover_the_vocabulary(V, rows):
         n = min(per_cu * 256, (V + rows - 1) // rows)
         a = ask([f"walks {V} {n} {rows}"])[0]
         assert a["wrong"] == 0 and a["end"] == V and a["most"] - a["least"] <= 32
+
+
+def test_sampling_tiles_are_as_wide_as_the_tokens_need():
+    """The widths that the GPU test of the sampling tiles names."""
+    width = {2: 256, 3: 320, 4: 384, 5: 288, 6: 352}       # FwdTile
+    cases = test_gpu_sample_widths
+    for T, d, V, w, rows in cases.CASES:
+        p = ask([f"plan {T} {d} {V} 1 0 0 0 -1"])[0]
+        assert (width[p["smp_tile"]], p["rows"]) == (w, rows), (T, d, V, p)
