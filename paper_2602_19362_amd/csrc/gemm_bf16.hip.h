@@ -693,18 +693,18 @@ __device__ __forceinline__ void stage_mn_pk(lds_char_ptr smem, const uint32_t (&
 }
 
 // Chunk q staged by stage_mn_pk -> packed n-side matrix whose rows are the m index (global row
-// m0 + ..., blocks of PACK_B rows) and whose k index is n; n_kt is the destination's strip pitch in
-// k-blocks, kb0 the first k-block (n0 / 64).
+// m0 + ..., blocks of kPackRowsB rows whatever the tile) and whose k index is n; n_kt is the destination's strip pitch in
+// k-blocks, piece0 the first 16-byte piece of a row (n0 / 8: tiles of 288 and 352 columns end in the middle of a k-block).
 template <class C>
-__device__ __forceinline__ void store_mn_pk_packed(lds_char_ptr smem, bf16_t* base, int n_kt, int m0, int kb0, int q) {
+__device__ __forceinline__ void store_mn_pk_packed(lds_char_ptr smem, bf16_t* base, int n_kt, int m0, int piece0, int q) {
   constexpr int CH = C::BN / 8;
   for (int idx = threadIdx.x; idx < C::MN_ROWS * CH; idx += C::NT) {
     const int m_l = idx / CH, ch = idx % CH;
     const int m = m0 + (m_l >> 5) * C::WROWS + q * 32 + (m_l & 31);
-    const int blk = m / C::PACK_B, r = m - blk * C::PACK_B;
+    const int blk = m / kPackRowsB, r = m - blk * kPackRowsB, piece = piece0 + ch;
     const u32x4 v = *(const __attribute__((address_space(3))) u32x4*)(smem + m_l * C::PITCH_MN + ch * 16);
-    char* dst = (char*)base + ((int64_t)blk * n_kt + kb0 + (ch >> 3)) * C::PITCH_B;
-    *(u32x4*)(dst + r * kPackRowBytes + (ch & 7) * 16) = v;
+    char* dst = (char*)base + ((int64_t)blk * n_kt + (piece >> 3)) * kPackBlockBytesB;
+    *(u32x4*)(dst + r * kPackRowBytes + (piece & 7) * 16) = v;
   }
 }
 
@@ -719,7 +719,7 @@ __device__ __forceinline__ void store_both_copies(lds_char_ptr smem, const uint3
     if (q > 0) lds_barrier();
     stage_mn_pk<C>(smem, pk, q);
     lds_barrier();
-    store_mn_pk_packed<C>(smem, GTp, gt_n_kt, m0, (int)(n0 / kPackK), q);
+    store_mn_pk_packed<C>(smem, GTp, gt_n_kt, m0, (int)(n0 / 8), q);
   }
   store_nm_packed_direct<C>(pk, Gp, g_n_kt, n0, m0 / kPackK);
 }

@@ -107,6 +107,7 @@ struct Plan {
   unsigned unaligned = 0;   // ... but these (Unaligned) are copied to an aligned place first
   TilePick fwd;        // tile and vocabulary splits of the scoring kernel (splits = soft-max partials per token)
   bool small_sweep = false, small_dw = false;   // 128 x 128 tiles (one panel, operands in place)
+  int width = Cfg::BN;        // token columns of the large tiles of sweep, recompute and dH, and rows per block of packed G
   int n_vt = 0;        // vocabulary tiles of the sweep: row sums per token
   DhPick dh;           // the last panel's dH contraction
   bool grads_fused = false;   // ... shares its launch with dW's (bf16: both in 128 x 128 tiles; fp32: few workgroups)
@@ -257,17 +258,45 @@ static bool small_tiles_pay(const SmallRate& r, int64_t M, int64_t N, int nk) {
 // pick minimises their time plus the partial sums' way through memory (8 bytes per element and split).  Whole loss calls at
 // V = 151936, one workgroup per tile / the count chosen: 1003 tokens, d = 4096 3.99 / 3.47 ms (five splits);
 // 6007 tokens, d = 2048 10.77 / 8.80 ms (two); 30011 tokens at d = 5120, whose last panel has 1211, 107.3 / 104.6 ms.
-static DhPick pick_dh(int64_t nv, int d, int nk, bool allow_small, size_t scratch) {
-  DhPick best;
-  double best_time = 1e300;
-  for (int small = 0; small <= (allow_small ? 1 : 0); ++small) {
-    const int64_t tiles = small ? tile_count<CfgSmall>(d, nv) : tile_count<Cfg>(d, nv);
-    for (int s = 1; s <= 64 && (s == 1 || (s * 4 <= nk && (size_t)s * nv * d * 4 <= scratch)); ++s) {
-      const int k = (nk + s - 1) / s;
-      const double time = (small ? small_time(kSmallDh, tiles * s, k) : large_time(tiles * s, k)) +
-                          (s > 1 ? 5 + 1.2e-6 * (double)s * nv * d : 0.0);
-      if (time < best_time - 1e-9) { best_time = time; best.small = small != 0; best.splits = s; }
-    }
+template <class Time>
+static double pick_dh_splits(Time&& time_of, int64_t tiles, int64_t nv, int d, int nk, size_t scratch, int& splits) {
+  double best = 1e300;
+  for (int s = 1; s <= 64 && (s == 1 || (s * 4 <= nk && (size_t)s * nv * d * 4 <= scratch)); ++s) {
+    const double time = time_of(tiles * s, (nk + s - 1) / s) + (s > 1 ? 5 + 1.2e-6 * (double)s * nv * d : 0.0);
+    if (time < best - 1e-9) { best = time; splits = s; }
+  }
+  return best;
+}
+static DhPick pick_dh(int64_t nv, int d, int nk, bool allow_small, size_t scratch, double* time_out = nullptr) {
+  DhPick large, small{true, 1};
+  const double a = pick_dh_splits(large_time, tile_count<Cfg>(d, nv), nv, d, nk, scratch, large.splits);
+  const double b = !allow_small ? 1e300 : pick_dh_splits([](int64_t tiles, int k) { return small_time(kSmallDh, tiles, k); },
+                                                         tile_count<CfgSmall>(d, nv), nv, d, nk, scratch, small.splits);
+  if (time_out) *time_out = a < b ? a : b;
+  return b < a - 1e-9 ? small : large;
+}
+
+// Large tiles of one panel's sweep and dH (operands in place) may be narrower than 384 columns where that pads fewer tokens. A
+// k-block of theirs takes kLossScale of one of 384 columns': narrow tiles read W more often and gain less than their columns.
+// The ratios come from 133 shapes (T = 80 .. 3000, d = 1000 .. 5120, V = 32000 .. 151936), each timed at every width: with them
+// 131 choices are within 1 % of the best width, none is 1.6 % off it and none slower than 384.  384 / the width chosen, us, V =
+// 151936: d = 4096, 200 tokens 1481 / 1400 (256), 300 1595 / 1541 (320), 400 2152 / 1938 (256), 777 3150 / 2813 (288), 1003
+// 3469 / 3379 (352); d = 2048, 800 1748 / 1535 (288).  1003 tokens at d = 1800, V = 100000, 384 / 352 / 256: 1317 / 1298 / 1377.
+// Where the sweep runs in small tiles all widths lose (100 tokens at d = 4096: 1175 / 1275), so those calls keep them.
+struct LossScale { int width; double scale; };
+constexpr LossScale kLossScale[] = {{256, 0.80}, {288, 0.83}, {320, 0.86}, {352, 0.93}};
+static int pick_width(int64_t T, int d, int V, double now, size_t scratch, DhPick& dh) {
+  const int64_t mt_v = (V + Cfg::BM - 1) / Cfg::BM, mt_d = (d + Cfg::BM - 1) / Cfg::BM;
+  const int nk_d = (d + kPackK - 1) / kPackK, nk_v = (V + kPackK - 1) / kPackK;
+  int best = Cfg::BN;
+  for (const LossScale& c : kLossScale) {
+    const int64_t tiles = (T + c.width - 1) / c.width, columns = tiles * c.width;
+    // fewer columns than 384 would take (which the panel has room for), and all of the token blocks that dW walks
+    if (columns >= round_up(T, Cfg::BN) || columns < round_up(T, kPackK)) continue;
+    DhPick pick;
+    const double dh_time = pick_dh_splits(large_time, mt_d * tiles, T, d, nk_v, scratch, pick.splits);
+    const double time = c.scale * (large_time(mt_v * tiles, nk_d) + dh_time);
+    if (time < now - 1e-9) { now = time; best = c.width; dh = pick; }
   }
   return best;
 }
@@ -417,13 +446,16 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
       const size_t packed_w = (size_t)p.n_rt_v * p.n_kt_d * kPackBlockBytesA;
       const bool lean = max_splits == 1;
       const size_t part_bytes = lean ? 0 : (packed_w > kPartDhBytes ? packed_w : kPartDhBytes);
+      double dh_time = 0;
       if (!p.rows) p.dh = pick_dh(last, d, p.n_kt_v, false, packed_w);
-      else p.dh = pick_dh(last, d, p.n_kt_v, true, part_bytes);
+      else p.dh = pick_dh(last, d, p.n_kt_v, true, part_bytes, &dh_time);
       p.small_dw = p.rows && T <= p.Tp && small_tiles_pay(kSmallDw, d, V, (int)((T + kPackK - 1) / kPackK));
       p.grads_fused = p.small_dw && p.dh.small;
       if (p.grads_fused && dh_hides_behind_dw(p.n_kt_v, (int)((T + kPackK - 1) / kPackK))) p.dh.splits = 1;
-      p.off_part = p.rows && p.dh.splits > 1 ? take((size_t)p.dh.splits * last * d * 4) : p.off_Wp;
       p.small_sweep = p.rows && T <= p.Tp && !lean && small_tiles_pay(kSmallSweep, V, T, p.n_kt_d);
+      if (p.rows && T > 0 && T <= p.Tp && !lean && !p.small_sweep && !p.grads_fused)
+        p.width = pick_width(T, d, V, large_time(tile_count<Cfg>(V, T), p.n_kt_d) + dh_time, part_bytes, p.dh);
+      p.off_part = p.rows && p.dh.splits > 1 ? take((size_t)p.dh.splits * last * d * 4) : p.off_Wp;
       p.n_vt = p.small_sweep ? (V + CfgSmall::BM - 1) / CfgSmall::BM : p.n_rt_v;
       if (!p.rows) p.off_WTp = take((size_t)p.n_rt_d * p.n_kt_v * kPackBlockBytesA);
       p.off_HTp = take((size_t)p.n_rt_d * p.n_kt_t * kPackBlockBytesA);
@@ -525,6 +557,11 @@ template <class C, bool ATR>
 static bool allow_dh() {
   return allow_big_lds(k_bwd_dh<C, false, ATR>, C::LDS_BYTES) && allow_big_lds(k_bwd_dh<C, true, ATR>, C::LDS_BYTES);
 }
+// ... of a loss call in large tiles of C's width, operands in place
+template <class C>
+static bool allow_loss() {
+  return allow_big_lds(k_sweep<C, true>, C::LDS_BYTES) && allow_big_lds(k_bwd_dz<C, true>, C::LDS_BYTES) && allow_dh<C, true>();
+}
 template <class C>
 static bool allow_grads() {
   return allow_big_lds(k_bwd_dw<C>, C::LDS_BYTES) && allow_big_lds(k_bwd_grads<C, false>, C::LDS_BYTES) &&
@@ -548,11 +585,11 @@ static bool prepare_kernels() {
          allow_big_lds(k_fwd_lse<CfgRef, false, false>, CfgRef::LDS_BYTES) &&
          allow_big_lds(k_sweep_begin<CfgRef, OaplBegin>, CfgRef::LDS_BYTES) &&
          allow_big_lds(k_sweep_begin<CfgRef, GrpoBegin>, CfgRef::LDS_BYTES) &&
-         allow_big_lds(k_bwd_dz<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_bwd_dz<Cfg, true>, Cfg::LDS_BYTES) &&
-         allow_big_lds(k_sweep<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_sweep<Cfg, true>, Cfg::LDS_BYTES) &&
+         allow_big_lds(k_bwd_dz<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_sweep<Cfg, false>, Cfg::LDS_BYTES) &&
+         allow_loss<Cfg256>() && allow_loss<Cfg288>() && allow_loss<Cfg320>() && allow_loss<Cfg352>() && allow_loss<Cfg>() &&
          allow_big_lds(k_sweep<CfgEarly, true>, CfgEarly::LDS_BYTES) &&
          allow_big_lds(k_sweep<CfgSmall, true>, CfgSmall::LDS_BYTES) &&
-         allow_big_lds(k_sweep<CfgDeep, true>, CfgDeep::LDS_BYTES) && allow_dh<Cfg, false>() && allow_dh<Cfg, true>() &&
+         allow_big_lds(k_sweep<CfgDeep, true>, CfgDeep::LDS_BYTES) && allow_dh<Cfg, false>() &&
          allow_dh<CfgSmall, true>() && allow_dh<CfgDeep, true>() && allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
          allow_grads<CfgSmall>() && allow_grads<CfgDeep>();
   });
@@ -836,6 +873,16 @@ static int forward_finish(const Plan& p, const float* logq, float* logprob_out, 
   return OAPL_OK;
 }
 
+// Calls f with the large tile of that many columns.
+template <class F>
+static void for_width(int width, F&& f) {
+  if (width == Cfg256::BN) f(Cfg256{});
+  else if (width == Cfg288::BN) f(Cfg288{});
+  else if (width == Cfg320::BN) f(Cfg320{});
+  else if (width == Cfg352::BN) f(Cfg352{});
+  else f(Cfg{});
+}
+
 template <class C, bool SPLIT, bool ATR>
 static void launch_dh(const DhArgs& args, hipStream_t st, Gate gate) {
   const unsigned grid = (unsigned)round_up(tile_count<C>(args.d, args.n_valid) * (SPLIT ? args.splits : 1), 8);
@@ -889,7 +936,7 @@ static int launch_gradients(const Plan& p, DhArgs dh, const DwArgs& dw, bool las
     ScopedKernelTimer tm(kBwdDh, st, timed);
     if (small && dh_groups <= kNumCU) launch_dh<CfgDeep, true>(dh, split, st, gate);
     else if (small) launch_dh<CfgSmall, true>(dh, split, st, gate);
-    else if (p.rows) launch_dh<Cfg, true>(dh, split, st, gate);
+    else if (p.rows) for_width(p.width, [&](auto c) { launch_dh<decltype(c), true>(dh, split, st, gate); });
     else launch_dh<Cfg, false>(dh, split, st, gate);
   }
   OAPL_LAUNCH_CHECK();
@@ -936,10 +983,17 @@ static int recompute_panel(const Plan& p, const void* H, const void* W, const in
   const int kt = (int)((nv + kPackK - 1) / kPackK), blocks = kt * p.n_rt_d, n_pack = pack ? (blocks + 1) / 2 : 0;
   {
     ScopedKernelTimer tm(kBwdDz, st, gate.flag == nullptr);
-    (p.rows ? k_bwd_dz<Cfg, true> : k_bwd_dz<Cfg, false>)<<<
-        (unsigned)(n_pack + round_up(p.n_rt_v * ((nv + Cfg::BN - 1) / Cfg::BN), 8)), Cfg::NT, Cfg::LDS_BYTES, st>>>(
-        x.W, x.H + t0 * x.ld, p.V, nv, p.d, p.n_kt_d, tokens + t0, (const float*)(ws + p.off_lse2) + t0,
-        (const float*)(ws + p.off_inv) + t0, G, p.n_kt_g, GT, p.n_kt_t, gate, n_pack, scaled_rows(p, H, t0, ws), kt, blocks);
+    const PackTransposed rows = scaled_rows(p, H, t0, ws);
+    auto launch = [&](auto kernel, int BN, int threads, int lds) {
+      kernel<<<(unsigned)(n_pack + round_up(p.n_rt_v * ((nv + BN - 1) / BN), 8)), threads, lds, st>>>(
+          x.W, x.H + t0 * x.ld, p.V, nv, p.d, p.n_kt_d, tokens + t0, (const float*)(ws + p.off_lse2) + t0,
+          (const float*)(ws + p.off_inv) + t0, G, p.n_kt_g, GT, p.n_kt_t, gate, n_pack, rows, kt, blocks);
+    };
+    if (!p.rows) launch(k_bwd_dz<Cfg, false>, Cfg::BN, Cfg::NT, Cfg::LDS_BYTES);
+    else for_width(p.width, [&](auto c) {
+      typedef decltype(c) C;
+      launch(k_bwd_dz<C, true>, C::BN, C::NT, C::LDS_BYTES);
+    });
   }
   OAPL_LAUNCH_CHECK();
   return OAPL_OK;
@@ -1105,6 +1159,10 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
       const bf16_t* Ht = x.H + t0 * x.ld;
       if (p.small_sweep && tile_count<CfgDeep>(V, nv) <= kNumCU)
         launch_sweep<CfgDeep, true>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
+      else if (p.width != Cfg::BN)
+        for_width(p.width, [&](auto c) {
+          launch_sweep<decltype(c), true>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
+        });
       else if (!p.small_sweep && p.rows && (nv <= Cfg::BN || tile_count<Cfg>(V, nv) <= kNumCU))
         launch_sweep<CfgEarly, true>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
       else if (p.small_sweep) launch_sweep<CfgSmall, true>(p, x.W, Ht, nv, ref2 + t0, Gbuf(k), GTbuf(k), spart, st, fast);
@@ -1114,7 +1172,7 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
     OAPL_LAUNCH_CHECK();
     k_sweep_finish<<<grid1d(nv, kFinishRows), kFinishSlices * kFinishRows, 0, st>>>(
         spart, p.n_vt, p.Tp, nv, ref2 + t0, zy + t0, logq + t0, tokens + t0, V,
-        logprob_out ? logprob_out + t0 : nullptr, diff + t0, nis + t0, Gbuf(k), p.n_kt_g, GTbuf(k), p.n_kt_t,
+        logprob_out ? logprob_out + t0 : nullptr, diff + t0, nis + t0, Gbuf(k), p.width, p.n_kt_g, GTbuf(k), p.n_kt_t,
         (int*)(ws + p.off_status), fast);
     OAPL_LAUNCH_CHECK();
     return OAPL_OK;

@@ -576,7 +576,7 @@ __global__ void __launch_bounds__(kFinishSlices * kFinishRows)
 k_sweep_finish(const float* __restrict__ spart, int n_vt, int64_t ld_s, int64_t n_valid,
                const float* __restrict__ ref2, const float* __restrict__ zy, const float* __restrict__ logq,
                const int32_t* __restrict__ tokens, int V, float* __restrict__ logprob_out,
-               double* __restrict__ diff, float* __restrict__ nis, bf16_t* __restrict__ Gp, int g_n_kt,
+               double* __restrict__ diff, float* __restrict__ nis, bf16_t* __restrict__ Gp, int g_rows, int g_n_kt,
                bf16_t* __restrict__ GTp, int gt_n_kt, int* __restrict__ status, Gate gate) {
   if (gate_closed(gate)) return;
   // kFinishRows token rows per workgroup; the tile sums of a row are added in kFinishSlices interleaved slices
@@ -612,11 +612,11 @@ k_sweep_finish(const float* __restrict__ spart, int n_vt, int64_t ld_s, int64_t 
     // error (<= 2^-8) moves to the row's other entries, whose joint weight in the gradient is small.
     const double kept = (double)(float)patch;
     if (kept != 0.0 && isfinite(entry)) row_factor *= entry / kept;
-    // both copies are n-side operands: blocks of kPackRowsB rows x 64 k
+    // both copies are n-side operands: blocks of g_rows tokens and of kPackRowsB vocabulary rows x 64 k
     const int64_t blk = (int64_t)kPackRowsB * kPackK;             // elements of a packed block
-    const int64_t nb = n / kPackRowsB, nr = n - nb * kPackRowsB;  // token row block / row inside it
+    const int64_t nb = n / g_rows, nr = n - nb * g_rows;          // token row block / row inside it
     const int yb = y / kPackRowsB, yr = y - yb * kPackRowsB;      // vocabulary row block / row inside it
-    Gp[(nb * g_n_kt + (y >> 6)) * blk + nr * kPackK + (y & 63)] = patch;
+    Gp[((nb * g_n_kt + (y >> 6)) * g_rows + nr) * kPackK + (y & 63)] = patch;
     GTp[((int64_t)yb * gt_n_kt + (n >> 6)) * blk + (int64_t)yr * kPackK + (n & 63)] = patch;
   }
   if (y < 0 || y >= V) record_token_error(status);

@@ -2,7 +2,7 @@
 import pytest
 
 from paper_2602_19362_amd import oapl
-from tests import test_gpu_dh_splits, test_gpu_f32_tiles, test_gpu_sample_widths, test_gpu_score_widths, test_gpu_small_tiles
+from tests import test_gpu_dh_splits, test_gpu_f32_tiles, test_gpu_loss_widths, test_gpu_sample_widths, test_gpu_score_widths, test_gpu_small_tiles
 from tests._plan import ask
 
 INT_MAX = 2 ** 31 - 1
@@ -73,6 +73,16 @@ def test_gpu_cases_have_the_plans_they_name(dtype, cases):
     plans = ask([f"plan {T} {d} {V} {dtype} 1 {cap} 0 -1" for T, d, V, cap, _ in cases])
     for (T, d, V, cap, want), plan in zip(cases, plans):
         assert plan["rc"] == 0 and {k: plan[k] for k in want} == want, (T, d, V, cap, plan)
+
+
+def test_loss_tiles_are_as_wide_as_the_tokens_need():
+    """The widths that the GPU test of the loss tiles names; small sweeps, packed operands and capped panels keep 384."""
+    d, V = test_gpu_loss_widths.D, test_gpu_loss_widths.V
+    plans = ask([f"plan {T} {d} {V} 1 1 0 0 -1" for T, _ in test_gpu_loss_widths.CASES])
+    assert [p["width"] for p in plans] == [w for _, w in test_gpu_loss_widths.CASES]
+    for q in ("plan 100 4096 151936 1 1 0 0 -1", "plan 8193 4096 151936 1 1 0 0 -1", "plan 777 1000 50003 1 1 384 0 -1",
+              "plan 0 1000 50003 1 1 0 0 -1"):
+        assert ask([q])[0]["width"] == 384, q
 
 
 def test_scoring_tiles_are_as_wide_as_the_tokens_need():
