@@ -16,6 +16,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
+typedef __attribute__((address_space(3))) char* lds_char_ptr;
 
 // 16 bytes of a caller's bf16 matrix, which may start at any element.
 __device__ __forceinline__ u32x4 load_any16(const bf16_t* p) {

@@ -102,8 +102,6 @@ struct TileCfg {
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of one CU");
 };
 
-typedef __attribute__((address_space(3))) char* lds_char_ptr;
-
 // s_waitcnt immediate for "at most n vector-memory operations still outstanding" (gfx9 encoding:
 // vmcnt in bits [3:0] and [15:14]; expcnt and lgkmcnt fields left at their maximum = no wait).
 __host__ __device__ constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }

@@ -1,18 +1,25 @@
-// fp32 contractions of the OAPL loss head on the matrix cores (v_mfma_f32_32x32x2_f32: fp32 products and sums).
+// fp32 contractions of the OAPL loss head, on the bf16 matrix cores: C[m][n] = sum_k A(m, k) * B(n, k).
 //
-// C[m][n] = sum_k A(m, k) * B(n, k).  Each operand comes either with k contiguous in memory (H and W for the logits,
-// dZ^T for dW) or with its row index contiguous (dZ^T and W for dH, H for dW); it lies in the LDS the way it lies in
-// memory, so nothing is transposed on the way, and the two orders differ only in how a lane picks its fragment:
-//   k contiguous:    [row][BK + 4 floats]; one 16-byte read gives a lane four k of its row (16 lanes: 16 bank groups)
-//   rows contiguous: [k][rows + 8 floats]; four 4-byte reads, 32 lanes on one row of 128 bytes, the halves 32 banks apart
-// A fragment's four k are 8g + 4 * (lane / 32) + 0..3; multiplication e takes element e of both operands, so the sum over
-// k is taken in another order than 0, 1, 2, ...: the same multiset of products.
+// An fp32 number is the sum of three bf16 numbers, each the rounding of what the ones before leave (24 bits; the signs of the
+// later parts make up for the bits between): x = x0 + x1 + x2, to the bit.  Of the nine products of two such sums six are taken,
+//     x0 y0  +  (x0 y1 + x1 y0)  +  (x1 y1 + x0 y2 + x2 y0),
+// and what is left out, x1 y2 + x2 y1 + x2 y2, is at most 2^-26 |x y|, a quarter of what an fp32 product's own rounding may be.
+// (Numbers below 2^-110 are held to 2^-134, half the least bf16 number: a thirty-fourth decimal place.)
+// v_mfma_f32_32x32x16_bf16 does a product exactly and sixteen times as fast as v_mfma_f32_32x32x2_f32 does an fp32 one.  The first
+// products are added up apart from the others: a matrix core's addition cuts addends far below its result off downwards (-0.003
+// ulp on average), which five times as many additions into the large sum turned into a bias of 2e-7 of a token's log-prob (with
+// two sums 2e-8).  Against fp64, relative errors of log-probs fp32 multiplications / here: 256 tokens at d = 64, V = 1024 3.3e-7
+// / 1.6e-7, 1501 at d = 768, V = 8192 6.9e-7 / 2.6e-7; of dW 5.5e-6 / 4.0e-6, 1.2e-5 / 4.9e-6; over 14 shapes up to those 0.42 and
+// 0.57 times.
 //
-// Bound by the matrix cores (256 flop per clock and CU, 64 clocks per instruction and SIMD) as soon as a few workgroups
-// sit on every CU: a 128 x 128 tile needs 8 bytes of operands per clock.  The earlier 64 x 64 tile of plain FMAs was
-// bound by its 4-byte LDS reads: a loss call of 1501 tokens at d = 768, V = 8192 took 2.99 ms with it and takes 0.59 ms
-// (about 95 TFLOP/s in each contraction; the matrix cores are 66 % busy at 2.4 GHz), one of 256 tokens at d = 64, V = 1024 242
-// us and now 35 us.
+// Each operand comes either with k contiguous in memory (H and W for the logits, dZ^T for dW) or with its row index contiguous
+// (dZ^T and W for dH, H for dW); in the LDS its parts lie with k contiguous, as the fragments want them.  A thread splits
+// what it loaded before it writes it there (11 vector operations for two numbers), once for all that read it.
+//
+// The matrix cores are busy about half of the time. What bounds it is the sum of things that share a SIMD and its clock: the
+// contraction of 8192 x 1024 x 768 takes 69 us, 67 without loads, 53 without splitting and LDS writes either (multiplications
+// and fragments alone, at 1.8 GHz, where the power limit holds those).  A loss call of 1501 tokens at d = 768, V = 8192 takes 401 us; with fp32
+// multiplications, whose matrix cores were 66 % busy, 590, with plain FMAs 2990.
 #pragma once
 
 #include "common.hip.h"
@@ -24,152 +31,315 @@ namespace oapl {
 struct F32Operand {
   const float* p;
   int64_t ld;    // elements between rows (k contiguous) or between k (rows contiguous)
-  bool vec;      // 16-byte loads: p 16-byte aligned and ld a multiple of 4
+  bool vec;      // p 16-byte aligned and ld a multiple of 4
 };
 
-// WM x WN wavefronts (4 in all), each TM x TN blocks of 32 x 32; BK k per LDS stage.
-template <int WM_, int WN_, int TM_, int TN_, int BK_>
+// WM x WN wavefronts, each TM x TN blocks of 32 x 32; BK k per LDS stage.
+template <int WM_, int WN_, int TM_, int TN_>
 struct F32Cfg {
-  static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, BK = BK_;
-  static constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
-  static_assert(WM * WN == 4 && BK % 8 == 0, "256 threads, whole groups of eight k");
-  // workgroups that the registers of a shared launch must leave room for on a CU: of the large tile four, as many as the LDS
-  // does (left alone it takes 130 registers and leaves room for three); the small one's 81 leave that room unasked
-  static constexpr int kPerCU = BM * BN >= 128 * 128 ? 4 : 2;
+  static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, BK = 32;
+  static constexpr int BM = WM * TM * 32, BN = WN * TN * 32, NT = WM * WN * 64;
+  static constexpr int STAGE_A = 3 * BM * BK * 2, STAGE_B = 3 * BN * BK * 2;   // LDS bytes of one stage
+  // eight wavefronts, a CU to themselves, have two stages
+  static constexpr bool TWO_STAGES = WM * WN == 8;
+  static constexpr int LDS = (TWO_STAGES ? 2 : 1) * (STAGE_A + STAGE_B);
+  static_assert(WM * WN == 4 || TWO_STAGES, "256 or 512 threads");
+  static_assert(LDS <= 160 * 1024, "LDS of one CU");
 };
-typedef F32Cfg<2, 2, 2, 2, 16> F32Large;   // 128 x 128, 40 KB of LDS
-typedef F32Cfg<2, 2, 1, 1, 32> F32Small;   // 64 x 64, 36 KB
-typedef F32Cfg<1, 4, 2, 1, 32> F32Flat;    // 64 x 128, 54 KB: logits of few tokens (a wavefront still owns 64 vocabulary rows)
+typedef F32Cfg<4, 2, 2, 2> F32Wide;    // 256 x 128, 144 KB of LDS
+typedef F32Cfg<2, 2, 2, 2> F32Large;   // 128 x 128, 48 KB
+typedef F32Cfg<2, 2, 1, 1> F32Small;   // 64 x 64, 24 KB
+typedef F32Cfg<1, 4, 2, 1> F32Flat;    // 64 x 128, 36 KB: logits of few tokens (a wavefront still owns 64 vocabulary rows)
 
-// One operand's ROWS x BK stage: global -> registers -> LDS.
-template <int ROWS, int BK, bool KC>
-struct F32Stage {
-  static constexpr int PITCH = KC ? BK + 4 : ROWS + 8;
-  static constexpr int FLOATS = KC ? ROWS * PITCH : BK * PITCH;
-  static constexpr int N = ROWS * BK / 4 / 256;     // 4-float pieces per thread
-  f32x4 v[N];
-
-  __device__ __forceinline__ void load(const F32Operand& o, int64_t r0, int64_t R, int64_t k0, int64_t k_end) {
+// The bf16 parts of two fp32 numbers, packed: x = hi + mid + lo.
+struct F32Parts {
+  uint32_t hi, mid, lo;
+};
+__device__ __forceinline__ uint32_t f32_bf16_pair(float x0, float x1) {
+  const bf16x2 v = {(bf16_t)x0, (bf16_t)x1};
+  uint32_t u = __builtin_bit_cast(uint32_t, v);
+  asm("" : "+v"(u));     // or the compiler converts x0 a second time, alone, for the difference
+  return u;
+}
+__device__ __forceinline__ F32Parts f32_split(float x0, float x1) {
+  F32Parts p;
+  p.hi = f32_bf16_pair(x0, x1);
+  const float r0 = x0 - __uint_as_float(p.hi << 16), r1 = x1 - __uint_as_float(p.hi & 0xFFFF0000u);
+  p.mid = f32_bf16_pair(r0, r1);
+  p.lo = f32_bf16_pair(r0 - __uint_as_float(p.mid << 16), r1 - __uint_as_float(p.mid & 0xFFFF0000u));
+  return p;
+}
+// Numbers that round to an infinite bf16: a finite one's first part is the largest bf16, and an infinite one is 1 + 0 +
+// infinity, so that its product with y is y's sign times infinity, NaN for y = 0, whatever y's own parts are.
+constexpr float kBf16Max = 3.3895313892515355e38f;
+__device__ __forceinline__ F32Parts f32_split_huge(float x0, float x1) {
+  float part[3][2];
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int idx = threadIdx.x + i * 256;
-      const int64_t r = r0 + (KC ? idx / (BK / 4) : idx % (ROWS / 4) * 4);
-      const int64_t k = k0 + (KC ? idx % (BK / 4) * 4 : idx / (ROWS / 4));
-      const float* p = o.p + (KC ? r * o.ld + k : k * o.ld + r);
-      const bool whole = KC ? r < R && k + 4 <= k_end : k < k_end && r + 4 <= R;
-      if (o.vec && whole) {
-        v[i] = *(const f32x4*)p;
+  for (int e = 0; e < 2; ++e) {
+    const float x = e == 0 ? x0 : x1;
+    const bool inf = fabsf(x) == __builtin_inff();
+    const float hi = inf ? copysignf(1.f, x) : fabsf(x) > kBf16Max ? copysignf(kBf16Max, x) : (float)(bf16_t)x;
+    const float mid = inf ? 0.f : (float)(bf16_t)(x - hi);
+    part[0][e] = hi;
+    part[1][e] = mid;
+    part[2][e] = inf ? x : x - hi - mid;
+  }
+  return F32Parts{f32_bf16_pair(part[0][0], part[0][1]), f32_bf16_pair(part[1][0], part[1][1]),
+                  f32_bf16_pair(part[2][0], part[2][1])};
+}
+
+// One operand's ROWS x 32 stage by NT threads: global -> registers -> three planes of bf16 parts in LDS, [row][k] whatever the
+// order in memory.  A thread has pieces of four k of one row.  k contiguous: eight lanes load the 128 bytes of a row, a
+// line, by 16 (by 32 in two loads every line is asked for twice).  Rows contiguous: 64 lanes load 64 rows of one k, and two
+// pieces, eight k, are written at once.  16-byte chunk c of row r lies at chunk c ^ (r / 4 % 4): 16 lanes that read one chunk
+// of consecutive rows, or write one, or write whole rows, touch all banks.
+template <int ROWS, int NT, bool KC>
+struct F32Stage {
+  static constexpr int PITCH = 64, PLANE = ROWS * PITCH;
+  static constexpr int N = ROWS * 8 / NT;     // pieces per thread
+  static __device__ __forceinline__ int at(int row, int c) { return row * PITCH + ((c ^ ((row >> 2) & 3)) << 4); }
+  const float* p[KC ? N : N / 2];   // KC: this thread's piece of the next stage; else the wavefront's, from the tile's first row
+  f32x4 v[N];
+  u32x2 hi[N], mid[N], lo[N];
+  int64_t ld;
+  uint32_t lane_row;        // not KC: the thread's row in the tile
+  int wave;
+
+  // not KC: chunk i of this wavefront
+  __device__ __forceinline__ int chunk(int i) const { return wave * 64 / ROWS + i * (NT / ROWS); }
+  // Rows past the matrix are its last row again: what they give is not stored.
+  __device__ __forceinline__ void init(const F32Operand& o, int64_t r0, int64_t R, int64_t k0) {
+    ld = o.ld;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int last = (int)(R - r0 < ROWS ? R - r0 : ROWS) - 1;
+    if constexpr (KC) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const int row = (threadIdx.x + i * NT) >> 3;
+        p[i] = o.p + (r0 + (row < last ? row : last)) * ld + k0 + (threadIdx.x & 7) * 4;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < N / 2; ++i) p[i] = o.p + (k0 + chunk(i) * 8) * ld + r0;
+      const int row = threadIdx.x % ROWS;
+      lane_row = (uint32_t)(row < last ? row : last);
+    }
+  }
+  // The next stage, of which `left` k exist; leaves the pointers at the one behind it.  k past the end are zeros.
+  __device__ __forceinline__ void load(int64_t left) {
+    if constexpr (KC) {
+      if (left >= 32) {
+        typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = *(const f32x4_any*)p[i];
       } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const bool ok = KC ? r < R && k + e < k_end : k < k_end && r + e < R;
-          v[i][e] = ok ? p[e] : 0.f;
-        }
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[i][e] = (int)(threadIdx.x & 7) * 4 + e < left ? p[i][e] : 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < N; ++i) p[i] += 32;
+    } else {
+#pragma unroll
+      for (int i = 0; i < N / 2; ++i) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          v[2 * i + e / 4][e % 4] = left >= 32 || chunk(i) * 8 + e < left ? (p[i] + e * ld)[lane_row] : 0.f;
+        p[i] += 32 * ld;
       }
     }
   }
-  __device__ __forceinline__ void store(float* s) const {
+  __device__ __forceinline__ void split() {
+    float big = 0.f;
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int idx = threadIdx.x + i * 256;
-      const int a = KC ? idx / (BK / 4) * PITCH + idx % (BK / 4) * 4 : idx / (ROWS / 4) * PITCH + idx % (ROWS / 4) * 4;
-      *(f32x4*)(s + a) = v[i];
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const float x0 = v[i][2 * e], x1 = v[i][2 * e + 1];
+        const F32Parts x = f32_split(x0, x1);
+        hi[i][e] = x.hi;
+        mid[i][e] = x.mid;
+        lo[i][e] = x.lo;
+        asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(big) : "v"(x0), "v"(x1));   // (fmaxf quiets its inputs first)
+      }
+    if (__builtin_expect(big > kBf16Max, 0)) {
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const F32Parts x = f32_split_huge(v[i][2 * e], v[i][2 * e + 1]);
+          hi[i][e] = x.hi;
+          mid[i][e] = x.mid;
+          lo[i][e] = x.lo;
+        }
     }
   }
-  // four k of row `row` (of the tile) in group g of eight, for this lane's half
-  static __device__ __forceinline__ f32x4 fragment(const float* s, int row, int g, int half) {
-    if (KC) return *(const f32x4*)(s + row * PITCH + g * 8 + half * 4);
-    f32x4 f;
+  __device__ __forceinline__ void store(lds_char_ptr s) const {
+    typedef __attribute__((address_space(3))) u32x2* piece;
+    typedef __attribute__((address_space(3))) u32x4* pieces;
+    if constexpr (KC) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) f[e] = s[(g * 8 + half * 4 + e) * PITCH + row];
-    return f;
+      for (int i = 0; i < N; ++i) {
+        const lds_char_ptr d = s + at((threadIdx.x + i * NT) >> 3, (threadIdx.x & 7) >> 1) + (threadIdx.x & 1) * 8;
+        *(piece)d = hi[i];
+        *(piece)(d + PLANE) = mid[i];
+        *(piece)(d + 2 * PLANE) = lo[i];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < N / 2; ++i) {
+        const lds_char_ptr d = s + at(threadIdx.x % ROWS, chunk(i));
+        *(pieces)d = __builtin_shufflevector(hi[2 * i], hi[2 * i + 1], 0, 1, 2, 3);
+        *(pieces)(d + PLANE) = __builtin_shufflevector(mid[2 * i], mid[2 * i + 1], 0, 1, 2, 3);
+        *(pieces)(d + 2 * PLANE) = __builtin_shufflevector(lo[2 * i], lo[2 * i + 1], 0, 1, 2, 3);
+      }
+    }
   }
 };
 
 // Row inside a 32 x 32 block of accumulator register r, before the lane-half term 4 * (lane / 32); the column is lane % 32.
 __device__ __forceinline__ constexpr int f32_acc_row(int r) { return 8 * (r >> 2) + (r & 3); }
 
-// LDS of a tile: two stages of each operand.
-template <class C, bool A_KC>
-constexpr int f32_lds_a() { return 2 * F32Stage<C::BM, C::BK, A_KC>::FLOATS; }
-template <class C, bool B_KC>
-constexpr int f32_lds_b() { return 2 * F32Stage<C::BN, C::BK, B_KC>::FLOATS; }
 constexpr int larger(int a, int b) { return a > b ? a : b; }
 
-// Tile at block (bx, by, bz): x and y = row and column tiles in the order the epilogue names, z = one of `nz` splits of k in
-// whole stages.
+// Tile at block (bx, by, bz): x and y = column and row of tiles, z = one of `nz` splits of k in whole stages.
 template <class C, bool A_KC, bool B_KC, class Epi>
 __device__ __forceinline__ void gemm_f32_tile(const F32Operand& A, const F32Operand& B, int64_t M, int64_t N, int64_t K,
                                               const Epi& epi, unsigned bx, unsigned by, unsigned bz, unsigned nz,
-                                              float* lds_a, float* lds_b) {
-  typedef F32Stage<C::BM, C::BK, A_KC> SA;
-  typedef F32Stage<C::BN, C::BK, B_KC> SB;
-  float (*As)[SA::FLOATS] = (float (*)[SA::FLOATS])lds_a;
-  float (*Bs)[SB::FLOATS] = (float (*)[SB::FLOATS])lds_b;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+                                              char* lds_raw) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef F32Stage<C::BM, C::NT, A_KC> SA;
+  typedef F32Stage<C::BN, C::NT, B_KC> SB;
+  constexpr int STAGE = C::STAGE_A + C::STAGE_B;
+  const lds_char_ptr lds = (lds_char_ptr)lds_raw;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
   const int wm = wave / C::WN, wn = wave % C::WN;
-  const int64_t m0 = (int64_t)(Epi::kRowsOnX ? bx : by) * C::BM;
-  const int64_t n0 = (int64_t)(Epi::kRowsOnX ? by : bx) * C::BN;
+  const int64_t m0 = (int64_t)by * C::BM, n0 = (int64_t)bx * C::BN;
   const int64_t stages = (K + C::BK - 1) / C::BK;
-  const int64_t kb = stages * bz / nz * C::BK;
-  int64_t ke = stages * (bz + 1) / nz * C::BK;
-  ke = ke < K ? ke : K;
+  const int64_t s0 = stages * bz / nz;
+  const int n_stages = (int)(stages * (bz + 1) / nz - s0);
+  const int64_t kb = s0 * C::BK, len = K - kb;
 
-  f32x16 acc[C::TM][C::TN];
+  // acc: the products of the first parts; small: the others, 2^-8 of those and less
+  f32x16 acc[C::TM][C::TN], small[C::TM][C::TN];
 #pragma unroll
   for (int i = 0; i < C::TM; ++i)
 #pragma unroll
     for (int j = 0; j < C::TN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = small[i][j][r] = 0.f;
 
   SA sa;
   SB sb;
-  if (kb < ke) {
-    sa.load(A, m0, M, kb, ke);
-    sb.load(B, n0, N, kb, ke);
-    sa.store(As[0]);
-    sb.store(Bs[0]);
-  }
-  __syncthreads();
-  int cur = 0;
-  for (int64_t k = kb; k < ke; k += C::BK) {
-    const bool more = k + C::BK < ke;
-    if (more) {     // the next stage's loads travel while this one is multiplied
-      sa.load(A, m0, M, k + C::BK, ke);
-      sb.load(B, n0, N, k + C::BK, ke);
+  sa.init(A, m0, M, kb);
+  sb.init(B, n0, N, kb);
+  auto load = [&](int s) {
+    sa.load(len - (int64_t)s * C::BK);
+    sb.load(len - (int64_t)s * C::BK);
+  };
+  auto split = [&] {
+    sa.split();
+    sb.split();
+  };
+  auto store = [&](lds_char_ptr to) {
+    sa.store(to);
+    sb.store(to + C::STAGE_A);
+  };
+  const int fa = SA::at(wm * C::TM * 32 + (lane & 31), half), fb = C::STAGE_A + SB::at(wn * C::TN * 32 + (lane & 31), half);
+  auto multiply = [&](const lds_char_ptr from) {
+    typedef const __attribute__((address_space(3))) bf16x8* fragment;
+    bf16x8 a[2][C::TM], b[2][C::TN], am[C::TM], bm[C::TN], al[C::TM], bl[C::TN];
+    auto read = [&](bf16x8 (&x)[C::TM], bf16x8 (&y)[C::TN], const int ks, const int q) {
+#pragma unroll
+      for (int i = 0; i < C::TM; ++i) x[i] = *(fragment)(from + (fa ^ (ks << 5)) + q * SA::PLANE + i * 32 * SA::PITCH);
+#pragma unroll
+      for (int j = 0; j < C::TN; ++j) y[j] = *(fragment)(from + (fb ^ (ks << 5)) + q * SB::PLANE + j * 32 * SB::PITCH);
+    };
+    auto products = [&](f32x16 (&to)[C::TM][C::TN], const bf16x8 (&x)[C::TM], const bf16x8 (&y)[C::TN]) {
+#pragma unroll
+      for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::TN; ++j) to[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[i], y[j], to[i][j], 0, 0, 0);
+    };
+    // fragments are requested eight multiplications and more ahead, but for a stage's first
+    read(a[0], b[0], 0, 0);
+    read(am, bm, 0, 1);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      read(al, bl, ks, 2);
+      __builtin_amdgcn_sched_barrier(0);
+      products(acc, a[ks], b[ks]);
+      products(small, a[ks], bm);
+      products(small, am, b[ks]);
+      products(small, am, bm);
+      __builtin_amdgcn_sched_barrier(0);
+      if (ks == 0) {
+        read(a[1], b[1], 1, 0);
+        read(am, bm, 1, 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      products(small, a[ks], bl);
+      products(small, al, b[ks]);
+      __builtin_amdgcn_sched_barrier(0);
     }
-#pragma unroll
-    for (int g = 0; g < C::BK / 8; ++g) {
-      f32x4 a[C::TM], b[C::TN];
-#pragma unroll
-      for (int i = 0; i < C::TM; ++i) a[i] = SA::fragment(As[cur], (wm * C::TM + i) * 32 + (lane & 31), g, half);
-#pragma unroll
-      for (int j = 0; j < C::TN; ++j) b[j] = SB::fragment(Bs[cur], (wn * C::TN + j) * 32 + (lane & 31), g, half);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-          for (int j = 0; j < C::TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
+  };
+  load(0);
+  split();
+  store(lds);
+  if constexpr (C::TWO_STAGES) {
+    // Two stages in LDS: s is multiplied while s + 1 is split and written, by half of the wavefronts, one per SIMD, before they
+    // multiply and by the others afterwards, so that a SIMD's two wavefronts do not both multiply and then both split. The
+    // barrier waits for the LDS only: loads stay in flight.
+    auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    auto next = [&](int s) {
+      if (s >= n_stages) return;
+      split();
+      store(lds + (s & 1) * STAGE);
+      if (s + 1 < n_stages) load(s + 1);
+    };
+    if (n_stages > 1) load(1);
+    barrier();
+    for (int s = 0; s < n_stages; ++s) {
+      if (wave >= 4) next(s + 1);
+      multiply(lds + (s & 1) * STAGE);
+      if (wave < 4) next(s + 1);
+      barrier();
     }
-    if (more) {     // the other buffer was last read before the previous barrier
-      sa.store(As[cur ^ 1]);
-      sb.store(Bs[cur ^ 1]);
-    }
+  } else {
     __syncthreads();
-    cur ^= 1;
+    for (int s = 0; s < n_stages; ++s) {
+      const bool more = s + 1 < n_stages;
+      if (more) load(s + 1);     // the next stage's loads travel while this one is multiplied
+      multiply(lds);
+      if (more) {
+        split();
+        __syncthreads();      // everyone has read the stage
+        store(lds);
+        __syncthreads();
+      }
+    }
   }
+#pragma unroll
+  for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+    for (int j = 0; j < C::TN; ++j) acc[i][j] += small[i][j];
   epi.template store<C::TM, C::TN>(acc, m0 + wm * C::TM * 32, n0 + wn * C::TN * 32 + (lane & 31), half, M, N, bz);
+#endif
 }
 
-// Grid as gemm_f32_tile's block (y holds at most 65535).  Two workgroups per CU at least: one's products cover the other's
-// stage turn.
+// A grid of f32_grid(columns * rows * splits) of tiles. Every XCD has a range of the splits, and of the rows in them, and walks
+// their columns first, so that few others read the same part of A: 1501 x 768 x 8192 in seven splits 10.6 MB per XCD in place of
+// all 75 (logits of 1501 tokens at d = 768, V = 8192 133 / 127 us, with the loads by whole lines).
+__host__ __device__ constexpr int64_t f32_grid(int64_t tiles) { return (tiles + 7) / 8 * 8; }
 template <class C, bool A_KC, bool B_KC, class Epi>
-__global__ void __launch_bounds__(256, 2) k_gemm_f32(F32Operand A, F32Operand B, int64_t M, int64_t N, int64_t K, Epi epi) {
-  __shared__ __attribute__((aligned(16))) float As[f32_lds_a<C, A_KC>()], Bs[f32_lds_b<C, B_KC>()];
-  gemm_f32_tile<C, A_KC, B_KC>(A, B, M, N, K, epi, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z, As, Bs);
+__global__ void __launch_bounds__(C::NT, 2) k_gemm_f32(F32Operand A, F32Operand B, int64_t M, int64_t N, int64_t K, Epi epi,
+                                                       unsigned splits) {
+  extern __shared__ __attribute__((aligned(256))) char smem_raw[];     // C::LDS
+  const unsigned nx = (unsigned)((N + C::BN - 1) / C::BN), ny = (unsigned)((M + C::BM - 1) / C::BM);
+  const unsigned i = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (i / nx >= ny * splits) return;
+  gemm_f32_tile<C, A_KC, B_KC>(A, B, M, N, K, epi, i % nx, i / nx % ny, i / nx / ny, splits, smem_raw);
 }
 
 // The epilogues get a wavefront's accumulators, its first row and the lane's first column.
@@ -177,8 +347,26 @@ __global__ void __launch_bounds__(256, 2) k_gemm_f32(F32Operand A, F32Operand B,
 // Logits: M = vocabulary, N = tokens.  Per token and 64 vocabulary rows (one wavefront) the pair
 // (m, s) = (max_v z, sum_v exp(z - m)); parts[v / 64][t].  With `zt` the logits themselves are kept as well, for a batch
 // whose gradient fits one panel: zt[v][t].
+// Visits column j of a wavefront's patch: f(p, value, row), p = the address of the row in a matrix of pitch `ld` whose rows
+// of this lane start at p0. `rows` of the patch exist (a wavefront's, so the usual whole patch takes no test per row), `left`
+// of this lane's.
+template <int TM, int TN, class F>
+__device__ __forceinline__ void f32_rows(float* p0, int64_t ld, int64_t rows, int left, const f32x16 (&acc)[TM][TN], int j, F f) {
+  if (rows >= TM * 32) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) f(p0 + (i * 32 + f32_acc_row(r)) * ld, acc[i][j][r], i * 32 + f32_acc_row(r));
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (i * 32 + f32_acc_row(r) < left) f(p0 + (i * 32 + f32_acc_row(r)) * ld, acc[i][j][r], i * 32 + f32_acc_row(r));
+}
+
 struct EpiLseF32 {
-  static constexpr bool kRowsOnX = true;
   float2* parts;
   int64_t T;
   float* upart;   // optional third partial u = sum_v exp(z - m) * z (for the entropy), or nullptr
@@ -193,14 +381,7 @@ struct EpiLseF32 {
     for (int j = 0; j < TN; ++j) {
       const int64_t t = n + j * 32;
       if (zt && t < N) {
-        float* z0 = zt + (m + 4 * half) * ldz + t;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            if (i * 32 + f32_acc_row(r) < left) *z0 = acc[i][j][r];
-            z0 += (r & 3) == 3 ? 5 * ldz : ldz;
-          }
+        f32_rows(zt + (m + 4 * half) * ldz + t, ldz, M - m, left, acc, j, [](float* p, float z, int) { *p = z; });
       }
       if (left < 64 - 4) {
 #pragma unroll
@@ -250,7 +431,6 @@ struct EpiLseF32 {
 // Sampling: M = vocabulary, N = tokens.  Per token and 64 vocabulary rows the best perturbed logit
 // z / temperature + Gumbel(Philox(seed; v / 4, t)) and its vocabulary index; parts[v / 64][t].
 struct EpiSampleF32 {
-  static constexpr bool kRowsOnX = true;
   float2* parts;
   int64_t T;
   float inv_temperature;
@@ -290,7 +470,6 @@ __device__ __forceinline__ float dz_f32(float z, int v, int y, float c, float ls
   return c * ((v == y ? 1.f : 0.f) - expf(z - lse));
 }
 struct EpiDzF32 {
-  static constexpr bool kRowsOnX = true;
   const int32_t* tokens;
   const float* lse;
   const float* coef;
@@ -304,15 +483,8 @@ struct EpiDzF32 {
       if (t >= N) continue;
       const float c = coef[t], l = lse[t];
       const int left = (int)(M - m < 64 ? M - m : 64) - 4 * half, y = tokens[t] - (int)m - 4 * half;
-      float* z0 = zt + (m + 4 * half) * ldz + t;
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = i * 32 + f32_acc_row(r);
-          if (row < left) *z0 = dz_f32(acc[i][j][r], row, y, c, l);
-          z0 += (r & 3) == 3 ? 5 * ldz : ldz;
-        }
+      f32_rows(zt + (m + 4 * half) * ldz + t, ldz, M - m, left, acc, j,
+               [&](float* p, float z, int row) { *p = dz_f32(z, row, y, c, l); });
     }
   }
 };
@@ -340,25 +512,21 @@ k_dz_f32(float* __restrict__ zt, int64_t ldz, int V, int64_t T, const int32_t* _
 
 // Plain store, or read-add-store, of the tile into C[m][n]; with several splits of k each writes its own [M][N] copy.
 struct EpiStoreF32 {
-  static constexpr bool kRowsOnX = false;
   float* C;
   int64_t ld;
   int accumulate;
   template <int TM, int TN>
   __device__ void store(f32x16 (&acc)[TM][TN], int64_t m, int64_t n, int half, int64_t M, int64_t N, unsigned split) const {
     float* out = C + (int64_t)split * M * N;
+    const int left = (int)(M - m < TM * 32 ? M - m : TM * 32) - 4 * half;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int64_t row = m + i * 32 + f32_acc_row(r) + 4 * half, col = n + j * 32;
-          if (row < M && col < N) {
-            float* p = out + row * ld + col;
-            *p = accumulate ? *p + acc[i][j][r] : acc[i][j][r];
-          }
-        }
+    for (int j = 0; j < TN; ++j) {
+      const int64_t col = n + j * 32;
+      if (col >= N) continue;
+      float* p0 = out + (m + 4 * half) * ld + col;
+      if (accumulate) f32_rows(p0, ld, M - m, left, acc, j, [](float* p, float x, int) { *p += x; });
+      else f32_rows(p0, ld, M - m, left, acc, j, [](float* p, float x, int) { *p = x; });
+    }
   }
 };
 
@@ -388,7 +556,7 @@ template <class C, class Epi, class Begin, int VEC>
 __global__ void __launch_bounds__(256, 2)
 k_scores_f32(Begin begin, const int32_t* __restrict__ tokens, float* __restrict__ zy, TokenInit init, F32Operand W, F32Operand H,
              int V, int64_t T, int d, Epi epi) {
-  __shared__ __attribute__((aligned(16))) float As[f32_lds_a<C, true>()], Bs[f32_lds_b<C, true>()];
+  __shared__ __attribute__((aligned(256))) char lds[C::LDS];
   int64_t b = blockIdx.x;
   if (b == 0) return begin.run(0, 1, kPlan | kRest);
   b -= 1;
@@ -396,7 +564,7 @@ k_scores_f32(Begin begin, const int32_t* __restrict__ tokens, float* __restrict_
   if (b < n_gather)
     return gather_logit<float, double, VEC>(b * 4 + (threadIdx.x >> 6), H.p, W.p, tokens, T, d, V, zy, nullptr, init);
   b -= n_gather;
-  gemm_f32_tile<C, true, true>(W, H, (int64_t)V, T, (int64_t)d, epi, b % rows, b / rows, 0, 1, As, Bs);
+  gemm_f32_tile<C, true, true>(W, H, (int64_t)V, T, (int64_t)d, epi, b / rows, b % rows, 0, 1, lds);
 }
 
 // One contraction with its splits; `grid` = (columns, rows, splits) of tiles.
@@ -409,19 +577,18 @@ struct F32Contraction {
 // dH (rows of dZ^T contiguous) and dW (k contiguous) of a batch of one panel in one launch: neither fills the chip to
 // the end, and they do not depend on each other.
 template <class CH, class CW>
-__global__ void __launch_bounds__(256, larger(CH::kPerCU, CW::kPerCU)) k_grads_f32(F32Contraction dh, F32Contraction dw) {
-  __shared__ __attribute__((aligned(16))) float As[larger(f32_lds_a<CH, false>(), f32_lds_a<CW, true>())],
-      Bs[larger(f32_lds_b<CH, false>(), f32_lds_b<CW, false>())];
+__global__ void __launch_bounds__(256, 2) k_grads_f32(F32Contraction dh, F32Contraction dw) {
+  __shared__ __attribute__((aligned(256))) char lds[larger(CH::LDS, CW::LDS)];
   const int64_t n_dh = (int64_t)dh.nx * dh.ny * dh.splits;
   int64_t i = blockIdx.x;
   if (i < n_dh) {
     gemm_f32_tile<CH, false, false>(dh.A, dh.B, dh.M, dh.N, dh.K, EpiStoreF32{dh.out, dh.N, 0}, i % dh.nx, i / dh.nx % dh.ny,
-                                    (unsigned)(i / ((int64_t)dh.nx * dh.ny)), dh.splits, As, Bs);
+                                    (unsigned)(i / ((int64_t)dh.nx * dh.ny)), dh.splits, lds);
     return;
   }
   i -= n_dh;
   gemm_f32_tile<CW, true, false>(dw.A, dw.B, dw.M, dw.N, dw.K, EpiStoreF32{dw.out, dw.N, 0}, i % dw.nx, i / dw.nx % dw.ny,
-                                 (unsigned)(i / ((int64_t)dw.nx * dw.ny)), dw.splits, As, Bs);
+                                 (unsigned)(i / ((int64_t)dw.nx * dw.ny)), dw.splits, lds);
 }
 
 }  // namespace oapl

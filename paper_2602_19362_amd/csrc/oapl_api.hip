@@ -114,6 +114,7 @@ struct Plan {
   TilePick smp;        // ... of the sampling kernel (splits = (score, index) partials per token)
   int64_t Tp = 0;      // rows of one backward panel
   F32Pick f32_dh, f32_dw;   // tile and splits of the fp32 gradient contractions (of the largest panel)
+  int wide_dh = 0, wide_dw = 0;   // ... or in 256 x 128 tiles with so many splits
   int64_t ldz = 0;     // fp32: row pitch of the transposed logits / dZ panel [V][ldz]
   int n_buf = 1;       // panel buffers of the single sweep (a ring; one if the batch is one panel)
   size_t size_G = 0, size_GT = 0;   // bytes of one panel buffer of each packed copy
@@ -307,10 +308,11 @@ static int pick_width(int64_t T, int d, int V, double now, size_t scratch, DhPic
 // / 131; 126, 113 196 / 184; 144, 125 267 / 247; 166, 112 285 / 297; 235, 125 363 / 439.
 static bool dh_hides_behind_dw(int nk_v, int nk_t) { return nk_v <= nk_t + nk_t / 8 + 2; }
 
-// Tile and splits of an M x N x K fp32 contraction: the least time of the last-finishing CU in clocks.  A tile of 128 x
-// 128 takes 128 clocks per k at the matrix cores' rate, one of 64 x 64 32 (40 with the latency a single workgroup per CU
-// shows), a workgroup 2000 to start and store; partial results cost 8 bytes per element and split at 1700 bytes per
-// clock, and a launch (5000).  `scratch` bounds the partial results.
+// Tile of 128 x 128 or 64 x 64 and splits of an M x N x K fp32 contraction: the least time of the last-finishing CU in clocks, 128
+// per k for a tile of 128 x 128 and 40 for one of 64 x 64 that has the CU to itself, 2000 for a workgroup to start and
+// store; partial results cost 8 bytes per element and split at 1700 bytes per clock, and a launch (5000).  The figures are those
+// of fp32 multiplications; from parts both tiles take about 0.65 times as long (24 calls of up to 2000 tokens at d <= 768, V <= 8192
+// 0.61 .. 1.04, 0.82 on average).  `scratch` bounds the partial results.
 static F32Pick pick_f32(int64_t M, int64_t N, int64_t K, int max_splits, size_t scratch) {
   F32Pick best;
   double best_time = 1e300;
@@ -323,6 +325,28 @@ static F32Pick pick_f32(int64_t M, int64_t N, int64_t K, int max_splits, size_t 
                           (s > 1 ? 5000.0 + (double)s * M * N * 8.0 / 1700.0 : 0.0);
       if (time < best_time - 1e-9) { best_time = time; best.large = large != 0; best.splits = s; }
     }
+  }
+  return best;
+}
+
+// ... in 256 x 128 tiles, a workgroup per CU: in how many splits, or 0 where the smaller tiles are the better. us for a CU's
+// workgroups and a stage of 32 k: 256 x 128 3.1 each; 128 x 128 2.7 alone, 3.8 two; 64 x 64 1.3 alone, 0.55 each and 0.4 several. dH
+// of 1501 tokens at d = 768, V = 8192 in seven splits 147 (128 x 128) / 127 us, dW 164 in two with their sum / 133; dH of 1300 tokens
+// at V = 8065 332 (64 x 64, one split) / 139; of 700 at d = 300, V = 8000 in 16 splits 43 (64 x 64) / 55.
+static int wide_splits_f32(const F32Pick& pick, int64_t M, int64_t N, int64_t K, int max_splits, size_t scratch) {
+  auto tiles = [&](int64_t bm, int64_t bn) { return (M + bm - 1) / bm * ((N + bn - 1) / bn); };
+  const int64_t stages = (K + F32Wide::BK - 1) / F32Wide::BK;
+  auto partials = [&](int s) { return s > 1 ? 2.5 + (double)s * M * N * 8.0 / 3.7e6 : 0.0; };
+  const int64_t n = tiles(pick.large ? F32Large::BM : F32Small::BM, pick.large ? F32Large::BN : F32Small::BN) * pick.splits;
+  const int64_t per_cu = (n + kNumCU - 1) / kNumCU;
+  const double stage = pick.large ? 3.8 * (double)(per_cu / 2) + 2.7 * (double)(per_cu % 2)
+                                  : per_cu == 1 ? 1.3 : 0.55 * (double)per_cu + 0.4;
+  double now = stage * (double)stages / pick.splits + 6.0 + partials(pick.splits);
+  int best = 0;
+  for (int s = 1; s <= max_splits && s <= 64 && (s == 1 || (2 * s <= stages && (size_t)(s * M * N) * 4 <= scratch)); ++s) {
+    const int64_t rounds = (tiles(F32Wide::BM, F32Wide::BN) * s + kNumCU - 1) / kNumCU;
+    const double time = (double)rounds * (3.1 * (double)stages / s + 6.0) + partials(s);
+    if (time < now - 1e-9) { now = time; best = s; }
   }
   return best;
 }
@@ -483,11 +507,15 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
       const size_t scratch = T <= p.Tp ? kPartF32Bytes : 0;   // panels of a longer batch are rows enough for whole tiles
       p.f32_dh = pick_f32(p.Tp, d, V, max_splits, scratch);
       p.f32_dw = pick_f32(V, d, p.Tp, max_splits, scratch);
-      const size_t dh = p.f32_dh.splits > 1 ? (size_t)p.f32_dh.splits * p.Tp * d * 4 : 0;
-      const size_t dw = p.f32_dw.splits > 1 ? (size_t)p.f32_dw.splits * V * d * 4 : 0;
       // few workgroups share a launch, and then both have their partial results at once
       p.grads_fused = T > 0 && T <= p.Tp && max_splits == kAnySplits &&
                       f32_groups(p.f32_dh, T, d) + f32_groups(p.f32_dw, V, d) <= kSharedGroupsF32;
+      if (!p.grads_fused) {
+        p.wide_dh = wide_splits_f32(p.f32_dh, p.Tp, d, V, max_splits, scratch);
+        p.wide_dw = wide_splits_f32(p.f32_dw, V, d, p.Tp, max_splits, scratch);
+      }
+      const int s_dh = p.wide_dh ? p.wide_dh : p.f32_dh.splits, s_dw = p.wide_dw ? p.wide_dw : p.f32_dw.splits;
+      const size_t dh = s_dh > 1 ? (size_t)s_dh * p.Tp * d * 4 : 0, dw = s_dw > 1 ? (size_t)s_dw * V * d * 4 : 0;
       if (p.grads_fused) {
         p.off_part = take(dh);
         p.off_part_dw = take(dw);
@@ -591,7 +619,9 @@ static bool prepare_kernels() {
          allow_big_lds(k_sweep<CfgSmall, true>, CfgSmall::LDS_BYTES) &&
          allow_big_lds(k_sweep<CfgDeep, true>, CfgDeep::LDS_BYTES) && allow_dh<Cfg, false>() &&
          allow_dh<CfgSmall, true>() && allow_dh<CfgDeep, true>() && allow_big_lds(k_bwd_dw<Cfg>, Cfg::LDS_BYTES) &&
-         allow_grads<CfgSmall>() && allow_grads<CfgDeep>();
+         allow_grads<CfgSmall>() && allow_grads<CfgDeep>() &&
+         allow_big_lds(k_gemm_f32<F32Wide, true, false, EpiStoreF32>, F32Wide::LDS) &&
+         allow_big_lds(k_gemm_f32<F32Wide, false, false, EpiStoreF32>, F32Wide::LDS);
   });
   return ok;
 }
@@ -703,15 +733,16 @@ static bool logits_large_f32(int V, int64_t T) {
 }
 
 // Logits of T token rows (transposed: M = vocabulary), in whatever form the epilogue leaves them.
+template <class C, class Epi>
+static void launch_logits_f32(const Plan& p, const F32Operand& A, const F32Operand& B, int64_t T, Epi epi, hipStream_t st) {
+  const int64_t tiles = (int64_t)grid1d(p.V, C::BM) * grid1d(T, C::BN);
+  k_gemm_f32<C, true, true><<<(unsigned)f32_grid(tiles), C::NT, C::LDS, st>>>(A, B, (int64_t)p.V, T, (int64_t)p.d, epi, 1);
+}
 template <class Epi>
 static void launch_logits_f32(const Plan& p, const void* H, const void* W, int64_t T, Epi epi, hipStream_t st) {
   const F32Operand A = f32_operand(W, p.d), B = f32_operand(H, p.d);
-  if (logits_large_f32(p.V, T))
-    k_gemm_f32<F32Large, true, true><<<dim3(grid1d(p.V, F32Large::BM), grid1d(T, F32Large::BN)), 256, 0, st>>>(
-        A, B, (int64_t)p.V, T, (int64_t)p.d, epi);
-  else
-    k_gemm_f32<F32Flat, true, true><<<dim3(grid1d(p.V, F32Flat::BM), grid1d(T, F32Flat::BN)), 256, 0, st>>>(
-        A, B, (int64_t)p.V, T, (int64_t)p.d, epi);
+  if (logits_large_f32(p.V, T)) launch_logits_f32<F32Large>(p, A, B, T, epi, st);
+  else launch_logits_f32<F32Flat>(p, A, B, T, epi, st);
 }
 
 // ... in the launch that a loss call of few tokens starts with (k_scores_f32).
@@ -726,28 +757,33 @@ static void launch_scores_f32(const Plan& p, const Begin& begin, const void* H, 
 }
 
 // out[m][n] (+)= sum_k A(m, k) B(n, k), B and (unless A_KC) A with their rows contiguous.
-static F32Contraction contraction_f32(const F32Pick& pick, const F32Operand& A, const F32Operand& B, int64_t M, int64_t N,
-                                      int64_t K, float* out) {
-  const int tile = pick.large ? F32Large::BM : F32Small::BM;
-  return F32Contraction{A, B, M, N, K, out, (int)grid1d(N, tile), (int)grid1d(M, tile), pick.splits};
+static F32Contraction contraction_f32(const F32Pick& pick, int wide, const F32Operand& A, const F32Operand& B, int64_t M,
+                                      int64_t N, int64_t K, float* out) {
+  const int bm = wide ? F32Wide::BM : pick.large ? F32Large::BM : F32Small::BM;
+  const int bn = wide ? F32Wide::BN : pick.large ? F32Large::BN : F32Small::BN;
+  return F32Contraction{A, B, M, N, K, out, (int)grid1d(N, bn), (int)grid1d(M, bm), wide ? wide : pick.splits};
+}
+template <class C, bool A_KC>
+static void launch_contract_f32(const F32Contraction& c, int accumulate, hipStream_t st) {
+  k_gemm_f32<C, A_KC, false><<<(unsigned)f32_grid((int64_t)c.nx * c.ny * c.splits), C::NT, C::LDS, st>>>(
+      c.A, c.B, c.M, c.N, c.K, EpiStoreF32{c.out, c.N, accumulate}, c.splits);
 }
 template <bool A_KC>
-static void launch_contract_f32(bool large, const F32Contraction& c, int accumulate, hipStream_t st) {
-  const EpiStoreF32 epi{c.out, c.N, accumulate};
-  const dim3 grid(c.nx, c.ny, c.splits);
-  if (large) k_gemm_f32<F32Large, A_KC, false><<<grid, 256, 0, st>>>(c.A, c.B, c.M, c.N, c.K, epi);
-  else k_gemm_f32<F32Small, A_KC, false><<<grid, 256, 0, st>>>(c.A, c.B, c.M, c.N, c.K, epi);
+static void launch_contract_f32(const F32Pick& pick, int wide, const F32Contraction& c, int accumulate, hipStream_t st) {
+  if (wide) launch_contract_f32<F32Wide, A_KC>(c, accumulate, st);
+  else if (pick.large) launch_contract_f32<F32Large, A_KC>(c, accumulate, st);
+  else launch_contract_f32<F32Small, A_KC>(c, accumulate, st);
 }
 
 // Both gradient contractions of a batch of one panel, and the sums of what was split.
 static int grads_f32(const Plan& p, const void* H, const void* W, const float* zt, float* dH, float* dW, char* ws,
                      hipStream_t st) {
-  float* part_dh = p.f32_dh.splits > 1 ? (float*)(ws + p.off_part) : nullptr;
-  float* part_dw = p.f32_dw.splits > 1 ? (float*)(ws + p.off_part_dw) : nullptr;
+  float* part_dh = (p.wide_dh ? p.wide_dh : p.f32_dh.splits) > 1 ? (float*)(ws + p.off_part) : nullptr;
+  float* part_dw = (p.wide_dw ? p.wide_dw : p.f32_dw.splits) > 1 ? (float*)(ws + p.off_part_dw) : nullptr;
   // dH[t][j] = sum_v dZ[t][v] W[v][j],  dW[v][j] = sum_t dZ[t][v] H[t][j]
   const F32Operand z = f32_operand(zt, p.ldz);
-  const F32Contraction dh = contraction_f32(p.f32_dh, z, f32_operand(W, p.d), p.T, p.d, p.V, part_dh ? part_dh : dH);
-  const F32Contraction dw = contraction_f32(p.f32_dw, z, f32_operand(H, p.d), p.V, p.d, p.T, part_dw ? part_dw : dW);
+  const F32Contraction dh = contraction_f32(p.f32_dh, p.wide_dh, z, f32_operand(W, p.d), p.T, p.d, p.V, part_dh ? part_dh : dH);
+  const F32Contraction dw = contraction_f32(p.f32_dw, p.wide_dw, z, f32_operand(H, p.d), p.V, p.d, p.T, part_dw ? part_dw : dW);
   const F32Reduction a{part_dh, dh.splits, part_dh ? dh.M * dh.N : 0, dH}, b{part_dw, dw.splits, part_dw ? dw.M * dw.N : 0, dW};
   const F32Reduction none{nullptr, 0, 0, nullptr};
   auto reduce = [&](const F32Reduction& x, const F32Reduction& y) {
@@ -755,11 +791,11 @@ static int grads_f32(const Plan& p, const void* H, const void* W, const float* z
     if (blocks > 0) k_reduce_f32<<<(unsigned)(blocks < 8192 ? blocks : 8192), 256, 0, st>>>(x, y);
   };
   if (!p.grads_fused) {
-    launch_contract_f32<false>(p.f32_dh.large, dh, 0, st);
+    launch_contract_f32<false>(p.f32_dh, p.wide_dh, dh, 0, st);
     OAPL_LAUNCH_CHECK();
     reduce(a, none);      // before the other's partial results, which have the same space
     OAPL_LAUNCH_CHECK();
-    launch_contract_f32<true>(p.f32_dw.large, dw, 0, st);
+    launch_contract_f32<true>(p.f32_dw, p.wide_dw, dw, 0, st);
     OAPL_LAUNCH_CHECK();
     reduce(b, none);
     OAPL_LAUNCH_CHECK();
@@ -1038,6 +1074,7 @@ static int backward_grads(const Plan& p, const void* H, const void* W, const int
     }
     return OAPL_OK;
   }
+  if ((p.wide_dh || p.wide_dw) && !prepare_kernels()) return OAPL_ERR_HIP;
   float* zt = (float*)(ws + p.off_G);   // dZ^T of a panel
   const float* lse = (const float*)(ws + p.off_lse2);
   const float* coef = (const float*)(ws + p.off_coef);
@@ -1052,12 +1089,12 @@ static int backward_grads(const Plan& p, const void* H, const void* W, const int
     launch_logits_f32(p, Hp, W, nv, EpiDzF32{tokens + t0, lse + t0, coef + t0, zt, p.ldz}, st);
     OAPL_LAUNCH_CHECK();
     // dH[t][j] = sum_v dZ[t][v] W[v][j]
-    launch_contract_f32<false>(p.f32_dh.large, contraction_f32(p.f32_dh, f32_operand(zt, p.ldz), f32_operand(W, d), nv, d, V,
-                                                               (float*)dH + t0 * d), 0, st);
+    launch_contract_f32<false>(p.f32_dh, p.wide_dh, contraction_f32(p.f32_dh, p.wide_dh, f32_operand(zt, p.ldz), f32_operand(W, d),
+                                                                    nv, d, V, (float*)dH + t0 * d), 0, st);
     OAPL_LAUNCH_CHECK();
     // dW[v][j] (+)= sum_t dZ[t][v] H[t][j]
-    launch_contract_f32<true>(p.f32_dw.large, contraction_f32(p.f32_dw, f32_operand(zt, p.ldz), f32_operand(Hp, d), V, d, nv, dW),
-                              t0 > 0 ? 1 : 0, st);
+    launch_contract_f32<true>(p.f32_dw, p.wide_dw, contraction_f32(p.f32_dw, p.wide_dw, f32_operand(zt, p.ldz), f32_operand(Hp, d), V,
+                                                                   d, nv, dW), t0 > 0 ? 1 : 0, st);
     OAPL_LAUNCH_CHECK();
   }
   return OAPL_OK;

@@ -66,8 +66,9 @@ int main() {
                     p.width, p.small_sweep, p.small_dw, p.dh.small, p.dh.splits, groups(p.small_sweep, V, last),
                     groups(p.small_dw, d, V), groups(p.dh.small, d, last) * p.dh.splits);
       else
-        std::printf(" logits_large=%d dh_large=%d dh_splits=%d dw_large=%d dw_splits=%d\n",
-                    logits_large_f32(V, T < p.Tp ? T : p.Tp), p.f32_dh.large, p.f32_dh.splits, p.f32_dw.large, p.f32_dw.splits);
+        std::printf(" logits_large=%d dh_large=%d dh_splits=%d dw_large=%d dw_splits=%d wide_dh=%d wide_dw=%d\n",
+                    logits_large_f32(V, T < p.Tp ? T : p.Tp), p.f32_dh.large, p.f32_dh.splits, p.f32_dw.large, p.f32_dw.splits,
+                    p.wide_dh, p.wide_dw);
     } else {
       std::printf("unknown query\n");
       return 1;
