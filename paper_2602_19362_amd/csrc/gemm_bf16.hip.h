@@ -1282,6 +1282,48 @@ k_sweep_begin(Begin begin, const bf16_t* __restrict__ W, const bf16_t* __restric
 #endif
 }
 
+// The first launch of a single sweep of few tokens over operands in place whose rows are long: what the call begins with
+// (workgroup 0; `steps` = 0: a launch of its own has done it) and the logits of the first 256 vocabulary entries, a tile of 64
+// tokens in `splits` parts over d, part[split][t][row], which the gather sums. Bound by the latency of a walk's loads, d / 64
+// blocks one after the other (0.8 us each): 1003 tokens at d = 4096 49 us in one part, 14 in eight.
+template <class C, class Begin>
+__global__ void __launch_bounds__(C::NT)
+k_ref_begin(Begin begin, int steps, const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int64_t T, int d, int n_kt,
+            int splits, float* __restrict__ part) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+  lds_char_ptr smem = (lds_char_ptr)smem_raw;
+  static_assert(C::NT == 256 && C::BM == 256 && C::NS == 4, "begin's steps are for 256 threads; walks start at any block");
+  if (blockIdx.x == 0) {
+    if (steps != 0) begin.run(0, 1, steps);
+    return;
+  }
+  const int64_t nt = (blockIdx.x - 1) / splits, n0 = nt * C::BN;
+  const int split = (blockIdx.x - 1) % splits;
+  const int k0 = (int)((int64_t)split * n_kt / splits), k1 = (int)((int64_t)(split + 1) * n_kt / splits);
+
+  Mainloop<C, true> ml;
+  ml.setup();
+  ml.rows_init(d);
+  if (k1 < n_kt) ml.vlast = ml.voff;      // this walk's last block is not the rows' last
+  ml.set_a(W + k0 * C::BK, 0, V, d, n_kt);
+  ml.set_b(H + k0 * C::BK, nt, T, d, n_kt);
+  f32x4 acc[C::MB][C::NB];
+  zero_acc<C>(acc);
+  ml.start(smem, k1 - k0);
+  ml.finish(smem, k1 - k0, acc);
+
+  const Lane<C> at;
+#pragma unroll
+  for (int j = 0; j < C::NB; ++j) {
+    const int64_t t = n0 + at.col0() + 16 * j;
+    if (t >= T) continue;
+#pragma unroll
+    for (int i = 0; i < C::MB; ++i) *(f32x4*)(part + ((int64_t)split * T + t) * C::BM + at.row0() + 16 * i) = acc[i][j];
+  }
+#endif
+}
+
 // ---------------------------------------------------------------------------
 // Single-sweep variant of steps a1, a2 and a8: ONE pass over the logits serves
 // both the log-sum-exp and the gradient.  The soft-max is written unnormalised

@@ -613,6 +613,8 @@ static bool prepare_kernels() {
          allow_big_lds(k_fwd_lse<CfgRef, false, false>, CfgRef::LDS_BYTES) &&
          allow_big_lds(k_sweep_begin<CfgRef, OaplBegin>, CfgRef::LDS_BYTES) &&
          allow_big_lds(k_sweep_begin<CfgRef, GrpoBegin>, CfgRef::LDS_BYTES) &&
+         allow_big_lds(k_ref_begin<CfgRef, OaplBegin>, CfgRef::LDS_BYTES) &&
+         allow_big_lds(k_ref_begin<CfgRef, GrpoBegin>, CfgRef::LDS_BYTES) &&
          allow_big_lds(k_bwd_dz<Cfg, false>, Cfg::LDS_BYTES) && allow_big_lds(k_sweep<Cfg, false>, Cfg::LDS_BYTES) &&
          allow_loss<Cfg256>() && allow_loss<Cfg288>() && allow_loss<Cfg320>() && allow_loss<Cfg352>() && allow_loss<Cfg>() &&
          allow_big_lds(k_sweep<CfgEarly, true>, CfgEarly::LDS_BYTES) &&
@@ -1139,6 +1141,17 @@ static bool sweep_begins_in_one_launch(const Plan& p, int n_seq, int n_groups) {
   return p.rows && p.d <= kOneLaunchHidden && begin_in_one_launch(n_seq, n_groups);
 }
 
+// Otherwise: in how many parts over d the reference pass's tiles come (k_ref_begin), as many as give every CU one workgroup, of
+// four k-blocks at least and eight parts at most, whose logits find room where the first panel will be; 0: it goes whole, with
+// the call's beginning in front of it. Beginning, reference pass and gather of 300 and 1003 tokens at d = 4096 65 us in three
+// launches, 25 in two; whole calls, us: 100 tokens, V = 8192 150 / 115, 1000 253 / 221, 300, V = 151936 1509 / 1463.
+static int ref_splits(const Plan& p) {
+  const int64_t tiles = grid1d(p.T, CfgRef::BN);
+  for (int s = 8; s >= 2; --s)
+    if (p.rows && p.d > kOneLaunchHidden && tiles * s <= kNumCU && 4 * s <= p.n_kt_d && (uint64_t)s * p.T * CfgRef::BM * 4 <= p.size_G) return s;
+  return 0;
+}
+
 // Steps a1-a3 and a8-a10 in ONE pass over the logits (bf16, T > 0).  Per panel of token rows:
 // k_sweep writes the unnormalised soft-max panel and its row sums, k_sweep_finish turns the sums
 // into log-probs; the objective (`objective(gate, factors)`, which must fill coef[t] = c_t * factor[t]
@@ -1167,7 +1180,7 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
   float* nis = (float*)(ws + p.off_inv);
   const float* omp = (const float*)(ws + p.off_omp);
 
-  const TokenInit init{(float*)(ws + p.off_coef), sample, ref2, diff, nis};
+  TokenInit init{(float*)(ws + p.off_coef), sample, nullptr, 0, 0, ref2, diff, nis};
   const bool one = sweep_begins_in_one_launch(p, begin.n_seq, begin.n_groups);
   // k_sweep_begin leaves tokens out of range to k_sweep_finish, which is closed for the panels behind a raised flag (for all,
   // if it was raised at the beginning): the fallback, which that flag opens, then looks at every token
@@ -1176,6 +1189,17 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
     k_sweep_begin<CfgRef><<<1 + grid1d(T, CfgRef::BN), CfgRef::NT, CfgRef::LDS_BYTES, st>>>(begin, x.W, x.H, V, T, d, p.n_kt_d,
                                                                                          tokens, (float*)(ws + p.off_zy), init);
     OAPL_LAUNCH_CHECK();
+  } else if (const int splits = ref_splits(p)) {
+    const bool begins = begin_in_one_launch(begin.n_seq, begin.n_groups);
+    if (!begins)
+      if (int rc = launch_begin(begin, st)) return rc;
+    init.sample_parts = (const float*)Gbuf(0);     // empty until the sweep
+    init.sample_splits = splits;
+    init.sample_rows = V < CfgRef::BM ? V : CfgRef::BM;
+    k_ref_begin<CfgRef><<<1 + grid1d(T, CfgRef::BN) * splits, CfgRef::NT, CfgRef::LDS_BYTES, st>>>(
+        begin, begins ? kPlan | kRest : 0, x.W, x.H, V, T, d, p.n_kt_d, splits, (float*)Gbuf(0));
+    OAPL_LAUNCH_CHECK();
+    if (int rc = gather_logits(p, H, W, tokens, init, ws, st)) return rc;
   } else {
     if (int rc = launch_begin(begin, st)) return rc;
     if (int rc = pack_wt(p, W, ws, st, kNoGate)) return rc;
@@ -1256,7 +1280,7 @@ static int two_pass_path(const Plan& p, const Begin& begin, const void* H, const
                          const float* logq, float* logprob_out, void* dH, float* dW, char* ws, hipStream_t st,
                          Objective&& objective) {
   const int64_t T = p.T;
-  const TokenInit init{p.bwd ? (float*)(ws + p.off_coef) : nullptr, nullptr, nullptr, nullptr, nullptr};
+  const TokenInit init{p.bwd ? (float*)(ws + p.off_coef) : nullptr, nullptr, nullptr, 0, 0, nullptr, nullptr, nullptr};
   const bool one = scores_in_one_launch_f32(p, begin.n_seq, begin.n_groups);
   if (one) {
     float* zt = p.bwd && T <= p.Tp ? (float*)(ws + p.off_G) : nullptr;

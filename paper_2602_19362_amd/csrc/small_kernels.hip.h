@@ -38,6 +38,8 @@ constexpr float kSweepLimit = 1.2676506e30f;   // 2^100: largest S_t the single 
 struct TokenInit {
   float* coef;            // or nullptr
   const float2* sample;   // or nullptr
+  const float* sample_parts;   // or, in place of that: the sample's logits, [sample_splits][T][256] to be summed (k_ref_begin)
+  int sample_splits, sample_rows;
   float* ref2;            // or nullptr: no single sweep
   double* diff;
   float* nis;
@@ -52,6 +54,21 @@ __device__ __forceinline__ void init_token(const TokenInit& init, int64_t t, flo
     init.nis[t] = 0.f;
   }
 }
+// The largest of token t's sampled logits, in the exp2 domain, from their parts: four of 256 rows per lane.
+__device__ __forceinline__ float largest_sampled(const TokenInit& init, int64_t t, int64_t T) {
+  const int lane = threadIdx.x & 63;
+  const f32x4* p = (const f32x4*)(init.sample_parts + t * 256) + lane;
+  f32x4 z = p[0];
+#pragma unroll 8
+  for (int s = 1; s < init.sample_splits; ++s) z += p[(int64_t)s * T * 64];
+  float largest = kNegHuge;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (4 * lane + e < init.sample_rows) largest = fmaxf(largest, z[e]);
+#pragma unroll
+  for (int o = 32; o > 0; o /= 2) largest = fmaxf(largest, __shfl_xor(largest, o, 64));
+  return largest * kLog2e;
+}
 // `err` == nullptr: a token out of range is recorded by a later launch (k_lse_finish), for the status header is being cleared
 // by this one.
 template <class T, class ACC, int VEC>
@@ -62,7 +79,8 @@ __device__ __forceinline__ void gather_logit(int64_t t /* of this wavefront */, 
   const int lane = threadIdx.x & 63;
   if (t >= Ttok) return;
   const int y = tokens[t];
-  auto finish = [&](float z) { init_token(init, t, z, init.sample ? init.sample[t].x : 0.f, zy); };
+  const float largest = init.sample_parts ? largest_sampled(init, t, Ttok) : init.sample ? init.sample[t].x : 0.f;
+  auto finish = [&](float z) { init_token(init, t, z, largest, zy); };
   if (y < 0 || y >= V) {
     if (lane == 0) {
       if (err) record_token_error(err);

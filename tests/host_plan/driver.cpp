@@ -62,9 +62,9 @@ int main() {
                   p.fwd.tile == kTile256 && early_pays(T, V, d), p.fwd.splits, p.smp.splits, (int)p.smp.tile);
       const int64_t last = T > 0 ? T - (T - 1) / p.Tp * p.Tp : 0;   // rows of the last panel
       if (dtype == OAPL_BF16)
-        std::printf(" width=%d small_sweep=%d small_dw=%d dh_small=%d dh_splits=%d sweep_groups=%lld dw_groups=%lld dh_groups=%lld\n",
+        std::printf(" width=%d small_sweep=%d small_dw=%d dh_small=%d dh_splits=%d sweep_groups=%lld dw_groups=%lld dh_groups=%lld ref_splits=%d\n",
                     p.width, p.small_sweep, p.small_dw, p.dh.small, p.dh.splits, groups(p.small_sweep, V, last),
-                    groups(p.small_dw, d, V), groups(p.dh.small, d, last) * p.dh.splits);
+                    groups(p.small_dw, d, V), groups(p.dh.small, d, last) * p.dh.splits, p.sweep ? ref_splits(p) : 0);
       else
         std::printf(" logits_large=%d dh_large=%d dh_splits=%d dw_large=%d dw_splits=%d wide_dh=%d wide_dw=%d\n",
                     logits_large_f32(V, T < p.Tp ? T : p.Tp), p.f32_dh.large, p.f32_dh.splits, p.f32_dw.large, p.f32_dw.splits,

@@ -2,7 +2,7 @@
 import pytest
 
 from paper_2602_19362_amd import oapl
-from tests import test_gpu_dh_splits, test_gpu_f32_parts, test_gpu_f32_tiles, test_gpu_loss_widths, test_gpu_sample_widths, test_gpu_score_widths, test_gpu_small_tiles
+from tests import test_gpu_dh_splits, test_gpu_f32_parts, test_gpu_f32_tiles, test_gpu_loss_widths, test_gpu_ref_splits, test_gpu_sample_widths, test_gpu_score_widths, test_gpu_small_tiles
 from tests._plan import ask
 
 INT_MAX = 2 ** 31 - 1
@@ -67,8 +67,9 @@ def test_a_few_missing_bytes_cost_a_few_splits():
     (oapl.OAPL_BF16, [(sum(lens), d, V, cap, want) for d, V, lens, cap, want in test_gpu_dh_splits.CASES]),
     (oapl.OAPL_BF16, [(T, d, V, 0, want) for d, V, T, want in test_gpu_small_tiles.CASES]),
     (oapl.OAPL_F32, [(sum(lens), d, V, cap, want) for d, V, lens, cap, want in test_gpu_f32_tiles.CASES]),
-    (oapl.OAPL_F32, [(sum(lens), d, V, cap, want) for d, V, lens, cap, want in test_gpu_f32_parts.CASES])],
-    ids=["dh_splits", "small_tiles", "f32_tiles", "f32_parts"])
+    (oapl.OAPL_F32, [(sum(lens), d, V, cap, want) for d, V, lens, cap, want in test_gpu_f32_parts.CASES]),
+    (oapl.OAPL_BF16, [(sum(lens), d, V, 0, want) for d, V, lens, want in test_gpu_ref_splits.CASES])],
+    ids=["dh_splits", "small_tiles", "f32_tiles", "f32_parts", "ref_splits"])
 def test_gpu_cases_have_the_plans_they_name(dtype, cases):
     """A change of the time models must not empty the GPU tests of the kernels they are there for."""
     plans = ask([f"plan {T} {d} {V} {dtype} 1 {cap} 0 -1" for T, d, V, cap, _ in cases])
