@@ -895,20 +895,30 @@ static int forward_partials(const Plan& p, const void* H, const void* W, bool en
 
 // Log-probs (and lse, entropy) from the partial sums and the sampled tokens' logits; with `logq` also what the objective
 // and the gradients need. `check_tokens`: the tokens, if the gather before left it to this launch to report those out of range.
-static int forward_finish(const Plan& p, const float* logq, float* logprob_out, float* lse_out, float* entropy_out,
-                          const int32_t* check_tokens, char* ws, hipStream_t st, Gate gate) {
-  const int64_t T = p.T;
-  if (T == 0) return OAPL_OK;
+static LseFinish finish_args(const Plan& p, const float* logq, float* logprob_out, float* lse_out, float* entropy_out,
+                             const int32_t* check_tokens, char* ws) {
   const bool loss = logq != nullptr;
-  const int slices = finish_slices(p.fwd.splits);
-  (p.dtype == OAPL_BF16 ? k_lse_finish<true> : k_lse_finish<false>)<<<grid1d(T, 256 / slices), 256, 0, st>>>(
-      (const float2*)(ws + p.off_fwd_partials), p.fwd.splits, T, (const float*)(ws + p.off_zy), logq, logprob_out, lse_out,
-      loss ? (float*)(ws + p.off_lse2) : nullptr, loss ? (double*)(ws + p.off_diff) : nullptr,
-      loss ? (float*)(ws + p.off_omp) : nullptr, loss ? (float*)(ws + p.off_inv) : nullptr,
-      entropy_out ? (const float*)(ws + p.off_upart) : nullptr, entropy_out, slices, check_tokens, p.V,
-      (int*)(ws + p.off_status), gate);
+  return LseFinish{(const float2*)(ws + p.off_fwd_partials), p.fwd.splits, p.T, (const float*)(ws + p.off_zy), logq, logprob_out,
+                   lse_out, loss ? (float*)(ws + p.off_lse2) : nullptr, loss ? (double*)(ws + p.off_diff) : nullptr,
+                   loss ? (float*)(ws + p.off_omp) : nullptr, loss ? (float*)(ws + p.off_inv) : nullptr,
+                   entropy_out ? (const float*)(ws + p.off_upart) : nullptr, entropy_out, finish_slices(p.fwd.splits),
+                   check_tokens, p.V, (int*)(ws + p.off_status)};
+}
+static int forward_finish(const Plan& p, const LseFinish& f, hipStream_t st, Gate gate) {
+  if (p.T == 0) return OAPL_OK;
+  (p.dtype == OAPL_BF16 ? k_lse_finish<true> : k_lse_finish<false>)<<<grid1d(p.T, 256 / f.slices), 256, 0, st>>>(f, gate);
   OAPL_LAUNCH_CHECK();
   return OAPL_OK;
+}
+
+// An fp32 loss call's log-probs are finished by the objective's launch where that is little work even for one workgroup (one
+// rollout may have all tokens): a dependent launch costs a small call 5 us whatever is in it. 256 tokens at d = 64, V = 1024 (16
+// partials each) 34.9 us in two launches, 31.6 in one; in one, 373 tokens of 32 partials (a rollout's workgroup has them one
+// after the other) take 6 us longer. In bf16, where the finish is the fallback's and closed, the launch that it
+// saves goes into the larger kernel (1000 tokens at d = 256, V = 1544 53.6 / 53.4).
+constexpr int64_t kFinishInObjective = 5000;
+static bool finish_in_objective(const Plan& p) {
+  return p.dtype == OAPL_F32 && p.T > 0 && p.T * p.fwd.splits <= kFinishInObjective;
 }
 
 // Calls f with the large tile of that many columns.
@@ -1243,14 +1253,15 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
   if (n_panels == 1) {
     if (int rc = sweep(0)) return rc;
     if (int rc = forward_partials(p, H, W, false, false, nullptr, ws, st, slow)) return rc;
-    if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, check, ws, st, slow)) return rc;
-    if (int rc = objective(kNoGate, TokenFactor{nis, omp, flag})) return rc;
+    const LseFinish finish = finish_args(p, logq, logprob_out, nullptr, nullptr, check, ws);
+    if (int rc = forward_finish(p, finish, st, slow)) return rc;
+    if (int rc = objective(kNoGate, TokenFactor{nis, omp, flag}, nullptr)) return rc;
     if (int rc = recompute_panel(p, H, W, tokens, 0, Gbuf(0), GTbuf(0), ws, st, slow, p.grads_fused)) return rc;
     return panel_gradients(p, H, W, 0, Gbuf(0), GTbuf(0), dH, dW, ws, st, kNoGate, true, p.grads_fused);
   }
 
   auto gradients = [&](int64_t k) -> int {
-    if (int rc = objective(fast, TokenFactor{nis, nullptr, nullptr})) return rc;
+    if (int rc = objective(fast, TokenFactor{nis, nullptr, nullptr}, nullptr)) return rc;
     return panel_gradients(p, H, W, k * p.Tp, Gbuf(k), GTbuf(k), dH, dW, ws, st, fast, true);
   };
   for (int64_t k = 0; k < n_panels; ++k) {
@@ -1261,8 +1272,8 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
   for (int64_t k = n_panels - (p.n_buf - 1); k < n_panels; ++k)
     if (int rc = gradients(k)) return rc;
   if (int rc = forward_partials(p, H, W, false, false, nullptr, ws, st, slow)) return rc;
-  if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, check, ws, st, slow)) return rc;
-  if (int rc = objective(slow, TokenFactor{omp, nullptr, nullptr})) return rc;
+  if (int rc = forward_finish(p, finish_args(p, logq, logprob_out, nullptr, nullptr, check, ws), st, slow)) return rc;
+  if (int rc = objective(slow, TokenFactor{omp, nullptr, nullptr}, nullptr)) return rc;
   return backward_grads(p, H, W, tokens, dH, dW, ws, st, slow, true);
 }
 
@@ -1292,9 +1303,12 @@ static int two_pass_path(const Plan& p, const Begin& begin, const void* H, const
     if (int rc = gather_logits(p, H, W, tokens, init, ws, st)) return rc;
     if (int rc = forward_partials(p, H, W, false, p.bwd, nullptr, ws, st, kNoGate)) return rc;
   }
-  if (int rc = forward_finish(p, logq, logprob_out, nullptr, nullptr, one ? tokens : nullptr, ws, st, kNoGate)) return rc;
+  const LseFinish finish = finish_args(p, logq, logprob_out, nullptr, nullptr, one ? tokens : nullptr, ws);
   const float* factor = p.bwd && p.dtype == OAPL_BF16 ? (const float*)(ws + p.off_omp) : nullptr;
-  if (int rc = objective(kNoGate, TokenFactor{factor, nullptr, nullptr})) return rc;
+  const bool together = finish_in_objective(p);
+  if (!together)
+    if (int rc = forward_finish(p, finish, st, kNoGate)) return rc;
+  if (int rc = objective(kNoGate, TokenFactor{factor, nullptr, nullptr}, together ? &finish : nullptr)) return rc;
   if (!p.bwd) return OAPL_OK;
   return backward_grads(p, H, W, tokens, dH, dW, ws, st, kNoGate, false);
 }
@@ -1419,12 +1433,12 @@ static int loss_impl(const void* H, const void* W, const int32_t* tokens, const 
   if (int rc = pack_operands(p, H, W, ws, st)) return rc;
 
   // Steps a4, a6, a7 from logprob - logq [T]
-  auto objective = [&](Gate gate, TokenFactor factors) -> int {
+  auto objective = [&](Gate gate, TokenFactor factors, const LseFinish* finish) -> int {
     return objective_steps(n_seq, [&](unsigned grid, int steps) {
-      k_oapl_objective<<<grid, 256, 0, st>>>(
+      (finish ? k_oapl_objective<true> : k_oapl_objective<false>)<<<grid, 256, 0, st>>>(
           (const double*)(ws + p.off_diff), rewards, group_ids, seq_offsets, n_seq, n_groups, T, (double)beta_loss,
           (double)loss_scale, vstar, factors, (double*)(ws + p.off_delta), bwd && T > 0 ? (float*)(ws + p.off_coef) : nullptr,
-          loss_out, seq_logratio_out, status, steps, gate);
+          loss_out, seq_logratio_out, status, steps, gate, finish ? *finish : LseFinish{});
     });
   };
   // bf16 with gradients: one sweep over the logits; the two-pass schedule behind it runs only if the
@@ -1467,11 +1481,12 @@ static int grpo_impl(const void* H, const void* W, const int32_t* tokens, const 
                         gstat + n_groups, gsize, adv, wseq, adv_out, status};
   if (int rc = pack_operands(p, H, W, ws, st)) return rc;
 
-  auto objective = [&](Gate gate, TokenFactor factors) -> int {
+  auto objective = [&](Gate gate, TokenFactor factors, const LseFinish* finish) -> int {
     return objective_steps(n_seq, [&](unsigned grid, int steps) {
-      k_grpo_objective<<<grid, 256, 0, st>>>(
+      (finish ? k_grpo_objective<true> : k_grpo_objective<false>)<<<grid, 256, 0, st>>>(
           (const double*)(ws + p.off_diff), logq, logp_old, seq_offsets, n_seq, T, adv, wseq, (double)clip_eps, factors,
-          bwd && T > 0 ? (float*)(ws + p.off_coef) : nullptr, (double*)(ws + p.off_delta), loss_out, status, steps, gate);
+          bwd && T > 0 ? (float*)(ws + p.off_coef) : nullptr, (double*)(ws + p.off_delta), loss_out, status, steps, gate,
+          finish ? *finish : LseFinish{});
     });
   };
   if (sweep) return sweep_path(p, begin, H, W, tokens, logq, logprob_out, dH, dW, ws, st, objective);
@@ -1577,7 +1592,7 @@ int32_t oapl_logprob_fwd(const void* H, const void* W, const int32_t* tokens, in
   if (int rc = pack_operands(p, H, W, ws, st)) return rc;
   if (int rc = forward_partials(p, H, W, entropy_out != nullptr, false, status, ws, st, kNoGate)) return rc;
   if (int rc = gather_logits(p, H, W, tokens, TokenInit{}, ws, st)) return rc;
-  return forward_finish(p, nullptr, logprob_out, lse_out, entropy_out, nullptr, ws, st, kNoGate);
+  return forward_finish(p, finish_args(p, nullptr, logprob_out, lse_out, entropy_out, nullptr, ws), st, kNoGate);
 }
 
 int32_t oapl_sample_tokens(const void* H, const void* W, int64_t T, int32_t d, int32_t V, int32_t dtype,

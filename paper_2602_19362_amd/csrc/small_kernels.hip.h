@@ -117,20 +117,39 @@ k_gather_logit(const T* __restrict__ H, const T* __restrict__ W, const int32_t* 
 // token are taken by `slices` (a power of two <= 256) threads, interleaved, and combined pairwise, so the few
 // tokens of a small call, which come with hundreds of partials each, are not walked by one thread each (777 tokens
 // with 64 partials: 47 us with one slice, 10 us with sixteen).
+struct LseFinish {
+  const float2* partials;
+  int n_parts;
+  int64_t Ttok;
+  const float *zy, *logq;
+  float *logprob_out, *lse_out, *lse2_ws;
+  double* diff_ws;
+  float *omp_ws, *inv_omp_ws;
+  const float* upart;
+  float* entropy_out;
+  int slices;
+  const int32_t* tokens;     // to check, or nullptr
+  int V;
+  int* err;
+};
+// Tokens t0 .. end - 1, at most 256 / slices of them, by a workgroup.
 template <bool LOG2>
-__global__ void __launch_bounds__(256)
-k_lse_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, const float* __restrict__ zy,
-             const float* __restrict__ logq, float* __restrict__ logprob_out, float* __restrict__ lse_out,
-             float* __restrict__ lse2_ws, double* __restrict__ diff_ws, float* __restrict__ omp_ws,
-             float* __restrict__ inv_omp_ws, const float* __restrict__ upart, float* __restrict__ entropy_out,
-             int slices, const int32_t* __restrict__ tokens /* to check, or nullptr */, int V, int* __restrict__ err, Gate gate) {
+__device__ __forceinline__ void lse_finish(const LseFinish& f, int64_t t0, int64_t end) {
   __shared__ float part_m[256];
   __shared__ double part_s[256], part_u[256];
-  if (gate_closed(gate)) return;
+  const float2* partials = f.partials;
+  const int n_parts = f.n_parts, slices = f.slices, V = f.V;
+  const int64_t Ttok = f.Ttok;
+  const float *zy = f.zy, *logq = f.logq, *upart = f.upart;
+  float *logprob_out = f.logprob_out, *lse_out = f.lse_out, *lse2_ws = f.lse2_ws, *omp_ws = f.omp_ws, *inv_omp_ws = f.inv_omp_ws,
+        *entropy_out = f.entropy_out;
+  double* diff_ws = f.diff_ws;
+  const int32_t* tokens = f.tokens;
+  int* err = f.err;
   const int rows = 256 / slices, col = threadIdx.x % rows, slice = threadIdx.x / rows;
-  const int64_t t = (int64_t)blockIdx.x * rows + col;
+  const int64_t t = t0 + col;
   float M = kNegHuge;
-  if (t < Ttok) {
+  if (t < end) {
 #pragma unroll 8
     for (int p = slice; p < n_parts; p += slices) M = fmaxf(M, partials[(int64_t)p * Ttok + t].x);
   }
@@ -142,7 +161,7 @@ k_lse_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, con
   __syncthreads();
   M = part_m[col];
   double S = 0.0, U = 0.0;
-  if (t < Ttok) {
+  if (t < end) {
 #pragma unroll 8
     for (int p = slice; p < n_parts; p += slices) {
       const float2 a = partials[(int64_t)p * Ttok + t];
@@ -161,7 +180,7 @@ k_lse_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, con
       part_u[threadIdx.x] = U += part_u[threadIdx.x + half * rows];
     }
   }
-  if (slice != 0 || t >= Ttok) return;
+  if (slice != 0 || t >= end) return;
   if (tokens && (tokens[t] < 0 || tokens[t] >= V)) record_token_error(err);
   const double lse = LOG2 ? ((double)M + log2(S)) * kLn2 : (double)M + log(S);
   double lp = (double)zy[t] - lse;   // NaN if the token was out of range
@@ -182,6 +201,11 @@ k_lse_finish(const float2* __restrict__ partials, int n_parts, int64_t Ttok, con
     omp_ws[t] = ok ? (float)omp : 0.f;
     inv_omp_ws[t] = ok ? (float)(1.0 / omp) : 0.f;
   }
+}
+template <bool LOG2>
+__global__ void __launch_bounds__(256) k_lse_finish(LseFinish f, Gate gate) {
+  if (gate_closed(gate)) return;
+  lse_finish<LOG2>(f, (int64_t)blockIdx.x * (256 / f.slices), f.Ttok);
 }
 
 // Picks, per token, the best (score, index) pair over the vocabulary splits (ties to the smaller index); slices as
@@ -480,6 +504,20 @@ __device__ __forceinline__ const float* token_factor(const TokenFactor f) {
   return f.flag != nullptr && *f.flag != 0 ? f.slow : f.fast;
 }
 
+// FINISH: the objective's launch makes the log-probs that it needs, each rollout's workgroup its tokens' (and the first and the
+// last those that malformed offsets leave out); fp32 calls, finish_in_objective in oapl_api.hip.
+__device__ __forceinline__ void finish_rollout(const LseFinish& f, const int64_t* off, int s0, int n_seq) {
+  int64_t a = 0, b = f.Ttok;
+  if (n_seq > 0) {
+    token_range(off, s0, f.Ttok, a, b);
+    if (s0 == 0) a = 0;
+    if (s0 == n_seq - 1) b = f.Ttok;
+  }
+  const int rows = 256 / f.slices;
+  for (int64_t t = a; t < b; t += rows) lse_finish<false>(f, t, b);
+  __syncthreads();
+}
+
 // Steps a4, a6, a7: per rollout
 //   Delta_s = sum_t diff[t]     (double, fixed order)
 //   delta_s = beta_l Delta_s - (r_s - V*_{g(s)})
@@ -487,14 +525,16 @@ __device__ __forceinline__ const float* token_factor(const TokenFactor f) {
 // and  loss = scale sum_s delta_s^2   (Eq. 3; one workgroup walks the rollouts, fixed summation order).
 // Also validates offsets and group ids; on a violation (or an empty prompt found by
 // group_value, whose V* is NaN) the loss is NaN and the status word is set.
+template <bool FINISH>
 __global__ void __launch_bounds__(256)
-k_oapl_objective(const double* __restrict__ diff, const float* __restrict__ rewards, const int32_t* __restrict__ gid,
+k_oapl_objective(const double* diff /* written here too (finish_rollout) */, const float* __restrict__ rewards, const int32_t* __restrict__ gid,
                  const int64_t* __restrict__ off, int n_seq, int n_groups, int64_t Ttok, double beta_l, double scale,
                  const double* __restrict__ vstar_ws, TokenFactor factors, double* Delta, float* __restrict__ coef,
-                 float* __restrict__ loss_out, float* __restrict__ seq_logratio_out, int* status, int steps, Gate gate) {
+                 float* __restrict__ loss_out, float* __restrict__ seq_logratio_out, int* status, int steps, Gate gate, LseFinish finish) {
   __shared__ int bad;
   if (gate_closed(gate)) return;
   const int tid = threadIdx.x, s0 = blockIdx.x;
+  if (FINISH && (steps & kRollouts)) finish_rollout(finish, off, s0, n_seq);
   auto advantage = [&](int s) {      // r_s - V*
     const int g = gid[s];
     return (double)rewards[s] - (g >= 0 && g < n_groups ? vstar_ws[g] : __builtin_nan(""));
@@ -545,13 +585,15 @@ k_oapl_objective(const double* __restrict__ diff, const float* __restrict__ rewa
 // it writes the loss gradient coefficient c_t = -w_s d term_t (times the factor) and the rollout's
 // loss share -w_s sum_t term_t (double, fixed order); loss = sum of the shares, NaN if an offsets / group error was
 // recorded.  lp comes as diff = lp - logq in double.
+template <bool FINISH>
 __global__ void __launch_bounds__(256)
-k_grpo_objective(const double* __restrict__ diff, const float* __restrict__ logq, const float* __restrict__ logp_old,
+k_grpo_objective(const double* diff /* written here too (finish_rollout) */, const float* __restrict__ logq, const float* __restrict__ logp_old,
                  const int64_t* __restrict__ off, int n_seq, int64_t Ttok, const float* __restrict__ adv,
                  const double* __restrict__ wseq, double clip_eps, TokenFactor factors, float* __restrict__ coef,
-                 double* seqterm, float* __restrict__ loss_out, int* status, int steps, Gate gate) {
+                 double* seqterm, float* __restrict__ loss_out, int* status, int steps, Gate gate, LseFinish finish) {
   if (gate_closed(gate)) return;
   const int tid = threadIdx.x, s0 = blockIdx.x;
+  if (FINISH && (steps & kRollouts)) finish_rollout(finish, off, s0, n_seq);
   if ((steps & kRollouts) && s0 < n_seq) {
     int64_t a, b;
     token_range(off, s0, Ttok, a, b);

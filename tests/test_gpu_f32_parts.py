@@ -55,3 +55,16 @@ def test_numbers_at_the_ends_of_the_range(d):
     assert abs(f64(lp)[ok] - (z[ok][np.arange(T)[ok] >= 0, np.arange(T)[ok]] - ref)).max() <= 1e-5
     assert np.isfinite(f64(ent)[ok]).all()
     assert not np.isfinite(f64(lse)[~ok]).any()
+
+
+@pytest.mark.parametrize("off", [[0, 40, 70], [5, 40, 70], [0, 60, 30], [50, 10, 20], [0, 200, 70], [-3, 10, 66], [0, 0, 0]])
+@pytest.mark.parametrize("d,V", [(40, 130), (40, 6000)])      # finished in the objective's launch and in one of its own
+def test_every_token_has_its_log_prob_whatever_the_offsets(d, V, off):
+    T = 70
+    b = _custom_batch("f32", d=d, V=V, lens=[40, 30], n_groups=1, seed=V, beta=1.0)
+    off = torch.tensor(off, dtype=torch.int64, device=b.H.device)
+    res = oapl.loss_fwd_bwd(b.H, b.W, b.tokens, b.logq, off, b.rewards, b.group_ids, 1, 1.0)
+    assert (oapl.read_device_status(res.workspace) != 0) == (off.tolist() != [0, 40, 70])
+    z = f64(b.H) @ f64(b.W).T
+    ref = z[np.arange(T), b.tokens.cpu().numpy()] - np.log(np.exp(z).sum(1))
+    assert abs(f64(res.logprob) - ref).max() <= 1e-5
