@@ -4,7 +4,8 @@
 // later parts make up for the bits between): x = x0 + x1 + x2, to the bit.  Of the nine products of two such sums six are taken,
 //     x0 y0  +  (x0 y1 + x1 y0)  +  (x1 y1 + x0 y2 + x2 y0),
 // and what is left out, x1 y2 + x2 y1 + x2 y2, is at most 2^-26 |x y|, a quarter of what an fp32 product's own rounding may be.
-// (Numbers below 2^-110 are held to 2^-134, half the least bf16 number: a thirty-fourth decimal place.)
+// A tile in which a number is past the parts' range, or a sum past that of fp32 at the parts' scale, infinite or NaN, is multiplied
+// once more, as v_mfma_f32_32x32x2_f32 does it: every fp32 number is an operand, to the last bit.
 // v_mfma_f32_32x32x16_bf16 does a product exactly and sixteen times as fast as v_mfma_f32_32x32x2_f32 does an fp32 one.  The first
 // products are added up apart from the others: a matrix core's addition cuts addends far below its result off downwards (-0.003
 // ulp on average), which five times as many additions into the large sum turned into a bias of 2e-7 of a token's log-prob (with
@@ -51,6 +52,11 @@ typedef F32Cfg<2, 2, 2, 2> F32Large;   // 128 x 128, 48 KB
 typedef F32Cfg<2, 2, 1, 1> F32Small;   // 64 x 64, 24 KB
 typedef F32Cfg<1, 4, 2, 1> F32Flat;    // 64 x 128, 36 KB: logits of few tokens (a wavefront still owns 64 vocabulary rows)
 
+// Numbers are multiplied by 2^24 before they are split, which makes every part of every one of them, down to the least, a normal
+// bf16 number or zero.  The parts of numbers from 2^104 on are infinite, the last one NaN, and so is every sum that they go into.
+constexpr float kF32Scale = 16777216.f;
+constexpr float kF32Unscale = 1.f / kF32Scale / kF32Scale;     // ... of a product
+
 // The bf16 parts of two fp32 numbers, packed: x = hi + mid + lo.
 struct F32Parts {
   uint32_t hi, mid, lo;
@@ -69,111 +75,85 @@ __device__ __forceinline__ F32Parts f32_split(float x0, float x1) {
   p.lo = f32_bf16_pair(r0 - __uint_as_float(p.mid << 16), r1 - __uint_as_float(p.mid & 0xFFFF0000u));
   return p;
 }
-// Numbers that round to an infinite bf16: a finite one's first part is the largest bf16, and an infinite one is 1 + 0 +
-// infinity, so that its product with y is y's sign times infinity, NaN for y = 0, whatever y's own parts are.
-constexpr float kBf16Max = 3.3895313892515355e38f;
-__device__ __forceinline__ F32Parts f32_split_huge(float x0, float x1) {
-  float part[3][2];
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    const float x = e == 0 ? x0 : x1;
-    const bool inf = fabsf(x) == __builtin_inff();
-    const float hi = inf ? copysignf(1.f, x) : fabsf(x) > kBf16Max ? copysignf(kBf16Max, x) : (float)(bf16_t)x;
-    const float mid = inf ? 0.f : (float)(bf16_t)(x - hi);
-    part[0][e] = hi;
-    part[1][e] = mid;
-    part[2][e] = inf ? x : x - hi - mid;
-  }
-  return F32Parts{f32_bf16_pair(part[0][0], part[0][1]), f32_bf16_pair(part[1][0], part[1][1]),
-                  f32_bf16_pair(part[2][0], part[2][1])};
-}
 
 // One operand's ROWS x 32 stage by NT threads: global -> registers -> three planes of bf16 parts in LDS, [row][k] whatever the
 // order in memory.  A thread has pieces of four k of one row.  k contiguous: eight lanes load the 128 bytes of a row, a
 // line, by 16 (by 32 in two loads every line is asked for twice).  Rows contiguous: 64 lanes load 64 rows of one k, and two
 // pieces, eight k, are written at once.  16-byte chunk c of row r lies at chunk c ^ (r / 4 % 4): 16 lanes that read one chunk
-// of consecutive rows, or write one, or write whole rows, touch all banks.
+// of consecutive rows, or write one, or write whole rows, touch all banks.  The numbers themselves (store_plain) take two
+// planes, sixteen k each.
 template <int ROWS, int NT, bool KC>
 struct F32Stage {
   static constexpr int PITCH = 64, PLANE = ROWS * PITCH;
   static constexpr int N = ROWS * 8 / NT;     // pieces per thread
   static __device__ __forceinline__ int at(int row, int c) { return row * PITCH + ((c ^ ((row >> 2) & 3)) << 4); }
-  const float* p[KC ? N : N / 2];   // KC: this thread's piece of the next stage; else the wavefront's, from the tile's first row
+  const float* p[KC ? 1 : N / 2];   // the next stage, from the tile's first row; not KC: the wavefront's chunks of it
   f32x4 v[N];
   u32x2 hi[N], mid[N], lo[N];
   int64_t ld;
-  uint32_t lane_row;        // not KC: the thread's row in the tile
+  uint32_t off[KC ? N : 1];         // KC: bytes from there to this thread's pieces (a tile has under 2^32); else the thread's row
   int wave;
 
   // not KC: chunk i of this wavefront
   __device__ __forceinline__ int chunk(int i) const { return wave * 64 / ROWS + i * (NT / ROWS); }
   // Rows past the matrix are its last row again: what they give is not stored.
-  __device__ __forceinline__ void init(const F32Operand& o, int64_t r0, int64_t R, int64_t k0) {
+  __device__ __forceinline__ void init(const F32Operand& o, int64_t r0, int64_t R, int64_t k0, unsigned tid) {
     ld = o.ld;
-    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int last = (int)(R - r0 < ROWS ? R - r0 : ROWS) - 1;
     if constexpr (KC) {
+      p[0] = o.p + r0 * ld + k0;
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        const int row = (threadIdx.x + i * NT) >> 3;
-        p[i] = o.p + (r0 + (row < last ? row : last)) * ld + k0 + (threadIdx.x & 7) * 4;
+        const int row = (tid + i * NT) >> 3;
+        off[i] = ((uint32_t)(row < last ? row : last) * (uint32_t)ld + (tid & 7) * 4) * 4;
       }
     } else {
 #pragma unroll
       for (int i = 0; i < N / 2; ++i) p[i] = o.p + (k0 + chunk(i) * 8) * ld + r0;
-      const int row = threadIdx.x % ROWS;
-      lane_row = (uint32_t)(row < last ? row : last);
+      const int row = tid % ROWS;
+      off[0] = (uint32_t)(row < last ? row : last);
     }
   }
   // The next stage, of which `left` k exist; leaves the pointers at the one behind it.  k past the end are zeros.
   __device__ __forceinline__ void load(int64_t left) {
     if constexpr (KC) {
+      auto piece = [&](int i) {
+        uint32_t o = off[i];
+        asm("" : "+v"(o));      // or the compiler steps N addresses of 64 bits
+        return (const char*)p[0] + o;
+      };
       if (left >= 32) {
         typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
-        for (int i = 0; i < N; ++i) v[i] = *(const f32x4_any*)p[i];
+        for (int i = 0; i < N; ++i) v[i] = *(const f32x4_any*)piece(i);
       } else {
 #pragma unroll
         for (int i = 0; i < N; ++i)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[i][e] = (int)(threadIdx.x & 7) * 4 + e < left ? p[i][e] : 0.f;
+          for (int e = 0; e < 4; ++e) v[i][e] = (int)(threadIdx.x & 7) * 4 + e < left ? ((const float*)piece(i))[e] : 0.f;
       }
-#pragma unroll
-      for (int i = 0; i < N; ++i) p[i] += 32;
+      p[0] += 32;
     } else {
 #pragma unroll
       for (int i = 0; i < N / 2; ++i) {
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-          v[2 * i + e / 4][e % 4] = left >= 32 || chunk(i) * 8 + e < left ? (p[i] + e * ld)[lane_row] : 0.f;
+          v[2 * i + e / 4][e % 4] = left >= 32 || chunk(i) * 8 + e < left ? (p[i] + e * ld)[off[0]] : 0.f;
         p[i] += 32 * ld;
       }
     }
   }
   __device__ __forceinline__ void split() {
-    float big = 0.f;
 #pragma unroll
     for (int i = 0; i < N; ++i)
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
-        const float x0 = v[i][2 * e], x1 = v[i][2 * e + 1];
-        const F32Parts x = f32_split(x0, x1);
+        const F32Parts x = f32_split(v[i][2 * e] * kF32Scale, v[i][2 * e + 1] * kF32Scale);
         hi[i][e] = x.hi;
         mid[i][e] = x.mid;
         lo[i][e] = x.lo;
-        asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(big) : "v"(x0), "v"(x1));   // (fmaxf quiets its inputs first)
       }
-    if (__builtin_expect(big > kBf16Max, 0)) {
-#pragma unroll
-      for (int i = 0; i < N; ++i)
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const F32Parts x = f32_split_huge(v[i][2 * e], v[i][2 * e + 1]);
-          hi[i][e] = x.hi;
-          mid[i][e] = x.mid;
-          lo[i][e] = x.lo;
-        }
-    }
   }
   __device__ __forceinline__ void store(lds_char_ptr s) const {
     typedef __attribute__((address_space(3))) u32x2* piece;
@@ -195,6 +175,24 @@ struct F32Stage {
         *(pieces)(d + 2 * PLANE) = __builtin_shufflevector(lo[2 * i], lo[2 * i + 1], 0, 1, 2, 3);
       }
     }
+  }
+  __device__ __forceinline__ void store_plain(lds_char_ptr s) const {
+    typedef __attribute__((address_space(3))) f32x4* piece;
+    if constexpr (KC) {
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        *(piece)(s + ((threadIdx.x & 7) >> 2) * PLANE + at((threadIdx.x + i * NT) >> 3, threadIdx.x & 3)) = v[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const int c = chunk(i / 2) * 2 + (i & 1);     // of eight
+        *(piece)(s + (c >> 2) * PLANE + at(threadIdx.x % ROWS, c & 3)) = v[i];
+      }
+    }
+  }
+  // ... back: the four k 8 * g + 4 * half of a row
+  static __device__ __forceinline__ f32x4 plain(lds_char_ptr s, int row, int g, int half) {
+    return *(const __attribute__((address_space(3))) f32x4*)(s + (g >> 1) * PLANE + at(row, (g & 1) * 2 + half));
   }
 };
 
@@ -232,8 +230,8 @@ __device__ __forceinline__ void gemm_f32_tile(const F32Operand& A, const F32Oper
 
   SA sa;
   SB sb;
-  sa.init(A, m0, M, kb);
-  sb.init(B, n0, N, kb);
+  sa.init(A, m0, M, kb, threadIdx.x);
+  sb.init(B, n0, N, kb, threadIdx.x);
   auto load = [&](int s) {
     sa.load(len - (int64_t)s * C::BK);
     sb.load(len - (int64_t)s * C::BK);
@@ -320,10 +318,53 @@ __device__ __forceinline__ void gemm_f32_tile(const F32Operand& A, const F32Oper
       }
     }
   }
+  float finite = 0.f;     // 0 times every sum: NaN if one is not finite
 #pragma unroll
   for (int i = 0; i < C::TM; ++i)
 #pragma unroll
-    for (int j = 0; j < C::TN; ++j) acc[i][j] += small[i][j];
+    for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float sum = acc[i][j][r] + small[i][j][r];
+        finite = __builtin_fmaf(sum, 0.f, finite);
+        acc[i][j][r] = sum * kF32Unscale;
+      }
+  // Numbers without parts (infinities and NaN among them), or sums that the scale took out of range: once more, with fp32
+  // multiplications.
+  if (__builtin_expect(__syncthreads_or(!(finite == 0.f)), 0)) {
+#pragma unroll
+    for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+      for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    unsigned tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));     // or the first pass keeps its addresses for this one
+    sa.init(A, m0, M, kb, tid);
+    sb.init(B, n0, N, kb, tid);
+    for (int s = 0; s < n_stages; ++s) {
+      load(s);
+      __syncthreads();      // everyone has read the stage before
+      sa.store_plain(lds);
+      sb.store_plain(lds + C::STAGE_A);
+      __syncthreads();
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        f32x4 a[C::TM], b[C::TN];
+#pragma unroll
+        for (int i = 0; i < C::TM; ++i) a[i] = SA::plain(lds, (wm * C::TM + i) * 32 + (lane & 31), g, half);
+#pragma unroll
+        for (int j = 0; j < C::TN; ++j) b[j] = SB::plain(lds + C::STAGE_A, (wn * C::TN + j) * 32 + (lane & 31), g, half);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+            for (int j = 0; j < C::TN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
+      }
+    }
+  }
   epi.template store<C::TM, C::TN>(acc, m0 + wm * C::TM * 32, n0 + wn * C::TN * 32 + (lane & 31), half, M, N, bz);
 #endif
 }
