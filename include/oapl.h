@@ -69,7 +69,7 @@ typedef enum {
 } oapl_status;
 
 typedef enum {
-  OAPL_F32 = 0,  /* H, W, dH are float; fp32 products and sums (matrix cores) */
+  OAPL_F32 = 0,  /* H, W, dH are float; products to 2^-34 of themselves, sums in fp32 (matrix cores) */
   OAPL_BF16 = 1  /* H, W, dH are bfloat16 (raw uint16 bit patterns); MFMA with fp32 accumulation */
 } oapl_dtype;
 
