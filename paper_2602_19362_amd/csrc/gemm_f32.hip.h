@@ -373,16 +373,21 @@ __device__ __forceinline__ void gemm_f32_tile(const F32Operand& A, const F32Oper
 #endif
 }
 
-// A grid of f32_grid(columns * rows * splits) of tiles. Every XCD has a range of the splits, and of the rows in them, and walks
-// their columns first, so that few others read the same part of A: 1501 x 768 x 8192 in seven splits 10.6 MB per XCD in place of
-// all 75 (logits of 1501 tokens at d = 768, V = 8192 133 / 127 us, with the loads by whole lines).
-__host__ __device__ constexpr int64_t f32_grid(int64_t tiles) { return (tiles + 7) / 8 * 8; }
+// A grid for so many tiles (columns * rows * splits), with as many threads in a dimension as HIP takes (2^32 less one) at 512 a
+// workgroup.  Every XCD has a range of the splits, and of the rows in them, and walks their columns first, so that few others
+// read the same part of A: 1501 x 768 x 8192 in seven splits 10.6 MB per XCD in place of all 75 (logits of 1501 tokens at d = 768,
+// V = 8192 133 / 127 us, with the loads by whole lines).
+static inline dim3 f32_grid(int64_t tiles) {
+  const int64_t x = (tiles + 7) / 8 * 8, most = 1 << 22;
+  return x <= most ? dim3((unsigned)x) : dim3((unsigned)most, (unsigned)((x + most - 1) / most));
+}
 template <class C, bool A_KC, bool B_KC, class Epi>
 __global__ void __launch_bounds__(C::NT, 2) k_gemm_f32(F32Operand A, F32Operand B, int64_t M, int64_t N, int64_t K, Epi epi,
                                                        unsigned splits) {
   extern __shared__ __attribute__((aligned(256))) char smem_raw[];     // C::LDS
   const unsigned nx = (unsigned)((N + C::BN - 1) / C::BN), ny = (unsigned)((M + C::BM - 1) / C::BM);
-  const unsigned i = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const unsigned block = blockIdx.y * gridDim.x + blockIdx.x;
+  const unsigned i = (block & 7) * (gridDim.x * gridDim.y >> 3) + (block >> 3);
   if (i / nx >= ny * splits) return;
   gemm_f32_tile<C, A_KC, B_KC>(A, B, M, N, K, epi, i % nx, i / nx % ny, i / nx / ny, splits, smem_raw);
 }

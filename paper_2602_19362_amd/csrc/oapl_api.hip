@@ -386,7 +386,7 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
   // and the packing kernels index token tiles with gridDim.y
   if ((int64_t)d > (1 << 21) || (int64_t)V > (1 << 21)) return false;
   if (dtype == OAPL_BF16 && T > (int64_t)65535 * 256) return false;
-  // the fp32 kernels index 64-row token tiles with gridDim.y
+  // the fp32 kernels' bytes from a tile's first row to its last (255 rows of dZ^T, at most T long) and their tiles are 32-bit
   if (dtype == OAPL_F32 && T > (int64_t)65535 * 64) return false;
   if ((int64_t)n_seq * n_groups > kGroupScanLimit) return false;
   const int64_t cap = panel_cap(dtype, max_panel_rows);
@@ -738,7 +738,7 @@ static bool logits_large_f32(int V, int64_t T) {
 template <class C, class Epi>
 static void launch_logits_f32(const Plan& p, const F32Operand& A, const F32Operand& B, int64_t T, Epi epi, hipStream_t st) {
   const int64_t tiles = (int64_t)grid1d(p.V, C::BM) * grid1d(T, C::BN);
-  k_gemm_f32<C, true, true><<<(unsigned)f32_grid(tiles), C::NT, C::LDS, st>>>(A, B, (int64_t)p.V, T, (int64_t)p.d, epi, 1);
+  k_gemm_f32<C, true, true><<<f32_grid(tiles), C::NT, C::LDS, st>>>(A, B, (int64_t)p.V, T, (int64_t)p.d, epi, 1);
 }
 template <class Epi>
 static void launch_logits_f32(const Plan& p, const void* H, const void* W, int64_t T, Epi epi, hipStream_t st) {
@@ -767,7 +767,7 @@ static F32Contraction contraction_f32(const F32Pick& pick, int wide, const F32Op
 }
 template <class C, bool A_KC>
 static void launch_contract_f32(const F32Contraction& c, int accumulate, hipStream_t st) {
-  k_gemm_f32<C, A_KC, false><<<(unsigned)f32_grid((int64_t)c.nx * c.ny * c.splits), C::NT, C::LDS, st>>>(
+  k_gemm_f32<C, A_KC, false><<<f32_grid((int64_t)c.nx * c.ny * c.splits), C::NT, C::LDS, st>>>(
       c.A, c.B, c.M, c.N, c.K, EpiStoreF32{c.out, c.N, accumulate}, c.splits);
 }
 template <bool A_KC>

@@ -52,6 +52,11 @@ int main() {
         least = w.r1 - w.r0 < least ? w.r1 - w.r0 : least;
       }
       std::printf("wrong=%d end=%d most=%d least=%d\n", wrong, at, most, least);
+    } else if (std::sscanf(line, "f32grid %lld", &T) == 1) {
+      // the launch of T tiles: workgroups, and the most threads in a dimension
+      const dim3 g = f32_grid(T);
+      const long long x = (long long)g.x * F32Wide::NT, y = g.y, z = g.z;
+      std::printf("tiles=%lld most=%lld rest=%d\n", (long long)g.x * y * z, x > y ? x : y, (int)(g.x % 8));
     } else if (std::sscanf(line, "plan %lld %d %d %d %d %lld %u %lld", &T, &d, &V, &dtype, &bwd, &cap, &unaligned, &have) == 8) {
       // the plan of a call of one rollout on `have` bytes (< 0: what the library asks for with panels of `cap` rows)
       if (have < 0) have = (long long)oapl_workspace_bytes_for(T, d, V, 1, 1, dtype, bwd, cap, 0, nullptr, nullptr);

@@ -141,3 +141,12 @@ def test_sampling_tiles_are_as_wide_as_the_tokens_need():
     for T, d, V, w, rows in cases.CASES:
         p = ask([f"plan {T} {d} {V} 1 0 0 0 -1"])[0]
         assert (width[p["smp_tile"]], p["rows"]) == (w, rows), (T, d, V, p)
+
+
+@pytest.mark.parametrize("tiles", [1, 8, 9, 1187, 2 ** 22, 2 ** 22 + 1, 2 ** 24 + 1187, 2 ** 30])
+def test_fp32_launches_hold_every_tile(tiles):
+    """Up to the tiles of the most tokens and the largest vocabulary: fewer threads than 2^32 in a dimension, a multiple of eight
+    workgroups in a row (XCDs take turns), and no more idle ones than a row of them."""
+    a = ask([f"f32grid {tiles}"])[0]
+    assert a["tiles"] >= tiles and a["most"] < 2 ** 32 and a["rest"] == 0
+    assert a["tiles"] - tiles < (8 if tiles <= 2 ** 22 else 2 ** 22)
