@@ -674,9 +674,11 @@ k_sweep_finish(const float* __restrict__ spart, int n_vt, int64_t ld_s, int64_t 
     if (kept != 0.0 && isfinite(entry)) row_factor *= entry / kept;
     // both copies are n-side operands: blocks of g_rows tokens and of kPackRowsB vocabulary rows x 64 k
     const int64_t blk = (int64_t)kPackRowsB * kPackK;             // elements of a packed block
-    const int64_t nb = n / g_rows, nr = n - nb * g_rows;          // token row block / row inside it
+    // token row block / row inside it: a division by a constant for all but the few calls in narrower tiles (64 bits by a
+    // variable: 165 instructions in a launch that the whole call waits for)
+    const uint32_t row = (uint32_t)n, nb = g_rows == kPackRowsB ? row / kPackRowsB : row / (uint32_t)g_rows, nr = row - nb * g_rows;
     const int yb = y / kPackRowsB, yr = y - yb * kPackRowsB;      // vocabulary row block / row inside it
-    Gp[((nb * g_n_kt + (y >> 6)) * g_rows + nr) * kPackK + (y & 63)] = patch;
+    Gp[(((int64_t)nb * g_n_kt + (y >> 6)) * g_rows + nr) * kPackK + (y & 63)] = patch;
     GTp[((int64_t)yb * gt_n_kt + (n >> 6)) * blk + (int64_t)yr * kPackK + (n & 63)] = patch;
   }
   if (y < 0 || y >= V) record_token_error(status);
