@@ -1435,10 +1435,14 @@ static int loss_impl(const void* H, const void* W, const int32_t* tokens, const 
   // Steps a4, a6, a7 from logprob - logq [T]
   auto objective = [&](Gate gate, TokenFactor factors, const LseFinish* finish) -> int {
     return objective_steps(n_seq, [&](unsigned grid, int steps) {
-      (finish ? k_oapl_objective<true> : k_oapl_objective<false>)<<<grid, 256, 0, st>>>(
-          (const double*)(ws + p.off_diff), rewards, group_ids, seq_offsets, n_seq, n_groups, T, (double)beta_loss,
-          (double)loss_scale, vstar, factors, (double*)(ws + p.off_delta), bwd && T > 0 ? (float*)(ws + p.off_coef) : nullptr,
-          loss_out, seq_logratio_out, status, steps, gate, finish ? *finish : LseFinish{});
+      auto run = [&](auto kernel, const auto& finish_arg) {
+        kernel<<<grid, 256, 0, st>>>(
+            (const double*)(ws + p.off_diff), rewards, group_ids, seq_offsets, n_seq, n_groups, T, (double)beta_loss,
+            (double)loss_scale, vstar, factors, (double*)(ws + p.off_delta), bwd && T > 0 ? (float*)(ws + p.off_coef) : nullptr,
+            loss_out, seq_logratio_out, status, steps, gate, finish_arg);
+      };
+      if (finish) run(k_oapl_objective<true>, *finish);
+      else run(k_oapl_objective<false>, NoFinish{});
     });
   };
   // bf16 with gradients: one sweep over the logits; the two-pass schedule behind it runs only if the
@@ -1483,10 +1487,14 @@ static int grpo_impl(const void* H, const void* W, const int32_t* tokens, const 
 
   auto objective = [&](Gate gate, TokenFactor factors, const LseFinish* finish) -> int {
     return objective_steps(n_seq, [&](unsigned grid, int steps) {
-      (finish ? k_grpo_objective<true> : k_grpo_objective<false>)<<<grid, 256, 0, st>>>(
-          (const double*)(ws + p.off_diff), logq, logp_old, seq_offsets, n_seq, T, adv, wseq, (double)clip_eps, factors,
-          bwd && T > 0 ? (float*)(ws + p.off_coef) : nullptr, (double*)(ws + p.off_delta), loss_out, status, steps, gate,
-          finish ? *finish : LseFinish{});
+      auto run = [&](auto kernel, const auto& finish_arg) {
+        kernel<<<grid, 256, 0, st>>>(
+            (const double*)(ws + p.off_diff), logq, logp_old, seq_offsets, n_seq, T, adv, wseq, (double)clip_eps, factors,
+            bwd && T > 0 ? (float*)(ws + p.off_coef) : nullptr, (double*)(ws + p.off_delta), loss_out, status, steps, gate,
+            finish_arg);
+      };
+      if (finish) run(k_grpo_objective<true>, *finish);
+      else run(k_grpo_objective<false>, NoFinish{});
     });
   };
   if (sweep) return sweep_path(p, begin, H, W, tokens, logq, logprob_out, dH, dW, ws, st, objective);

@@ -4,6 +4,8 @@
 // three V x d contractions; written for exactness and a fixed summation order.
 #pragma once
 
+#include <type_traits>
+
 #include "common.hip.h"
 #include "rng.hip.h"
 
@@ -517,6 +519,12 @@ __device__ __forceinline__ void finish_rollout(const LseFinish& f, const int64_t
   for (int64_t t = a; t < b; t += rows) lse_finish<false>(f, t, b);
   __syncthreads();
 }
+// Only the kernels that finish log-probs take what that needs, and write what they sum up.
+struct NoFinish {};
+template <bool FINISH>
+using FinishArg = std::conditional_t<FINISH, LseFinish, NoFinish>;
+template <bool FINISH>
+using DiffArg = std::conditional_t<FINISH, const double*, const double* __restrict__>;
 
 // Steps a4, a6, a7: per rollout
 //   Delta_s = sum_t diff[t]     (double, fixed order)
@@ -527,14 +535,17 @@ __device__ __forceinline__ void finish_rollout(const LseFinish& f, const int64_t
 // group_value, whose V* is NaN) the loss is NaN and the status word is set.
 template <bool FINISH>
 __global__ void __launch_bounds__(256)
-k_oapl_objective(const double* diff /* written here too (finish_rollout) */, const float* __restrict__ rewards, const int32_t* __restrict__ gid,
+k_oapl_objective(DiffArg<FINISH> diff, const float* __restrict__ rewards, const int32_t* __restrict__ gid,
                  const int64_t* __restrict__ off, int n_seq, int n_groups, int64_t Ttok, double beta_l, double scale,
                  const double* __restrict__ vstar_ws, TokenFactor factors, double* Delta, float* __restrict__ coef,
-                 float* __restrict__ loss_out, float* __restrict__ seq_logratio_out, int* status, int steps, Gate gate, LseFinish finish) {
+                 float* __restrict__ loss_out, float* __restrict__ seq_logratio_out, int* status, int steps, Gate gate,
+                 FinishArg<FINISH> finish) {
   __shared__ int bad;
   if (gate_closed(gate)) return;
   const int tid = threadIdx.x, s0 = blockIdx.x;
-  if (FINISH && (steps & kRollouts)) finish_rollout(finish, off, s0, n_seq);
+  if constexpr (FINISH) {
+    if (steps & kRollouts) finish_rollout(finish, off, s0, n_seq);
+  }
   auto advantage = [&](int s) {      // r_s - V*
     const int g = gid[s];
     return (double)rewards[s] - (g >= 0 && g < n_groups ? vstar_ws[g] : __builtin_nan(""));
@@ -587,13 +598,15 @@ k_oapl_objective(const double* diff /* written here too (finish_rollout) */, con
 // recorded.  lp comes as diff = lp - logq in double.
 template <bool FINISH>
 __global__ void __launch_bounds__(256)
-k_grpo_objective(const double* diff /* written here too (finish_rollout) */, const float* __restrict__ logq, const float* __restrict__ logp_old,
+k_grpo_objective(DiffArg<FINISH> diff, const float* __restrict__ logq, const float* __restrict__ logp_old,
                  const int64_t* __restrict__ off, int n_seq, int64_t Ttok, const float* __restrict__ adv,
                  const double* __restrict__ wseq, double clip_eps, TokenFactor factors, float* __restrict__ coef,
-                 double* seqterm, float* __restrict__ loss_out, int* status, int steps, Gate gate, LseFinish finish) {
+                 double* seqterm, float* __restrict__ loss_out, int* status, int steps, Gate gate, FinishArg<FINISH> finish) {
   if (gate_closed(gate)) return;
   const int tid = threadIdx.x, s0 = blockIdx.x;
-  if (FINISH && (steps & kRollouts)) finish_rollout(finish, off, s0, n_seq);
+  if constexpr (FINISH) {
+    if (steps & kRollouts) finish_rollout(finish, off, s0, n_seq);
+  }
   if ((steps & kRollouts) && s0 < n_seq) {
     int64_t a, b;
     token_range(off, s0, Ttok, a, b);
