@@ -911,14 +911,17 @@ static int forward_finish(const Plan& p, const LseFinish& f, hipStream_t st, Gat
   return OAPL_OK;
 }
 
-// An fp32 loss call's log-probs are finished by the objective's launch where that is little work even for one workgroup (one
-// rollout may have all tokens): a dependent launch costs a small call 5 us whatever is in it. 256 tokens at d = 64, V = 1024 (16
-// partials each) 34.9 us in two launches, 31.6 in one; in one, 373 tokens of 32 partials (a rollout's workgroup has them one
-// after the other) take 6 us longer. In bf16, where the finish is the fallback's and closed, the launch that it
-// saves goes into the larger kernel (1000 tokens at d = 256, V = 1544 53.6 / 53.4).
-constexpr int64_t kFinishInObjective = 5000;
+// An fp32 loss call's log-probs are finished by the objective's launch where that is little work for one workgroup: a dependent
+// launch costs a small call 5 us whatever is in it, and a rollout's workgroup has its tokens in rounds of 256 / slices, 4 us each,
+// that a launch of its own has side by side.  Up to two rounds of tokens, so that even one rollout with all of them takes no longer:
+// one launch less / one more, d = 64, us: one rollout, V = 64, 512 tokens (2 rounds) 31.5 / 36.3, 1536 (6) 35.5 / 36.7, 2048 (8) 40.2 /
+// 36.1, V = 1024, 128 (2) 33.2 / 35.2, 192 (3) 39.5 / 35.6, V = 8192, 16 (2) 35.9 / 36.1, 32 (4) 43.4 / 35.8.  Up to four rounds where
+// rollouts of twice the mean length have one: 256 tokens of eight rollouts, V = 1024, 31.7 / 35 (all of them in one of the eight,
+// which the host does not see, 39).  In bf16, where the finish is the fallback's and closed, the launch that it saves goes into the
+// larger kernel (1000 tokens at d = 256, V = 1544 53.6 / 53.4).
 static bool finish_in_objective(const Plan& p) {
-  return p.dtype == OAPL_F32 && p.T > 0 && p.T * p.fwd.splits <= kFinishInObjective;
+  const int64_t round = 256 / finish_slices(p.fwd.splits);
+  return p.dtype == OAPL_F32 && p.T > 0 && (p.T <= 2 * round || (p.T <= 4 * round && 2 * p.T <= round * p.n_seq));
 }
 
 // Calls f with the large tile of that many columns.

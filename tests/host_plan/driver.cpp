@@ -57,6 +57,11 @@ int main() {
       const dim3 g = f32_grid(T);
       const long long x = (long long)g.x * F32Wide::NT, y = g.y, z = g.z;
       std::printf("tiles=%lld most=%lld rest=%d\n", (long long)g.x * y * z, x > y ? x : y, (int)(g.x % 8));
+    } else if (std::sscanf(line, "finish %lld %d %d", &T, &V, &n_seq) == 3) {
+      // an fp32 loss call's log-probs: in the objective's launch?
+      Plan p;
+      const bool ok = make_plan(p, T, 64, V, n_seq, 1, OAPL_F32, true, 0);
+      std::printf("ok=%d together=%d\n", ok, finish_in_objective(p));
     } else if (std::sscanf(line, "plan %lld %d %d %d %d %lld %u %lld", &T, &d, &V, &dtype, &bwd, &cap, &unaligned, &have) == 8) {
       // the plan of a call of one rollout on `have` bytes (< 0: what the library asks for with panels of `cap` rows)
       if (have < 0) have = (long long)oapl_workspace_bytes_for(T, d, V, 1, 1, dtype, bwd, cap, 0, nullptr, nullptr);

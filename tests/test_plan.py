@@ -150,3 +150,12 @@ def test_fp32_launches_hold_every_tile(tiles):
     a = ask([f"f32grid {tiles}"])[0]
     assert a["tiles"] >= tiles and a["most"] < 2 ** 32 and a["rest"] == 0
     assert a["tiles"] - tiles < (8 if tiles <= 2 ** 22 else 2 ** 22)
+
+
+@pytest.mark.parametrize("T,V,rollouts,together", [
+    (5000, 64, 1, 0), (2048, 64, 1, 0), (513, 64, 1, 0), (512, 64, 1, 1), (32, 8192, 4, 0), (16, 8192, 1, 1),
+    (256, 1024, 8, 1), (257, 1024, 64, 0), (256, 1024, 7, 0), (256, 1024, 1, 0), (128, 1024, 1, 1), (100, 64, 0, 1)])
+def test_log_probs_are_finished_with_the_objective_where_that_is_short(T, V, rollouts, together):
+    """Rounds of 256 tokens at V = 64, 64 at 1024 and 8 at 8192, one after the other if one rollout has them."""
+    a = ask([f"finish {T} {V} {rollouts}"])[0]
+    assert a == dict(ok=1, together=together)
