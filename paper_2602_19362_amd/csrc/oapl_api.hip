@@ -32,7 +32,8 @@ typedef TileCfg<2, 2, 4, 4, 4, kPackRowsB> CfgDeep;
 // tile.  128 x 64 (48 KB of LDS, three workgroups per CU to keep W streaming through each other's barriers) serves up to 64 tokens,
 // 128 x 128 (two per CU) up to 128.  From there on a tile is one per CU and 256 tall, and its width follows from the token count
 // (pick_tile); up to 256 tokens it may be 320 tall instead, where that divides the rows of a CU into fewer or better filled
-// tiles (V = 151936, 594 rows per CU: two tiles of 297 in place of three of 198).
+// tiles (V = 151936, 594 rows per CU: two tiles of 297 in place of three of 198; scoring and sampling 200 tokens at d = 3000
+// 249 / 271 and 266 / 286 us, at d = 512 46 / 51, 59 / 67; with loads that go out early (Cfg256Early) 254, 265).
 typedef TileCfg<4, 1, 2, 4, 2> Cfg64;
 typedef TileCfg<4, 2, 2, 4, 2> Cfg128;
 typedef TileCfg<4, 2, 4, 8, 2> Cfg256;
@@ -176,28 +177,67 @@ static TilePick pick_splits(FwdTile tile, int64_t T, int V, int max_splits, doub
 }
 
 // Tile and splits over row-major operands.  Up to 256 tokens the call is bound by reading W, and as many workgroups as the CUs
-// hold at once share its rows evenly. Beyond, the wide tile is the cheapest per column and a narrower one pads fewer columns: the
+// hold at once share its rows evenly, but for ranges in which a W that is not read once (once_pays) is read faster in whole tiles.
+// Whole / even, us, scoring and sampling:
+//   64 tokens: even pays only where whole tiles are 3.7 .. 4 per CU, so that their second round is a third full (even / whole over
+//     d = 256 .. 4104, V = 101000 1.00 .. 1.11, 110000 0.96 .. 1.10, 122000 0.89 .. 1.00, 130000 0.90 .. 1.01, 140000 0.98 ..
+//     1.06): d = 1000, V = 104857 53.4 / 54.6, 47.6 / 50.8; 125829 56.3 / 54.4, 52.2 / 52.2; 151936 75 / 78, 71 / 74.  Up to three
+//     per CU there is no difference.  16 tokens: also where they are 3.1 .. 4.3 per CU (V = 101000 0.98 .. 1.02, 107000 0.92 ..
+//     1.00, 122000 0.87 .. 0.93, 140000 0.96 .. 1.04, 151936 0.95 .. 1.04), unless W is small (d = 320, V = 109000 22 / 23.4; d =
+//     256 to 1.09).
+//   128 tokens: W about as large as the memory-side cache, which keeps more of what is read in order: d = 1000, V = 121634 (232
+//     MiB) 60.7 / 54.9, 61.0 / 52.9; 133169 (254) 70.5 / 82.2, 76.5 / 80.9; 140509 (268) 94.7 / 88.0, 94.6 / 87.2.  And sampling on
+//     small hidden sizes, where drawing for the rows that shares leave empty shows: V = 83200 (2.5 tiles per CU), d = 64 16.5 /
+//     18.5, 272 23.0 / 24.4, 320 22.3 / 23.3, 448 28.5 / 27.2; V = 100400 (3.1) d = 64 22.9 / 21.1, 272 30.3 / 28.0.
+//   256 tokens: W in that cache and a CU's rows two tiles that even walks leave two thirds full: d = 768, V = 84900 45.4 / 48.4,
+//     54.6 / 57.3; d = 512, V = 109300 39.0 / 39.7, 48.1 / 48.7, 115400 41.5 / 40.6, 51.7 / 49.6; d = 1000, V = 84900 (162 MiB)
+//     64.0 / 64.0, 73.3 / 73.0.
+// Beyond, the wide tile is the cheapest per column and a narrower one pads fewer columns: the
 // time of one 256-row tile of 256 / 288 / 320 / 352 / 384 columns is in the ratio of kScoreCost (it scales with d), in sampling,
 // whose epilogue draws for every logit, of kSampleCost (8064 tokens, all rounds full, d = 4096 101 / 116 / 133 / 139 / 155 us, d =
 // 2048 55 / 63 / 71 / 75 / 85). Scoring with 256, 320 and 384 alone / all five: 350 tokens at d = 4096 433 / 403 us, 700 725 / 674,
-// 777 825 / 779, 1003 996 / 941, 1400 1412 / 1292, 2500 and more the same.  Sampling with 256 alone / all five, V = 151936: d = 4096, 300
-// tokens 563 / 396 us, 384 551 / 460, 600 775 / 656, 1003 1106 / 1009; d = 2048 292 / 230, 303 / 267, 421 / 364, 586 / 550.
+// 777 825 / 779, 1003 996 / 941, 1400 1412 / 1292, 2500 and more the same.  Sampling with 256 alone / all five, V = 151936: d =
+// 4096, 300 tokens 563 / 396 us, 384 551 / 460, 600 775 / 656, 1003 1106 / 1009; d = 2048 292 / 230, 303 / 267, 421 / 364, 586 /
+// 550.
 struct TileCosts {
   double w256, w288, w320, w352, w384;
 };
+constexpr int64_t kFewest = 16, kWhole16 = 96;                // tokens; MiB
+constexpr int kEvenFrom16 = 794, kEvenTo16 = 1100;            // tiles of 128 rows
+constexpr int kEvenFrom64 = 947, kEvenTo64 = 4 * kNumCU;      // tiles of 128 rows
+constexpr int64_t kWholeFrom128 = 244, kWholeTo128 = 264;     // MiB
+constexpr int kWholeHidden128 = 384;
+constexpr int64_t kWhole256 = 160;                            // MiB
+constexpr int kEvenRows256 = 448;                             // rows per CU
 constexpr TileCosts kScoreCost{105.0, 115.5, 126.0, 138.0, 150.0}, kSampleCost{100.0, 115.0, 128.0, 137.0, 152.0};
-static TilePick pick_tile(int64_t T, int V, int max_splits, const TileCosts& cost) {
-  auto workgroups = [&](int per_cu, int rows) {      // at most one per tile of `rows` rows
-    const int tiles = (V + rows - 1) / rows, most = per_cu * kNumCU < max_splits ? per_cu * kNumCU : max_splits;
-    return tiles < most ? tiles : most;
+static TilePick pick_tile(int64_t T, int d, int V, int max_splits, bool sampling) {
+  const TileCosts& cost = sampling ? kSampleCost : kScoreCost;
+  const int64_t bytes = (int64_t)V * d * 2, MiB = 1 << 20;
+  const int tiles = (V + Cfg64::BM - 1) / Cfg64::BM;      // of 128 rows
+  const bool once = once_pays(T, V, d);
+  auto even = [&](FwdTile tile, int per_cu, int rows) {   // a share per workgroup, at most one per tile of `rows` rows
+    const int n = (V + rows - 1) / rows, most = per_cu * kNumCU < max_splits ? per_cu * kNumCU : max_splits;
+    return TilePick{tile, n < most ? n : most, true};
   };
-  if (T <= Cfg64::BN) return TilePick{kTile64, workgroups(3, Cfg64::BM), true};
-  if (T <= Cfg128::BN) return TilePick{kTile128, workgroups(2, Cfg128::BM), true};
+  auto whole = [&](FwdTile tile) { return TilePick{tile, tiles < max_splits ? tiles : max_splits}; };
+  if (T <= Cfg64::BN) {
+    const bool few = T <= kFewest && tiles > kEvenFrom16 && tiles < kEvenTo16 && bytes > kWhole16 * MiB;
+    return once || few || (tiles > kEvenFrom64 && tiles < kEvenTo64) ? even(kTile64, 3, Cfg64::BM) : whole(kTile64);
+  }
+  if (T <= Cfg128::BN) {
+    const bool cached = bytes > kWholeFrom128 * MiB && bytes <= kWholeTo128 * MiB;
+    const bool draws = sampling && d <= kWholeHidden128 && tiles > 2 * kNumCU && tiles <= 3 * kNumCU;
+    return once || !(cached || draws) ? even(kTile128, 2, Cfg128::BM) : whole(kTile128);
+  }
   if (T <= Cfg256::BN) {
     // the least tile rows: of 256, or of 320 where they are fewer
-    const int splits = workgroups(1, Cfg256::BM), rows = (int)round_up((V + splits - 1) / splits, 16);
+    TilePick pick = even(kTile256, 1, Cfg256::BM);
+    const int rows = (int)round_up((V + pick.splits - 1) / pick.splits, 16);
     const int flat = (rows + Cfg256::BM - 1) / Cfg256::BM, tall = (rows + Cfg256Tall::BM - 1) / Cfg256Tall::BM;
-    return TilePick{kTile256, splits, true, tall * Cfg256Tall::BM < flat * Cfg256::BM};
+    pick.tall = tall * Cfg256Tall::BM < flat * Cfg256::BM;
+    if (!once && !pick.tall && bytes <= kWhole256 * MiB && rows > Cfg256Tall::BM && rows <= kEvenRows256)
+      return pick_splits<Cfg256>(kTile256, T, V, max_splits);
+    return pick;
   }
   double best_time, time;
   TilePick best = pick_splits<Cfg256>(kTile256, T, V, max_splits, cost.w256, &best_time);
@@ -211,14 +251,14 @@ static TilePick pick_tile(int64_t T, int V, int max_splits, const TileCosts& cos
   return best;
 }
 
-static TilePick pick_fwd(bool rows, int64_t T, int V, int max_splits) {
-  return rows ? pick_tile(T, V, max_splits, kScoreCost) : pick_splits<Cfg>(kTile384, T, V, max_splits);
+static TilePick pick_fwd(bool rows, int64_t T, int d, int V, int max_splits) {
+  return rows ? pick_tile(T, d, V, max_splits, false) : pick_splits<Cfg>(kTile384, T, V, max_splits);
 }
 
 // ... of the sampling kernel: over packed operands 256 or 384 columns (V = 151936, 256 alone / both: 12288 tokens at d = 4096 12.7 /
 // 11.3 ms, 32768 35.5 / 31.9; 16384 at d = 2048 8.16 in tiles of 256, 8.54 in tiles of 384).
-static TilePick pick_sample(bool rows, int64_t T, int V, int max_splits) {
-  if (rows) return pick_tile(T, V, max_splits, kSampleCost);
+static TilePick pick_sample(bool rows, int64_t T, int d, int V, int max_splits) {
+  if (rows) return pick_tile(T, d, V, max_splits, true);
   double narrow_time, wide_time;
   const TilePick narrow = pick_splits<Cfg256>(kTile256, T, V, max_splits, kSampleCost.w256, &narrow_time);
   const TilePick wide = pick_splits<Cfg>(kTile384, T, V, max_splits, kSampleCost.w384, &wide_time);
@@ -397,8 +437,8 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
     const int MT = (V + Cfg::BM - 1) / Cfg::BM;
     p.rows = rows_pay(T, d);
     p.unaligned = p.rows ? unaligned : 0;
-    if (!bwd) p.fwd = pick_fwd(p.rows, T, V, max_splits);
-    p.smp = pick_sample(p.rows, T, V, max_splits);
+    if (!bwd) p.fwd = pick_fwd(p.rows, T, d, V, max_splits);
+    p.smp = pick_sample(p.rows, T, d, V, max_splits);
     // Panel size: a multiple of the token tile, at most `cap` rows.  One panel if T fits; otherwise
     // the size (between half the cap and the cap) that costs the fewest rounds of kNumCU workgroups in
     // the dH contraction -- its tiles (d / 256 x panel rows / 384, each K = V long) are few and long, so
@@ -495,7 +535,7 @@ static bool make_plan(Plan& p, int64_t T, int d, int V, int n_seq, int n_groups,
       // as many vocabulary splits as that space takes, so small panels do not leave the scoring pass short of workgroups
       // (two passes over 16411 tokens at d = 4096 in panels of 6144, with the 32 x 32 x 16 loop: 66 ms, 113 ms with one split)
       const size_t room = (p.size_G + p.size_GT) * p.n_buf / (Tn * 8);
-      p.fwd = pick_fwd(p.rows, T, V, room < (size_t)kAnySplits ? (room > 1 ? (int)room : 1) : kAnySplits);
+      p.fwd = pick_fwd(p.rows, T, d, V, room < (size_t)kAnySplits ? (room > 1 ? (int)room : 1) : kAnySplits);
       if (p.fwd.splits > 1) p.off_fwd_partials = p.off_G;
       // single-sweep path: reference exponents and per-vocabulary-tile row sums of one panel
       p.sweep = true;

@@ -67,9 +67,11 @@ int main() {
       if (have < 0) have = (long long)oapl_workspace_bytes_for(T, d, V, 1, 1, dtype, bwd, cap, 0, nullptr, nullptr);
       Plan p;
       const int rc = fit_plan(p, T, d, V, 1, 1, dtype, bwd != 0, unaligned, (void*)(uintptr_t)256, (size_t)have);
-      std::printf("rc=%d have=%lld total=%lld rows=%d copies=%u panel=%lld buffers=%d fwd_tile=%d fwd_early=%d fwd_splits=%d smp_splits=%d smp_tile=%d",
+      std::printf("rc=%d have=%lld total=%lld rows=%d copies=%u panel=%lld buffers=%d fwd_tile=%d fwd_early=%d fwd_splits=%d smp_splits=%d smp_tile=%d "
+                  "once=%d even=%d tall=%d smp_even=%d smp_tall=%d",
                   rc, have, (long long)p.total, p.rows ? 1 : 0, p.unaligned, (long long)p.Tp, p.n_buf, (int)p.fwd.tile,
-                  p.fwd.tile == kTile256 && early_pays(T, V, d), p.fwd.splits, p.smp.splits, (int)p.smp.tile);
+                  p.fwd.tile == kTile256 && (once_pays(T, V, d) || (!p.fwd.tall && early_pays(T, V, d))), p.fwd.splits,
+                  p.smp.splits, (int)p.smp.tile, p.rows && once_pays(T, V, d), p.fwd.balanced, p.fwd.tall, p.smp.balanced, p.smp.tall);
       const int64_t last = T > 0 ? T - (T - 1) / p.Tp * p.Tp : 0;   // rows of the last panel
       if (dtype == OAPL_BF16)
         std::printf(" width=%d small_sweep=%d small_dw=%d dh_small=%d dh_splits=%d sweep_groups=%lld dw_groups=%lld dh_groups=%lld ref_splits=%d\n",

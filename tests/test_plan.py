@@ -2,7 +2,8 @@
 import pytest
 
 from paper_2602_19362_amd import oapl
-from tests import test_gpu_dh_splits, test_gpu_f32_parts, test_gpu_f32_tiles, test_gpu_loss_widths, test_gpu_ref_splits, test_gpu_sample_widths, test_gpu_score_widths, test_gpu_small_tiles
+from tests import (test_gpu_dh_splits, test_gpu_f32_parts, test_gpu_f32_tiles, test_gpu_loss_widths, test_gpu_ref_splits,
+                   test_gpu_row_walks, test_gpu_sample_widths, test_gpu_score_widths, test_gpu_small_tiles)
 from tests._plan import ask
 
 INT_MAX = 2 ** 31 - 1
@@ -132,6 +133,35 @@ def test_balanced_walks_cover_the_vocabulary(V, rows):
         n = min(per_cu * 256, (V + rows - 1) // rows)
         a = ask([f"walks {V} {n} {rows}"])[0]
         assert a["wrong"] == 0 and a["end"] == V and a["most"] - a["least"] <= 32
+
+
+def test_few_tokens_have_the_walks_they_need():
+    """What the GPU test of the walks names, scoring and sampling alike."""
+    for d, V, tokens, walks in test_gpu_row_walks.CASES:
+        for T, want in zip(tokens, walks, strict=True):
+            p = ask([f"plan {T} {d} {V} 1 0 0 0 -1"])[0]
+            for even, tall in ((p["even"], p["tall"]), (p["smp_even"], p["smp_tall"])):
+                assert "o" * p["once"] + "e" * even + "t" * tall == want, (T, d, V, p)
+
+
+@pytest.mark.parametrize("T,d,V,even", [
+    (64, 1000, 104857, 0), (48, 1800, 101000, 0), (64, 1000, 121217, 1), (64, 1000, 121216, 0), (64, 1000, 130944, 1),
+    (17, 1000, 130945, 0), (1, 1000, 151936, 0), (16, 1000, 101632, 0), (1, 1000, 101633, 1), (16, 1000, 140672, 1),
+    (16, 1000, 140673, 0), (16, 480, 104857, 0), (16, 480, 104858, 1), (16, 320, 122000, 1), (17, 1000, 104858, 0),
+    (128, 1000, 127926, 1), (65, 1000, 127927, 0), (128, 1000, 138412, 0), (128, 1000, 138413, 1), (200, 768, 84900, 0),
+    (200, 768, 109226, 0), (200, 768, 109227, 1), (256, 128, 114688, 0), (256, 128, 114689, 1), (256, 512, 65000, 1)])
+def test_walks_are_even_where_that_is_faster(T, d, V, even):
+    """On both sides of each line: 3.1, 3.7, 4 and 4.3 whole tiles per CU, W of 96, 160, 244 and 264 MiB, 448 rows per CU."""
+    p = ask([f"plan {T} {d} {V} 1 0 0 0 -1"])[0]
+    assert (p["even"], p["smp_even"], p["once"]) == (even, even, 0), p
+
+
+@pytest.mark.parametrize("T,d,V,even", [
+    (128, 384, 65536, 1), (128, 384, 65537, 0), (65, 64, 98304, 0), (128, 64, 98305, 1), (128, 392, 83200, 1)])
+def test_draws_on_small_hidden_sizes_take_whole_tiles(T, d, V, even):
+    """Two to three tiles per CU, up to d = 384; scoring does not."""
+    p = ask([f"plan {T} {d} {V} 1 0 0 0 -1"])[0]
+    assert (p["even"], p["smp_even"], p["once"]) == (1, even, 0), p
 
 
 def test_sampling_tiles_are_as_wide_as_the_tokens_need():
