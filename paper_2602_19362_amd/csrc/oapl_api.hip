@@ -319,17 +319,25 @@ static DhPick pick_dh(int64_t nv, int d, int nk, bool allow_small, size_t scratc
 
 // Large tiles of one panel's sweep and dH (operands in place) may be narrower than 384 columns where that pads fewer tokens. A
 // k-block of theirs takes kLossScale of one of 384 columns': narrow tiles read W more often and gain less than their columns.
-// The ratios come from 133 shapes (T = 80 .. 3000, d = 1000 .. 5120, V = 32000 .. 151936), each timed at every width: with them
-// 131 choices are within 1 % of the best width, none is 1.6 % off it and none slower than 384.  384 / the width chosen, us, V =
-// 151936: d = 4096, 200 tokens 1481 / 1400 (256), 300 1595 / 1541 (320), 400 2152 / 1938 (256), 777 3150 / 2813 (288), 1003
+// The ratios come from 133 shapes (T = 80 .. 3000, d = 1000 .. 5120, V = 32000 .. 151936), each timed at every width. 384 / the
+// width chosen, us, V = 151936: d = 4096, 200 tokens 1481 / 1400 (256), 300 1595 / 1541 (320), 400 2152 / 1938 (256), 777 3150 / 2813 (288), 1003
 // 3469 / 3379 (352); d = 2048, 800 1748 / 1535 (288).  1003 tokens at d = 1800, V = 100000, 384 / 352 / 256: 1317 / 1298 / 1377.
 // Where the sweep runs in small tiles all widths lose (100 tokens at d = 4096: 1175 / 1275), so those calls keep them.
+// Rounds are not as sharp as the model has them (a last one of few tiles is short), so a gain of under 5 % is not taken: of 279
+// shapes with T up to 8192 and any d and V that a narrower width promises to serve better, 31 of under 5 % came out at 1.00 times on
+// average and up to 1.19 (d = 1624, V = 12314, 3678 tokens 493 / 588), the others at 0.95, 1.01 at the most once dH's small tiles,
+// which are better than their model where there are many, are kept (d = 680, V = 21976, 3230 tokens 456 / 512; up to 917 tokens
+// 0.86 .. 0.99).
+constexpr double kNarrowGain = 0.95;
+constexpr int64_t kNarrowSmallDh = 1024;
 struct LossScale { int width; double scale; };
 constexpr LossScale kLossScale[] = {{256, 0.80}, {288, 0.83}, {320, 0.86}, {352, 0.93}};
 static int pick_width(int64_t T, int d, int V, double now, size_t scratch, DhPick& dh) {
   const int64_t mt_v = (V + Cfg::BM - 1) / Cfg::BM, mt_d = (d + Cfg::BM - 1) / Cfg::BM;
   const int nk_d = (d + kPackK - 1) / kPackK, nk_v = (V + kPackK - 1) / kPackK;
   int best = Cfg::BN;
+  if (dh.small && T > kNarrowSmallDh) return best;
+  now *= kNarrowGain;
   for (const LossScale& c : kLossScale) {
     const int64_t tiles = (T + c.width - 1) / c.width, columns = tiles * c.width;
     // fewer columns than 384 would take (which the panel has room for), and all of the token blocks that dW walks

@@ -88,6 +88,14 @@ def test_loss_tiles_are_as_wide_as_the_tokens_need():
         assert ask([q])[0]["width"] == 384, q
 
 
+@pytest.mark.parametrize("T,d,V,width", [
+    (3678, 1624, 12314, 384), (2849, 1160, 86626, 384), (2116, 936, 28945, 384),      # 1 .. 4 % by the model
+    (3230, 680, 21976, 384), (917, 816, 21429, 320), (393, 584, 26488, 256),          # dH in small tiles
+    (3989, 2688, 2364, 256), (3495, 2288, 138621, 320), (5081, 3712, 25440, 352)])
+def test_loss_tiles_are_narrower_only_where_that_is_sure_to_pay(T, d, V, width):
+    assert ask([f"plan {T} {d} {V} 1 1 0 0 -1"])[0]["width"] == width
+
+
 def test_scoring_tiles_are_as_wide_as_the_tokens_need():
     """The widths that the GPU test of the scoring tiles names."""
     width = {2: 256, 3: 320, 4: 384, 5: 288, 6: 352}       # FwdTile
