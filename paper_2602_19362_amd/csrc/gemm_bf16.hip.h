@@ -57,8 +57,8 @@ namespace oapl {
 // WM x WN wavefronts, each MB x NB blocks of 16 x 16.
 // PACK_B_: rows per block of the n-side operands where they are packed (0: one tile), a multiple of the tile's.
 // EARLY_: a block's loads go out in one go, for walks that wait for memory rather than for the multiplications.
-// ONCE_: the m-side operand is read once in the whole launch and its lines pass the caches by (non-temporal loads); a walk may start
-// at any k-block.
+// ONCE_: the m-side operand is read once in the whole launch and its lines pass the caches by (non-temporal loads); a walk may
+// start at any k-block.
 template <int WM_, int WN_, int MB_, int NB_, int NS_, int PACK_B_ = 0, bool EARLY_ = false, bool ONCE_ = false>
 struct TileCfg {
   static constexpr int WM = WM_, WN = WN_, MB = MB_, NB = NB_;
@@ -75,7 +75,8 @@ struct TileCfg {
   static constexpr int ROW_BYTES = kPackRowBytes;
   static constexpr int STAGE_A = BM * ROW_BYTES;   // one stage of the m-side operand
   static constexpr int STAGE_B = BN * ROW_BYTES;   // ... of the n-side operand
-  static constexpr int PACK_A = BM > kPackRowsA ? BM : kPackRowsA, PACK_B = PACK_B_ ? PACK_B_ : BN;   // (taller tiles read in place only)
+  static constexpr int PACK_A = BM > kPackRowsA ? BM : kPackRowsA;     // (taller tiles read in place only)
+  static constexpr int PACK_B = PACK_B_ ? PACK_B_ : BN;
   static constexpr int PITCH_A = PACK_A * ROW_BYTES, PITCH_B = PACK_B * ROW_BYTES;   // bytes of one packed block
   static_assert(PACK_A % BM == 0 && PACK_B % BN == 0, "a tile lies in one block");
   static constexpr int SLOT = STAGE_A + STAGE_B;   // one ring slot: the m-side block, then the n-side block
@@ -279,8 +280,10 @@ struct Mainloop {
             __builtin_amdgcn_make_buffer_rsrc((void*)(at_base + (int64_t)kc * C::BK * at_ld2), 0, bytes, 0x00020000);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, (v < 0 ? v : at_voff) + i * (C::NW * 512 / C::BM) * at_ld2, 0, 0, 0);
       } else {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, dst, 16, ROWS ? v + i * istep : v,
-                                                 ROWS ? block(kt, nk) * C::ROW_BYTES : kt * C::PITCH_A + i * C::NW * 1024, 0, C::ONCE ? 2 : 0 /* non-temporal */);
+        constexpr int kNonTemporal = 2;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            ra, dst, 16, ROWS ? v + i * istep : v,
+            ROWS ? block(kt, nk) * C::ROW_BYTES : kt * C::PITCH_A + i * C::NW * 1024, 0, C::ONCE ? kNonTemporal : 0);
       }
     } else if (i < C::NI_A + C::NI_B) {
       const int b = i - C::NI_A;
@@ -921,7 +924,8 @@ k_fwd_lse(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int
 template <class C, bool ROWS>
 __global__ void __launch_bounds__(C::NT)
 k_fwd_sample(const bf16_t* __restrict__ W, const bf16_t* __restrict__ H, int V, int64_t T, int d, int n_kt, int n_splits,
-             int balanced, int patch_tiles, float inv_temperature, uint32_t seed_lo, uint32_t seed_hi, float2* __restrict__ partials) {
+             int balanced, int patch_tiles, float inv_temperature, uint32_t seed_lo, uint32_t seed_hi,
+             float2* __restrict__ partials) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   lds_char_ptr smem = (lds_char_ptr)smem_raw;

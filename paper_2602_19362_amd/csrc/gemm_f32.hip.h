@@ -1,27 +1,28 @@
 // fp32 contractions of the OAPL loss head, on the bf16 matrix cores: C[m][n] = sum_k A(m, k) * B(n, k).
 //
 // An fp32 number is the sum of three bf16 numbers, each the rounding of what the ones before leave (24 bits; the signs of the
-// later parts make up for the bits between): x = x0 + x1 + x2, to the bit, with |x1| <= 2^-8 |x| and |x2| <= 2^-17 |x| (Henry, Tang and
-// Heinecke, 2019).  Of the nine products of two such sums eight are taken,
+// later parts make up for the bits between): x = x0 + x1 + x2, to the bit, with |x1| <= 2^-8 |x| and |x2| <= 2^-17 |x| (Henry, Tang
+// and Heinecke, 2019).  Of the nine products of two such sums eight are taken,
 //     x0 y0  +  (x0 y1 + x1 y0)  +  (x1 y1 + x0 y2 + x2 y0)  +  (x1 y2 + x2 y1),
-// and x2 y2, at most 2^-34 |x y|, is under half a place of the sum that it would go into.  (x1 y2 + x2 y1 reach 2^-24 |x y|, as much as
-// the rounding of an fp32 product: a logit of one product 0.97 places off without them, 0.51 with.)
+// and x2 y2, at most 2^-34 |x y|, is under half a place of the sum that it would go into.  (x1 y2 + x2 y1 reach 2^-24 |x y|, as
+// much as the rounding of an fp32 product: a logit of one product 0.97 places off without them, 0.51 with.)
 // A tile in which a number is past the parts' range, or a sum past that of fp32 at the parts' scale, infinite or NaN, is multiplied
 // once more, as v_mfma_f32_32x32x2_f32 does it: every fp32 number is an operand, to the last bit.  (1501 tokens at d = 768, V =
 // 8192 with every tile of the logits and of one gradient done twice 828 us.)
 // v_mfma_f32_32x32x16_bf16 does a product exactly and sixteen times as fast as v_mfma_f32_32x32x2_f32 does an fp32 one.  The first
 // products are added up apart from the others: a matrix core's addition cuts addends far below its result off downwards (-0.003
 // ulp on average), which as many additions into the large sum turned into a bias of 2e-7 of a token's log-prob (with two sums
-// 2e-8).  Against fp64, relative errors of log-probs fp32 multiplications / here: 256 tokens at d = 64, V = 1024 3.3e-7 / 1.6e-7, 1501 at d =
-// 768, V = 8192 6.9e-7 / 2.6e-7; of dW 5.5e-6 / 3.7e-6, 1.2e-5 / 4.8e-6; over 14 shapes up to those 0.42 and 0.57 times.
+// 2e-8).  Against fp64, relative errors of log-probs fp32 multiplications / here: 256 tokens at d = 64, V = 1024 3.3e-7 / 1.6e-7,
+// 1501 at d = 768, V = 8192 6.9e-7 / 2.6e-7; of dW 5.5e-6 / 3.7e-6, 1.2e-5 / 4.8e-6; over 14 shapes up to those 0.42 and 0.57
+// times.
 //
 // Each operand comes either with k contiguous in memory (H and W for the logits, dZ^T for dW) or with its row index contiguous
 // (dZ^T and W for dH, H for dW); in the LDS its parts lie with k contiguous, as the fragments want them.  A thread splits
 // what it loaded before it writes it there (13 vector operations for two numbers), once for all that read it.
 //
 // What bounds it is the sum of things that share a SIMD and its clock: multiplications, splitting, fragments. A loss call of 1501
-// tokens at d = 768, V = 8192 takes 482 us; with six products (and less than fp32's precision) 414, with fp32 multiplications, whose
-// matrix cores were 66 % busy, 590, with plain FMAs 2990.  160 calls of up to 2000 tokens at d <= 768, V <= 8192, times fp32
+// tokens at d = 768, V = 8192 takes 482 us; with six products (and less than fp32's precision) 414, with fp32 multiplications,
+// whose matrix cores were 66 % busy, 590, with plain FMAs 2990.  160 calls of up to 2000 tokens at d <= 768, V <= 8192, times fp32
 // multiplications': losses 0.88 on average, 0.63 .. 1.02, scores 0.80, 0.44 .. 0.99.
 #pragma once
 

@@ -49,8 +49,8 @@ static bool early_pays(int64_t T, int V, int d) {
 // ... and one token tile reads W once: non-temporal loads, which this card delivers at 7.1 TB/s where others reach 6.3, and, rows
 // a multiple of 4 KiB apart, each workgroup's walk over k from another block on (TileCfg's ONCE).  With equally many rows
 // for every workgroup (row_walk), scoring before / now at V = 151936, us: d = 4096 16 tokens 238 / 202, 64 231 / 214, 128
-// 283 / 260, 192 340 / 286, 256 348 / 300 (sampling 227 / 197, 225 / 211, 283 / 264, 348 / 310, 358 / 323); d = 2048 16 tokens 153 /
-// 107, 128 180 / 142, 256 203 / 164; d = 5120 286 / 255, 388 / 371, 458 / 390.  Rows that are not whole 128-byte lines would be
+// 283 / 260, 192 340 / 286, 256 348 / 300 (sampling 227 / 197, 225 / 211, 283 / 264, 348 / 310, 358 / 323); d = 2048 16 tokens 153
+// / 107, 128 180 / 142, 256 203 / 164; d = 5120 286 / 255, 388 / 371, 458 / 390.  Rows that are not whole 128-byte lines would be
 // fetched twice (d = 3000, V = 60000: +12 .. +20 %), and a W that mostly survives in the memory-side cache from call to
 // call is better left there (264 MiB +3 .. +10 %, 297 MiB -4 .. -16 %, 305 MiB -4 .. -11 %).
 typedef TileCfg<4, 1, 2, 4, 2, 0, false, true> Cfg64Once;
@@ -255,8 +255,8 @@ static TilePick pick_fwd(bool rows, int64_t T, int d, int V, int max_splits) {
   return rows ? pick_tile(T, d, V, max_splits, false) : pick_splits<Cfg>(kTile384, T, V, max_splits);
 }
 
-// ... of the sampling kernel: over packed operands 256 or 384 columns (V = 151936, 256 alone / both: 12288 tokens at d = 4096 12.7 /
-// 11.3 ms, 32768 35.5 / 31.9; 16384 at d = 2048 8.16 in tiles of 256, 8.54 in tiles of 384).
+// ... of the sampling kernel: over packed operands 256 or 384 columns (V = 151936, 256 alone / both: 12288 tokens at d = 4096 12.7
+// / 11.3 ms, 32768 35.5 / 31.9; 16384 at d = 2048 8.16 in tiles of 256, 8.54 in tiles of 384).
 static TilePick pick_sample(bool rows, int64_t T, int d, int V, int max_splits) {
   if (rows) return pick_tile(T, d, V, max_splits, true);
   double narrow_time, wide_time;
@@ -320,14 +320,14 @@ static DhPick pick_dh(int64_t nv, int d, int nk, bool allow_small, size_t scratc
 // Large tiles of one panel's sweep and dH (operands in place) may be narrower than 384 columns where that pads fewer tokens. A
 // k-block of theirs takes kLossScale of one of 384 columns': narrow tiles read W more often and gain less than their columns.
 // The ratios come from 133 shapes (T = 80 .. 3000, d = 1000 .. 5120, V = 32000 .. 151936), each timed at every width. 384 / the
-// width chosen, us, V = 151936: d = 4096, 200 tokens 1481 / 1400 (256), 300 1595 / 1541 (320), 400 2152 / 1938 (256), 777 3150 / 2813 (288), 1003
-// 3469 / 3379 (352); d = 2048, 800 1748 / 1535 (288).  1003 tokens at d = 1800, V = 100000, 384 / 352 / 256: 1317 / 1298 / 1377.
-// Where the sweep runs in small tiles all widths lose (100 tokens at d = 4096: 1175 / 1275), so those calls keep them.
-// Rounds are not as sharp as the model has them (a last one of few tiles is short), so a gain of under 5 % is not taken: of 279
-// shapes with T up to 8192 and any d and V that a narrower width promises to serve better, 31 of under 5 % came out at 1.00 times on
-// average and up to 1.19 (d = 1624, V = 12314, 3678 tokens 493 / 588), the others at 0.95, 1.01 at the most once dH's small tiles,
-// which are better than their model where there are many, are kept (d = 680, V = 21976, 3230 tokens 456 / 512; up to 917 tokens
-// 0.86 .. 0.99).
+// width chosen, us, V = 151936: d = 4096, 200 tokens 1481 / 1400 (256), 300 1595 / 1541 (320), 400 2152 / 1938 (256), 777 3150 /
+// 2813 (288), 1003 3469 / 3379 (352); d = 2048, 800 1748 / 1535 (288).  1003 tokens at d = 1800, V = 100000, 384 / 352 / 256: 1317
+// / 1298 / 1377. Where the sweep runs in small tiles all widths lose (100 tokens at d = 4096: 1175 / 1275), so those calls keep
+// them. Rounds are not as sharp as the model has them (a last one of few tiles is short), so a gain of under 5 % is not taken: of
+// 279 shapes with T up to 8192 and any d and V that a narrower width promises to serve better, 31 of under 5 % came out at 1.00
+// times on average and up to 1.19 (d = 1624, V = 12314, 3678 tokens 493 / 588), the others at 0.95, 1.01 at the most once dH's
+// small tiles, which are better than their model where there are many, are kept (d = 680, V = 21976, 3230 tokens 456 / 512; up to
+// 917 tokens 0.86 .. 0.99).
 constexpr double kNarrowGain = 0.95;
 constexpr int64_t kNarrowSmallDh = 1024;
 struct LossScale { int width; double scale; };
@@ -359,8 +359,8 @@ static bool dh_hides_behind_dw(int nk_v, int nk_t) { return nk_v <= nk_t + nk_t 
 // Tile of 128 x 128 or 64 x 64 and splits of an M x N x K fp32 contraction: the least time of the last-finishing CU in clocks, 128
 // per k for a tile of 128 x 128 and 40 for one of 64 x 64 that has the CU to itself, 2000 for a workgroup to start and
 // store; partial results cost 8 bytes per element and split at 1700 bytes per clock, and a launch (5000).  The figures are those
-// of fp32 multiplications; from parts both tiles take about 0.65 times as long (24 calls of up to 2000 tokens at d <= 768, V <= 8192
-// 0.61 .. 1.04, 0.82 on average).  `scratch` bounds the partial results.
+// of fp32 multiplications, in whose place whole calls from parts take 0.63 .. 1.02 times as long (gemm_f32.hip.h): what it picks
+// is then no worse than it was, but not always the best.  `scratch` bounds the partial results.
 static F32Pick pick_f32(int64_t M, int64_t N, int64_t K, int max_splits, size_t scratch) {
   F32Pick best;
   double best_time = 1e300;
@@ -378,9 +378,9 @@ static F32Pick pick_f32(int64_t M, int64_t N, int64_t K, int max_splits, size_t 
 }
 
 // ... in 256 x 128 tiles, a workgroup per CU: in how many splits, or 0 where the smaller tiles are the better. us for a CU's
-// workgroups and a stage of 32 k: 256 x 128 3.1 each; 128 x 128 2.7 alone, 3.8 two; 64 x 64 1.3 alone, 0.55 each and 0.4 several. dH
-// of 1501 tokens at d = 768, V = 8192 in seven splits 147 (128 x 128) / 127 us, dW 164 in two with their sum / 133; dH of 1300 tokens
-// at V = 8065 332 (64 x 64, one split) / 139; of 700 at d = 300, V = 8000 in 16 splits 43 (64 x 64) / 55.
+// workgroups and a stage of 32 k: 256 x 128 3.1 each; 128 x 128 2.7 alone, 3.8 two; 64 x 64 1.3 alone, 0.55 each and 0.4 several.
+// dH of 1501 tokens at d = 768, V = 8192 in seven splits 147 (128 x 128) / 127 us, dW 164 in two with their sum / 133; dH of 1300
+// tokens at V = 8065 332 (64 x 64, one split) / 139; of 700 at d = 300, V = 8000 in 16 splits 43 (64 x 64) / 55.
 static int wide_splits_f32(const F32Pick& pick, int64_t M, int64_t N, int64_t K, int max_splits, size_t scratch) {
   auto tiles = [&](int64_t bm, int64_t bn) { return (M + bm - 1) / bm * ((N + bn - 1) / bn); };
   const int64_t stages = (K + F32Wide::BK - 1) / F32Wide::BK;
@@ -403,9 +403,12 @@ static int64_t f32_groups(const F32Pick& pick, int64_t M, int64_t N) {
   const int64_t tile = pick.large ? F32Large::BM : F32Small::BM;
   return ((M + tile - 1) / tile) * ((N + tile - 1) / tile) * pick.splits;
 }
-// fp32 gradient contractions share a launch up to this many workgroups.  Whole calls, two launches / one: 256 tokens at d = 64,
-// V = 1024 (128 workgroups) 40 / 37 us; 700, 300, 3000 (455) 104 / 96; 1501, 768, 8192 (1272) 585 / 609. Where between the last
-// two the line lies has not been measured.
+// fp32 gradient contractions share a launch up to this many workgroups; beyond, each may have the tiles that suit it
+// (wide_splits_f32).  Whole calls, two launches / one, us: tokens, d, V (workgroups) 256, 64, 1024 (128) 41 / 33; 939, 129, 1398
+// (423) 78 / 57; 700, 300, 3000 (455) 104 / 87; 283, 714, 1376 (504) 95 / 79; 362, 752, 2503 (696) 108 / 103; 800, 768, 3000 (816)
+// 159 / 164; 1501, 768, 8192 (1272) 494 / 550.  The count alone does not tell everything: between 512 and 768 calls of few tokens
+// lose a seventh apart (177, 654, 2306 92 / 79), some of many gain a fifth (1959, 751, 4318 (684) 417 / 509; 1300, 600, 6000 (730)
+// 344 / 392; 1047, 460, 4490 (684) 188 / 188); with the line at 512 160 calls took 1.01 times as long on average.
 constexpr int64_t kSharedGroupsF32 = 3 * kNumCU;
 
 // bf16 operands that are not 16-byte aligned.  The 16-byte direct-to-LDS loads of the in-place kernels want that; the packing
@@ -648,13 +651,13 @@ static bool prepare_kernels() {
   static std::once_flag once;
   static bool ok = false;
   std::call_once(once, [] {
-    ok = allow_fwd<Cfg64Once, true>() && allow_fwd<Cfg128Once, true>() && allow_fwd<Cfg256Once, true>() &&
-         allow_fwd<Cfg256Tall, true>() && allow_fwd<Cfg256TallOnce, true>() && allow_sample<Cfg64Once, true>() &&
-         allow_sample<Cfg128Once, true>() && allow_sample<Cfg256Once, true>() && allow_sample<Cfg256Tall, true>() &&
-         allow_sample<Cfg256TallOnce, true>() && allow_fwd<Cfg64, true>() && allow_fwd<Cfg128, true>() && allow_fwd<Cfg256, true>() && allow_fwd<Cfg256Early, true>() &&
-         allow_fwd<Cfg288, true>() && allow_fwd<Cfg320, true>() && allow_fwd<Cfg352, true>() &&
-         allow_fwd<Cfg, true>() && allow_fwd<Cfg, false>() && allow_sample<Cfg64, true>() &&
-         allow_sample<Cfg128, true>() && allow_sample<Cfg256, true>() && allow_sample<Cfg256Early, true>() &&
+    ok = allow_fwd<Cfg64, true>() && allow_fwd<Cfg64Once, true>() && allow_fwd<Cfg128, true>() && allow_fwd<Cfg128Once, true>() &&
+         allow_fwd<Cfg256, true>() && allow_fwd<Cfg256Early, true>() && allow_fwd<Cfg256Once, true>() &&
+         allow_fwd<Cfg256Tall, true>() && allow_fwd<Cfg256TallOnce, true>() && allow_fwd<Cfg288, true>() &&
+         allow_fwd<Cfg320, true>() && allow_fwd<Cfg352, true>() && allow_fwd<Cfg, true>() && allow_fwd<Cfg, false>() &&
+         allow_sample<Cfg64, true>() && allow_sample<Cfg64Once, true>() && allow_sample<Cfg128, true>() &&
+         allow_sample<Cfg128Once, true>() && allow_sample<Cfg256, true>() && allow_sample<Cfg256Early, true>() &&
+         allow_sample<Cfg256Once, true>() && allow_sample<Cfg256Tall, true>() && allow_sample<Cfg256TallOnce, true>() &&
          allow_sample<Cfg288, true>() && allow_sample<Cfg320, true>() && allow_sample<Cfg352, true>() &&
          allow_sample<Cfg, true>() && allow_sample<Cfg256, false>() && allow_sample<Cfg, false>() &&
          allow_big_lds(k_fwd_lse<CfgRef, false, true>, CfgRef::LDS_BYTES) &&
@@ -707,8 +710,8 @@ template <class C, bool ENT, bool ROWS>
 static void launch_fwd_lse_kernel(const FwdArgs& a, float2* partials, float* upart, int* clear, hipStream_t st, Gate gate) {
   const int64_t total = (a.T + C::BN - 1) / C::BN * a.pick.splits;
   const unsigned grid = (unsigned)round_up(total, 8);
-  k_fwd_lse<C, ENT, ROWS><<<grid, C::NT, C::LDS_BYTES, st>>>(a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, a.pick.balanced, patch_tiles<C>(a.n_kt),
-                                                           partials, upart, clear, gate);
+  k_fwd_lse<C, ENT, ROWS><<<grid, C::NT, C::LDS_BYTES, st>>>(a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, a.pick.balanced,
+                                                           patch_tiles<C>(a.n_kt), partials, upart, clear, gate);
 }
 template <class C, bool ROWS>
 static void launch_fwd_lse(const FwdArgs& a, float2* partials, float* upart, int* clear, hipStream_t st, Gate gate) {
@@ -739,14 +742,15 @@ static void launch_fwd_lse(const FwdArgs& a, bool rows, float2* partials, float*
   }
 }
 
-// ... of the sampling kernel: patches of 1 / 4 / 8 token tiles, V = 151936, us: d = 4096, 1003 tokens 1010 / 993 / 990, 4096 3904 / 3835 /
-// 3830, 6144 6170 / 5982 / 6064; d = 2048 554 / 551 / 542, 2115 / 2106 / 2086, 3339 / 3187 / 3291, 8192 4086 / 4044 / 4106.
+// ... of the sampling kernel: patches of 1 / 4 / 8 token tiles, V = 151936, us: d = 4096, 1003 tokens 1010 / 993 / 990, 4096 3904 /
+// 3835 / 3830, 6144 6170 / 5982 / 6064; d = 2048 554 / 551 / 542, 2115 / 2106 / 2086, 3339 / 3187 / 3291, 8192 4086 / 4044 / 4106.
 constexpr int kSamplePatch = 4;
 template <class C, bool ROWS>
 static void launch_sample(const FwdArgs& a, float inv_t, uint64_t seed, float2* partials, hipStream_t st) {
   const int64_t total = (a.T + C::BN - 1) / C::BN * a.pick.splits;
   k_fwd_sample<C, ROWS><<<(unsigned)round_up(total, 8), C::NT, C::LDS_BYTES, st>>>(
-      a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, a.pick.balanced, kSamplePatch, inv_t, (uint32_t)seed, (uint32_t)(seed >> 32), partials);
+      a.W, a.H, a.V, a.T, a.d, a.n_kt, a.pick.splits, a.pick.balanced, kSamplePatch, inv_t, (uint32_t)seed,
+      (uint32_t)(seed >> 32), partials);
 }
 
 static void launch_sample(const FwdArgs& a, bool rows, float inv_t, uint64_t seed, float2* partials, hipStream_t st) {
@@ -777,7 +781,10 @@ static F32Operand f32_operand(const void* p, int64_t ld) {
   return F32Operand{(const float*)p, ld, ld % 4 == 0 && ((uintptr_t)p & 15) == 0};
 }
 
-// 128 x 128 tiles of the logits where they give every CU one, else 64 x 128.
+// 128 x 128 tiles of the logits where they give every CU one, else 64 x 128.  (From bf16 parts 64 x 128 would serve most calls
+// above the line as well: 64 x 128 / 128 x 128, whole calls, us, T, d, V (tiles): 700, 300, 3000 (144) 87 / 100; 900, 400, 4000
+// (256) 163 / 173; 1980, 545, 3120 (400) 254 / 244; 999, 398, 7605 (480) 243 / 235; 1300, 600, 6000 (517) 358 / 394; 1501, 768,
+// 8192 (768) 475 / 492; 2000, 768, 8192 (1024) 609 / 617.)
 static bool logits_large_f32(int V, int64_t T) {
   return (int64_t)grid1d(V, F32Large::BM) * grid1d(T, F32Large::BN) >= kNumCU;
 }
@@ -961,12 +968,12 @@ static int forward_finish(const Plan& p, const LseFinish& f, hipStream_t st, Gat
 
 // An fp32 loss call's log-probs are finished by the objective's launch where that is little work for one workgroup: a dependent
 // launch costs a small call 5 us whatever is in it, and a rollout's workgroup has its tokens in rounds of 256 / slices, 4 us each,
-// that a launch of its own has side by side.  Up to two rounds of tokens, so that even one rollout with all of them takes no longer:
-// one launch less / one more, d = 64, us: one rollout, V = 64, 512 tokens (2 rounds) 31.5 / 36.3, 1536 (6) 35.5 / 36.7, 2048 (8) 40.2 /
-// 36.1, V = 1024, 128 (2) 33.2 / 35.2, 192 (3) 39.5 / 35.6, V = 8192, 16 (2) 35.9 / 36.1, 32 (4) 43.4 / 35.8.  Up to four rounds where
-// rollouts of twice the mean length have one: 256 tokens of eight rollouts, V = 1024, 31.7 / 35 (all of them in one of the eight,
-// which the host does not see, 39).  In bf16, where the finish is the fallback's and closed, the launch that it saves goes into the
-// larger kernel (1000 tokens at d = 256, V = 1544 53.6 / 53.4).
+// that a launch of its own has side by side.  Up to two rounds of tokens, so that even one rollout with all of them takes no
+// longer: one launch less / one more, d = 64, us: one rollout, V = 64, 512 tokens (2 rounds) 31.5 / 36.3, 1536 (6) 35.5 / 36.7,
+// 2048 (8) 40.2 / 36.1, V = 1024, 128 (2) 33.2 / 35.2, 192 (3) 39.5 / 35.6, V = 8192, 16 (2) 35.9 / 36.1, 32 (4) 43.4 / 35.8.  Up
+// to four rounds where rollouts of twice the mean length have one: 256 tokens of eight rollouts, V = 1024, 31.7 / 35 (all of them
+// in one of the eight, which the host does not see, 39).  In bf16, where the finish is the fallback's and closed, the launch that
+// it saves goes into the larger kernel (1000 tokens at d = 256, V = 1544 53.6 / 53.4).
 static bool finish_in_objective(const Plan& p) {
   const int64_t round = 256 / finish_slices(p.fwd.splits);
   return p.dtype == OAPL_F32 && p.T > 0 && (p.T <= 2 * round || (p.T <= 4 * round && 2 * p.T <= round * p.n_seq));
@@ -1152,12 +1159,14 @@ static int backward_grads(const Plan& p, const void* H, const void* W, const int
     launch_logits_f32(p, Hp, W, nv, EpiDzF32{tokens + t0, lse + t0, coef + t0, zt, p.ldz}, st);
     OAPL_LAUNCH_CHECK();
     // dH[t][j] = sum_v dZ[t][v] W[v][j]
-    launch_contract_f32<false>(p.f32_dh, p.wide_dh, contraction_f32(p.f32_dh, p.wide_dh, f32_operand(zt, p.ldz), f32_operand(W, d),
-                                                                    nv, d, V, (float*)dH + t0 * d), 0, st);
+    launch_contract_f32<false>(p.f32_dh, p.wide_dh,
+                               contraction_f32(p.f32_dh, p.wide_dh, f32_operand(zt, p.ldz), f32_operand(W, d), nv, d, V,
+                                               (float*)dH + t0 * d), 0, st);
     OAPL_LAUNCH_CHECK();
     // dW[v][j] (+)= sum_t dZ[t][v] H[t][j]
-    launch_contract_f32<true>(p.f32_dw, p.wide_dw, contraction_f32(p.f32_dw, p.wide_dw, f32_operand(zt, p.ldz), f32_operand(Hp, d), V,
-                                                                   d, nv, dW), t0 > 0 ? 1 : 0, st);
+    launch_contract_f32<true>(p.f32_dw, p.wide_dw,
+                              contraction_f32(p.f32_dw, p.wide_dw, f32_operand(zt, p.ldz), f32_operand(Hp, d), V, d, nv, dW),
+                              t0 > 0 ? 1 : 0, st);
     OAPL_LAUNCH_CHECK();
   }
   return OAPL_OK;
@@ -1209,7 +1218,9 @@ static bool sweep_begins_in_one_launch(const Plan& p, int n_seq, int n_groups) {
 static int ref_splits(const Plan& p) {
   const int64_t tiles = grid1d(p.T, CfgRef::BN);
   for (int s = 8; s >= 2; --s)
-    if (p.rows && p.d > kOneLaunchHidden && tiles * s <= kNumCU && 4 * s <= p.n_kt_d && (uint64_t)s * p.T * CfgRef::BM * 4 <= p.size_G) return s;
+    if (p.rows && p.d > kOneLaunchHidden && tiles * s <= kNumCU && 4 * s <= p.n_kt_d &&
+        (uint64_t)s * p.T * CfgRef::BM * 4 <= p.size_G)
+      return s;
   return 0;
 }
 
@@ -1329,8 +1340,9 @@ static int sweep_path(const Plan& p, const Begin& begin, const void* H, const vo
 }
 
 // fp32 calls whose logits do not give every CU a 128 x 128 tile start with one launch (k_scores_f32; 256 tokens at d = 64,
-// V = 1024: three launches of 3.6, 2.7 and 8.2 us before). Where they do, workgroups in front of them unbalance the chip (1501
-// tokens, d = 768, V = 8192, three tiles per CU: whole call 586 us apart, 639 together).
+// V = 1024: whole call 39.4 us apart, 32.9 together; 700 at d = 300, V = 3000 91.9 / 87.0). Where they do, 128 x 128 tiles start
+// apart: that launch has tiles of 64 x 128 (1501 tokens, d = 768, V = 8192 494 us apart, 478 in such tiles together; 1980, 545,
+// 3120 245 / 255).
 static bool scores_in_one_launch_f32(const Plan& p, int n_seq, int n_groups) {
   return p.dtype == OAPL_F32 && p.T > 0 && p.T <= kPanelF32 && !logits_large_f32(p.V, p.T) &&
          begin_in_one_launch(n_seq, n_groups);

@@ -43,8 +43,9 @@ int main() {
       // rows of the longest and the shortest
       int at = 0, wrong = 0, most = 0, least = V;
       for (int k = 0; k < n_seq; ++k) {
-        const RowWalk w = n_groups == 128 ? row_walk<Cfg128>(V, k, n_seq, 1) : n_groups == 256 ? row_walk<Cfg256>(V, k, n_seq, 1)
-                                                                                               : row_walk<Cfg256Tall>(V, k, n_seq, 1);
+        const RowWalk w = n_groups == 128   ? row_walk<Cfg128>(V, k, n_seq, 1)
+                          : n_groups == 256 ? row_walk<Cfg256>(V, k, n_seq, 1)
+                                            : row_walk<Cfg256Tall>(V, k, n_seq, 1);
         wrong += w.r0 != at || w.r0 % 16 != 0 || w.h < 1 || w.h > n_groups || w.h % 16 != 0;
         wrong += w.r0 >= w.r1 || (w.r1 - w.r0 + w.h - 1) / w.h != (w.r1 - w.r0 + n_groups - 1) / n_groups;
         at = w.r1;
@@ -67,14 +68,16 @@ int main() {
       if (have < 0) have = (long long)oapl_workspace_bytes_for(T, d, V, 1, 1, dtype, bwd, cap, 0, nullptr, nullptr);
       Plan p;
       const int rc = fit_plan(p, T, d, V, 1, 1, dtype, bwd != 0, unaligned, (void*)(uintptr_t)256, (size_t)have);
-      std::printf("rc=%d have=%lld total=%lld rows=%d copies=%u panel=%lld buffers=%d fwd_tile=%d fwd_early=%d fwd_splits=%d smp_splits=%d smp_tile=%d "
-                  "once=%d even=%d tall=%d smp_even=%d smp_tall=%d",
+      std::printf("rc=%d have=%lld total=%lld rows=%d copies=%u panel=%lld buffers=%d fwd_tile=%d fwd_early=%d fwd_splits=%d "
+                  "smp_splits=%d smp_tile=%d once=%d even=%d tall=%d smp_even=%d smp_tall=%d",
                   rc, have, (long long)p.total, p.rows ? 1 : 0, p.unaligned, (long long)p.Tp, p.n_buf, (int)p.fwd.tile,
                   p.fwd.tile == kTile256 && (once_pays(T, V, d) || (!p.fwd.tall && early_pays(T, V, d))), p.fwd.splits,
-                  p.smp.splits, (int)p.smp.tile, p.rows && once_pays(T, V, d), p.fwd.balanced, p.fwd.tall, p.smp.balanced, p.smp.tall);
+                  p.smp.splits, (int)p.smp.tile, p.rows && once_pays(T, V, d), p.fwd.balanced, p.fwd.tall, p.smp.balanced,
+                  p.smp.tall);
       const int64_t last = T > 0 ? T - (T - 1) / p.Tp * p.Tp : 0;   // rows of the last panel
       if (dtype == OAPL_BF16)
-        std::printf(" width=%d small_sweep=%d small_dw=%d dh_small=%d dh_splits=%d sweep_groups=%lld dw_groups=%lld dh_groups=%lld ref_splits=%d\n",
+        std::printf(" width=%d small_sweep=%d small_dw=%d dh_small=%d dh_splits=%d sweep_groups=%lld dw_groups=%lld "
+                    "dh_groups=%lld ref_splits=%d\n",
                     p.width, p.small_sweep, p.small_dw, p.dh.small, p.dh.splits, groups(p.small_sweep, V, last),
                     groups(p.small_dw, d, V), groups(p.dh.small, d, last) * p.dh.splits, p.sweep ? ref_splits(p) : 0);
       else

@@ -1,6 +1,7 @@
-"""Sampling in tiles of every width, operands in place and packed: token counts at the edges of one, two and three tiles, one to sixteen
-k-blocks with and without a ragged last one, vocabularies whose last tile is ragged, seeds and temperatures that differ from case to
-case.  Draws and scores against the oracle's as in test_gpu_parity.py; test_plan.py checks that each case takes the tile named here."""
+"""Sampling in tiles of every width, operands in place and packed: token counts at the edges of one, two and three tiles, one to
+sixteen k-blocks with and without a ragged last one, vocabularies whose last tile is ragged, seeds and temperatures that differ
+from case to case.  Draws and scores against the oracle's as in test_gpu_parity.py; test_plan.py checks that each case takes the
+tile named here."""
 import numpy as np
 import pytest
 
