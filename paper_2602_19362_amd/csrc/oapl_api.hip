@@ -46,13 +46,14 @@ typedef TileCfg<4, 2, 4, 8, 2, 0, true> Cfg256Early;
 static bool early_pays(int64_t T, int V, int d) {
   return T <= 2 * Cfg256Early::BN && (int64_t)V * d * 2 > (int64_t)256 << 20;
 }
-// ... and one token tile reads W once: non-temporal loads, which this card delivers at 7.1 TB/s where others reach 6.3, and, rows
-// a multiple of 4 KiB apart, each workgroup's walk over k from another block on (TileCfg's ONCE).  With equally many rows
-// for every workgroup (row_walk), scoring before / now at V = 151936, us: d = 4096 16 tokens 238 / 202, 64 231 / 214, 128
-// 283 / 260, 192 340 / 286, 256 348 / 300 (sampling 227 / 197, 225 / 211, 283 / 264, 348 / 310, 358 / 323); d = 2048 16 tokens 153
-// / 107, 128 180 / 142, 256 203 / 164; d = 5120 286 / 255, 388 / 371, 458 / 390.  Rows that are not whole 128-byte lines would be
-// fetched twice (d = 3000, V = 60000: +12 .. +20 %), and a W that mostly survives in the memory-side cache from call to
-// call is better left there (264 MiB +3 .. +10 %, 297 MiB -4 .. -16 %, 305 MiB -4 .. -11 %).
+// ... and one token tile reads W once: non-temporal loads, with which 16 and 64 tokens at d = 4096 and 5120 read it at 5.8 .. 6.8
+// TB/s (5.5 .. 6.1 with others; of 256 tokens 3.8 .. 4.5, 3.7 .. 4.2), and, rows a multiple of 4 KiB apart, each workgroup's walk
+// over k from another block on (TileCfg's ONCE).  With equally many rows for every workgroup (row_walk), scoring before / now at V
+// = 151936, us: d = 4096 16 tokens 238 / 202, 64 231 / 214, 128 283 / 260, 192 340 / 286, 256 348 / 300 (sampling 227 / 197, 225 /
+// 211, 283 / 264, 348 / 310, 358 / 323); d = 2048 16 tokens 153 / 107, 128 180 / 142, 256 203 / 164; d = 5120 286 / 255, 388 / 371,
+// 458 / 390.  Rows that are not whole 128-byte lines would be fetched twice (d = 3000, V = 60000: +12 .. +20 %), and a W that
+// mostly survives in the memory-side cache from call to call is better left there (264 MiB +3 .. +10 %, 297 MiB -4 .. -16 %, 305
+// MiB -4 .. -11 %).
 typedef TileCfg<4, 1, 2, 4, 2, 0, false, true> Cfg64Once;
 typedef TileCfg<4, 2, 2, 4, 2, 0, false, true> Cfg128Once;
 typedef TileCfg<4, 2, 4, 8, 2, 0, true, true> Cfg256Once;
