@@ -186,13 +186,16 @@ static TilePick pick_splits(FwdTile tile, int64_t T, int V, int max_splits, doub
 //     per CU there is no difference.  16 tokens: also where they are 3.1 .. 4.3 per CU (V = 101000 0.98 .. 1.02, 107000 0.92 ..
 //     1.00, 122000 0.87 .. 0.93, 140000 0.96 .. 1.04, 151936 0.95 .. 1.04), unless W is small (d = 320, V = 109000 22 / 23.4; d =
 //     256 to 1.09).
-//   128 tokens: W about as large as the memory-side cache, which keeps more of what is read in order: d = 1000, V = 121634 (232
-//     MiB) 60.7 / 54.9, 61.0 / 52.9; 133169 (254) 70.5 / 82.2, 76.5 / 80.9; 140509 (268) 94.7 / 88.0, 94.6 / 87.2.  And sampling on
-//     small hidden sizes, where drawing for the rows that shares leave empty shows: V = 83200 (2.5 tiles per CU), d = 64 16.5 /
-//     18.5, 272 23.0 / 24.4, 320 22.3 / 23.3, 448 28.5 / 27.2; V = 100400 (3.1) d = 64 22.9 / 21.1, 272 30.3 / 28.0.
+//   128 tokens: rows that are not whole 128-byte lines and W about as large as the memory-side cache, which then keeps more of what
+//     is read in order: d = 904, V = 142671 (246 MiB) 74 / 83 on one box, 66.9 / 65.9 on another; d = 1000, V = 134217 (256) 75.6 /
+//     85.2, 72.3 / 83.3; V = 140509 (268) 94.7 / 88.0, 94.6 / 87.2 (whole lines: d = 960, V = 139810 (256) 63.2 / 64.4, 65.0 / 64.8;
+//     d = 1088 57.8 / 56.4, 58.6 / 54.0).  And sampling on small hidden sizes, where drawing for the rows that shares leave empty
+//     shows: V = 83200 (2.5 tiles per CU), d = 64 16.5 / 18.5, 272 23.0 / 24.4, 320 22.3 / 23.3, 448 28.5 / 27.2; V = 100400 (3.1)
+//     d = 64 22.9 / 21.1, 272 30.3 / 28.0.
 //   256 tokens: W in that cache and a CU's rows two tiles that even walks leave two thirds full: d = 768, V = 84900 45.4 / 48.4,
-//     54.6 / 57.3; d = 512, V = 109300 39.0 / 39.7, 48.1 / 48.7, 115400 41.5 / 40.6, 51.7 / 49.6; d = 1000, V = 84900 (162 MiB)
-//     64.0 / 64.0, 73.3 / 73.0.
+//     54.6 / 57.3; d = 512, V = 109300 39.0 / 39.7, 48.1 / 48.7, 115400 41.5 / 40.6, 51.7 / 49.6; d = 1152, V = 97000 (213 MiB)
+//     63.0 / 67.4, 71.9 / 75.3; d = 1472, V = 91000 (255) 1.02 times; rows that are not whole lines, d = 648, V = 106000 (131 MiB)
+//     0.98, d = 872, V = 91000 (151) 1.00, d = 1000, V = 114000 (217) 69.8 / 69.1, d = 1480, V = 91000 (257) 1.13.
 // Beyond, the wide tile is the cheapest per column and a narrower one pads fewer columns: the
 // time of one 256-row tile of 256 / 288 / 320 / 352 / 384 columns is in the ratio of kScoreCost (it scales with d), in sampling,
 // whose epilogue draws for every logit, of kSampleCost (8064 tokens, all rounds full, d = 4096 101 / 116 / 133 / 139 / 155 us, d =
@@ -208,14 +211,14 @@ constexpr int kEvenFrom16 = 794, kEvenTo16 = 1100;            // tiles of 128 ro
 constexpr int kEvenFrom64 = 947, kEvenTo64 = 4 * kNumCU;      // tiles of 128 rows
 constexpr int64_t kWholeFrom128 = 244, kWholeTo128 = 264;     // MiB
 constexpr int kWholeHidden128 = 384;
-constexpr int64_t kWhole256 = 160;                            // MiB
+constexpr int64_t kWhole256 = 160, kWholeLines256 = 250;      // MiB
 constexpr int kEvenRows256 = 448;                             // rows per CU
 constexpr TileCosts kScoreCost{105.0, 115.5, 126.0, 138.0, 150.0}, kSampleCost{100.0, 115.0, 128.0, 137.0, 152.0};
 static TilePick pick_tile(int64_t T, int d, int V, int max_splits, bool sampling) {
   const TileCosts& cost = sampling ? kSampleCost : kScoreCost;
   const int64_t bytes = (int64_t)V * d * 2, MiB = 1 << 20;
   const int tiles = (V + Cfg64::BM - 1) / Cfg64::BM;      // of 128 rows
-  const bool once = once_pays(T, V, d);
+  const bool once = once_pays(T, V, d), lines = d % kPackK == 0;     // rows of whole 128-byte lines
   auto even = [&](FwdTile tile, int per_cu, int rows) {   // a share per workgroup, at most one per tile of `rows` rows
     const int n = (V + rows - 1) / rows, most = per_cu * kNumCU < max_splits ? per_cu * kNumCU : max_splits;
     return TilePick{tile, n < most ? n : most, true};
@@ -226,7 +229,7 @@ static TilePick pick_tile(int64_t T, int d, int V, int max_splits, bool sampling
     return once || few || (tiles > kEvenFrom64 && tiles < kEvenTo64) ? even(kTile64, 3, Cfg64::BM) : whole(kTile64);
   }
   if (T <= Cfg128::BN) {
-    const bool cached = bytes > kWholeFrom128 * MiB && bytes <= kWholeTo128 * MiB;
+    const bool cached = !lines && bytes > kWholeFrom128 * MiB && bytes <= kWholeTo128 * MiB;
     const bool draws = sampling && d <= kWholeHidden128 && tiles > 2 * kNumCU && tiles <= 3 * kNumCU;
     return once || !(cached || draws) ? even(kTile128, 2, Cfg128::BM) : whole(kTile128);
   }
@@ -236,7 +239,7 @@ static TilePick pick_tile(int64_t T, int d, int V, int max_splits, bool sampling
     const int rows = (int)round_up((V + pick.splits - 1) / pick.splits, 16);
     const int flat = (rows + Cfg256::BM - 1) / Cfg256::BM, tall = (rows + Cfg256Tall::BM - 1) / Cfg256Tall::BM;
     pick.tall = tall * Cfg256Tall::BM < flat * Cfg256::BM;
-    if (!once && !pick.tall && bytes <= kWhole256 * MiB && rows > Cfg256Tall::BM && rows <= kEvenRows256)
+    if (!once && !pick.tall && bytes <= (lines ? kWholeLines256 : kWhole256) * MiB && rows > Cfg256Tall::BM && rows <= kEvenRows256)
       return pick_splits<Cfg256>(kTile256, T, V, max_splits);
     return pick;
   }

@@ -156,10 +156,12 @@ def test_few_tokens_have_the_walks_they_need():
     (64, 1000, 104857, 0), (48, 1800, 101000, 0), (64, 1000, 121217, 1), (64, 1000, 121216, 0), (64, 1000, 130944, 1),
     (17, 1000, 130945, 0), (1, 1000, 151936, 0), (16, 1000, 101632, 0), (1, 1000, 101633, 1), (16, 1000, 140672, 1),
     (16, 1000, 140673, 0), (16, 480, 104857, 0), (16, 480, 104858, 1), (16, 320, 122000, 1), (17, 1000, 104858, 0),
-    (128, 1000, 127926, 1), (65, 1000, 127927, 0), (128, 1000, 138412, 0), (128, 1000, 138413, 1), (200, 768, 84900, 0),
-    (200, 768, 109226, 0), (200, 768, 109227, 1), (256, 128, 114688, 0), (256, 128, 114689, 1), (256, 512, 65000, 1)])
+    (128, 1000, 127926, 1), (65, 1000, 127927, 0), (128, 1000, 138412, 0), (128, 1000, 138413, 1), (128, 1024, 131073, 1),
+    (200, 760, 84900, 0), (200, 776, 108100, 0), (200, 776, 108101, 1), (200, 1152, 113777, 0), (200, 1152, 113778, 1),
+    (256, 128, 114688, 0), (256, 128, 114689, 1), (256, 512, 65000, 1)])
 def test_walks_are_even_where_that_is_faster(T, d, V, even):
-    """On both sides of each line: 3.1, 3.7, 4 and 4.3 whole tiles per CU, W of 96, 160, 244 and 264 MiB, 448 rows per CU."""
+    """On both sides of each line: 3.1, 3.7, 4 and 4.3 whole tiles per CU, W of 96, 160, 244, 250 and 264 MiB, rows of whole
+    lines and others, 448 rows per CU."""
     p = ask([f"plan {T} {d} {V} 1 0 0 0 -1"])[0]
     assert (p["even"], p["smp_even"], p["once"]) == (even, even, 0), p
 
