@@ -30,11 +30,11 @@ PEAK_BF16_TFLOPS = 2516.6     # MI355X dense bf16 MFMA: 256 CU x 4096 flop/clk x
 # sources at run time and the figure is reported as null when they differ.
 TRAFFIC = {
     "workload": "qwen7b",
-    "sources_sha256_16": "bef6575aba669673",
+    "sources_sha256_16": "bd0506c0d57a3e33",
     "per_launch_bytes": {          # averages over the step's 12 panels (11 of 12288 rows, one of 5729)
-        "k_sweep": {"read": 17.51e9, "write": 7.22e9},
-        "k_bwd_dh": {"read": 17.15e9, "write": 0.10e9},
-        "k_bwd_dw": {"read": 20.88e9, "write": 2.49e9},
+        "k_sweep": {"read": 17.38e9, "write": 7.22e9},
+        "k_bwd_dh": {"read": 17.24e9, "write": 0.10e9},
+        "k_bwd_dw": {"read": 19.63e9, "write": 2.49e9},
     },
 }
 

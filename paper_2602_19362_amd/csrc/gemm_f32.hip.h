@@ -22,10 +22,10 @@
 //
 // What bounds it is the sum of things that share a SIMD and its clock, multiplications, splitting and fragments, and the waits
 // between them: at 1501 x 8192 x 768 matrix cores are busy 0.40 .. 0.46 of the time (at 2.1 GHz), vector ALUs 0.22 .. 0.33, the LDS
-// 0.15 .. 0.21; 116 .. 122 TFLOP/s of fp32 products. A loss call of 1501
-// tokens at d = 768, V = 8192 takes 482 us; with six products (and less than fp32's precision) 414, with fp32 multiplications,
-// whose matrix cores were 66 % busy, 590, with plain FMAs 2990.  160 calls of up to 2000 tokens at d <= 768, V <= 8192, times fp32
-// multiplications': losses 0.88 on average, 0.63 .. 1.02, scores 0.80, 0.44 .. 0.99.
+// 0.15 .. 0.21; 116 .. 122 TFLOP/s of fp32 products.  A loss call of 1501 tokens at d = 768, V = 8192 takes 482 us; with six
+// products (and less than fp32's precision) 414, with fp32 multiplications, whose matrix cores were 66 % busy, 590, with plain FMAs
+// 2990.  160 calls of up to 2000 tokens at d <= 768, V <= 8192, times fp32 multiplications': losses 0.88 on average, 0.63 .. 1.02,
+// scores 0.80, 0.44 .. 0.99.
 #pragma once
 
 #include "common.hip.h"

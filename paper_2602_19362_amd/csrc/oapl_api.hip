@@ -188,10 +188,10 @@ static TilePick pick_splits(FwdTile tile, int64_t T, int V, int max_splits, doub
 //     256 to 1.09).
 //   128 tokens: rows that are not whole 128-byte lines and W about as large as the memory-side cache, which then keeps more of what
 //     is read in order: d = 904, V = 142671 (246 MiB) 74 / 83 on one box, 66.9 / 65.9 on another; d = 1000, V = 134217 (256) 75.6 /
-//     85.2, 72.3 / 83.3; V = 140509 (268) 94.7 / 88.0, 94.6 / 87.2 (whole lines: d = 960, V = 139810 (256) 63.2 / 64.4, 65.0 / 64.8;
-//     d = 1088 57.8 / 56.4, 58.6 / 54.0).  And sampling on small hidden sizes, where drawing for the rows that shares leave empty
-//     shows: V = 83200 (2.5 tiles per CU), d = 64 16.5 / 18.5, 272 23.0 / 24.4, 320 22.3 / 23.3, 448 28.5 / 27.2; V = 100400 (3.1)
-//     d = 64 22.9 / 21.1, 272 30.3 / 28.0.
+//     85.2, 72.3 / 83.3; V = 140509 (268) 94.7 / 88.0, 94.6 / 87.2 (whole lines: d = 960, V = 139810 (256) 63.2 / 64.4, 65.0 /
+//     64.8; d = 1088 57.8 / 56.4, 58.6 / 54.0).  And sampling on small hidden sizes, where drawing for the rows that shares leave
+//     empty shows: V = 83200 (2.5 tiles per CU), d = 64 16.5 / 18.5, 272 23.0 / 24.4, 320 22.3 / 23.3, 448 28.5 / 27.2; V = 100400
+//     (3.1) d = 64 22.9 / 21.1, 272 30.3 / 28.0.
 //   256 tokens: W in that cache and a CU's rows two tiles that even walks leave two thirds full: d = 768, V = 84900 45.4 / 48.4,
 //     54.6 / 57.3; d = 512, V = 109300 39.0 / 39.7, 48.1 / 48.7, 115400 41.5 / 40.6, 51.7 / 49.6; d = 1152, V = 97000 (213 MiB)
 //     63.0 / 67.4, 71.9 / 75.3; d = 1472, V = 91000 (255) 1.02 times; rows that are not whole lines, d = 648, V = 106000 (131 MiB)
@@ -199,10 +199,10 @@ static TilePick pick_splits(FwdTile tile, int64_t T, int V, int max_splits, doub
 // Beyond, the wide tile is the cheapest per column and a narrower one pads fewer columns: the
 // time of one 256-row tile of 256 / 288 / 320 / 352 / 384 columns is in the ratio of kScoreCost (it scales with d), in sampling,
 // whose epilogue draws for every logit, of kSampleCost (8064 tokens, all rounds full, d = 4096 101 / 116 / 133 / 139 / 155 us, d =
-// 2048 55 / 63 / 71 / 75 / 85). Scoring with 256, 320 and 384 alone / all five: 350 tokens at d = 4096 433 / 403 us, 700 725 / 674,
-// 777 825 / 779, 1003 996 / 941, 1400 1412 / 1292, 2500 and more the same.  Sampling with 256 alone / all five, V = 151936: d =
-// 4096, 300 tokens 563 / 396 us, 384 551 / 460, 600 775 / 656, 1003 1106 / 1009; d = 2048 292 / 230, 303 / 267, 421 / 364, 586 /
-// 550.
+// 2048 55 / 63 / 71 / 75 / 85; 384 columns with 32 registers in scratch). Scoring with 256, 320 and 384 alone / all five: 350
+// tokens at d = 4096 433 / 403 us, 700 725 / 674, 777 825 / 779, 1003 996 / 941, 1400 1412 / 1292, 2500 and more the same.
+// Sampling with 256 alone / all five, V = 151936: d = 4096, 300 tokens 563 / 396 us, 384 551 / 460, 600 775 / 656, 1003 1106 /
+// 1009; d = 2048 292 / 230, 303 / 267, 421 / 364, 586 / 550.
 struct TileCosts {
   double w256, w288, w320, w352, w384;
 };
