@@ -30,7 +30,7 @@ def test_wide_gradient_tiles(d, V, lens, cap):
 
 @pytest.mark.parametrize("d", [5, 40])
 def test_numbers_at_the_ends_of_the_range(d):
-    """Numbers past the largest bf16 (their first part would be infinite), infinite ones and NaN: logits as fp32 products give
+    """Numbers past the largest bf16 (their first part is infinite), infinite ones and NaN: logits as fp32 products give
     them.  Infinity times a number is infinite with the product's sign whatever the number's later parts are, times zero NaN."""
     T, V = 70, 130
     g = torch.Generator(device="cuda:0").manual_seed(d)
@@ -38,7 +38,7 @@ def test_numbers_at_the_ends_of_the_range(d):
     W = torch.randn(V, d, generator=g, device="cuda:0")
     tokens = torch.arange(T, device="cuda:0").to(torch.int32)
     big = torch.finfo(torch.float32).max
-    H[:, 1] = 2.0 ** -126             # (a power of two is one part; below 2^-110 the last of three parts loses bits)
+    H[:, 1] = 2.0 ** -126             # (numbers with all their bits: test_gpu_f32_range.py)
     W[:, 1] = big * (1 - 2.0 ** -9 * torch.rand(V, generator=g, device="cuda:0"))
     assert (W[:, 1].to(torch.bfloat16).isinf()).any() and W[:, 1].isfinite().all()
     W[100, 2] = -float("inf")         # a logit of -inf for every token: never drawn, no part of any sum
